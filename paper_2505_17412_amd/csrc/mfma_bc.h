@@ -1,4 +1,4 @@
-// Staging of whole key blocks into LDS and the work-chunk lookup of the block-centric selection kernels (gfx950,
+// Staging of whole key blocks into LDS and the workgroup-to-chunk map of the block-centric selection kernels (gfx950,
 // wave64); the tile layout itself (PTile) is the one of mfma_qc.h.
 #pragma once
 
@@ -33,19 +33,6 @@ __device__ inline void p_stage2(const bf16_t *xa, const bf16_t *xb, uint32_t str
         *reinterpret_cast<bf16x8 *>(tb + off[u]) = rb[u];
       }
   }
-}
-
-// Work chunk -> (key, chunk inside the key) by bisection over the chunk prefix sums; false when w is past the end.
-__device__ inline bool bc_find_chunk(const int32_t *chunk_start, int nkeys, int w, int &key, int &chunk) {
-  if (w >= chunk_start[nkeys]) return false;
-  int lo = 0, hi = nkeys;  // chunk_start[lo] <= w < chunk_start[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (chunk_start[mid] <= w) lo = mid; else hi = mid;
-  }
-  key = lo;
-  chunk = w - chunk_start[lo];
-  return true;
 }
 
 // Workgroup id -> work chunk.  Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2); the map

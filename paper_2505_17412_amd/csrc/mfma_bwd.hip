@@ -264,7 +264,7 @@ struct DkvArgs {
   const int32_t *sel_start, *sel_list;  // selection branch: query positions per (g, block)
   float *dK, *dV;                       // [rows][Hkv][D] fp32 (rows: sorted tokens, or compression blocks)
   const int32_t *chunk_start;           // selection branch: [Hkv*Ns+1] first work chunk of each (g, block)
-  const int32_t *chunk_order;           // selection branch: execution order of the work chunks
+  const ChunkRef *chunk_order;          // selection branch: execution order of the work chunks
   const int32_t *part_row_start;        // selection branch: [Hkv*Ns+1] first row of each (g, block)'s partial sums
   int chunk_len;                        // selection branch: query tokens per work chunk
   int tiles_per_block;                  // key tiles reserved per block in the grid
@@ -303,12 +303,11 @@ __global__ __launch_bounds__(64 * NW) void m_bwd_dkv(DkvArgs a) {
     Kr = a.v.Ks; Vr = a.v.Vs;
   } else if (MODE == DKV_SLC) {
     // 1-D launch: the key tiles of one work chunk get workgroup ids 8 apart, i.e. they run on the same XCD close in
-    // time, so the chunk's query rows are fetched into that L2 once.  Find the chunk's (g, block) by bisection over
-    // the chunk prefix sums.
+    // time, so the chunk's query rows are fetched into that L2 once.
     const int per8 = 8 * a.tiles_per_block;
     const int nkeys = a.v.Hkv * a.v.Ns, wi = (int)(blockIdx.x / per8) * 8 + (int)(blockIdx.x % 8);
-    int key, chunk;
-    if (wi >= a.chunk_start[nkeys] || !bc_find_chunk(a.chunk_start, nkeys, a.chunk_order[wi], key, chunk)) return;
+    if (wi >= a.chunk_start[nkeys]) return;
+    const int key = a.chunk_order[wi].key, chunk = a.chunk_order[wi].chunk;
     g = key / a.v.Ns; blk = key % a.v.Ns; tile = (int)(blockIdx.x % per8) / 8;
     kbeg = a.v.slc_start[blk]; kend = a.v.slc_start[blk + 1];
     qbeg = a.sel_start[key] + chunk * a.chunk_len;
@@ -608,12 +607,12 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   }
   {
     ProfScope ps(PROF_BWD_INVERT, s);
-    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, true, s);
+    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, true, true, s);
     if (rc != SSA_OK) return rc;
   }
   {
     ProfScope ps1(PROF_BWD_DQ, s);
-    const int rc = slc_dq_kernel(v, D, w, idx, s);
+    const int rc = slc_dq_kernel(v, D, w, s);
     if (rc != SSA_OK) return rc;
   }
   {

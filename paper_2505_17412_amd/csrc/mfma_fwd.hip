@@ -371,12 +371,12 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, const SelIndex &
   }
   {
     ProfScope ps(PROF_FWD_INVERT, s);
-    const int rc = sel_index_build(a.idx, a.v.perm, a.v.slc_start, a.v.N, a.v.Hkv, a.v.T, a.v.Ns, sel, false, s);
+    const int rc = sel_index_build(a.idx, a.v.perm, a.v.slc_start, a.v.N, a.v.Hkv, a.v.T, a.v.Ns, sel, true, false, s);
     if (rc != SSA_OK) return rc;
   }
   {
     ProfScope ps(PROF_SLC_FWD, s);
-    const int rc = slc_forward_kernel(a.v, D, a.Q, a.idx, sel, part, s);
+    const int rc = slc_forward_kernel(a.v, D, a.Q, sel, part, s);
     if (rc != SSA_OK) return rc;
   }
   {

@@ -11,22 +11,27 @@ int mfma_forward_kernels(const MfmaView &v, int D, const void *q, const void *ga
 
 // Inverse of the selection (sel_index.hip): per (KV head, selection block) key = g*Ns + b, the ascending list of sorted
 // positions of the tokens that selected it, and the cuts of the lists into work chunks.
+struct ChunkRef { int32_t key, chunk; };  // a work chunk: its list (key) and its number inside the list
 struct SelIndex {
-  uint32_t *bits;                 // [Hkv*Ns][ceil(N/32)] bit (key, pos): token at pos selected the block
+  uint32_t *cnt;                  // [Hkv*Ns][tiles of sorted positions] entries of the key before the tile
   uint32_t *counts;               // [Hkv*Ns]
   int32_t *start, *list;          // [Hkv*Ns+1], [N*Hkv*T]
+  uint8_t *rank;                  // [N*Hkv*T]: place of the key's block in the row of I of the listed token
   int32_t *chunk_start, *part_row_start;  // [Hkv*Ns+1] each: dK/dV work chunks and partial-sum rows per key
   int32_t *bc_chunk_start;        // [Hkv*Ns+1]: work chunks of the block-centric forward / dQ kernels
-  int32_t *order, *bc_order;      // execution order of the chunks of either chunking (chunk ids; see m_chunk_order)
-  int chunk_len, bc_chunk_len;    // query tokens per chunk of either kind (at least 256)
+  uint32_t *bins;                 // bucket counters of the two execution orders
+  int4 *slot, *bc_slot;           // bucket, number in the bucket, key, chunk of every chunk
+  ChunkRef *order, *bc_order;     // the chunks of either chunking in execution order (see m_chunk_order)
+  int chunk_len, bc_chunk_len;    // query tokens per chunk: at least 256 (dK/dV), BC_CHUNK_MIN .. BC_CHUNK
 };
 size_t sel_index_bytes(int N, int Hkv, int T, int Ns);
 SelIndex sel_index_carve(void *ws, int N, int Hkv, int T, int Ns, int chunk_len, int bc_chunk_len);
 int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_start, int N, int Hkv, int T, int Ns,
-                    const SelIndex &x, bool want_dkv_order, hipStream_t s);
+                    const SelIndex &x, bool want_bc_order, bool want_dkv_order, hipStream_t s);
 
 // Block-centric selection kernels: query tokens per work chunk, and the per-(token, KV head, rank) partial results.
-constexpr int BC_CHUNK = 256;
+constexpr int BC_CHUNK = 256, BC_CHUNK_MIN = 32;
+int bc_chunk_len(int N, int Hkv, int T);
 struct SlcPartials {
   bf16_t *o;    // [N][Hkv][T][hs][D]: unnormalised partial output (forward) / partial dQ (backward) per selected block
   float *ml;    // [N][Hkv][T][hs][2]: running maximum (raw score units) and sum of the partial softmax (forward only)
@@ -34,7 +39,7 @@ struct SlcPartials {
 
 // Block-centric selection kernels (mfma_slc.hip), forward: partials per selected block, then the per-token merge that
 // also writes the gated sum of eq. (4) (out_branch [3,N,Hq,D]: branches 0 and 2 read, 1 written; lse [3,N,Hq]).
-int slc_forward_kernel(const MfmaView &v, int D, const void *q, const int32_t *idx, const SelIndex &sel,
+int slc_forward_kernel(const MfmaView &v, int D, const void *q, const SelIndex &sel,
                        const SlcPartials &part, hipStream_t s);
 int slc_merge_kernel(const MfmaView &v, int D, const SlcPartials &part, const int32_t *idx, const void *gates,
                      void *out_branch, float *lse, void *out, hipStream_t s);
@@ -56,7 +61,7 @@ struct BwdBuffers {
 };
 // Block-centric selection kernels, backward: partial dQ per selected block (w.part.o), then the per-token sum onto the
 // fp32 dQ of the other two branches (w.dQp), written to dq.
-int slc_dq_kernel(const MfmaView &v, int D, const BwdBuffers &w, const int32_t *idx, hipStream_t s);
+int slc_dq_kernel(const MfmaView &v, int D, const BwdBuffers &w, hipStream_t s);
 int slc_dq_merge_kernel(const MfmaView &v, int D, const BwdBuffers &w, const int32_t *idx, void *dq, hipStream_t s);
 int mfma_backward_kernels(const MfmaView &v, int D, const BwdBuffers &w, const void *q, const void *gates,
                           const void *out_branch, const float *lse, const int32_t *idx, const void *dout, void *dq,

@@ -200,6 +200,15 @@ bool mfma_supported(const ssa_ctx &c) {
   return true;
 }
 
+// Query tokens per work chunk of the block-centric kernels: long chunks stage a block's K and V rarely, short ones give a
+// small problem enough workgroups for 256 compute units (two each).
+int bc_chunk_len(int N, int Hkv, int T) {
+  const long long entries = (long long)N * Hkv * T;
+  int len = BC_CHUNK;
+  while (len > BC_CHUNK_MIN && entries / len < 1024) len /= 2;
+  return len;
+}
+
 size_t mfma_forward_workspace(const ssa_ctx &c) { return fwd_plan(c).total; }
 size_t mfma_backward_workspace(const ssa_ctx &c) {
   return mfma_bwd_supported(c) ? bwd_plan(c).total : generic_backward_workspace(c);
@@ -229,7 +238,7 @@ int mfma_backward(const ssa_ctx &c, const void *q, const void *k, const void *v,
   w.deltag = (float *)(ws + p.deltag);
   w.Qs = (bf16_t *)(ws + p.qs); w.dOg = (bf16_t *)(ws + p.dos); w.dQp = (float *)(ws + p.dqp);
   w.dKs = (float *)(ws + p.dks); w.dVs = (float *)(ws + p.dvs); w.dKc = (float *)(ws + p.dkc); w.dVc = (float *)(ws + p.dvc);
-  w.sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, BC_CHUNK);
+  w.sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, bc_chunk_len(c.N, c.Hkv, c.T));
   w.q_splits = p.q_splits;
   w.pK = (float *)(ws + p.pk); w.pV = (float *)(ws + p.pv); w.max_chunks = p.max_chunks;
   w.part = SlcPartials{(bf16_t *)(ws + p.pdq), nullptr};
@@ -250,7 +259,7 @@ int mfma_forward(const ssa_ctx &c, const void *q, const void *k, const void *v, 
   if (rc != SSA_OK) return rc;
   MfmaView view = make_view(c);
   view.Ks = o.Ks; view.Vs = o.Vs; view.Kc = o.Kc; view.Vc = o.Vc;
-  const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, 1024, BC_CHUNK);
+  const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, 1024, bc_chunk_len(c.N, c.Hkv, c.T));
   const SlcPartials part{(bf16_t *)(ws + p.po), (float *)(ws + p.pml)};
   return mfma_forward_kernels(view, c.d, q, gates, out, lse ? lse : (float *)(ws + p.lse),
                               topk_idx ? topk_idx : (int32_t *)(ws + p.idx), out_branch ? out_branch : (void *)(ws + p.ob),

@@ -26,8 +26,10 @@ namespace {
 struct BcFwdArgs {
   MfmaView v;
   const bf16_t *Q;
-  const int32_t *idx;  // [N,Hkv,T]
-  const int32_t *sel_start, *sel_list, *chunk_start, *chunk_order;
+  const int32_t *sel_start, *sel_list, *chunk_start;
+  const uint8_t *sel_rank;
+  const ChunkRef *chunk_order;
+  int chunk_len;
   bf16_t *po;  // [N][Hkv][T][hs][D]
   float *pml;  // [N][Hkv][T][hs][2]
 };
@@ -106,21 +108,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
   unsigned char *Kt = smem, *Vt = Kt + MAXT * P::BYTES;
   int *tl = (int *)(Vt + MAXT * P::BYTES), *sl = tl + BC_CHUNK;
   const int wid = threadIdx.x >> 6, quad = threadIdx.x >> 4 & 3;
-  const int hs = a.v.hs, Hkv = a.v.Hkv, T = a.v.T, Ns = a.v.Ns;
+  const int hs = a.v.hs, Hkv = a.v.Hkv, Ns = a.v.Ns;
   const int wi = bc_chunk_of_workgroup(a.chunk_start[Hkv * Ns]);
-  int key, chunk;
-  if (wi < 0 || !bc_find_chunk(a.chunk_start, Hkv * Ns, a.chunk_order[wi], key, chunk)) return;
+  if (wi < 0) return;
+  const int key = a.chunk_order[wi].key, chunk = a.chunk_order[wi].chunk;
   const int g = key / Ns, blk = key % Ns;
   const int kbeg = a.v.slc_start[blk], kend = a.v.slc_start[blk + 1];
-  const int qbeg = a.sel_start[key] + chunk * BC_CHUNK, cnt = min(a.sel_start[key + 1] - qbeg, BC_CHUNK);
+  const int qbeg = a.sel_start[key] + chunk * a.chunk_len, cnt = min(a.sel_start[key + 1] - qbeg, a.chunk_len);
   // the chunk's tokens (caller indices) and the rank of this block in each token's row of I
   for (int i = threadIdx.x; i < cnt; i += 64 * NW) {
-    const int tok = a.v.perm[a.sel_list[qbeg + i]];
-    const int32_t *row = a.idx + ((size_t)tok * Hkv + g) * T;
-    int j = 0;
-    while (j < T - 1 && row[j] != blk) ++j;
-    tl[i] = tok;
-    sl[i] = j;
+    tl[i] = a.v.perm[a.sel_list[qbeg + i]];
+    sl[i] = a.sel_rank[qbeg + i];
   }
   const int tpw = 16 / hs;  // tokens per wavefront step
   const int n_it = (cnt + tpw - 1) / tpw;
@@ -234,8 +232,10 @@ struct BcDqArgs {
   MfmaView v;
   const bf16_t *Qs, *dOs;             // [N(pos)][Hq][D] sorted copies: Q, and the selection gate times dO
   const float *lse2s, *deltas;        // selection branch: [N(pos)][Hq]
-  const int32_t *idx;                 // [N,Hkv,T]
-  const int32_t *sel_start, *sel_list, *chunk_start, *chunk_order;
+  const int32_t *sel_start, *sel_list, *chunk_start;
+  const uint8_t *sel_rank;
+  const ChunkRef *chunk_order;
+  int chunk_len;
   bf16_t *pdq;                        // [N(pos)][Hkv][T][hs][D]
 };
 
@@ -304,21 +304,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
   unsigned char *Kt = smem, *Vt = Kt + MAXT * P::BYTES;
   int *tl = (int *)(Vt + MAXT * P::BYTES), *sl = tl + BC_CHUNK;
   const int wid = threadIdx.x >> 6, quad = threadIdx.x >> 4 & 3;
-  const int hs = a.v.hs, Hkv = a.v.Hkv, T = a.v.T, Ns = a.v.Ns;
+  const int hs = a.v.hs, Hkv = a.v.Hkv, Ns = a.v.Ns;
   const int wi = bc_chunk_of_workgroup(a.chunk_start[Hkv * Ns]);
-  int key, chunk;
-  if (wi < 0 || !bc_find_chunk(a.chunk_start, Hkv * Ns, a.chunk_order[wi], key, chunk)) return;
+  if (wi < 0) return;
+  const int key = a.chunk_order[wi].key, chunk = a.chunk_order[wi].chunk;
   const int g = key / Ns, blk = key % Ns;
   const int kbeg = a.v.slc_start[blk], kend = a.v.slc_start[blk + 1];
-  const int qbeg = a.sel_start[key] + chunk * BC_CHUNK, cnt = min(a.sel_start[key + 1] - qbeg, BC_CHUNK);
+  const int qbeg = a.sel_start[key] + chunk * a.chunk_len, cnt = min(a.sel_start[key + 1] - qbeg, a.chunk_len);
   // the chunk's tokens (sorted positions) and the rank of this block in each token's row of I
   for (int i = threadIdx.x; i < cnt; i += 64 * NW) {
-    const int pos = a.sel_list[qbeg + i];
-    const int32_t *row = a.idx + ((size_t)a.v.perm[pos] * Hkv + g) * T;
-    int j = 0;
-    while (j < T - 1 && row[j] != blk) ++j;
-    tl[i] = pos;
-    sl[i] = j;
+    tl[i] = a.sel_list[qbeg + i];
+    sl[i] = a.sel_rank[qbeg + i];
   }
   const int tpw = 16 / hs;
   const int n_it = (cnt + tpw - 1) / tpw;
@@ -403,13 +399,13 @@ __global__ __launch_bounds__(256) void m_dq_merge(DqMergeArgs a) {
 template <int D> struct BcShape { static constexpr int NW = 8, KSEG = 256; };
 
 // upper bound of the number of chunks: every (KV head, block) list adds at most one partly filled chunk
-unsigned chunk_bound(const MfmaView &v) {
+unsigned chunk_bound(const MfmaView &v, int chunk_len) {
   const size_t entries = (size_t)v.N * v.Hkv * v.T;
-  return (unsigned)(entries / BC_CHUNK + (size_t)v.Hkv * v.Ns);
+  return (unsigned)(entries / chunk_len + (size_t)v.Hkv * v.Ns);
 }
 
 template <int D>
-int launch_slc_forward(const MfmaView &v, const bf16_t *q, const int32_t *idx, const SelIndex &sel, const SlcPartials &part,
+int launch_slc_forward(const MfmaView &v, const bf16_t *q, const SelIndex &sel, const SlcPartials &part,
                        hipStream_t s) {
   using BS = BcShape<D>;
   static std::once_flag once;  // raise the dynamic LDS limit once per process for this instantiation
@@ -417,13 +413,13 @@ int launch_slc_forward(const MfmaView &v, const bf16_t *q, const int32_t *idx, c
     (void)hipFuncSetAttribute((const void *)m_slc_fwd_bc<D, BS::NW, BS::KSEG>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               160 * 1024);
   });
-  BcFwdArgs b{v, q, idx, sel.start, sel.list, sel.bc_chunk_start, sel.bc_order, part.o, part.ml};
-  m_slc_fwd_bc<D, BS::NW, BS::KSEG><<<dim3((chunk_bound(v) + 7) / 8 * 8), 64 * BS::NW, bc_lds_bytes<D, BS::KSEG>(), s>>>(b);
+  BcFwdArgs b{v, q, sel.start, sel.list, sel.bc_chunk_start, sel.rank, sel.bc_order, sel.bc_chunk_len, part.o, part.ml};
+  m_slc_fwd_bc<D, BS::NW, BS::KSEG><<<dim3((chunk_bound(v, sel.bc_chunk_len) + 7) / 8 * 8), 64 * BS::NW, bc_lds_bytes<D, BS::KSEG>(), s>>>(b);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
 template <int D>
-int launch_slc_dq(const MfmaView &v, const BwdBuffers &w, const int32_t *idx, hipStream_t s) {
+int launch_slc_dq(const MfmaView &v, const BwdBuffers &w, hipStream_t s) {
   using BS = BcShape<D>;
   static std::once_flag once;
   std::call_once(once, [] {
@@ -431,20 +427,20 @@ int launch_slc_dq(const MfmaView &v, const BwdBuffers &w, const int32_t *idx, hi
                               160 * 1024);
   });
   const size_t NH = (size_t)v.N * v.Hq;
-  BcDqArgs b{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, idx, w.sel.start, w.sel.list, w.sel.bc_chunk_start,
-             w.sel.bc_order, w.part.o};
-  m_bwd_dq_bc<D, BS::NW, BS::KSEG><<<dim3((chunk_bound(v) + 7) / 8 * 8), 64 * BS::NW, bc_dq_lds_bytes<D, BS::KSEG>(), s>>>(b);
+  BcDqArgs b{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.start, w.sel.list, w.sel.bc_chunk_start,
+             w.sel.rank, w.sel.bc_order, w.sel.bc_chunk_len, w.part.o};
+  m_bwd_dq_bc<D, BS::NW, BS::KSEG><<<dim3((chunk_bound(v, w.sel.bc_chunk_len) + 7) / 8 * 8), 64 * BS::NW, bc_dq_lds_bytes<D, BS::KSEG>(), s>>>(b);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
 }  // namespace
 
-int slc_forward_kernel(const MfmaView &v, int D, const void *q, const int32_t *idx, const SelIndex &sel,
+int slc_forward_kernel(const MfmaView &v, int D, const void *q, const SelIndex &sel,
                        const SlcPartials &part, hipStream_t s) {
   switch (D) {
-    case 32: return launch_slc_forward<32>(v, (const bf16_t *)q, idx, sel, part, s);
-    case 64: return launch_slc_forward<64>(v, (const bf16_t *)q, idx, sel, part, s);
-    case 128: return launch_slc_forward<128>(v, (const bf16_t *)q, idx, sel, part, s);
+    case 32: return launch_slc_forward<32>(v, (const bf16_t *)q, sel, part, s);
+    case 64: return launch_slc_forward<64>(v, (const bf16_t *)q, sel, part, s);
+    case 128: return launch_slc_forward<128>(v, (const bf16_t *)q, sel, part, s);
     default: return SSA_ERR_UNSUPPORTED;
   }
 }
@@ -458,11 +454,11 @@ int slc_merge_kernel(const MfmaView &v, int D, const SlcPartials &part, const in
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
-int slc_dq_kernel(const MfmaView &v, int D, const BwdBuffers &w, const int32_t *idx, hipStream_t s) {
+int slc_dq_kernel(const MfmaView &v, int D, const BwdBuffers &w, hipStream_t s) {
   switch (D) {
-    case 32: return launch_slc_dq<32>(v, w, idx, s);
-    case 64: return launch_slc_dq<64>(v, w, idx, s);
-    case 128: return launch_slc_dq<128>(v, w, idx, s);
+    case 32: return launch_slc_dq<32>(v, w, s);
+    case 64: return launch_slc_dq<64>(v, w, s);
+    case 128: return launch_slc_dq<128>(v, w, s);
     default: return SSA_ERR_UNSUPPORTED;
   }
 }
