@@ -1,166 +1,541 @@
-// Generic SSA path: fp32 arithmetic on the vector ALUs, one wavefront per (token, query head) or per key row.
-// Serves SSA_F32 problems and every shape the bf16 MFMA kernels do not cover.  Same mathematics as the MFMA
-// path (paper eq. (2)-(6), Algorithm 1, window paragraph), written for clarity, not speed.
+// Generic SSA path: fp32 arithmetic (fp32 matrix instructions), any head_dim <= 128 (multiple of 8) and any head grouping up
+// to 64 query heads per KV head.  Serves SSA_F32 problems and every shape the bf16 MFMA kernels do not cover.  Same
+// mathematics as the MFMA path (paper eq. (2)-(6), Algorithm 1, window paragraph).
+//
+// One 16 x 16 tile of v_mfma_f32_16x16x4_f32 (A: lane l gives row l & 15, contraction index l >> 4; B: column l & 15, the
+// same index; C: column l & 15, rows 4*(l >> 4) .. +3; "n" = l & 15, "quad" = l >> 4) is 16 keys x 16 query columns, the
+// columns being (token, head) pairs of one KV head.  The index order inside a contraction is free, which removes every
+// data movement between the two products of a tile:
+//   * scores: step (s, i) contracts dims 16*s + 4*quad + i, so a lane's share of a row is DT 16-byte pieces;
+//   * the next product contracts over keys, step i over keys 4*quad + i: exactly the four scores a lane holds, and the other
+//     operand is DT consecutive dims (n*DT ..) of row 4*quad + i, one vector load; result row r of block b is dim r*DT + b.
+// Operands come straight from memory (one KV head's rows stay in the caches), with the next tile's in flight during a
+// tile; there is no LDS staging and no barrier inside a walk.  The wavefronts of a workgroup share their 16 columns (or
+// 16 keys) and deal the tiles of the walk out among them, so that a problem of a few thousand rows fills the chip; their
+// partial results meet in LDS and are added in wavefront order (every sum in one fixed order: no atomics).
+// Bound: latency of the walks at a few thousand tokens (2874 tokens, 4 heads of 32, forward + backward: 6.55 -> 0.27 ms;
+// the former kernels ran one row per wavefront with the dims in a scalar loop), fp32 matrix rate above (6000 tokens, 16 heads of
+// 64: 35-60 of the 136 TFLOP/s a large fp32 product reaches).
 #include "ssa_internal.h"
 #include "profile.h"
 #include "topk_device.h"
 #include "mfma_launch.h"
 
+#include <mutex>
+
 namespace {
 
 constexpr int WAVE = 64;
+constexpr int NW = 4;        // wavefronts of the query-centric kernels
+// wavefronts of the key-centric kernel (its operands of 128 dims want the registers of one wavefront per SIMD)
+template <int DT> constexpr int nw_key() { return DT == 8 ? 4 : 8; }
+constexpr float LOG2E_F = 1.4426950408889634f, LN2_F = 0.6931471805599453f;
 
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-  return v;
-}
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
+typedef __attribute__((ext_vector_type(4))) float f4;
 
 struct BlkView {
-  const int32_t *perm, *tok_item, *tok_cmp, *tok_win, *cmp_start, *slc_start, *win_start, *slc_child_start, *cmp_batch,
-      *slc_batch;
+  const int32_t *perm, *tok_item, *tok_cmp, *tok_slc, *tok_win, *cmp_start, *slc_start, *win_start, *slc_child_start, *cmp_slc,
+      *cmp_batch, *slc_batch, *item_start;
+  int N, B, Nc, Ns;
 };
 
 static BlkView view_of(const ssa_blocks *b) {
-  return BlkView{b->perm, b->tok_item, b->tok_cmp, b->tok_win, b->cmp_start, b->slc_start, b->win_start,
-                 b->slc_child_start, b->cmp_batch, b->slc_batch};
+  return BlkView{b->perm, b->tok_item, b->tok_cmp, b->tok_slc, b->tok_win, b->cmp_start, b->slc_start, b->win_start,
+                 b->slc_child_start, b->cmp_slc, b->cmp_batch, b->slc_batch, b->item_start, b->N, b->B, b->Nc, b->Ns};
 }
 
-// Sorted fp32 copies of K,V and their per-compression-block means (eq. (5), mean pool over active tokens).
+__device__ inline f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+__device__ inline f4 ld4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
+__device__ inline f4 ld4(const uint16_t *p) {
+  const uint2 w = *reinterpret_cast<const uint2 *>(p);
+  return f4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xFFFF0000u)};
+}
+__device__ inline void st4(float *p, f4 v) { *reinterpret_cast<f4 *>(p) = v; }
+__device__ inline void st4(uint16_t *p, f4 v) {
+  *reinterpret_cast<ushort4 *>(p) = make_ushort4(f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3]));
+}
+
+// DT consecutive elements (DT = 1, 2, 4, 8) from an address aligned to their size.
+template <int DT, typename T>
+__device__ inline void ld_chunk(const T *p, float (&o)[DT]) {
+  struct alignas(DT * sizeof(T) < 16 ? DT * sizeof(T) : 16) C { T v[DT]; };
+  const C c = *reinterpret_cast<const C *>(p);
+#pragma unroll
+  for (int b = 0; b < DT; ++b) o[b] = io<T>::ld(c.v + b);
+}
+template <int DT, typename T>
+__device__ inline void st_chunk(T *p, const float (&o)[DT]) {
+  struct alignas(DT * sizeof(T) < 16 ? DT * sizeof(T) : 16) C { T v[DT]; };
+  C c;
+#pragma unroll
+  for (int b = 0; b < DT; ++b) io<T>::st(c.v + b, o[b]);
+  *reinterpret_cast<C *>(p) = c;
+}
+
+// A lane's 4*DT consecutive result dims (acc[b][i]: dim 4*DT*quad + i*DT + b of column n) to or from a row of floats.
+template <int DT>
+__device__ inline void acc_put(float *row, const f4 (&acc)[DT], int d = 16 * DT) {
+  const int quad = threadIdx.x >> 4 & 3;
+#pragma unroll
+  for (int w = 0; w < DT; ++w) {
+    f4 x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = acc[(4 * w + j) % DT][(4 * w + j) / DT];
+    if (4 * DT * quad + 4 * w < d) st4(row + 4 * DT * quad + 4 * w, x);
+  }
+}
+template <int DT>
+__device__ inline void acc_add(const float *row, f4 (&acc)[DT]) {
+  const int quad = threadIdx.x >> 4 & 3;
+#pragma unroll
+  for (int w = 0; w < DT; ++w) {
+    const f4 x = ld4(row + 4 * DT * quad + 4 * w);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[(4 * w + j) % DT][(4 * w + j) / DT] += x[j];
+  }
+}
+
+// Reductions over the four quads of a column (lanes 16 apart), result in all of them.
+__device__ inline float quad_sum(float v) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+__device__ inline float quad_max(float v) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ inline unsigned wave_min_u(unsigned v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v = min(v, (unsigned)__shfl_xor((int)v, off));
+  return v;
+}
+__device__ inline int wave_max_i32(int v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off));
+  return v;
+}
+
+// Sorted fp32 copies of K,V and their per-compression-block means (eq. (5), mean pool over active tokens).  One workgroup
+// per compression block; thread t keeps the 4 elements t % C of tokens t / C, t / C + 256 / C, ... (C = pieces of a row, at
+// most 256), whose sums meet in LDS in thread order.
 template <typename T>
-__global__ void g_sort_pool(const T *__restrict__ K, const T *__restrict__ V, BlkView bv, int row /*Hkv*d*/,
-                            float *__restrict__ Ks, float *__restrict__ Vs, float *__restrict__ Kc,
-                            float *__restrict__ Vc) {
+__global__ __launch_bounds__(256) void g_sort_pool(const T *__restrict__ K, const T *__restrict__ V, BlkView bv, int row /*Hkv*d*/,
+                                                   float *__restrict__ Ks, float *__restrict__ Vs, float *__restrict__ Kc,
+                                                   float *__restrict__ Vc) {
+  __shared__ f4 part[2][256];
   const int c = blockIdx.x;
   const int b = bv.cmp_start[c], e = bv.cmp_start[c + 1];
   const float inv = 1.0f / (float)(e - b);
-  for (int i = threadIdx.x; i < row; i += blockDim.x) {
-    float sk = 0.f, sv = 0.f;
-    for (int pos = b; pos < e; ++pos) {
-      const size_t src = (size_t)bv.perm[pos] * row + i;
-      const float kk = io<T>::ld(K + src), vv = io<T>::ld(V + src);
-      Ks[(size_t)pos * row + i] = kk;
-      Vs[(size_t)pos * row + i] = vv;
-      sk += kk;
-      sv += vv;
+  const int c4 = row / 4, C = min(c4, 256), ngrp = 256 / C, grp = threadIdx.x / C;
+  for (int f0 = 0; f0 < c4; f0 += C) {
+    const int f = f0 + (int)threadIdx.x % C;
+    f4 sk = {0.f, 0.f, 0.f, 0.f}, sv = sk;
+    if (grp < ngrp && f < c4)
+#pragma unroll 2
+      for (int pos = b + grp; pos < e; pos += ngrp) {
+        const size_t src = (size_t)bv.perm[pos] * row + 4 * f, dst = (size_t)pos * row + 4 * f;
+        const f4 kk = ld4(K + src), vv = ld4(V + src);
+        st4(Ks + dst, kk);
+        st4(Vs + dst, vv);
+        sk += kk;
+        sv += vv;
+      }
+    part[0][threadIdx.x] = sk;
+    part[1][threadIdx.x] = sv;
+    __syncthreads();
+    if ((int)threadIdx.x < C && f < c4) {
+      for (int gi = 1; gi < ngrp; ++gi) { sk += part[0][gi * C + threadIdx.x]; sv += part[1][gi * C + threadIdx.x]; }
+      f4 ok, ov;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { ok[i] = io<T>::round(sk[i] * inv); ov[i] = io<T>::round(sv[i] * inv); }
+      st4(Kc + (size_t)c * row + 4 * f, ok);
+      st4(Vc + (size_t)c * row + 4 * f, ov);
     }
-    // rounded to the element type: a bf16 problem sees the same pooled rows here as in the matrix-core kernels, whose
-    // forward may have produced the lse this path's backward is given
-    Kc[(size_t)c * row + i] = io<T>::round(sk * inv);
-    Vc[(size_t)c * row + i] = io<T>::round(sv * inv);
+    __syncthreads();
   }
 }
 
-// Online-softmax state of one query row spread over a wavefront (lanes hold output dims lane and lane+64).
-struct RowState {
-  float m, l, a0, a1;
+// The 16 query columns of a workgroup: with h_s <= 16 heads per KV head, tpt tokens x h_s heads (columns past tpt*h_s are
+// unused); with more heads, one token's heads 16 at a time.
+struct Cols {
+  int tok, h, pos, slot;
+  bool valid;
+};
+__host__ __device__ inline int tokens_per_tile(int hs) { return hs <= 16 ? 16 / hs : 1; }
+__host__ __device__ inline int tiles_per_token(int hs) { return hs <= 16 ? 1 : (hs + 15) / 16; }
+__device__ inline Cols columns(const BlkView &bv, int hs, int g, int tile) {
+  const int n = threadIdx.x & 15;
+  Cols c;
+  if (hs <= 16) {
+    const int tpt = 16 / hs;
+    c.slot = n / hs;
+    c.pos = tile * tpt + c.slot;
+    c.h = g * hs + n % hs;
+    c.valid = c.slot < tpt && c.pos < bv.N;
+  } else {
+    const int ct = (hs + 15) / 16, hh = (tile % ct) * 16 + n;
+    c.slot = 0;
+    c.pos = tile / ct;
+    c.h = g * hs + hh;
+    c.valid = hh < hs;
+  }
+  if (!c.valid) { c.pos = 0; c.h = g * hs; }
+  c.tok = bv.perm[c.pos];
+  return c;
+}
+
+// A lane's share of one row as a score operand: dims 16*s + 4*quad .. +3, s < DT; zero past d and for a missing row.
+template <typename T, int DT>
+__device__ inline void ld_row(const T *row, int d, bool valid, f4 (&o)[DT]) {
+  const int quad = threadIdx.x >> 4 & 3;
+#pragma unroll
+  for (int s = 0; s < DT; ++s) {
+    const int dim = 16 * s + 4 * quad;
+    o[s] = valid && dim < d ? ld4(row + dim) : f4{0.f, 0.f, 0.f, 0.f};
+  }
+}
+// The same for key rows, where garbage past d is harmless (it meets the zeros of the other operand): no selects.
+template <int DT>
+__device__ inline void ld_key(const float *row, int d, f4 (&o)[DT]) {
+  const int quad = threadIdx.x >> 4 & 3;
+#pragma unroll
+  for (int s = 0; s < DT; ++s) o[s] = ld4(row + (16 * s + 4 * quad < d ? 16 * s + 4 * quad : 0));
+}
+
+template <int DT>
+__device__ inline f4 dot16(const f4 (&a)[DT], const f4 (&b)[DT]) {
+  f4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
+#pragma unroll
+  for (int s = 0; s < DT; ++s)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i & 1) c1 = mfma4(a[s][i], b[s][i], c1);
+      else c0 = mfma4(a[s][i], b[s][i], c0);
+    }
+  return c0 + c1;
+}
+
+// Walks: next() moves to this wavefront's next 16-key tile.  kb: its first key; last: the last existing key of its range;
+// lo, hi: the keys this lane's column may see.
+struct RangeWalk {  // one range [k0, k1) for all columns, with a window of its own per column
+  int kb, k1, lo, hi, last, step;
+  __device__ RangeWalk(int k0, int k1_, int lo_, int hi_, int wid, int nw)
+      : kb(k0 + 16 * (wid - nw)), k1(k1_), lo(lo_), hi(hi_), last(k1_ - 1), step(16 * nw) {}
+  __device__ bool next() { kb += step; return kb < k1; }
+};
+// The union of the selected blocks of a workgroup's tokens, ascending, in LDS: keys [k0, k1) of the block and a bit per
+// token that selected it.
+struct UnionEntry { int k0, k1; unsigned tokens; };
+struct UnionWalk {
+  const UnionEntry *u, *end;
+  int kb, kend, lo, hi, last, step, wid, nw, phase;
+  unsigned bit;  // this lane's column: 1 << token slot, 0 for an unused column
+  __device__ UnionWalk(const UnionEntry *u_, int count, int slot, bool valid, int wid_, int nw_)
+      : u(u_), end(u_ + count), kb(0), kend(0), lo(0), hi(0), last(0), step(16 * nw_), wid(wid_), nw(nw_), phase(0),
+        bit(valid ? 1u << slot : 0u) {}
+  __device__ bool next() {
+    kb += step;
+    while (kb >= kend) {
+      if (u == end) return false;
+      const int k0 = __builtin_amdgcn_readfirstlane(u->k0);
+      kend = __builtin_amdgcn_readfirstlane(u->k1);
+      const bool on = (u->tokens & bit) != 0;
+      ++u;
+      last = kend - 1;
+      lo = on ? k0 : 0;
+      hi = on ? kend : 0;
+      kb = k0 + 16 * ((wid - phase + nw) % nw);
+      phase = (phase + (kend - k0 + 15) / 16) % nw;
+    }
+    return true;
+  }
 };
 
-__device__ inline void attend_range(RowState &st, const float *qs /*LDS, pre-scaled*/, float *ps /*LDS[64]*/,
-                                    const float *__restrict__ Kb, const float *__restrict__ Vb, int kb, int ke, int Hkv,
-                                    int g, int d) {
-  const int lane = threadIdx.x;
-  for (int k0 = kb; k0 < ke; k0 += WAVE) {
-    const int key = k0 + lane;
-    float s = -INFINITY;
-    if (key < ke) {
-      const float *kr = Kb + ((size_t)key * Hkv + g) * d;
-      float acc = 0.f;
-      for (int i = 0; i < d; ++i) acc += qs[i] * kr[i];
-      s = acc;
-    }
-    const float mn = fmaxf(st.m, wave_max(s));
-    const float p = key < ke ? __expf(s - mn) : 0.f;
-    const float alpha = __expf(st.m - mn);  // exp(-inf) = 0 on the first tile
-    st.l = st.l * alpha + wave_sum(p);
-    st.a0 *= alpha;
-    st.a1 *= alpha;
-    st.m = mn;
-    ps[lane] = p;
-    __syncthreads();
-    const int n = min(WAVE, ke - k0);
-    for (int kk = 0; kk < n; ++kk) {
-      const float *vr = Vb + ((size_t)(k0 + kk) * Hkv + g) * d;
-      const float pv = ps[kk];
-      if (lane < d) st.a0 += pv * vr[lane];
-      if (lane + WAVE < d) st.a1 += pv * vr[lane + WAVE];
-    }
-    __syncthreads();
+// Builds the union of the selected blocks of tokens pos0 .. pos0+ntok-1 (rows of I in any order, invalid ids ignored).
+// LDS: raw [ntok*T], first [ntok*T], u [ntok*T]; returns the number of entries.
+__host__ __device__ inline size_t union_lds_bytes(int ntok, int T) { return (size_t)ntok * T * (sizeof(UnionEntry) + 8); }
+__device__ inline int build_union(const BlkView &bv, const int32_t *idx, int Hkv, int T, int g, int pos0, int ntok, int cap,
+                                  unsigned *smem, UnionEntry *&u) {
+  unsigned *raw = smem, *first = raw + cap;
+  u = (UnionEntry *)(first + cap);
+  const int n = ntok * T;
+  for (int e = threadIdx.x; e < n; e += blockDim.x) {
+    const int t = e / T, b = idx[((size_t)bv.perm[pos0 + t] * Hkv + g) * T + e % T];
+    raw[e] = b >= 0 && b < bv.Ns ? (unsigned)b : ~0u;
   }
-}
-
-// branch: 0 compression, 1 selection, 2 window.  One wavefront per (sorted position, query head).
-template <typename T>
-__global__ void g_attn_fwd(int branch, const T *__restrict__ Q, BlkView bv, const int32_t *__restrict__ idx, int N,
-                           int Hq, int Hkv, int d, int Tk, float scale, const float *__restrict__ Kb,
-                           const float *__restrict__ Vb, T *__restrict__ Ob, float *__restrict__ lse) {
-  __shared__ float qs[128];
-  __shared__ float ps[WAVE];
-  const int pos = blockIdx.x / Hq, h = blockIdx.x % Hq, hs = Hq / Hkv, g = h / hs, lane = threadIdx.x;
-  const int tok = bv.perm[pos];
-  for (int i = lane; i < d; i += WAVE) qs[i] = io<T>::ld(Q + ((size_t)tok * Hq + h) * d + i) * scale;
   __syncthreads();
-  RowState st{-INFINITY, 0.f, 0.f, 0.f};
-  if (branch == 0) {
-    const int item = bv.tok_item[pos];
-    attend_range(st, qs, ps, Kb, Vb, bv.cmp_batch[item], bv.cmp_batch[item + 1], Hkv, g, d);
-  } else if (branch == 2) {
-    const int w = bv.tok_win[pos];
-    attend_range(st, qs, ps, Kb, Vb, bv.win_start[w], bv.win_start[w + 1], Hkv, g, d);
-  } else {
-    const int32_t *row = idx + ((size_t)tok * Hkv + g) * Tk;
-    for (int j = 0; j < Tk; ++j) {
-      const int b = row[j];
-      if (b < 0) break;
-      attend_range(st, qs, ps, Kb, Vb, bv.slc_start[b], bv.slc_start[b + 1], Hkv, g, d);
-    }
+  for (int e = threadIdx.x; e < n; e += blockDim.x) {
+    const unsigned v = raw[e];
+    bool f = v != ~0u;
+    for (int i = 0; i < e; ++i) f = f && raw[i] != v;
+    first[e] = f ? 1u : 0u;
   }
-  const float inv = st.l > 0.f ? 1.0f / st.l : 0.f;
-  T *o = Ob + (((size_t)branch * N + tok) * Hq + h) * d;
-  if (lane < d) io<T>::st(o + lane, st.a0 * inv);
-  if (lane + WAVE < d) io<T>::st(o + lane + WAVE, st.a1 * inv);
-  if (lane == 0) lse[((size_t)branch * N + tok) * Hq + h] = st.l > 0.f ? st.m + __logf(st.l) : -INFINITY;
-}
-
-// Selection scores (eq. (6)) and top-k.  One wavefront per (sorted position, KV head).
-template <typename T>
-__global__ void g_scores_topk(const T *__restrict__ Q, BlkView bv, int N, int Hq, int Hkv, int d, int Tk, float scale,
-                              const float *__restrict__ Kc, const float *__restrict__ lse_cmp /*[N,Hq] caller order*/,
-                              int32_t *__restrict__ idx, int s_max) {
-  extern __shared__ float smem[];
-  const int hs = Hq / Hkv;
-  float *S = smem;                       // [s_max]
-  float *qs = S + s_max;                 // [hs][d]
-  float *ls = qs + hs * d;               // [hs]
-  uint32_t *sel = (uint32_t *)(ls + hs); // [(s_max+31)/32]
-  const int pos = blockIdx.x / Hkv, g = blockIdx.x % Hkv, lane = threadIdx.x;
-  const int tok = bv.perm[pos], item = bv.tok_item[pos];
-  for (int i = lane; i < hs * d; i += WAVE) qs[i] = io<T>::ld(Q + ((size_t)tok * Hq + g * hs) * d + i) * scale;
-  for (int i = lane; i < hs; i += WAVE) ls[i] = lse_cmp[(size_t)tok * Hq + g * hs + i];
   __syncthreads();
-  const int s0 = bv.slc_batch[item], s1 = bv.slc_batch[item + 1];
-  for (int b = s0 + lane; b < s1; b += WAVE) {
-    float acc = 0.f;
-    for (int c = bv.slc_child_start[b]; c < bv.slc_child_start[b + 1]; ++c) {
-      const float *kr = Kc + ((size_t)c * Hkv + g) * d;
-      for (int hl = 0; hl < hs; ++hl) {
-        float s = 0.f;
-        for (int i = 0; i < d; ++i) s += qs[hl * d + i] * kr[i];
-        acc += __expf(s - ls[hl]);
+  for (int e = threadIdx.x; e < n; e += blockDim.x) {
+    if (!first[e]) continue;
+    const unsigned v = raw[e];
+    unsigned tokens = 0u;
+    int r = 0;
+    for (int t = 0, i = 0; t < ntok; ++t)
+      for (int j = 0; j < T; ++j, ++i) {
+        if (raw[i] == v) tokens |= 1u << t;
+        r += raw[i] < v ? (int)first[i] : 0;
       }
-    }
-    S[b - s0] = acc;
+    u[r] = UnionEntry{bv.slc_start[v], bv.slc_start[v + 1], tokens};
   }
+  int total = 0;
+  for (int i = threadIdx.x & 63; i < n; i += WAVE) total += (int)first[i];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) total += __shfl_xor(total, off);
   __syncthreads();
-  topk_wave(S, s1 - s0, Tk, s0, idx + ((size_t)tok * Hkv + g) * Tk, sel);
+  return __builtin_amdgcn_readfirstlane(total);
 }
 
-__global__ void g_topk_from_scores(const float *__restrict__ scores, BlkView bv, int N, int Hkv, int Tk, int s_max,
+// ---- forward ------------------------------------------------------------------------------------------------------------
+template <int DT>
+struct FwdTile {
+  f4 k[DT];
+  float vt[4][DT];
+};
+template <int DT>
+__device__ inline void ld_fwd_tile(FwdTile<DT> &t, const float *Kg, const float *Vg, int stride, int d, int kb, int last) {
+  const int n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, c = n * DT < d ? n * DT : 0;
+  ld_key<DT>(Kg + (size_t)min(kb + n, last) * stride, d, t.k);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ld_chunk<DT>(Vg + (size_t)min(kb + 4 * quad + i, last) * stride + c, t.vt[i]);
+}
+
+template <int DT>
+struct State {
+  f4 o[DT];
+  float m, l;  // reference maximum (log2 units) of the column; this lane's share of the sum
+};
+
+// Softmax attention of the 16 columns over a walk (Algorithm 1's inner loop).  The reference maximum is raised lazily: a
+// column's exponents stay below 2^8, and the result does not depend on the reference.
+template <int DT, class Walk>
+__device__ inline void attend(State<DT> &st, const f4 (&q)[DT], Walk w, const float *Kg, const float *Vg, int stride, int d, float sl2) {
+  const int quad = threadIdx.x >> 4 & 3;
+  st.m = -INFINITY;
+  st.l = 0.f;
+#pragma unroll
+  for (int b = 0; b < DT; ++b) st.o[b] = f4{0.f, 0.f, 0.f, 0.f};
+  bool more = w.next();
+  FwdTile<DT> cur, nxt;
+  if (more) ld_fwd_tile(cur, Kg, Vg, stride, d, w.kb, w.last);
+  while (more) {
+    const int rel = w.kb + 4 * quad - w.lo, len = w.hi - w.lo;
+    more = w.next();
+    if (more) ld_fwd_tile(nxt, Kg, Vg, stride, d, w.kb, w.last);
+    f4 v = dot16<DT>(cur.k, q);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (unsigned)(rel + i) < (unsigned)len ? v[i] * sl2 : -INFINITY;
+    const float pm = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+    if (__any(pm > st.m + 8.f)) {
+      const float mn = fmaxf(st.m, quad_max(pm));
+      const float alpha = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st.m - mn);
+      st.m = mn;
+      st.l *= alpha;
+#pragma unroll
+      for (int b = 0; b < DT; ++b) st.o[b] *= alpha;
+    }
+    const float neg = st.m == -INFINITY ? -INFINITY : -st.m;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float p = __builtin_amdgcn_exp2f(v[i] + neg);
+      st.l += p;
+#pragma unroll
+      for (int b = 0; b < DT; ++b) st.o[b] = mfma4(cur.vt[i][b], p, st.o[b]);
+    }
+    cur = nxt;
+  }
+}
+
+// Merge of the wavefronts' states through LDS: thread t gets column t / 16, dims (t % 16)*DT .. +DT-1, normalised, and the
+// column's log-sum-exp (natural).
+template <int DT>
+struct MergeBuf {
+  float ml[NW][16][2];
+  float o[NW][16][16 * DT + 4];
+};
+template <int DT>
+__device__ inline float merge_waves(MergeBuf<DT> &mb, const State<DT> &st, float (&o)[DT]) {
+  const int wid = threadIdx.x >> 6, n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
+  const float l = quad_sum(st.l);
+  __syncthreads();  // the buffer may still be read from the merge before
+  if (quad == 0) { mb.ml[wid][n][0] = st.m; mb.ml[wid][n][1] = l; }
+  acc_put<DT>(mb.o[wid][n], st.o);
+  __syncthreads();
+  const int col = threadIdx.x >> 4, c = (threadIdx.x & 15) * DT;
+  float M = -INFINITY, L = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, mb.ml[w][col][0]);
+#pragma unroll
+  for (int b = 0; b < DT; ++b) o[b] = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const float mw = mb.ml[w][col][0], f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+    L += f * mb.ml[w][col][1];
+#pragma unroll
+    for (int b = 0; b < DT; ++b) o[b] += f * mb.o[w][col][c + b];
+  }
+  const float inv = L > 0.f ? 1.0f / L : 0.f;
+#pragma unroll
+  for (int b = 0; b < DT; ++b) o[b] *= inv;
+  return L > 0.f ? M * LN2_F + __logf(L) : -INFINITY;
+}
+
+struct FwdArgs {
+  const void *Q, *gates;
+  BlkView bv;
+  const int32_t *idx;
+  int Hq, Hkv, hs, d, T;
+  float sl2;
+  const float *K, *V;    // cmp kernel: pooled rows; selection + window kernel: token rows
+  void *Ob, *out;
+  float *lse;
+};
+
+// Bounds [lo, hi) of the union over valid columns.
+__device__ inline void union_range(int lo, int hi, bool valid, int &k0, int &k1) {
+  k0 = (int)__builtin_amdgcn_readfirstlane((int)wave_min_u(valid ? (unsigned)lo : 0x7fffffffu));
+  k1 = __builtin_amdgcn_readfirstlane(wave_max_i32(valid ? hi : 0));
+  if (k1 <= k0) k0 = k1 = 0;
+}
+
+// Compression branch: one workgroup per 16 columns.
+template <typename T, int DT>
+__global__ __launch_bounds__(64 * NW) void g_cmp_fwd(FwdArgs a) {
+  __shared__ MergeBuf<DT> mb;
+  __shared__ int scol[16];
+  const int g = blockIdx.y, wid = threadIdx.x >> 6;
+  const Cols c = columns(a.bv, a.hs, g, blockIdx.x);
+  if (threadIdx.x < 16) scol[threadIdx.x] = c.valid ? c.tok * a.Hq + c.h : -1;
+  const int item = a.bv.tok_item[c.pos], lo = c.valid ? a.bv.cmp_batch[item] : 0, hi = c.valid ? a.bv.cmp_batch[item + 1] : 0;
+  int k0, k1;
+  union_range(lo, hi, c.valid, k0, k1);
+  f4 q[DT];
+  ld_row<T, DT>((const T *)a.Q + ((size_t)c.tok * a.Hq + c.h) * a.d, a.d, c.valid, q);
+  State<DT> st;
+  attend<DT>(st, q, RangeWalk(k0, k1, lo, hi, wid, NW), a.K + g * a.d, a.V + g * a.d, a.Hkv * a.d, a.d, a.sl2);
+  float o[DT];
+  const float lse = merge_waves<DT>(mb, st, o);
+  const int th = scol[threadIdx.x >> 4], ch = (threadIdx.x & 15) * DT;
+  if (th < 0) return;
+  if (ch < a.d) st_chunk<DT>((T *)a.Ob + (size_t)th * a.d + ch, o);
+  if (ch == 0) a.lse[th] = lse;
+}
+
+// Window branch, selection branch and the gated sum of eq. (4): one workgroup per 16 columns.
+template <typename T, int DT>
+__global__ __launch_bounds__(64 * NW) void g_slc_win_fwd(FwdArgs a) {
+  extern __shared__ unsigned ids[];  // build_union
+  __shared__ MergeBuf<DT> mb;
+  __shared__ int scol[16];
+  const int g = blockIdx.y, wid = threadIdx.x >> 6, stride = a.Hkv * a.d;
+  const Cols c = columns(a.bv, a.hs, g, blockIdx.x);
+  if (threadIdx.x < 16) scol[threadIdx.x] = c.valid ? c.tok * a.Hq + c.h : -1;
+  const int tpt = tokens_per_tile(a.hs), pos0 = (int)blockIdx.x / tiles_per_token(a.hs) * tpt;
+  UnionEntry *un;
+  const int n_un = build_union(a.bv, a.idx, a.Hkv, a.T, g, pos0, min(tpt, a.bv.N - pos0), tpt * a.T, ids, un);
+  f4 q[DT];
+  ld_row<T, DT>((const T *)a.Q + ((size_t)c.tok * a.Hq + c.h) * a.d, a.d, c.valid, q);
+  const float *Kg = a.K + g * a.d, *Vg = a.V + g * a.d;
+  const int win = a.bv.tok_win[c.pos], lo = c.valid ? a.bv.win_start[win] : 0, hi = c.valid ? a.bv.win_start[win + 1] : 0;
+  int k0, k1;
+  union_range(lo, hi, c.valid, k0, k1);
+  State<DT> st;
+  float ow[DT], os[DT];
+  attend<DT>(st, q, RangeWalk(k0, k1, lo, hi, wid, NW), Kg, Vg, stride, a.d, a.sl2);
+  const float lse_w = merge_waves<DT>(mb, st, ow);
+  attend<DT>(st, q, UnionWalk(un, n_un, c.slot, c.valid, wid, NW), Kg, Vg, stride, a.d, a.sl2);
+  const float lse_s = merge_waves<DT>(mb, st, os);
+  const int th = scol[threadIdx.x >> 4], ch = (threadIdx.x & 15) * DT;
+  if (th < 0) return;
+  const size_t NH = (size_t)a.bv.N * a.Hq;
+  if (ch == 0) { a.lse[NH + th] = lse_s; a.lse[2 * NH + th] = lse_w; }
+  if (ch >= a.d) return;
+  T *Ob = (T *)a.Ob;
+  const size_t off = (size_t)th * a.d + ch;
+  st_chunk<DT>(Ob + NH * a.d + off, os);
+  st_chunk<DT>(Ob + 2 * NH * a.d + off, ow);
+  float oc[DT], r[DT];
+  ld_chunk<DT>(Ob + off, oc);
+  const T *gt = (const T *)a.gates + (size_t)th * 3;
+  const float w0 = io<T>::ld(gt), w1 = io<T>::ld(gt + 1), w2 = io<T>::ld(gt + 2);
+#pragma unroll
+  for (int b = 0; b < DT; ++b) r[b] = w0 * oc[b] + w1 * io<T>::round(os[b]) + w2 * io<T>::round(ow[b]);
+  st_chunk<DT>((T *)a.out + off, r);
+}
+
+// Selection scores (eq. (6)) and top-k.  One workgroup per tw tokens of one KV head: chunks of KC pooled keys, their
+// probabilities in LDS per column, then one thread per (token, selection block) adds its children's probabilities head by
+// head in a fixed order.
+constexpr int KC = 256;
+struct ScoreArgs {
+  const void *Q;
+  BlkView bv;
+  const float *Kc, *lse;  // lse: compression branch [N,Hq], caller order
+  int32_t *idx;
+  int Hq, Hkv, hs, d, T, tw, s_max;
+  float sl2;
+};
+size_t score_lds_bytes(int tw, int s_max) { return ((size_t)16 * (KC + 4) + (size_t)tw * s_max + (size_t)NW * ((s_max + 31) / 32)) * 4; }
+
+template <typename T, int DT>
+__global__ __launch_bounds__(64 * NW) void g_scores_topk(ScoreArgs a) {
+  extern __shared__ float sm[];
+  float *P = sm, *S = P + 16 * (KC + 4);  // P [16 columns][KC + 4], S [tw][s_max]
+  uint32_t *marks = (uint32_t *)(S + (size_t)a.tw * a.s_max);
+  const int g = blockIdx.y, wid = threadIdx.x >> 6, n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
+  const int pos0 = blockIdx.x * a.tw, ntok = min(a.tw, a.bv.N - pos0), hc = min(a.hs, 16), cts = tiles_per_token(a.hs);
+  for (int i = threadIdx.x; i < a.tw * a.s_max; i += 64 * NW) S[i] = 0.f;
+  const int i0 = a.bv.tok_item[pos0], i1 = a.bv.tok_item[pos0 + ntok - 1];
+  const int k0 = a.bv.cmp_batch[i0], k1 = a.bv.cmp_batch[i1 + 1];
+  for (int kc = k0; kc < k1; kc += KC) {
+    const int ke = min(kc + KC, k1), b0 = a.bv.cmp_slc[kc], nb = a.bv.cmp_slc[ke - 1] + 1 - b0;
+    for (int ct = 0; ct < cts; ++ct) {
+      const int slot = cts == 1 ? n / hc : 0, head = cts == 1 ? n % hc : ct * 16 + n;
+      const bool valid = slot < ntok && head < a.hs;
+      const size_t th = (size_t)a.bv.perm[pos0 + (valid ? slot : 0)] * a.Hq + g * a.hs + (valid ? head : 0);
+      f4 q[DT];
+      ld_row<T, DT>((const T *)a.Q + th * a.d, a.d, valid, q);
+      const float nl = valid ? -a.lse[th] * LOG2E_F : -INFINITY;
+      for (int kb = kc + 16 * wid; kb < ke; kb += 16 * NW) {
+        f4 k[DT];
+        ld_key<DT>(a.Kc + ((size_t)min(kb + n, k1 - 1) * a.Hkv + g) * a.d, a.d, k);
+        const f4 v = dot16<DT>(k, q);
+        f4 p;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(v[i], a.sl2, nl));
+        st4(P + n * (KC + 4) + kb - kc + 4 * quad, p);
+      }
+      __syncthreads();
+      const int nh = cts == 1 ? a.hs : min(16, a.hs - ct * 16);
+      for (int e = threadIdx.x; e < ntok * nb; e += 64 * NW) {
+        const int sl = e / nb, b = b0 + e % nb, item = a.bv.tok_item[pos0 + sl], s0 = a.bv.slc_batch[item];
+        if (b < s0 || b >= a.bv.slc_batch[item + 1]) continue;
+        const int c0 = max(a.bv.slc_child_start[b], kc), c1 = min(a.bv.slc_child_start[b + 1], ke);
+        float acc = S[(size_t)sl * a.s_max + b - s0];
+        for (int c = c0; c < c1; ++c)
+          for (int hl = 0; hl < nh; ++hl) acc += P[(sl * nh * (cts == 1) + hl) * (KC + 4) + c - kc];
+        S[(size_t)sl * a.s_max + b - s0] = acc;
+      }
+      __syncthreads();
+    }
+  }
+  for (int sl = wid; sl < ntok; sl += NW) {
+    const int item = a.bv.tok_item[pos0 + sl], s0 = a.bv.slc_batch[item], cnt = a.bv.slc_batch[item + 1] - s0;
+    topk_wave(S + (size_t)sl * a.s_max, cnt, a.T, s0, a.idx + ((size_t)a.bv.perm[pos0 + sl] * a.Hkv + g) * a.T, marks + wid * ((a.s_max + 31) / 32));
+  }
+}
+
+__global__ void g_topk_from_scores(const float *__restrict__ scores, BlkView bv, int Hkv, int Tk, int s_max,
                                    const int32_t *__restrict__ inv_perm, int32_t *__restrict__ idx) {
   extern __shared__ float smem[];
   float *S = smem;
@@ -173,213 +548,329 @@ __global__ void g_topk_from_scores(const float *__restrict__ scores, BlkView bv,
   topk_wave(S, n, Tk, s0, idx + ((size_t)tok * Hkv + g) * Tk, sel);
 }
 
-// eq. (4): out = sum_b gate_b * out_b
-template <typename T>
-__global__ void g_combine(const T *__restrict__ Ob, const T *__restrict__ gates, size_t N, int Hq, int d,
-                          T *__restrict__ out) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t total = N * Hq * d;
-  if (i >= total) return;
-  const size_t th = i / d;
-  float acc = 0.f;
-  for (int b = 0; b < 3; ++b) acc += io<T>::ld(gates + th * 3 + b) * io<T>::ld(Ob + (size_t)b * total + i);
-  io<T>::st(out + i, acc);
+// ---- backward -----------------------------------------------------------------------------------------------------------
+// Per (query row, key) pair of branch b with gate w: P = exp(S - lse), dS = P (w <dO, V> - delta) scale, delta = w <dO, O_b>;
+// dV += w P dO, dQ += dS K, dK += dS Q.
+template <int DT>
+struct DqTile {
+  f4 k[DT], v[DT];
+  float kt[4][DT];
+};
+template <int DT>
+__device__ inline void ld_dq_tile(DqTile<DT> &t, const float *Kg, const float *Vg, int stride, int d, int kb, int last) {
+  const int n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, c = n * DT < d ? n * DT : 0;
+  const size_t r = (size_t)min(kb + n, last) * stride;
+  ld_key<DT>(Kg + r, d, t.k);
+  ld_key<DT>(Vg + r, d, t.v);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ld_chunk<DT>(Kg + (size_t)min(kb + 4 * quad + i, last) * stride + c, t.kt[i]);
 }
 
-// dgates[t,h,b] = <dO, O_b>; delta[b,t,h] = gate_b * dgates  (= <gate_b*dO, O_b>, the softmax-backward row term)
-template <typename T>
-__global__ void g_bwd_pre(const T *__restrict__ dO, const T *__restrict__ Ob, const T *__restrict__ gates, size_t N,
-                          int Hq, int d, T *__restrict__ dgates, float *__restrict__ delta) {
-  const size_t th = blockIdx.x;  // token*Hq + head, caller order
-  const int lane = threadIdx.x;
-  for (int b = 0; b < 3; ++b) {
-    float acc = 0.f;
-    for (int i = lane; i < d; i += WAVE)
-      acc += io<T>::ld(dO + th * d + i) * io<T>::ld(Ob + ((size_t)b * N * Hq + th) * d + i);
-    acc = wave_sum(acc);
-    if (lane == 0) {
-      io<T>::st(dgates + th * 3 + b, acc);
-      delta[(size_t)b * N * Hq + th] = acc * io<T>::ld(gates + th * 3 + b);
+struct RowInfo { float lse2, delta, w; };
+
+template <int DT, class Walk>
+__device__ inline void attend_bwd(f4 (&dq)[DT], const f4 (&q)[DT], const f4 (&go)[DT], const RowInfo &ri, Walk w, const float *Kg,
+                                  const float *Vg, int stride, int d, float sl2, float scale) {
+  const int quad = threadIdx.x >> 4 & 3;
+  bool more = w.next();
+  DqTile<DT> cur, nxt;
+  if (more) ld_dq_tile(cur, Kg, Vg, stride, d, w.kb, w.last);
+  while (more) {
+    const int rel = w.kb + 4 * quad - w.lo, len = w.hi - w.lo;
+    more = w.next();
+    if (more) ld_dq_tile(nxt, Kg, Vg, stride, d, w.kb, w.last);
+    const f4 s = dot16<DT>(cur.k, q), dp = dot16<DT>(cur.v, go);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float p = (unsigned)(rel + i) < (unsigned)len ? __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], sl2, -ri.lse2)) : 0.f;
+      const float ds = p * (ri.w * dp[i] - ri.delta) * scale;
+#pragma unroll
+      for (int b = 0; b < DT; ++b) dq[b] = mfma4(cur.kt[i][b], ds, dq[b]);
     }
+    cur = nxt;
   }
 }
 
-struct BwdRow {
-  float dq0, dq1;
+struct DqArgs {
+  const void *Q, *dO, *Ob, *gates;
+  BlkView bv;
+  const int32_t *idx;
+  int Hq, Hkv, hs, d, T;
+  float scale, sl2;
+  const float *Ks, *Vs, *Kc, *Vc, *lse;
+  void *dQ, *dgates;
+  f4 *info;  // [3][N*Hq]: lse (log2 units), delta, gate
 };
 
-__device__ inline void attend_range_bwd(BwdRow &r, const float *qs /*unscaled*/, const float *gb, float *dss, float lse,
-                                        float delta, float scale, const float *__restrict__ Kb,
-                                        const float *__restrict__ Vb, int kb, int ke, int Hkv, int g, int d) {
-  const int lane = threadIdx.x;
-  for (int k0 = kb; k0 < ke; k0 += WAVE) {
-    const int key = k0 + lane;
-    float ds = 0.f;
-    if (key < ke) {
-      const float *kr = Kb + ((size_t)key * Hkv + g) * d;
-      const float *vr = Vb + ((size_t)key * Hkv + g) * d;
-      float s = 0.f, dp = 0.f;
-      for (int i = 0; i < d; ++i) {
-        s += qs[i] * kr[i];
-        dp += gb[i] * vr[i];
-      }
-      ds = __expf(s * scale - lse) * (dp - delta) * scale;
-    }
-    dss[lane] = ds;
-    __syncthreads();
-    const int n = min(WAVE, ke - k0);
-    for (int kk = 0; kk < n; ++kk) {
-      const size_t row = ((size_t)(k0 + kk) * Hkv + g) * d;
-      const float dv = dss[kk];
-      if (lane < d) r.dq0 += dv * Kb[row + lane];
-      if (lane + WAVE < d) r.dq1 += dv * Kb[row + lane + WAVE];
-    }
-    __syncthreads();
-  }
-}
-
-// dQ of all three branches for one (sorted position, head): query-centric, the keys of each branch in turn.
-template <typename T>
-__global__ void g_attn_bwd_dq(const T *__restrict__ Q, const T *__restrict__ dO, const T *__restrict__ gates, BlkView bv,
-                              const int32_t *__restrict__ idx, int N, int Hq, int Hkv, int d, int Tk, float scale,
-                              const float *__restrict__ Ks, const float *__restrict__ Vs, const float *__restrict__ Kc,
-                              const float *__restrict__ Vc, const float *__restrict__ lse, const float *__restrict__ delta,
-                              T *__restrict__ dQ) {
-  __shared__ float qs[128], go[128], gb[128], dss[WAVE];
-  const int pos = blockIdx.x / Hq, h = blockIdx.x % Hq, hs = Hq / Hkv, g = h / hs, lane = threadIdx.x;
-  const int tok = bv.perm[pos];
-  const size_t th = (size_t)tok * Hq + h;
-  for (int i = lane; i < d; i += WAVE) {
-    qs[i] = io<T>::ld(Q + th * d + i);
-    go[i] = io<T>::ld(dO + th * d + i);
-  }
-  BwdRow r{0.f, 0.f};
-  for (int branch = 0; branch < 3; ++branch) {
-    __syncthreads();
-    const float w = io<T>::ld(gates + th * 3 + branch);
-    for (int i = lane; i < d; i += WAVE) gb[i] = w * go[i];
-    __syncthreads();
-    const float l = lse[(size_t)branch * N * Hq + th], dl = delta[(size_t)branch * N * Hq + th];
-    if (branch == 0) {
-      const int item = bv.tok_item[pos];
-      attend_range_bwd(r, qs, gb, dss, l, dl, scale, Kc, Vc, bv.cmp_batch[item], bv.cmp_batch[item + 1], Hkv, g, d);
-    } else if (branch == 2) {
-      const int wdw = bv.tok_win[pos];
-      attend_range_bwd(r, qs, gb, dss, l, dl, scale, Ks, Vs, bv.win_start[wdw], bv.win_start[wdw + 1], Hkv, g, d);
-    } else {
-      const int32_t *row = idx + ((size_t)tok * Hkv + g) * Tk;
-      for (int j = 0; j < Tk; ++j) {
-        const int b = row[j];
-        if (b < 0) break;
-        attend_range_bwd(r, qs, gb, dss, l, dl, scale, Ks, Vs, bv.slc_start[b], bv.slc_start[b + 1], Hkv, g, d);
-      }
+// dgates, the row scalars and dQ of all three branches for 16 columns.
+template <typename T, int DT>
+__global__ __launch_bounds__(64 * NW) void g_bwd_dq(DqArgs a) {
+  extern __shared__ unsigned ids[];
+  __shared__ float part[NW][16][16 * DT + 4];
+  __shared__ int scol[16];
+  const int g = blockIdx.y, wid = threadIdx.x >> 6, n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, stride = a.Hkv * a.d;
+  const Cols c = columns(a.bv, a.hs, g, blockIdx.x);
+  if (threadIdx.x < 16) scol[threadIdx.x] = c.valid ? c.tok * a.Hq + c.h : -1;
+  const int tpt = tokens_per_tile(a.hs), pos0 = (int)blockIdx.x / tiles_per_token(a.hs) * tpt;
+  UnionEntry *un;
+  const int n_un = build_union(a.bv, a.idx, a.Hkv, a.T, g, pos0, min(tpt, a.bv.N - pos0), tpt * a.T, ids, un);
+  const size_t th = (size_t)c.tok * a.Hq + c.h, NH = (size_t)a.bv.N * a.Hq;
+  f4 q[DT], go[DT];
+  ld_row<T, DT>((const T *)a.Q + th * a.d, a.d, c.valid, q);
+  ld_row<T, DT>((const T *)a.dO + th * a.d, a.d, c.valid, go);
+  RowInfo ri[3];
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    f4 ob[DT];
+    ld_row<T, DT>((const T *)a.Ob + (b * NH + th) * a.d, a.d, c.valid, ob);
+    float dot = 0.f;
+#pragma unroll
+    for (int s = 0; s < DT; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dot += go[s][i] * ob[s][i];
+    dot = quad_sum(dot);
+    const float w = io<T>::ld((const T *)a.gates + th * 3 + b), l2 = a.lse[b * NH + th] * LOG2E_F;
+    ri[b] = RowInfo{c.valid ? l2 : INFINITY, w * dot, w};
+    if (wid == b && quad == 0 && c.valid) {  // (NW >= 3 wavefronts share the columns)
+      io<T>::st((T *)a.dgates + th * 3 + b, dot);
+      a.info[b * NH + th] = f4{l2, w * dot, w, 0.f};
     }
   }
-  if (lane < d) io<T>::st(dQ + th * d + lane, r.dq0);
-  if (lane + WAVE < d) io<T>::st(dQ + th * d + lane + WAVE, r.dq1);
-}
-
-// dK, dV of one key row (sorted token, or compression block when `pooled`) and KV head: key-centric, so that every sum
-// runs in one fixed order and no floating-point atomic is needed (results are the same from run to run).  The queries
-// that attend the key: for a token, the tokens of its window (window branch), then the tokens whose selected sets hold
-// its selection block, in ascending sorted position (selection branch; lists from the inverse selection index); for a
-// compression block, every token of its batch item.  64 query rows (token x head of the group) at a time: each lane
-// forms its row's probability and dS, then the lanes, now standing for output dims, add the 64 contributions in order.
-template <typename T>
-__global__ void g_attn_bwd_dkv(int pooled, const T *__restrict__ Q, const T *__restrict__ dO, const T *__restrict__ gates,
-                               BlkView bv, const int32_t *__restrict__ tok_slc, const int32_t *__restrict__ item_start,
-                               const int32_t *__restrict__ sel_start, const int32_t *__restrict__ sel_list, int N, int B,
-                               int Ns, int Hq, int Hkv, int d, float scale, const float *__restrict__ Kr,
-                               const float *__restrict__ Vr, const float *__restrict__ lse,
-                               const float *__restrict__ delta, float *__restrict__ dK, float *__restrict__ dV) {
-  __shared__ float ks[128], vs[128], ps[WAVE], dss[WAVE];
-  __shared__ size_t qth[WAVE];
-  const int key = blockIdx.x, g = blockIdx.y, hs = Hq / Hkv, lane = threadIdx.x;
-  const size_t krow = ((size_t)key * Hkv + g) * d;
-  for (int i = lane; i < d; i += WAVE) {
-    ks[i] = Kr[krow + i];
-    vs[i] = Vr[krow + i];
+  f4 dq[DT];
+#pragma unroll
+  for (int b = 0; b < DT; ++b) dq[b] = f4{0.f, 0.f, 0.f, 0.f};
+  int k0, k1;
+  {
+    const int item = a.bv.tok_item[c.pos], lo = c.valid ? a.bv.cmp_batch[item] : 0, hi = c.valid ? a.bv.cmp_batch[item + 1] : 0;
+    union_range(lo, hi, c.valid, k0, k1);
+    attend_bwd<DT>(dq, q, go, ri[0], RangeWalk(k0, k1, lo, hi, wid, NW), a.Kc + g * a.d, a.Vc + g * a.d, stride, a.d, a.sl2, a.scale);
   }
+  const float *Kg = a.Ks + g * a.d, *Vg = a.Vs + g * a.d;
+  attend_bwd<DT>(dq, q, go, ri[1], UnionWalk(un, n_un, c.slot, c.valid, wid, NW), Kg, Vg, stride, a.d, a.sl2, a.scale);
+  {
+    const int win = a.bv.tok_win[c.pos], lo = c.valid ? a.bv.win_start[win] : 0, hi = c.valid ? a.bv.win_start[win + 1] : 0;
+    union_range(lo, hi, c.valid, k0, k1);
+    attend_bwd<DT>(dq, q, go, ri[2], RangeWalk(k0, k1, lo, hi, wid, NW), Kg, Vg, stride, a.d, a.sl2, a.scale);
+  }
+  acc_put<DT>(part[wid][n], dq);
   __syncthreads();
-  float dk0 = 0.f, dk1 = 0.f, dv0 = 0.f, dv1 = 0.f;
-  const size_t NH = (size_t)N * Hq;
-  // queries e = 0 .. count*hs-1: token number e / hs of the list, head g*hs + e % hs
-  auto run = [&](int branch, const int32_t *list, int first, int count) {
-    for (int e0 = 0; e0 < count * hs; e0 += WAVE) {
-      const int e = e0 + lane;
-      float p = 0.f, ds = 0.f;
-      size_t th = 0;
-      if (e < count * hs) {
-        const int pos = list ? list[first + e / hs] : first + e / hs;
-        th = (size_t)bv.perm[pos] * Hq + g * hs + e % hs;
-        const float w = io<T>::ld(gates + th * 3 + branch);
-        float s = 0.f, dp = 0.f;
-        for (int i = 0; i < d; ++i) {
-          s += io<T>::ld(Q + th * d + i) * ks[i];
-          dp += io<T>::ld(dO + th * d + i) * vs[i];
-        }
-        const float pr = __expf(s * scale - lse[branch * NH + th]);
-        ds = pr * (w * dp - delta[branch * NH + th]) * scale;
-        p = pr * w;
-      }
-      ps[lane] = p;
-      dss[lane] = ds;
-      qth[lane] = th;
-      __syncthreads();
-      const int n = min(WAVE, count * hs - e0);
-      for (int kk = 0; kk < n; ++kk) {
-        const size_t row = qth[kk] * d;
-        if (lane < d) {
-          dv0 += ps[kk] * io<T>::ld(dO + row + lane);
-          dk0 += dss[kk] * io<T>::ld(Q + row + lane);
-        }
-        if (lane + WAVE < d) {
-          dv1 += ps[kk] * io<T>::ld(dO + row + lane + WAVE);
-          dk1 += dss[kk] * io<T>::ld(Q + row + lane + WAVE);
-        }
-      }
-      __syncthreads();
-    }
-  };
-  if (pooled) {
-    int item = 0;
-    while (item + 1 < B && key >= bv.cmp_batch[item + 1]) ++item;
-    run(0, nullptr, item_start[item], item_start[item + 1] - item_start[item]);
-  } else {
-    const int w = bv.tok_win[key];
-    run(2, nullptr, bv.win_start[w], bv.win_start[w + 1] - bv.win_start[w]);
-    const int sk = g * Ns + tok_slc[key];
-    run(1, sel_list, sel_start[sk], sel_start[sk + 1] - sel_start[sk]);
+  const int col = threadIdx.x >> 4, ch = (threadIdx.x & 15) * DT, to = scol[col];
+  if (to < 0 || ch >= a.d) return;
+  float r[DT];
+#pragma unroll
+  for (int b = 0; b < DT; ++b) {
+    r[b] = part[0][col][ch + b];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) r[b] += part[w][col][ch + b];
   }
-  if (lane < d) { dK[krow + lane] = dk0; dV[krow + lane] = dv0; }
-  if (lane + WAVE < d) { dK[krow + lane + WAVE] = dk1; dV[krow + lane + WAVE] = dv1; }
+  st_chunk<DT>((T *)a.dQ + (size_t)to * a.d + ch, r);
 }
 
-// dK[tok] = dKs[pos] + dKc[cmp(pos)] / count (gradient of the mean pool), scattered back to caller order.
+// dK, dV of 16 keys of one KV head: the query rows (token x head of the group) that attend to them in tiles of 16, dealt out
+// to the wavefronts.  Three kinds of workgroup in one launch:
+//   window:      16 consecutive sorted tokens; queries: the tokens of their windows;
+//   selection:   16 tokens of one selection block; queries: a chunk of the block's selector list;
+//   compression: 16 pooled keys; queries: one part of their items' tokens.
+struct DkvArgs {
+  const void *Q, *dO;
+  BlkView bv;
+  int Hq, Hkv, hs, d;
+  float scale, sl2;
+  const float *Ks, *Vs, *Kc, *Vc;
+  const f4 *info;
+  const int32_t *sel_start, *sel_list, *chunk_start, *part_row_start;
+  const ChunkRef *chunk_order;
+  int chunk_len, slc_tiles, cmp_splits;
+  int n_win, n_slc;              // workgroups of the first two kinds
+  float *dKs, *dVs, *pK, *pV, *dKc, *dVc;  // window part [N][Hkv][d]; selection partials [rows][d]; [splits][Nc][Hkv][d]
+};
+
+template <typename T, int DT>
+__global__ __launch_bounds__(64 * nw_key<DT>()) void g_bwd_dkv(DkvArgs a) {
+  constexpr int NW_KEY = nw_key<DT>();
+  __shared__ float part[NW_KEY / 2][2][16][16 * DT + 4];
+  const int wid = threadIdx.x >> 6, n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, stride = a.Hkv * a.d;
+  int g, branch, key0, kend, q0, q1, qlo, qhi;  // q: token indices (sorted positions, or places in the list)
+  const int32_t *list = nullptr;
+  const float *Kr = a.Ks, *Vr = a.Vs;
+  float *oK, *oV;     // row of key0
+  int ostride;
+  int wg = blockIdx.x;
+  if (wg < a.n_win) {
+    branch = 2;
+    g = wg % a.Hkv;
+    key0 = wg / a.Hkv * 16;
+    kend = a.bv.N;
+    const int w = a.bv.tok_win[min(key0 + n, kend - 1)];
+    qlo = a.bv.win_start[w];
+    qhi = a.bv.win_start[w + 1];
+    union_range(qlo, qhi, true, q0, q1);
+    oK = a.dKs + (size_t)key0 * stride + g * a.d;
+    oV = a.dVs + (size_t)key0 * stride + g * a.d;
+    ostride = stride;
+  } else if ((wg -= a.n_win) < a.n_slc) {
+    branch = 1;
+    const int ci = wg / a.slc_tiles, tile = wg % a.slc_tiles;
+    if (ci >= a.chunk_start[a.Hkv * a.bv.Ns]) return;
+    const ChunkRef cr = a.chunk_order[ci];
+    g = cr.key / a.bv.Ns;
+    const int blk = cr.key % a.bv.Ns, kbeg = a.bv.slc_start[blk];
+    kend = a.bv.slc_start[blk + 1];
+    key0 = kbeg + 16 * tile;
+    if (key0 >= kend) return;
+    list = a.sel_list;
+    q0 = qlo = a.sel_start[cr.key] + cr.chunk * a.chunk_len;
+    q1 = qhi = min(a.sel_start[cr.key + 1], q0 + a.chunk_len);
+    const size_t row = (size_t)a.part_row_start[cr.key] + (size_t)cr.chunk * (kend - kbeg) + (key0 - kbeg);
+    oK = a.pK + row * a.d;
+    oV = a.pV + row * a.d;
+    ostride = a.d;
+  } else {
+    wg -= a.n_slc;
+    branch = 0;
+    const int sp = wg % a.cmp_splits;
+    wg /= a.cmp_splits;
+    g = wg % a.Hkv;
+    key0 = wg / a.Hkv * 16;
+    kend = a.bv.Nc;
+    const int item = a.bv.tok_item[a.bv.cmp_start[min(key0 + n, kend - 1)]];
+    qlo = a.bv.item_start[item];
+    qhi = a.bv.item_start[item + 1];
+    union_range(qlo, qhi, true, q0, q1);
+    const int per = (q1 - q0 + a.cmp_splits - 1) / a.cmp_splits;
+    q0 = min(q1, q0 + sp * per);
+    q1 = min(q1, q0 + per);
+    Kr = a.Kc;
+    Vr = a.Vc;
+    oK = a.dKc + ((size_t)sp * a.bv.Nc + key0) * stride + g * a.d;
+    oV = a.dVc + ((size_t)sp * a.bv.Nc + key0) * stride + g * a.d;
+    ostride = stride;
+  }
+  const bool key_on = key0 + n < kend;
+  f4 k[DT], v[DT];
+  {
+    const size_t r = (size_t)min(key0 + n, kend - 1) * stride + g * a.d;
+    ld_row<float, DT>(Kr + r, a.d, key_on, k);
+    ld_row<float, DT>(Vr + r, a.d, key_on, v);
+  }
+  f4 dk[DT], dv[DT];
+#pragma unroll
+  for (int b = 0; b < DT; ++b) dk[b] = dv[b] = f4{0.f, 0.f, 0.f, 0.f};
+  const int ne = (q1 - q0) * a.hs;
+  const f4 *info = a.info + (size_t)branch * a.bv.N * a.Hq;
+  const T *Q = (const T *)a.Q, *dO = (const T *)a.dO;
+  const int c = n * DT < a.d ? n * DT : 0;
+  // element e of the walk: token q0 + e / h_s, head e % h_s.  A lane follows element 16*wid + n, + 16*NW_KEY, ... (token
+  // and head advance by constants); th: its row of the caller's tensors, ql: its token index, both clamped past the end.
+  const int dt_ = 16 * NW_KEY / a.hs, dh = 16 * NW_KEY - dt_ * a.hs;
+  int tq = (16 * wid + n) / a.hs, hd = 16 * wid + n - tq * a.hs;
+  auto row_of = [&](int t) { return a.bv.perm[list ? list[t] : t] * a.Hq + g * a.hs + hd; };
+  int th = ne > 0 ? row_of(min(q0 + tq, q1 - 1)) : 0, ql = q0 + tq;
+  for (int e0 = 16 * wid; e0 < ne; e0 += 16 * NW_KEY) {
+    f4 qr[DT], gr[DT];
+    const int rows = th, qls = ql;  // lane n's row; the rows 4*quad + i of the second product are those of lanes 4*quad + i
+#pragma unroll
+    for (int s = 0; s < DT; ++s) {
+      const int dim = 16 * s + 4 * quad < a.d ? 16 * s + 4 * quad : 0;
+      qr[s] = ld4(Q + (size_t)rows * a.d + dim);
+      gr[s] = ld4(dO + (size_t)rows * a.d + dim);
+    }
+    float qt[4][DT], gt[4][DT];
+    f4 inf[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = __shfl(rows, 4 * quad + i);
+      inf[i] = info[r];
+      ld_chunk<DT>(Q + (size_t)r * a.d + c, qt[i]);
+      ld_chunk<DT>(dO + (size_t)r * a.d + c, gt[i]);
+    }
+    tq += dt_;
+    hd += dh;
+    if (hd >= a.hs) { hd -= a.hs; ++tq; }
+    ql = q0 + tq;
+    if (e0 + 16 * NW_KEY < ne) th = row_of(min(ql, q1 - 1));
+    const f4 s = dot16<DT>(qr, k), dp = dot16<DT>(gr, v);  // rows: query rows 4*quad + i, column: key n
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int qi = __shfl(qls, 4 * quad + i);
+      const bool on = qi < q1 && qi >= qlo && qi < qhi;
+      const float p = on ? __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.sl2, -inf[i][0])) : 0.f;
+      const float ds = p * (inf[i][2] * dp[i] - inf[i][1]) * a.scale, pw = p * inf[i][2];
+#pragma unroll
+      for (int b = 0; b < DT; ++b) {
+        dv[b] = mfma4(gt[i][b], pw, dv[b]);
+        dk[b] = mfma4(qt[i][b], ds, dk[b]);
+      }
+    }
+  }
+  // sums of the wavefronts in a fixed tree: the upper half hands its sums to the lower half, and so on
+  for (int h = NW_KEY / 2; h >= 1; h /= 2) {
+    if (wid >= h && wid < 2 * h) {
+      acc_put<DT>(part[wid - h][0][n], dk);
+      acc_put<DT>(part[wid - h][1][n], dv);
+    }
+    __syncthreads();
+    if (wid < h) {
+      acc_add<DT>(part[wid][0][n], dk);
+      acc_add<DT>(part[wid][1][n], dv);
+    }
+    __syncthreads();
+  }
+  if (wid != 0 || !key_on) return;
+  acc_put<DT>(oK + (size_t)n * ostride, dk, a.d);
+  acc_put<DT>(oV + (size_t)n * ostride, dv, a.d);
+}
+
+// dK[tok] = window part + the selection chunks in order + (the compression splits in order) / count (gradient of the mean
+// pool), scattered back to caller order.  One thread per (sorted position, 4 elements of the row).
+struct FinishArgs {
+  BlkView bv;
+  int Hkv, d, splits;
+  const int32_t *chunk_start, *part_row_start;
+  const float *dKs, *dVs, *pK, *pV, *dKc, *dVc;
+  void *dK, *dV;
+};
 template <typename T>
-__global__ void g_unpool_scatter(BlkView bv, size_t N, int row, const float *__restrict__ dKs,
-                                 const float *__restrict__ dVs, const float *__restrict__ dKc,
-                                 const float *__restrict__ dVc, T *__restrict__ dK, T *__restrict__ dV) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N * row) return;
-  const size_t pos = i / row;
-  const int f = (int)(i % row);
-  const int c = bv.tok_cmp[pos];
-  const float inv = 1.0f / (float)(bv.cmp_start[c + 1] - bv.cmp_start[c]);
-  const size_t dst = (size_t)bv.perm[pos] * row + f;
-  io<T>::st(dK + dst, dKs[i] + dKc[(size_t)c * row + f] * inv);
-  io<T>::st(dV + dst, dVs[i] + dVc[(size_t)c * row + f] * inv);
+__global__ __launch_bounds__(256) void g_bwd_finish(FinishArgs a) {
+  const int row = a.Hkv * a.d, per = row / 4;
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (size_t)a.bv.N * per) return;
+  const int pos = (int)(i / per), f = (int)(i % per) * 4, g = f / a.d, dim = f % a.d;
+  f4 k = ld4(a.dKs + (size_t)pos * row + f), v = ld4(a.dVs + (size_t)pos * row + f);
+  const int b = a.bv.tok_slc[pos], key = g * a.bv.Ns + b, klen = a.bv.slc_start[b + 1] - a.bv.slc_start[b];
+  const int nch = a.chunk_start[key + 1] - a.chunk_start[key];
+  const size_t r0 = (size_t)a.part_row_start[key] + (pos - a.bv.slc_start[b]);
+#pragma unroll 4
+  for (int c = 0; c < nch; ++c) {
+    const size_t off = (r0 + (size_t)c * klen) * a.d + dim;
+    k += ld4(a.pK + off);
+    v += ld4(a.pV + off);
+  }
+  const int cb = a.bv.tok_cmp[pos];
+  const float inv = 1.0f / (float)(a.bv.cmp_start[cb + 1] - a.bv.cmp_start[cb]);
+  f4 ck = {0.f, 0.f, 0.f, 0.f}, cv = ck;
+#pragma unroll 4
+  for (int s = 0; s < a.splits; ++s) {
+    const size_t off = ((size_t)s * a.bv.Nc + cb) * row + f;
+    ck += ld4(a.dKc + off);
+    cv += ld4(a.dVc + off);
+  }
+  const size_t dst = (size_t)a.bv.perm[pos] * row + f;
+  st4((T *)a.dK + dst, k + ck * inv);
+  st4((T *)a.dV + dst, v + cv * inv);
 }
 
 struct GenericPlan {
-  size_t ks, vs, kc, vc, ob, lse, idx, delta, dks, dvs, dkc, dvc, sel, total;
+  size_t ks, vs, kc, vc, ob, lse, idx, info, dks, dvs, pk, pv, dkc, dvc, sel, total;
+  int chunk_len, max_chunks, splits;
 };
 
 GenericPlan plan(const ssa_ctx &c, bool bwd) {
   GenericPlan p{};
+  const ssa_blocks *b = c.blk;
   const size_t esz = c.dtype == SSA_F32 ? 4 : 2;
   const size_t kv = align_up((size_t)c.N * c.Hkv * c.d * 4 + 4, 256);
-  const size_t kvc = align_up((size_t)c.blk->Nc * c.Hkv * c.d * 4 + 4, 256);
+  const size_t kvc = align_up((size_t)b->Nc * c.Hkv * c.d * 4 + 4, 256);
   size_t off = 0;
   auto take = [&](size_t n) { size_t r = off; off += align_up(n, 256); return r; };
   p.ks = take(kv); p.vs = take(kv); p.kc = take(kvc); p.vc = take(kvc);
@@ -388,70 +879,103 @@ GenericPlan plan(const ssa_ctx &c, bool bwd) {
     p.lse = take((size_t)3 * c.N * c.Hq * 4 + 4);
     p.idx = take((size_t)c.N * c.Hkv * c.T * 4 + 4);
   } else {
-    p.delta = take((size_t)3 * c.N * c.Hq * 4 + 4);
-    p.dks = take(kv); p.dvs = take(kv); p.dkc = take(kvc); p.dvc = take(kvc);
-    p.sel = take(sel_index_bytes(c.N, c.Hkv, c.T, c.blk->Ns));
+    p.info = take((size_t)3 * c.N * c.Hq * 16);
+    p.dks = take(kv); p.dvs = take(kv);
+    // selection lists are cut into chunks whose partial dK, dV are added in order; chunks grow until the partial sums fit in
+    // about 1 GiB (rows <= slc_tok_max * full chunks + one partly filled chunk per key)
+    const size_t entries = (size_t)c.N * c.Hkv * c.T, keys = (size_t)c.Hkv * b->Ns;
+    size_t rows;
+    for (p.chunk_len = 256;; p.chunk_len *= 2) {
+      rows = (size_t)b->slc_tok_max * (entries / p.chunk_len + 1) + (size_t)c.N * c.Hkv;
+      if (rows * c.d * 8 <= ((size_t)1 << 30) || p.chunk_len >= (1 << 20)) break;
+    }
+    p.max_chunks = (int)(entries / p.chunk_len + keys + 1);
+    p.pk = take(rows * c.d * 4); p.pv = take(rows * c.d * 4);
+    // compression branch: the query range in parts, so that about 512 workgroups share it, of 128 query rows or more
+    const long long wgs = (long long)((b->Nc + 15) / 16) * c.Hkv, most = (long long)c.N * c.hs / 128 + 1;
+    long long sp = (512 + wgs - 1) / (wgs > 0 ? wgs : 1);
+    sp = sp > most ? most : sp;
+    p.splits = (int)(sp < 1 ? 1 : sp > 64 ? 64 : sp);
+    p.dkc = take(kvc * p.splits); p.dvc = take(kvc * p.splits);
+    p.sel = take(sel_index_bytes(c.N, c.Hkv, c.T, b->Ns));
   }
   p.total = off;
   return p;
 }
 
-size_t scores_lds_bytes(const ssa_ctx &c) {
-  return ((size_t)c.blk->s_max + (size_t)c.hs * c.d + c.hs + ((size_t)c.blk->s_max + 31) / 32 + 4) * 4;
+// Tokens per workgroup of the score kernel: a tile's worth, fewer where their score rows would not fit the LDS.
+int score_tokens(const ssa_ctx &c) {
+  int tw = tokens_per_tile(c.hs);
+  while (tw > 1 && score_lds_bytes(tw, c.blk->s_max) > 64 * 1024) tw /= 2;
+  return tw;
 }
 
-template <typename T>
+template <typename T, int DT>
 int forward_t(const ssa_ctx &c, const void *q, const void *k, const void *v, const void *gates, void *out, float *lse,
               int32_t *topk_idx, void *out_branch, char *ws) {
   const GenericPlan p = plan(c, false);
   const BlkView bv = view_of(c.blk);
   float *Ks = (float *)(ws + p.ks), *Vs = (float *)(ws + p.vs), *Kc = (float *)(ws + p.kc), *Vc = (float *)(ws + p.vc);
-  T *Ob = out_branch ? (T *)out_branch : (T *)(ws + p.ob);
+  void *Ob = out_branch ? out_branch : (void *)(ws + p.ob);
   float *L = lse ? lse : (float *)(ws + p.lse);
   int32_t *I = topk_idx ? topk_idx : (int32_t *)(ws + p.idx);
-  const int N = c.N, row = c.Hkv * c.d;
-  if (scores_lds_bytes(c) > 60000) return SSA_ERR_UNSUPPORTED;
-  g_sort_pool<T><<<c.blk->Nc, 256, 0, c.stream>>>((const T *)k, (const T *)v, bv, row, Ks, Vs, Kc, Vc);
-  g_attn_fwd<T><<<N * c.Hq, WAVE, 0, c.stream>>>(0, (const T *)q, bv, nullptr, N, c.Hq, c.Hkv, c.d, c.T, c.scale, Kc, Vc, Ob, L);
-  g_scores_topk<T><<<N * c.Hkv, WAVE, scores_lds_bytes(c), c.stream>>>((const T *)q, bv, N, c.Hq, c.Hkv, c.d, c.T, c.scale, Kc, L, I,
-                                                                      c.blk->s_max);
-  g_attn_fwd<T><<<N * c.Hq, WAVE, 0, c.stream>>>(1, (const T *)q, bv, I, N, c.Hq, c.Hkv, c.d, c.T, c.scale, Ks, Vs, Ob, L);
-  g_attn_fwd<T><<<N * c.Hq, WAVE, 0, c.stream>>>(2, (const T *)q, bv, nullptr, N, c.Hq, c.Hkv, c.d, c.T, c.scale, Ks, Vs, Ob, L);
-  const size_t total = (size_t)N * c.Hq * c.d;
-  g_combine<T><<<(unsigned)((total + 255) / 256), 256, 0, c.stream>>>(Ob, (const T *)gates, (size_t)N, c.Hq, c.d, (T *)out);
+  const int tw = score_tokens(c), tpt = tokens_per_tile(c.hs);
+  const size_t lds = score_lds_bytes(tw, c.blk->s_max);
+  if (lds > 150 * 1024) return SSA_ERR_UNSUPPORTED;
+  static std::once_flag once;
+  std::call_once(once, [] {
+    (void)hipFuncSetAttribute((const void *)g_scores_topk<T, DT>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  });
+  const float sl2 = c.scale * LOG2E_F;
+  const dim3 grid((unsigned)((c.N + tpt - 1) / tpt * tiles_per_token(c.hs)), c.Hkv);
+  g_sort_pool<T><<<c.blk->Nc, 256, 0, c.stream>>>((const T *)k, (const T *)v, bv, c.Hkv * c.d, Ks, Vs, Kc, Vc);
+  FwdArgs a{q, gates, bv, I, c.Hq, c.Hkv, c.hs, c.d, c.T, sl2, Kc, Vc, Ob, out, L};
+  g_cmp_fwd<T, DT><<<grid, 64 * NW, 0, c.stream>>>(a);
+  ScoreArgs sa{q, bv, Kc, L, I, c.Hq, c.Hkv, c.hs, c.d, c.T, tw, c.blk->s_max, sl2};
+  g_scores_topk<T, DT><<<dim3((c.N + tw - 1) / tw, c.Hkv), 64 * NW, lds, c.stream>>>(sa);
+  a.K = Ks; a.V = Vs;
+  g_slc_win_fwd<T, DT><<<grid, 64 * NW, union_lds_bytes(tpt, c.T), c.stream>>>(a);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
-template <typename T>
+template <typename T, int DT>
 int backward_t(const ssa_ctx &c, const void *q, const void *k, const void *v, const void *gates, const void *out_branch,
                const float *lse, const int32_t *topk_idx, const void *dout, void *dq, void *dk, void *dv, void *dgates,
                char *ws) {
   const GenericPlan p = plan(c, true);
   const BlkView bv = view_of(c.blk);
   float *Ks = (float *)(ws + p.ks), *Vs = (float *)(ws + p.vs), *Kc = (float *)(ws + p.kc), *Vc = (float *)(ws + p.vc);
-  float *delta = (float *)(ws + p.delta);
+  f4 *info = (f4 *)(ws + p.info);
   float *dKs = (float *)(ws + p.dks), *dVs = (float *)(ws + p.dvs), *dKc = (float *)(ws + p.dkc), *dVc = (float *)(ws + p.dvc);
-  const int N = c.N, row = c.Hkv * c.d;
+  float *pK = (float *)(ws + p.pk), *pV = (float *)(ws + p.pv);
+  const int tpt = tokens_per_tile(c.hs), row = c.Hkv * c.d;
+  const float sl2 = c.scale * LOG2E_F;
+  const dim3 grid((unsigned)((c.N + tpt - 1) / tpt * tiles_per_token(c.hs)), c.Hkv);
   g_sort_pool<T><<<c.blk->Nc, 256, 0, c.stream>>>((const T *)k, (const T *)v, bv, row, Ks, Vs, Kc, Vc);
-  g_bwd_pre<T><<<N * c.Hq, WAVE, 0, c.stream>>>((const T *)dout, (const T *)out_branch, (const T *)gates, (size_t)N, c.Hq, c.d,
-                                                (T *)dgates, delta);
-  g_attn_bwd_dq<T><<<N * c.Hq, WAVE, 0, c.stream>>>((const T *)q, (const T *)dout, (const T *)gates, bv, topk_idx, N, c.Hq, c.Hkv,
-                                                    c.d, c.T, c.scale, Ks, Vs, Kc, Vc, lse, delta, (T *)dq);
-  const SelIndex sel = sel_index_carve(ws + p.sel, N, c.Hkv, c.T, c.blk->Ns, 1024, 1024);
-  const int rc = sel_index_build(topk_idx, c.blk->perm, c.blk->slc_start, N, c.Hkv, c.T, c.blk->Ns, sel, false, false, c.stream);
+  DqArgs a{q, dout, out_branch, gates, bv, topk_idx, c.Hq, c.Hkv, c.hs, c.d, c.T, c.scale, sl2, Ks, Vs, Kc, Vc, lse, dq, dgates, info};
+  g_bwd_dq<T, DT><<<grid, 64 * NW, union_lds_bytes(tpt, c.T), c.stream>>>(a);
+  const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, BC_CHUNK);
+  const int rc = sel_index_build(topk_idx, c.blk->perm, c.blk->slc_start, c.N, c.Hkv, c.T, c.blk->Ns, sel, false, true, c.stream);
   if (rc != SSA_OK) return rc;
-  g_attn_bwd_dkv<T><<<dim3(N, c.Hkv), WAVE, 0, c.stream>>>(0, (const T *)q, (const T *)dout, (const T *)gates, bv, c.blk->tok_slc,
-                                                          c.blk->item_start, sel.start, sel.list, N, c.B, c.blk->Ns, c.Hq, c.Hkv,
-                                                          c.d, c.scale, Ks, Vs, lse, delta, dKs, dVs);
-  g_attn_bwd_dkv<T><<<dim3(c.blk->Nc, c.Hkv), WAVE, 0, c.stream>>>(1, (const T *)q, (const T *)dout, (const T *)gates, bv,
-                                                                  c.blk->tok_slc, c.blk->item_start, sel.start, sel.list, N, c.B,
-                                                                  c.blk->Ns, c.Hq, c.Hkv, c.d, c.scale, Kc, Vc, lse, delta, dKc,
-                                                                  dVc);
-  const size_t total = (size_t)N * row;
-  g_unpool_scatter<T><<<(unsigned)((total + 255) / 256), 256, 0, c.stream>>>(bv, (size_t)N, row, dKs, dVs, dKc, dVc, (T *)dk,
-                                                                            (T *)dv);
+  DkvArgs b{q, dout, bv, c.Hq, c.Hkv, c.hs, c.d, c.scale, sl2, Ks, Vs, Kc, Vc, info, sel.start, sel.list, sel.chunk_start,
+            sel.part_row_start, sel.order, sel.chunk_len, (c.blk->slc_tok_max + 15) / 16, p.splits, 0, 0, dKs, dVs, pK, pV, dKc, dVc};
+  b.n_win = (c.N + 15) / 16 * c.Hkv;
+  b.n_slc = p.max_chunks * b.slc_tiles;
+  const int n_cmp = (c.blk->Nc + 15) / 16 * c.Hkv * p.splits;
+  g_bwd_dkv<T, DT><<<b.n_win + b.n_slc + n_cmp, 64 * nw_key<DT>(), 0, c.stream>>>(b);
+  FinishArgs f{bv, c.Hkv, c.d, p.splits, sel.chunk_start, sel.part_row_start, dKs, dVs, pK, pV, dKc, dVc, dk, dv};
+  const size_t items = (size_t)c.N * row / 4;
+  g_bwd_finish<T><<<(unsigned)((items + 255) / 256), 256, 0, c.stream>>>(f);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
+
+// blocks of 16 dims a row is padded to in the registers
+#define SSA_GENERIC_DISPATCH(fn, ...)                                                                  \
+  (c.dtype == SSA_F32                                                                                  \
+       ? (c.d <= 16 ? fn<float, 1>(__VA_ARGS__) : c.d <= 32 ? fn<float, 2>(__VA_ARGS__)                \
+          : c.d <= 64 ? fn<float, 4>(__VA_ARGS__) : fn<float, 8>(__VA_ARGS__))                         \
+       : (c.d <= 16 ? fn<uint16_t, 1>(__VA_ARGS__) : c.d <= 32 ? fn<uint16_t, 2>(__VA_ARGS__)          \
+          : c.d <= 64 ? fn<uint16_t, 4>(__VA_ARGS__) : fn<uint16_t, 8>(__VA_ARGS__)))
 
 }  // namespace
 
@@ -463,9 +987,7 @@ int generic_forward(const ssa_ctx &c, const void *q, const void *k, const void *
   if (ws_bytes < plan(c, false).total) return SSA_ERR_WORKSPACE;
   if (c.N == 0) return SSA_OK;
   ProfScope ps(PROF_GENERIC, c.stream);
-  return c.dtype == SSA_F32
-             ? forward_t<float>(c, q, k, v, gates, out, lse, topk_idx, out_branch, (char *)ws)
-             : forward_t<uint16_t>(c, q, k, v, gates, out, lse, topk_idx, out_branch, (char *)ws);
+  return SSA_GENERIC_DISPATCH(forward_t, c, q, k, v, gates, out, lse, topk_idx, out_branch, (char *)ws);
 }
 
 int generic_backward(const ssa_ctx &c, const void *q, const void *k, const void *v, const void *gates,
@@ -474,9 +996,7 @@ int generic_backward(const ssa_ctx &c, const void *q, const void *k, const void 
   if (ws_bytes < plan(c, true).total) return SSA_ERR_WORKSPACE;
   if (c.N == 0) return SSA_OK;
   ProfScope ps(PROF_GENERIC, c.stream);
-  return c.dtype == SSA_F32
-             ? backward_t<float>(c, q, k, v, gates, out_branch, lse, topk_idx, dout, dq, dk, dv, dgates, (char *)ws)
-             : backward_t<uint16_t>(c, q, k, v, gates, out_branch, lse, topk_idx, dout, dq, dk, dv, dgates, (char *)ws);
+  return SSA_GENERIC_DISPATCH(backward_t, c, q, k, v, gates, out_branch, lse, topk_idx, dout, dq, dk, dv, dgates, (char *)ws);
 }
 
 int launch_topk_from_scores(const ssa_ctx &c, const float *scores, int32_t *topk_idx) {
@@ -484,7 +1004,7 @@ int launch_topk_from_scores(const ssa_ctx &c, const float *scores, int32_t *topk
   const int s_max = c.blk->s_max;
   const size_t lds = ((size_t)s_max + ((size_t)s_max + 31) / 32 + 4) * 4;
   if (lds > 60000) return SSA_ERR_UNSUPPORTED;
-  g_topk_from_scores<<<c.N * c.Hkv, WAVE, lds, c.stream>>>(scores, view_of(c.blk), c.N, c.Hkv, c.T, s_max, c.blk->inv_perm,
+  g_topk_from_scores<<<c.N * c.Hkv, WAVE, lds, c.stream>>>(scores, view_of(c.blk), c.Hkv, c.T, s_max, c.blk->inv_perm,
                                                           topk_idx);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
