@@ -6,13 +6,24 @@
 // aligned cube is a contiguous run of the Morton order): key = (batch item << 3*bits) | Morton(x,y,z).
 // Integer work only; results are bit-exact and independent of scheduling (stable LSD radix sort, no
 // order-dependent atomics).
+//
+// Bound: launch latency (62k tokens are 0.7 MB in, 3 MB out: a microsecond of memory time), so the work is cut into as few
+// dependent launches as possible: 11-bit digits (two passes up to 22 key bits instead of three), the key kernel counts the
+// first digit, every scatter workgroup forms its own offsets from the tile histograms (about 32 tiles below 256k tokens, a
+// tile taking 1..16 keys per thread), the last scatter writes straight into the handle, and the kernel that finds the
+// maxima hands the counts to the host through pinned memory.  Seven launches instead of 18 plus four copies; with the
+// allocations kept (see DevicePool), a build of 62k tokens, its arrays read out and destroyed: 228 -> 112 us (two thirds of it on the host).
 #include "ssa_internal.h"
+
+#include <mutex>
+#include <vector>
 
 namespace {
 
-constexpr int SORT_TILE = 256;  // one key per thread, 4 wavefronts per workgroup
+constexpr int SORT_THREADS = 512, SORT_WAVES = SORT_THREADS / 64;
+constexpr int DIGIT_BITS_MAX = 11, BINS_MAX = 1 << DIGIT_BITS_MAX;
 
-enum { META_ERR = 0, META_NC, META_NS, META_NW, META_SMAX, META_CMAX, META_SLC_TOK, META_WIN_TOK, META_CMP_TOK, META_N };
+enum { META_ERR = 0, META_NC, META_NS, META_NW, META_SMAX, META_CMAX, META_SLC_TOK, META_WIN_TOK, META_CMP_TOK, META_N, META_DONE = META_N, META_INTS };
 
 // Spread the low 10 bits of v so that bit i lands on bit 3i.
 __device__ inline uint32_t spread3(uint32_t v) {
@@ -24,39 +35,70 @@ __device__ inline uint32_t spread3(uint32_t v) {
   return v;
 }
 
-__global__ void k_make_keys(const int32_t *__restrict__ coords, const int32_t *__restrict__ offs, int N, int B, int G,
-                            int bits, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, int32_t *meta) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  for (int j = i; j <= B; j += gridDim.x * blockDim.x) {
-    const int o = offs[j];
-    const bool bad = (j == 0 && o != 0) || (j == B && o != N) || (j > 0 && o < offs[j - 1]) || o < 0 || o > N;
-    if (bad) atomicOr(&meta[META_ERR], 1);
-  }
-  if (i >= N) return;
-  int lo = 0, hi = B;  // offs[lo] <= i < offs[hi] for valid offsets
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (offs[mid] <= i) lo = mid; else hi = mid;
-  }
-  int x = coords[3 * i], y = coords[3 * i + 1], z = coords[3 * i + 2];
-  if ((unsigned)x >= (unsigned)G || (unsigned)y >= (unsigned)G || (unsigned)z >= (unsigned)G) {
-    atomicOr(&meta[META_ERR], 2);
-    x = y = z = 0;
-  }
-  const uint64_t code = (uint64_t)((spread3((uint32_t)x) << 2) | (spread3((uint32_t)y) << 1) | spread3((uint32_t)z));
-  keys[i] = ((uint64_t)lo << (3 * bits)) | code;
-  vals[i] = (uint32_t)i;
+// A tile is SORT_THREADS * R consecutive keys; wavefront w of its workgroup owns keys 64*R*w .., R rounds of 64.
+template <int R>
+__device__ inline int tile_key(int round) {
+  return blockIdx.x * (SORT_THREADS * R) + (threadIdx.x >> 6) * (64 * R) + round * 64 + (threadIdx.x & 63);
 }
 
-// Per-tile digit histogram, stored digit-major so that one linear scan yields the scatter offsets.
-__global__ void k_sort_hist(const uint64_t *__restrict__ keys, int N, int shift, int nTiles, uint32_t *__restrict__ hist) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
+// Keys of all tokens and the tile histograms of the first digit (hist[tile][digit]).  err[tile]: bit 0 bad batch offsets,
+// bit 1 a coordinate out of range.  Workgroup 0 clears the maxima.
+template <int R>
+__global__ __launch_bounds__(SORT_THREADS) void k_keys_hist(const int32_t *__restrict__ coords, const int32_t *__restrict__ offs,
+                                                            int N, int B, int G, int bits, int dbits, uint64_t *__restrict__ keys,
+                                                            uint32_t *__restrict__ hist, int32_t *__restrict__ err, int32_t *meta) {
+  __shared__ uint32_t h[BINS_MAX];
+  __shared__ int bad_any;
+  const int nb = 1 << dbits;
+  for (int i = threadIdx.x; i < nb; i += SORT_THREADS) h[i] = 0;
+  if (threadIdx.x == 0) bad_any = 0;
+  if (blockIdx.x == 0 && threadIdx.x < META_INTS) meta[threadIdx.x] = 0;
   __syncthreads();
-  const int i = blockIdx.x * SORT_TILE + threadIdx.x;
-  if (i < N) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & 255u], 1u);
+  int bad_bits = 0;
+  for (int j = blockIdx.x * SORT_THREADS + threadIdx.x; j <= B; j += gridDim.x * SORT_THREADS) {
+    const int o = offs[j];
+    if ((j == 0 && o != 0) || (j == B && o != N) || (j > 0 && o < offs[j - 1]) || o < 0 || o > N) bad_bits |= 1;
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = tile_key<R>(r);
+    if (i >= N) continue;
+    int lo = 0, hi = B;  // offs[lo] <= i < offs[hi] for valid offsets
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (offs[mid] <= i) lo = mid; else hi = mid;
+    }
+    int x = coords[3 * i], y = coords[3 * i + 1], z = coords[3 * i + 2];
+    if ((unsigned)x >= (unsigned)G || (unsigned)y >= (unsigned)G || (unsigned)z >= (unsigned)G) {
+      bad_bits |= 2;
+      x = y = z = 0;
+    }
+    const uint64_t code = (uint64_t)((spread3((uint32_t)x) << 2) | (spread3((uint32_t)y) << 1) | spread3((uint32_t)z));
+    const uint64_t key = ((uint64_t)lo << (3 * bits)) | code;
+    keys[i] = key;
+    atomicAdd(&h[(uint32_t)key & (uint32_t)(nb - 1)], 1u);
+  }
+  if (bad_bits) atomicOr(&bad_any, bad_bits);
   __syncthreads();
-  hist[threadIdx.x * nTiles + blockIdx.x] = h[threadIdx.x];
+  for (int i = threadIdx.x; i < nb; i += SORT_THREADS) hist[(size_t)blockIdx.x * nb + i] = h[i];
+  if (threadIdx.x == 0) err[blockIdx.x] = bad_any;
+}
+
+// Tile histograms of a later digit.
+template <int R>
+__global__ __launch_bounds__(SORT_THREADS) void k_sort_hist(const uint64_t *__restrict__ keys, int N, int shift, int dbits,
+                                                            uint32_t *__restrict__ hist) {
+  __shared__ uint32_t h[BINS_MAX];
+  const int nb = 1 << dbits;
+  for (int i = threadIdx.x; i < nb; i += SORT_THREADS) h[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = tile_key<R>(r);
+    if (i < N) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & (uint32_t)(nb - 1)], 1u);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < nb; i += SORT_THREADS) hist[(size_t)blockIdx.x * nb + i] = h[i];
 }
 
 // Exclusive prefix sum over the `n` threads of a workgroup (n <= 1024 a multiple of 64): returns the sum of v over the
@@ -82,76 +124,115 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t *part, uint
   return base + inc - v;
 }
 
-// Scatter offsets of one radix pass from the digit-major tile histogram hist[digit][tile]: workgroup d turns row d
-// into its exclusive prefix over the tiles (in place) and leaves the row total in totals[d] ...
-__global__ __launch_bounds__(256) void k_scan_rows(uint32_t *hist, int nTiles, uint32_t *totals) {
-  __shared__ uint32_t part[5];
-  uint32_t *row = hist + (size_t)blockIdx.x * nTiles;
-  uint32_t carry = 0;
-  for (int t0 = 0; t0 < nTiles; t0 += 256) {
-    const int t = t0 + threadIdx.x;
-    const uint32_t v = t < nTiles ? row[t] : 0u;
-    uint32_t all;
-    const uint32_t ex = block_exclusive_scan(v, part, &all);
-    if (t < nTiles) row[t] = carry + ex;
-    carry += all;
-  }
-  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
-}
-// ... and one workgroup turns the 256 digit totals into the digits' base offsets.
-__global__ __launch_bounds__(256) void k_scan_totals(uint32_t *totals) {
-  __shared__ uint32_t part[5];
-  const uint32_t v = totals[threadIdx.x];
-  const uint32_t ex = block_exclusive_scan(v, part, nullptr);
-  totals[threadIdx.x] = ex;
-}
-
-// Stable scatter of one 8-bit digit: rank inside the wavefront by ballot matching, wavefronts in order.
-__global__ void k_sort_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
-                               uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int N, int shift, int nTiles,
-                               const uint32_t *__restrict__ offs, const uint32_t *__restrict__ digit_base) {
-  __shared__ uint32_t wcnt[SORT_TILE / 64][256];
-  for (int w = 0; w < SORT_TILE / 64; ++w) wcnt[w][threadIdx.x] = 0;
-  __syncthreads();
-  const int i = blockIdx.x * SORT_TILE + threadIdx.x;
-  const bool valid = i < N;
-  const uint64_t key = valid ? kin[i] : 0ull;
-  const uint32_t digit = (uint32_t)(key >> shift) & 255u;
-  uint64_t peers = __ballot(valid);
+// Stable scatter of one digit.  The workgroup sums the tile histograms into its offset per digit (keys of smaller digits +
+// keys of this digit in earlier tiles); inside the tile a key's rank is the count of its digit in earlier wavefronts
+// (16-bit counters per wavefront, turned into prefixes) plus its rank inside its wavefront by ballot matching.
+// vin == NULL: the values are the positions themselves (first pass).
+static_assert(BINS_MAX / 4 <= SORT_THREADS, "a thread serves four digits");
+constexpr size_t SCATTER_LDS = (size_t)SORT_WAVES * BINS_MAX * 2 + BINS_MAX * 4 + 32 * 4;
+template <int R>
+__global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
+                                                               uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int N,
+                                                               int shift, int dbits, int nTiles, const uint32_t *__restrict__ hist) {
+  extern __shared__ uint32_t sort_smem[];
+  const int nb = 1 << dbits, half = nb / 2, quarter = nb / 4, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint32_t *wcnt = sort_smem;                              // [SORT_WAVES][nb/2] packed pairs of 16-bit counters
+  uint32_t *offs = wcnt + SORT_WAVES * half;               // [nb]
+  uint32_t *part = offs + nb;
+  uint64_t key[R];
+  uint32_t val[R];
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const bool bit = (digit >> b) & 1u;
-    const uint64_t m = __ballot(bit);
-    peers &= bit ? m : ~m;
+  for (int r = 0; r < R; ++r) {
+    const int i = tile_key<R>(r);
+    key[r] = i < N ? kin[i] : 0ull;
+    val[r] = i < N ? (vin ? vin[i] : (uint32_t)i) : 0u;
   }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const uint32_t rank = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
-  if (valid && rank == 0) wcnt[w][digit] = (uint32_t)__popcll(peers);
+  for (int i = tid; i < SORT_WAVES * half; i += SORT_THREADS) wcnt[i] = 0u;
+  // thread t < nb/4 serves digits 4t .. 4t+3
+  uint32_t before[4] = {0u, 0u, 0u, 0u}, all[4] = {0u, 0u, 0u, 0u};
+  if (tid < quarter) {
+    const uint4 *row = reinterpret_cast<const uint4 *>(hist) + tid;
+    for (int t0 = 0; t0 < nTiles; t0 += 16) {  // 16 loads in flight, whatever the remainder
+      uint4 x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = row[(size_t)min(t0 + u, nTiles - 1) * quarter];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int t = t0 + u;
+        const uint32_t c[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          all[j] += t < nTiles ? c[j] : 0u;
+          before[j] += t < (int)blockIdx.x ? c[j] : 0u;
+        }
+      }
+    }
+  }
+  uint32_t ex = block_exclusive_scan(all[0] + all[1] + all[2] + all[3], part, nullptr);
+  if (tid < quarter) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      offs[4 * tid + j] = ex + before[j];
+      ex += all[j];
+    }
+  }
   __syncthreads();
-  if (valid) {
-    uint32_t pos = digit_base[digit] + offs[digit * nTiles + blockIdx.x] + rank;
-    for (int ww = 0; ww < w; ++ww) pos += wcnt[ww][digit];
-    kout[pos] = key;
-    vout[pos] = vin[i];
+  uint16_t *mine = reinterpret_cast<uint16_t *>(wcnt + w * half);
+  uint32_t rank[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool valid = tile_key<R>(r) < N;
+    const uint32_t digit = (uint32_t)(key[r] >> shift) & (uint32_t)(nb - 1);
+    uint64_t peers = __ballot(valid);
+    for (int b = 0; b < dbits; ++b) {
+      const bool bit = (digit >> b) & 1u;
+      const uint64_t m = __ballot(bit);
+      peers &= bit ? m : ~m;
+    }
+    const uint32_t below = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull)), base = mine[digit];
+    rank[r] = base + below;
+    __builtin_amdgcn_wave_barrier();
+    if (valid && below == 0) mine[digit] = (uint16_t)(base + __popcll(peers));
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  if (tid < quarter) {
+    uint2 c[SORT_WAVES], run = make_uint2(0u, 0u);
+#pragma unroll
+    for (int ww = 0; ww < SORT_WAVES; ++ww) c[ww] = *reinterpret_cast<const uint2 *>(wcnt + ww * half + 2 * tid);
+#pragma unroll
+    for (int ww = 0; ww < SORT_WAVES; ++ww) {
+      *reinterpret_cast<uint2 *>(wcnt + ww * half + 2 * tid) = run;
+      run.x += c[ww].x;  // (no 16-bit half reaches 2^16: a tile has at most 8192 keys)
+      run.y += c[ww].y;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (tile_key<R>(r) >= N) continue;
+    const uint32_t digit = (uint32_t)(key[r] >> shift) & (uint32_t)(nb - 1);
+    const uint32_t pos = offs[digit] + mine[digit] + rank[r];
+    kout[pos] = key[r];
+    vout[pos] = val[r];
   }
 }
 
 struct CsrOut {
   int32_t *perm, *inv_perm, *tok_item, *tok_cmp, *tok_slc, *tok_win;
-  int32_t *cmp_start, *slc_start, *win_start, *slc_child_start, *cmp_slc, *cmp_batch, *slc_batch;
+  int32_t *cmp_start, *slc_start, *win_start, *slc_child_start, *cmp_slc, *cmp_batch, *slc_batch, *item_start;
 };
 
 // Block ids are running counts of block heads (a token whose key prefix differs from its predecessor's) at the three
-// granularities.  Three launches: per-tile head counts, their prefix over the tiles (one small workgroup), then every
-// tile numbers its own tokens and writes all per-token and per-block arrays.
-constexpr int CSR_TILE = 256;
+// granularities.  Two launches: per-tile head counts, then every tile sums the counts before it, numbers its own tokens
+// and writes all per-token and per-block arrays.
+constexpr int CSR_TILE = 512;
 struct Heads { bool c, s, w; };
 
 // Where the blocks begin and which item a sorted position belongs to, for the two kinds of partition.
 // Voxel grid: sorted (item << item_shift | Morton) keys; a block of side m is a change of the key above 3*log2(m) bits.
 struct GridSrc {
   const uint64_t *ks;
-  const uint32_t *vals;  // sorted position -> caller index
   int sc, ss, sw, item_shift;
   __device__ Heads heads(int i) const {
     const uint64_t k = ks[i], p = i == 0 ? 0ull : ks[i - 1];
@@ -159,7 +240,7 @@ struct GridSrc {
     return Heads{first || (k >> sc) != (p >> sc), first || (k >> ss) != (p >> ss), first || (k >> sw) != (p >> sw)};
   }
   __device__ int item(int i) const { return (int)(ks[i] >> item_shift); }
-  __device__ int32_t source(int i) const { return (int32_t)vals[i]; }
+  __device__ int32_t source(int i, const int32_t *perm) const { return perm[i]; }  // written by the sort
 };
 // Sequences: the caller's order is the token order; blocks are runs of lc / ls / lw tokens counted from the start of
 // each sequence (the last one of a sequence may be shorter).
@@ -178,7 +259,7 @@ struct SeqSrc {
     const int pos = i - offs[item(i)];
     return Heads{pos % lc == 0, pos % ls == 0, pos % lw == 0};
   }
-  __device__ int32_t source(int i) const { return i; }
+  __device__ int32_t source(int i, int32_t *perm) const { return perm[i] = i; }
 };
 
 template <class Src>
@@ -199,39 +280,29 @@ __global__ __launch_bounds__(CSR_TILE) void k_csr_count(Src src, int N, int nTil
   if (threadIdx.x < 3) tile_cnt[threadIdx.x * nTiles + blockIdx.x] = cnt[threadIdx.x];
 }
 
-// Exclusive prefix of the three count rows over the tiles (in place); one workgroup.
-__global__ __launch_bounds__(256) void k_csr_scan(uint32_t *tile_cnt, int nTiles) {
-  __shared__ uint32_t part[5];
-  for (int x = 0; x < 3; ++x) {
-    uint32_t *row = tile_cnt + (size_t)x * nTiles;
-    uint32_t carry = 0;
-    for (int t0 = 0; t0 < nTiles; t0 += 256) {
-      const int t = t0 + threadIdx.x;
-      const uint32_t v = t < nTiles ? row[t] : 0u;
-      uint32_t all;
-      const uint32_t ex = block_exclusive_scan(v, part, &all);
-      if (t < nTiles) row[t] = carry + ex;
-      carry += all;
-    }
-  }
-}
-
 template <class Src>
-__global__ __launch_bounds__(CSR_TILE) void k_csr_write(Src src, int N, int B, int nTiles,
-                                                        const uint32_t *__restrict__ tile_base, CsrOut o, int32_t *meta) {
-  __shared__ uint32_t part[5];
+__global__ __launch_bounds__(CSR_TILE) void k_csr_write(Src src, int N, int B, int nTiles, const int32_t *__restrict__ offs,
+                                                        const uint32_t *__restrict__ tile_cnt, CsrOut o, int32_t *meta) {
+  __shared__ uint32_t part[CSR_TILE / 64 + 1];
   const int i = blockIdx.x * CSR_TILE + threadIdx.x;
+  for (int j = i; j <= B; j += gridDim.x * CSR_TILE) o.item_start[j] = offs[j];
   Heads h{false, false, false};
   if (i < N) h = src.heads(i);
-  // inclusive head counts up to and including token i
-  const int idc = (int)(tile_base[blockIdx.x] + block_exclusive_scan(h.c, part, nullptr) + h.c) - 1;
-  const int ids = (int)(tile_base[nTiles + blockIdx.x] + block_exclusive_scan(h.s, part, nullptr) + h.s) - 1;
-  const int idw = (int)(tile_base[2 * nTiles + blockIdx.x] + block_exclusive_scan(h.w, part, nullptr) + h.w) - 1;
+  // inclusive head counts up to and including token i: heads of earlier tiles + heads of this tile
+  uint32_t base[3];
+#pragma unroll
+  for (int x = 0; x < 3; ++x) {
+    uint32_t c = 0;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += CSR_TILE) c += tile_cnt[x * nTiles + t];
+    (void)block_exclusive_scan(c, part, &base[x]);
+  }
+  const int idc = (int)(base[0] + block_exclusive_scan(h.c, part, nullptr) + h.c) - 1;
+  const int ids = (int)(base[1] + block_exclusive_scan(h.s, part, nullptr) + h.s) - 1;
+  const int idw = (int)(base[2] + block_exclusive_scan(h.w, part, nullptr) + h.w) - 1;
   if (i >= N) return;
   const int item = src.item(i);
   const int pitem = i == 0 ? -1 : src.item(i - 1);
-  const int32_t from = src.source(i);
-  o.perm[i] = from;
+  const int32_t from = src.source(i, o.perm);
   o.inv_perm[from] = i;
   o.tok_item[i] = item;
   o.tok_cmp[i] = idc;
@@ -258,45 +329,175 @@ __global__ void k_check_offsets(const int32_t *__restrict__ offs, int N, int B, 
   }
 }
 
-// Largest per-item block counts and per-block token counts (integer max: order independent).
-__global__ void k_maxima(CsrOut o, int B, int32_t *meta) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int Nc = meta[META_NC], Ns = meta[META_NS], Nw = meta[META_NW];
-  if (i < B) {
-    atomicMax(&meta[META_SMAX], o.slc_batch[i + 1] - o.slc_batch[i]);
-    atomicMax(&meta[META_CMAX], o.cmp_batch[i + 1] - o.cmp_batch[i]);
+// Largest per-item block counts and per-block token counts (integer max: order independent), then the counts to the host:
+// the workgroup that finishes last copies them (and the error bits of the tiles) into pinned memory.
+constexpr int MAX_THREADS = 512;
+__global__ __launch_bounds__(MAX_THREADS) void k_maxima(CsrOut o, int B, const int32_t *__restrict__ err, int n_err, int32_t *meta,
+                                                        int32_t *host_meta) {
+  __shared__ int best[5], last;
+  if (threadIdx.x < 5) best[threadIdx.x] = 0;
+  __syncthreads();
+  const int Nc = meta[META_NC], Ns = meta[META_NS], Nw = meta[META_NW], i0 = blockIdx.x * MAX_THREADS + threadIdx.x;
+  const int stride = gridDim.x * MAX_THREADS;
+  int m[5] = {0, 0, 0, 0, 0};  // in the order META_SMAX .. META_CMP_TOK
+  for (int i = i0; i < B; i += stride) {
+    m[0] = max(m[0], o.slc_batch[i + 1] - o.slc_batch[i]);
+    m[1] = max(m[1], o.cmp_batch[i + 1] - o.cmp_batch[i]);
   }
-  if (i < Nc) atomicMax(&meta[META_CMP_TOK], o.cmp_start[i + 1] - o.cmp_start[i]);
-  if (i < Ns) atomicMax(&meta[META_SLC_TOK], o.slc_start[i + 1] - o.slc_start[i]);
-  if (i < Nw) atomicMax(&meta[META_WIN_TOK], o.win_start[i + 1] - o.win_start[i]);
+  for (int i = i0; i < Ns; i += stride) m[2] = max(m[2], o.slc_start[i + 1] - o.slc_start[i]);
+  for (int i = i0; i < Nw; i += stride) m[3] = max(m[3], o.win_start[i + 1] - o.win_start[i]);
+  for (int i = i0; i < Nc; i += stride) m[4] = max(m[4], o.cmp_start[i + 1] - o.cmp_start[i]);
+#pragma unroll
+  for (int x = 0; x < 5; ++x) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m[x] = max(m[x], __shfl_xor(m[x], off));
+    if ((threadIdx.x & 63) == 0) atomicMax(&best[x], m[x]);
+  }
+  __syncthreads();
+  // (device-scope atomics meet in memory; their returned values are waited for, so they are done before META_DONE counts
+  // this workgroup, without a fence that would write back the caches)
+  if (threadIdx.x < 5) {
+    const int old = atomicMax(&meta[META_SMAX + threadIdx.x], best[threadIdx.x]);
+    asm volatile("" : : "v"(old));
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) last = atomicAdd(&meta[META_DONE], 1) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  int e = 0;
+  for (int i = threadIdx.x; i < n_err; i += MAX_THREADS) e |= err[i];
+  if (e) {
+    const int old = atomicOr(&meta[META_ERR], e);
+    asm volatile("" : : "v"(old));
+  }
+  __syncthreads();
+  if (threadIdx.x < META_N) host_meta[threadIdx.x] = atomicAdd(&meta[threadIdx.x], 0);
+}
+
+// Read-out of one index array (a launch costs less than a runtime copy of this size).
+__global__ __launch_bounds__(256) void k_copy(const int32_t *__restrict__ src, size_t n, int32_t *__restrict__ dst) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
+}
+
+// Device memory of destroyed handles and of the build's scratch, kept for the next build: hipMalloc and hipFree cost more
+// than the kernels of a small build.  At most 64 MiB in 16 blocks; what does not fit is freed at once, and everything kept is
+// given back when an allocation fails.  A block enters only when no work can still use it, so any stream or thread may
+// take it.
+class DevicePool {
+ public:
+  static DevicePool &get() {
+    static DevicePool *p = new DevicePool();  // never destroyed: the runtime may be gone when static destructors run
+    return *p;
+  }
+  // bytes is rounded up; *got receives the size to hand back to give()
+  void *take(int device, size_t bytes, size_t *got) {
+    bytes = align_up(bytes, bytes < ((size_t)1 << 20) ? (size_t)1 << 16 : (size_t)1 << 20);
+    {
+      std::lock_guard<std::mutex> l(mu_);
+      size_t best = blocks_.size();
+      for (size_t i = 0; i < blocks_.size(); ++i)
+        if (blocks_[i].device == device && blocks_[i].bytes >= bytes && blocks_[i].bytes <= 4 * bytes &&
+            (best == blocks_.size() || blocks_[i].bytes < blocks_[best].bytes))
+          best = i;
+      if (best < blocks_.size()) {
+        void *p = blocks_[best].p;
+        *got = blocks_[best].bytes;
+        total_ -= *got;
+        blocks_.erase(blocks_.begin() + (long)best);
+        return p;
+      }
+    }
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      release();
+      if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    }
+    *got = bytes;
+    return p;
+  }
+  void give(int device, void *p, size_t bytes) {
+    {
+      std::lock_guard<std::mutex> l(mu_);
+      if (blocks_.size() < 16 && total_ + bytes <= ((size_t)64 << 20)) {
+        blocks_.push_back(Block{p, bytes, device});
+        total_ += bytes;
+        return;
+      }
+    }
+    (void)hipFree(p);
+  }
+
+ private:
+  struct Block { void *p; size_t bytes; int device; };
+  void release() {
+    std::lock_guard<std::mutex> l(mu_);
+    for (const Block &b : blocks_) (void)hipFree(b.p);
+    blocks_.clear();
+    total_ = 0;
+  }
+  std::mutex mu_;
+  std::vector<Block> blocks_;
+  size_t total_ = 0;
+};
+
+// Pinned slots through which the kernels hand their counts to the host (one per build in progress).
+class PinnedSlots {
+ public:
+  static PinnedSlots &get() {
+    static PinnedSlots *p = new PinnedSlots();
+    return *p;
+  }
+  int32_t *take() {
+    std::lock_guard<std::mutex> l(mu_);
+    if (free_.empty()) {
+      void *p = nullptr;
+      if (hipHostMalloc(&p, SLOT_INTS * 4 * 32, hipHostMallocPortable) != hipSuccess) return nullptr;
+      for (int i = 0; i < 32; ++i) free_.push_back((int32_t *)p + i * SLOT_INTS);
+    }
+    int32_t *s = free_.back();
+    free_.pop_back();
+    return s;
+  }
+  void give(int32_t *s) {
+    std::lock_guard<std::mutex> l(mu_);
+    free_.push_back(s);
+  }
+
+ private:
+  static constexpr int SLOT_INTS = 32;
+  static_assert(META_INTS <= SLOT_INTS, "a slot holds the counts");
+  std::mutex mu_;
+  std::vector<int32_t *> free_;
+};
+
+// Kernels of the sort for R keys per thread.  k1: second key array; the sorted keys end in kdst, the caller indices in vdst.
+template <int R>
+void launch_sort(const int32_t *coords, const int32_t *offs, int N, int B, int G, int bits, int total_bits, uint64_t *k0, uint64_t *k1,
+                 uint32_t *v1, uint64_t *kdst, uint32_t *vdst, uint32_t *hist, int32_t *err, int32_t *meta, int nTiles, hipStream_t s) {
+  static std::once_flag once;
+  std::call_once(once, [] {
+    (void)hipFuncSetAttribute((const void *)k_sort_scatter<R>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCATTER_LDS);
+  });
+  const int passes = (total_bits + DIGIT_BITS_MAX - 1) / DIGIT_BITS_MAX;
+  const int dbits = (total_bits + passes - 1) / passes;
+  const size_t lds = ((size_t)SORT_WAVES * 2 + 4) * ((size_t)1 << dbits) + 32 * 4;
+  k_keys_hist<R><<<nTiles, SORT_THREADS, 0, s>>>(coords, offs, N, B, G, bits, dbits, k0, hist, err, meta);
+  uint64_t *kin = k0, *kalt = k1;
+  uint32_t *vin = nullptr, *valt = v1, *vspare = v1 + N;
+  for (int p = 0; p < passes; ++p) {
+    const bool final = p == passes - 1;
+    uint64_t *ko = final ? kdst : kalt;
+    uint32_t *vo = final ? vdst : valt;
+    if (p > 0) k_sort_hist<R><<<nTiles, SORT_THREADS, 0, s>>>(kin, N, p * dbits, dbits, hist);
+    k_sort_scatter<R><<<nTiles, SORT_THREADS, lds, s>>>(kin, vin, ko, vo, N, p * dbits, dbits, nTiles, hist);
+    kalt = kin;
+    kin = ko;
+    vin = vo;
+    uint32_t *t = valt; valt = vspare; vspare = t;
+  }
 }
 
 }  // namespace
-
-// Stable LSD radix sort of n (key, value) pairs by the low `bits` bits of the keys, 8 bits per pass, ping-ponging between
-// (k0, v0) and (k1, v1); `aux` holds sort_pairs_aux_bytes(n) bytes.  Returns 0 when the sorted pairs end in (k0, v0),
-// 1 when they end in (k1, v1).  Four launches per pass on `stream`, no allocation, no synchronisation.
-size_t sort_pairs_aux_bytes(int n) {
-  const int nTiles = (n + SORT_TILE - 1) / SORT_TILE;
-  return align_up((size_t)256 * (nTiles > 0 ? nTiles : 1) * 4, 256) + 256 * 4;
-}
-int sort_pairs(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, void *aux, int n, int bits, hipStream_t stream) {
-  const int nTiles = (n + SORT_TILE - 1) / SORT_TILE;
-  uint32_t *hist = (uint32_t *)aux;
-  uint32_t *digit_base = (uint32_t *)((char *)aux + align_up((size_t)256 * (nTiles > 0 ? nTiles : 1) * 4, 256));
-  int where = 0;
-  if (n <= 0) return where;
-  for (int shift = 0; shift < bits; shift += 8) {
-    k_sort_hist<<<nTiles, SORT_TILE, 0, stream>>>(k0, n, shift, nTiles, hist);
-    k_scan_rows<<<256, 256, 0, stream>>>(hist, nTiles, digit_base);
-    k_scan_totals<<<1, 256, 0, stream>>>(digit_base);
-    k_sort_scatter<<<nTiles, SORT_TILE, 0, stream>>>(k0, v0, k1, v1, n, shift, nTiles, hist, digit_base);
-    uint64_t *tk = k0; k0 = k1; k1 = tk;
-    uint32_t *tv = v0; v0 = v1; v1 = tv;
-    where ^= 1;
-  }
-  return where;
-}
 
 // Common part of the two builders: grid_mode = voxel partition (sort by Morton key), else sequences in caller order.
 static int build_handle(const ssa_params_t *p, const int32_t *coords, const int32_t *batch_offsets, bool grid_mode,
@@ -304,7 +505,7 @@ static int build_handle(const ssa_params_t *p, const int32_t *coords, const int3
   const int N = p->n_tokens, B = p->n_batch;
   int bits = 1;
   while ((1 << bits) < p->grid) ++bits;
-  int item_bits = 1;
+  int item_bits = 0;
   while ((1ll << item_bits) < (long long)B) ++item_bits;
 
   ssa_blocks *h = new ssa_blocks();
@@ -312,9 +513,11 @@ static int build_handle(const ssa_params_t *p, const int32_t *coords, const int3
   h->bits = grid_mode ? bits : 0;
   h->dims = grid_mode ? 3 : 1;
   if (hipGetDevice(&h->device) != hipSuccess) { delete h; return SSA_ERR_HIP; }
+  DevicePool &pool = DevicePool::get();
   const size_t n1 = (size_t)N + 1;
   const size_t ints = 2 * (size_t)N + 6 * (size_t)N + 4 * n1 + (size_t)N + 3 * ((size_t)B + 1) + 64;
-  if (hipMalloc(&h->base, ints * sizeof(int32_t)) != hipSuccess) { delete h; return SSA_ERR_HIP; }
+  h->base = pool.take(h->device, ints * sizeof(int32_t), &h->bytes);
+  if (!h->base) { delete h; return SSA_ERR_HIP; }
   int32_t *w = (int32_t *)h->base;
   auto take = [&](size_t n) { int32_t *r = w; w += n; return r; };
   h->sorted_keys = (uint64_t *)take(2 * (size_t)N);  // first: the allocation's alignment serves the 8-byte keys
@@ -323,87 +526,84 @@ static int build_handle(const ssa_params_t *p, const int32_t *coords, const int3
   h->slc_child_start = take(n1); h->cmp_slc = take(N); h->cmp_batch = take(B + 1); h->slc_batch = take(B + 1);
   h->item_start = take(B + 1);
 
-  int32_t meta_h[META_N] = {0};
-  const int nTiles = (N + SORT_TILE - 1) / SORT_TILE;
-  void *tmp = nullptr;
-  const size_t key_b = align_up((size_t)N * 8, 256), val_b = align_up((size_t)N * 4, 256);
-  const size_t hist_b = align_up((size_t)256 * (nTiles > 0 ? nTiles : 1) * 4, 256);
-  const int csrTiles = (N + CSR_TILE - 1) / CSR_TILE;
-  const size_t aux_b = align_up((size_t)(256 + 3 * (csrTiles > 0 ? csrTiles : 1)) * 4, 256);  // digit bases | CSR tile counts
-  const size_t tmp_bytes = (grid_mode ? 2 * key_b + 2 * val_b + hist_b : 0) + aux_b + 256;
+  // keys per thread of the sort: about 32 tiles, whose histograms every scatter workgroup reads (16 and 64 tiles: +2, +3 %)
+  int R = 1;
+  while (R < 16 && (long long)N > 32ll * SORT_THREADS * R) R *= 2;
+  const int nTiles = N > 0 ? (N + SORT_THREADS * R - 1) / (SORT_THREADS * R) : 1;
+  const int csrTiles = N > 0 ? (N + CSR_TILE - 1) / CSR_TILE : 1;
+  const size_t key_b = align_up((size_t)N * 8, 256), val_b = align_up((size_t)2 * N * 4, 256);
+  const size_t hist_b = align_up((size_t)BINS_MAX * nTiles * 4, 256), err_b = align_up((size_t)nTiles * 4, 256);
+  const size_t cnt_b = align_up((size_t)3 * csrTiles * 4, 256);
+  const size_t tmp_bytes = (grid_mode ? 2 * key_b + val_b + hist_b : 0) + err_b + cnt_b + 256;
+  size_t tmp_got = 0;
+  void *tmp = pool.take(h->device, tmp_bytes, &tmp_got);
+  int32_t *host_meta = PinnedSlots::get().take();
+  // nothing goes back to the pools while the stream may still use it
   auto fail = [&](int code) {
-    if (tmp) (void)hipFree(tmp);
-    (void)hipFree(h->base);
+    const bool idle = hipStreamSynchronize(stream) == hipSuccess;
+    if (tmp) { if (idle) pool.give(h->device, tmp, tmp_got); else (void)hipFree(tmp); }
+    if (idle) pool.give(h->device, h->base, h->bytes); else (void)hipFree(h->base);
+    if (host_meta && idle) PinnedSlots::get().give(host_meta);
     delete h;
     return code;
   };
-  if (hipMalloc(&tmp, tmp_bytes) != hipSuccess) return fail(SSA_ERR_HIP);
+  if (!tmp || !host_meta) return fail(SSA_ERR_HIP);
   char *tp = (char *)tmp;
-  uint64_t *k0 = nullptr, *k1 = nullptr;
-  uint32_t *v0 = nullptr, *v1 = nullptr, *hist = nullptr;
-  if (grid_mode) {
-    k0 = (uint64_t *)tp; tp += key_b;
-    k1 = (uint64_t *)tp; tp += key_b;
-    v0 = (uint32_t *)tp; tp += val_b;
-    v1 = (uint32_t *)tp; tp += val_b;
-    hist = (uint32_t *)tp; tp += hist_b;
-  }
-  uint32_t *digit_base = (uint32_t *)tp, *tile_cnt = digit_base + 256; tp += aux_b;
-  int32_t *meta = (int32_t *)tp;
-  if (hipMemsetAsync(meta, 0, 256, stream) != hipSuccess) return fail(SSA_ERR_HIP);
+  auto tmp_take = [&](size_t n) { char *r = tp; tp += n; return r; };
+  int32_t *err = (int32_t *)tmp_take(err_b);
+  uint32_t *tile_cnt = (uint32_t *)tmp_take(cnt_b);
+  int32_t *meta = (int32_t *)tmp_take(256);
   CsrOut o{h->perm, h->inv_perm, h->tok_item, h->tok_cmp, h->tok_slc, h->tok_win, h->cmp_start, h->slc_start,
-           h->win_start, h->slc_child_start, h->cmp_slc, h->cmp_batch, h->slc_batch};
-  if (N == 0) {
-    // no tokens: every start array is a single zero; the offsets are still validated (all must be zero)
-    if (hipMemsetAsync(h->base, 0, ints * sizeof(int32_t), stream) != hipSuccess) return fail(SSA_ERR_HIP);
-    k_check_offsets<<<1, 256, 0, stream>>>(batch_offsets, 0, B, meta);
-  } else if (grid_mode) {
-    k_make_keys<<<(N + 255) / 256, 256, 0, stream>>>(coords, batch_offsets, N, B, p->grid, bits, k0, v0, meta);
-    const int total_bits = 3 * bits + item_bits;
-    for (int shift = 0; shift < total_bits; shift += 8) {
-      k_sort_hist<<<nTiles, SORT_TILE, 0, stream>>>(k0, N, shift, nTiles, hist);
-      k_scan_rows<<<256, 256, 0, stream>>>(hist, nTiles, digit_base);
-      k_scan_totals<<<1, 256, 0, stream>>>(digit_base);
-      k_sort_scatter<<<nTiles, SORT_TILE, 0, stream>>>(k0, v0, k1, v1, N, shift, nTiles, hist, digit_base);
-      uint64_t *tk = k0; k0 = k1; k1 = tk;
-      uint32_t *tv = v0; v0 = v1; v1 = tv;
-    }
-    const GridSrc src{k0, v0, 3 * ilog2_exact(p->m_cmp), 3 * ilog2_exact(p->m_slc), 3 * ilog2_exact(p->m_win), 3 * bits};
+           h->win_start, h->slc_child_start, h->cmp_slc, h->cmp_batch, h->slc_batch, h->item_start};
+  int n_err = 0;
+  auto csr = [&](auto src) {
     k_csr_count<<<csrTiles, CSR_TILE, 0, stream>>>(src, N, csrTiles, tile_cnt);
-    k_csr_scan<<<1, 256, 0, stream>>>(tile_cnt, csrTiles);
-    k_csr_write<<<csrTiles, CSR_TILE, 0, stream>>>(src, N, B, csrTiles, tile_cnt, o, meta);
-    if (hipMemcpyAsync(h->sorted_keys, k0, (size_t)N * sizeof(uint64_t), hipMemcpyDeviceToDevice, stream) != hipSuccess)
-      return fail(SSA_ERR_HIP);
-  } else {
+    k_csr_write<<<csrTiles, CSR_TILE, 0, stream>>>(src, N, B, csrTiles, batch_offsets, tile_cnt, o, meta);
+  };
+  if (!grid_mode || N == 0) {
     // The offsets are checked first and the result is read back before any kernel searches them: SeqSrc::item assumes
     // ascending offsets that start at 0 and end at N.
+    if (hipMemsetAsync(meta, 0, 256, stream) != hipSuccess) return fail(SSA_ERR_HIP);
     k_check_offsets<<<1, 256, 0, stream>>>(batch_offsets, N, B, meta);
-    if (hipMemcpyAsync(meta_h, meta, sizeof(meta_h), hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(SSA_ERR_HIP);
+    if (hipMemcpyAsync(host_meta, meta, META_N * sizeof(int32_t), hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(SSA_ERR_HIP);
     if (hipStreamSynchronize(stream) != hipSuccess) return fail(SSA_ERR_HIP);
-    if (meta_h[META_ERR] & 1) return fail(SSA_ERR_BAD_OFFSETS);
-    const SeqSrc src{batch_offsets, B, p->m_cmp, p->m_slc, p->m_win};
-    k_csr_count<<<csrTiles, CSR_TILE, 0, stream>>>(src, N, csrTiles, tile_cnt);
-    k_csr_scan<<<1, 256, 0, stream>>>(tile_cnt, csrTiles);
-    k_csr_write<<<csrTiles, CSR_TILE, 0, stream>>>(src, N, B, csrTiles, tile_cnt, o, meta);
+    if (host_meta[META_ERR] & 1) return fail(SSA_ERR_BAD_OFFSETS);
+  }
+  if (N == 0) {  // no tokens: every start array is a single zero
+    if (hipMemsetAsync(h->base, 0, ints * sizeof(int32_t), stream) != hipSuccess) return fail(SSA_ERR_HIP);
+  } else if (grid_mode) {
+    uint64_t *k0 = (uint64_t *)tmp_take(key_b), *k1 = (uint64_t *)tmp_take(key_b);
+    uint32_t *v1 = (uint32_t *)tmp_take(val_b), *hist = (uint32_t *)tmp_take(hist_b);
+    auto sort = [&](auto r) {
+      launch_sort<decltype(r)::value>(coords, batch_offsets, N, B, p->grid, bits, 3 * bits + item_bits, k0, k1, v1, h->sorted_keys,
+                                      (uint32_t *)h->perm, hist, err, meta, nTiles, stream);
+    };
+    switch (R) {
+      case 1: sort(std::integral_constant<int, 1>()); break;
+      case 2: sort(std::integral_constant<int, 2>()); break;
+      case 4: sort(std::integral_constant<int, 4>()); break;
+      case 8: sort(std::integral_constant<int, 8>()); break;
+      default: sort(std::integral_constant<int, 16>()); break;
+    }
+    n_err = nTiles;
+    csr(GridSrc{h->sorted_keys, 3 * ilog2_exact(p->m_cmp), 3 * ilog2_exact(p->m_slc), 3 * ilog2_exact(p->m_win), 3 * bits});
+  } else {
+    csr(SeqSrc{batch_offsets, B, p->m_cmp, p->m_slc, p->m_win});
     if (hipMemsetAsync(h->sorted_keys, 0, (size_t)N * sizeof(uint64_t), stream) != hipSuccess) return fail(SSA_ERR_HIP);
   }
   if (N > 0) {
-    const int span = (N > B ? N : B);
-    k_maxima<<<(span + 255) / 256, 256, 0, stream>>>(o, B, meta);
+    const int span = N > B ? N : B, wgs = (span + 4 * MAX_THREADS - 1) / (4 * MAX_THREADS);
+    k_maxima<<<wgs < 64 ? wgs : 64, MAX_THREADS, 0, stream>>>(o, B, err, n_err, meta, host_meta);
   }
-  if (hipMemcpyAsync(h->item_start, batch_offsets, ((size_t)B + 1) * sizeof(int32_t), hipMemcpyDeviceToDevice, stream) !=
-      hipSuccess)
-    return fail(SSA_ERR_HIP);
   if (hipGetLastError() != hipSuccess) return fail(SSA_ERR_HIP);
-  if (hipMemcpyAsync(meta_h, meta, sizeof(meta_h), hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(SSA_ERR_HIP);
   if (hipStreamSynchronize(stream) != hipSuccess) return fail(SSA_ERR_HIP);
-  if (meta_h[META_ERR] & 1) return fail(SSA_ERR_BAD_OFFSETS);
-  if (meta_h[META_ERR] & 2) return fail(SSA_ERR_COORD_RANGE);
-  (void)hipFree(tmp);
-  tmp = nullptr;
-  h->Nc = meta_h[META_NC]; h->Ns = meta_h[META_NS]; h->Nw = meta_h[META_NW];
-  h->s_max = meta_h[META_SMAX]; h->c_max = meta_h[META_CMAX]; h->slc_tok_max = meta_h[META_SLC_TOK];
-  h->win_tok_max = meta_h[META_WIN_TOK]; h->cmp_tok_max = meta_h[META_CMP_TOK];
+  if (host_meta[META_ERR] & 1) return fail(SSA_ERR_BAD_OFFSETS);
+  if (host_meta[META_ERR] & 2) return fail(SSA_ERR_COORD_RANGE);
+  h->Nc = host_meta[META_NC]; h->Ns = host_meta[META_NS]; h->Nw = host_meta[META_NW];
+  h->s_max = host_meta[META_SMAX]; h->c_max = host_meta[META_CMAX]; h->slc_tok_max = host_meta[META_SLC_TOK];
+  h->win_tok_max = host_meta[META_WIN_TOK]; h->cmp_tok_max = host_meta[META_CMP_TOK];
+  pool.give(h->device, tmp, tmp_got);
+  PinnedSlots::get().give(host_meta);
   *out = h;
   return SSA_OK;
 }
@@ -464,12 +664,21 @@ extern "C" int ssa_blocks_export(const ssa_blocks_t *b, int which, void *dst, si
   }
   if (bytes < n * sizeof(int32_t)) return SSA_ERR_WORKSPACE;
   if (n == 0) return SSA_OK;
-  SSA_HIP_TRY(hipMemcpyAsync(dst, src, n * sizeof(int32_t), hipMemcpyDeviceToDevice, (hipStream_t)stream));
-  return SSA_OK;
+  const size_t wgs = (n + 1023) / 1024;
+  k_copy<<<(unsigned)(wgs < 1024 ? wgs : 1024), 256, 0, (hipStream_t)stream>>>(src, n, (int32_t *)dst);
+  return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
 extern "C" void ssa_blocks_destroy(ssa_blocks_t *b) {
   if (!b) return;
-  if (b->base) (void)hipFree(b->base);
+  if (b->base) {
+    // work on any stream may still read the arrays: they are kept for the next build only once the device is idle (hipFree
+    // would wait for the same)
+    int dev = -1;
+    if (hipGetDevice(&dev) == hipSuccess && dev == b->device && hipDeviceSynchronize() == hipSuccess)
+      DevicePool::get().give(b->device, b->base, b->bytes);
+    else
+      (void)hipFree(b->base);
+  }
   delete b;
 }

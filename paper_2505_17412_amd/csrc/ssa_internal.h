@@ -27,7 +27,8 @@ struct ssa_blocks {
   int32_t cmp_tok_max;  // max tokens in one compression block
   int device;
   int dims;  // 3: voxel-grid partition (Morton order); 1: sequences in caller order (block sizes are token counts)
-  void *base;  // single device allocation holding every array below
+  void *base;  // single device allocation holding every array below, `bytes` long
+  size_t bytes;
   int32_t *perm, *inv_perm, *tok_item, *tok_cmp, *tok_slc, *tok_win;
   int32_t *cmp_start, *slc_start, *win_start, *slc_child_start, *cmp_slc, *cmp_batch, *slc_batch;
   int32_t *item_start;  // [B+1] sorted-position range of each batch item (a copy of the batch offsets)
@@ -104,7 +105,3 @@ int mfma_forward(const ssa_ctx &c, const void *q, const void *k, const void *v, 
 int mfma_backward(const ssa_ctx &c, const void *q, const void *k, const void *v, const void *gates,
                   const void *out_branch, const float *lse, const int32_t *topk_idx, const void *dout, void *dq,
                   void *dk, void *dv, void *dgates, void *ws, size_t ws_bytes);
-
-// ---- stable radix sort of (uint64 key, uint32 value) pairs: build_blocks.hip
-size_t sort_pairs_aux_bytes(int n);
-int sort_pairs(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, void *aux, int n, int bits, hipStream_t stream);

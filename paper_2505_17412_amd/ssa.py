@@ -138,11 +138,15 @@ class Blocks:
     def __init__(self, handle: int, params: ssa_params_t):
         self.handle = handle
         self.params = params
+        self._counts: Optional[Tuple[int, int, int]] = None  # fixed for the life of the handle
+        self._sizes: Optional[dict] = None
 
     def counts(self) -> Tuple[int, int, int]:
-        a, b, c = C.c_int32(), C.c_int32(), C.c_int32()
-        _check(lib().ssa_blocks_counts(self.handle, C.byref(a), C.byref(b), C.byref(c)), "ssa_blocks_counts")
-        return a.value, b.value, c.value
+        if self._counts is None:
+            a, b, c = C.c_int32(), C.c_int32(), C.c_int32()
+            _check(lib().ssa_blocks_counts(self.handle, C.byref(a), C.byref(b), C.byref(c)), "ssa_blocks_counts")
+            self._counts = a.value, b.value, c.value
+        return self._counts
 
     def max_slc_per_item(self) -> int:
         a = C.c_int32()
@@ -150,10 +154,12 @@ class Blocks:
         return a.value
 
     def export(self, name: str) -> torch.Tensor:
-        nc, ns, nw = self.counts()
-        p = self.params
-        n = dict(perm=p.n_tokens, inv_perm=p.n_tokens, cmp_start=nc + 1, slc_start=ns + 1, win_start=nw + 1,
-                 slc_child_start=ns + 1, cmp_batch=p.n_batch + 1, slc_batch=p.n_batch + 1, tok_win=p.n_tokens)[name]
+        if self._sizes is None:
+            nc, ns, nw = self.counts()
+            p = self.params
+            self._sizes = dict(perm=p.n_tokens, inv_perm=p.n_tokens, cmp_start=nc + 1, slc_start=ns + 1, win_start=nw + 1,
+                               slc_child_start=ns + 1, cmp_batch=p.n_batch + 1, slc_batch=p.n_batch + 1, tok_win=p.n_tokens)
+        n = self._sizes[name]
         dst = torch.empty(max(n, 1), dtype=torch.int32, device="cuda")
         _check(lib().ssa_blocks_export(self.handle, ARRAYS[name], dst.data_ptr(), dst.numel() * 4, _stream()),
                "ssa_blocks_export")

@@ -1,0 +1,33 @@
+"""GPU: the partition's sort at the edges of its tiles and digits, and memory kept from one handle to the next; compared bit
+for bit with the oracle's block structure."""
+import numpy as np
+import pytest
+
+from paper_2505_17412_amd import inputs
+from tests import util
+from tests.test_gpu_blocks import build_blocks, check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("seed,grid,n,m,dup", [
+    (61, 2, (8,), (1, 2, 2), False),                              # 3 key bits: one pass of the smallest digit
+    (62, 64, (16384,), (4, 8, 8), False), (63, 64, (16385,), (4, 8, 8), False),   # one and two keys per thread
+    (64, 128, (140000, 130000), (4, 8, 8), False),                # 16 keys per thread, several tiles
+    (65, 512, (40000, 0, 9), (4, 8, 16), True),                   # three passes, duplicates
+])
+def test_sort_tile_and_digit_edges(seed, grid, n, m, dup):
+    check(inputs.random_points_workload(seed, grid, n, 2, 1, 8, m, 2, allow_duplicates=dup))
+
+
+def test_kept_memory_is_safe_across_handles():
+    """Handles built and destroyed in turn (the memory of a destroyed one serves the next) hold their own arrays."""
+    wls = [inputs.random_points_workload(70 + i, 32, (500 + 37 * i, 200), 2, 1, 8, (2, 4, 8), 2) for i in range(6)]
+    alive = []
+    for rep in range(3):
+        for wl in wls:
+            check(wl)
+        alive = [util.build_blocks_gpu(wl)[1] for wl in wls[:3]]
+    for wl, blk in zip(wls[:3], alive):
+        ref = build_blocks(wl.coords, wl.batch_offsets, wl.grid, wl.m_cmp, wl.m_slc, wl.m_win)
+        assert np.array_equal(blk.export("perm").cpu().numpy(), ref.perm)
