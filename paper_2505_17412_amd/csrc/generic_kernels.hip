@@ -678,9 +678,9 @@ struct DkvArgs {
   float scale, sl2;
   const float *Ks, *Vs, *Kc, *Vc;
   const f4 *info;
-  const int32_t *sel_start, *sel_list, *chunk_start, *part_row_start;
+  const int32_t *sel_list, *chunk_start, *part_row_start;  // lists of caller indices
   const ChunkRef *chunk_order;
-  int chunk_len, slc_tiles, cmp_splits;
+  int slc_tiles, cmp_splits;
   int n_win, n_slc;              // workgroups of the first two kinds
   float *dKs, *dVs, *pK, *pV, *dKc, *dVc;  // window part [N][Hkv][d]; selection partials [rows][d]; [splits][Nc][Hkv][d]
 };
@@ -719,8 +719,8 @@ __global__ __launch_bounds__(64 * nw_key<DT>()) void g_bwd_dkv(DkvArgs a) {
     key0 = kbeg + 16 * tile;
     if (key0 >= kend) return;
     list = a.sel_list;
-    q0 = qlo = a.sel_start[cr.key] + cr.chunk * a.chunk_len;
-    q1 = qhi = min(a.sel_start[cr.key + 1], q0 + a.chunk_len);
+    q0 = qlo = cr.first;
+    q1 = qhi = cr.first + cr.count;
     const size_t row = (size_t)a.part_row_start[cr.key] + (size_t)cr.chunk * (kend - kbeg) + (key0 - kbeg);
     oK = a.pK + row * a.d;
     oV = a.pV + row * a.d;
@@ -764,7 +764,7 @@ __global__ __launch_bounds__(64 * nw_key<DT>()) void g_bwd_dkv(DkvArgs a) {
   // and head advance by constants); th: its row of the caller's tensors, ql: its token index, both clamped past the end.
   const int dt_ = 16 * NW_KEY / a.hs, dh = 16 * NW_KEY - dt_ * a.hs;
   int tq = (16 * wid + n) / a.hs, hd = 16 * wid + n - tq * a.hs;
-  auto row_of = [&](int t) { return a.bv.perm[list ? list[t] : t] * a.Hq + g * a.hs + hd; };
+  auto row_of = [&](int t) { return (list ? list[t] : a.bv.perm[t]) * a.Hq + g * a.hs + hd; };
   int th = ne > 0 ? row_of(min(q0 + tq, q1 - 1)) : 0, ql = q0 + tq;
   for (int e0 = 16 * wid; e0 < ne; e0 += 16 * NW_KEY) {
     f4 qr[DT], gr[DT];
@@ -955,10 +955,10 @@ int backward_t(const ssa_ctx &c, const void *q, const void *k, const void *v, co
   DqArgs a{q, dout, out_branch, gates, bv, topk_idx, c.Hq, c.Hkv, c.hs, c.d, c.T, c.scale, sl2, Ks, Vs, Kc, Vc, lse, dq, dgates, info};
   g_bwd_dq<T, DT><<<grid, 64 * NW, union_lds_bytes(tpt, c.T), c.stream>>>(a);
   const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, BC_CHUNK);
-  const int rc = sel_index_build(topk_idx, c.blk->perm, c.blk->slc_start, c.N, c.Hkv, c.T, c.blk->Ns, sel, false, true, c.stream);
+  const int rc = sel_index_build(topk_idx, c.blk->perm, c.blk->slc_start, c.N, c.Hkv, c.T, c.blk->Ns, sel, true, false, true, c.stream);
   if (rc != SSA_OK) return rc;
-  DkvArgs b{q, dout, bv, c.Hq, c.Hkv, c.hs, c.d, c.scale, sl2, Ks, Vs, Kc, Vc, info, sel.start, sel.list, sel.chunk_start,
-            sel.part_row_start, sel.order, sel.chunk_len, (c.blk->slc_tok_max + 15) / 16, p.splits, 0, 0, dKs, dVs, pK, pV, dKc, dVc};
+  DkvArgs b{q, dout, bv, c.Hq, c.Hkv, c.hs, c.d, c.scale, sl2, Ks, Vs, Kc, Vc, info, sel.list, sel.chunk_start,
+            sel.part_row_start, sel.order, (c.blk->slc_tok_max + 15) / 16, p.splits, 0, 0, dKs, dVs, pK, pV, dKc, dVc};
   b.n_win = (c.N + 15) / 16 * c.Hkv;
   b.n_slc = p.max_chunks * b.slc_tiles;
   const int n_cmp = (c.blk->Nc + 15) / 16 * c.Hkv * p.splits;

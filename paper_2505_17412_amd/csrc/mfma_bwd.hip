@@ -307,12 +307,13 @@ __global__ __launch_bounds__(64 * NW) void m_bwd_dkv(DkvArgs a) {
     const int per8 = 8 * a.tiles_per_block;
     const int nkeys = a.v.Hkv * a.v.Ns, wi = (int)(blockIdx.x / per8) * 8 + (int)(blockIdx.x % 8);
     if (wi >= a.chunk_start[nkeys]) return;
-    const int key = a.chunk_order[wi].key, chunk = a.chunk_order[wi].chunk;
+    const ChunkRef cr = a.chunk_order[wi];
+    const int key = cr.key;
     g = key / a.v.Ns; blk = key % a.v.Ns; tile = (int)(blockIdx.x % per8) / 8;
     kbeg = a.v.slc_start[blk]; kend = a.v.slc_start[blk + 1];
-    qbeg = a.sel_start[key] + chunk * a.chunk_len;
-    qend = min(a.sel_start[key + 1], qbeg + a.chunk_len);
-    out_row0 = (size_t)a.part_row_start[key] + (size_t)chunk * (kend - kbeg);
+    qbeg = cr.first;
+    qend = cr.first + cr.count;
+    out_row0 = (size_t)a.part_row_start[key] + (size_t)cr.chunk * (kend - kbeg);
     Kr = a.v.Ks; Vr = a.v.Vs;
   } else {
     blk = blockIdx.x / a.tiles_per_block; tile = blockIdx.x % a.tiles_per_block;  // blk = batch item
@@ -607,7 +608,7 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   }
   {
     ProfScope ps(PROF_BWD_INVERT, s);
-    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, true, true, s);
+    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, false, true, true, s);
     if (rc != SSA_OK) return rc;
   }
   {

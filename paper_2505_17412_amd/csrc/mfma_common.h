@@ -69,6 +69,14 @@ __device__ inline float group_sum(float v, int hs) {
   return v;
 }
 
+// Maximum over the four lanes 16 apart that share a column of a 16 x 16 tile, in all of them (two register swaps, no LDS).
+__device__ inline float column_max(float v) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // Dims of an accumulator whose rows came from a transposed tile operand.  The transposing LDS read takes the 16 rows
 // of dim block dt from two 16-byte segments of a row that lie 32 bytes apart (see PTile in mfma_qc.h: that pairing is
 // what keeps the read free of bank conflicts), so the block covers dims b .. b + 7 and b + 16 .. b + 23 with
@@ -77,64 +85,63 @@ __device__ inline float group_sum(float v, int hs) {
 __device__ inline int tr_dim(int dt, int n) { return 32 * (dt >> 1) + 8 * (dt & 1) + 16 * (n >> 3) + (n & 7); }
 __device__ inline int acc_dim(int dt, int quad) { return tr_dim(dt, 4 * quad); }
 
-// Store the accumulator tile of one query column block to row-major rows of D bf16: on entry lane (n, quad) holds, for
-// every dim block dt, the 4 dims acc_dim(dt, quad) .. +3 of column n, i.e. 8 bytes in each of D/16 places of its row.
-// Within a group of four dim blocks (64 dims) the dim index is 32*dt1 + 16*quad1 + 8*dt0 + 4*quad0 + i (dt1, dt0 and
-// quad1, quad0 the bits of dt & 3 and of quad): exchanging dt1 with quad0 (one round of v_permlane16_swap: lanes 16
-// apart hold the same column) leaves every lane with 16 consecutive dims, so a row goes out as 32-byte pieces, four
-// lanes covering 64 consecutive dims, instead of 8-byte pieces.  `row`: this lane's row (column n); scale: factor
-// applied before rounding; lanes with !valid take part in the exchange and store nothing.  D = 64 or 128.
+// Store the accumulator tile of 16 query columns to row-major rows of D bf16 (base + row*D): on entry lane (n, quad) holds,
+// for every dim block dt, the 4 dims acc_dim(dt, quad) .. +3 of column n, i.e. 8 bytes in each of D/16 places of its row.
+// Within a pair of dim blocks (32 dims, dt = 2*h + dt0) the dim index is 16*quad1 + 8*dt0 + 4*quad0 + i (quad1, quad0 the
+// bits of quad): exchanging dt0 with quad0 (one round of v_permlane16_swap: lanes 16 apart hold the same column) leaves
+// every lane with 8 consecutive dims of its column, and the four lanes of a column with 32 dims.  Where a row has two such
+// groups of 32 (D a multiple of 64), lanes n and n + 8 then trade one group against the other (a rotation by 8 inside the
+// 16 lanes), so that each store instruction writes 128 contiguous bytes of 8 rows instead of 64 of 16: with several heads
+// per KV head those rows are neighbours and whole cache lines go out at once.  `row`: this lane's row (column n); lanes
+// with !valid take part in the exchanges and store nothing (the lanes of a column agree on valid).
 template <int D>
-__device__ inline void store_row_tile_if(bf16_t *row, const f32x4 (&o)[D / 16], float scale, bool valid) {
-  static_assert(D % 64 == 0, "groups of four dim blocks");
-  const int quad = threadIdx.x >> 4 & 3;
+__device__ inline void store_partial_row(bf16_t *base, uint32_t row, const f32x4 (&o)[D / 16], bool valid) {
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  const int n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
+  u32x4 g[D / 32];  // dims 32*h + 8*quad .. +7
 #pragma unroll
-  for (int h = 0; h < D / 64; ++h) {
-    unsigned lo[4], hi[4];  // packed bf16 pairs: dims (0,1) and (2,3) of the lane's 4-dim group of dim block 4*h + j
+  for (int h = 0; h < D / 32; ++h) {
+    u32x2 w[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < 2; ++j) {
       bf16x4 x;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = (__bf16)(o[4 * h + j][i] * scale);
-      typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
-      const u32x2 w = __builtin_bit_cast(u32x2, x);
-      lo[j] = w[0];
-      hi[j] = w[1];
+      for (int i = 0; i < 4; ++i) x[i] = (__bf16)o[2 * h + j][i];
+      w[j] = __builtin_bit_cast(u32x2, x);
     }
-    auto swap16 = [](unsigned &a, unsigned &b) {  // odd 16-lane rows of a <-> even 16-lane rows of b
-      const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-      a = r[0]; b = r[1];
-    };
-    swap16(lo[0], lo[2]); swap16(hi[0], hi[2]); swap16(lo[1], lo[3]); swap16(hi[1], hi[3]);
-    // register j = 2*j1 + j0 now holds dims 64*h + 32*quad0 + 16*quad1 + 8*j0 + 4*j1 .. +3
-    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-    if (valid) {
-      u32x4 *dst = reinterpret_cast<u32x4 *>(row + 64 * h + 32 * (quad & 1) + 16 * (quad >> 1));
-      // written once, read once much later by the merge kernel: streaming stores, so the rows do not push the query
-      // rows (which every selected block reads again) out of the caches
-      __builtin_nontemporal_store(u32x4{lo[0], hi[0], lo[2], hi[2]}, dst);
-      __builtin_nontemporal_store(u32x4{lo[1], hi[1], lo[3], hi[3]}, dst + 1);
-    }
+    // odd 16-lane rows of the first <-> even 16-lane rows of the second
+    const auto a = __builtin_amdgcn_permlane16_swap(w[0][0], w[1][0], false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(w[0][1], w[1][1], false, false);
+    g[h] = u32x4{a[0], b[0], a[1], b[1]};
   }
-}
-
-// One row of D bf16 per query column from the accumulator tile `o` (unscaled); lanes with !valid store nothing (the
-// lanes of a column agree on valid).  Wide stores where the dim blocks come in fours, 8-byte pieces otherwise.
-template <int D>
-__device__ inline void store_partial_row(bf16_t *row, const f32x4 (&o)[D / 16], bool valid) {
+  // written once, read once much later by the merge kernel: streaming stores, so the rows do not push the query rows (which
+  // every selected block reads again) out of the caches
   if constexpr (D % 64 == 0) {
-    store_row_tile_if<D>(row, o, 1.0f, valid);  // the lane exchange runs with every lane on; only the stores are conditional
-  } else {
-    const int quad = threadIdx.x >> 4 & 3;
-    if (valid) {
+    auto upper = [](unsigned keep, unsigned from) {  // lanes n >= 8 take `from` of lane n - 8
+      return (unsigned)__builtin_amdgcn_update_dpp((int)keep, (int)from, 0x128, 0xF, 0xC, false);
+    };
+    auto lower = [](unsigned keep, unsigned from) {  // lanes n < 8 take `from` of lane n + 8
+      return (unsigned)__builtin_amdgcn_update_dpp((int)keep, (int)from, 0x128, 0xF, 0x3, false);
+    };
+    const unsigned rv = valid ? row : ~0u;
+    const unsigned r0 = upper(rv, rv), r1 = lower(rv, rv);  // rows of the first eight columns, of the last eight
+    const int off = 8 * quad + 32 * (n >> 3);
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) {
-        bf16x4 x;
+    for (int h = 0; h < D / 64; ++h) {
+      u32x4 x, y;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = (__bf16)o[dt][i];
-        *reinterpret_cast<bf16x4 *>(row + acc_dim(dt, quad)) = x;
+      for (int i = 0; i < 4; ++i) {
+        x[i] = upper(g[2 * h][i], g[2 * h + 1][i]);
+        y[i] = lower(g[2 * h + 1][i], g[2 * h][i]);
       }
+      if (r0 != ~0u) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(base + (size_t)r0 * D + 64 * h + off));
+      if (r1 != ~0u) __builtin_nontemporal_store(y, reinterpret_cast<u32x4 *>(base + (size_t)r1 * D + 64 * h + off));
     }
+  } else {
+#pragma unroll
+    for (int h = 0; h < D / 32; ++h)
+      if (valid) __builtin_nontemporal_store(g[h], reinterpret_cast<u32x4 *>(base + (size_t)row * D + 32 * h + 8 * quad));
   }
 }
 

@@ -371,7 +371,7 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, const SelIndex &
   }
   {
     ProfScope ps(PROF_FWD_INVERT, s);
-    const int rc = sel_index_build(a.idx, a.v.perm, a.v.slc_start, a.v.N, a.v.Hkv, a.v.T, a.v.Ns, sel, true, false, s);
+    const int rc = sel_index_build(a.idx, a.v.perm, a.v.slc_start, a.v.N, a.v.Hkv, a.v.T, a.v.Ns, sel, true, true, false, s);
     if (rc != SSA_OK) return rc;
   }
   {

@@ -11,11 +11,11 @@ int mfma_forward_kernels(const MfmaView &v, int D, const void *q, const void *ga
 
 // Inverse of the selection (sel_index.hip): per (KV head, selection block) key = g*Ns + b, the ascending list of sorted
 // positions of the tokens that selected it, and the cuts of the lists into work chunks.
-struct ChunkRef { int32_t key, chunk; };  // a work chunk: its list (key) and its number inside the list
+struct ChunkRef { int32_t key, chunk, first, count; };  // a work chunk: its list (key), its number inside the list, its entries
 struct SelIndex {
   uint32_t *cnt;                  // [Hkv*Ns][tiles of sorted positions] entries of the key before the tile
   uint32_t *counts;               // [Hkv*Ns]
-  int32_t *start, *list;          // [Hkv*Ns+1], [N*Hkv*T]
+  int32_t *start, *list;          // [Hkv*Ns+1], [N*Hkv*T]: sorted positions, or caller indices in position order
   uint8_t *rank;                  // [N*Hkv*T]: place of the key's block in the row of I of the listed token
   int32_t *chunk_start, *part_row_start;  // [Hkv*Ns+1] each: dK/dV work chunks and partial-sum rows per key
   int32_t *bc_chunk_start;        // [Hkv*Ns+1]: work chunks of the block-centric forward / dQ kernels
@@ -27,14 +27,14 @@ struct SelIndex {
 size_t sel_index_bytes(int N, int Hkv, int T, int Ns);
 SelIndex sel_index_carve(void *ws, int N, int Hkv, int T, int Ns, int chunk_len, int bc_chunk_len);
 int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_start, int N, int Hkv, int T, int Ns,
-                    const SelIndex &x, bool want_bc_order, bool want_dkv_order, hipStream_t s);
+                    const SelIndex &x, bool caller_indices, bool want_bc_order, bool want_dkv_order, hipStream_t s);
 
 // Block-centric selection kernels: query tokens per work chunk, and the per-(token, KV head, rank) partial results.
 constexpr int BC_CHUNK = 256, BC_CHUNK_MIN = 32;
 int bc_chunk_len(int N, int Hkv, int T);
 struct SlcPartials {
   bf16_t *o;    // [N][Hkv][T][hs][D]: unnormalised partial output (forward) / partial dQ (backward) per selected block
-  float *ml;    // [N][Hkv][T][hs][2]: running maximum (raw score units) and sum of the partial softmax (forward only)
+  float *ml;    // [N][Hkv][T][hs][2]: reference exponent (log2 units) and sum of the partial softmax (forward only)
 };
 
 // Block-centric selection kernels (mfma_slc.hip), forward: partials per selected block, then the per-token merge that

@@ -22,146 +22,247 @@ namespace {
 // unnormalised output in bf16 with its running maximum and sum (Algorithm 1's o, m, l for that block alone), merged per
 // token afterwards (m_slc_merge).  A wavefront that meets a block longer than KSEG picks its own partial up again for
 // the next segment.
+// Bound: the sum of matrix and vector issue (a synthetic copy of one 16-column tile with its LDS reads takes 116 ns per SIMD
+// at four wavefronts, of which this kernel's tiles and steps take 145), and for short blocks the partial rows going out.
+// One column block at head_dim 64 (128 registers, four wavefronts per SIMD; two blocks at two or four wavefronts: 1111 and
+// 1038 us against 989), two at head_dim 128, where the accumulators leave two wavefronts anyway.  62k tokens, 16 heads of
+// 64, top-16: 1090 -> 990 us (no maximum and no rescaling after the first tile, chunk entries prepared in LDS, list entries
+// and chunk bounds read directly); 153k tokens, heads of 128: 12.4 -> 11.3 ms; blocks of 64 keys (sequences): 807 -> 738 us
+// with whole-line stores.
 // ---------------------------------------------------------------------------------------------------------
 struct BcFwdArgs {
   MfmaView v;
   const bf16_t *Q;
-  const int32_t *sel_start, *sel_list, *chunk_start;
+  const int32_t *sel_list, *chunk_start;  // lists of caller indices
   const uint8_t *sel_rank;
   const ChunkRef *chunk_order;
-  int chunk_len;
   bf16_t *po;  // [N][Hkv][T][hs][D]
   float *pml;  // [N][Hkv][T][hs][2]
 };
 
-// LDS plan (bytes): K tiles | V tiles (KSEG/32 tiles each, PTile layout) | token ids [BC_CHUNK] | ranks [BC_CHUNK]
+// LDS plan (bytes): K tiles | V tiles (KSEG/32 tiles each, PTile layout) | chunk entries [BC_CHUNK][2]
 template <int D, int KSEG>
 constexpr size_t bc_lds_bytes() { return (size_t)2 * (KSEG / 32) * PTile<D, false>::BYTES + (size_t)2 * BC_CHUNK * sizeof(int); }
 
-// Query operands and partial-row index of one wavefront step: column n stands for chunk entry step*(16/h_s) + n/h_s,
-// head n % h_s of the KV group.
-template <int D>
+// Query operands and partial-row index of one wavefront step: column n of column block cb stands for chunk entry
+// (step*CB + cb)*(16/h_s) + n/h_s, head n % h_s of the KV group.  Columns past the end of the chunk repeat its last entry
+// and are not stored.
+template <int D, int CB>
 struct BcRows {
-  bf16x8 qop[D / 32];
-  uint32_t prow;  // ((tok*Hkv + g)*T + rank)*hs + head: row of the partial arrays (below 2^32: N*Hq*T is)
-  bool valid;
+  bf16x8 qop[CB][D / 32];
+  uint32_t prow[CB];  // ((tok*Hkv + g)*T + rank)*hs + head: row of the partial arrays (below 2^32: N*Hq*T is)
+  bool valid[CB];
 };
 
-template <int D>
-__device__ inline void bc_load_rows(const BcFwdArgs &a, const int *tl, const int *sl, int step, int cnt, int g, BcRows<D> &r) {
-  const int n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
-  const int hs = a.v.hs, hl = n % hs;
-  const int e = step * (16 / hs) + n / hs;
-  r.valid = e < cnt;
-  const int tok = r.valid ? tl[e] : 0, rank = r.valid ? sl[e] : 0;
-  const bf16_t *src = a.Q + ((size_t)tok * a.v.Hq + g * hs + hl) * D + 8 * quad;
+// qoff, prow0: per chunk entry the byte offset of the token's query rows of this KV group and its first partial row.
+template <int D, int CB>
+__device__ inline void bc_load_rows(const unsigned char *Q, const uint2 *ent, int step, int cnt, int lg_tpw, int slot, uint32_t lane_off,
+                                    int hl, BcRows<D, CB> &r) {
 #pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks) r.qop[ks] = r.valid ? ld8(src + 32 * ks) : zero8();
-  r.prow = (uint32_t)((((size_t)tok * a.v.Hkv + g) * a.v.T + rank) * hs + hl);
+  for (int cb = 0; cb < CB; ++cb) {
+    const int e = ((step * CB + cb) << lg_tpw) + slot;
+    r.valid[cb] = e < cnt;
+    const uint2 x = ent[min(e, cnt - 1)];
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) r.qop[cb][ks] = *reinterpret_cast<const bf16x8 *>(Q + (x.x + lane_off) + 64 * ks);
+    r.prow[cb] = x.y + hl;
+  }
 }
 
-// One online-softmax step (Algorithm 1, inner loop body) of 16 query columns over one 32-key LDS tile.  kt, vt: the K
-// and V tile, ln: the lane offsets of their operands (see PTile).  MASK: keys from index nk on (counted from the segment start;
-// this tile starts at key0) do not exist.  Lazy reference maximum as in fwd_tile.
-template <int D, bool MASK>
-__device__ inline void bc_fwd_tile(FwdState<D, 1> &st, const bf16x8 (&qop)[D / 32], lds_cptr kt, lds_cptr vt,
-                                   const typename PTile<D, false>::Lanes &ln, int key0, int nk, float sl2, float slack,
-                                   const bf16x8 &ones) {
-  f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+// Scores of CB blocks of 16 query columns over one 32-key LDS tile: v[j] = key 8*quad + j of the tile, column n.
+template <int D, int CB>
+__device__ inline void bc_scores(const bf16x8 (&qop)[CB][D / 32], lds_cptr kt, const typename PTile<D, false>::Lanes &ln, float (&v)[CB][8]) {
+  f32x4 s[CB][2];
 #pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks) {
-    s0 = mfma16(p_row_operand<D, false>(kt, ln, 0, ks), qop[ks], s0);
-    s1 = mfma16(p_row_operand<D, false>(kt, ln, 1, ks), qop[ks], s1);
-  }
-  float v[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
+  for (int cb = 0; cb < CB; ++cb) s[cb][0] = s[cb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < D / 32; ++ks)
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+      const bf16x8 k = p_row_operand<D, false>(kt, ln, sub, ks);
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) s[cb][sub] = mfma16(k, qop[cb][ks], s[cb][sub]);
+    }
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[cb][j] = s[cb][j >> 2][j & 3];
+}
+
+// One step of the softmax (Algorithm 1, inner loop body) over one tile.  The reference exponent of a column is the maximum
+// of its first tile (FIRST; log2 units, st.m) and stays: later tiles cost a fused multiply-add, an exponential and half a
+// conversion per score, no maximum and no rescaling.  The result does not depend on the reference as long as nothing leaves
+// the range of the floats, which the caller checks on the finished sums (bc_in_range).
+// MASK: only the first `left` keys of the tile exist.
+template <int D, int CB, bool MASK, bool FIRST>
+__device__ inline void bc_fwd_tile(FwdState<D, CB> &st, const bf16x8 (&qop)[CB][D / 32], lds_cptr kt, lds_cptr vt,
+                                   const typename PTile<D, false>::Lanes &ln, int left, float sl2, const bf16x8 &ones) {
+  float v[CB][8];
+  bc_scores<D, CB>(qop, kt, ln, v);
   if (MASK) {
-    const int first = key0 + 8 * (int)(threadIdx.x >> 4 & 3);
+    const int first = 8 * (int)(threadIdx.x >> 4 & 3);
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (first + j >= nk) v[j] = -INFINITY;
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (first + j >= left) v[cb][j] = -INFINITY;
   }
-  const float pm = fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7])));
-  if (__builtin_expect(__any(pm > st.m[0] + slack), 0)) {
+  if (FIRST) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      const float(&x)[8] = v[cb];
+      st.m[cb] = column_max(fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])))) * sl2;
+    }
+  }
+  bf16x8 pb[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pb[cb][j] = (__bf16)fast_exp2(__builtin_fmaf(v[cb][j], sl2, -st.m[cb]));
+    // the normaliser on the matrix pipe: an all-ones A operand sums the 32 probabilities of every column, in the same bf16
+    // rounding the numerator uses, and leaves the total in every lane of the column
+    st.l[cb] = mfma16(ones, pb[cb], st.l[cb]);
+  }
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt) {
+    const bf16x8 av = p_tr_operand<D, false>(vt, ln, dt);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) st.o[cb][dt] = mfma16(av, pb[cb], st.o[cb][dt]);
+  }
+}
+
+// The first tile's maximum contributes 1 to the sum, so nothing that counts is lost below; a sum under 2^60 leaves room for
+// values of the same size.
+__device__ inline bool bc_in_range(float l) { return l < 0x1p60f; }
+
+// The same step with a running maximum (raised lazily, see fwd_tile): what a column whose scores rise far above its first
+// tile's goes through instead.  st.m in log2 units.
+template <int D>
+__device__ inline void bc_fwd_tile_safe(FwdState<D, 1> &st, const bf16x8 (&qop)[1][D / 32], lds_cptr kt, lds_cptr vt,
+                                        const typename PTile<D, false>::Lanes &ln, int left, float sl2, const bf16x8 &ones) {
+  float v[1][8];
+  bc_scores<D, 1>(qop, kt, ln, v);
+  const int first = 8 * (int)(threadIdx.x >> 4 & 3);
+  float pm = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    v[0][j] = first + j < left ? v[0][j] * sl2 : -INFINITY;
+    pm = fmaxf(pm, v[0][j]);
+  }
+  if (__any(pm > st.m[0] + 8.f)) {
     float tmax = fmaxf(pm, __shfl_xor(pm, 16));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     const float mn = fmaxf(st.m[0], tmax);
-    const float alpha = mn == -INFINITY ? 1.0f : fast_exp2((st.m[0] - mn) * sl2);
+    const float alpha = mn == -INFINITY ? 1.0f : fast_exp2(st.m[0] - mn);
     st.l[0][0] *= alpha;
     st.m[0] = mn;
 #pragma unroll
     for (int dt = 0; dt < D / 16; ++dt) st.o[0][dt] *= alpha;
   }
-  const float neg = st.m[0] != -INFINITY ? -st.m[0] * sl2 : -INFINITY;
+  const float neg = st.m[0] != -INFINITY ? -st.m[0] : -INFINITY;
   bf16x8 pb;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) pb[j] = (__bf16)fast_exp2(__builtin_fmaf(v[j], sl2, neg));
+  for (int j = 0; j < 8; ++j) pb[j] = (__bf16)fast_exp2(v[0][j] + neg);
   st.l[0] = mfma16(ones, pb, st.l[0]);
 #pragma unroll
   for (int dt = 0; dt < D / 16; ++dt) st.o[0][dt] = mfma16(p_tr_operand<D, false>(vt, ln, dt), pb, st.o[0][dt]);
 }
 
-template <int D, int NW, int KSEG>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 4 : 2))) void m_slc_fwd_bc(BcFwdArgs a) {
+// Partial of the earlier segments of a long block, picked up again.
+template <int D>
+__device__ inline void bc_pick_up(const BcFwdArgs &a, uint32_t prow, bool valid, f32x4 (&o)[D / 16], f32x4 &l, float &m) {
+  const int quad = threadIdx.x >> 4 & 3;
+  m = 0.f;
+  if (!valid) return;
+  const float2 ml = *reinterpret_cast<const float2 *>(a.pml + (size_t)prow * 2);
+  m = ml.x;
+  l[0] = ml.y;
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt) {
+    const bf16x4 x = *reinterpret_cast<const bf16x4 *>(a.po + (size_t)prow * D + acc_dim(dt, quad));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[dt][i] = (float)x[i];
+  }
+}
+
+template <int D, int CB, int NW, int KSEG, int WPE>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) void m_slc_fwd_bc(BcFwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   using P = PTile<D, false>;
   constexpr int MAXT = KSEG / 32;
   unsigned char *Kt = smem, *Vt = Kt + MAXT * P::BYTES;
-  int *tl = (int *)(Vt + MAXT * P::BYTES), *sl = tl + BC_CHUNK;
-  const int wid = threadIdx.x >> 6, quad = threadIdx.x >> 4 & 3;
+  uint2 *ent = (uint2 *)(Vt + MAXT * P::BYTES);
+  const int wid = threadIdx.x >> 6, quad = threadIdx.x >> 4 & 3, n = threadIdx.x & 15;
   const int hs = a.v.hs, Hkv = a.v.Hkv, Ns = a.v.Ns;
   const int wi = bc_chunk_of_workgroup(a.chunk_start[Hkv * Ns]);
   if (wi < 0) return;
-  const int key = a.chunk_order[wi].key, chunk = a.chunk_order[wi].chunk;
-  const int g = key / Ns, blk = key % Ns;
+  const ChunkRef cr = a.chunk_order[wi];
+  const int g = cr.key / Ns, blk = cr.key % Ns;
   const int kbeg = a.v.slc_start[blk], kend = a.v.slc_start[blk + 1];
-  const int qbeg = a.sel_start[key] + chunk * a.chunk_len, cnt = min(a.sel_start[key + 1] - qbeg, a.chunk_len);
-  // the chunk's tokens (caller indices) and the rank of this block in each token's row of I
+  const int qbeg = cr.first, cnt = cr.count;
   for (int i = threadIdx.x; i < cnt; i += 64 * NW) {
-    tl[i] = a.v.perm[a.sel_list[qbeg + i]];
-    sl[i] = a.sel_rank[qbeg + i];
+    const uint32_t tok = (uint32_t)a.sel_list[qbeg + i];
+    ent[i] = make_uint2((tok * a.v.Hq + g * hs) * (D * 2), ((tok * Hkv + g) * a.v.T + a.sel_rank[qbeg + i]) * hs);
   }
-  const int tpw = 16 / hs;  // tokens per wavefront step
-  const int n_it = (cnt + tpw - 1) / tpw;
+  const int lg_tpw = 31 - __builtin_clz(16 / hs), slot = n / hs, hl = n % hs;
+  const uint32_t lane_off = (uint32_t)(hl * D * 2 + 16 * quad);
+  const unsigned char *Qb = (const unsigned char *)a.Q;
+  const int n_it = (cnt + (CB << lg_tpw) - 1) / (CB << lg_tpw);
   const uint32_t kstride = (uint32_t)(Hkv * D);
-  const float sl2 = a.v.sl2, slack = 8.0f / sl2;
+  const float sl2 = a.v.sl2;
   const bf16x8 ones = ones_operand();
   const typename P::Lanes ln = P::lanes();
   const lds_cptr kl = (lds_cptr)Kt, vl = (lds_cptr)Vt;
   __syncthreads();
-  BcRows<D> cur;
-  if (wid < n_it) bc_load_rows<D>(a, tl, sl, wid, cnt, g, cur);  // in flight while the block is staged
+  BcRows<D, CB> cur;
+  if (wid < n_it) bc_load_rows<D, CB>(Qb, ent, wid, cnt, lg_tpw, slot, lane_off, hl, cur);  // in flight while the block is staged
   for (int k0 = kbeg; k0 < kend; k0 += KSEG) {
     const int nk = min(KSEG, kend - k0), nfull = nk >> 5;
     if (k0 > kbeg) {
       __syncthreads();  // every wavefront is done with the previous segment
-      if (wid < n_it) bc_load_rows<D>(a, tl, sl, wid, cnt, g, cur);
+      if (wid < n_it) bc_load_rows<D, CB>(Qb, ent, wid, cnt, lg_tpw, slot, lane_off, hl, cur);
     }
     p_stage2<D, false, 64 * NW>(a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D, kstride, k0, (nk + 31) >> 5, Kt, Vt);
     __syncthreads();
     for (int it = wid; it < n_it; it += NW) {
-      BcRows<D> nxt;  // the next step's operands are requested before this step's arithmetic
-      if (it + NW < n_it) bc_load_rows<D>(a, tl, sl, it + NW, cnt, g, nxt);
-      FwdState<D, 1> st;
+      BcRows<D, CB> nxt;  // the next step's operands are requested before this step's arithmetic
+      if (it + NW < n_it) bc_load_rows<D, CB>(Qb, ent, it + NW, cnt, lg_tpw, slot, lane_off, hl, nxt);
+      FwdState<D, CB> st;
       init_state(st);
-      if (k0 > kbeg && cur.valid) {  // pick the partial of the earlier segments up again
-        const float2 ml = *reinterpret_cast<const float2 *>(a.pml + (size_t)cur.prow * 2);
-        st.m[0] = ml.x;
-        st.l[0][0] = ml.y;
+      const bool fresh = k0 == kbeg;
+      if (!fresh)
 #pragma unroll
-        for (int dt = 0; dt < D / 16; ++dt) {
-          const bf16x4 x = *reinterpret_cast<const bf16x4 *>(a.po + (size_t)cur.prow * D + acc_dim(dt, quad));
+        for (int cb = 0; cb < CB; ++cb) bc_pick_up<D>(a, cur.prow[cb], cur.valid[cb], st.o[cb], st.l[cb], st.m[cb]);
+      if (fresh && nfull > 0) bc_fwd_tile<D, CB, false, true>(st, cur.qop, kl, vl, ln, 32, sl2, ones);
+      else if (fresh) bc_fwd_tile<D, CB, true, true>(st, cur.qop, kl, vl, ln, nk, sl2, ones);
+      else if (nfull > 0) bc_fwd_tile<D, CB, false, false>(st, cur.qop, kl, vl, ln, 32, sl2, ones);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) st.o[0][dt][i] = (float)x[i];
+      for (int t = 1; t < MAXT; ++t)
+        if (t < nfull) bc_fwd_tile<D, CB, false, false>(st, cur.qop, kl + t * P::BYTES, vl + t * P::BYTES, ln, 32, sl2, ones);
+      if ((nk & 31) && (nfull > 0 || !fresh))
+        bc_fwd_tile<D, CB, true, false>(st, cur.qop, kl + nfull * P::BYTES, vl + nfull * P::BYTES, ln, nk & 31, sl2, ones);
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        if (__builtin_expect(__any(cur.valid[cb] && !bc_in_range(st.l[cb][0])), 0)) {
+          FwdState<D, 1> safe;
+          init_state(safe);
+          bf16x8 q1[1][D / 32];
+#pragma unroll
+          for (int ks = 0; ks < D / 32; ++ks) q1[0][ks] = cur.qop[cb][ks];
+          if (k0 > kbeg) bc_pick_up<D>(a, cur.prow[cb], cur.valid[cb], safe.o[0], safe.l[0], safe.m[0]);
+#pragma unroll 1
+          for (int t = 0; t < (nk + 31) >> 5; ++t)
+            bc_fwd_tile_safe<D>(safe, q1, kl + t * P::BYTES, vl + t * P::BYTES, ln, nk - 32 * t, sl2, ones);
+          st.m[cb] = safe.m[0];
+          st.l[cb] = safe.l[0];
+#pragma unroll
+          for (int dt = 0; dt < D / 16; ++dt) st.o[cb][dt] = safe.o[0][dt];
         }
+        // (a column past the end of the chunk points at row 0 of the partial arrays and is not stored)
+        store_partial_row<D>(a.po, cur.prow[cb], st.o[cb], cur.valid[cb]);
+        if (cur.valid[cb] && quad == 0)
+          *reinterpret_cast<float2 *>(a.pml + (size_t)cur.prow[cb] * 2) = make_float2(st.m[cb], st.l[cb][0]);
       }
-#pragma unroll
-      for (int t = 0; t < MAXT; ++t)
-        if (t < nfull) bc_fwd_tile<D, false>(st, cur.qop, kl + t * P::BYTES, vl + t * P::BYTES, ln, 32 * t, nk, sl2, slack, ones);
-      if (nk & 31)
-        bc_fwd_tile<D, true>(st, cur.qop, kl + nfull * P::BYTES, vl + nfull * P::BYTES, ln, 32 * nfull, nk, sl2, slack, ones);
-      // (a column past the end of the chunk points at row 0 of the partial arrays and is not stored)
-      store_partial_row<D>(a.po + (size_t)cur.prow * D, st.o[0], cur.valid);
-      if (cur.valid && quad == 0) *reinterpret_cast<float2 *>(a.pml + (size_t)cur.prow * 2) = make_float2(st.m[0], st.l[0][0]);
       cur = nxt;
     }
   }
@@ -179,7 +280,6 @@ struct MergeArgs {
   float *lse;  // [3,N,Hq]
   bf16_t *out;
   int N, Hq, Hkv, hs, T, D;
-  float sl2;
 };
 
 __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
@@ -200,7 +300,7 @@ __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
     const size_t r = (slot0 + j) * a.hs + hl;
     const float2 ml = *reinterpret_cast<const float2 *>(a.pml + r * 2);
     const bf16x8 x = ld8(a.po + r * a.D + 8 * c8);
-    const float wj = ml.x == -INFINITY ? 0.f : fast_exp2((ml.x - M) * a.sl2);
+    const float wj = ml.x == -INFINITY ? 0.f : fast_exp2(ml.x - M);
     L += wj * ml.y;
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] += wj * (float)x[e];
@@ -212,7 +312,7 @@ __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) os[e] = (__bf16)(acc[e] * inv);
   *reinterpret_cast<bf16x8 *>(a.Ob + NH * a.D + off) = os;
-  if (c8 == 0) a.lse[NH + th] = L > 0.f ? (M * a.sl2 + __log2f(L)) * LN2 : -INFINITY;
+  if (c8 == 0) a.lse[NH + th] = L > 0.f ? (M + __log2f(L)) * LN2 : -INFINITY;
   const float w0 = bf16_to_f32(a.gates[th * 3]), w1 = bf16_to_f32(a.gates[th * 3 + 1]), w2 = bf16_to_f32(a.gates[th * 3 + 2]);
   const bf16x8 x0 = ld8(a.Ob + off), x2 = ld8(a.Ob + 2 * NH * a.D + off);
   bf16x8 o;
@@ -232,10 +332,9 @@ struct BcDqArgs {
   MfmaView v;
   const bf16_t *Qs, *dOs;             // [N(pos)][Hq][D] sorted copies: Q, and the selection gate times dO
   const float *lse2s, *deltas;        // selection branch: [N(pos)][Hq]
-  const int32_t *sel_start, *sel_list, *chunk_start;
+  const int32_t *sel_list, *chunk_start;
   const uint8_t *sel_rank;
   const ChunkRef *chunk_order;
-  int chunk_len;
   bf16_t *pdq;                        // [N(pos)][Hkv][T][hs][D]
 };
 
@@ -307,10 +406,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
   const int hs = a.v.hs, Hkv = a.v.Hkv, Ns = a.v.Ns;
   const int wi = bc_chunk_of_workgroup(a.chunk_start[Hkv * Ns]);
   if (wi < 0) return;
-  const int key = a.chunk_order[wi].key, chunk = a.chunk_order[wi].chunk;
-  const int g = key / Ns, blk = key % Ns;
+  const ChunkRef cr = a.chunk_order[wi];
+  const int g = cr.key / Ns, blk = cr.key % Ns;
   const int kbeg = a.v.slc_start[blk], kend = a.v.slc_start[blk + 1];
-  const int qbeg = a.sel_start[key] + chunk * a.chunk_len, cnt = min(a.sel_start[key + 1] - qbeg, a.chunk_len);
+  const int qbeg = cr.first, cnt = cr.count;
   // the chunk's tokens (sorted positions) and the rank of this block in each token's row of I
   for (int i = threadIdx.x; i < cnt; i += 64 * NW) {
     tl[i] = a.sel_list[qbeg + i];
@@ -351,7 +450,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
       for (int t = 0; t < MAXT; ++t)
         if (t < nfull) bc_dq_tile<D, false>(acc, cur, kt + t * P::BYTES, vt + t * P::BYTES, ln, 32 * t, nk, sl2);
       if (nk & 31) bc_dq_tile<D, true>(acc, cur, kt + nfull * P::BYTES, vt + nfull * P::BYTES, ln, 32 * nfull, nk, sl2);
-      store_partial_row<D>(a.pdq + (size_t)cur.prow * D, acc, cur.valid);
+      store_partial_row<D>(a.pdq, cur.prow, acc, cur.valid);
       cur = nxt;
     }
   }
@@ -397,6 +496,10 @@ __global__ __launch_bounds__(256) void m_dq_merge(DqMergeArgs a) {
 
 // Shape of the block-centric kernels per head dimension: wavefronts per workgroup, keys held in LDS at a time.
 template <int D> struct BcShape { static constexpr int NW = 8, KSEG = 256; };
+// Forward: 16-column blocks per wavefront, wavefronts per workgroup and per SIMD (see m_slc_fwd_bc for the figures).
+template <int D> struct BcFwdShape { static constexpr int CB = 2, NW = 8, KSEG = 256, WPE = 4; };
+template <> struct BcFwdShape<64> { static constexpr int CB = 1, NW = 8, KSEG = 256, WPE = 4; };
+template <> struct BcFwdShape<128> { static constexpr int CB = 2, NW = 8, KSEG = 256, WPE = 2; };
 
 // upper bound of the number of chunks: every (KV head, block) list adds at most one partly filled chunk
 unsigned chunk_bound(const MfmaView &v, int chunk_len) {
@@ -407,14 +510,14 @@ unsigned chunk_bound(const MfmaView &v, int chunk_len) {
 template <int D>
 int launch_slc_forward(const MfmaView &v, const bf16_t *q, const SelIndex &sel, const SlcPartials &part,
                        hipStream_t s) {
-  using BS = BcShape<D>;
+  using BS = BcFwdShape<D>;
+  auto kernel = m_slc_fwd_bc<D, BS::CB, BS::NW, BS::KSEG, BS::WPE>;
   static std::once_flag once;  // raise the dynamic LDS limit once per process for this instantiation
-  std::call_once(once, [] {
-    (void)hipFuncSetAttribute((const void *)m_slc_fwd_bc<D, BS::NW, BS::KSEG>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              160 * 1024);
+  std::call_once(once, [&] {
+    (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   });
-  BcFwdArgs b{v, q, sel.start, sel.list, sel.bc_chunk_start, sel.rank, sel.bc_order, sel.bc_chunk_len, part.o, part.ml};
-  m_slc_fwd_bc<D, BS::NW, BS::KSEG><<<dim3((chunk_bound(v, sel.bc_chunk_len) + 7) / 8 * 8), 64 * BS::NW, bc_lds_bytes<D, BS::KSEG>(), s>>>(b);
+  BcFwdArgs b{v, q, sel.list, sel.bc_chunk_start, sel.rank, sel.bc_order, part.o, part.ml};
+  kernel<<<dim3((chunk_bound(v, sel.bc_chunk_len) + 7) / 8 * 8), 64 * BS::NW, bc_lds_bytes<D, BS::KSEG>(), s>>>(b);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
@@ -427,8 +530,7 @@ int launch_slc_dq(const MfmaView &v, const BwdBuffers &w, hipStream_t s) {
                               160 * 1024);
   });
   const size_t NH = (size_t)v.N * v.Hq;
-  BcDqArgs b{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.start, w.sel.list, w.sel.bc_chunk_start,
-             w.sel.rank, w.sel.bc_order, w.sel.bc_chunk_len, w.part.o};
+  BcDqArgs b{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.list, w.sel.bc_chunk_start, w.sel.rank, w.sel.bc_order, w.part.o};
   m_bwd_dq_bc<D, BS::NW, BS::KSEG><<<dim3((chunk_bound(v, w.sel.bc_chunk_len) + 7) / 8 * 8), 64 * BS::NW, bc_dq_lds_bytes<D, BS::KSEG>(), s>>>(b);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
@@ -448,7 +550,7 @@ int slc_forward_kernel(const MfmaView &v, int D, const void *q, const SelIndex &
 int slc_merge_kernel(const MfmaView &v, int D, const SlcPartials &part, const int32_t *idx, const void *gates,
                      void *out_branch, float *lse, void *out, hipStream_t s) {
   MergeArgs m{part.o, part.ml, idx, (const bf16_t *)gates, (bf16_t *)out_branch, lse, (bf16_t *)out,
-              v.N, v.Hq, v.Hkv, v.hs, v.T, D, v.sl2};
+              v.N, v.Hq, v.Hkv, v.hs, v.T, D};
   const size_t threads = (size_t)v.N * v.Hq * (D / 8);
   m_slc_merge<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(m);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;

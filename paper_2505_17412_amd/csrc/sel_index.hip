@@ -146,7 +146,7 @@ struct OrderArgs {
   const int32_t *chunk_start;  // [keys+1]
   uint32_t *bins;              // [Hkv * bins_per_head] counters
   int4 *slot;                  // [chunks]: bucket, number inside the bucket, key, chunk inside the key
-  ChunkRef *order;             // [chunks]: key, chunk inside the key
+  ChunkRef *order;             // [chunks] in execution order
   int chunk_len;
 };
 
@@ -156,7 +156,7 @@ template <int R>
 __global__ __launch_bounds__(SEL_THREADS) void m_sel_fill(SelArgs a, int n_tiles, const uint32_t *__restrict__ cnt,
                                                           const int32_t *__restrict__ start, int32_t *__restrict__ list,
                                                           uint8_t *__restrict__ rank, OrderArgs o0, OrderArgs o1, int bucket,
-                                                          int bins_per_head) {
+                                                          int bins_per_head, bool caller_indices) {
   extern __shared__ __align__(16) uint32_t sel_bits[];
   const int tile = blockIdx.x, g = blockIdx.y, b0 = blockIdx.z * KEY_TILE, nb = min(KEY_TILE, a.Ns - b0);
   for (int i = threadIdx.x; i < nb * TILE_WORDS; i += SEL_THREADS) sel_bits[i] = 0u;
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(SEL_THREADS) void m_sel_fill(SelArgs a, int n_tiles
     for (int x = 0; x < TILE_WORDS - 1; ++x) before += x < (pl >> 5) ? __popc(w[x]) : 0u;
     const int key = g * a.Ns + b[u];
     const int r = (int)(cnt[(size_t)key * n_tiles + tile] + before), at = start[key] + r;
-    list[at] = p0 + pl;
+    list[at] = caller_indices ? a.perm[p0 + pl] : p0 + pl;
     rank[at] = (uint8_t)j;
     const int bin = g * bins_per_head + (p0 + pl) / bucket;
     auto first = [&](const OrderArgs &o) {
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(SEL_THREADS) void m_sel_fill(SelArgs a, int n_tiles
 // counters of m_sel_fill) does not touch any result.  One workgroup per chunking: the prefix of the bucket counters in LDS,
 // then every chunk goes to bucket start + number in the bucket.
 constexpr int ORDER_BINS = 8192;
-__global__ __launch_bounds__(1024) void m_chunk_order(OrderArgs o0, OrderArgs o1, int n_keys, int n_bins) {
+__global__ __launch_bounds__(1024) void m_chunk_order(OrderArgs o0, OrderArgs o1, const int32_t *__restrict__ start, int n_keys, int n_bins) {
   __shared__ uint32_t base[ORDER_BINS];
   __shared__ uint32_t part[16];
   const OrderArgs &o = blockIdx.x == 0 ? o0 : o1;
@@ -229,7 +229,8 @@ __global__ __launch_bounds__(1024) void m_chunk_order(OrderArgs o0, OrderArgs o1
   __syncthreads();
   for (int c = tid; c < total; c += 1024) {
     const int4 s = o.slot[c];
-    o.order[base[s.x] + (uint32_t)s.y] = ChunkRef{s.z, s.w};
+    const int first = start[s.z] + s.w * o.chunk_len;
+    o.order[base[s.x] + (uint32_t)s.y] = ChunkRef{s.z, s.w, first, min(o.chunk_len, start[s.z + 1] - first)};
   }
 }
 
@@ -273,7 +274,7 @@ SelIndex sel_index_carve(void *ws_, int N, int Hkv, int T, int Ns, int chunk_len
 }
 
 int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_start, int N, int Hkv, int T, int Ns,
-                    const SelIndex &x, bool want_bc_order, bool want_dkv_order, hipStream_t s) {
+                    const SelIndex &x, bool caller_indices, bool want_bc_order, bool want_dkv_order, hipStream_t s) {
   const int tiles = pos_tiles(N), keys = Hkv * Ns;
   // bucket width of the execution orders: Hkv * ceil(N / bucket) buckets fit the LDS table
   int bucket = 64;
@@ -288,11 +289,11 @@ int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_
   m_sel_scan_tiles<<<(keys + 3) / 4, 256, 0, s>>>(x.cnt, keys, tiles, x.counts);
   m_scan_counts<<<1, 1024, 0, s>>>(x.counts, keys, Ns, x.chunk_len, x.bc_chunk_len, slc_start, x.start, x.chunk_start,
                                    x.part_row_start, x.bc_chunk_start);
-  if (T <= 16) m_sel_fill<1><<<grid, SEL_THREADS, lds, s>>>(a, tiles, x.cnt, x.start, x.list, x.rank, bc, dkv, bucket, bph);
-  else if (T <= 32) m_sel_fill<2><<<grid, SEL_THREADS, lds, s>>>(a, tiles, x.cnt, x.start, x.list, x.rank, bc, dkv, bucket, bph);
-  else m_sel_fill<4><<<grid, SEL_THREADS, lds, s>>>(a, tiles, x.cnt, x.start, x.list, x.rank, bc, dkv, bucket, bph);
-  if (want_bc_order && want_dkv_order) m_chunk_order<<<2, 1024, 0, s>>>(bc, dkv, keys, n_bins);
-  else if (want_bc_order) m_chunk_order<<<1, 1024, 0, s>>>(bc, bc, keys, n_bins);
-  else if (want_dkv_order) m_chunk_order<<<1, 1024, 0, s>>>(dkv, dkv, keys, n_bins);
+  if (T <= 16) m_sel_fill<1><<<grid, SEL_THREADS, lds, s>>>(a, tiles, x.cnt, x.start, x.list, x.rank, bc, dkv, bucket, bph, caller_indices);
+  else if (T <= 32) m_sel_fill<2><<<grid, SEL_THREADS, lds, s>>>(a, tiles, x.cnt, x.start, x.list, x.rank, bc, dkv, bucket, bph, caller_indices);
+  else m_sel_fill<4><<<grid, SEL_THREADS, lds, s>>>(a, tiles, x.cnt, x.start, x.list, x.rank, bc, dkv, bucket, bph, caller_indices);
+  if (want_bc_order && want_dkv_order) m_chunk_order<<<2, 1024, 0, s>>>(bc, dkv, x.start, keys, n_bins);
+  else if (want_bc_order) m_chunk_order<<<1, 1024, 0, s>>>(bc, bc, x.start, keys, n_bins);
+  else if (want_dkv_order) m_chunk_order<<<1, 1024, 0, s>>>(dkv, dkv, x.start, keys, n_bins);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
