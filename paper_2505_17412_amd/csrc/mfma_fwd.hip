@@ -111,6 +111,68 @@ __device__ inline void fwd_tile(FwdState<D, CB> &st, const QRows<D, CB> &q, lds_
   }
 }
 
+// The same step inside a walk all of whose columns see every key of the tile and have a reference maximum already: the
+// reference stays, which leaves a fused multiply-add, an exponential and half a conversion per score.  The result does not
+// depend on the reference unless the sums leave the range of the floats; the caller checks that at the end of the walk
+// (sums_in_range) and repeats the walk with fwd_tile alone if they do.
+template <int D, int CB>
+__device__ inline void fwd_tile_fixed(FwdState<D, CB> &st, const QRows<D, CB> &q, lds_cptr kt, lds_cptr vt,
+                                      const typename PTile<D>::Lanes &ln, const bool (&act)[CB], float sl2, const bf16x8 &ones) {
+  float s[CB][8];
+  score_tile<D, CB>(kt, ln, q, act, s);
+  bf16x8 pb[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    const float neg = -st.m[cb] * sl2;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pb[cb][j] = (__bf16)fast_exp2(__builtin_fmaf(s[cb][j], sl2, neg));
+    st.l[cb] = mfma16(ones, pb[cb], st.l[cb]);
+  }
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt) {
+    const bf16x8 av = p_tr_operand<D>(vt, ln, dt);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) st.o[cb][dt] = mfma16(av, pb[cb], st.o[cb][dt]);
+  }
+}
+template <int D, int CB>
+__device__ inline bool sums_in_range(const FwdState<D, CB> &st, const QRows<D, CB> &q) {
+  bool ok = true;
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) ok = ok && (!q.valid[cb] || st.l[cb][0] < 0x1p60f);
+  return ok;
+}
+
+// One whole walk of a workgroup over the key range [rs, re) (in LDS at rng[0], rng[1]; rng[2] = 0), columns restricted to [lo, hi).  uniform:
+// every column sees exactly [rs, re).
+template <int D, int CB>
+__device__ inline void fwd_walk(FwdState<D, CB> &st, const QRows<D, CB> &q, const TileSrc<2> &src, bf16_t *stage0, int *rng, int rs,
+                                int re, bool uniform, const int (&lo)[CB], const int (&hi)[CB], const bool (&on)[CB], float sl2) {
+  using L = StageLayout<D, 2>;
+  const bf16x8 ones = ones_operand();
+  const float slack = 8.0f / sl2;
+  const typename PTile<D>::Lanes ln = PTile<D>::lanes();
+  bool act[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) act[cb] = true;
+#pragma unroll 1
+  for (bool fixed = uniform;; fixed = false) {
+    init_state(st);
+    const int first = rs & ~7;  // the first tile sets the references
+    run_pipeline<D, 2>(
+        src, stage0, rng, rng + 1, re > rs ? 1 : 0, [](int) {},
+        [&](const bf16_t *stg, int kb, int) {
+          const lds_cptr kt = (lds_cptr)L::row_tile((bf16_t *)stg, 0), vt = (lds_cptr)L::row_tile((bf16_t *)stg, 1);
+          if (fixed && kb != first && kb + 32 <= re) fwd_tile_fixed<D, CB>(st, q, kt, vt, ln, act, sl2, ones);
+          else fwd_tile<D, CB, true>(st, q, kt, vt, ln, kb, lo, hi, on, act, sl2, slack, ones);
+        });
+    if (!fixed) break;
+    if (!sums_in_range<D, CB>(st, q)) rng[2] = 1;
+    __syncthreads();
+    if (!lds_uniform(rng + 2)) break;
+  }
+}
+
 // Normalise (Algorithm 1: o * exp(m - l)), store the branch output and its log-sum-exp; lse2[cb] in log2 units.
 template <int D, int CB>
 __device__ inline void finish(const FwdArgs &a, FwdState<D, CB> &st, int branch, const QRows<D, CB> &q, float (&lse2)[CB]) {
@@ -143,6 +205,79 @@ __host__ __device__ inline size_t cmp_lds_bytes(int tw, int s_max) {
   return (size_t)2 * StageLayout<D, 2>::ELEMS * sizeof(bf16_t) + 32 + ((size_t)tw * s_max + 4 * ((s_max + 31) / 32) + 4 * 4 * 16) * 4;
 }
 
+// Second walk of the compression kernel: eq. (6) scores with the normaliser known, for HS = 4, 8 or 16 heads per KV head,
+// over steps of two 32-key tiles.  Scores NOT transposed (query rows x keys): a lane holds four heads of ONE token for one
+// key of each 16-key sub-tile, and adds them in-lane.  With 8 or 16 heads one register swap between lanes 16 apart adds the
+// other heads of both sub-tiles at once and leaves every lane with ONE key, that of sub-tile quad & 1, and one integer LDS
+// atomic adds the sum onto the key's selection block.  l4: -lse per row (log2 units).
+template <int D, int CB, int HS>
+__device__ inline void score_walk(const FwdArgs &a, const QRows<D, CB> &q, const typename PTile<D>::Lanes &ln, const TileSrc<2> &src,
+                                  bf16_t *stage0, const int *rng, int rs, int re, bool uniform, const float (&l4)[CB][4],
+                                  const int (&klo)[CB], const int (&khi)[CB], const int (&kbase)[CB], uint32_t *S, float sl2) {
+  using L = StageLayout<D, 2>;
+  const int quad = threadIdx.x >> 4 & 3, last = a.v.Nc - 1;
+  const int off0 = tile_key_row(0, HS >= 8 ? quad & 1 : 0), off1 = tile_key_row(0, 1);
+  run_pipeline<D, 2, 256, 2, 64>(
+      src, stage0, rng, rng + 1, re > rs ? 1 : 0, [](int) {},
+      [&](const bf16_t *stg2, int kb2, int) {
+        // the selection blocks of this lane's keys, requested before the matrix instructions
+        int sb[2][2];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          sb[half][0] = a.v.cmp_slc[min(kb2 + 32 * half + off0, last)];
+          sb[half][1] = HS >= 8 ? 0 : a.v.cmp_slc[min(kb2 + 32 * half + off1, last)];
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const bf16_t *stg = L::row_tile((bf16_t *)stg2, half);
+          const int kb = kb2 + 32 * half;
+          float t[CB][2];
+#pragma unroll
+          for (int sub = 0; sub < 2; ++sub) {
+            f32x4 c[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) c[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < D / 32; ++ks) {
+              const bf16x8 kop = p_row_operand<D>((lds_cptr)stg, ln, sub, ks);
+#pragma unroll
+              for (int cb = 0; cb < CB; ++cb) c[cb] = mfma16(q.qop[cb][ks], kop, c[cb]);
+            }
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+              float p[4];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) p[i] = fast_exp2(__builtin_fmaf(c[cb][i], sl2, l4[cb][i]));
+              t[cb][sub] = ((p[0] + p[1]) + p[2]) + p[3];
+            }
+          }
+          const bool whole = uniform && kb >= rs && kb + 32 <= re;
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) {
+            auto add = [&](float v, int key, int sblk, bool mine) {
+              if (mine && (whole || (key >= klo[cb] && key < khi[cb]))) atomicAdd(&S[kbase[cb] + sblk], (uint32_t)(v * SCORE_FIX));
+            };
+            if (HS >= 8) {
+              const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(t[cb][0]), __float_as_uint(t[cb][1]), false, false);
+              float v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+              if (HS == 16) {
+                const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+                v = __uint_as_float(y[0]) + __uint_as_float(y[1]);
+              }
+              add(v, kb + off0, sb[half][0], HS == 8 || quad < 2);
+            } else {
+              add(t[cb][0], kb + off0, sb[half][0], true);
+              add(t[cb][1], kb + off1, sb[half][1], true);
+            }
+          }
+        }
+      });
+}
+
+// Bound: the sum of matrix and vector issue over both walks (per 32-key tile 13 matrix instructions, 39 vector instructions
+// and 16 exponentials; at four wavefronts per SIMD the pipes overlap little).  62k tokens, 2247 pooled keys, 16 heads of 64:
+// 1690 -> 1494 us, 65k tokens in sequences: 1075 -> 852 us (no maximum after the first tile; score walk specialised per head
+// count, one atomic per two keys' worth of lanes; top-k search ends where exactly T entries are separated).
 // Compression branch (eq. (4) first term over the mean-pooled keys of eq. (5)), then the selection scores of
 // eq. (6) accumulated per selection block in LDS as fixed-point integers (integer adds commute, so the result
 // does not depend on scheduling), then the top-k.
@@ -173,27 +308,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 4
   int rs, re;
   bool uniform;
   wg_range<CB>(ints, lo, hi, q.valid, rs, re, uniform);
-  if (threadIdx.x == 0) { ints[4] = rs; ints[5] = re; }
+  if (threadIdx.x == 0) { ints[4] = rs; ints[5] = re; ints[6] = 0; }
   __syncthreads();
   const int nr = re > rs ? 1 : 0;
   bool act[CB], on[CB];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) { act[cb] = true; on[cb] = q.valid[cb]; }
-  const float slack = 8.0f / a.v.sl2;
   TileSrc<2> src{{a.v.Kc + (size_t)g * D, a.v.Vc + (size_t)g * D}, (uint32_t)(a.v.Hkv * D)};
   FwdState<D, CB> st;
-  init_state(st);
-  const bf16x8 ones = ones_operand();
   const float sl2 = a.v.sl2;
   const typename PTile<D>::Lanes ln = PTile<D>::lanes();
-  run_pipeline<D, 2>(
-      src, stage0, ints + 4, ints + 5, nr, [](int) {},
-      [&](const bf16_t *stg, int kb, int) {
-        if (uniform && kb >= rs && kb + 32 <= re)
-          fwd_tile<D, CB, false>(st, q, (lds_cptr)L::row_tile((bf16_t *)stg, 0), (lds_cptr)L::row_tile((bf16_t *)stg, 1), ln, kb, lo, hi, on, act, sl2, slack, ones);
-        else
-          fwd_tile<D, CB, true>(st, q, (lds_cptr)L::row_tile((bf16_t *)stg, 0), (lds_cptr)L::row_tile((bf16_t *)stg, 1), ln, kb, lo, hi, on, act, sl2, slack, ones);
-      });
+  fwd_walk<D, CB>(st, q, src, stage0, ints + 4, rs, re, uniform, lo, hi, on, sl2);
   float lse2[CB];
   finish<D, CB>(a, st, 0, q, lse2);
 
@@ -210,59 +335,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 4
       if (quad == 0) lse_l[(wid * CB + cb) * 16 + n] = lse2[cb];
     __syncthreads();
     float l4[CB][4];
-    int klo[CB], khi[CB], ks0[CB], kslot[CB];
-    bool owner[CB];
+    int klo[CB], khi[CB], kbase[CB];
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) l4[cb][i] = lse_l[(wid * CB + cb) * 16 + 4 * quad + i];
-      kslot[cb] = (wid * CB + cb) * (16 / hs) + (4 * quad) / hs;  // the token of this lane's four rows
-      const int pos = wg_pos0 + kslot[cb];
+      for (int i = 0; i < 4; ++i) l4[cb][i] = -lse_l[(wid * CB + cb) * 16 + 4 * quad + i];
+      const int kslot = (wid * CB + cb) * (16 / hs) + (4 * quad) / hs;  // the token of this lane's four rows
+      const int pos = wg_pos0 + kslot;
       const bool ok = pos < a.v.N;
       const int item = ok ? a.v.tok_item[pos] : 0;
       klo[cb] = ok ? a.v.cmp_batch[item] : 0;
       khi[cb] = ok ? a.v.cmp_batch[item + 1] : 0;
-      ks0[cb] = ok ? a.v.slc_batch[item] : 0;
-      owner[cb] = (4 * quad) % hs == 0;
+      kbase[cb] = kslot * s_max - (ok ? a.v.slc_batch[item] : 0);
+      // rows of tokens that do not exist: probability 0 (their lse is that of an empty sum)
+      if (!ok)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) l4[cb][i] = -INFINITY;
     }
     // two consecutive 32-key tiles per step: half the barriers and staging rounds of a walk that has little work per key
     TileSrc<2> ksrc2{{a.v.Kc + (size_t)g * D, a.v.Kc + (size_t)g * D + (size_t)32 * a.v.Hkv * D}, (uint32_t)(a.v.Hkv * D)};
-    run_pipeline<D, 2, 256, 2, 64>(
-        ksrc2, stage0, ints + 4, ints + 5, nr, [](int) {},
-        [&](const bf16_t *stg2, int kb2, int) {
-#pragma unroll
-          for (int half = 0; half < 2; ++half) {
-            const bf16_t *stg = L::row_tile((bf16_t *)stg2, half);
-            const int kb = kb2 + 32 * half;
-            // the selection block of this lane's key in either sub-tile, requested before the matrix instructions
-            int sblk[2];
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) sblk[sub] = a.v.cmp_slc[min(tile_key_row(kb, sub), a.v.Nc - 1)];
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-              f32x4 c[CB];
-#pragma unroll
-              for (int cb = 0; cb < CB; ++cb) c[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-              for (int ks = 0; ks < D / 32; ++ks) {
-                const bf16x8 kop = p_row_operand<D>((lds_cptr)stg, ln, sub, ks);
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) c[cb] = mfma16(q.qop[cb][ks], kop, c[cb]);
-              }
-              const int key = tile_key_row(kb, sub);  // column n of sub-tile `sub` sits in row slot 16*sub + n
-#pragma unroll
-              for (int cb = 0; cb < CB; ++cb) {
-                float t = 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) t += fast_exp2(__builtin_fmaf(c[cb][i], sl2, -l4[cb][i]));
-                if (hs >= 8) t += __shfl_xor(t, 16);
-                if (hs >= 16) t += __shfl_xor(t, 32);
-                if (owner[cb] && key >= klo[cb] && key < khi[cb])
-                  atomicAdd(&S[(size_t)kslot[cb] * s_max + sblk[sub] - ks0[cb]], (uint32_t)(t * SCORE_FIX));
-              }
-            }
-          }
-        });
+    auto walk = [&](auto hs_c) {  // a walk per head count: the tile code is straight-line
+      constexpr int HS = decltype(hs_c)::value;
+      score_walk<D, CB, HS>(a, q, ln, ksrc2, stage0, ints + 4, rs, re, uniform, l4, klo, khi, kbase, S, sl2);
+    };
+    if (hs == 4) walk(std::integral_constant<int, 4>());
+    else if (hs == 8) walk(std::integral_constant<int, 8>());
+    else walk(std::integral_constant<int, 16>());
   } else {
     __syncthreads();
     run_pipeline<D, 1>(
@@ -299,7 +397,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 4
     const int tok = a.v.perm[pos], it = a.v.tok_item[pos];
     const int b0 = a.v.slc_batch[it], nb = a.v.slc_batch[it + 1] - b0;
     int32_t *row = a.idx + ((size_t)tok * a.v.Hkv + g) * a.v.T;
-    if (s_max <= 512) topk_wave_bits<8>(S + (size_t)slot * s_max, nb, a.v.T, b0, row);
+    if (s_max <= 64) topk_wave_bits<1>(S + (size_t)slot * s_max, nb, a.v.T, b0, row);
+    else if (s_max <= 128) topk_wave_bits<2>(S + (size_t)slot * s_max, nb, a.v.T, b0, row);
+    else if (s_max <= 256) topk_wave_bits<4>(S + (size_t)slot * s_max, nb, a.v.T, b0, row);
+    else if (s_max <= 512) topk_wave_bits<8>(S + (size_t)slot * s_max, nb, a.v.T, b0, row);
     else if (s_max <= 1024) topk_wave_bits<16>(S + (size_t)slot * s_max, nb, a.v.T, b0, row);
     else topk_wave_u32(S + (size_t)slot * s_max, nb, a.v.T, b0, row, sel);
   }
@@ -319,35 +420,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 4
   QRows<D, CB> q;
   load_rows<D, CB>(a.Q, a.v, wg_pos0, g, q);
   int lo[CB], hi[CB];
-  bool act[CB], on[CB];
-  const float slack = 8.0f / a.v.sl2;
+  bool on[CB];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     const int w = q.valid[cb] ? a.v.tok_win[q.pos[cb]] : 0;
     lo[cb] = q.valid[cb] ? a.v.win_start[w] : 0;
     hi[cb] = q.valid[cb] ? a.v.win_start[w + 1] : 0;
-    act[cb] = true;
     on[cb] = q.valid[cb];
   }
   int rs, re;
   bool uniform;
   wg_range<CB>(ints, lo, hi, q.valid, rs, re, uniform);
-  if (threadIdx.x == 0) { ints[4] = rs; ints[5] = re; }
+  if (threadIdx.x == 0) { ints[4] = rs; ints[5] = re; ints[6] = 0; }
   __syncthreads();
   TileSrc<2> src{{a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D}, (uint32_t)(a.v.Hkv * D)};
   FwdState<D, CB> st;
-  init_state(st);
-  const bf16x8 ones = ones_operand();
-  const float sl2 = a.v.sl2;
-  const typename PTile<D>::Lanes ln = PTile<D>::lanes();
-  run_pipeline<D, 2>(
-      src, stage0, ints + 4, ints + 5, re > rs ? 1 : 0, [](int) {},
-      [&](const bf16_t *stg, int kb, int) {
-        if (uniform && kb >= rs && kb + 32 <= re)
-          fwd_tile<D, CB, false>(st, q, (lds_cptr)L::row_tile((bf16_t *)stg, 0), (lds_cptr)L::row_tile((bf16_t *)stg, 1), ln, kb, lo, hi, on, act, sl2, slack, ones);
-        else
-          fwd_tile<D, CB, true>(st, q, (lds_cptr)L::row_tile((bf16_t *)stg, 0), (lds_cptr)L::row_tile((bf16_t *)stg, 1), ln, kb, lo, hi, on, act, sl2, slack, ones);
-      });
+  fwd_walk<D, CB>(st, q, src, stage0, ints + 4, rs, re, uniform, lo, hi, on, a.v.sl2);
   float lse2[CB];
   finish<D, CB>(a, st, 2, q, lse2);
 }

@@ -319,11 +319,23 @@ __device__ inline void run_pipeline(const TileSrc<NROW> &src, bf16_t *stage0, co
   __syncthreads();
 }
 
+// Maximum over the wavefront, uniform (row permutations inside 16 lanes, then register swaps).
+__device__ inline uint32_t wave_max_dpp(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));   // xor 1
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));   // xor 2
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));  // half-row mirror
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));  // row mirror
+  auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max((uint32_t)r[0], (uint32_t)r[1]);
+  r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return __builtin_amdgcn_readfirstlane((int)max((uint32_t)r[0], (uint32_t)r[1]));
+}
+
 // Top-k over unsigned fixed-point scores S[0..n) held in LDS by one wavefront, ties to the lowest index, entirely in
 // registers and wave ballots (no lane exchange, no LDS traffic inside the search).  Lane l keeps entries l, l+64, ...
 // (up to R per lane, n <= 64*R).  The T-th largest value is found by building it bit by bit from the top: a
 // candidate threshold is kept when at least T entries reach it (one compare + ballot + population count per
-// register and bit).  Entries above the threshold are selected, entries equal to it in ascending index order until
+// register and bit), and the search ends at the bit where exactly T do.  Entries above the threshold are selected, entries equal to it in ascending index order until
 // T are reached.  Writes T ids (base + index) in ascending order, padded with -1.
 template <int R>
 __device__ inline void topk_wave_bits(const uint32_t *S, int n, int T, int base, int32_t *out) {
@@ -338,12 +350,18 @@ __device__ inline void topk_wave_bits(const uint32_t *S, int n, int T, int base,
   const int Tn = T < n ? T : n;
   uint32_t thr = 0u;
   if (Tn > 0) {
-    for (int b = 31; b >= 0; --b) {
+    // from the highest bit any entry has down to the bit that separates exactly Tn entries from the rest
+    uint32_t top = val[0];
+#pragma unroll
+    for (int r = 1; r < R; ++r) top = max(top, val[r]);
+    top = wave_max_dpp(top);
+    for (int b = 31 - __builtin_clz(top); b >= 0; --b) {
       const uint32_t cand = thr | (1u << b);
       int cnt = 0;
 #pragma unroll
       for (int r = 0; r < R; ++r) cnt += __popcll(__ballot(val[r] >= cand));
       if (cnt >= Tn) thr = cand;
+      if (cnt == Tn) break;
     }
   }
   int greater = 0;
