@@ -39,7 +39,7 @@ def algorithmic_flops(wl, blk_arrays, idx):
 # bench.py kernel name -> kernel name prefix in the rocprofv3 summaries
 ROCPROF_NAME = {
     "cmp_fwd_scores_topk": "m_cmp_fwd<", "slc_fwd": "m_slc_fwd_bc<", "win_fwd": "m_win_fwd<",
-    "bwd_dq_cmp_win": "m_bwd_dq<{d},", "bwd_dq_slc": "m_bwd_dq_bc<{d},",
+    "bwd_dq_cmp_win": "m_bwd_dq<{d},", "bwd_dq_slc": "m_bwd_dq_bc<{d},", "bwd_slc": "m_slc_bwd<{d},",
     "bwd_dkv_win": "m_bwd_dkv<{d}, {kb}, 0,", "bwd_dkv_slc": "m_bwd_dkv<{d}, {kb}, 1,", "bwd_dkv_cmp": "m_bwd_dkv<{d}, {kb}, 2,",
 }
 
@@ -563,6 +563,7 @@ def bench_workload(name, args, steps, warmup, cpu_seconds):
     kflops = {
         "cmp_fwd_scores_topk": 4 * d * pairs["cmp"], "slc_fwd": 4 * d * pairs["slc"], "win_fwd": 4 * d * pairs["win"],
         "bwd_dq_cmp_win": 6 * d * (pairs["cmp"] + pairs["win"]), "bwd_dq_slc": 6 * d * pairs["slc"], "bwd_dkv_cmp": 4 * d * pairs["cmp"], "bwd_dkv_slc": 4 * d * pairs["slc"],
+        "bwd_slc": 10 * d * pairs["slc"],  # both in one pass (head_dim 32, 64)
         "bwd_dkv_win": 4 * d * pairs["win"], "generic_path": (14 if bwd else 4) * d * all_pairs,
     }
     dom = max(kern_ms, key=kern_ms.get) if kern_ms else None

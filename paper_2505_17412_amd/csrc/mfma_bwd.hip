@@ -8,8 +8,8 @@
 // Three kernel families, all free of floating-point atomics (results do not depend on scheduling):
 //   * m_bwd_dq: query-centric, same walk as the forward kernels (transposed scores, keys in the lanes), for the
 //     compression and window branches;
-//   * m_bwd_dq_bc: the selection branch's dQ, block-centric like its forward kernel (one partial dQ row per selected
-//     block, added per token in rank order by m_dq_merge);
+//   * m_slc_bwd: the selection branch, block-centric like its forward kernel: dK, dV and one partial dQ row per selected
+//     block, added per token in rank order by m_dq_merge; at head_dim 128 two kernels, m_bwd_dq_bc and m_bwd_dkv;
 //   * m_bwd_dkv: key-centric; a wavefront owns 16*KB keys and streams the query rows that attend to them
 //     (scores with the query rows in the lanes); the contractions over query rows take Q^T and dO^T from the
 //     staged row-major tiles through the transposing LDS read.
@@ -608,10 +608,14 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   }
   {
     ProfScope ps(PROF_BWD_INVERT, s);
-    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, false, true, true, s);
+    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, false, !slc_bwd_fused(D), true, s);
     if (rc != SSA_OK) return rc;
   }
-  {
+  if constexpr (slc_bwd_fused(D)) {
+    ProfScope ps1(PROF_BWD_SLC, s);
+    const int rc = slc_bwd_kernel(v, D, w, blk->slc_tok_max, s);
+    if (rc != SSA_OK) return rc;
+  } else {
     ProfScope ps1(PROF_BWD_DQ, s);
     const int rc = slc_dq_kernel(v, D, w, s);
     if (rc != SSA_OK) return rc;
@@ -630,7 +634,7 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   static std::once_flag dkv_once;
   std::call_once(dkv_once, [] {
     (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_WIN, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if constexpr (!slc_bwd_fused(D)) (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_CMP, DKV_WAVES_CMP, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   });
   DkvArgs base{v, w.Qs, nullptr, nullptr, nullptr, w.sel.start, w.sel.list,
@@ -642,16 +646,13 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     a.tiles_per_block = (blk->win_tok_max + WG_KEYS - 1) / WG_KEYS;
     m_bwd_dkv<D, KB_KEYS, DKV_WIN, DKV_WAVES, ST><<<dim3(blk->Nw * a.tiles_per_block, Hkv), 64 * DKV_WAVES, dkv_lds, s>>>(a);
   }
-  {
+  if constexpr (!slc_bwd_fused(D)) {
     ProfScope ps(PROF_BWD_DKV_SLC, s);
     DkvArgs a = base;
     a.lse2s = w.lse2s + NH; a.deltas = w.deltag + NH; a.dOs = w.dOg + NH * D;
     a.dK = w.pK; a.dV = w.pV;
     a.tiles_per_block = (blk->slc_tok_max + WG_KEYS - 1) / WG_KEYS;
     m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST><<<dim3((w.max_chunks + 7) / 8 * 8 * a.tiles_per_block), 64 * DKV_WAVES, dkv_lds, s>>>(a);
-    const size_t items = (size_t)N * Hkv * (D / 4);
-    m_slc_reduce<<<(unsigned)((items + 255) / 256), 256, 0, s>>>(blk->tok_slc, v.slc_start, w.sel.chunk_start, w.sel.part_row_start, N,
-                                                                 Hkv, v.Ns, D, w.pK, w.pV, w.dKs, w.dVs);
   }
   {
     ProfScope ps(PROF_BWD_DKV_CMP, s);
@@ -664,6 +665,9 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   }
   {
     ProfScope ps(PROF_BWD_FINISH, s);
+    const size_t items = (size_t)N * Hkv * (D / 4);
+    m_slc_reduce<<<(unsigned)((items + 255) / 256), 256, 0, s>>>(blk->tok_slc, v.slc_start, w.sel.chunk_start, w.sel.part_row_start, N,
+                                                                 Hkv, v.Ns, D, w.pK, w.pV, w.dKs, w.dVs);
     m_bwd_finish<<<v.Nc, 128, 0, s>>>(v.perm, v.cmp_start, v.Nc, row, w.q_splits, w.dKs, w.dVs, w.dKc, w.dVc, (bf16_t *)dk,
                                       (bf16_t *)dv, w.dKc_out, w.dVc_out);
   }

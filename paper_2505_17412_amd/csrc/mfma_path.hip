@@ -164,9 +164,12 @@ BwdPlan bwd_plan(const ssa_ctx &c) {
   p.sel = take(sel_index_bytes(c.N, c.Hkv, c.T, b->Ns));
   // selection-branch work chunks: every (g, block) list is cut into pieces of chunk_len query tokens whose partial
   // dK/dV are summed afterwards in a fixed order.  Bounds: chunks <= entries/chunk_len + keys; partial rows <=
-  // slc_tok_max * entries/chunk_len + N*Hkv.  chunk_len grows until the partial sums fit in about 1 GiB.
+  // slc_tok_max * entries/chunk_len + N*Hkv.  A chunk is one workgroup.  The one-pass kernel wants some thousands of them, so
+  // that the last ones to end leave few compute units idle, and chunks of 512 rather than 256 once there are enough (half the
+  // partial dK and dV rows: 256 and 512 tokens took 527 and 616 us at 21 k tokens, 1430 and 1407 at 65 k; 1024 was slower).  The
+  // two-kernel form (d = 128) measured best at 1024.  chunk_len grows until the partial sums fit in about 1 GiB.
   const size_t entries = (size_t)c.N * c.Hkv * c.T;
-  p.chunk_len = 1024;
+  p.chunk_len = !slc_bwd_fused(c.d) ? 1024 : entries / 256 < 4096 ? 256 : 512;
   size_t rows;
   for (;;) {
     rows = (size_t)b->slc_tok_max * (entries / p.chunk_len + 1) + (size_t)c.N * c.Hkv;
@@ -175,7 +178,7 @@ BwdPlan bwd_plan(const ssa_ctx &c) {
   }
   p.max_chunks = (int)(entries / p.chunk_len + keys + 1);
   p.pk = take(rows * c.d * 4); p.pv = take(rows * c.d * 4);
-  p.pdq = take((size_t)c.N * c.Hkv * c.T * c.hs * c.d * 2);  // one partial dQ row per (token, query head, selected block)
+  p.pdq = take(((size_t)c.N * c.Hkv * c.T * c.hs + 1) * c.d * 2);  // one partial dQ row per (token, query head, selected block), one spare
   p.total = off;
   return p;
 }

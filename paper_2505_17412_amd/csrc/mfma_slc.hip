@@ -557,12 +557,8 @@ int slc_merge_kernel(const MfmaView &v, int D, const SlcPartials &part, const in
 }
 
 int slc_dq_kernel(const MfmaView &v, int D, const BwdBuffers &w, hipStream_t s) {
-  switch (D) {
-    case 32: return launch_slc_dq<32>(v, w, s);
-    case 64: return launch_slc_dq<64>(v, w, s);
-    case 128: return launch_slc_dq<128>(v, w, s);
-    default: return SSA_ERR_UNSUPPORTED;
-  }
+  static_assert(!slc_bwd_fused(128), "the head_dim this kernel is for");
+  return D == 128 ? launch_slc_dq<128>(v, w, s) : SSA_ERR_UNSUPPORTED;
 }
 
 int slc_dq_merge_kernel(const MfmaView &v, int D, const BwdBuffers &w, const int32_t *idx, void *dq, hipStream_t s) {
