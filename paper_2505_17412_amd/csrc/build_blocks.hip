@@ -664,6 +664,11 @@ extern "C" int ssa_blocks_export(const ssa_blocks_t *b, int which, void *dst, si
   }
   if (bytes < n * sizeof(int32_t)) return SSA_ERR_WORKSPACE;
   if (n == 0) return SSA_OK;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev != b->device) {  // a kernel reaches another device's memory only with peer access
+    SSA_HIP_TRY(hipMemcpyAsync(dst, src, n * sizeof(int32_t), hipMemcpyDeviceToDevice, (hipStream_t)stream));
+    return SSA_OK;
+  }
   const size_t wgs = (n + 1023) / 1024;
   k_copy<<<(unsigned)(wgs < 1024 ? wgs : 1024), 256, 0, (hipStream_t)stream>>>(src, n, (int32_t *)dst);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;

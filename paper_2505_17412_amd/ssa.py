@@ -169,6 +169,7 @@ class Blocks:
         if self.handle:
             lib().ssa_blocks_destroy(self.handle)
             self.handle = None
+            self._counts = self._sizes = None
 
     def __del__(self):
         try:

@@ -31,3 +31,16 @@ def test_kept_memory_is_safe_across_handles():
     for wl, blk in zip(wls[:3], alive):
         ref = build_blocks(wl.coords, wl.batch_offsets, wl.grid, wl.m_cmp, wl.m_slc, wl.m_win)
         assert np.array_equal(blk.export("perm").cpu().numpy(), ref.perm)
+
+
+def test_destroyed_handle_is_refused():
+    """A destroyed handle reports no counts and exports nothing, whatever was asked of it before."""
+    wl = inputs.random_points_workload(77, 16, (300,), 2, 1, 32, (4, 8, 8), 2, "f32")
+    _, blk = util.build_blocks_gpu(wl)
+    assert blk.counts()[0] > 0
+    blk.export("perm")
+    blk.destroy()
+    with pytest.raises(Exception):
+        blk.counts()
+    with pytest.raises(Exception):
+        blk.export("perm")
