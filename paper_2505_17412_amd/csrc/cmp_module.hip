@@ -16,11 +16,18 @@
 // the same kernel on mirrored offsets with the weights read the other way round; the weight gradient contracts
 // over tokens, its two operands come from row-major LDS tiles through the transposing LDS read.  No floating
 // point atomics anywhere: partial sums are written per chunk and added in a fixed order.
+//
+// A layer runs the module on its keys and on its values: every launch takes one or two tensors (blockIdx.z), which
+// share the neighbour table and together fill the chip where one alone does not.
 #include "mfma_common.h"
 #include "mfma_qc.h"
 #include "profile.h"
+#include "cmp_internal.h"
 
 namespace {
+
+// one entry per tensor of a launch; blockIdx.z picks it
+template <class T> struct Pair { T v[2]; };
 
 __device__ inline uint32_t compact3(uint64_t v64) {  // bits 0,3,6,.. of v -> bits 0,1,2,..
   uint32_t v = (uint32_t)v64 & 0x09249249u;
@@ -70,8 +77,10 @@ __global__ void c_neighbors(const uint64_t *__restrict__ keys, const int32_t *__
 }
 
 // U[pos] = x[perm[pos]] + PE[place of the token inside its block]   (bf16, sorted order)
-__global__ void c_add_pe(const bf16_t *__restrict__ x, const bf16_t *__restrict__ pe, const int32_t *__restrict__ perm,
-                         const uint64_t *__restrict__ keys, int N, int C, int bits, int m, bf16_t *__restrict__ U) {
+__global__ void c_add_pe(Pair<const bf16_t *> xs, Pair<const bf16_t *> pes, const int32_t *__restrict__ perm,
+                         const uint64_t *__restrict__ keys, int N, int C, int bits, int m, Pair<bf16_t *> Us) {
+  const bf16_t *__restrict__ x = xs.v[blockIdx.z], *__restrict__ pe = pes.v[blockIdx.z];
+  bf16_t *__restrict__ U = Us.v[blockIdx.z];
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int per = C / 8;
   if (i >= (size_t)N * per) return;
@@ -86,7 +95,9 @@ __global__ void c_add_pe(const bf16_t *__restrict__ x, const bf16_t *__restrict_
 }
 
 // Wt[o][c_out][c_in] = w[o][c_in][c_out]
-__global__ void c_transpose_w(const bf16_t *__restrict__ w, int C, bf16_t *__restrict__ wt) {
+__global__ void c_transpose_w(Pair<const bf16_t *> ws, int C, Pair<bf16_t *> wts) {
+  const bf16_t *__restrict__ w = ws.v[blockIdx.z];
+  bf16_t *__restrict__ wt = wts.v[blockIdx.z];
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (size_t)27 * C * C) return;
   const int ci = (int)(i % C), co = (int)(i / C % C), o = (int)(i / ((size_t)C * C));
@@ -96,10 +107,12 @@ __global__ void c_transpose_w(const bf16_t *__restrict__ w, int C, bf16_t *__res
 // Gather-GEMM: out[pos][n] = bias[n] + sum_o sum_k in[nbr[pos][o']][k] * Bw[o][n][k], o' = o (forward) or 26 - o
 // (data gradient: the token that took `pos` as its neighbour o sits at the mirrored offset).  Bw holds, per offset,
 // a [C][C] matrix with the contraction index contiguous.
+struct ConvSrc { const bf16_t *in, *w, *bias; float *out; };
 template <int C, bool MIRROR, int MT, int NBW>
-__global__ __launch_bounds__(256) void c_conv(const bf16_t *__restrict__ in, const int32_t *__restrict__ nbr,
-                                              const bf16_t *__restrict__ Bw, const bf16_t *__restrict__ bias, int N,
-                                              float *__restrict__ out) {
+__global__ __launch_bounds__(256) void c_conv(Pair<ConvSrc> srcs, const int32_t *__restrict__ nbr, int N) {
+  const ConvSrc cs = srcs.v[blockIdx.z];
+  const bf16_t *__restrict__ in = cs.in, *__restrict__ Bw = cs.w, *__restrict__ bias = cs.bias;
+  float *__restrict__ out = cs.out;
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
   const int pos0 = (blockIdx.x * 4 + wid) * 16 * MT;  // a wavefront owns MT tiles of 16 tokens: every weight operand
   if (pos0 >= N) return;                               // it loads feeds MT matrix instructions
@@ -156,20 +169,22 @@ __global__ __launch_bounds__(256) void c_conv(const bf16_t *__restrict__ in, con
   }
 }
 
-// The same gather-GEMM for C = 128 with both operands staged through LDS: a workgroup owns TOK tokens, wavefront w the
-// output channels 32w .. 32w+31.  Per offset the 128 x 128 weights (32 KB) and the TOK gathered rows are written to LDS
-// once and read by all four wavefronts as conflict-free row-operand reads; the data of the next offset is in flight in
-// registers meanwhile, its row indices taken from a copy of the tile's neighbour table in LDS.  Row r of a 16-row MFMA
-// tile stands for LDS row 8*(r >> 2) + 4*a + (r & 3) of its 32-row tile (a = which half), for tokens and for channels
-// alike; the store at the end undoes that numbering.
-constexpr int CONV_TOK = 128;  // tokens per workgroup of the staged convolution
+// The same gather-GEMM for C = 128: a workgroup owns TOK tokens, wavefront w the output channels 32w .. 32w+31.  Per offset
+// the TOK gathered rows go through LDS (two buffers, one barrier per offset) and are read by all four wavefronts as
+// conflict-free row operands; the weights of a wavefront's channels are nobody else's, so they go from memory straight into
+// its operand registers.  Rows and weights of the next offset are in flight during the products of this one, the row indices
+// taken from a copy of the tile's neighbour table in LDS.  Row r of a 16-row MFMA tile stands for LDS row
+// 8*(r >> 2) + 4*a + (r & 3) of its 32-row tile (a = which half), for tokens and for channels alike; the store at the end
+// undoes that numbering.
+// Bound: LDS operand reads (one per two matrix instructions) and their latency; about half of the gathered rows of a surface
+// are zeros.  Keys and values of 10.7 k tokens: 118 us in two launches of 83 workgroups, weights through LDS -> 66 us.
 template <bool MIRROR, int TOK>
-__global__ __launch_bounds__(256) void c_conv128(const bf16_t *__restrict__ in, const int32_t *__restrict__ nbr,
-                                                 const bf16_t *__restrict__ Bw, const bf16_t *__restrict__ bias, int N,
-                                                 float *__restrict__ out) {
+__global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32_t *__restrict__ nbr, int N) {
   constexpr int C = 128, MT = TOK / 16, AI = TOK / 16;  // AI: gathered 16-byte items per thread (TOK x 16 / 256)
   using G = TileGeom<C>;
-  __shared__ __align__(16) bf16_t sw[4 * G::ROW_ELEMS], sa[(TOK / 32) * G::ROW_ELEMS];
+  const ConvSrc cs = srcs.v[blockIdx.z];
+  const bf16_t *__restrict__ in = cs.in, *__restrict__ Bw = cs.w;
+  __shared__ __align__(16) bf16_t sa[2][(TOK / 32) * G::ROW_ELEMS];
   __shared__ int any_flag[27];
   __shared__ int32_t snbr[TOK * 27];
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
@@ -187,15 +202,16 @@ __global__ __launch_bounds__(256) void c_conv128(const bf16_t *__restrict__ in, 
   f32x4 acc[MT][2];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) acc[mt][0] = acc[mt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // staging roles: the weights are 128 rows x 16 segments = 2048 items (8 per thread), the gathered rows TOK x 16
-  bf16x8 rw[8], ra[AI];
-  auto fetch = [&](int o) {
-    const bf16_t *Bo = Bw + (size_t)o * C * C;
+  struct Weights { bf16x8 v[2][C / 32]; };
+  Weights wa, wb;
+  bf16x8 ra[AI];
+  const int wrow = 32 * wid + 8 * (n >> 2) + (n & 3);  // channel of half 0; half 1 is 4 further
+  auto fetch = [&](int o, Weights &w) {
+    const bf16_t *Bo = Bw + (size_t)o * C * C + (size_t)wrow * C + 8 * quad;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int it = threadIdx.x + 256 * i;
-      rw[i] = ld8(Bo + (size_t)(it / 16) * C + 8 * (it % 16));
-    }
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int ks = 0; ks < C / 32; ++ks) w.v[a][ks] = ld8(Bo + 4 * a * C + 32 * ks);
     const int oo = MIRROR ? 26 - o : o;
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
@@ -204,67 +220,77 @@ __global__ __launch_bounds__(256) void c_conv128(const bf16_t *__restrict__ in, 
       ra[i] = src >= 0 ? ld8(in + (size_t)src * C + 8 * (it % 16)) : zero8();
     }
   };
-  int o = 0;
-  while (o < 27 && !any_flag[o]) ++o;
-  if (o < 27) fetch(o);
-  while (o < 27) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int it = threadIdx.x + 256 * i, row = it / 16;
-      *reinterpret_cast<bf16x8 *>(sw + (row >> 5) * G::ROW_ELEMS + G::row_off(row & 31, it % 16)) = rw[i];
-    }
+  auto next = [&](int o) {
+    while (o < 27 && !any_flag[o]) ++o;
+    return o;
+  };
+  // one offset: its rows (in registers) to LDS buffer `buf`, the next offset's operands requested, the products
+  auto step = [&](int &o, int buf, Weights &cur, Weights &nxt) {
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
       const int it = threadIdx.x + 256 * i, row = it / 16;
-      *reinterpret_cast<bf16x8 *>(sa + (row >> 5) * G::ROW_ELEMS + G::row_off(row & 31, it % 16)) = ra[i];
+      *reinterpret_cast<bf16x8 *>(sa[buf] + (row >> 5) * G::ROW_ELEMS + G::row_off(row & 31, it % 16)) = ra[i];
     }
-    __syncthreads();
-    int nxt = o + 1;
-    while (nxt < 27 && !any_flag[nxt]) ++nxt;
-    if (nxt < 27) fetch(nxt);
+    __syncthreads();  // (the other buffer was last read before this barrier)
+    o = next(o + 1);
+    if (o < 27) fetch(o, nxt);
 #pragma unroll
-    for (int ks = 0; ks < C / 32; ++ks) {
-      const bf16x8 b0 = lds_row_operand<C>(sw + wid * G::ROW_ELEMS, 0, ks), b1 = lds_row_operand<C>(sw + wid * G::ROW_ELEMS, 1, ks);
+    for (int ks = 0; ks < C / 32; ++ks)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        const bf16x8 av = lds_row_operand<C>(sa + (mt >> 1) * G::ROW_ELEMS, mt & 1, ks);
-        acc[mt][0] = mfma16(av, b0, acc[mt][0]);
-        acc[mt][1] = mfma16(av, b1, acc[mt][1]);
+        const bf16x8 av = lds_row_operand<C>(sa[buf] + (mt >> 1) * G::ROW_ELEMS, mt & 1, ks);
+        acc[mt][0] = mfma16(av, cur.v[0][ks], acc[mt][0]);
+        acc[mt][1] = mfma16(av, cur.v[1][ks], acc[mt][1]);
       }
-    }
-    __syncthreads();
-    o = nxt;
+  };
+  int o = next(0);
+  if (o < 27) fetch(o, wa);
+  while (o < 27) {
+    step(o, 0, wa, wb);
+    if (o >= 27) break;
+    step(o, 1, wb, wa);
   }
   // lane: column n of half a -> channel 32*wid + 8*(n >> 2) + 4*a + (n & 3); rows 4*quad + i of tile mt -> token
   // pos0 + 32*(mt >> 1) + 8*quad + 4*(mt & 1) + i
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
-    const int ch = 32 * wid + 8 * (n >> 2) + 4 * a + (n & 3);
-    const float bs = bias ? bf16_to_f32(bias[ch]) : 0.f;
+    const int ch = wrow + 4 * a;
+    const float bs = cs.bias ? bf16_to_f32(cs.bias[ch]) : 0.f;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int t = pos0 + 32 * (mt >> 1) + 8 * quad + 4 * (mt & 1) + i;
-        if (t < N) out[(size_t)t * C + ch] = acc[mt][a][i] + bs;
+        if (t < N) cs.out[(size_t)t * C + ch] = acc[mt][a][i] + bs;
       }
   }
 }
 
 // Mean over the tokens of each compression block (contiguous in sorted order); one workgroup per block.
-__global__ void c_pool(const float *__restrict__ Y, const int32_t *__restrict__ cmp_start, int C, bf16_t *__restrict__ xc) {
+__global__ void c_pool(Pair<const float *> Ys, const int32_t *__restrict__ cmp_start, int C, Pair<bf16_t *> xcs) {
+  const float *__restrict__ Y = Ys.v[blockIdx.z];
   const int c = blockIdx.x, b = cmp_start[c], e = cmp_start[c + 1];
   const float inv = 1.0f / (float)(e - b);  // same arithmetic as the plain mean pool of the attention path
   for (int f = threadIdx.x; f < C; f += blockDim.x) {
     float s = 0.f;
-    for (int pos = b; pos < e; ++pos) s += Y[(size_t)pos * C + f];
-    xc[(size_t)c * C + f] = f32_to_bf16(s * inv);
+    int pos = b;
+    for (; pos + 8 <= e; pos += 8) {  // eight rows in flight; the order of the additions stays
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = Y[(size_t)(pos + u) * C + f];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; pos < e; ++pos) s += Y[(size_t)pos * C + f];
+    xcs.v[blockIdx.z][(size_t)c * C + f] = f32_to_bf16(s * inv);
   }
 }
 
 // dY[pos] = dXc[block(pos)] / count(block)   (bf16, sorted order): gradient of the mean pool
-__global__ void c_expand(const float *__restrict__ dxc, const int32_t *__restrict__ tok_cmp,
-                         const int32_t *__restrict__ cmp_start, int N, int C, bf16_t *__restrict__ dY) {
+__global__ void c_expand(Pair<const float *> dxcs, const int32_t *__restrict__ tok_cmp,
+                         const int32_t *__restrict__ cmp_start, int N, int C, Pair<bf16_t *> dYs) {
+  const float *__restrict__ dxc = dxcs.v[blockIdx.z];
+  bf16_t *__restrict__ dY = dYs.v[blockIdx.z];
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int per = C / 8;
   if (i >= (size_t)N * per) return;
@@ -280,7 +306,9 @@ __global__ void c_expand(const float *__restrict__ dxc, const int32_t *__restric
 // dbias[f] = sum over blocks of dXc[c][f]  (the pool's 1/count and the block's count cancel): partial sums over
 // DBIAS_PARTS row ranges, added in order by c_sum_parts.
 constexpr int DBIAS_PARTS = 32;
-__global__ void c_dbias_partial(const float *__restrict__ dxc, int Nc, int C, float *__restrict__ part) {
+__global__ void c_dbias_partial(Pair<const float *> dxcs, int Nc, int C, Pair<float *> parts) {
+  const float *__restrict__ dxc = dxcs.v[blockIdx.z];
+  float *__restrict__ part = parts.v[blockIdx.z];
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= C) return;
   const int per = (Nc + DBIAS_PARTS - 1) / DBIAS_PARTS;
@@ -291,7 +319,9 @@ __global__ void c_dbias_partial(const float *__restrict__ dxc, int Nc, int C, fl
 }
 
 // dx[perm[pos]] += dU[pos]   (caller order, parameter dtype)
-__global__ void c_dx_accum(const float *__restrict__ dU, const int32_t *__restrict__ perm, int N, int C, bf16_t *dx) {
+__global__ void c_dx_accum(Pair<const float *> dUs, const int32_t *__restrict__ perm, int N, int C, Pair<bf16_t *> dxs) {
+  const float *__restrict__ dU = dUs.v[blockIdx.z];
+  bf16_t *dx = dxs.v[blockIdx.z];
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int per = C / 8;
   if (i >= (size_t)N * per) return;
@@ -306,17 +336,30 @@ __global__ void c_dx_accum(const float *__restrict__ dU, const int32_t *__restri
 
 // dPE, first stage: the tokens of chunk blockIdx.x are visited in order, thread f owns channel f of every table row
 // (LDS [m^3][C] fp32), so no two threads ever add to the same cell.
-__global__ void c_dpe_partial(const float *__restrict__ dU, const uint64_t *__restrict__ keys, int N, int C, int bits, int m,
-                              int chunk, float *__restrict__ part) {
+__global__ void c_dpe_partial(Pair<const float *> dUs, const uint64_t *__restrict__ keys, int N, int C, int bits, int m,
+                              int chunk, Pair<float *> parts) {
   extern __shared__ float tbl[];
+  const float *__restrict__ dU = dUs.v[blockIdx.z];
+  float *__restrict__ part = parts.v[blockIdx.z];
   const int rows = m * m * m;
   for (int i = threadIdx.x; i < rows * C; i += blockDim.x) tbl[i] = 0.f;
   __syncthreads();
   const int b = blockIdx.x * chunk, e = min(N, b + chunk);
-  for (int pos = b; pos < e; ++pos) {
-    const Site s = decode(keys[pos], bits);
-    const int p = ((s.x & (m - 1)) * m + (s.y & (m - 1))) * m + (s.z & (m - 1));
-    for (int f = threadIdx.x; f < C; f += blockDim.x) tbl[p * C + f] += dU[(size_t)pos * C + f];
+  for (int p0 = b; p0 < e; p0 += 8) {  // eight tokens' rows in flight, added in token order
+    int row[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const Site s = decode(keys[min(p0 + u, e - 1)], bits);
+      row[u] = (((s.x & (m - 1)) * m + (s.y & (m - 1))) * m + (s.z & (m - 1))) * C;
+    }
+    for (int f = threadIdx.x; f < C; f += blockDim.x) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = dU[(size_t)min(p0 + u, e - 1) * C + f];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (p0 + u < e) tbl[row[u] + f] += v[u];
+    }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < rows * C; i += blockDim.x) part[(size_t)blockIdx.x * rows * C + i] = tbl[i];
@@ -325,65 +368,117 @@ __global__ void c_dpe_partial(const float *__restrict__ dU, const uint64_t *__re
 // Ordered sum of partial results: out[g][i] = sum of part[g*group + j][i], j = 0 .. group-1 (parts past n_parts are
 // skipped).  One launch with group = n_parts gives the total; two launches (group, then the group results) keep
 // the work parallel when there are many parts.  The order of the additions is fixed either way.
-__global__ void c_sum_parts(const float *__restrict__ part, int n_parts, int n_groups, size_t len, float *__restrict__ out) {
+__global__ void c_sum_parts(Pair<const float *> parts, int n_parts, int n_groups, size_t len, Pair<float *> outs) {
+  const float *__restrict__ part = parts.v[blockIdx.z];
+  float *__restrict__ out = outs.v[blockIdx.z];
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= len) return;
   const int group = (n_parts + n_groups - 1) / n_groups;
   const int g = blockIdx.y, b = g * group, e = min(n_parts, b + group);
   float s = 0.f;
+#pragma unroll 8
   for (int k = b; k < e; ++k) s += part[(size_t)k * len + i];
   out[(size_t)g * len + i] = s;
 }
 
 // Weight gradient: dW[o][ci][co] = sum_pos U[nbr[pos][o]][ci] * dY[pos][co], a contraction over tokens.  A workgroup
-// takes one offset, one chunk of tokens and one CT x CT tile of the C x C matrix; 32-token tiles of the gathered U
-// rows and of dY go through LDS row-major, both MFMA operands are transposing LDS reads of them.  Wave w owns the
-// 16-row blocks w, w+4, .. of the tile.
+// takes one offset, one chunk of tokens and one CT x CT tile of the C x C matrix.  The tokens of a segment that have a
+// neighbour at the offset are listed first (in order, by ballots): on a surface that is about half of them, and the others
+// add nothing.  32-row tiles of the listed U and dY rows go through LDS row-major (two buffers, one barrier per tile, the
+// next tile's rows in flight), both MFMA operands are transposing LDS reads of them.  Wave w owns the 16-row blocks w, w+4,
+// .. of the tile.
+// Bound: latency of the gathers, so 1024 tokens per workgroup where that fills the chip (see mod_plan).  Keys and values of
+// 10.7 k tokens: 180 us (every token multiplied, loads not ahead of the products) -> 38 us; the whole module forward,
+// twice forward and once backward in a layer's training step: 2430 -> 1903 us of the step.
+constexpr int DW_SEG = 1024;  // tokens listed at a time
 template <int CT>
-__global__ __launch_bounds__(256) void c_dw(const bf16_t *__restrict__ U, const bf16_t *__restrict__ dY,
-                                            const int32_t *__restrict__ nbr, int N, int C, int chunk,
-                                            float *__restrict__ part) {
+__global__ __launch_bounds__(256) void c_dw(Pair<const bf16_t *> Us, Pair<const bf16_t *> dYs,
+                                            const int32_t *__restrict__ nbr, int N, int C, int chunk, Pair<float *> parts) {
   using G = TileGeom<CT>;
-  __shared__ __align__(16) bf16_t su[G::ROW_ELEMS], sy[G::ROW_ELEMS];
-  const int o = blockIdx.x, s = blockIdx.y, tiles = C / CT;
-  const int ci0 = ((int)blockIdx.z / tiles) * CT, co0 = ((int)blockIdx.z % tiles) * CT;
+  __shared__ __align__(16) bf16_t su[2][G::ROW_ELEMS], sy[2][G::ROW_ELEMS];
+  __shared__ int2 list[DW_SEG];           // (neighbour, token)
+  __shared__ int count[DW_SEG / 256][4];  // listed tokens per round and wavefront
+  const int tiles = C / CT, zt = (int)blockIdx.z % (tiles * tiles), src = (int)blockIdx.z / (tiles * tiles);
+  const bf16_t *__restrict__ U = Us.v[src], *__restrict__ dY = dYs.v[src];
+  const int o = blockIdx.x, s = blockIdx.y;
+  const int ci0 = (zt / tiles) * CT, co0 = (zt % tiles) * CT;
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
   constexpr int MB = CT / 16 / 4 > 0 ? CT / 16 / 4 : 1;  // 16-row blocks per wave
   constexpr int NBK = CT / 16;
-  const bool wave_on = wid < CT / 16;
+  constexpr int NI = G::ROW_ITEMS > 256 ? G::ROW_ITEMS / 256 : 1, SEGS = CT / 8;  // 16-byte items per thread and tile
+  const bool wave_on = wid < CT / 16, stages = (int)threadIdx.x < G::ROW_ITEMS;
   f32x4 acc[MB][NBK];
 #pragma unroll
   for (int a = 0; a < MB; ++a)
 #pragma unroll
     for (int nb = 0; nb < NBK; ++nb) acc[a][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int b = s * chunk, e = min(N, b + chunk);
-  for (int t0 = b; t0 < e; t0 += 32) {
-    for (int it = threadIdx.x; it < G::ROW_ITEMS; it += 256) {
-      const int row = it / (CT / 8), seg = it % (CT / 8);
-      const int pos = t0 + row;
-      const int src = pos < e ? nbr[(size_t)pos * 27 + o] : -1;
-      const bf16x8 xu = src >= 0 ? ld8(U + (size_t)src * C + ci0 + 8 * seg) : zero8();
-      const bf16x8 xy = (pos < e && src >= 0) ? ld8(dY + (size_t)pos * C + co0 + 8 * seg) : zero8();
-      *reinterpret_cast<bf16x8 *>(su + G::row_off(row, seg)) = xu;
-      *reinterpret_cast<bf16x8 *>(sy + G::row_off(row, seg)) = xy;
+  int buf = 0;
+  for (int s0 = b; s0 < e; s0 += DW_SEG) {
+    int nb_of[DW_SEG / 256];
+    uint64_t has[DW_SEG / 256];
+#pragma unroll
+    for (int r = 0; r < DW_SEG / 256; ++r) {
+      const int pos = s0 + 256 * r + (int)threadIdx.x;
+      nb_of[r] = pos < e ? nbr[(size_t)pos * 27 + o] : -1;
     }
+#pragma unroll
+    for (int r = 0; r < DW_SEG / 256; ++r) {
+      has[r] = __ballot(nb_of[r] >= 0);
+      if (lane == 0) count[r][wid] = __popcll(has[r]);
+    }
+    __syncthreads();  // (the list of the segment before was last read before its last barrier)
+    int total = 0;
+#pragma unroll
+    for (int r = 0; r < DW_SEG / 256; ++r)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (w == wid && nb_of[r] >= 0)
+          list[total + __popcll(has[r] & ((1ull << lane) - 1ull))] = make_int2(nb_of[r], s0 + 256 * r + (int)threadIdx.x);
+        total += count[r][w];
+      }
     __syncthreads();
-    if (wave_on) {
-      bf16x8 av[MB];
+    bf16x8 xu[NI], xy[NI];
+    auto fetch = [&](int t0) {
 #pragma unroll
-      for (int a = 0; a < MB; ++a) av[a] = lds_tr_operand<CT>(su, wid + 4 * a);
+      for (int i = 0; i < NI; ++i) {
+        const int it = threadIdx.x + 256 * i, row = t0 + it / SEGS, seg = it % SEGS;
+        xu[i] = xy[i] = zero8();
+        if (stages && row < total) {
+          const int2 l = list[row];
+          xu[i] = ld8(U + (size_t)l.x * C + ci0 + 8 * seg);
+          xy[i] = ld8(dY + (size_t)l.y * C + co0 + 8 * seg);
+        }
+      }
+    };
+    fetch(0);
+    for (int t0 = 0; t0 < total; t0 += 32, buf ^= 1) {
 #pragma unroll
-      for (int nb = 0; nb < NBK; ++nb) {
-        const bf16x8 bv = lds_tr_operand<CT>(sy, nb);
+      for (int i = 0; i < NI; ++i) {
+        const int it = threadIdx.x + 256 * i;
+        if (stages) {
+          *reinterpret_cast<bf16x8 *>(su[buf] + G::row_off(it / SEGS, it % SEGS)) = xu[i];
+          *reinterpret_cast<bf16x8 *>(sy[buf] + G::row_off(it / SEGS, it % SEGS)) = xy[i];
+        }
+      }
+      __syncthreads();  // (the other buffer was last read before this barrier)
+      if (t0 + 32 < total) fetch(t0 + 32);
+      if (wave_on) {
+        bf16x8 av[MB];
 #pragma unroll
-        for (int a = 0; a < MB; ++a) acc[a][nb] = mfma16(av[a], bv, acc[a][nb]);
+        for (int a = 0; a < MB; ++a) av[a] = lds_tr_operand<CT>(su[buf], wid + 4 * a);
+#pragma unroll
+        for (int nb = 0; nb < NBK; ++nb) {
+          const bf16x8 bv = lds_tr_operand<CT>(sy[buf], nb);
+#pragma unroll
+          for (int a = 0; a < MB; ++a) acc[a][nb] = mfma16(av[a], bv, acc[a][nb]);
+        }
       }
     }
-    __syncthreads();
   }
   if (!wave_on) return;
   // C layout: lane holds column co = 16*nb + n, rows ci = 16*(wid + 4a) + 4*quad + i
-  float *dst = part + ((size_t)s * 27 + o) * C * C;
+  float *dst = parts.v[src] + ((size_t)s * 27 + o) * C * C;
 #pragma unroll
   for (int a = 0; a < MB; ++a)
 #pragma unroll
@@ -395,35 +490,46 @@ __global__ __launch_bounds__(256) void c_dw(const bf16_t *__restrict__ U, const 
 
 constexpr int PE_GROUPS = 32;  // first-level groups of the ordered dPE sum
 
+// Workspace of a pass over n tensors; per-tensor arrays lie one after the other.  The inputs (neighbour table and U) have a
+// region of their own: a backward pass that follows a recomputed forward pass finds them there.
 struct ModPlan {
-  size_t nbr, u, wt, y, dy, du, pw, ppe, ppe2, pb, total;
+  size_t nbr, u, inputs_total;
+  size_t wt, y, dy, du, pw, ppe, ppe2, pb, total;
+  size_t rows16, rows32, wlen, plen;  // bytes per tensor of [N][C] bf16 / fp32; elements of the weights and of the PE table
   int dw_chunks, dw_chunk, pe_chunks, pe_chunk;
 };
 
-ModPlan mod_plan(int N, int C, int m, bool backward) {
+ModPlan mod_plan(int N, int C, int m, int n, bool backward) {
   ModPlan p{};
   size_t off = 0;
-  auto take = [&](size_t n) { size_t r = off; off += align_up(n, 256); return r; };
+  auto take = [&](size_t b) { size_t r = off; off += align_up(b, 256); return r; };
+  p.rows16 = align_up((size_t)N * C * 2, 256);
+  p.rows32 = align_up((size_t)N * C * 4, 256);
+  p.wlen = (size_t)27 * C * C;
+  p.plen = (size_t)m * m * m * C;
   p.nbr = take((size_t)N * 27 * 4);
-  p.u = take((size_t)N * C * 2);
+  p.u = take(n * p.rows16);
+  p.inputs_total = off;
+  off = 0;
   if (!backward) {
-    p.wt = take((size_t)27 * C * C * 2);
-    p.y = take((size_t)N * C * 4);
+    p.wt = take(n * p.wlen * 2);
+    p.y = take(n * p.rows32);
   } else {
-    p.dy = take((size_t)N * C * 2);
-    p.du = take((size_t)N * C * 4);
-    p.dw_chunks = N > 0 ? (N + 2047) / 2048 : 1;
+    p.dy = take(n * p.rows16);
+    p.du = take(n * p.rows32);
+    // a chunk is a workgroup per offset: 1024 tokens of a small problem fill the chip, 32 chunks bound the partial sums
+    p.dw_chunks = N > 0 ? (N + 1023) / 1024 : 1;
     if (p.dw_chunks > 32) p.dw_chunks = 32;
     p.dw_chunk = ((N + p.dw_chunks - 1) / p.dw_chunks + 31) / 32 * 32;
     if (p.dw_chunk < 32) p.dw_chunk = 32;
-    p.pw = take((size_t)p.dw_chunks * 27 * C * C * 4);
+    p.pw = take(n * p.dw_chunks * p.wlen * 4);
     p.pe_chunks = N > 0 ? (N + 63) / 64 : 1;
     if (p.pe_chunks > 1024) p.pe_chunks = 1024;
     p.pe_chunk = (N + p.pe_chunks - 1) / p.pe_chunks;
     if (p.pe_chunk < 1) p.pe_chunk = 1;
-    p.ppe = take((size_t)p.pe_chunks * m * m * m * C * 4);
-    p.ppe2 = take((size_t)PE_GROUPS * m * m * m * C * 4);
-    p.pb = take((size_t)DBIAS_PARTS * C * 4);
+    p.ppe = take(n * p.pe_chunks * p.plen * 4);
+    p.ppe2 = take(n * PE_GROUPS * p.plen * 4);
+    p.pb = take((size_t)n * DBIAS_PARTS * C * 4);
   }
   p.total = off;
   return p;
@@ -443,102 +549,162 @@ int check(const ssa_params_t *p, const ssa_blocks_t *b, int *C) {
 }
 
 template <bool MIRROR>
-void launch_conv(int C, const bf16_t *in, const int32_t *nbr, const bf16_t *Bw, const bf16_t *bias, int N, float *out,
-                 hipStream_t s) {
+void launch_conv(int C, const Pair<ConvSrc> &src, int n, const int32_t *nbr, int N, hipStream_t s) {
   // 64 tokens per wavefront and up to 128 output channels per workgroup row (blockIdx.y picks the channel range)
-  const dim3 grid((unsigned)((N + 255) / 256), (unsigned)(C > 128 ? C / 128 : 1));
+  const dim3 grid((unsigned)((N + 255) / 256), (unsigned)(C > 128 ? C / 128 : 1), n);
   switch (C) {
-    case 32: c_conv<32, MIRROR, 4, 2><<<grid, 256, 0, s>>>(in, nbr, Bw, bias, N, out); break;
-    case 64: c_conv<64, MIRROR, 4, 4><<<grid, 256, 0, s>>>(in, nbr, Bw, bias, N, out); break;
-    case 128: c_conv128<MIRROR, CONV_TOK><<<(unsigned)((N + CONV_TOK - 1) / CONV_TOK), 256, 0, s>>>(in, nbr, Bw, bias, N, out); break;
-    default: c_conv<256, MIRROR, 4, 8><<<grid, 256, 0, s>>>(in, nbr, Bw, bias, N, out); break;
+    case 32: c_conv<32, MIRROR, 4, 2><<<grid, 256, 0, s>>>(src, nbr, N); break;
+    case 64: c_conv<64, MIRROR, 4, 4><<<grid, 256, 0, s>>>(src, nbr, N); break;
+    case 128:
+      // 128 tokens per workgroup read the weights half as often, 64 fill the chip where there are fewer than 128 workgroups of
+      // 128 (one module forward, 64 against 128: 66 and 78 us at 10.7 k tokens, 85 and 82 at 20 k, 165 and 157 at 58 k)
+      if ((size_t)N * n > 16384) c_conv128<MIRROR, 128><<<dim3((unsigned)((N + 127) / 128), 1, n), 256, 0, s>>>(src, nbr, N);
+      else c_conv128<MIRROR, 64><<<dim3((unsigned)((N + 63) / 64), 1, n), 256, 0, s>>>(src, nbr, N);
+      break;
+    default: c_conv<256, MIRROR, 4, 8><<<grid, 256, 0, s>>>(src, nbr, N); break;
   }
+}
+
+// A Pair of pointers, `stride` bytes apart, into a workspace.
+template <class T>
+Pair<T *> carve(char *ws, size_t off, size_t stride) {
+  return Pair<T *>{{(T *)(ws + off), (T *)(ws + off + stride)}};
+}
+template <class T>
+Pair<const T *> as_const(const Pair<T *> &p) { return Pair<const T *>{{p.v[0], p.v[1]}}; }
+
+// Neighbour table and U of the n tensors.
+void prepare_inputs(const ssa_blocks_t *b, int C, int n, const CmpTensor *t, const ModPlan &pl, char *in, hipStream_t s) {
+  const int N = b->N;
+  c_neighbors<<<(unsigned)(((size_t)N * 27 + 255) / 256), 256, 0, s>>>(b->sorted_keys, b->item_start, N, b->G, b->bits, (int32_t *)(in + pl.nbr));
+  const Pair<const bf16_t *> x{{(const bf16_t *)t[0].x, (const bf16_t *)t[n - 1].x}};
+  const Pair<const bf16_t *> pe{{(const bf16_t *)t[0].w->pe, (const bf16_t *)t[n - 1].w->pe}};
+  const size_t items = (size_t)N * (C / 8);
+  c_add_pe<<<dim3((unsigned)((items + 255) / 256), 1, n), 256, 0, s>>>(x, pe, b->perm, b->sorted_keys, N, C, b->bits, b->m_cmp,
+                                                                       carve<bf16_t>(in, pl.u, pl.rows16));
 }
 
 }  // namespace
 
-extern "C" size_t ssa_compress_workspace_bytes(const ssa_params_t *p, const ssa_blocks_t *b, int for_backward) {
+size_t cmp_module_workspace(const ssa_params_t *p, const ssa_blocks_t *b, int n, bool backward) {
   int C;
   if (check(p, b, &C) != SSA_OK) return 0;
-  return mod_plan(b->N, C, b->m_cmp, for_backward != 0).total + 256;
+  return mod_plan(b->N, C, b->m_cmp, n, backward).total + 256;
+}
+size_t cmp_module_input_bytes(const ssa_params_t *p, const ssa_blocks_t *b, int n) {
+  int C;
+  if (check(p, b, &C) != SSA_OK) return 0;
+  return mod_plan(b->N, C, b->m_cmp, n, false).inputs_total + 256;
+}
+
+// n = 1 or 2 tensors; the arguments are checked and N > 0.
+int cmp_module_forward(const ssa_params_t *p, const ssa_blocks_t *b, int n, const CmpTensor *t, void *in_, void *ws_, hipStream_t s) {
+  const int N = b->N, C = p->n_heads_kv * p->head_dim;
+  const ModPlan pl = mod_plan(N, C, b->m_cmp, n, false);
+  char *in = (char *)align_up((size_t)in_, 256), *ws = (char *)align_up((size_t)ws_, 256);
+  const Pair<bf16_t *> U = carve<bf16_t>(in, pl.u, pl.rows16), Wt = carve<bf16_t>(ws, pl.wt, pl.wlen * 2);
+  const Pair<float *> Y = carve<float>(ws, pl.y, pl.rows32);
+  ProfScope ps(PROF_CMP_MODULE, s);
+  prepare_inputs(b, C, n, t, pl, in, s);
+  const Pair<const bf16_t *> w{{(const bf16_t *)t[0].w->w, (const bf16_t *)t[n - 1].w->w}};
+  c_transpose_w<<<dim3((unsigned)((pl.wlen + 255) / 256), 1, n), 256, 0, s>>>(w, C, Wt);
+  Pair<ConvSrc> src{};
+  for (int i = 0; i < n; ++i) src.v[i] = ConvSrc{U.v[i], Wt.v[i], (const bf16_t *)t[i].w->bias, Y.v[i]};
+  launch_conv<false>(C, src, n, (const int32_t *)(in + pl.nbr), N, s);
+  c_pool<<<dim3(b->Nc, 1, n), 128, 0, s>>>(as_const(Y), b->cmp_start, C, Pair<bf16_t *>{{(bf16_t *)t[0].xc, (bf16_t *)t[n - 1].xc}});
+  return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
+}
+
+// prepared: the input region holds the neighbour table and U of these tensors from cmp_module_forward on the same n.
+int cmp_module_backward(const ssa_params_t *p, const ssa_blocks_t *b, int n, const CmpTensor *t, bool prepared, void *in_, void *ws_,
+                        hipStream_t s) {
+  const int N = b->N, m = b->m_cmp, C = p->n_heads_kv * p->head_dim;
+  const ModPlan pl = mod_plan(N, C, m, n, true);
+  char *in = (char *)align_up((size_t)in_, 256), *ws = (char *)align_up((size_t)ws_, 256);
+  const int32_t *nbr = (const int32_t *)(in + pl.nbr);
+  const Pair<bf16_t *> U = carve<bf16_t>(in, pl.u, pl.rows16), dY = carve<bf16_t>(ws, pl.dy, pl.rows16);
+  const Pair<float *> dU = carve<float>(ws, pl.du, pl.rows32), pw = carve<float>(ws, pl.pw, pl.dw_chunks * pl.wlen * 4);
+  const Pair<float *> ppe = carve<float>(ws, pl.ppe, pl.pe_chunks * pl.plen * 4), ppe2 = carve<float>(ws, pl.ppe2, PE_GROUPS * pl.plen * 4);
+  const Pair<float *> pb = carve<float>(ws, pl.pb, (size_t)DBIAS_PARTS * C * 4);
+  const Pair<const float *> dxc{{t[0].dxc, t[n - 1].dxc}};
+  ProfScope ps(PROF_CMP_MODULE_BWD, s);
+  if (!prepared) prepare_inputs(b, C, n, t, pl, in, s);
+  const size_t items = (size_t)N * (C / 8);
+  const dim3 igrid((unsigned)((items + 255) / 256), 1, n);
+  c_expand<<<igrid, 256, 0, s>>>(dxc, b->tok_cmp, b->cmp_start, N, C, dY);
+  c_dbias_partial<<<dim3((C + 63) / 64, DBIAS_PARTS, n), 64, 0, s>>>(dxc, b->Nc, C, pb);
+  c_sum_parts<<<dim3((C + 255) / 256, 1, n), 256, 0, s>>>(as_const(pb), DBIAS_PARTS, 1, (size_t)C, Pair<float *>{{t[0].dbias, t[n - 1].dbias}});
+  // data gradient: dU[pos] = sum_o dY[token that took pos as neighbour o] * w[o]^T; w as given has c_out contiguous
+  Pair<ConvSrc> src{};
+  for (int i = 0; i < n; ++i) src.v[i] = ConvSrc{dY.v[i], (const bf16_t *)t[i].w->w, nullptr, dU.v[i]};
+  launch_conv<true>(C, src, n, nbr, N, s);
+  c_dx_accum<<<igrid, 256, 0, s>>>(as_const(dU), b->perm, N, C, Pair<bf16_t *>{{(bf16_t *)t[0].dx, (bf16_t *)t[n - 1].dx}});
+  const unsigned pgrid = (unsigned)((pl.plen + 255) / 256);
+  c_dpe_partial<<<dim3(pl.pe_chunks, 1, n), 128, pl.plen * 4, s>>>(as_const(dU), b->sorted_keys, N, C, b->bits, m, pl.pe_chunk, ppe);
+  c_sum_parts<<<dim3(pgrid, PE_GROUPS, n), 256, 0, s>>>(as_const(ppe), pl.pe_chunks, PE_GROUPS, pl.plen, ppe2);
+  c_sum_parts<<<dim3(pgrid, 1, n), 256, 0, s>>>(as_const(ppe2), PE_GROUPS, 1, pl.plen, Pair<float *>{{t[0].dpe, t[n - 1].dpe}});
+  const int CT = C < 128 ? C : 128;
+  const dim3 g(27, pl.dw_chunks, (C / CT) * (C / CT) * n);
+  switch (CT) {
+    case 32: c_dw<32><<<g, 256, 0, s>>>(as_const(U), as_const(dY), nbr, N, C, pl.dw_chunk, pw); break;
+    case 64: c_dw<64><<<g, 256, 0, s>>>(as_const(U), as_const(dY), nbr, N, C, pl.dw_chunk, pw); break;
+    default: c_dw<128><<<g, 256, 0, s>>>(as_const(U), as_const(dY), nbr, N, C, pl.dw_chunk, pw); break;
+  }
+  c_sum_parts<<<dim3((unsigned)((pl.wlen + 255) / 256), 1, n), 256, 0, s>>>(as_const(pw), pl.dw_chunks, 1, pl.wlen,
+                                                                            Pair<float *>{{t[0].dw, t[n - 1].dw}});
+  return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
+}
+
+// Argument checks of the public calls on one tensor (backward: the gradients too).
+int cmp_module_check(const CmpTensor &t, bool backward) {
+  if (!t.x || !t.w || !t.w->pe || !t.w->w || !t.w->bias) return SSA_ERR_NULL;
+  if (!backward) {
+    if (!t.xc) return SSA_ERR_NULL;
+    return aligned16(t.x, t.w->pe, t.w->w, t.w->bias, t.xc) ? SSA_OK : SSA_ERR_ALIGNMENT;
+  }
+  if (!t.dxc || !t.dx || !t.dpe || !t.dw || !t.dbias) return SSA_ERR_NULL;
+  return aligned16(t.x, t.w->pe, t.w->w, t.w->bias, t.dxc, t.dx, t.dpe, t.dw, t.dbias) ? SSA_OK : SSA_ERR_ALIGNMENT;
+}
+
+extern "C" size_t ssa_compress_workspace_bytes(const ssa_params_t *p, const ssa_blocks_t *b, int for_backward) {
+  const size_t n = cmp_module_workspace(p, b, 1, for_backward != 0);
+  return n == 0 ? 0 : n + cmp_module_input_bytes(p, b, 1);
 }
 
 extern "C" int ssa_compress_forward(const ssa_params_t *p, const ssa_blocks_t *b, const void *x,
-                                    const ssa_cmp_weights_t *wts, void *x_cmp, void *ws_, size_t ws_bytes, void *stream) {
+                                    const ssa_cmp_weights_t *wts, void *x_cmp, void *ws, size_t ws_bytes, void *stream) {
   int C;
-  const int rc = check(p, b, &C);
+  int rc = check(p, b, &C);
   if (rc != SSA_OK) return rc;
   if (b->N == 0) return SSA_OK;
-  if (!x || !wts || !wts->pe || !wts->w || !wts->bias || !x_cmp) return SSA_ERR_NULL;
-  if (!aligned16(x, wts->pe, wts->w, wts->bias, x_cmp)) return SSA_ERR_ALIGNMENT;
-  if (!ws_ || ws_bytes < ssa_compress_workspace_bytes(p, b, 0)) return SSA_ERR_WORKSPACE;
-  hipStream_t s = (hipStream_t)stream;
-  const int N = b->N;
-  const ModPlan pl = mod_plan(N, C, b->m_cmp, false);
-  char *ws = (char *)align_up((size_t)ws_, 256);
-  int32_t *nbr = (int32_t *)(ws + pl.nbr);
-  bf16_t *U = (bf16_t *)(ws + pl.u), *Wt = (bf16_t *)(ws + pl.wt);
-  float *Y = (float *)(ws + pl.y);
-  ProfScope ps(PROF_CMP_MODULE, s);
-  c_neighbors<<<(unsigned)(((size_t)N * 27 + 255) / 256), 256, 0, s>>>(b->sorted_keys, b->item_start, N, b->G, b->bits, nbr);
-  const size_t items = (size_t)N * (C / 8);
-  c_add_pe<<<(unsigned)((items + 255) / 256), 256, 0, s>>>((const bf16_t *)x, (const bf16_t *)wts->pe, b->perm, b->sorted_keys, N,
-                                                             C, b->bits, b->m_cmp, U);
-  c_transpose_w<<<(unsigned)(((size_t)27 * C * C + 255) / 256), 256, 0, s>>>((const bf16_t *)wts->w, C, Wt);
-  launch_conv<false>(C, U, nbr, Wt, (const bf16_t *)wts->bias, N, Y, s);
-  c_pool<<<b->Nc, 128, 0, s>>>(Y, b->cmp_start, C, (bf16_t *)x_cmp);
-  return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
+  CmpTensor t{};
+  t.x = x; t.w = wts; t.xc = x_cmp;
+  rc = cmp_module_check(t, false);
+  if (rc != SSA_OK) return rc;
+  if (!ws || ws_bytes < ssa_compress_workspace_bytes(p, b, 0)) return SSA_ERR_WORKSPACE;
+  return cmp_module_forward(p, b, 1, &t, ws, (char *)ws + cmp_module_input_bytes(p, b, 1), (hipStream_t)stream);
 }
 
 extern "C" int ssa_compress_backward(const ssa_params_t *p, const ssa_blocks_t *b, const void *x,
                                      const ssa_cmp_weights_t *wts, const float *dx_cmp, void *dx_accum, float *dpe,
-                                     float *dw, float *dbias, void *ws_, size_t ws_bytes, void *stream) {
+                                     float *dw, float *dbias, void *ws, size_t ws_bytes, void *stream) {
   int C;
-  const int rc = check(p, b, &C);
+  int rc = check(p, b, &C);
   if (rc != SSA_OK) return rc;
   hipStream_t s = (hipStream_t)stream;
   if (b->N == 0) {  // no tokens: the parameter gradients are zero
     if (!dpe || !dw || !dbias) return SSA_ERR_NULL;
     const size_t plen0 = (size_t)b->m_cmp * b->m_cmp * b->m_cmp * C, wlen0 = (size_t)27 * C * C;
-    c_sum_parts<<<(unsigned)((plen0 + 255) / 256), 256, 0, s>>>(nullptr, 0, 1, plen0, dpe);
-    c_sum_parts<<<(unsigned)((wlen0 + 255) / 256), 256, 0, s>>>(nullptr, 0, 1, wlen0, dw);
-    c_sum_parts<<<(C + 255) / 256, 256, 0, s>>>(nullptr, 0, 1, (size_t)C, dbias);
+    const Pair<const float *> none{};
+    c_sum_parts<<<(unsigned)((plen0 + 255) / 256), 256, 0, s>>>(none, 0, 1, plen0, Pair<float *>{{dpe, dpe}});
+    c_sum_parts<<<(unsigned)((wlen0 + 255) / 256), 256, 0, s>>>(none, 0, 1, wlen0, Pair<float *>{{dw, dw}});
+    c_sum_parts<<<(C + 255) / 256, 256, 0, s>>>(none, 0, 1, (size_t)C, Pair<float *>{{dbias, dbias}});
     return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
   }
-  if (!x || !wts || !wts->pe || !wts->w || !wts->bias || !dx_cmp || !dx_accum || !dpe || !dw || !dbias) return SSA_ERR_NULL;
-  if (!aligned16(x, wts->pe, wts->w, wts->bias, dx_cmp, dx_accum, dpe, dw, dbias)) return SSA_ERR_ALIGNMENT;
-  if (!ws_ || ws_bytes < ssa_compress_workspace_bytes(p, b, 1)) return SSA_ERR_WORKSPACE;
-  const int N = b->N, m = b->m_cmp;
-  const ModPlan pl = mod_plan(N, C, m, true);
-  char *ws = (char *)align_up((size_t)ws_, 256);
-  int32_t *nbr = (int32_t *)(ws + pl.nbr);
-  bf16_t *U = (bf16_t *)(ws + pl.u), *dY = (bf16_t *)(ws + pl.dy);
-  float *dU = (float *)(ws + pl.du), *pw = (float *)(ws + pl.pw), *ppe = (float *)(ws + pl.ppe);
-  float *ppe2 = (float *)(ws + pl.ppe2), *pb = (float *)(ws + pl.pb);
-  ProfScope ps(PROF_CMP_MODULE_BWD, s);
-  c_neighbors<<<(unsigned)(((size_t)N * 27 + 255) / 256), 256, 0, s>>>(b->sorted_keys, b->item_start, N, b->G, b->bits, nbr);
-  const size_t items = (size_t)N * (C / 8);
-  const unsigned igrid = (unsigned)((items + 255) / 256);
-  c_add_pe<<<igrid, 256, 0, s>>>((const bf16_t *)x, (const bf16_t *)wts->pe, b->perm, b->sorted_keys, N, C, b->bits, m, U);
-  c_expand<<<igrid, 256, 0, s>>>(dx_cmp, b->tok_cmp, b->cmp_start, N, C, dY);
-  c_dbias_partial<<<dim3((C + 63) / 64, DBIAS_PARTS), 64, 0, s>>>(dx_cmp, b->Nc, C, pb);
-  c_sum_parts<<<(C + 255) / 256, 256, 0, s>>>(pb, DBIAS_PARTS, 1, (size_t)C, dbias);
-  // data gradient: dU[pos] = sum_o dY[token that took pos as neighbour o] * w[o]^T; w as given has c_out contiguous
-  launch_conv<true>(C, dY, nbr, (const bf16_t *)wts->w, nullptr, N, dU, s);
-  c_dx_accum<<<igrid, 256, 0, s>>>(dU, b->perm, N, C, (bf16_t *)dx_accum);
-  const int rows = m * m * m;
-  const size_t plen = (size_t)rows * C;
-  c_dpe_partial<<<pl.pe_chunks, 128, plen * 4, s>>>(dU, b->sorted_keys, N, C, b->bits, m, pl.pe_chunk, ppe);
-  c_sum_parts<<<dim3((unsigned)((plen + 255) / 256), PE_GROUPS), 256, 0, s>>>(ppe, pl.pe_chunks, PE_GROUPS, plen, ppe2);
-  c_sum_parts<<<(unsigned)((plen + 255) / 256), 256, 0, s>>>(ppe2, PE_GROUPS, 1, plen, dpe);
-  const int CT = C < 128 ? C : 128;
-  const dim3 g(27, pl.dw_chunks, (C / CT) * (C / CT));
-  switch (CT) {
-    case 32: c_dw<32><<<g, 256, 0, s>>>(U, dY, nbr, N, C, pl.dw_chunk, pw); break;
-    case 64: c_dw<64><<<g, 256, 0, s>>>(U, dY, nbr, N, C, pl.dw_chunk, pw); break;
-    default: c_dw<128><<<g, 256, 0, s>>>(U, dY, nbr, N, C, pl.dw_chunk, pw); break;
-  }
-  const size_t wlen = (size_t)27 * C * C;
-  c_sum_parts<<<(unsigned)((wlen + 255) / 256), 256, 0, s>>>(pw, pl.dw_chunks, 1, wlen, dw);
-  return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
+  CmpTensor t{};
+  t.x = x; t.w = wts; t.dxc = dx_cmp; t.dx = dx_accum; t.dpe = dpe; t.dw = dw; t.dbias = dbias;
+  rc = cmp_module_check(t, true);
+  if (rc != SSA_OK) return rc;
+  if (!ws || ws_bytes < ssa_compress_workspace_bytes(p, b, 1)) return SSA_ERR_WORKSPACE;
+  return cmp_module_backward(p, b, 1, &t, false, ws, (char *)ws + cmp_module_input_bytes(p, b, 1), s);
 }

@@ -6,6 +6,7 @@
 // saved activations and the workspace and orders the launches on the caller's stream.
 #include "linear_internal.h"
 #include "profile.h"
+#include "cmp_internal.h"
 
 namespace {
 
@@ -31,12 +32,12 @@ SavedPlan saved_plan(const ssa_params_t *p) {
 }
 
 struct BwdPlan {
-  size_t d_o, dq, dk, dv, dg, kc, vc, dkc, dvc, scratch, scratch_bytes, total;
+  size_t d_o, dq, dk, dv, dg, kc, vc, dkc, dvc, mod_in, scratch, scratch_bytes, total;
 };
 
 // Forward workspace: the learned module's block tokens in front of a scratch region shared by the parts.
 struct FwdPlan {
-  size_t kc, vc, scratch, scratch_bytes, total;
+  size_t kc, vc, mod_in, scratch, scratch_bytes, total;
 };
 
 // 0: mean pool; 1: learned compression module on keys and values; -1: some but not all of its pointers given
@@ -55,7 +56,8 @@ FwdPlan fwd_plan(const ssa_params_t *p, const ssa_blocks_t *b, int Dm) {
   auto take = [&](size_t bytes) { const size_t r = off; off += align_up(bytes, 256); return r; };
   w.kc = take((size_t)b->Nc * ckv * 2);
   w.vc = take((size_t)b->Nc * ckv * 2);
-  w.scratch_bytes = max3(ssa_workspace_bytes(p, b, 0), ssa_gate_workspace_bytes(p, Dm, 0), ssa_compress_workspace_bytes(p, b, 0)) + 256;
+  w.scratch_bytes = max3(ssa_workspace_bytes(p, b, 0), ssa_gate_workspace_bytes(p, Dm, 0), cmp_module_workspace(p, b, 2, false)) + 256;
+  w.mod_in = take(cmp_module_input_bytes(p, b, 2));
   w.scratch = take(w.scratch_bytes);
   w.total = off;
   return w;
@@ -78,11 +80,21 @@ BwdPlan bwd_plan(const ssa_params_t *p, const ssa_blocks_t *b, int Dm) {
   const size_t wt = align_up(cq * Dm * 2, 256) + 2 * align_up(ckv * Dm * 2, 256);  // transposed Wq, Wk, Wv
   const size_t lin = max3(ssa_linear_workspace_bytes(p->n_tokens, (int)cq, Dm, 1), lin_dw_workspace(p->n_tokens, Dm, (int)cq),
                           lin_dw_workspace(p->n_tokens, Dm, (int)ckv));
-  const size_t mod = max3(ssa_compress_workspace_bytes(p, b, 0), ssa_compress_workspace_bytes(p, b, 1), 0);
+  const size_t mod = max3(cmp_module_workspace(p, b, 2, false), cmp_module_workspace(p, b, 2, true), 0);
+  w.mod_in = take(cmp_module_input_bytes(p, b, 2));
   w.scratch_bytes = max3(max3(wt, lin, mod), ssa_workspace_bytes(p, b, 1), ssa_gate_workspace_bytes(p, Dm, 1)) + 256;
   w.scratch = take(w.scratch_bytes);
   w.total = off;
   return w;
+}
+
+// The module on keys and values together.
+int module_forward(const ssa_params_t *p, const ssa_blocks_t *b, const CmpTensor (&t)[2], void *in, void *ws, hipStream_t s) {
+  for (const CmpTensor &x : t) {
+    const int rc = cmp_module_check(x, false);
+    if (rc != SSA_OK) return rc;
+  }
+  return cmp_module_forward(p, b, 2, t, in, ws, s);
 }
 
 int layer_check(const ssa_params_t *p, const ssa_blocks_t *b, int Dm) {
@@ -143,8 +155,10 @@ extern "C" int ssa_layer_forward(const ssa_params_t *p, const ssa_blocks_t *b, i
   if (rc == SSA_OK) rc = ssa_gate_forward(p, d_model, x, w->wg, w->bg, sv + s.gates, scratch, pl.scratch_bytes, stream);
   if (rc == SSA_OK && mode == 1) {
     const ssa_cmp_weights_t ck{w->pe_k, w->wc_k, w->bc_k}, cv{w->pe_v, w->wc_v, w->bc_v};
-    rc = ssa_compress_forward(p, b, sv + s.k, &ck, wsb + pl.kc, scratch, pl.scratch_bytes, stream);
-    if (rc == SSA_OK) rc = ssa_compress_forward(p, b, sv + s.v, &cv, wsb + pl.vc, scratch, pl.scratch_bytes, stream);
+    CmpTensor t[2]{};
+    t[0].x = sv + s.k; t[0].w = &ck; t[0].xc = wsb + pl.kc;
+    t[1].x = sv + s.v; t[1].w = &cv; t[1].xc = wsb + pl.vc;
+    rc = module_forward(p, b, t, wsb + pl.mod_in, scratch, (hipStream_t)stream);
     if (rc == SSA_OK)
       rc = ssa_forward_pooled(p, b, sv + s.q, sv + s.k, sv + s.v, sv + s.gates, wsb + pl.kc, wsb + pl.vc, sv + s.o,
                               (float *)(sv + s.lse), (int32_t *)(sv + s.idx), sv + s.ob, scratch, pl.scratch_bytes, stream);
@@ -200,15 +214,16 @@ extern "C" int ssa_layer_backward(const ssa_params_t *p, const ssa_blocks_t *b, 
     // the module onto dk and dv
     void *kc = ws + pl.kc, *vc = ws + pl.vc;
     float *dkc = (float *)(ws + pl.dkc), *dvc = (float *)(ws + pl.dvc);
-    rc = ssa_compress_forward(p, b, sv + s.k, &ck, kc, scratch, pl.scratch_bytes, stream);
-    if (rc == SSA_OK) rc = ssa_compress_forward(p, b, sv + s.v, &cv, vc, scratch, pl.scratch_bytes, stream);
+    CmpTensor t[2]{};
+    t[0].x = sv + s.k; t[0].w = &ck; t[0].xc = kc; t[0].dxc = dkc; t[0].dx = dk; t[0].dpe = g->dpe_k; t[0].dw = g->dwc_k; t[0].dbias = g->dbc_k;
+    t[1].x = sv + s.v; t[1].w = &cv; t[1].xc = vc; t[1].dxc = dvc; t[1].dx = dv; t[1].dpe = g->dpe_v; t[1].dw = g->dwc_v; t[1].dbias = g->dbc_v;
+    rc = module_forward(p, b, t, ws + pl.mod_in, scratch, st);
     if (rc == SSA_OK)
       rc = ssa_backward_pooled(p, b, sv + s.q, sv + s.k, sv + s.v, sv + s.gates, kc, vc, sv + s.ob, (const float *)(sv + s.lse),
                                (const int32_t *)(sv + s.idx), d_o, dq, dk, dv, dg, dkc, dvc, scratch, pl.scratch_bytes, stream);
-    if (rc == SSA_OK)
-      rc = ssa_compress_backward(p, b, sv + s.k, &ck, dkc, dk, g->dpe_k, g->dwc_k, g->dbc_k, scratch, pl.scratch_bytes, stream);
-    if (rc == SSA_OK)
-      rc = ssa_compress_backward(p, b, sv + s.v, &cv, dvc, dv, g->dpe_v, g->dwc_v, g->dbc_v, scratch, pl.scratch_bytes, stream);
+    for (const CmpTensor &x : t)
+      if (rc == SSA_OK) rc = cmp_module_check(x, true);
+    if (rc == SSA_OK) rc = cmp_module_backward(p, b, 2, t, true, ws + pl.mod_in, scratch, st);
   } else {
     rc = ssa_backward(p, b, sv + s.q, sv + s.k, sv + s.v, sv + s.gates, sv + s.ob, (const float *)(sv + s.lse),
                       (const int32_t *)(sv + s.idx), d_o, dq, dk, dv, dg, scratch, pl.scratch_bytes, stream);
