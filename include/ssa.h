@@ -23,6 +23,9 @@
  *   - ssa_forward / ssa_backward enqueue work on `stream` (a hipStream_t passed as void*) and return without
  *     synchronising; they never allocate.  ssa_build_blocks allocates the handle's arrays and synchronises
  *     the stream once to learn the block counts.
+ *   - Infinities and NaN: on the fp32-arithmetic path (SSA_F32, and bf16 shapes the matrix-core kernels do not cover) a
+ *     non-finite element reaches the rows that attend to it and no others.  On the bf16 matrix-core path it may also reach
+ *     rows that share a tile of keys or queries with it, of a neighbouring batch item among them.
  *   - Return value: 0 on success, a negative ssa_status_t otherwise.  On a validation error nothing is
  *     launched and no output is written.
  */

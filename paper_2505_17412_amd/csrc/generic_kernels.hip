@@ -109,6 +109,7 @@ __device__ inline float quad_max(float v) {
   a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
+__device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }  // in a scalar register
 __device__ inline unsigned wave_min_u(unsigned v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v = min(v, (unsigned)__shfl_xor((int)v, off));
@@ -191,15 +192,16 @@ __device__ inline Cols columns(const BlkView &bv, int hs, int g, int tile) {
 
 // A lane's share of one row as a score operand: dims 16*s + 4*quad .. +3, s < DT; zero past d and for a missing row.
 template <typename T, int DT>
-__device__ inline void ld_row(const T *row, int d, bool valid, f4 (&o)[DT]) {
-  const int quad = threadIdx.x >> 4 & 3;
+__device__ inline void ld_row(const T *row, int d, bool valid, f4 (&o)[DT], int quad) {
 #pragma unroll
   for (int s = 0; s < DT; ++s) {
     const int dim = 16 * s + 4 * quad;
     o[s] = valid && dim < d ? ld4(row + dim) : f4{0.f, 0.f, 0.f, 0.f};
   }
 }
-// The same for key rows, where garbage past d is harmless (it meets the zeros of the other operand): no selects.
+template <typename T, int DT>
+__device__ inline void ld_row(const T *row, int d, bool valid, f4 (&o)[DT]) { ld_row<T, DT>(row, d, valid, o, threadIdx.x >> 4 & 3); }
+// The same for key rows, where finite garbage past d is harmless (it meets the zeros of the other operand): no selects.
 template <int DT>
 __device__ inline void ld_key(const float *row, int d, f4 (&o)[DT]) {
   const int quad = threadIdx.x >> 4 & 3;
@@ -218,6 +220,46 @@ __device__ inline f4 dot16(const f4 (&a)[DT], const f4 (&b)[DT]) {
       else c0 = mfma4(a[s][i], b[s][i], c0);
     }
   return c0 + c1;
+}
+
+// Infinities and NaN.  A tile multiplies every key with every column, and the zero weight of a key that a column may not see
+// does not cancel a non-finite element of that key.  Such an element leaves a non-finite sum, so a walk that ends with one is
+// repeated one key at a time (the *_alone functions), each key added only to the columns that see it: what a row does not
+// attend to never reaches it (a NaN of one batch item stays in that item), nor does a row's own element through padding.  A walk over finite data pays one look at its
+// sums.  The repeated walks are written for few registers, not for speed.
+template <int DT>
+__device__ inline bool finite_sums(const f4 (&acc)[DT]) {
+  unsigned most = 0u;
+#pragma unroll
+  for (int b = 0; b < DT; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) most = max(most, __float_as_uint(acc[b][i]) & 0x7FFFFFFFu);
+  asm volatile("" : "+v"(most));  // (the comparison stays one of integers: this file is compiled as if NaN did not occur)
+  return most < 0x7F800000u;
+}
+// The thread's number, hidden from the compiler: what a repeated walk derives from it is not kept in registers from the start.
+__device__ inline int thread_again() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+// Element `row` (of 16, uniform) of lane n's column, from the lane that holds it (w: rows 4*quad .. +3 of column n).
+__device__ inline float of_row(const f4 &w, int row) {
+  const float x = row & 2 ? (row & 1 ? w[3] : w[2]) : (row & 1 ? w[1] : w[0]);
+  return __shfl(x, (int)(threadIdx.x & 15) + 16 * (row >> 2));
+}
+// acc += row * w for one row of the other operand (lane n's DT elements of it at p), in the columns with `mine`.
+template <int DT, typename T>
+__device__ inline void add_alone(f4 (&acc)[DT], const T *p, float w, bool mine) {
+  const bool first = (threadIdx.x & 48) == 0;  // the row is index 0 of the contraction
+  float x[DT];
+  ld_chunk<DT>(p, x);
+#pragma unroll
+  for (int b = 0; b < DT; ++b) {
+    const f4 r = mfma4(first ? x[b] : 0.f, first ? w : 0.f, acc[b]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[b][i] = mine ? r[i] : acc[b][i];
+  }
 }
 
 // Walks: next() moves to this wavefront's next 16-key tile.  kb: its first key; last: the last existing key of its range;
@@ -316,15 +358,63 @@ struct State {
   float m, l;  // reference maximum (log2 units) of the column; this lane's share of the sum
 };
 
+template <int DT>
+__device__ inline void clear(State<DT> &st) {
+  st.m = -INFINITY;
+  st.l = 0.f;
+#pragma unroll
+  for (int b = 0; b < DT; ++b) st.o[b] = f4{0.f, 0.f, 0.f, 0.f};
+}
+// Scores of one tile (masked: the column sees keys rel .. rel + 3 inside [0, len)) to probabilities, the reference raised where needed.
+template <int DT>
+__device__ inline void softmax_reference(State<DT> &st, f4 &v, int rel, int len, float sl2) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = (unsigned)(rel + i) < (unsigned)len ? v[i] * sl2 : -INFINITY;
+  const float pm = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+  if (__any(pm > st.m + 8.f)) {
+    const float mn = fmaxf(st.m, quad_max(pm));
+    const float alpha = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st.m - mn);
+    st.m = mn;
+    st.l *= alpha;
+#pragma unroll
+    for (int b = 0; b < DT; ++b) st.o[b] *= alpha;
+  }
+}
+template <int DT>
+__device__ inline f4 softmax_step(State<DT> &st, f4 v, int rel, int len, float sl2) {
+  softmax_reference(st, v, rel, len, sl2);
+  const float neg = st.m == -INFINITY ? -INFINITY : -st.m;
+  f4 p;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    p[i] = __builtin_amdgcn_exp2f(v[i] + neg);
+    st.l += p[i];
+  }
+  return p;
+}
+
+template <int DT, class Walk>
+__device__ inline void attend_alone(State<DT> &st, const f4 (&q)[DT], Walk w, const float *Kg, const float *Vg, int stride, int d, float sl2) {
+  const int t = thread_again(), n = t & 15, quad = t >> 4 & 3, c = n * DT < d ? n * DT : 0;
+  clear(st);
+#pragma unroll 1
+  while (w.next()) {
+    f4 k[DT];
+    ld_row<float, DT>(Kg + (size_t)min(w.kb + n, w.last) * stride, d, true, k, quad);
+    const f4 p = softmax_step(st, dot16<DT>(k, q), w.kb + 4 * quad - w.lo, w.hi - w.lo, sl2);
+#pragma unroll 1
+    for (int key = 0; key < 16; ++key)
+      add_alone<DT>(st.o, Vg + (size_t)min(w.kb + key, w.last) * stride + c, of_row(p, key), (unsigned)(w.kb + key - w.lo) < (unsigned)(w.hi - w.lo));
+  }
+}
+
 // Softmax attention of the 16 columns over a walk (Algorithm 1's inner loop).  The reference maximum is raised lazily: a
 // column's exponents stay below 2^8, and the result does not depend on the reference.
 template <int DT, class Walk>
 __device__ inline void attend(State<DT> &st, const f4 (&q)[DT], Walk w, const float *Kg, const float *Vg, int stride, int d, float sl2) {
   const int quad = threadIdx.x >> 4 & 3;
-  st.m = -INFINITY;
-  st.l = 0.f;
-#pragma unroll
-  for (int b = 0; b < DT; ++b) st.o[b] = f4{0.f, 0.f, 0.f, 0.f};
+  const Walk again = w;
+  clear(st);
   bool more = w.next();
   FwdTile<DT> cur, nxt;
   if (more) ld_fwd_tile(cur, Kg, Vg, stride, d, w.kb, w.last);
@@ -333,17 +423,7 @@ __device__ inline void attend(State<DT> &st, const f4 (&q)[DT], Walk w, const fl
     more = w.next();
     if (more) ld_fwd_tile(nxt, Kg, Vg, stride, d, w.kb, w.last);
     f4 v = dot16<DT>(cur.k, q);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = (unsigned)(rel + i) < (unsigned)len ? v[i] * sl2 : -INFINITY;
-    const float pm = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
-    if (__any(pm > st.m + 8.f)) {
-      const float mn = fmaxf(st.m, quad_max(pm));
-      const float alpha = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st.m - mn);
-      st.m = mn;
-      st.l *= alpha;
-#pragma unroll
-      for (int b = 0; b < DT; ++b) st.o[b] *= alpha;
-    }
+    softmax_reference(st, v, rel, len, sl2);
     const float neg = st.m == -INFINITY ? -INFINITY : -st.m;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -354,6 +434,7 @@ __device__ inline void attend(State<DT> &st, const f4 (&q)[DT], Walk w, const fl
     }
     cur = nxt;
   }
+  if (__builtin_expect(!__all(finite_sums<DT>(st.o)), 0)) attend_alone<DT>(st, q, again, Kg, Vg, stride, d, sl2);
 }
 
 // Merge of the wavefronts' states through LDS: thread t gets column t / 16, dims (t % 16)*DT .. +DT-1, normalised, and the
@@ -408,12 +489,13 @@ __device__ inline void union_range(int lo, int hi, bool valid, int &k0, int &k1)
   if (k1 <= k0) k0 = k1 = 0;
 }
 
-// Compression branch: one workgroup per 16 columns.
+// Compression branch: one workgroup per 16 columns.  (The repeated walk's code would cost the kernel a wavefront per SIMD; the
+// bound keeps it at what the tile loop takes.)
 template <typename T, int DT>
-__global__ __launch_bounds__(64 * NW) void g_cmp_fwd(FwdArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DT == 2 ? 6 : DT == 4 ? 4 : 1))) void g_cmp_fwd(FwdArgs a) {
   __shared__ MergeBuf<DT> mb;
   __shared__ int scol[16];
-  const int g = blockIdx.y, wid = threadIdx.x >> 6;
+  const int g = blockIdx.y, wid = wave_id();
   const Cols c = columns(a.bv, a.hs, g, blockIdx.x);
   if (threadIdx.x < 16) scol[threadIdx.x] = c.valid ? c.tok * a.Hq + c.h : -1;
   const int item = a.bv.tok_item[c.pos], lo = c.valid ? a.bv.cmp_batch[item] : 0, hi = c.valid ? a.bv.cmp_batch[item + 1] : 0;
@@ -437,7 +519,7 @@ __global__ __launch_bounds__(64 * NW) void g_slc_win_fwd(FwdArgs a) {
   extern __shared__ unsigned ids[];  // build_union
   __shared__ MergeBuf<DT> mb;
   __shared__ int scol[16];
-  const int g = blockIdx.y, wid = threadIdx.x >> 6, stride = a.Hkv * a.d;
+  const int g = blockIdx.y, wid = wave_id(), stride = a.Hkv * a.d;
   const Cols c = columns(a.bv, a.hs, g, blockIdx.x);
   if (threadIdx.x < 16) scol[threadIdx.x] = c.valid ? c.tok * a.Hq + c.h : -1;
   const int tpt = tokens_per_tile(a.hs), pos0 = (int)blockIdx.x / tiles_per_token(a.hs) * tpt;
@@ -492,7 +574,7 @@ __global__ __launch_bounds__(64 * NW) void g_scores_topk(ScoreArgs a) {
   extern __shared__ float sm[];
   float *P = sm, *S = P + 16 * (KC + 4);  // P [16 columns][KC + 4], S [tw][s_max]
   uint32_t *marks = (uint32_t *)(S + (size_t)a.tw * a.s_max);
-  const int g = blockIdx.y, wid = threadIdx.x >> 6, n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
+  const int g = blockIdx.y, wid = wave_id(), n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
   const int pos0 = blockIdx.x * a.tw, ntok = min(a.tw, a.bv.N - pos0), hc = min(a.hs, 16), cts = tiles_per_token(a.hs);
   for (int i = threadIdx.x; i < a.tw * a.s_max; i += 64 * NW) S[i] = 0.f;
   const int i0 = a.bv.tok_item[pos0], i1 = a.bv.tok_item[pos0 + ntok - 1];
@@ -508,7 +590,7 @@ __global__ __launch_bounds__(64 * NW) void g_scores_topk(ScoreArgs a) {
       const float nl = valid ? -a.lse[th] * LOG2E_F : -INFINITY;
       for (int kb = kc + 16 * wid; kb < ke; kb += 16 * NW) {
         f4 k[DT];
-        ld_key<DT>(a.Kc + ((size_t)min(kb + n, k1 - 1) * a.Hkv + g) * a.d, a.d, k);
+        ld_row<float, DT>(a.Kc + ((size_t)min(kb + n, k1 - 1) * a.Hkv + g) * a.d, a.d, true, k);
         const f4 v = dot16<DT>(k, q);
         f4 p;
 #pragma unroll
@@ -591,6 +673,26 @@ __device__ inline void attend_bwd(f4 (&dq)[DT], const f4 (&q)[DT], const f4 (&go
   }
 }
 
+template <int DT, class Walk>
+__device__ inline void attend_bwd_alone(f4 (&dq)[DT], const f4 (&q)[DT], const f4 (&go)[DT], const RowInfo &ri, Walk w, const float *Kg,
+                                        const float *Vg, int stride, int d, float sl2, float scale) {
+  const int t = thread_again(), n = t & 15, quad = t >> 4 & 3, c = n * DT < d ? n * DT : 0;
+#pragma unroll 1
+  while (w.next()) {
+    const size_t r = (size_t)min(w.kb + n, w.last) * stride;
+    f4 x[DT], ds;
+    ld_row<float, DT>(Kg + r, d, true, x, quad);
+    const f4 s = dot16<DT>(x, q);
+    ld_row<float, DT>(Vg + r, d, true, x, quad);
+    const f4 dp = dot16<DT>(x, go);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ds[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], sl2, -ri.lse2)) * (ri.w * dp[i] - ri.delta) * scale;
+#pragma unroll 1
+    for (int key = 0; key < 16; ++key)
+      add_alone<DT>(dq, Kg + (size_t)min(w.kb + key, w.last) * stride + c, of_row(ds, key), (unsigned)(w.kb + key - w.lo) < (unsigned)(w.hi - w.lo));
+  }
+}
+
 struct DqArgs {
   const void *Q, *dO, *Ob, *gates;
   BlkView bv;
@@ -604,11 +706,11 @@ struct DqArgs {
 
 // dgates, the row scalars and dQ of all three branches for 16 columns.
 template <typename T, int DT>
-__global__ __launch_bounds__(64 * NW) void g_bwd_dq(DqArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DT <= 2 ? 4 : 1))) void g_bwd_dq(DqArgs a) {
   extern __shared__ unsigned ids[];
   __shared__ float part[NW][16][16 * DT + 4];
   __shared__ int scol[16];
-  const int g = blockIdx.y, wid = threadIdx.x >> 6, n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, stride = a.Hkv * a.d;
+  const int g = blockIdx.y, wid = wave_id(), n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, stride = a.Hkv * a.d;
   const Cols c = columns(a.bv, a.hs, g, blockIdx.x);
   if (threadIdx.x < 16) scol[threadIdx.x] = c.valid ? c.tok * a.Hq + c.h : -1;
   const int tpt = tokens_per_tile(a.hs), pos0 = (int)blockIdx.x / tiles_per_token(a.hs) * tpt;
@@ -637,21 +739,29 @@ __global__ __launch_bounds__(64 * NW) void g_bwd_dq(DqArgs a) {
     }
   }
   f4 dq[DT];
-#pragma unroll
-  for (int b = 0; b < DT; ++b) dq[b] = f4{0.f, 0.f, 0.f, 0.f};
-  int k0, k1;
-  {
-    const int item = a.bv.tok_item[c.pos], lo = c.valid ? a.bv.cmp_batch[item] : 0, hi = c.valid ? a.bv.cmp_batch[item + 1] : 0;
-    union_range(lo, hi, c.valid, k0, k1);
-    attend_bwd<DT>(dq, q, go, ri[0], RangeWalk(k0, k1, lo, hi, wid, NW), a.Kc + g * a.d, a.Vc + g * a.d, stride, a.d, a.sl2, a.scale);
-  }
   const float *Kg = a.Ks + g * a.d, *Vg = a.Vs + g * a.d;
-  attend_bwd<DT>(dq, q, go, ri[1], UnionWalk(un, n_un, c.slot, c.valid, wid, NW), Kg, Vg, stride, a.d, a.sl2, a.scale);
-  {
-    const int win = a.bv.tok_win[c.pos], lo = c.valid ? a.bv.win_start[win] : 0, hi = c.valid ? a.bv.win_start[win + 1] : 0;
-    union_range(lo, hi, c.valid, k0, k1);
-    attend_bwd<DT>(dq, q, go, ri[2], RangeWalk(k0, k1, lo, hi, wid, NW), Kg, Vg, stride, a.d, a.sl2, a.scale);
-  }
+  auto walks = [&](auto alone) {
+    auto one = [&](const RowInfo &r, auto w, const float *K, const float *V) {
+      if constexpr (decltype(alone)::value) attend_bwd_alone<DT>(dq, q, go, r, w, K, V, stride, a.d, a.sl2, a.scale);
+      else attend_bwd<DT>(dq, q, go, r, w, K, V, stride, a.d, a.sl2, a.scale);
+    };
+#pragma unroll
+    for (int b = 0; b < DT; ++b) dq[b] = f4{0.f, 0.f, 0.f, 0.f};
+    int k0, k1;
+    {
+      const int item = a.bv.tok_item[c.pos], lo = c.valid ? a.bv.cmp_batch[item] : 0, hi = c.valid ? a.bv.cmp_batch[item + 1] : 0;
+      union_range(lo, hi, c.valid, k0, k1);
+      one(ri[0], RangeWalk(k0, k1, lo, hi, wid, NW), a.Kc + g * a.d, a.Vc + g * a.d);
+    }
+    one(ri[1], UnionWalk(un, n_un, c.slot, c.valid, wid, NW), Kg, Vg);
+    {
+      const int win = a.bv.tok_win[c.pos], lo = c.valid ? a.bv.win_start[win] : 0, hi = c.valid ? a.bv.win_start[win + 1] : 0;
+      union_range(lo, hi, c.valid, k0, k1);
+      one(ri[2], RangeWalk(k0, k1, lo, hi, wid, NW), Kg, Vg);
+    }
+  };
+  walks(std::false_type());
+  if (__builtin_expect(!__all(finite_sums<DT>(dq)), 0)) walks(std::true_type());
   acc_put<DT>(part[wid][n], dq);
   __syncthreads();
   const int col = threadIdx.x >> 4, ch = (threadIdx.x & 15) * DT, to = scol[col];
@@ -686,10 +796,10 @@ struct DkvArgs {
 };
 
 template <typename T, int DT>
-__global__ __launch_bounds__(64 * nw_key<DT>()) void g_bwd_dkv(DkvArgs a) {
+__global__ __launch_bounds__(64 * nw_key<DT>()) __attribute__((amdgpu_waves_per_eu(DT <= 2 ? 4 : 1))) void g_bwd_dkv(DkvArgs a) {
   constexpr int NW_KEY = nw_key<DT>();
   __shared__ float part[NW_KEY / 2][2][16][16 * DT + 4];
-  const int wid = threadIdx.x >> 6, n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, stride = a.Hkv * a.d;
+  const int wid = wave_id(), n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, stride = a.Hkv * a.d;
   int g, branch, key0, kend, q0, q1, qlo, qhi;  // q: token indices (sorted positions, or places in the list)
   const int32_t *list = nullptr;
   const float *Kr = a.Ks, *Vr = a.Vs;
@@ -800,6 +910,36 @@ __global__ __launch_bounds__(64 * nw_key<DT>()) void g_bwd_dkv(DkvArgs a) {
       for (int b = 0; b < DT; ++b) {
         dv[b] = mfma4(gt[i][b], pw, dv[b]);
         dk[b] = mfma4(qt[i][b], ds, dk[b]);
+      }
+    }
+  }
+  if (__builtin_expect(!__all(finite_sums<DT>(dk) && finite_sums<DT>(dv)), 0)) {  // once more, one query row at a time
+#pragma unroll
+    for (int b = 0; b < DT; ++b) dk[b] = dv[b] = f4{0.f, 0.f, 0.f, 0.f};
+    const int thr = thread_again(), n = thr & 15, quad = thr >> 4 & 3, c = n * DT < a.d ? n * DT : 0;
+#pragma unroll 1
+    for (int e0 = 16 * wid; e0 < ne; e0 += 16 * NW_KEY) {
+      const int e = min(e0 + n, ne - 1), t = q0 + e / a.hs, qls = e0 + n < ne ? t : q1;
+      const int row = (list ? list[t] : a.bv.perm[t]) * a.Hq + g * a.hs + e % a.hs;
+      f4 x[DT], pw, ds;
+      ld_row<T, DT>(Q + (size_t)row * a.d, a.d, true, x, quad);
+      const f4 s = dot16<DT>(x, k);
+      ld_row<T, DT>(dO + (size_t)row * a.d, a.d, true, x, quad);
+      const f4 dp = dot16<DT>(x, v);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f4 inf = info[__shfl(row, 4 * quad + i)];
+        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.sl2, -inf[0]));
+        ds[i] = p * (inf[2] * dp[i] - inf[1]) * a.scale;
+        pw[i] = p * inf[2];
+      }
+#pragma unroll 1
+      for (int r = 0; r < 16; ++r) {
+        const int qi = __shfl(qls, r);
+        const bool mine = qi < q1 && qi >= qlo && qi < qhi;
+        const size_t off = (size_t)__shfl(row, r) * a.d + c;
+        add_alone<DT>(dv, dO + off, of_row(pw, r), mine);
+        add_alone<DT>(dk, Q + off, of_row(ds, r), mine);
       }
     }
   }
