@@ -14,6 +14,7 @@
 // maxima hands the counts to the host through pinned memory.  Seven launches instead of 18 plus four copies; with the
 // allocations kept (see DevicePool), a build of 62k tokens, its arrays read out and destroyed: 228 -> 112 us (two thirds of it on the host).
 #include "ssa_internal.h"
+#include "device_pool.h"
 
 #include <mutex>
 #include <vector>
@@ -378,67 +379,6 @@ __global__ __launch_bounds__(MAX_THREADS) void k_maxima(CsrOut o, int B, const i
 __global__ __launch_bounds__(256) void k_copy(const int32_t *__restrict__ src, size_t n, int32_t *__restrict__ dst) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
 }
-
-// Device memory of destroyed handles and of the build's scratch, kept for the next build: hipMalloc and hipFree cost more
-// than the kernels of a small build.  At most 64 MiB in 16 blocks; what does not fit is freed at once, and everything kept is
-// given back when an allocation fails.  A block enters only when no work can still use it, so any stream or thread may
-// take it.
-class DevicePool {
- public:
-  static DevicePool &get() {
-    static DevicePool *p = new DevicePool();  // never destroyed: the runtime may be gone when static destructors run
-    return *p;
-  }
-  // bytes is rounded up; *got receives the size to hand back to give()
-  void *take(int device, size_t bytes, size_t *got) {
-    bytes = align_up(bytes, bytes < ((size_t)1 << 20) ? (size_t)1 << 16 : (size_t)1 << 20);
-    {
-      std::lock_guard<std::mutex> l(mu_);
-      size_t best = blocks_.size();
-      for (size_t i = 0; i < blocks_.size(); ++i)
-        if (blocks_[i].device == device && blocks_[i].bytes >= bytes && blocks_[i].bytes <= 4 * bytes &&
-            (best == blocks_.size() || blocks_[i].bytes < blocks_[best].bytes))
-          best = i;
-      if (best < blocks_.size()) {
-        void *p = blocks_[best].p;
-        *got = blocks_[best].bytes;
-        total_ -= *got;
-        blocks_.erase(blocks_.begin() + (long)best);
-        return p;
-      }
-    }
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-      release();
-      if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
-    }
-    *got = bytes;
-    return p;
-  }
-  void give(int device, void *p, size_t bytes) {
-    {
-      std::lock_guard<std::mutex> l(mu_);
-      if (blocks_.size() < 16 && total_ + bytes <= ((size_t)64 << 20)) {
-        blocks_.push_back(Block{p, bytes, device});
-        total_ += bytes;
-        return;
-      }
-    }
-    (void)hipFree(p);
-  }
-
- private:
-  struct Block { void *p; size_t bytes; int device; };
-  void release() {
-    std::lock_guard<std::mutex> l(mu_);
-    for (const Block &b : blocks_) (void)hipFree(b.p);
-    blocks_.clear();
-    total_ = 0;
-  }
-  std::mutex mu_;
-  std::vector<Block> blocks_;
-  size_t total_ = 0;
-};
 
 // Pinned slots through which the kernels hand their counts to the host (one per build in progress).
 class PinnedSlots {
