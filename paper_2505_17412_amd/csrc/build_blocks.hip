@@ -617,10 +617,9 @@ extern "C" int ssa_blocks_export(const ssa_blocks_t *b, int which, void *dst, si
 extern "C" void ssa_blocks_destroy(ssa_blocks_t *b) {
   if (!b) return;
   if (b->base) {
-    // work on any stream may still read the arrays: they are kept for the next build only once the device is idle (hipFree
-    // would wait for the same)
+    // work on any stream may still read the arrays: they are kept for the next build only once the device is idle
     int dev = -1;
-    if (hipGetDevice(&dev) == hipSuccess && dev == b->device && hipDeviceSynchronize() == hipSuccess)
+    if (hipGetDevice(&dev) == hipSuccess && dev == b->device && DevicePool::wait_idle())
       DevicePool::get().give(b->device, b->base, b->bytes);
     else
       (void)hipFree(b->base);

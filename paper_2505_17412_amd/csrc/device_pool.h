@@ -61,6 +61,15 @@ class DevicePool {
     }
     (void)hipFree(p);
   }
+  // Waits for all work on the current device.  By freeing a small allocation: hipFree waits for the device, and in a relaxed or
+  // another thread's stream capture it is allowed, where hipDeviceSynchronize invalidates the capture.  (Build, read-out and
+  // destruction of 62k tokens: 123 us, as with hipDeviceSynchronize; freeing the arrays themselves 166 us.)
+  static bool wait_idle() {
+    void *p = nullptr;
+    if (hipMalloc(&p, 256) == hipSuccess) return hipFree(p) == hipSuccess;
+    (void)hipGetLastError();
+    return false;
+  }
 
  private:
   struct Block { void *p; size_t bytes; int device; };
