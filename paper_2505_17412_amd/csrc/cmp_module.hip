@@ -177,7 +177,11 @@ __global__ __launch_bounds__(256) void c_conv(Pair<ConvSrc> srcs, const int32_t 
 // 8*(r >> 2) + 4*a + (r & 3) of its 32-row tile (a = which half), for tokens and for channels alike; the store at the end
 // undoes that numbering.
 // Bound: LDS operand reads (one per two matrix instructions) and their latency; about half of the gathered rows of a surface
-// are zeros.  Keys and values of 10.7 k tokens: 118 us in two launches of 83 workgroups, weights through LDS -> 66 us.
+// are zeros.  At 64 tokens the products of an offset are too short to hide a weight loaded behind its last use, so the next
+// offset has registers of its own (200, two wavefronts per SIMD).  At 128 tokens those registers would cost the second
+// wavefront, so a weight is loaded again in place (210; with a second set 283 and one wavefront).  Module forward of one tensor,
+// 128 tokens with a second set -> in place: 20 k tokens 84 -> 83 us, 40 k 147 -> 114, 62 k 164 -> 126, 150 k 379 -> 296; keys and
+// values together at 17 k 148 -> 111, at 10.7 k 88 -> 90.
 template <bool MIRROR, int TOK>
 __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32_t *__restrict__ nbr, int N) {
   constexpr int C = 128, MT = TOK / 16, AI = TOK / 16;  // AI: gathered 16-byte items per thread (TOK x 16 / 256)
@@ -202,16 +206,18 @@ __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32
   f32x4 acc[MT][2];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) acc[mt][0] = acc[mt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // weights of one offset; with 64 tokens those of the next one have registers of their own
+  constexpr bool AHEAD = TOK == 64;
   struct Weights { bf16x8 v[2][C / 32]; };
   Weights wa, wb;
   bf16x8 ra[AI];
   const int wrow = 32 * wid + 8 * (n >> 2) + (n & 3);  // channel of half 0; half 1 is 4 further
-  auto fetch = [&](int o, Weights &w) {
-    const bf16_t *Bo = Bw + (size_t)o * C * C + (size_t)wrow * C + 8 * quad;
+  const bf16_t *Bl = Bw + (size_t)wrow * C + 8 * quad;
+  auto fetch_weights = [&](int o, int ks, Weights &w) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int ks = 0; ks < C / 32; ++ks) w.v[a][ks] = ld8(Bo + 4 * a * C + 32 * ks);
+    for (int a = 0; a < 2; ++a) w.v[a][ks] = ld8(Bl + (size_t)o * C * C + 4 * a * C + 32 * ks);
+  };
+  auto fetch_rows = [&](int o) {
     const int oo = MIRROR ? 26 - o : o;
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
@@ -224,7 +230,8 @@ __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32
     while (o < 27 && !any_flag[o]) ++o;
     return o;
   };
-  // one offset: its rows (in registers) to LDS buffer `buf`, the next offset's operands requested, the products
+  // one offset: its rows (in registers) to LDS buffer `buf`, the next offset's operands requested, the products; with cur and
+  // nxt the same registers a weight is loaded again as soon as this offset is done with it
   auto step = [&](int &o, int buf, Weights &cur, Weights &nxt) {
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
@@ -233,22 +240,36 @@ __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32
     }
     __syncthreads();  // (the other buffer was last read before this barrier)
     o = next(o + 1);
-    if (o < 27) fetch(o, nxt);
+    if (AHEAD && o < 27)
 #pragma unroll
-    for (int ks = 0; ks < C / 32; ++ks)
+      for (int ks = 0; ks < C / 32; ++ks) fetch_weights(o, ks, nxt);
+    if (o < 27) fetch_rows(o);
+#pragma unroll
+    for (int ks = 0; ks < C / 32; ++ks) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const bf16x8 av = lds_row_operand<C>(sa[buf] + (mt >> 1) * G::ROW_ELEMS, mt & 1, ks);
         acc[mt][0] = mfma16(av, cur.v[0][ks], acc[mt][0]);
         acc[mt][1] = mfma16(av, cur.v[1][ks], acc[mt][1]);
       }
+      if (!AHEAD) fetch_weights(min(o, 26), ks, nxt);  // (past the last offset: loaded and not used)
+    }
   };
   int o = next(0);
-  if (o < 27) fetch(o, wa);
-  while (o < 27) {
-    step(o, 0, wa, wb);
-    if (o >= 27) break;
-    step(o, 1, wb, wa);
+  if (o < 27) {  // (in the order of a step's requests: the compiler then counts what a step has to wait for)
+    if (!AHEAD) fetch_rows(o);
+#pragma unroll
+    for (int ks = 0; ks < C / 32; ++ks) fetch_weights(o, ks, wa);
+    if (AHEAD) fetch_rows(o);
+  }
+  if constexpr (AHEAD) {
+    while (o < 27) {
+      step(o, 0, wa, wb);
+      if (o >= 27) break;
+      step(o, 1, wb, wa);
+    }
+  } else {
+    for (int buf = 0; o < 27; buf ^= 1) step(o, buf, wa, wa);
   }
   // lane: column n of half a -> channel 32*wid + 8*(n >> 2) + 4*a + (n & 3); rows 4*quad + i of tile mt -> token
   // pos0 + 32*(mt >> 1) + 8*quad + 4*(mt & 1) + i
@@ -556,8 +577,9 @@ void launch_conv(int C, const Pair<ConvSrc> &src, int n, const int32_t *nbr, int
     case 32: c_conv<32, MIRROR, 4, 2><<<grid, 256, 0, s>>>(src, nbr, N); break;
     case 64: c_conv<64, MIRROR, 4, 4><<<grid, 256, 0, s>>>(src, nbr, N); break;
     case 128:
-      // 128 tokens per workgroup read the weights half as often, 64 fill the chip where there are fewer than 128 workgroups of
-      // 128 (one module forward, 64 against 128: 66 and 78 us at 10.7 k tokens, 85 and 82 at 20 k, 165 and 157 at 58 k)
+      // 128 tokens per workgroup read the weights half as often, 64 fill the chip while 256 workgroups of 64 do not (one module
+      // forward, 64 against 128 tokens: 68 and 84 us at 14 k tokens, 89 and 86 at 17 k, 93 and 89 at 26 k, 171 and 126 at 62 k; of
+      // keys and values 71 and 86 at 8 k, 94 and 91 at 10.7 k)
       if ((size_t)N * n > 16384) c_conv128<MIRROR, 128><<<dim3((unsigned)((N + 127) / 128), 1, n), 256, 0, s>>>(src, nbr, N);
       else c_conv128<MIRROR, 64><<<dim3((unsigned)((N + 63) / 64), 1, n), 256, 0, s>>>(src, nbr, N);
       break;
