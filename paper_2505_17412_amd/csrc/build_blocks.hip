@@ -125,16 +125,46 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t *part, uint
   return base + inc - v;
 }
 
+// Many tiles: the histograms' exclusive prefixes over the tiles, in place, and the totals per digit.  One workgroup per 64
+// digits, a wavefront per 16th of the tiles.
+constexpr int PREFIX_SEGS = 16;
+__global__ __launch_bounds__(64 * PREFIX_SEGS) void k_tile_prefix(uint32_t *__restrict__ hist, int nb, int nTiles, uint32_t *__restrict__ totals) {
+  __shared__ uint32_t sums[PREFIX_SEGS][64];
+  const int lane = threadIdx.x & 63, seg = threadIdx.x >> 6, digit = blockIdx.x * 64 + lane;
+  const int per = (nTiles + PREFIX_SEGS - 1) / PREFIX_SEGS, t0 = min(nTiles, seg * per), t1 = min(nTiles, t0 + per);
+  uint32_t own = 0;
+  if (digit < nb)
+#pragma unroll 8
+    for (int t = t0; t < t1; ++t) own += hist[(size_t)t * nb + digit];
+  sums[seg][lane] = own;
+  __syncthreads();
+  if (digit >= nb) return;
+  uint32_t run = 0;
+  for (int w = 0; w < seg; ++w) run += sums[w][lane];
+  if (seg == PREFIX_SEGS - 1) totals[digit] = run + own;
+  for (int t = t0; t < t1; t += 8) {
+    uint32_t v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = hist[(size_t)min(t + u, t1 - 1) * nb + digit];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (t + u < t1) hist[(size_t)(t + u) * nb + digit] = run;
+      run += v[u];
+    }
+  }
+}
+
 // Stable scatter of one digit.  The workgroup sums the tile histograms into its offset per digit (keys of smaller digits +
-// keys of this digit in earlier tiles); inside the tile a key's rank is the count of its digit in earlier wavefronts
-// (16-bit counters per wavefront, turned into prefixes) plus its rank inside its wavefront by ballot matching.
-// vin == NULL: the values are the positions themselves (first pass).
+// keys of this digit in earlier tiles), or finds the sums ready (totals != NULL, see k_tile_prefix); inside the tile a key's
+// rank is the count of its digit in earlier wavefronts (16-bit counters per wavefront, turned into prefixes) plus its rank
+// inside its wavefront by ballot matching.  vin == NULL: the values are the positions themselves (first pass).
 static_assert(BINS_MAX / 4 <= SORT_THREADS, "a thread serves four digits");
 constexpr size_t SCATTER_LDS = (size_t)SORT_WAVES * BINS_MAX * 2 + BINS_MAX * 4 + 32 * 4;
 template <int R>
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                                                                uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int N,
-                                                               int shift, int dbits, int nTiles, const uint32_t *__restrict__ hist) {
+                                                               int shift, int dbits, int nTiles, const uint32_t *__restrict__ hist,
+                                                               const uint32_t *__restrict__ totals) {
   extern __shared__ uint32_t sort_smem[];
   const int nb = 1 << dbits, half = nb / 2, quarter = nb / 4, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   uint32_t *wcnt = sort_smem;                              // [SORT_WAVES][nb/2] packed pairs of 16-bit counters
@@ -151,7 +181,11 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const uint64_t *_
   for (int i = tid; i < SORT_WAVES * half; i += SORT_THREADS) wcnt[i] = 0u;
   // thread t < nb/4 serves digits 4t .. 4t+3
   uint32_t before[4] = {0u, 0u, 0u, 0u}, all[4] = {0u, 0u, 0u, 0u};
-  if (tid < quarter) {
+  if (tid < quarter && totals) {
+    const uint4 b = reinterpret_cast<const uint4 *>(hist)[(size_t)blockIdx.x * quarter + tid], t = reinterpret_cast<const uint4 *>(totals)[tid];
+    before[0] = b.x; before[1] = b.y; before[2] = b.z; before[3] = b.w;
+    all[0] = t.x; all[1] = t.y; all[2] = t.z; all[3] = t.w;
+  } else if (tid < quarter) {
     const uint4 *row = reinterpret_cast<const uint4 *>(hist) + tid;
     for (int t0 = 0; t0 < nTiles; t0 += 16) {  // 16 loads in flight, whatever the remainder
       uint4 x[16];
@@ -281,9 +315,23 @@ __global__ __launch_bounds__(CSR_TILE) void k_csr_count(Src src, int N, int nTil
   if (threadIdx.x < 3) tile_cnt[threadIdx.x * nTiles + blockIdx.x] = cnt[threadIdx.x];
 }
 
+// Many tiles: exclusive prefixes of the three count rows over the tiles, in place; a workgroup per row.
+__global__ __launch_bounds__(1024) void k_csr_prefix(uint32_t *__restrict__ tile_cnt, int nTiles) {
+  __shared__ uint32_t part[1024 / 64 + 1];
+  uint32_t *row = tile_cnt + (size_t)blockIdx.x * nTiles, carry = 0;
+  for (int t0 = 0; t0 < nTiles; t0 += 1024) {
+    const int t = t0 + threadIdx.x;
+    const uint32_t v = t < nTiles ? row[t] : 0u;
+    uint32_t sum;
+    const uint32_t ex = block_exclusive_scan(v, part, &sum);
+    if (t < nTiles) row[t] = carry + ex;
+    carry += sum;
+  }
+}
+
 template <class Src>
 __global__ __launch_bounds__(CSR_TILE) void k_csr_write(Src src, int N, int B, int nTiles, const int32_t *__restrict__ offs,
-                                                        const uint32_t *__restrict__ tile_cnt, CsrOut o, int32_t *meta) {
+                                                        const uint32_t *__restrict__ tile_cnt, bool summed, CsrOut o, int32_t *meta) {
   __shared__ uint32_t part[CSR_TILE / 64 + 1];
   const int i = blockIdx.x * CSR_TILE + threadIdx.x;
   for (int j = i; j <= B; j += gridDim.x * CSR_TILE) o.item_start[j] = offs[j];
@@ -293,6 +341,10 @@ __global__ __launch_bounds__(CSR_TILE) void k_csr_write(Src src, int N, int B, i
   uint32_t base[3];
 #pragma unroll
   for (int x = 0; x < 3; ++x) {
+    if (summed) {
+      base[x] = tile_cnt[x * nTiles + blockIdx.x];
+      continue;
+    }
     uint32_t c = 0;
     for (int t = threadIdx.x; t < (int)blockIdx.x; t += CSR_TILE) c += tile_cnt[x * nTiles + t];
     (void)block_exclusive_scan(c, part, &base[x]);
@@ -413,7 +465,8 @@ class PinnedSlots {
 // Kernels of the sort for R keys per thread.  k1: second key array; the sorted keys end in kdst, the caller indices in vdst.
 template <int R>
 void launch_sort(const int32_t *coords, const int32_t *offs, int N, int B, int G, int bits, int total_bits, uint64_t *k0, uint64_t *k1,
-                 uint32_t *v1, uint64_t *kdst, uint32_t *vdst, uint32_t *hist, int32_t *err, int32_t *meta, int nTiles, hipStream_t s) {
+                 uint32_t *v1, uint64_t *kdst, uint32_t *vdst, uint32_t *hist, uint32_t *totals, int32_t *err, int32_t *meta, int nTiles,
+                 hipStream_t s) {
   static std::once_flag once;
   std::call_once(once, [] {
     (void)hipFuncSetAttribute((const void *)k_sort_scatter<R>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCATTER_LDS);
@@ -429,7 +482,8 @@ void launch_sort(const int32_t *coords, const int32_t *offs, int N, int B, int G
     uint64_t *ko = final ? kdst : kalt;
     uint32_t *vo = final ? vdst : valt;
     if (p > 0) k_sort_hist<R><<<nTiles, SORT_THREADS, 0, s>>>(kin, N, p * dbits, dbits, hist);
-    k_sort_scatter<R><<<nTiles, SORT_THREADS, lds, s>>>(kin, vin, ko, vo, N, p * dbits, dbits, nTiles, hist);
+    if (totals) k_tile_prefix<<<((1 << dbits) + 63) / 64, 64 * PREFIX_SEGS, 0, s>>>(hist, 1 << dbits, nTiles, totals);
+    k_sort_scatter<R><<<nTiles, SORT_THREADS, lds, s>>>(kin, vin, ko, vo, N, p * dbits, dbits, nTiles, hist, totals);
     kalt = kin;
     kin = ko;
     vin = vo;
@@ -438,6 +492,11 @@ void launch_sort(const int32_t *coords, const int32_t *offs, int N, int B, int G
 }
 
 }  // namespace
+
+// Up to so many tokens every workgroup sums what the tiles before it counted; that work grows with the square of the tile count,
+// so beyond it a launch forms the prefixes once (sort and block arrays with the sums, with the prefixes: 83 + 33 and 89 + 31 us at
+// 500 k tokens, 102 + 53 and 98 + 46 at 1 M, 188 + 111 and 168 + 77 at 2 M, 3591 + 1883 and 1441 + 666 at 16 M).
+constexpr int SUM_TOKENS_MAX = 1 << 20;
 
 // Common part of the two builders: grid_mode = voxel partition (sort by Morton key), else sequences in caller order.
 static int build_handle(const ssa_params_t *p, const int32_t *coords, const int32_t *batch_offsets, bool grid_mode,
@@ -474,7 +533,7 @@ static int build_handle(const ssa_params_t *p, const int32_t *coords, const int3
   const size_t key_b = align_up((size_t)N * 8, 256), val_b = align_up((size_t)2 * N * 4, 256);
   const size_t hist_b = align_up((size_t)BINS_MAX * nTiles * 4, 256), err_b = align_up((size_t)nTiles * 4, 256);
   const size_t cnt_b = align_up((size_t)3 * csrTiles * 4, 256);
-  const size_t tmp_bytes = (grid_mode ? 2 * key_b + val_b + hist_b : 0) + err_b + cnt_b + 256;
+  const size_t tmp_bytes = (grid_mode ? 2 * key_b + val_b + hist_b + BINS_MAX * 4 : 0) + err_b + cnt_b + 256;
   size_t tmp_got = 0;
   void *tmp = pool.take(h->device, tmp_bytes, &tmp_got);
   int32_t *host_meta = PinnedSlots::get().take();
@@ -498,7 +557,9 @@ static int build_handle(const ssa_params_t *p, const int32_t *coords, const int3
   int n_err = 0;
   auto csr = [&](auto src) {
     k_csr_count<<<csrTiles, CSR_TILE, 0, stream>>>(src, N, csrTiles, tile_cnt);
-    k_csr_write<<<csrTiles, CSR_TILE, 0, stream>>>(src, N, B, csrTiles, batch_offsets, tile_cnt, o, meta);
+    const bool summed = N > SUM_TOKENS_MAX;
+    if (summed) k_csr_prefix<<<3, 1024, 0, stream>>>(tile_cnt, csrTiles);
+    k_csr_write<<<csrTiles, CSR_TILE, 0, stream>>>(src, N, B, csrTiles, batch_offsets, tile_cnt, summed, o, meta);
   };
   if (!grid_mode || N == 0) {
     // The offsets are checked first and the result is read back before any kernel searches them: SeqSrc::item assumes
@@ -513,10 +574,11 @@ static int build_handle(const ssa_params_t *p, const int32_t *coords, const int3
     if (hipMemsetAsync(h->base, 0, ints * sizeof(int32_t), stream) != hipSuccess) return fail(SSA_ERR_HIP);
   } else if (grid_mode) {
     uint64_t *k0 = (uint64_t *)tmp_take(key_b), *k1 = (uint64_t *)tmp_take(key_b);
-    uint32_t *v1 = (uint32_t *)tmp_take(val_b), *hist = (uint32_t *)tmp_take(hist_b);
+    uint32_t *v1 = (uint32_t *)tmp_take(val_b), *hist = (uint32_t *)tmp_take(hist_b), *totals = (uint32_t *)tmp_take(BINS_MAX * 4);
+    if (N <= SUM_TOKENS_MAX) totals = nullptr;
     auto sort = [&](auto r) {
       launch_sort<decltype(r)::value>(coords, batch_offsets, N, B, p->grid, bits, 3 * bits + item_bits, k0, k1, v1, h->sorted_keys,
-                                      (uint32_t *)h->perm, hist, err, meta, nTiles, stream);
+                                      (uint32_t *)h->perm, hist, totals, err, meta, nTiles, stream);
     };
     switch (R) {
       case 1: sort(std::integral_constant<int, 1>()); break;
