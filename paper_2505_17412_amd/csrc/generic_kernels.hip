@@ -791,7 +791,8 @@ struct DkvArgs {
   const int32_t *sel_list, *chunk_start, *part_row_start;  // lists of caller indices
   const ChunkRef *chunk_order;
   int slc_tiles, cmp_splits;
-  int n_win, n_slc;              // workgroups of the first two kinds
+  long long n_win, n_slc;        // workgroups of the first two kinds
+  long long first;               // number of this launch's first workgroup
   float *dKs, *dVs, *pK, *pV, *dKc, *dVc;  // window part [N][Hkv][d]; selection partials [rows][d]; [splits][Nc][Hkv][d]
 };
 
@@ -805,8 +806,9 @@ __global__ __launch_bounds__(64 * nw_key<DT>()) __attribute__((amdgpu_waves_per_
   const float *Kr = a.Ks, *Vr = a.Vs;
   float *oK, *oV;     // row of key0
   int ostride;
-  int wg = blockIdx.x;
-  if (wg < a.n_win) {
+  const long long w0 = a.first + blockIdx.x, w1 = w0 - a.n_win;
+  if (w1 < 0) {
+    const int wg = (int)w0;
     branch = 2;
     g = wg % a.Hkv;
     key0 = wg / a.Hkv * 16;
@@ -818,9 +820,9 @@ __global__ __launch_bounds__(64 * nw_key<DT>()) __attribute__((amdgpu_waves_per_
     oK = a.dKs + (size_t)key0 * stride + g * a.d;
     oV = a.dVs + (size_t)key0 * stride + g * a.d;
     ostride = stride;
-  } else if ((wg -= a.n_win) < a.n_slc) {
+  } else if (w1 < a.n_slc) {
     branch = 1;
-    const int ci = wg / a.slc_tiles, tile = wg % a.slc_tiles;
+    const int ci = (int)(w1 / a.slc_tiles), tile = (int)(w1 % a.slc_tiles);
     if (ci >= a.chunk_start[a.Hkv * a.bv.Ns]) return;
     const ChunkRef cr = a.chunk_order[ci];
     g = cr.key / a.bv.Ns;
@@ -836,7 +838,7 @@ __global__ __launch_bounds__(64 * nw_key<DT>()) __attribute__((amdgpu_waves_per_
     oV = a.pV + row * a.d;
     ostride = a.d;
   } else {
-    wg -= a.n_slc;
+    int wg = (int)(w1 - a.n_slc);
     branch = 0;
     const int sp = wg % a.cmp_splits;
     wg /= a.cmp_splits;
@@ -1098,11 +1100,15 @@ int backward_t(const ssa_ctx &c, const void *q, const void *k, const void *v, co
   const int rc = sel_index_build(topk_idx, c.blk->perm, c.blk->slc_start, c.N, c.Hkv, c.T, c.blk->Ns, sel, true, false, true, c.stream);
   if (rc != SSA_OK) return rc;
   DkvArgs b{q, dout, bv, c.Hq, c.Hkv, c.hs, c.d, c.scale, sl2, Ks, Vs, Kc, Vc, info, sel.list, sel.chunk_start,
-            sel.part_row_start, sel.order, (c.blk->slc_tok_max + 15) / 16, p.splits, 0, 0, dKs, dVs, pK, pV, dKc, dVc};
-  b.n_win = (c.N + 15) / 16 * c.Hkv;
-  b.n_slc = p.max_chunks * b.slc_tiles;
-  const int n_cmp = (c.blk->Nc + 15) / 16 * c.Hkv * p.splits;
-  g_bwd_dkv<T, DT><<<b.n_win + b.n_slc + n_cmp, 64 * nw_key<DT>(), 0, c.stream>>>(b);
+            sel.part_row_start, sel.order, (c.blk->slc_tok_max + 15) / 16, p.splits, 0, 0, 0, dKs, dVs, pK, pV, dKc, dVc};
+  b.n_win = (long long)((c.N + 15) / 16) * c.Hkv;
+  b.n_slc = (long long)p.max_chunks * b.slc_tiles;
+  const long long wgs = b.n_win + b.n_slc + (long long)((c.blk->Nc + 15) / 16) * c.Hkv * p.splits;
+  // a selection chunk has workgroups for the longest block's tiles: one long block among many short ones makes more of them than
+  // one launch can have (2^32 threads)
+  constexpr long long MOST = (1ll << 31) / (64 * nw_key<DT>());
+  for (; b.first < wgs; b.first += MOST)
+    g_bwd_dkv<T, DT><<<(unsigned)(wgs - b.first < MOST ? wgs - b.first : MOST), 64 * nw_key<DT>(), 0, c.stream>>>(b);
   FinishArgs f{bv, c.Hkv, c.d, p.splits, sel.chunk_start, sel.part_row_start, dKs, dVs, pK, pV, dKc, dVc, dk, dv};
   const size_t items = (size_t)c.N * row / 4;
   g_bwd_finish<T><<<(unsigned)((items + 255) / 256), 256, 0, c.stream>>>(f);

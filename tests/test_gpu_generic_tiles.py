@@ -1,6 +1,7 @@
 """GPU: the fp32-arithmetic kernels at the edges of their 16 x 16 tiles: head groupings that do not fill 16 columns or exceed
 them, head dimensions that are no multiple of 16, an item of one token, ragged items, long selection rows, more than 256 pooled keys per
 item (chunks of the score kernel), score rows that leave the kernel fewer tokens per workgroup."""
+import numpy as np
 import pytest
 
 from paper_2505_17412_amd import inputs
@@ -21,3 +22,14 @@ pytestmark = pytest.mark.gpu
 ])
 def test_generic_tile_edges(seed, grid, n, hq, hkv, d, m, topk, dtype):
     full_parity(inputs.random_points_workload(seed, grid, n, hq, hkv, d, m, topk, dtype))
+
+
+def test_one_long_block_among_many_short_ones():
+    """Half of the tokens on one voxel, the rest alone in their blocks: (longest block's tiles) x (selection chunks) is more
+    workgroups than one launch of the key-centric kernel can have."""
+    wl = inputs.random_points_workload(407, 64, (18000,), 2, 2, 8, (1, 2, 2), 2, "f32")
+    rng = np.random.default_rng(407)
+    block = rng.choice(32 ** 3, size=9000, replace=False)
+    wl.coords[:9000] = 2 * np.stack(np.unravel_index(block, (32, 32, 32)), axis=-1)
+    wl.coords[9000:] = wl.coords[0]
+    full_parity(wl, queries=np.arange(0, 18000, 41))
