@@ -18,3 +18,25 @@ def test_scores_of_hundreds(seed, hq, hkv, d, factor):
     s = np.einsum("nhd,mhd->hnm", wl.q[:64, ::hq // hkv], wl.k) / np.sqrt(d)
     assert np.ptp(s, axis=-1).min() > 200.0  # natural units: the largest exceeds any first tile by far for most rows
     full_parity(wl, backward=False)
+
+
+@pytest.mark.parametrize("seed,lens,hq,hkv,d,m_slc,topk", [
+    (511, (1144, 300), 16, 2, 64, 286, 4),   # second segment of 30 keys: no full tile
+    (512, (1144, 300), 8, 1, 32, 286, 4),
+    (513, (1144, 300), 16, 2, 128, 286, 4),
+    (514, (1700,), 8, 2, 64, 800, 3),        # four segments, the last of 32 keys
+    (515, (1700,), 4, 2, 32, 800, 3),
+    (516, (1700,), 16, 1, 128, 800, 3),
+])
+def test_later_segments_of_a_long_block_exceed_the_first(seed, lens, hq, hkv, d, m_slc, topk):
+    """Blocks longer than the 256 keys held at a time: the partial result of the earlier segments is picked up again, and a later
+    segment's scores exceed its reference.  Every block is selected, one-token compression blocks keep their keys exact."""
+    wl = inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=(1, m_slc, 70), topk=topk)
+    place = np.concatenate([np.arange(n) for n in lens]) % m_slc
+    wl.k = inputs.round_to_bf16(wl.k * np.array([0.02, 0.5, 0.1, 1.0])[np.minimum(place // 256, 3)][:, None, None])
+    wl.q = inputs.round_to_bf16(wl.q * 60.0)
+    # log2 units by which a block's largest score exceeds the largest of its first tile, over the first block's columns
+    s = np.einsum("nhd,mhd->hnm", wl.q[:64, ::hq // hkv], wl.k[:m_slc]) / np.sqrt(d) * np.log2(np.e)
+    excess = s.max(axis=-1) - s[..., :32].max(axis=-1)
+    assert (excess > 60.0).mean() > 0.5  # their sums leave the range (2^60) and the running maximum has to take over
+    full_parity(wl, backward=False)
