@@ -261,12 +261,11 @@ struct DkvArgs {
   MfmaView v;
   const bf16_t *Qs, *dOs;             // sorted copies [N(pos)][Hq][D]: Q, and the branch's gate * dO
   const float *lse2s, *deltas;        // already offset to the branch: [N(pos)][Hq]; delta over the rounded gate * dO rows
-  const int32_t *sel_start, *sel_list;  // selection branch: query positions per (g, block)
+  const int32_t *sel_list;              // selection branch: query positions per (g, block)
   float *dK, *dV;                       // [rows][Hkv][D] fp32 (rows: sorted tokens, or compression blocks)
   const int32_t *chunk_start;           // selection branch: [Hkv*Ns+1] first work chunk of each (g, block)
   const ChunkRef *chunk_order;          // selection branch: execution order of the work chunks
   const int32_t *part_row_start;        // selection branch: [Hkv*Ns+1] first row of each (g, block)'s partial sums
-  int chunk_len;                        // selection branch: query tokens per work chunk
   int tiles_per_block;                  // key tiles reserved per block in the grid
   int q_splits;                         // compression branch: query range split into this many parts
 };
@@ -570,7 +569,6 @@ __global__ void m_bwd_finish(const int32_t *__restrict__ perm, const int32_t *__
   }
 }
 
-// Shape of the block-centric selection dQ kernel per head dimension: wavefronts per workgroup, keys held in LDS at a time.
 // 16-column blocks per wavefront of the compression + window dQ kernel: with two, every K and V operand read from LDS
 // feeds two matrix instructions (202 registers, two waves per SIMD; 1.15 -> 1.09 ms at the benchmark shape); head_dim
 // 128 keeps one (its accumulators alone would double).
@@ -637,8 +635,7 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     if constexpr (!slc_bwd_fused(D)) (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_CMP, DKV_WAVES_CMP, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   });
-  DkvArgs base{v, w.Qs, nullptr, nullptr, nullptr, w.sel.start, w.sel.list,
-               w.dKs, w.dVs, w.sel.chunk_start, w.sel.order, w.sel.part_row_start, w.sel.chunk_len, 1, 1};
+  DkvArgs base{v, w.Qs, nullptr, nullptr, nullptr, w.sel.list, w.dKs, w.dVs, w.sel.chunk_start, w.sel.order, w.sel.part_row_start, 1, 1};
   {
     ProfScope ps(PROF_BWD_DKV_WIN, s);
     DkvArgs a = base;

@@ -61,7 +61,7 @@ __device__ inline void score_tile(lds_cptr kt, const typename PTile<D>::Lanes &l
 // units (so every exp2 argument stays below 8 and nothing overflows) does the wavefront take the update path
 // with its cross-lane maximum and rescale of o and l; otherwise the tile needs no cross-lane traffic at all.
 // The log-sum-exp reported at the end does not depend on which reference was used.
-template <int D, int CB, bool MASK>
+template <int D, int CB>
 __device__ inline void fwd_tile(FwdState<D, CB> &st, const QRows<D, CB> &q, lds_cptr kt, lds_cptr vt,
                                 const typename PTile<D>::Lanes &ln, int kb,
                                 const int (&lo)[CB], const int (&hi)[CB], const bool (&on)[CB], const bool (&act)[CB],
@@ -74,14 +74,12 @@ __device__ inline void fwd_tile(FwdState<D, CB> &st, const QRows<D, CB> &q, lds_
   for (int cb = 0; cb < CB; ++cb) {
     if (!act[cb]) continue;
     float(&v)[8] = s[cb];
-    if (MASK) {
-      // lo <= key < hi as one unsigned comparison of (key - lo) against the range length
-      const int rel = kb + 8 * quad - lo[cb];
-      const unsigned len = (unsigned)(hi[cb] - lo[cb]);
+    // lo <= key < hi as one unsigned comparison of (key - lo) against the range length
+    const int rel = kb + 8 * quad - lo[cb];
+    const unsigned len = (unsigned)(hi[cb] - lo[cb]);
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if ((unsigned)(rel + j) >= len) v[j] = -INFINITY;
-    }
+    for (int j = 0; j < 8; ++j)
+      if ((unsigned)(rel + j) >= len) v[j] = -INFINITY;
     float pm = fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7])));
     if (!on[cb]) pm = -INFINITY;
     if (__builtin_expect(__any(pm > st.m[cb] + slack), 0)) {  // rare after the first tiles: keep the common path free of copies
@@ -164,7 +162,7 @@ __device__ inline void fwd_walk(FwdState<D, CB> &st, const QRows<D, CB> &q, cons
         [&](const bf16_t *stg, int kb, int) {
           const lds_cptr kt = (lds_cptr)L::row_tile((bf16_t *)stg, 0), vt = (lds_cptr)L::row_tile((bf16_t *)stg, 1);
           if (fixed && kb != first && kb + 32 <= re) fwd_tile_fixed<D, CB>(st, q, kt, vt, ln, act, sl2, ones);
-          else fwd_tile<D, CB, true>(st, q, kt, vt, ln, kb, lo, hi, on, act, sl2, slack, ones);
+          else fwd_tile<D, CB>(st, q, kt, vt, ln, kb, lo, hi, on, act, sl2, slack, ones);
         });
     if (!fixed) break;
     if (!sums_in_range<D, CB>(st, q)) rng[2] = 1;

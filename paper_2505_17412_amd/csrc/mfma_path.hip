@@ -204,7 +204,7 @@ bool mfma_supported(const ssa_ctx &c) {
 }
 
 // Query tokens per work chunk of the block-centric kernels: long chunks stage a block's K and V rarely, short ones give a
-// small problem enough workgroups for 256 compute units (two each).
+// small problem enough workgroups for 256 compute units (four each).
 int bc_chunk_len(int N, int Hkv, int T) {
   const long long entries = (long long)N * Hkv * T;
   int len = BC_CHUNK;

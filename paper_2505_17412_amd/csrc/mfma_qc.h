@@ -355,7 +355,7 @@ __device__ inline void topk_wave_bits(const uint32_t *S, int n, int T, int base,
 #pragma unroll
     for (int r = 1; r < R; ++r) top = max(top, val[r]);
     top = wave_max_dpp(top);
-    for (int b = 31 - __builtin_clz(top); b >= 0; --b) {
+    for (int b = 31 - __builtin_clz(top | 1u); b >= 0; --b) {
       const uint32_t cand = thr | (1u << b);
       int cnt = 0;
 #pragma unroll

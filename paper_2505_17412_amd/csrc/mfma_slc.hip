@@ -258,7 +258,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
 #pragma unroll
           for (int dt = 0; dt < D / 16; ++dt) st.o[cb][dt] = safe.o[0][dt];
         }
-        // (a column past the end of the chunk points at row 0 of the partial arrays and is not stored)
+        // (a column past the end of the chunk repeats the chunk's last entry and is not stored)
         store_partial_row<D>(a.po, cur.prow[cb], st.o[cb], cur.valid[cb]);
         if (cur.valid[cb] && quad == 0)
           *reinterpret_cast<float2 *>(a.pml + (size_t)cur.prow[cb] * 2) = make_float2(st.m[cb], st.l[cb][0]);

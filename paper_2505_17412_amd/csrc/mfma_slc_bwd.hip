@@ -8,10 +8,11 @@
 // dQ of the same rows, which the wavefronts share out by output dims.  Two separate kernels form S and dP twice, 14 matrix
 // products per pair instead of 10, and fetch the query rows twice.
 //
-// What bounds it is the sum of the pipes of a SIMD, not one of them: per 32 keys x 32 query rows (d = 64) 24 + 8 matrix
-// instructions of 16.8 cycles, 16 exponentials and some 100 VALU instructions, 34 LDS reads and writes of 9 to 16 cycles, about
-// 1300 cycles in all; 1450 are measured, with two wavefronts per SIMD (registers, 256).  The rest is lost where a block does not
-// fill its workgroup's tiles.  Time of the two kernels before -> now: 62 k tokens of a 128^3 shell 3344 -> 3240 us, four such
+// The pipes of a SIMD take turns: per 32 keys x 32 query rows (d = 64) 32 + 8 matrix instructions of 16.8 cycles (S, dP, dV, dK;
+// dQ), 16 exponentials and some 100 VALU instructions, 34 LDS operands of 9 to 16 cycles, about 1430 cycles one after the other;
+// 1450 are measured, with two wavefronts per SIMD (registers).  That describes the schedule and is no lower bound: all wavefronts
+// pass the same phase behind one barrier, wait 43 % of their life and keep the matrix pipes 27 % busy.  Besides, a block that
+// does not fill its workgroup's tiles leaves wavefronts idle.  Time of the two kernels before -> now: 62 k tokens of a 128^3 shell 3344 -> 3240 us, four such
 // shapes (147 k) 8834 -> 7200, 65 k tokens in sequences with blocks of 64 2155 -> 1300, 21 k tokens in three 64^3 shells 642 -> 506.
 #include "mfma_common.h"
 #include "mfma_launch.h"
@@ -194,7 +195,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int h = 0; h < 2; ++h)  // query rows 4*(n & 3) .. +3 of the block, keys 8*quad + 4*h + (n >> 2)
       ds_r0[h] = SH::DS_OFF + ds_off(8 * quad + 4 * h + (n >> 2), 2 * qb0 + ((n >> 1) & 1)) + 8 * (n & 1);
     const int dq_w = SH::DQ_OFF + (16 * qb0 + n) * (D * 2) + ((((acc_dim(dtw, quad) >> 3) ^ (n >> 1)) & (D / 8 - 1)) << 4) + (quad & 1) * 8;
-    __syncthreads();  // the K tiles are read: their place may be overwritten
 
     auto scores = [&](int st, auto tiles) {  // stage st: S, dP, P, dS; dV, dK; dS to LDS
       constexpr int KT = decltype(tiles)::value;
