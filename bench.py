@@ -444,7 +444,7 @@ def ablation_sweep(args):
             branch_ms = {
                 "cmp": ks["cmp_fwd_scores_topk"] + dq_cw * f_c + ks["bwd_dkv_cmp"],
                 "slc": ks["slc_fwd"] + ks["fwd_invert_selection"] + ks["slc_merge_combine"] + ks["bwd_dq_slc"] + ks["bwd_dq_merge"]
-                       + ks["bwd_dkv_slc"] + ks["bwd_invert_selection"],
+                       + ks["bwd_dkv_slc"] + ks["bwd_slc_reduce"] + ks["bwd_invert_selection"],
                 "win": ks["win_fwd"] + dq_cw * (1 - f_c) + ks["bwd_dkv_win"],
             }
             other = sum(ks.values()) + ks["prep_sort_pool"] - sum(branch_ms.values())

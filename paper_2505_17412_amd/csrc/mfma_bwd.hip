@@ -661,10 +661,13 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     m_bwd_dkv<D, KB_KEYS, DKV_CMP, DKV_WAVES_CMP, ST><<<dim3(B * a.tiles_per_block, Hkv, w.q_splits), 64 * DKV_WAVES_CMP, dkv_lds, s>>>(a);
   }
   {
-    ProfScope ps(PROF_BWD_FINISH, s);
+    ProfScope ps(PROF_BWD_SLC_REDUCE, s);
     const size_t items = (size_t)N * Hkv * (D / 4);
     m_slc_reduce<<<(unsigned)((items + 255) / 256), 256, 0, s>>>(blk->tok_slc, v.slc_start, w.sel.chunk_start, w.sel.part_row_start, N,
                                                                  Hkv, v.Ns, D, w.pK, w.pV, w.dKs, w.dVs);
+  }
+  {
+    ProfScope ps(PROF_BWD_FINISH, s);
     m_bwd_finish<<<v.Nc, 128, 0, s>>>(v.perm, v.cmp_start, v.Nc, row, w.q_splits, w.dKs, w.dVs, w.dKc, w.dVc, (bf16_t *)dk,
                                       (bf16_t *)dv, w.dKc_out, w.dVc_out);
   }
