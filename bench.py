@@ -14,7 +14,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16
-FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32 vector ALU
+FP32_PEAK_TFLOPS = 157.3  # MI355X fp32, matrix instructions and vector ALU alike
 # kernels of ssa_forward as the profiling hook names them (prep_sort_pool also runs in ssa_backward)
 FWD_KERNELS = ("prep_sort_pool", "cmp_fwd_scores_topk", "fwd_invert_selection", "slc_fwd", "win_fwd", "slc_merge_combine")
 HBM_PEAK_GBS = 8000.0
@@ -572,11 +572,11 @@ def bench_workload(name, args, steps, warmup, cpu_seconds):
         ach = kflops[dom] / (kern_ms[dom] * 1e-3) / 1e12
         # a committed traffic figure covers the named workload in its own head shape only
         traffic, source = recorded_traffic(dom, name, d) if not args.heads else (None, None)
-        # the generic kernels (fp32 problems, shapes the MFMA kernels do not cover) do their contractions on the
-        # vector ALU: priced against the fp32 vector peak
+        # the generic kernels (fp32 problems, shapes the bf16 kernels do not cover) do their contractions with fp32 matrix
+        # instructions: priced against the fp32 peak
         generic = dom == "generic_path"
-        peak = FP32_VECTOR_PEAK_TFLOPS if generic else MFMA_BF16_PEAK_TFLOPS
-        roofline = {"bound": "alu" if generic else "mfma", "kernel": dom, "achieved": round(ach, 2), "peak": peak,
+        peak = FP32_PEAK_TFLOPS if generic else MFMA_BF16_PEAK_TFLOPS
+        roofline = {"bound": "mfma", "kernel": dom, "achieved": round(ach, 2), "peak": peak,
                     "unit": "TFLOP/s", "frac": round(ach / peak, 4),
                     "traffic": traffic, "traffic_source": source, "kernel_ms": round(kern_ms[dom], 4)}
     total_flops = (14 if bwd else 4) * d * all_pairs

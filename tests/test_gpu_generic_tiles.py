@@ -24,6 +24,12 @@ def test_generic_tile_edges(seed, grid, n, hq, hkv, d, m, topk, dtype):
     full_parity(inputs.random_points_workload(seed, grid, n, hq, hkv, d, m, topk, dtype))
 
 
+def test_score_row_that_leaves_the_kernel_one_token_at_a_time():
+    """15000 selection blocks in one item: a token's scores take most of the LDS, one token per workgroup."""
+    wl = inputs.make_sequence_workload(408, (30000,), 2, 1, 8, (1, 2, 4), 4, "f32")
+    full_parity(wl, queries=np.arange(5, 30000, 997, dtype=np.int32))
+
+
 def test_one_long_block_among_many_short_ones():
     """Half of the tokens on one voxel, the rest alone in their blocks: (longest block's tiles) x (selection chunks) is more
     workgroups than one launch of the key-centric kernel can have."""
