@@ -24,7 +24,8 @@ namespace {
 constexpr int SORT_THREADS = 512, SORT_WAVES = SORT_THREADS / 64;
 constexpr int DIGIT_BITS_MAX = 11, BINS_MAX = 1 << DIGIT_BITS_MAX;
 
-enum { META_ERR = 0, META_NC, META_NS, META_NW, META_SMAX, META_CMAX, META_SLC_TOK, META_WIN_TOK, META_CMP_TOK, META_N, META_DONE = META_N, META_INTS };
+enum { META_ERR = 0, META_NC, META_NS, META_NW, META_SMAX, META_CMAX, META_SLC_TOK, META_WIN_TOK, META_CMP_TOK, META_SLC_128,
+       META_SLC_256, META_N, META_DONE = META_N, META_INTS };
 
 // Spread the low 10 bits of v so that bit i lands on bit 3i.
 __device__ inline uint32_t spread3(uint32_t v) {
@@ -382,22 +383,28 @@ __global__ void k_check_offsets(const int32_t *__restrict__ offs, int N, int B, 
   }
 }
 
-// Largest per-item block counts and per-block token counts (integer max: order independent), then the counts to the host:
+// Largest per-item block counts and per-block token counts, and the tokens in long selection blocks (integer max and sum: order
+// independent), then the counts to the host:
 // the workgroup that finishes last copies them (and the error bits of the tiles) into pinned memory.
 constexpr int MAX_THREADS = 512;
 __global__ __launch_bounds__(MAX_THREADS) void k_maxima(CsrOut o, int B, const int32_t *__restrict__ err, int n_err, int32_t *meta,
                                                         int32_t *host_meta) {
-  __shared__ int best[5], last;
-  if (threadIdx.x < 5) best[threadIdx.x] = 0;
+  __shared__ int best[7], last;
+  if (threadIdx.x < 7) best[threadIdx.x] = 0;
   __syncthreads();
   const int Nc = meta[META_NC], Ns = meta[META_NS], Nw = meta[META_NW], i0 = blockIdx.x * MAX_THREADS + threadIdx.x;
   const int stride = gridDim.x * MAX_THREADS;
-  int m[5] = {0, 0, 0, 0, 0};  // in the order META_SMAX .. META_CMP_TOK
+  int m[5] = {0, 0, 0, 0, 0}, sum[2] = {0, 0};  // in the order META_SMAX .. META_CMP_TOK, META_SLC_128, META_SLC_256
   for (int i = i0; i < B; i += stride) {
     m[0] = max(m[0], o.slc_batch[i + 1] - o.slc_batch[i]);
     m[1] = max(m[1], o.cmp_batch[i + 1] - o.cmp_batch[i]);
   }
-  for (int i = i0; i < Ns; i += stride) m[2] = max(m[2], o.slc_start[i + 1] - o.slc_start[i]);
+  for (int i = i0; i < Ns; i += stride) {
+    const int len = o.slc_start[i + 1] - o.slc_start[i];
+    m[2] = max(m[2], len);
+    sum[0] += len > 128 ? len : 0;
+    sum[1] += len > 256 ? len : 0;
+  }
   for (int i = i0; i < Nw; i += stride) m[3] = max(m[3], o.win_start[i + 1] - o.win_start[i]);
   for (int i = i0; i < Nc; i += stride) m[4] = max(m[4], o.cmp_start[i + 1] - o.cmp_start[i]);
 #pragma unroll
@@ -406,11 +413,22 @@ __global__ __launch_bounds__(MAX_THREADS) void k_maxima(CsrOut o, int B, const i
     for (int off = 32; off >= 1; off >>= 1) m[x] = max(m[x], __shfl_xor(m[x], off));
     if ((threadIdx.x & 63) == 0) atomicMax(&best[x], m[x]);
   }
+  if (__any(sum[0] != 0)) {  // (sum[1] counts a part of sum[0])
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) sum[x] += __shfl_xor(sum[x], off);
+      if ((threadIdx.x & 63) == 0) atomicAdd(&best[5 + x], sum[x]);
+    }
+  }
   __syncthreads();
   // (device-scope atomics meet in memory; their returned values are waited for, so they are done before META_DONE counts
   // this workgroup, without a fence that would write back the caches)
   if (threadIdx.x < 5) {
     const int old = atomicMax(&meta[META_SMAX + threadIdx.x], best[threadIdx.x]);
+    asm volatile("" : : "v"(old));
+  } else if (threadIdx.x >> 1 == 32 && best[5 + (threadIdx.x & 1)]) {  // (two lanes of the second wavefront, beside the maxima)
+    const int old = atomicAdd(&meta[META_SLC_128 + (threadIdx.x & 1)], best[5 + (threadIdx.x & 1)]);
     asm volatile("" : : "v"(old));
   }
   __syncthreads();
@@ -604,6 +622,7 @@ static int build_handle(const ssa_params_t *p, const int32_t *coords, const int3
   h->Nc = host_meta[META_NC]; h->Ns = host_meta[META_NS]; h->Nw = host_meta[META_NW];
   h->s_max = host_meta[META_SMAX]; h->c_max = host_meta[META_CMAX]; h->slc_tok_max = host_meta[META_SLC_TOK];
   h->win_tok_max = host_meta[META_WIN_TOK]; h->cmp_tok_max = host_meta[META_CMP_TOK];
+  h->slc_tok_128 = host_meta[META_SLC_128]; h->slc_tok_256 = host_meta[META_SLC_256];
   pool.give(h->device, tmp, tmp_got);
   PinnedSlots::get().give(host_meta);
   *out = h;

@@ -9,7 +9,7 @@
 //   * m_bwd_dq: query-centric, same walk as the forward kernels (transposed scores, keys in the lanes), for the
 //     compression and window branches;
 //   * m_slc_bwd: the selection branch, block-centric like its forward kernel: dK, dV and one partial dQ row per selected
-//     block, added per token in rank order by m_dq_merge; at head_dim 128 two kernels, m_bwd_dq_bc and m_bwd_dkv;
+//     block, added per token in rank order by m_dq_merge; where long blocks dominate and at head_dim 128, two kernels, m_bwd_dq_bc and m_bwd_dkv;
 //   * m_bwd_dkv: key-centric; a wavefront owns 16*KB keys and streams the query rows that attend to them
 //     (scores with the query rows in the lanes); the contractions over query rows take Q^T and dO^T from the
 //     staged row-major tiles through the transposing LDS read.
@@ -587,6 +587,7 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
                     const ssa_blocks *blk, int B, hipStream_t s) {
   const int N = v.N, Hq = v.Hq, Hkv = v.Hkv, row = Hkv * D;
   const size_t NH = (size_t)N * Hq;
+  const bool two_kernels = slc_bwd_two_kernels(blk, D, Hkv, v.T);  // selection branch
   {
     ProfScope ps(PROF_BWD_PRE, s);
     PreArgs a{(const bf16_t *)q, (const bf16_t *)dout, (const bf16_t *)out_branch, (const bf16_t *)gates, lse, v.perm,
@@ -606,10 +607,10 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   }
   {
     ProfScope ps(PROF_BWD_INVERT, s);
-    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, false, !slc_bwd_fused(D), true, s);
+    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, false, two_kernels, true, s);
     if (rc != SSA_OK) return rc;
   }
-  if constexpr (slc_bwd_fused(D)) {
+  if (!two_kernels) {
     ProfScope ps1(PROF_BWD_SLC, s);
     const int rc = slc_bwd_kernel(v, D, w, blk->slc_tok_max, s);
     if (rc != SSA_OK) return rc;
@@ -632,7 +633,7 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   static std::once_flag dkv_once;
   std::call_once(dkv_once, [] {
     (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_WIN, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if constexpr (!slc_bwd_fused(D)) (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_CMP, DKV_WAVES_CMP, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   });
   DkvArgs base{v, w.Qs, nullptr, nullptr, nullptr, w.sel.list, w.dKs, w.dVs, w.sel.chunk_start, w.sel.order, w.sel.part_row_start, 1, 1};
@@ -643,7 +644,7 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     a.tiles_per_block = (blk->win_tok_max + WG_KEYS - 1) / WG_KEYS;
     m_bwd_dkv<D, KB_KEYS, DKV_WIN, DKV_WAVES, ST><<<dim3(blk->Nw * a.tiles_per_block, Hkv), 64 * DKV_WAVES, dkv_lds, s>>>(a);
   }
-  if constexpr (!slc_bwd_fused(D)) {
+  if (two_kernels) {
     ProfScope ps(PROF_BWD_DKV_SLC, s);
     DkvArgs a = base;
     a.lse2s = w.lse2s + NH; a.deltas = w.deltag + NH; a.dOs = w.dOg + NH * D;

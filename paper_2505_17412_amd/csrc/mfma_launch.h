@@ -63,9 +63,9 @@ struct BwdBuffers {
 // fp32 dQ of the other two branches (w.dQp), written to dq.
 int slc_dq_kernel(const MfmaView &v, int D, const BwdBuffers &w, hipStream_t s);
 // Both at once (mfma_slc_bwd.hip): partial dQ per selected block and the per-chunk partial dK/dV of the selection branch.
-// For head_dim 128 the operands of 32 keys and their dK and dV take more registers than a wavefront has: two kernels there.
-constexpr bool slc_bwd_fused(int D) { return D <= 64; }
 int slc_bwd_kernel(const MfmaView &v, int D, const BwdBuffers &w, int slc_tok_max, hipStream_t s);
+// Whether the selection branch's backward takes the two kernels (slc_dq_kernel and the key-centric one) instead.
+bool slc_bwd_two_kernels(const ssa_blocks *b, int D, int Hkv, int T);
 int slc_dq_merge_kernel(const MfmaView &v, int D, const BwdBuffers &w, const int32_t *idx, void *dq, hipStream_t s);
 int mfma_backward_kernels(const MfmaView &v, int D, const BwdBuffers &w, const void *q, const void *gates,
                           const void *out_branch, const float *lse, const int32_t *idx, const void *dout, void *dq,

@@ -3,6 +3,23 @@
 #include "mfma_launch.h"
 #include "profile.h"
 
+// The one-pass selection backward takes a block's keys in segments, each a whole pass over the query rows: it is the faster form
+// where most keys lie in blocks of one segment (at head_dim 32, where a product is half as long and the barriers weigh more,
+// of one of 128 keys).  Backward of all branches, us, one pass / two kernels, with the share of tokens in longer blocks.
+// d = 64: 60 k tokens 0: 6510 / 6850; 90 k 0.09: 11130 / 12160; 24 k 0.21: 1774 / 1778; 96 k 0.25: 14930 / 14590; 30 k 0.64:
+// 2950 / 2435; 60 k in 512-key blocks 1: 6700 / 5680.  d = 32: 48 k 0.31: 5520 / 5900; 51 k 0.42: 6635 / 6165; 110 k 0.85: 24040 /
+// 19940.  Small problems are faster in fewer launches whatever their blocks: up to 512 keys, 48 k selections 503 / 538, 80 k 820 /
+// 730.  The key-centric kernel has workgroups for the longest block's tiles of 128 keys in every chunk: one block of many thousand
+// tokens among many short ones would launch millions that find no key.  At head_dim 128 the operands of 32 keys and their dK and
+// dV take more registers than a wavefront has: two kernels.
+bool slc_bwd_two_kernels(const ssa_blocks *b, int D, int Hkv, int T) {
+  if (D > 64) return true;
+  const long long entries = (long long)b->N * Hkv * T;
+  const long long workgroups = (entries / 1024 + (long long)Hkv * b->Ns + 1) * ((b->slc_tok_max + 127) / 128);
+  if (entries < 65536 || workgroups > 1 << 22) return false;
+  return D == 64 ? 5ll * b->slc_tok_256 > b->N : 3ll * b->slc_tok_128 > b->N;
+}
+
 namespace {
 
 struct Tail { bf16_t *p; size_t begin, end; };  // element range to clear
@@ -167,9 +184,9 @@ BwdPlan bwd_plan(const ssa_ctx &c) {
   // slc_tok_max * entries/chunk_len + N*Hkv.  A chunk is one workgroup.  The one-pass kernel wants some thousands of them, so
   // that the last ones to end leave few compute units idle, and chunks of 512 rather than 256 once there are enough (half the
   // partial dK and dV rows: 256 and 512 tokens took 527 and 616 us at 21 k tokens, 1430 and 1407 at 65 k; 1024 was slower).  The
-  // two-kernel form (d = 128) measured best at 1024.  chunk_len grows until the partial sums fit in about 1 GiB.
+  // two-kernel form measured best at 1024.  chunk_len grows until the partial sums fit in about 1 GiB.
   const size_t entries = (size_t)c.N * c.Hkv * c.T;
-  p.chunk_len = !slc_bwd_fused(c.d) ? 1024 : entries / 256 < 4096 ? 256 : 512;
+  p.chunk_len = slc_bwd_two_kernels(b, c.d, c.Hkv, c.T) ? 1024 : entries / 256 < 4096 ? 256 : 512;
   size_t rows;
   for (;;) {
     rows = (size_t)b->slc_tok_max * (entries / p.chunk_len + 1) + (size_t)c.N * c.Hkv;

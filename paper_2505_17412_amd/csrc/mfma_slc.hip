@@ -322,7 +322,8 @@ __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dQ of the selection branch, block-centric: the same exchange of loops as the forward kernel m_slc_fwd_bc.  A workgroup
+// dQ of the selection branch where it does not go with dK and dV (slc_bwd_two_kernels), block-centric: the same exchange of
+// loops as the forward kernel m_slc_fwd_bc.  A workgroup
 // holds one selection block's K and V rows in LDS and runs through a chunk of the tokens that selected it; every
 // wavefront takes 16/h_s tokens per step on its own (query and dO rows in registers, no barrier, no column that did
 // not select the block).  One bf16 partial dQ per (token, KV head, selected block) goes to memory; m_dq_merge adds them
@@ -494,8 +495,8 @@ __global__ __launch_bounds__(256) void m_dq_merge(DqMergeArgs a) {
   *reinterpret_cast<bf16x8 *>(a.dQ + ((size_t)tok * a.Hq + h) * a.D + 8 * c8) = o;
 }
 
-// Shape of the block-centric kernels per head dimension: wavefronts per workgroup, keys held in LDS at a time.
-template <int D> struct BcShape { static constexpr int NW = 8, KSEG = 256; };
+// dQ: wavefronts per workgroup, keys held in LDS at a time.
+constexpr int DQ_WAVES = 8, DQ_KSEG = 256;
 // Forward: 16-column blocks per wavefront, wavefronts per workgroup and per SIMD (see m_slc_fwd_bc for the figures).
 template <int D> struct BcFwdShape { static constexpr int CB = 2, NW = 8, KSEG = 256, WPE = 4; };
 template <> struct BcFwdShape<64> { static constexpr int CB = 1, NW = 8, KSEG = 256, WPE = 4; };
@@ -523,15 +524,14 @@ int launch_slc_forward(const MfmaView &v, const bf16_t *q, const SelIndex &sel, 
 
 template <int D>
 int launch_slc_dq(const MfmaView &v, const BwdBuffers &w, hipStream_t s) {
-  using BS = BcShape<D>;
   static std::once_flag once;
   std::call_once(once, [] {
-    (void)hipFuncSetAttribute((const void *)m_bwd_dq_bc<D, BS::NW, BS::KSEG>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void *)m_bwd_dq_bc<D, DQ_WAVES, DQ_KSEG>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               160 * 1024);
   });
   const size_t NH = (size_t)v.N * v.Hq;
   BcDqArgs b{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.list, w.sel.bc_chunk_start, w.sel.rank, w.sel.bc_order, w.part.o};
-  m_bwd_dq_bc<D, BS::NW, BS::KSEG><<<dim3((chunk_bound(v, w.sel.bc_chunk_len) + 7) / 8 * 8), 64 * BS::NW, bc_dq_lds_bytes<D, BS::KSEG>(), s>>>(b);
+  m_bwd_dq_bc<D, DQ_WAVES, DQ_KSEG><<<dim3((chunk_bound(v, w.sel.bc_chunk_len) + 7) / 8 * 8), 64 * DQ_WAVES, bc_dq_lds_bytes<D, DQ_KSEG>(), s>>>(b);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
@@ -557,8 +557,12 @@ int slc_merge_kernel(const MfmaView &v, int D, const SlcPartials &part, const in
 }
 
 int slc_dq_kernel(const MfmaView &v, int D, const BwdBuffers &w, hipStream_t s) {
-  static_assert(!slc_bwd_fused(128), "the head_dim this kernel is for");
-  return D == 128 ? launch_slc_dq<128>(v, w, s) : SSA_ERR_UNSUPPORTED;
+  switch (D) {
+    case 32: return launch_slc_dq<32>(v, w, s);
+    case 64: return launch_slc_dq<64>(v, w, s);
+    case 128: return launch_slc_dq<128>(v, w, s);
+    default: return SSA_ERR_UNSUPPORTED;
+  }
 }
 
 int slc_dq_merge_kernel(const MfmaView &v, int D, const BwdBuffers &w, const int32_t *idx, void *dq, hipStream_t s) {

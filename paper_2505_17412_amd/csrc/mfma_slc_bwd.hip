@@ -3,17 +3,19 @@
 // (the dO rows are gate * dO); dV += P^T dO, dK += dS^T Q, dQ += dS K (the softmax scale is applied to the finished sums).
 //
 // A workgroup owns the keys of one selection block (32 per wavefront, as matrix operands in registers with their dK and dV
-// accumulators) and streams the query rows of a chunk of the tokens that selected the block, 64 rows per stage through LDS.
+// accumulators; the keys of a longer block in segments) and streams the query rows of a chunk of the tokens that selected the
+// block, 64 rows per stage through LDS.
 // Scores and dP are formed once: the dS tiles stay in registers for dK and go to LDS, transposed for free by the layout, for
 // dQ of the same rows, which the wavefronts share out by output dims.  Two separate kernels form S and dP twice, 14 matrix
-// products per pair instead of 10, and fetch the query rows twice.
+// products per pair instead of 10, and fetch the query rows twice; but a segment costs a whole pass over the query rows whatever
+// its length, with the dQ rows of the segment before read back, so that long blocks are left to them where there are many.
 //
 // The pipes of a SIMD take turns: per 32 keys x 32 query rows (d = 64) 32 + 8 matrix instructions of 16.8 cycles (S, dP, dV, dK;
 // dQ), 16 exponentials and some 100 VALU instructions, 34 LDS operands of 9 to 16 cycles, about 1430 cycles one after the other;
 // 1450 are measured, with two wavefronts per SIMD (registers).  That describes the schedule and is no lower bound: all wavefronts
 // pass the same phase behind one barrier, wait 43 % of their life and keep the matrix pipes 27 % busy.  Besides, a block that
-// does not fill its workgroup's tiles leaves wavefronts idle.  Time of the two kernels before -> now: 62 k tokens of a 128^3 shell 3344 -> 3240 us, four such
-// shapes (147 k) 8834 -> 7200, 65 k tokens in sequences with blocks of 64 2155 -> 1300, 21 k tokens in three 64^3 shells 642 -> 506.
+// does not fill its workgroup's tiles leaves wavefronts idle.  Time of the two kernels -> one pass: 62 k tokens of a 128^3 shell
+// 3344 -> 3240 us, four such shapes (147 k) 8834 -> 7200, 65 k tokens in sequences with blocks of 64 2155 -> 1300, 21 k tokens in three 64^3 shells 642 -> 506.
 #include "mfma_common.h"
 #include "mfma_launch.h"
 #include "mfma_qc.h"
@@ -64,7 +66,8 @@ __device__ inline int ds_off(int key, int unit) {
   return key * 128 + ((unit ^ (((key >> 2) & 1) | (key & 2) | ((key >> 1) & 4))) << 4);
 }
 
-template <int D, int NW>
+// SEG: blocks of more than KEYS keys are served, in segments (its second form of the stage loop spills 7 registers at d = 64).
+template <int D, int NW, bool SEG>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void m_slc_bwd(SlcBwdArgs a) {
   using P = PTile<D>;
   using SH = SlcBwdShape<D, NW>;
@@ -148,7 +151,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   };
 
   // blocks longer than a workgroup's keys are taken in segments, dQ continuing from the partial rows of the segment before
-  for (int ks0 = kbeg; ks0 < kend; ks0 += SH::KEYS) {
+  int ks0 = kbeg;
+  do {
     const int nk = min(SH::KEYS, kend - ks0), n_ks = (nk + 31) >> 5;
     // this wavefront's tiles of 16 keys: number wid and, if there are so many, wid + NW.  Wavefronts without a tile still
     // stage rows, share the dQ product and keep the barriers.
@@ -258,22 +262,28 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
       }
     };
-    auto dq_product = [&](int st, auto cont) {  // rows of stage st: this wavefront's dims of dQ, to LDS
-      f32x4 acc[QB];
+    // this wavefront's share of the partial rows of stage st from the segment before (written by this workgroup, read past the
+    // L1); rows that do not exist read the spare row, and their sums go back there
+    struct Partials { uint64_t w[QB]; };
+    auto load_partials = [&](int st, Partials &p) {
       const uint32_t *rows = (const uint32_t *)(smem + SH::ROW_OFF) + (st & 3) * ROWS;
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
-        acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (decltype(cont)::value) {  // continue from the partial of the segment before (written by this workgroup, read past the L1)
-          const int row = 16 * (qb0 + q) + n;
-          const uint32_t pr = rows[row / hs];
-          if (pr != dummy) {
-            const uint64_t w = __hip_atomic_load((const uint64_t *)(a.pdq + (size_t)(pr + row % hs) * D + acc_dim(dtw, quad)),
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const bf16x4 x = __builtin_bit_cast(bf16x4, w);
+        const int row = 16 * (qb0 + q) + n;
+        const uint32_t pr = rows[row / hs];
+        p.w[q] = __hip_atomic_load((const uint64_t *)(a.pdq + (size_t)(pr + (pr == dummy ? 0 : row % hs)) * D + acc_dim(dtw, quad)),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    };
+    auto dq_product = [&](int st, auto cont, const Partials &p) {  // rows of stage st: this wavefront's dims of dQ, to LDS
+      f32x4 acc[QB];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[q][i] = (float)x[i];
-          }
+      for (int q = 0; q < QB; ++q) {
+        acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (decltype(cont)::value) {
+          const bf16x4 x = __builtin_bit_cast(bf16x4, p.w[q]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[q][i] = (float)x[i];
         }
       }
       const lds_cptr base = (lds_cptr)smem + (SH::DOUBLE ? (st & 1) * SH::DS_B : 0);
@@ -324,8 +334,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       store_dq(-1);  // (to the spare row: the loop is entered with the same loads and stores outstanding as an iteration leaves)
 #pragma unroll 1
       for (int i = 0; i < n_st + 1 + SH::LAG; ++i) {
+        Partials part{};
         store_stage(i, regs);
         __syncthreads();
+        if constexpr (decltype(cont)::value) load_partials(i - SH::LAG, part);
         load_stage(i + 1, regs, pos);
         load_positions(i + 2, pos);
         store_dq(i - 1 - SH::LAG);
@@ -334,11 +346,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
           else if (my_tiles == 1) scores(i, std::integral_constant<int, 1>());
         }
         if (!SH::DOUBLE) __syncthreads();
-        if (i >= SH::LAG && i < n_st + SH::LAG) dq_product(i - SH::LAG, cont);
+        if (i >= SH::LAG && i < n_st + SH::LAG) dq_product(i - SH::LAG, cont, part);
       }
     };
-    if (ks0 == kbeg) stream(std::false_type());
-    else stream(std::true_type());
+    if (!SEG || ks0 == kbeg) stream(std::false_type());
+    else if constexpr (SEG) stream(std::true_type());
     {
 #pragma unroll
       for (int kbk = 0; kbk < KB; ++kbk) {
@@ -353,21 +365,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
       }
     }
-    if (ks0 + SH::KEYS < kend) {  // the next segment reads the partial rows back
+    ks0 += SH::KEYS;
+    if (SEG && ks0 < kend) {  // the next segment reads the partial rows back
       __threadfence();
       __syncthreads();
     }
-  }
+  } while (SEG && ks0 < kend);
 }
 
-template <int D, int NW>
+template <int D, int NW, bool SEG>
 void launch(SlcBwdArgs a, int lo, int hi, unsigned chunks, hipStream_t s) {
   using SH = SlcBwdShape<D, NW>;
   static std::once_flag once;  // raise the dynamic LDS limit once per process for this instantiation
-  std::call_once(once, [] { (void)hipFuncSetAttribute((const void *)m_slc_bwd<D, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_B); });
+  std::call_once(once, [] { (void)hipFuncSetAttribute((const void *)m_slc_bwd<D, NW, SEG>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_B); });
   a.len_lo = lo;
   a.len_hi = hi;
-  m_slc_bwd<D, NW><<<dim3(chunks), SH::NTHR, SH::LDS_B, s>>>(a);
+  m_slc_bwd<D, NW, SEG><<<dim3(chunks), SH::NTHR, SH::LDS_B, s>>>(a);
 }
 
 template <int D>
@@ -375,11 +388,14 @@ int launch_slc_bwd(const MfmaView &v, const BwdBuffers &w, int slc_tok_max, hipS
   const size_t NH = (size_t)v.N * v.Hq;
   SlcBwdArgs a{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.list, w.sel.chunk_start, w.sel.part_row_start, w.sel.rank,
                w.sel.order, w.part.o, w.pK, w.pV, 0, 0};
+  constexpr int SHORT = SlcBwdShape<D, 4>::KEYS, LONG = SlcBwdShape<D, 8>::KEYS;
+  const unsigned chunks = (unsigned)w.max_chunks;
   // blocks of up to 128 keys: 4 wavefronts, two workgroups per compute unit; longer ones: 8 wavefronts, so that dQ of a
   // block is complete after 256 keys (4 wavefronts, which read the partial row of the first 128 keys back, took 3770 us for
   // 3390 with the line at 160 keys, 5170 at 192)
-  launch<D, 4>(a, 0, SlcBwdShape<D, 4>::KEYS, (unsigned)w.max_chunks, s);
-  if (slc_tok_max > SlcBwdShape<D, 4>::KEYS) launch<D, 8>(a, SlcBwdShape<D, 4>::KEYS, 0x7fffffff, (unsigned)w.max_chunks, s);
+  launch<D, 4, false>(a, 0, SHORT, chunks, s);
+  if (slc_tok_max > LONG) launch<D, 8, true>(a, SHORT, 0x7fffffff, chunks, s);
+  else if (slc_tok_max > SHORT) launch<D, 8, false>(a, SHORT, LONG, chunks, s);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 

@@ -23,6 +23,7 @@ struct ssa_blocks {
   int32_t s_max;        // max selection blocks in one item
   int32_t c_max;        // max compression blocks in one item
   int32_t slc_tok_max;  // max tokens in one selection block
+  int32_t slc_tok_128, slc_tok_256;  // tokens in selection blocks of more than 128 / 256 tokens
   int32_t win_tok_max;  // max tokens in one window
   int32_t cmp_tok_max;  // max tokens in one compression block
   int device;

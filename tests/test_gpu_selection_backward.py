@@ -1,6 +1,8 @@
-"""GPU: the one-pass selection backward at the edges of its workgroups, on sequences, where the lengths of the selection
-blocks can be set: tiles of 16 keys, 128 keys for four wavefronts, 256 for eight, longer blocks in segments; 4 to 64 tokens
-per stage; query lists shorter than a stage.  Tolerances of the other parity tests."""
+"""GPU: the selection backward at the edges of its workgroups, on sequences, where the lengths of the selection blocks can be set.
+One pass: tiles of 16 keys, 128 keys for four wavefronts, 256 for eight, longer blocks in segments; 4 to 64 tokens per stage;
+query lists shorter than a stage.  Two kernels (long blocks in a problem of 2^16 selections or more) on either side of the line
+between the forms.  Tolerances of the other parity tests."""
+import numpy as np
 import pytest
 
 from paper_2505_17412_amd import inputs
@@ -17,6 +19,24 @@ pytestmark = pytest.mark.gpu
     (505, (1300, 513), 8, 1, 32, (16, 256, 64), 2),      # eight full wavefronts, a block of one key
     (506, (1200,), 8, 1, 64, (26, 286, 128), 3),         # 30 keys in a second segment
     (507, (1700,), 4, 1, 32, (40, 800, 64), 2),          # four segments, the last of 32 keys; 16 tokens per stage
+    (508, (1025,), 16, 1, 64, (32, 256, 64), 64),        # 65600 selections, no block beyond 256 keys: one pass
+    (509, (1028,), 16, 1, 64, (1, 257, 64), 64),         # one key more: two kernels, the last key a segment of its own
+    (510, (1025,), 8, 1, 32, (32, 128, 64), 64),         # head_dim 32, no block beyond 128 keys: one pass
+    (511, (1032,), 8, 1, 32, (43, 129, 64), 64),         # one key more: two kernels
+    (512, (1100, 30), 4, 2, 64, (40, 600, 64), 32),      # two kernels, blocks of 30, 500 and 600 keys
+    (513, (1023,), 16, 1, 64, (40, 600, 64), 64),        # 65472 selections: one pass
 ])
 def test_selection_backward_edges(seed, lens, hq, hkv, d, l, topk):
     full_parity(inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk))
+
+
+def test_one_long_block_among_many_short_ones():
+    """Half of the tokens on one voxel, the rest alone in their blocks: the two kernels would launch 5 million workgroups."""
+    wl = inputs.random_points_workload(520, 64, (18300,) + (300,) * 60, 16, 2, 64, (1, 2, 2), 2, "bf16")
+    rng = np.random.default_rng(520)
+    for a, b in zip(wl.batch_offsets[:-1], wl.batch_offsets[1:]):
+        first = b - 300
+        block = rng.choice(32 ** 3, size=300, replace=False)
+        wl.coords[first:b] = 2 * np.stack(np.unravel_index(block, (32, 32, 32)), axis=-1)
+        wl.coords[a:first] = wl.coords[first]
+    full_parity(wl, queries=np.arange(0, wl.n_tokens, 41, dtype=np.int32))

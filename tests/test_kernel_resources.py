@@ -32,3 +32,10 @@ def test_convolution_of_128_channels_keeps_two_wavefronts_per_simd(tmp_path):
     assert len(conv) == 4  # both directions, 64 and 128 tokens per workgroup
     for name, r in conv.items():
         assert r["Occupancy"] >= 2 and r["VGPRs Spill"] == 0, (name, r)
+
+
+def test_one_pass_selection_backward_fits_its_registers(tmp_path):
+    kernels = {k: v for k, v in resources("mfma_slc_bwd.hip", tmp_path).items() if re.search(r"m_slc_bwdILi\d+ELi\dELb0", k)}
+    assert len(kernels) == 4  # blocks of one segment: head_dim 32 and 64, 4 and 8 wavefronts
+    for name, r in kernels.items():
+        assert r["Occupancy"] >= 2 and r["VGPRs Spill"] == 0, (name, r)
