@@ -408,18 +408,17 @@ __global__ __launch_bounds__(MAX_THREADS) void k_maxima(CsrOut o, int B, const i
   for (int i = i0; i < Nw; i += stride) m[3] = max(m[3], o.win_start[i + 1] - o.win_start[i]);
   for (int i = i0; i < Nc; i += stride) m[4] = max(m[4], o.cmp_start[i + 1] - o.cmp_start[i]);
 #pragma unroll
-  for (int x = 0; x < 5; ++x) {
+  for (int off = 32; off >= 1; off >>= 1) {  // (seven independent chains of lane exchanges)
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m[x] = max(m[x], __shfl_xor(m[x], off));
-    if ((threadIdx.x & 63) == 0) atomicMax(&best[x], m[x]);
+    for (int x = 0; x < 5; ++x) m[x] = max(m[x], __shfl_xor(m[x], off));
+    sum[0] += __shfl_xor(sum[0], off);
+    sum[1] += __shfl_xor(sum[1], off);
   }
-  if (__any(sum[0] != 0)) {  // (sum[1] counts a part of sum[0])
+  if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) sum[x] += __shfl_xor(sum[x], off);
-      if ((threadIdx.x & 63) == 0) atomicAdd(&best[5 + x], sum[x]);
-    }
+    for (int x = 0; x < 5; ++x) atomicMax(&best[x], m[x]);
+    if (sum[0]) atomicAdd(&best[5], sum[0]);
+    if (sum[1]) atomicAdd(&best[6], sum[1]);
   }
   __syncthreads();
   // (device-scope atomics meet in memory; their returned values are waited for, so they are done before META_DONE counts

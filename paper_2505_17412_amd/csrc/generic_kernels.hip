@@ -15,7 +15,7 @@
 // partial results meet in LDS and are added in wavefront order (every sum in one fixed order: no atomics).
 // Bound: latency of the walks at a few thousand tokens (2874 tokens, 4 heads of 32, forward + backward: 6.55 -> 0.27 ms;
 // the former kernels ran one row per wavefront with the dims in a scalar loop), fp32 matrix rate above (6000 tokens, 16 heads of
-// 64: 35-60 of the 136 TFLOP/s a large fp32 product reaches).
+// 64: 35-60 of the 153 TFLOP/s a large fp32 product reaches).
 #include "ssa_internal.h"
 #include "profile.h"
 #include "topk_device.h"

@@ -13,7 +13,7 @@
 // The pipes of a SIMD take turns: per 32 keys x 32 query rows (d = 64) 32 + 8 matrix instructions of 16.8 cycles (S, dP, dV, dK;
 // dQ), 16 exponentials and some 100 VALU instructions, 34 LDS operands of 9 to 16 cycles, about 1430 cycles one after the other;
 // 1450 are measured, with two wavefronts per SIMD (registers).  That describes the schedule and is no lower bound: all wavefronts
-// pass the same phase behind one barrier, wait 43 % of their life and keep the matrix pipes 27 % busy.  Besides, a block that
+// pass the same phase behind one barrier, wait 41 % of their life and keep the matrix pipes 26 % busy.  Besides, a block that
 // does not fill its workgroup's tiles leaves wavefronts idle.  Time of the two kernels -> one pass: 62 k tokens of a 128^3 shell
 // 3344 -> 3240 us, four such shapes (147 k) 8834 -> 7200, 65 k tokens in sequences with blocks of 64 2155 -> 1300, 21 k tokens in three 64^3 shells 642 -> 506.
 #include "mfma_common.h"
