@@ -41,7 +41,21 @@ __device__ inline bf16x8 ones_operand() {
   asm volatile("" : "+v"(w));
   return __builtin_bit_cast(bf16x8, w);
 }
+// A uniform factor of the per-score arithmetic, kept in a vector register: a vector instruction of three vector operands
+// issues every 2.7 cycles with four wavefronts per SIMD, one with a scalar operand every 4.5 (measured on v_fma, v_fmac and
+// v_mul alike).  The empty asm makes the value opaque, so it is not moved back to a scalar register.
+__device__ inline float in_vgpr(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Waits for every load and store in flight (vmcnt(0), the other counters untouched).  The compiler knows the instruction: in front
+// of a loop it lets the waits inside count on what an iteration leaves in flight, stores behind its loads among them.
+__device__ inline void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// A value that is the same in all lanes, in a scalar register: branches and loops on it are scalar ones.
+__device__ inline int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 __device__ inline int wave_min_i(int v) {
 #pragma unroll

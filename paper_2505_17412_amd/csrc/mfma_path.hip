@@ -109,7 +109,7 @@ FwdPlan fwd_plan(const ssa_ctx &c) {
   p.lse = take((size_t)3 * c.N * c.Hq * 4);
   p.idx = take((size_t)c.N * c.Hkv * c.T * 4);
   p.sel = take(sel_index_bytes(c.N, c.Hkv, c.T, c.blk->Ns));
-  const size_t slots = (size_t)c.N * c.Hkv * c.T * c.hs;  // one partial row per (token, query head, selected block)
+  const size_t slots = (size_t)c.N * c.Hkv * c.T * c.hs + 1;  // one partial row per (token, query head, selected block), one spare
   p.po = take(slots * c.d * 2);
   p.pml = take(slots * 2 * 4);
   p.total = off;

@@ -6,6 +6,7 @@
 #include "mfma_launch.h"
 #include "mfma_qc.h"
 #include "mfma_bc.h"
+#include "mfma_t32.h"
 
 #include <mutex>
 
@@ -16,19 +17,19 @@ namespace {
 // the inner one over the query tokens that selected the block.  A workgroup takes one (KV head, selection block) and a
 // chunk of up to BC_CHUNK tokens of that block's selector list, puts the block's K and V rows into LDS ONCE (up to KSEG
 // keys; longer blocks in several segments) and lets every wavefront run, on its own and without any barrier, through
-// groups of CB*16/h_s tokens: all CB*16 query columns of a matrix tile then take part in every key tile (nothing is
-// computed for a token that did not select the block), the K and V^T operands read from LDS feed CB column blocks,
-// and no wavefront waits for another.  The price is one partial result per (token, KV head, selected block): the
-// unnormalised output in bf16 with its running maximum and sum (Algorithm 1's o, m, l for that block alone), merged per
-// token afterwards (m_slc_merge).  A wavefront that meets a block longer than KSEG picks its own partial up again for
-// the next segment.
-// Bound: the sum of matrix and vector issue (a synthetic copy of one 16-column tile with its LDS reads takes 116 ns per SIMD
-// at four wavefronts, of which this kernel's tiles and steps take 145), and for short blocks the partial rows going out.
-// One column block at head_dim 64 (128 registers, four wavefronts per SIMD; two blocks at two or four wavefronts: 1111 and
-// 1038 us against 989), two at head_dim 128, where the accumulators leave two wavefronts anyway.  62k tokens, 16 heads of
-// 64, top-16: 1090 -> 990 us (no maximum and no rescaling after the first tile, chunk entries prepared in LDS, list entries
-// and chunk bounds read directly); 153k tokens, heads of 128: 12.4 -> 11.3 ms; blocks of 64 keys (sequences): 807 -> 738 us
-// with whole-line stores.
+// steps of 32/h_s tokens: all 32 query columns of a matrix tile then take part in every key tile (nothing is
+// computed for a token that did not select the block) and no wavefront waits for another.  The price is one partial result per
+// (token, KV head, selected block): the unnormalised output in bf16 with its reference exponent and sum (Algorithm 1's o, m, l for
+// that block alone), merged per token afterwards (m_slc_merge).  A wavefront that meets a block longer than KSEG picks its own
+// partial up again for the next segment.
+// Bound: for blocks of ordinary length the sum of matrix and vector issue (a tile of 32 x 32 scores at head_dim 64 is 288 matrix
+// cycles and about 250 of exponentials, conversions and multiply-adds; a synthetic copy takes 226 ns per SIMD at four wavefronts,
+// with the clock down to 1.8 GHz), beside the partial rows going out (2.0 GB at 62k tokens = 440 us of writing; without any tile
+// but the last of a block 770 us).  32 columns per wavefront against 16: an operand read from LDS feeds twice the matrix work, and
+// the four SIMDs no longer ask LDS for every cycle it has.  Four wavefronts per SIMD at head_dim 64 (126 registers; the query rows of
+// the next step are loaded into the registers of this step's as soon as its last scores are formed).  A step's stores are not waited
+// for by the next one (t32_store_rows, wait_loads).  62k tokens, 16 heads of 64, top-16: 1010 -> 888 us; 11k tokens, top-8: 155 ->
+// 130; sequences of 64-key blocks 755 -> 650; 153k tokens, heads of 128: 10.4 -> 9.3 ms (with 16 columns per wavefront before).
 // ---------------------------------------------------------------------------------------------------------
 struct BcFwdArgs {
   MfmaView v;
@@ -36,98 +37,86 @@ struct BcFwdArgs {
   const int32_t *sel_list, *chunk_start;  // lists of caller indices
   const uint8_t *sel_rank;
   const ChunkRef *chunk_order;
-  bf16_t *po;  // [N][Hkv][T][hs][D]
-  float *pml;  // [N][Hkv][T][hs][2]
+  bf16_t *po;  // [N][Hkv][T][hs][D] and a spare row
+  float *pml;  // [N][Hkv][T][hs][2], the same
 };
 
-// LDS plan (bytes): K tiles | V tiles (KSEG/32 tiles each, PTile layout) | chunk entries [BC_CHUNK][2]
+// LDS plan (bytes): K tiles | V tiles (KSEG/32 tiles each) | chunk entries [BC_CHUNK][2] | what the last tile's scores start from
 template <int D, int KSEG>
-constexpr size_t bc_lds_bytes() { return (size_t)2 * (KSEG / 32) * PTile<D, false>::BYTES + (size_t)2 * BC_CHUNK * sizeof(int); }
+constexpr size_t bc_lds_bytes() { return (size_t)2 * (KSEG / 32) * T32<D, false>::BYTES + (size_t)2 * BC_CHUNK * sizeof(int) + 32 * sizeof(float); }
 
-// Query operands and partial-row index of one wavefront step: column n of column block cb stands for chunk entry
-// (step*CB + cb)*(16/h_s) + n/h_s, head n % h_s of the KV group.  Columns past the end of the chunk repeat its last entry
-// and are not stored.
-template <int D, int CB>
+// Query operands and partial-row index of one wavefront step: column n stands for chunk entry step*(32/h_s) + n/h_s, head
+// n % h_s of the KV group.  Columns past the end of the chunk take the query rows of its last entry and the spare partial row.
+template <int D>
 struct BcRows {
-  bf16x8 qop[CB][D / 32];
-  uint32_t prow[CB];  // ((tok*Hkv + g)*T + rank)*hs + head: row of the partial arrays (below 2^32: N*Hq*T is)
-  bool valid[CB];
+  bf16x8 qop[D / 16];
+  uint32_t prow;  // ((tok*Hkv + g)*T + rank)*hs + head: row of the partial arrays (below 2^32: N*Hq*T is), or the spare one
 };
 
-// qoff, prow0: per chunk entry the byte offset of the token's query rows of this KV group and its first partial row.
-template <int D, int CB>
+// ent: per chunk entry the byte offset of the token's query rows of this KV group and its first partial row.
+template <int D>
 __device__ inline void bc_load_rows(const unsigned char *Q, const uint2 *ent, int step, int cnt, int lg_tpw, int slot, uint32_t lane_off,
-                                    int hl, BcRows<D, CB> &r) {
+                                    int hl, uint32_t spare, BcRows<D> &r) {
+  const int e = (step << lg_tpw) + slot;
+  const uint2 x = ent[min(e, cnt - 1)];
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    const int e = ((step * CB + cb) << lg_tpw) + slot;
-    r.valid[cb] = e < cnt;
-    const uint2 x = ent[min(e, cnt - 1)];
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) r.qop[cb][ks] = *reinterpret_cast<const bf16x8 *>(Q + (x.x + lane_off) + 64 * ks);
-    r.prow[cb] = x.y + hl;
-  }
+  for (int ks = 0; ks < D / 16; ++ks) r.qop[ks] = *reinterpret_cast<const bf16x8 *>(Q + (x.x + lane_off) + 32 * ks);
+  r.prow = e < cnt ? x.y + hl : spare;
 }
 
-// Scores of CB blocks of 16 query columns over one 32-key LDS tile: v[j] = key 8*quad + j of the tile, column n.
-template <int D, int CB>
-__device__ inline void bc_scores(const bf16x8 (&qop)[CB][D / 32], lds_cptr kt, const typename PTile<D, false>::Lanes &ln, float (&v)[CB][8]) {
-  f32x4 s[CB][2];
+// What the score accumulators of a segment's last tile start from: 0, and -inf for the keys that do not exist (their rows in LDS
+// are zeros).
+__device__ inline f32x16 bc_tail(const float *tail) {
+  f32x16 s;
+  int first = t32_row(0);
+  asm volatile("" : "+v"(first));  // (or the 16 values stay in registers between the steps)
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) s[cb][0] = s[cb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 x = *reinterpret_cast<const f32x4 *>(tail + first + 8 * i);
 #pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks)
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      const bf16x8 k = p_row_operand<D, false>(kt, ln, sub, ks);
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) s[cb][sub] = mfma16(k, qop[cb][ks], s[cb][sub]);
-    }
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[cb][j] = s[cb][j >> 2][j & 3];
+    for (int j = 0; j < 4; ++j) s[4 * i + j] = x[j];
+  }
+  return s;
+}
+__device__ inline void bc_write_tail(float *tail, int left) {
+  if (threadIdx.x < 32) tail[threadIdx.x] = (int)threadIdx.x < left ? 0.f : -INFINITY;
 }
 
-// One step of the softmax (Algorithm 1, inner loop body) over one tile.  The reference exponent of a column is the maximum
-// of its first tile (FIRST; log2 units, st.m) and stays: later tiles cost a fused multiply-add, an exponential and half a
-// conversion per score, no maximum and no rescaling.  The result does not depend on the reference as long as nothing leaves
-// the range of the floats, which the caller checks on the finished sums (bc_in_range).
-// MASK: only the first `left` keys of the tile exist.
-template <int D, int CB, bool MASK, bool FIRST>
-__device__ inline void bc_fwd_tile(FwdState<D, CB> &st, const bf16x8 (&qop)[CB][D / 32], lds_cptr kt, lds_cptr vt,
-                                   const typename PTile<D, false>::Lanes &ln, int left, float sl2, const bf16x8 &ones) {
-  float v[CB][8];
-  bc_scores<D, CB>(qop, kt, ln, v);
-  if (MASK) {
-    const int first = 8 * (int)(threadIdx.x >> 4 & 3);
+// Transposed scores of 32 query columns over one 32-key LDS tile: element i = key t32_row(i), column n.
+template <int D>
+__device__ inline f32x16 bc_scores(const bf16x8 (&qop)[D / 16], lds_cptr kt, const typename T32<D, false>::Lanes &ln, f32x16 s) {
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+  for (int ks = 0; ks < D / 16; ++ks) s = mfma32(T32<D, false>::row(kt, ln, ks), qop[ks], s);
+  return s;
+}
+
+// Softmax state of 32 query columns: unnormalised output (transposed), sum (l[0]), reference exponent (log2 units).
+template <int D>
+struct BcState {
+  f32x16 o[D / 32];
+  f32x4 l;
+  float m;
+};
+
+// One step of the softmax (Algorithm 1, inner loop body) over one tile with scores s.  The reference exponent of a column is the
+// maximum of its first tile (bc_reference) and stays: later tiles cost a fused multiply-add, an exponential and half a conversion
+// per score, no maximum and no rescaling.  The result does not depend on the reference as long as nothing leaves the range of the
+// floats, which the caller checks on the finished sums (bc_in_range).
+__device__ inline float bc_reference(const f32x16 &s, float sl2) { return t32_column_max(max16(s)) * sl2; }
+template <int D, bool FIRST = false>
+__device__ inline void bc_fwd_tile(BcState<D> &st, const f32x16 &s, lds_cptr vt, const typename T32<D, false>::Lanes &ln, float sl2,
+                                   const bf16x8 &ones) {
+  if (FIRST) st.m = bc_reference(s, sl2);
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (first + j >= left) v[cb][j] = -INFINITY;
-  }
-  if (FIRST) {
+  for (int kc = 0; kc < 2; ++kc) {
+    const bool fresh = FIRST && kc == 0;  // (no registers to clear: the products start from a constant)
+    bf16x8 p;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-      const float(&x)[8] = v[cb];
-      st.m[cb] = column_max(fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])))) * sl2;
-    }
-  }
-  bf16x8 pb[CB];
+    for (int j = 0; j < 8; ++j) p[j] = (__bf16)fast_exp2(__builtin_fmaf(s[8 * kc + j], sl2, -st.m));
+    // the normaliser on the matrix pipe, in the same bf16 rounding the numerator uses
+    st.l = mfma16(ones, p, fresh ? f32x4{0.f, 0.f, 0.f, 0.f} : st.l);
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) pb[cb][j] = (__bf16)fast_exp2(__builtin_fmaf(v[cb][j], sl2, -st.m[cb]));
-    // the normaliser on the matrix pipe: an all-ones A operand sums the 32 probabilities of every column, in the same bf16
-    // rounding the numerator uses, and leaves the total in every lane of the column
-    st.l[cb] = mfma16(ones, pb[cb], st.l[cb]);
-  }
-#pragma unroll
-  for (int dt = 0; dt < D / 16; ++dt) {
-    const bf16x8 av = p_tr_operand<D, false>(vt, ln, dt);
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) st.o[cb][dt] = mfma16(av, pb[cb], st.o[cb][dt]);
+    for (int db = 0; db < D / 32; ++db) st.o[db] = mfma32(T32<D, false>::tr(vt, ln, db, kc), p, fresh ? splat16(0.f) : st.o[db]);
   }
 }
 
@@ -135,135 +124,138 @@ __device__ inline void bc_fwd_tile(FwdState<D, CB> &st, const bf16x8 (&qop)[CB][
 // values of the same size.
 __device__ inline bool bc_in_range(float l) { return l < 0x1p60f; }
 
-// The same step with a running maximum (raised lazily, see fwd_tile): what a column whose scores rise far above its first
-// tile's goes through instead.  st.m in log2 units.
+// The same step with a running maximum (raised lazily): what a column whose scores rise far above its first tile's goes
+// through instead.
 template <int D>
-__device__ inline void bc_fwd_tile_safe(FwdState<D, 1> &st, const bf16x8 (&qop)[1][D / 32], lds_cptr kt, lds_cptr vt,
-                                        const typename PTile<D, false>::Lanes &ln, int left, float sl2, const bf16x8 &ones) {
-  float v[1][8];
-  bc_scores<D, 1>(qop, kt, ln, v);
-  const int first = 8 * (int)(threadIdx.x >> 4 & 3);
-  float pm = -INFINITY;
+__device__ inline void bc_fwd_tile_safe(BcState<D> &st, const bf16x8 (&qop)[D / 16], lds_cptr kt, lds_cptr vt,
+                                        const typename T32<D, false>::Lanes &ln, const f32x16 &s0, float sl2, const bf16x8 &ones) {
+  f32x16 s = bc_scores<D>(qop, kt, ln, s0);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    v[0][j] = first + j < left ? v[0][j] * sl2 : -INFINITY;
-    pm = fmaxf(pm, v[0][j]);
+  for (int i = 0; i < 16; ++i) s[i] *= sl2;
+  const float pm = max16(s);
+  if (__any(pm > st.m + 8.f)) {
+    const float mn = fmaxf(st.m, t32_column_max(pm));
+    const float alpha = mn == -INFINITY ? 1.0f : fast_exp2(st.m - mn);
+    st.l[0] *= alpha;
+    st.m = mn;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) st.o[db] *= alpha;
   }
-  if (__any(pm > st.m[0] + 8.f)) {
-    float tmax = fmaxf(pm, __shfl_xor(pm, 16));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-    const float mn = fmaxf(st.m[0], tmax);
-    const float alpha = mn == -INFINITY ? 1.0f : fast_exp2(st.m[0] - mn);
-    st.l[0][0] *= alpha;
-    st.m[0] = mn;
+  const float neg = st.m != -INFINITY ? -st.m : -INFINITY;
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) st.o[0][dt] *= alpha;
+  for (int kc = 0; kc < 2; ++kc) {
+    bf16x8 p;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = (__bf16)fast_exp2(s[8 * kc + j] + neg);
+    st.l = mfma16(ones, p, st.l);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) st.o[db] = mfma32(T32<D, false>::tr(vt, ln, db, kc), p, st.o[db]);
   }
-  const float neg = st.m[0] != -INFINITY ? -st.m[0] : -INFINITY;
-  bf16x8 pb;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) pb[j] = (__bf16)fast_exp2(v[0][j] + neg);
-  st.l[0] = mfma16(ones, pb, st.l[0]);
-#pragma unroll
-  for (int dt = 0; dt < D / 16; ++dt) st.o[0][dt] = mfma16(p_tr_operand<D, false>(vt, ln, dt), pb, st.o[0][dt]);
 }
 
-// Partial of the earlier segments of a long block, picked up again.
+// The 8 + 8 dims of block db that a lane holds of its column's row.
 template <int D>
-__device__ inline void bc_pick_up(const BcFwdArgs &a, uint32_t prow, bool valid, f32x4 (&o)[D / 16], f32x4 &l, float &m) {
-  const int quad = threadIdx.x >> 4 & 3;
-  m = 0.f;
-  if (!valid) return;
+__device__ inline void bc_pick_up_row(const bf16_t *rows, uint32_t prow, f32x16 (&o)[D / 32]) {
+  const bf16_t *src = rows + (size_t)prow * D + 8 * (threadIdx.x >> 5 & 1);
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const bf16x8 x = ld8(src + 32 * db + 16 * k);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[db][8 * k + i] = (float)x[i];
+    }
+}
+
+// The partial of the earlier segments, picked up again.
+template <int D>
+__device__ inline void bc_pick_up(const BcFwdArgs &a, uint32_t prow, BcState<D> &st) {
   const float2 ml = *reinterpret_cast<const float2 *>(a.pml + (size_t)prow * 2);
-  m = ml.x;
-  l[0] = ml.y;
-#pragma unroll
-  for (int dt = 0; dt < D / 16; ++dt) {
-    const bf16x4 x = *reinterpret_cast<const bf16x4 *>(a.po + (size_t)prow * D + acc_dim(dt, quad));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[dt][i] = (float)x[i];
-  }
+  st.m = ml.x;
+  st.l = f32x4{ml.y, 0.f, 0.f, 0.f};
+  bc_pick_up_row<D>(a.po, prow, st.o);
 }
 
-template <int D, int CB, int NW, int KSEG, int WPE>
+template <int D, int NW, int KSEG, int WPE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) void m_slc_fwd_bc(BcFwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  using P = PTile<D, false>;
+  using T = T32<D, false>;
   constexpr int MAXT = KSEG / 32;
-  unsigned char *Kt = smem, *Vt = Kt + MAXT * P::BYTES;
-  uint2 *ent = (uint2 *)(Vt + MAXT * P::BYTES);
-  const int wid = threadIdx.x >> 6, quad = threadIdx.x >> 4 & 3, n = threadIdx.x & 15;
+  unsigned char *Kt = smem, *Vt = Kt + MAXT * T::BYTES;
+  uint2 *ent = (uint2 *)(Vt + MAXT * T::BYTES);
+  float *tail = (float *)(ent + BC_CHUNK);
+  const int wid = uniform(threadIdx.x >> 6), h = threadIdx.x >> 5 & 1, n = threadIdx.x & 31;
   const int hs = a.v.hs, Hkv = a.v.Hkv, Ns = a.v.Ns;
   const int wi = bc_chunk_of_workgroup(a.chunk_start[Hkv * Ns]);
   if (wi < 0) return;
   const ChunkRef cr = a.chunk_order[wi];
-  const int g = cr.key / Ns, blk = cr.key % Ns;
-  const int kbeg = a.v.slc_start[blk], kend = a.v.slc_start[blk + 1];
-  const int qbeg = cr.first, cnt = cr.count;
+  const int key = uniform(cr.key), g = key / Ns, blk = key % Ns;
+  const int kbeg = uniform(a.v.slc_start[blk]), kend = uniform(a.v.slc_start[blk + 1]);
+  const int qbeg = uniform(cr.first), cnt = uniform(cr.count);
   for (int i = threadIdx.x; i < cnt; i += 64 * NW) {
     const uint32_t tok = (uint32_t)a.sel_list[qbeg + i];
     ent[i] = make_uint2((tok * a.v.Hq + g * hs) * (D * 2), ((tok * Hkv + g) * a.v.T + a.sel_rank[qbeg + i]) * hs);
   }
-  const int lg_tpw = 31 - __builtin_clz(16 / hs), slot = n / hs, hl = n % hs;
-  const uint32_t lane_off = (uint32_t)(hl * D * 2 + 16 * quad);
+  const int lg_tpw = 31 - __builtin_clz(32 / hs), slot = n / hs, hl = n % hs;
+  const uint32_t lane_off = (uint32_t)(hl * D * 2 + 16 * h);
   const unsigned char *Qb = (const unsigned char *)a.Q;
-  const int n_it = (cnt + (CB << lg_tpw) - 1) / (CB << lg_tpw);
+  const int n_it = (cnt + (1 << lg_tpw) - 1) >> lg_tpw;
   const uint32_t kstride = (uint32_t)(Hkv * D);
-  const float sl2 = a.v.sl2;
-  const bf16x8 ones = ones_operand();
-  const typename P::Lanes ln = P::lanes();
+  const float sl2 = in_vgpr(a.v.sl2);
+  const bf16x8 ones = column_ones();
+  const typename T::Lanes ln = T::lanes();
   const lds_cptr kl = (lds_cptr)Kt, vl = (lds_cptr)Vt;
+  const uint32_t spare = (uint32_t)((size_t)a.v.N * a.v.Hq * a.v.T);  // behind the last partial row
   __syncthreads();
-  BcRows<D, CB> cur;
-  if (wid < n_it) bc_load_rows<D, CB>(Qb, ent, wid, cnt, lg_tpw, slot, lane_off, hl, cur);  // in flight while the block is staged
+  BcRows<D> cur;
+  if (wid < n_it) bc_load_rows<D>(Qb, ent, wid, cnt, lg_tpw, slot, lane_off, hl, spare, cur);  // in flight while the block is staged
   for (int k0 = kbeg; k0 < kend; k0 += KSEG) {
-    const int nk = min(KSEG, kend - k0), nfull = nk >> 5;
+    const int nk = min(KSEG, kend - k0), last = (nk - 1) >> 5;
     if (k0 > kbeg) {
       __syncthreads();  // every wavefront is done with the previous segment
-      if (wid < n_it) bc_load_rows<D, CB>(Qb, ent, wid, cnt, lg_tpw, slot, lane_off, hl, cur);
+      if (wid < n_it) bc_load_rows<D>(Qb, ent, wid, cnt, lg_tpw, slot, lane_off, hl, spare, cur);
     }
-    p_stage2<D, false, 64 * NW>(a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D, kstride, k0, (nk + 31) >> 5, Kt, Vt);
+    t32_stage2<D, false, 64 * NW>(a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D, kstride, k0, nk, Kt, Vt);
+    bc_write_tail(tail, nk - 32 * last);
+    wait_loads();  // (so that the step loop is entered with no load outstanding and its waits count what an iteration leaves)
     __syncthreads();
+    const bool fresh = k0 == kbeg;
+    const lds_cptr klast = kl + last * T::BYTES, vlast = vl + last * T::BYTES;
     for (int it = wid; it < n_it; it += NW) {
-      BcRows<D, CB> nxt;  // the next step's operands are requested before this step's arithmetic
-      if (it + NW < n_it) bc_load_rows<D, CB>(Qb, ent, it + NW, cnt, lg_tpw, slot, lane_off, hl, nxt);
-      FwdState<D, CB> st;
-      init_state(st);
-      const bool fresh = k0 == kbeg;
-      if (!fresh)
+      const uint32_t prow = cur.prow;
+      BcState<D> st;
+      if (!fresh) bc_pick_up<D>(a, prow, st);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) bc_pick_up<D>(a, cur.prow[cb], cur.valid[cb], st.o[cb], st.l[cb], st.m[cb]);
-      if (fresh && nfull > 0) bc_fwd_tile<D, CB, false, true>(st, cur.qop, kl, vl, ln, 32, sl2, ones);
-      else if (fresh) bc_fwd_tile<D, CB, true, true>(st, cur.qop, kl, vl, ln, nk, sl2, ones);
-      else if (nfull > 0) bc_fwd_tile<D, CB, false, false>(st, cur.qop, kl, vl, ln, 32, sl2, ones);
-#pragma unroll
-      for (int t = 1; t < MAXT; ++t)
-        if (t < nfull) bc_fwd_tile<D, CB, false, false>(st, cur.qop, kl + t * P::BYTES, vl + t * P::BYTES, ln, 32, sl2, ones);
-      if ((nk & 31) && (nfull > 0 || !fresh))
-        bc_fwd_tile<D, CB, true, false>(st, cur.qop, kl + nfull * P::BYTES, vl + nfull * P::BYTES, ln, nk & 31, sl2, ones);
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) {
-        if (__builtin_expect(__any(cur.valid[cb] && !bc_in_range(st.l[cb][0])), 0)) {
-          FwdState<D, 1> safe;
-          init_state(safe);
-          bf16x8 q1[1][D / 32];
-#pragma unroll
-          for (int ks = 0; ks < D / 32; ++ks) q1[0][ks] = cur.qop[cb][ks];
-          if (k0 > kbeg) bc_pick_up<D>(a, cur.prow[cb], cur.valid[cb], safe.o[0], safe.l[0], safe.m[0]);
-#pragma unroll 1
-          for (int t = 0; t < (nk + 31) >> 5; ++t)
-            bc_fwd_tile_safe<D>(safe, q1, kl + t * P::BYTES, vl + t * P::BYTES, ln, nk - 32 * t, sl2, ones);
-          st.m[cb] = safe.m[0];
-          st.l[cb] = safe.l[0];
-#pragma unroll
-          for (int dt = 0; dt < D / 16; ++dt) st.o[cb][dt] = safe.o[0][dt];
+      for (int t = 0; t < MAXT - 1; ++t)
+        if (t < last) {
+          const f32x16 s = bc_scores<D>(cur.qop, kl + t * T::BYTES, ln, splat16(0.f));
+          if (t == 0 && fresh) bc_fwd_tile<D, true>(st, s, vl, ln, sl2, ones);
+          else bc_fwd_tile<D>(st, s, vl + t * T::BYTES, ln, sl2, ones);
         }
-        // (a column past the end of the chunk repeats the chunk's last entry and is not stored)
-        store_partial_row<D>(a.po, cur.prow[cb], st.o[cb], cur.valid[cb]);
-        if (cur.valid[cb] && quad == 0)
-          *reinterpret_cast<float2 *>(a.pml + (size_t)cur.prow[cb] * 2) = make_float2(st.m[cb], st.l[cb][0]);
+      {
+        const f32x16 s = bc_scores<D>(cur.qop, klast, ln, bc_tail(tail));
+        // the query rows are done with: those of the next step take their registers
+        if (it + NW < n_it) bc_load_rows<D>(Qb, ent, it + NW, cnt, lg_tpw, slot, lane_off, hl, spare, cur);
+        if (last == 0 && fresh) bc_fwd_tile<D, true>(st, s, vlast, ln, sl2, ones);
+        else bc_fwd_tile<D>(st, s, vlast, ln, sl2, ones);
       }
-      cur = nxt;
+      if (__builtin_expect(__any(!bc_in_range(st.l[0])), 0)) {
+        BcRows<D> r;
+        bc_load_rows<D>(Qb, ent, it, cnt, lg_tpw, slot, lane_off, hl, spare, r);
+        if (fresh) {
+#pragma unroll
+          for (int db = 0; db < D / 32; ++db) st.o[db] = splat16(0.f);
+          st.l = f32x4{0.f, 0.f, 0.f, 0.f};
+          st.m = -INFINITY;
+        } else {
+          bc_pick_up<D>(a, prow, st);
+        }
+#pragma unroll 1
+        for (int t = 0; t <= last; ++t)
+          bc_fwd_tile_safe<D>(st, r.qop, kl + t * T::BYTES, vl + t * T::BYTES, ln, t < last ? splat16(0.f) : bc_tail(tail), sl2, ones);
+      }
+      t32_store_rows<D>(a.po, prow, st.o);
+      *reinterpret_cast<float2 *>(a.pml + (size_t)prow * 2) = make_float2(st.m, st.l[0]);  // (both lanes of a column: the same)
     }
   }
 }
@@ -323,11 +315,11 @@ __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
 
 // ---------------------------------------------------------------------------------------------------------
 // dQ of the selection branch where it does not go with dK and dV (slc_bwd_two_kernels), block-centric: the same exchange of
-// loops as the forward kernel m_slc_fwd_bc.  A workgroup
+// loops as the forward kernel m_slc_fwd_bc, with the same tiles of 32 keys x 32 columns.  A workgroup
 // holds one selection block's K and V rows in LDS and runs through a chunk of the tokens that selected it; every
-// wavefront takes 16/h_s tokens per step on its own (query and dO rows in registers, no barrier, no column that did
+// wavefront takes 32/h_s tokens per step on its own (query and dO rows in registers, no barrier, no column that did
 // not select the block).  One bf16 partial dQ per (token, KV head, selected block) goes to memory; m_dq_merge adds them
-// in rank order onto the fp32 compression + window part.
+// in rank order onto the fp32 compression + window part.  153k tokens, heads of 128: 14.3 -> 12.0 ms (16 columns before).
 // ---------------------------------------------------------------------------------------------------------
 struct BcDqArgs {
   MfmaView v;
@@ -336,123 +328,126 @@ struct BcDqArgs {
   const int32_t *sel_list, *chunk_start;
   const uint8_t *sel_rank;
   const ChunkRef *chunk_order;
-  bf16_t *pdq;                        // [N(pos)][Hkv][T][hs][D]
+  bf16_t *pdq;                        // [N(pos)][Hkv][T][hs][D] and a spare row
 };
 
 template <int D>
 struct BcDqRows {
-  bf16x8 qop[D / 32], dop[D / 32];
+  bf16x8 qop[D / 16], dop[D / 16];
   float lse2, nd;   // lse in log2 units; -delta (delta = gate * <dO, O>)
-  uint32_t prow;         // ((pos*Hkv + g)*T + rank)*hs + head
-  bool valid;
+  uint32_t prow;    // ((pos*Hkv + g)*T + rank)*hs + head, or the spare row
 };
 
 template <int D>
 __device__ inline void bc_dq_load_rows(const BcDqArgs &a, const int *tl, const int *sl, int step, int cnt, int g, BcDqRows<D> &r) {
-  const int n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
+  const int n = threadIdx.x & 31, h = threadIdx.x >> 5 & 1;
   const int hs = a.v.hs, hl = n % hs;
-  const int e = step * (16 / hs) + n / hs;
-  r.valid = e < cnt;
-  const int pos = r.valid ? tl[e] : 0, rank = r.valid ? sl[e] : 0;
-  const size_t th = (size_t)pos * a.v.Hq + g * hs + hl;
+  const int e = step * (32 / hs) + n / hs;
+  const int pos = tl[min(e, cnt - 1)], rank = sl[min(e, cnt - 1)];
+  const uint32_t th = (uint32_t)pos * a.v.Hq + g * hs + hl;
 #pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks) {
-    r.qop[ks] = r.valid ? ld8(a.Qs + th * D + 8 * quad + 32 * ks) : zero8();
-    r.dop[ks] = r.valid ? ld8(a.dOs + th * D + 8 * quad + 32 * ks) : zero8();
+  for (int ks = 0; ks < D / 16; ++ks) {
+    r.qop[ks] = ld8(a.Qs + (size_t)th * D + 8 * h + 16 * ks);
+    r.dop[ks] = ld8(a.dOs + (size_t)th * D + 8 * h + 16 * ks);
   }
-  r.lse2 = r.valid ? a.lse2s[th] : INFINITY;  // a missing column gets P = exp2(-inf) = 0
+  r.lse2 = a.lse2s[th];
   r.nd = -a.deltas[th];
-  r.prow = (uint32_t)((((size_t)pos * a.v.Hkv + g) * a.v.T + rank) * hs + hl);
+  r.prow = e < cnt ? (((uint32_t)pos * a.v.Hkv + g) * a.v.T + rank) * hs + hl : (uint32_t)((size_t)a.v.N * a.v.Hq * a.v.T);
 }
 
 // One 32-key LDS tile: transposed scores (K rows) and dP (V rows, against gate * dO; the accumulators start from
 // -delta of their column, so the matrix instruction leaves dP - delta), dS^T = P (dP - delta), then dQ^T += K^T dS^T
 // with K^T read from the same K tile through the transposing LDS load.  The softmax scale of dS is applied by the merge
 // kernel, once per output element.
-template <int D, bool MASK>
-__device__ inline void bc_dq_tile(f32x4 (&acc)[D / 16], const BcDqRows<D> &r, lds_cptr kt, lds_cptr vt,
-                                  const typename PTile<D, false>::Lanes &ln, int key0, int nk, float sl2) {
-  f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, p0 = {r.nd, r.nd, r.nd, r.nd}, p1 = p0;
+template <int D>
+__device__ inline void bc_dq_scores(const BcDqRows<D> &r, lds_cptr kt, lds_cptr vt, const typename T32<D, false>::Lanes &ln, f32x16 &s,
+                                    f32x16 &dp) {
+  using T = T32<D, false>;
+  dp = splat16(r.nd);
 #pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks) {
-    s0 = mfma16(p_row_operand<D, false>(kt, ln, 0, ks), r.qop[ks], s0);
-    s1 = mfma16(p_row_operand<D, false>(kt, ln, 1, ks), r.qop[ks], s1);
-    p0 = mfma16(p_row_operand<D, false>(vt, ln, 0, ks), r.dop[ks], p0);
-    p1 = mfma16(p_row_operand<D, false>(vt, ln, 1, ks), r.dop[ks], p1);
+  for (int ks = 0; ks < D / 16; ++ks) {
+    s = mfma32(T::row(kt, ln, ks), r.qop[ks], s);
+    dp = mfma32(T::row(vt, ln, ks), r.dop[ks], dp);
   }
-  bf16x8 ds;
-  const int first = key0 + 8 * (int)(threadIdx.x >> 4 & 3);
+}
+template <int D, bool FIRST = false>
+__device__ inline void bc_dq_tile(f32x16 (&acc)[D / 32], const f32x16 &s, const f32x16 &dp, lds_cptr kt,
+                                  const typename T32<D, false>::Lanes &ln, float lse2, float sl2) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float sv = j < 4 ? s0[j & 3] : s1[j & 3], dp = j < 4 ? p0[j & 3] : p1[j & 3];
-    float p = fast_exp2(__builtin_fmaf(sv, sl2, -r.lse2));
-    if (MASK && first + j >= nk) p = 0.f;
-    ds[j] = (__bf16)(p * dp);  // dp = gate * dP - delta: the dO rows are gate * dO
+  for (int kc = 0; kc < 2; ++kc) {
+    bf16x8 ds;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)  // dp = gate * dP - delta: the dO rows are gate * dO
+      ds[j] = (__bf16)(fast_exp2(__builtin_fmaf(s[8 * kc + j], sl2, -lse2)) * dp[8 * kc + j]);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) acc[db] = mfma32(T32<D, false>::tr(kt, ln, db, kc), ds, FIRST && kc == 0 ? splat16(0.f) : acc[db]);
   }
-#pragma unroll
-  for (int dt = 0; dt < D / 16; ++dt) acc[dt] = mfma16(p_tr_operand<D, false>(kt, ln, dt), ds, acc[dt]);
 }
 
-template <int D, int KSEG>
-constexpr size_t bc_dq_lds_bytes() { return (size_t)2 * (KSEG / 32) * PTile<D, false>::BYTES + (size_t)2 * BC_CHUNK * sizeof(int); }
-
-template <int D, int NW, int KSEG>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 4 : 2))) void m_bwd_dq_bc(BcDqArgs a) {
+template <int D, int NW, int KSEG, int WPE>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) void m_bwd_dq_bc(BcDqArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  using P = PTile<D, false>;
+  using T = T32<D, false>;
   constexpr int MAXT = KSEG / 32;
-  unsigned char *Kt = smem, *Vt = Kt + MAXT * P::BYTES;
-  int *tl = (int *)(Vt + MAXT * P::BYTES), *sl = tl + BC_CHUNK;
-  const int wid = threadIdx.x >> 6, quad = threadIdx.x >> 4 & 3;
+  unsigned char *Kt = smem, *Vt = Kt + MAXT * T::BYTES;
+  int *tl = (int *)(Vt + MAXT * T::BYTES), *sl = tl + BC_CHUNK;
+  float *tail = (float *)(sl + BC_CHUNK);
+  const int wid = uniform(threadIdx.x >> 6);
   const int hs = a.v.hs, Hkv = a.v.Hkv, Ns = a.v.Ns;
   const int wi = bc_chunk_of_workgroup(a.chunk_start[Hkv * Ns]);
   if (wi < 0) return;
   const ChunkRef cr = a.chunk_order[wi];
-  const int g = cr.key / Ns, blk = cr.key % Ns;
-  const int kbeg = a.v.slc_start[blk], kend = a.v.slc_start[blk + 1];
-  const int qbeg = cr.first, cnt = cr.count;
+  const int key = uniform(cr.key), g = key / Ns, blk = key % Ns;
+  const int kbeg = uniform(a.v.slc_start[blk]), kend = uniform(a.v.slc_start[blk + 1]);
+  const int qbeg = uniform(cr.first), cnt = uniform(cr.count);
   // the chunk's tokens (sorted positions) and the rank of this block in each token's row of I
   for (int i = threadIdx.x; i < cnt; i += 64 * NW) {
     tl[i] = a.sel_list[qbeg + i];
     sl[i] = a.sel_rank[qbeg + i];
   }
-  const int tpw = 16 / hs;
+  const int tpw = 32 / hs;
   const int n_it = (cnt + tpw - 1) / tpw;
   const uint32_t kstride = (uint32_t)(Hkv * D);
-  const float sl2 = a.v.sl2;
-  const typename P::Lanes ln = P::lanes();
+  const float sl2 = in_vgpr(a.v.sl2);
+  const typename T::Lanes ln = T::lanes();
   const lds_cptr kt = (lds_cptr)Kt, vt = (lds_cptr)Vt;
   __syncthreads();
   BcDqRows<D> cur;
   if (wid < n_it) bc_dq_load_rows<D>(a, tl, sl, wid, cnt, g, cur);
   for (int k0 = kbeg; k0 < kend; k0 += KSEG) {
-    const int nk = min(KSEG, kend - k0), nfull = nk >> 5;
+    const int nk = min(KSEG, kend - k0), last = (nk - 1) >> 5;
     if (k0 > kbeg) {
       __syncthreads();
       if (wid < n_it) bc_dq_load_rows<D>(a, tl, sl, wid, cnt, g, cur);
     }
-    p_stage2<D, false, 64 * NW>(a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D, kstride, k0, (nk + 31) >> 5, Kt, Vt);
+    t32_stage2<D, false, 64 * NW>(a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D, kstride, k0, nk, Kt, Vt);
+    bc_write_tail(tail, nk - 32 * last);
+    wait_loads();  // (so that the step loop is entered with no load outstanding and its waits count what an iteration leaves)
     __syncthreads();
+    const lds_cptr klast = kt + last * T::BYTES, vlast = vt + last * T::BYTES;
     for (int it = wid; it < n_it; it += NW) {
-      BcDqRows<D> nxt;
-      if (it + NW < n_it) bc_dq_load_rows<D>(a, tl, sl, it + NW, cnt, g, nxt);
-      f32x4 acc[D / 16];
+      const uint32_t prow = cur.prow;
+      const float lse2 = cur.lse2;
+      f32x16 acc[D / 32];
+      const bool fresh = k0 == kbeg;
+      if (!fresh) bc_pick_up_row<D>(a.pdq, prow, acc);  // continue from the partial of the earlier segments
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (k0 > kbeg && cur.valid) {  // continue from the partial of the earlier segments
-#pragma unroll
-        for (int dt = 0; dt < D / 16; ++dt) {
-          const bf16x4 x = *reinterpret_cast<const bf16x4 *>(a.pdq + (size_t)cur.prow * D + acc_dim(dt, quad));
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[dt][i] = (float)x[i];
+      for (int t = 0; t < MAXT - 1; ++t)
+        if (t < last) {
+          f32x16 s = splat16(0.f), dp;
+          bc_dq_scores<D>(cur, kt + t * T::BYTES, vt + t * T::BYTES, ln, s, dp);
+          if (t == 0 && fresh) bc_dq_tile<D, true>(acc, s, dp, kt, ln, lse2, sl2);
+          else bc_dq_tile<D>(acc, s, dp, kt + t * T::BYTES, ln, lse2, sl2);
         }
+      {
+        f32x16 s = bc_tail(tail), dp;
+        bc_dq_scores<D>(cur, klast, vlast, ln, s, dp);
+        // the rows are done with: those of the next step take their registers
+        if (it + NW < n_it) bc_dq_load_rows<D>(a, tl, sl, it + NW, cnt, g, cur);
+        if (last == 0 && fresh) bc_dq_tile<D, true>(acc, s, dp, klast, ln, lse2, sl2);
+        else bc_dq_tile<D>(acc, s, dp, klast, ln, lse2, sl2);
       }
-#pragma unroll
-      for (int t = 0; t < MAXT; ++t)
-        if (t < nfull) bc_dq_tile<D, false>(acc, cur, kt + t * P::BYTES, vt + t * P::BYTES, ln, 32 * t, nk, sl2);
-      if (nk & 31) bc_dq_tile<D, true>(acc, cur, kt + nfull * P::BYTES, vt + nfull * P::BYTES, ln, 32 * nfull, nk, sl2);
-      store_partial_row<D>(a.pdq, cur.prow, acc, cur.valid);
-      cur = nxt;
+      t32_store_rows<D>(a.pdq, prow, acc);
     }
   }
 }
@@ -497,10 +492,10 @@ __global__ __launch_bounds__(256) void m_dq_merge(DqMergeArgs a) {
 
 // dQ: wavefronts per workgroup, keys held in LDS at a time.
 constexpr int DQ_WAVES = 8, DQ_KSEG = 256;
-// Forward: 16-column blocks per wavefront, wavefronts per workgroup and per SIMD (see m_slc_fwd_bc for the figures).
-template <int D> struct BcFwdShape { static constexpr int CB = 2, NW = 8, KSEG = 256, WPE = 4; };
-template <> struct BcFwdShape<64> { static constexpr int CB = 1, NW = 8, KSEG = 256, WPE = 4; };
-template <> struct BcFwdShape<128> { static constexpr int CB = 2, NW = 8, KSEG = 256, WPE = 2; };
+template <int D> constexpr int dq_wpe() { return D == 32 ? 4 : 2; }
+// Forward: wavefronts per workgroup and per SIMD, keys in LDS at a time (see m_slc_fwd_bc for the figures).
+template <int D> struct BcFwdShape { static constexpr int NW = 8, KSEG = 256, WPE = 4; };
+template <> struct BcFwdShape<128> { static constexpr int NW = 8, KSEG = 256, WPE = 2; };
 
 // upper bound of the number of chunks: every (KV head, block) list adds at most one partly filled chunk
 unsigned chunk_bound(const MfmaView &v, int chunk_len) {
@@ -512,7 +507,7 @@ template <int D>
 int launch_slc_forward(const MfmaView &v, const bf16_t *q, const SelIndex &sel, const SlcPartials &part,
                        hipStream_t s) {
   using BS = BcFwdShape<D>;
-  auto kernel = m_slc_fwd_bc<D, BS::CB, BS::NW, BS::KSEG, BS::WPE>;
+  auto kernel = m_slc_fwd_bc<D, BS::NW, BS::KSEG, BS::WPE>;
   static std::once_flag once;  // raise the dynamic LDS limit once per process for this instantiation
   std::call_once(once, [&] {
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -526,12 +521,12 @@ template <int D>
 int launch_slc_dq(const MfmaView &v, const BwdBuffers &w, hipStream_t s) {
   static std::once_flag once;
   std::call_once(once, [] {
-    (void)hipFuncSetAttribute((const void *)m_bwd_dq_bc<D, DQ_WAVES, DQ_KSEG>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void *)m_bwd_dq_bc<D, DQ_WAVES, DQ_KSEG, dq_wpe<D>()>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               160 * 1024);
   });
   const size_t NH = (size_t)v.N * v.Hq;
   BcDqArgs b{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.list, w.sel.bc_chunk_start, w.sel.rank, w.sel.bc_order, w.part.o};
-  m_bwd_dq_bc<D, DQ_WAVES, DQ_KSEG><<<dim3((chunk_bound(v, w.sel.bc_chunk_len) + 7) / 8 * 8), 64 * DQ_WAVES, bc_dq_lds_bytes<D, DQ_KSEG>(), s>>>(b);
+  m_bwd_dq_bc<D, DQ_WAVES, DQ_KSEG, dq_wpe<D>()><<<dim3((chunk_bound(v, w.sel.bc_chunk_len) + 7) / 8 * 8), 64 * DQ_WAVES, bc_lds_bytes<D, DQ_KSEG>(), s>>>(b);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 

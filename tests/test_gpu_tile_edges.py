@@ -1,0 +1,25 @@
+"""GPU: the 32 x 32 tiles of the attention kernels at their edges, on sequences, where the lengths of the blocks can be set: key
+ranges of one key to one key past a segment of 256, a last tile of 1, 31 or 32 keys, 2 to 32 tokens in a wavefront's 32 columns with
+a remainder, token counts that leave the last workgroup or chunk a single token, every head grouping and head dimension.
+Tolerances of the other parity tests."""
+import pytest
+
+from paper_2505_17412_amd import inputs
+from tests.test_gpu_parity import full_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("seed,lens,hq,hkv,d,l,topk", [
+    (901, (130,), 2, 2, 64, (1, 2, 3), 5),               # blocks of two keys; 32 tokens in 32 columns, 2 in the last step
+    (902, (33, 1, 64), 4, 2, 32, (4, 32, 31), 2),        # one full tile; items of one token; windows of 31
+    (903, (34, 99), 4, 1, 64, (3, 33, 33), 3),           # one key in the second tile
+    (904, (200, 63), 8, 1, 128, (7, 63, 64), 2),         # 31 keys in the second tile; 4 tokens per step
+    (905, (257,), 16, 1, 64, (8, 64, 65), 4),            # two tokens per step, a step of one; a last block of one key
+    (906, (513, 255), 16, 2, 128, (17, 255, 257), 2),    # 31 keys in the eighth tile
+    (907, (530,), 2, 1, 128, (16, 256, 256), 3),         # a whole segment, then blocks of 256 and 18
+    (908, (771,), 8, 2, 64, (1, 257, 300), 3),           # one key in a second segment
+    (909, (300, 129), 1, 1, 32, (2, 130, 96), 2),        # one head
+])
+def test_tile_edges(seed, lens, hq, hkv, d, l, topk):
+    full_parity(inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk))
