@@ -16,7 +16,6 @@
 #include "mfma_common.h"
 #include "mfma_launch.h"
 #include "mfma_qc.h"
-#include "mfma_bc.h"
 #include "profile.h"
 
 #include <mutex>
@@ -114,142 +113,86 @@ struct DqArgs {
   float *dQp;  // [N(pos)][Hq][D] fp32: compression + window part of dQ
 };
 
-// One staged 32-key tile: transposed scores (K rows) and dP (V rows), then dQ^T += K^T dS^T (the K rows again, read
-// through the transposing LDS load).  kt, vt: the staged K and V tiles, ln: the lane offsets of their operands (PTile).
-// lse2 is +inf for a column whose token did not select the current block, which makes its P exactly zero.
-template <int D, int CB, bool MASK>
-__device__ inline void dq_tile(f32x4 (&acc)[CB][D / 16], const QRows<D, CB> &q, const bf16x8 (&dop)[CB][D / 32],
-                               lds_cptr kt, lds_cptr vt, const typename PTile<D>::Lanes &ln, int kb, const int (&lo)[CB],
-                               const int (&hi)[CB], const bool (&act)[CB], float sl2, float scale, const float (&lse2)[CB],
-                               const float (&delta)[CB], const float (&gw)[CB]) {
-  const int quad = threadIdx.x >> 4 & 3;
-  float gws[CB], dls[CB];  // gate and delta with the softmax scale folded in: dS = P (gate dP - delta) scale
+// dS of a 32-key tile with raw scores s and dP, and dQ^T += K^T dS^T (the K rows again, read through the transposing LDS load).
+// lse2 per column; gws, dls: gate and delta with the softmax scale folded in, dS = P (gate dP - delta) scale.
+template <int D>
+__device__ inline void dq_tile(f32x16 (&acc)[D / 32], const f32x16 &s, const f32x16 &dp, lds_cptr kt, const typename T32<D, true>::Lanes &ln,
+                               float sl2, float lse2, float gws, float dls) {
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) { gws[cb] = gw[cb] * scale; dls[cb] = delta[cb] * scale; }
-  f32x4 s0[CB], s1[CB], p0[CB], p1[CB];
+  for (int kc = 0; kc < 2; ++kc) {
+    bf16x8 ds;
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) s0[cb] = s1[cb] = p0[cb] = p1[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 8; ++j)
+      ds[j] = (__bf16)(fast_exp2(__builtin_fmaf(s[8 * kc + j], sl2, -lse2)) * __builtin_fmaf(gws, dp[8 * kc + j], -dls));
 #pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks) {
-    const bf16x8 k0 = p_row_operand<D>(kt, ln, 0, ks), k1 = p_row_operand<D>(kt, ln, 1, ks);
-    const bf16x8 v0 = p_row_operand<D>(vt, ln, 0, ks), v1 = p_row_operand<D>(vt, ln, 1, ks);
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-      if (act[cb]) {
-        s0[cb] = mfma16(k0, q.qop[cb][ks], s0[cb]);
-        s1[cb] = mfma16(k1, q.qop[cb][ks], s1[cb]);
-        p0[cb] = mfma16(v0, dop[cb][ks], p0[cb]);
-        p1[cb] = mfma16(v1, dop[cb][ks], p1[cb]);
-      }
-  }
-  bf16x8 dsb[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    if (!act[cb]) continue;
-    const int rel = kb + 8 * quad - lo[cb];
-    const unsigned len = (unsigned)(hi[cb] - lo[cb]);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float sv = j < 4 ? s0[cb][j & 3] : s1[cb][j & 3];
-      const float dp = j < 4 ? p0[cb][j & 3] : p1[cb][j & 3];
-      float p = fast_exp2(__builtin_fmaf(sv, sl2, -lse2[cb]));
-      if (MASK && (unsigned)(rel + j) >= len) p = 0.f;  // lo <= key < hi as one unsigned comparison
-      dsb[cb][j] = (__bf16)(p * __builtin_fmaf(gws[cb], dp, -dls[cb]));
-    }
-  }
-#pragma unroll
-  for (int dt = 0; dt < D / 16; ++dt) {
-    const bf16x8 ktd = p_tr_operand<D>(kt, ln, dt);
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-      if (act[cb]) acc[cb][dt] = mfma16(ktd, dsb[cb], acc[cb][dt]);
+    for (int db = 0; db < D / 32; ++db) acc[db] = mfma32(T32<D, true>::tr(kt, ln, db, kc), ds, acc[db]);
   }
 }
 
-// LDS plan of the dQ kernel (bytes): two stages (K rows, V rows) | 8 ints
+// LDS plan of the dQ kernel (bytes): two stages (K rows, V rows) | what the last tile's scores start from
 template <int D>
-__host__ __device__ inline size_t dq_lds_bytes() { return (size_t)2 * StageLayout<D, 2>::ELEMS * sizeof(bf16_t) + 32; }
+__host__ __device__ inline size_t dq_lds_bytes() { return (size_t)4 * T32<D, true>::BYTES + 128; }
 
 // dQ of the compression branch, then of the (small) window branch, in the sorted token order; the sum is kept in fp32 by
-// sorted position (dQp) for the merge with the selection branch's partials.
-template <int D, int CB, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 && CB == 1 ? 4 : 2))) void m_bwd_dq(DqArgs a) {
+// sorted position (dQp) for the merge with the selection branch's partials.  Bound as the forward walk (per 32 x 32 scores 384
+// matrix cycles and about 280 of vector work at head_dim 64).  Three wavefronts per SIMD at head_dim 64 (163 registers).
+// 62k tokens, 16 heads of 64: 1140 -> 990 us (two blocks of 16 columns per wavefront at two per SIMD before), 21k tokens in three
+// 64^3 shells 155 -> 114, sequences 790 -> 665, 153k tokens, heads of 128: 9.0 -> 7.1 ms.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_bwd_dq(DqArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  using L = StageLayout<D, 2>;
-  bf16_t *stage0 = (bf16_t *)smem;
-  int *ints = (int *)(stage0 + 2 * L::ELEMS);
-  const int quad = threadIdx.x >> 4 & 3;
-  const int hs = a.v.hs, N = a.v.N, TW = NW * CB * 16 / hs;
+  using T = T32<D, true>;
+  unsigned char *stage0 = smem;
+  float *tail = (float *)(smem + 4 * T::BYTES);
+  const int h = threadIdx.x >> 5 & 1;
+  const int N = a.v.N, TW = 32 * NW / a.v.hs;
   const TileMap tm = xcd_tile_map((N + TW - 1) / TW, a.v.Hkv);
   if (!tm.valid) return;
-  const int g = tm.g, wg_pos0 = tm.tile * TW;
-  QRows<D, CB> q;
-  load_rows<D, CB>(a.Q, a.v, wg_pos0, g, q);
-  bf16x8 dop[CB][D / 32];
-  size_t rs_[CB];  // row of the per-row arrays, which are laid out by sorted position
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    const bf16_t *src = a.dO + ((size_t)q.tok[cb] * a.v.Hq + q.h[cb]) * D + 8 * quad;
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) dop[cb][ks] = q.valid[cb] ? ld8(src + 32 * ks) : zero8();
-    rs_[cb] = (size_t)(q.valid[cb] ? q.pos[cb] : 0) * a.v.Hq + q.h[cb];
-  }
+  const int g = tm.g, wg_pos0 = tm.tile * TW, wg_last = min(wg_pos0 + TW, N) - 1;
+  const QCol q = query_col(a.v, wg_pos0, g);
+  bf16x8 qop[D / 16], dop[D / 16];
+  load_col<D>(a.Q, a.v, q, qop);
+  load_col<D>(a.dO, a.v, q, dop);
+  const size_t row = (size_t)q.pos * a.v.Hq + q.h;  // of the per-row arrays, which are laid out by sorted position
   const size_t NH = (size_t)N * a.v.Hq;
-  f32x4 acc[CB][D / 16];
+  f32x16 acc[D / 32];
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) acc[cb][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float sl2 = a.v.sl2, scale = a.v.scale;
-  const size_t kstride = (size_t)a.v.Hkv * D;
-  const typename PTile<D>::Lanes ln = PTile<D>::lanes();
-  int lo[CB], hi[CB];
-  bool act[CB];
-  float lse2[CB], delta[CB], gw[CB];
-  // one key range per branch, per-lane [lo, hi)
+  for (int db = 0; db < D / 32; ++db) acc[db] = splat16(0.f);
+  const float sl2 = in_vgpr(a.v.sl2), scale = a.v.scale;
+  const uint32_t kstride = (uint32_t)(a.v.Hkv * D);
+  const typename T::Lanes ln = T::lanes();
+  // one key range per branch: the items (windows) of the workgroup's tokens are neighbours, and so are their keys
+#pragma unroll 1
   for (int branch = 0; branch <= 2; branch += 2) {
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-      if (branch == 0) {
-        const int item = q.valid[cb] ? a.v.tok_item[q.pos[cb]] : 0;
-        lo[cb] = q.valid[cb] ? a.v.cmp_batch[item] : 0;
-        hi[cb] = q.valid[cb] ? a.v.cmp_batch[item + 1] : 0;
-      } else {
-        const int w = q.valid[cb] ? a.v.tok_win[q.pos[cb]] : 0;
-        lo[cb] = q.valid[cb] ? a.v.win_start[w] : 0;
-        hi[cb] = q.valid[cb] ? a.v.win_start[w + 1] : 0;
-      }
-      act[cb] = true;
-      lse2[cb] = a.lse2s[branch * NH + rs_[cb]];
-      delta[cb] = a.deltas[branch * NH + rs_[cb]];
-      gw[cb] = a.gws[branch * NH + rs_[cb]];
-    }
-    int rs, re;
-    bool uniform;
-    wg_range<CB>(ints, lo, hi, q.valid, rs, re, uniform);
-    if (threadIdx.x == 0) { ints[4] = rs; ints[5] = re; }
+    const int32_t *of_tok = branch == 0 ? a.v.tok_item : a.v.tok_win, *start = branch == 0 ? a.v.cmp_batch : a.v.win_start;
+    const bf16_t *K = (branch == 0 ? a.v.Kc : a.v.Ks) + (size_t)g * D, *V = (branch == 0 ? a.v.Vc : a.v.Vs) + (size_t)g * D;
+    const int r0 = uniform(of_tok[wg_pos0]), r1 = uniform(of_tok[wg_last]), own = of_tok[q.pos];
+    const int rs = uniform(start[r0]), re = uniform(start[r1 + 1]), lo = start[own], hi = start[own + 1];
+    const float lse2 = a.lse2s[branch * NH + row], gws = a.gws[branch * NH + row] * scale, dls = a.deltas[branch * NH + row] * scale;
+    t32_write_tail(tail, (re - rs - 1) % 32 + 1);
     __syncthreads();
-    TileSrc<2> src = branch == 0
-        ? TileSrc<2>{{a.v.Kc + (size_t)g * D, a.v.Vc + (size_t)g * D}, (uint32_t)kstride}
-        : TileSrc<2>{{a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D}, (uint32_t)kstride};
-    run_pipeline<D, 2, 64 * NW, 2>(
-        src, stage0, ints + 4, ints + 5, re > rs ? 1 : 0, [](int) {},
-        [&](const bf16_t *stg, int kb, int) {
-          bf16_t *st = (bf16_t *)stg;
-          if (uniform && kb >= rs && kb + 32 <= re)
-            dq_tile<D, CB, false>(acc, q, dop, (lds_cptr)L::row_tile(st, 0), (lds_cptr)L::row_tile(st, 1), ln, kb, lo, hi, act, sl2,
-                                  scale, lse2, delta, gw);
-          else
-            dq_tile<D, CB, true>(acc, q, dop, (lds_cptr)L::row_tile(st, 0), (lds_cptr)L::row_tile(st, 1), ln, kb, lo, hi, act, sl2,
-                                 scale, lse2, delta, gw);
-        });
-  }
+    t32_pipeline<D, 2, 64 * NW, 32, T32_PF>(T32Src<2>{{K, V}, kstride}, stage0, rs, re, [&](lds_cptr kt, int kb) {
+      f32x16 s, dp = splat16(0.f);
+      if (kb + 32 <= re) s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
+      else s = t32_scores<D, true>(qop, kt, ln, t32_tail(tail));
+      if (r0 != r1) {
+        const int rel = kb - lo;
+        const unsigned len = (unsigned)(hi - lo);
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    if (!q.valid[cb]) continue;
-#pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) *reinterpret_cast<f32x4 *>(a.dQp + rs_[cb] * D + acc_dim(dt, quad)) = acc[cb][dt];
+        for (int i = 0; i < 16; ++i)
+          if ((unsigned)(rel + t32_key(i)) >= len) s[i] = -INFINITY;  // lo <= key < hi as one comparison
+      }
+      dp = t32_scores<D, true>(dop, kt + T::BYTES, ln, dp);
+      dq_tile<D>(acc, s, dp, kt, ln, sl2, lse2, gws, dls);
+    });
   }
+  if (!q.valid) return;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; i += 4)
+      *reinterpret_cast<f32x4 *>(a.dQp + row * D + 32 * db + 16 * (i >> 3) + 8 * h + (i & 4)) =
+          f32x4{acc[db][i], acc[db][i + 1], acc[db][i + 2], acc[db][i + 3]};
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -569,10 +512,6 @@ __global__ void m_bwd_finish(const int32_t *__restrict__ perm, const int32_t *__
   }
 }
 
-// 16-column blocks per wavefront of the compression + window dQ kernel: with two, every K and V operand read from LDS
-// feeds two matrix instructions (202 registers, two waves per SIMD; 1.15 -> 1.09 ms at the benchmark shape); head_dim
-// 128 keeps one (its accumulators alone would double).
-template <int D> constexpr int dq_cb() { return D <= 64 ? 2 : 1; }
 constexpr int KB_KEYS_MAX = 2;  // key blocks of 16 per wavefront in the dK/dV kernels (1 at head_dim 128: registers)
 // wavefronts per workgroup there (16*KB_KEYS keys each): blocks and windows hold ~130 tokens, an item's pooled keys
 // thousands, so the compression branch takes wider workgroups (fewer passes over the query rows)
@@ -594,16 +533,12 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
               N, Hq, Hkv, v.hs, D, (bf16_t *)dgates, w.lse2s, w.deltas, w.gws, w.deltag, w.Qs, w.dOg};
     m_bwd_pre<<<N, 256, (size_t)Hq * D * sizeof(bf16_t), s>>>(a);
   }
-  static std::once_flag dq_once;  // raise the dynamic LDS limit once per process for this instantiation
-  std::call_once(dq_once, [] {
-    (void)hipFuncSetAttribute((const void *)m_bwd_dq<D, dq_cb<D>(), 4>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  });
   {
     ProfScope ps0(PROF_BWD_DQ_CMP, s);
     DqArgs a{v, (const bf16_t *)q, (const bf16_t *)dout, w.lse2s, w.deltas, w.gws, w.dQp};
-    constexpr int CB = dq_cb<D>(), NW0 = 4;
-    const int tw0 = NW0 * CB * 16 / v.hs;
-    m_bwd_dq<D, CB, NW0><<<dim3(xcd_grid_size((N + tw0 - 1) / tw0, Hkv)), 64 * NW0, dq_lds_bytes<D>(), s>>>(a);
+    constexpr int NW0 = 4;
+    const int tw0 = 32 * NW0 / v.hs;
+    m_bwd_dq<D, NW0><<<dim3(xcd_grid_size((N + tw0 - 1) / tw0, Hkv)), 64 * NW0, dq_lds_bytes<D>(), s>>>(a);
   }
   {
     ProfScope ps(PROF_BWD_INVERT, s);

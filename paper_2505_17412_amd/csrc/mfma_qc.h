@@ -1,28 +1,21 @@
-// LDS tile layout of all attention kernels, and the query-centric tile pipeline of the compression and window
-// kernels, forward and dQ (gfx950, wave64).
-//
-// Pipeline: a workgroup of 4 wavefronts owns 4*CB*16 query rows (consecutive sorted tokens x the heads of one KV
-// group); each wavefront keeps CB blocks of 16 query columns in registers.  The workgroup walks a contiguous key range
-// (the item's pooled keys, the token's window).  Every 32-key tile is loaded once per workgroup, global -> registers ->
-// LDS, double buffered so the loads of the next tiles fly while a tile is consumed; all four wavefronts then take their
-// MFMA A operands from LDS.  (The selection branch has kernels of its own: see mfma_bc.h.)
+// LDS tile layouts of the 16 x 16 x 32 matrix kernels (dK/dV, the one-pass selection backward, the projections, the gate predictor
+// and the compression module), the workgroup map of the query-centric attention kernels and the top-k search (gfx950, wave64).
 #pragma once
 
 #include "mfma_common.h"
+#include "mfma_t32.h"
 #include "topk_device.h"
 
 // LDS geometry of one staged tile set.
 // Row-major tiles (32 rows of D bf16, no padding) are stored as [16-byte segment][row slot][8 elements]: the slot of
-// row k is sigma(k) = 16*((k>>2)&1) + 4*(k>>3) + (k&3), i.e. the 16 rows lane n = 0..15 of sub-tile a reads (see
-// tile_key_row) occupy the consecutive slots 16a .. 16a+15, so one operand read of a 16-lane quad covers 256
+// row k is sigma(k) = 16*((k>>2)&1) + 4*(k>>3) + (k&3), i.e. the 16 rows lane n = 0..15 of sub-tile a reads (the
+// key-tile convention of mfma_common.h) occupy the consecutive slots 16a .. 16a+15, so one operand read of a 16-lane quad covers 256
 // contiguous bytes.  The slot is XORed with (segment & 7): reads stay a permutation of the same 16 slots, and the
 // 8 threads that stage one row (8 segments, 512 bytes apart) land in 8 different 16-byte bank groups.
 template <int D>
 struct TileGeom {
   static constexpr int ROW_ELEMS = 32 * D;
   static constexpr int ROW_ITEMS = 32 * D / 8;                  // 16-byte items of a row-major tile
-  // 16-byte items per thread when NTHR threads stage a tile
-  static constexpr int row_per_thread(int nthr) { return (ROW_ITEMS + nthr - 1) / nthr; }
   __device__ static inline int sigma(int row) { return 16 * ((row >> 2) & 1) + 4 * (row >> 3) + (row & 3); }
   // element offset of (row slot, 16-byte segment) inside a row-major tile
   __device__ static inline int slot_off(int slot, int seg) { return ((seg << 5) + (slot ^ (seg & 7))) << 3; }
@@ -32,15 +25,13 @@ struct TileGeom {
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-// Tile layout of the attention kernels in LDS.  A 32-row tile of a row-major bf16 array is kept as D/8 planes of 512
-// bytes, one per 16-byte segment of a row; a plane holds the 32 rows' segments in the slot order sigma(row) (the order
+// Tile layout of the dK/dV kernels and the one-pass selection backward in LDS.  A 32-row tile of a row-major bf16 array is kept
+// as D/8 planes of 512 bytes, one per 16-byte segment of a row; a plane holds the 32 rows' segments in the slot order sigma(row) (the order
 // in which the lanes of the two 16-row matrix sub-tiles read them).  The slot is XORed with a per-plane constant,
 // swz(seg), chosen so that all three access patterns are free of LDS bank conflicts (measured with the LDS counters:
 // 0 conflict cycles per instruction for each):
 //   * staging writes: the 8 threads that stage one row write 8 planes, 512 bytes apart; the low three bits of swz
-//     (seg & 7, present with SWZ only) put them in 8 different 16-byte bank groups.  Kernels that stage a block once
-//     and read it many times leave them out (SWZ = false): their lane offsets then differ between contraction steps
-//     and between dim blocks by constants only, which saves the registers that hold them;
+//     (seg & 7) put them in 8 different 16-byte bank groups;
 //   * row operands (16-byte reads): the four quads of a wavefront read planes 4*ks .. 4*ks + 3, each 16 consecutive
 //     slots; the two quads served together (0,1 and 2,3) must not differ in bit 3 of swz, so that bit is the same for
 //     segments 4*ks, 4*ks + 1 and for 4*ks + 2, 4*ks + 3;
@@ -53,13 +44,13 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 // operands) or the output-dim block (transposed operands) only through the swizzle, so a kernel keeps D/32 + D/16
 // lane offsets in registers (Lanes) and the sub-tile, the row half, the tile index and the LDS stage all move the
 // address by constants, which the LDS instructions take as immediate offsets: a tile costs no address arithmetic.
-template <int D, bool SWZ = true>
+template <int D>
 struct PTile {
   static constexpr int SEGS = D / 8;
   static constexpr int PLANE_B = 512;            // bytes per plane: 32 row slots of 16 bytes
   static constexpr int BYTES = SEGS * PLANE_B;   // bytes per 32-row tile
   static constexpr int ITEMS = 32 * SEGS;        // 16-byte items per tile
-  __device__ static inline int swz(int seg) { return (SWZ ? seg & 7 : 0) ^ (((seg >> 1) & 1) << 3); }
+  __device__ static inline int swz(int seg) { return (seg & 7) ^ (((seg >> 1) & 1) << 3); }
   __device__ static inline int slot_off(int slot, int seg) { return seg * PLANE_B + ((slot ^ swz(seg)) << 4); }
   __device__ static inline int off(int row, int seg) { return slot_off(TileGeom<D>::sigma(row), seg); }
   // first of the two segments (s, s + 2) that dim block dt of a transposed operand is read from
@@ -79,11 +70,9 @@ struct PTile {
   }
 };
 
-typedef const __attribute__((address_space(3))) unsigned char *lds_cptr;
-
-// A operand of sub-tile a, contraction step ks (row = key, see tile_key_row) from the tile at `tile` (uniform address).
-template <int D, bool SWZ = true>
-__device__ inline bf16x8 p_row_operand(lds_cptr tile, const typename PTile<D, SWZ>::Lanes &l, int a, int ks) {
+// A operand of sub-tile a, contraction step ks (row = key, in the key-tile convention) from the tile at `tile` (uniform address).
+template <int D>
+__device__ inline bf16x8 p_row_operand(lds_cptr tile, const typename PTile<D>::Lanes &l, int a, int ks) {
   return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>(tile + l.row[ks] + a * 256);
 }
 
@@ -93,8 +82,8 @@ __device__ inline bf16x8 p_row_operand(lds_cptr tile, const typename PTile<D, SW
 // 8 + (i >> 2), 12 + (i >> 2).  With lane p pointing at row 8*quad + (p >> 2) and at the 4-dim piece (p & 3) of the
 // block (pieces 0, 1 in segment tr_seg(dt), pieces 2, 3 in the segment two further), lane i ends up with dim
 // tr_dim(dt, i) of rows 8*quad .. +3; a second read covers rows +4 .. +7.
-template <int D, bool SWZ = true>
-__device__ inline bf16x8 p_tr_operand(lds_cptr tile, const typename PTile<D, SWZ>::Lanes &l, int dt) {
+template <int D>
+__device__ inline bf16x8 p_tr_operand(lds_cptr tile, const typename PTile<D>::Lanes &l, int dt) {
   typedef __attribute__((address_space(3))) s16x4 *tr_ptr;
   const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(tile + l.tr[dt]));
   const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(tile + l.tr[dt] + 256));
@@ -103,59 +92,7 @@ __device__ inline bf16x8 p_tr_operand(lds_cptr tile, const typename PTile<D, SWZ
   return __builtin_bit_cast(bf16x8, both);
 }
 
-// Registers holding one tile set on its way from global memory to LDS.
-template <int D, int NROW, int NTHR = 256>
-struct TileRegs {
-  bf16x8 r[NROW][TileGeom<D>::row_per_thread(NTHR)];
-};
-
-// Global sources of a tile set: row-major arrays [rows][Hkv][D], already offset to the KV group.
-template <int NROW>
-struct TileSrc {
-  const bf16_t *row[NROW];
-  uint32_t kstride;  // elements between consecutive rows of a row-major array (Hkv*D); whole arrays stay below 2^31 elements
-};
-
-template <int D, int NROW, int NTHR>
-__device__ inline void tile_load(TileRegs<D, NROW, NTHR> &regs, const TileSrc<NROW> &src, int kb) {
-  using G = TileGeom<D>;
-#pragma unroll
-  for (int x = 0; x < NROW; ++x)
-#pragma unroll
-    for (int i = 0; i < G::row_per_thread(NTHR); ++i) {
-      const int it = threadIdx.x + NTHR * i;
-      if (G::ROW_ITEMS % NTHR == 0 || it < G::ROW_ITEMS) {
-        const int row = it / (D / 8), seg = it % (D / 8);
-        regs.r[x][i] = ld8(src.row[x] + ((uint32_t)(kb + row) * (uint32_t)src.kstride + (uint32_t)(seg * 8)));
-      }
-    }
-}
-
-// LDS buffer layout of one stage: NROW tiles in the padded layout.
-template <int D, int NROW>
-struct StageLayout {
-  static constexpr int TILE_ELEMS = PTile<D>::BYTES / 2;
-  static constexpr int ELEMS = NROW * TILE_ELEMS;
-  __device__ static inline bf16_t *row_tile(bf16_t *stage, int x) { return stage + x * TILE_ELEMS; }
-};
-
-template <int D, int NROW, int NTHR>
-__device__ inline void tile_store(const TileRegs<D, NROW, NTHR> &regs, bf16_t *stage) {
-  using G = TileGeom<D>;
-  using L = StageLayout<D, NROW>;
-#pragma unroll
-  for (int x = 0; x < NROW; ++x)
-#pragma unroll
-    for (int i = 0; i < G::row_per_thread(NTHR); ++i) {
-      const int it = threadIdx.x + NTHR * i;
-      if (G::ROW_ITEMS % NTHR == 0 || it < G::ROW_ITEMS) {
-        const int row = it / (D / 8), seg = it % (D / 8);
-        *reinterpret_cast<bf16x8 *>((unsigned char *)L::row_tile(stage, x) + PTile<D>::off(row, seg)) = regs.r[x][i];
-      }
-    }
-}
-
-// A operand of sub-tile a, contraction step ks, from a row-major LDS tile (row = key, see tile_key_row).
+// A operand of sub-tile a, contraction step ks, from a row-major LDS tile (row = key, in the key-tile convention).
 template <int D>
 __device__ inline bf16x8 lds_row_operand(const bf16_t *tile, int a, int ks) {
   const int n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
@@ -182,32 +119,7 @@ __device__ inline bf16x8 lds_tr_operand(const bf16_t *tile, int dt) {
   return __builtin_bit_cast(bf16x8, both);
 }
 
-// Cursor over the tiles of a list of key ranges held in LDS (rng_s/rng_e), uniform across the workgroup.  The end of
-// the current range is kept in the cursor: LDS is read only when the walk moves to another range.
-struct TileIter {
-  int r, kb, end;
-};
 __device__ inline int lds_uniform(const int *p) { return __builtin_amdgcn_readfirstlane(*p); }
-__device__ inline TileIter iter_begin(const int *rng_s, const int *rng_e, int nr) {
-  TileIter it{0, 0, 0};
-  if (nr > 0) {
-    it.kb = lds_uniform(rng_s) & ~7;
-    it.end = lds_uniform(rng_e);
-  }
-  return it;
-}
-__device__ inline TileIter iter_next(TileIter it, const int *rng_s, const int *rng_e, int nr, int step = 32) {
-  it.kb += step;
-  if (it.kb >= it.end) {
-    ++it.r;
-    if (it.r < nr) {
-      it.kb = lds_uniform(rng_s + it.r) & ~7;
-      it.end = lds_uniform(rng_e + it.r);
-    }
-  }
-  return it;
-}
-
 // Workgroup -> (token tile, KV group).  Workgroups of a 1-D launch are dealt round-robin to the 8 XCDs, each with
 // its own L2; this map keeps every XCD on ONE KV group and one contiguous run of token tiles, so the K/V rows it
 // touches (one group's pooled keys, the windows and selected blocks of neighbouring tokens) stay L2 resident.
@@ -228,95 +140,6 @@ __device__ inline TileMap xcd_tile_map(int n_tiles, int Hkv) {
   const int tpp = (n_tiles + parts - 1) / parts;
   const int tile = part * tpp + idx;
   return TileMap{tile, g, idx < tpp && tile < n_tiles};
-}
-
-// The query rows of one wavefront: CB blocks of 16 columns; column n of block cb is workgroup row
-// (wave*CB + cb)*16 + n = (token slot) * h_s + (head inside the group).
-template <int D, int CB>
-struct QRows {
-  bf16x8 qop[CB][D / 32];
-  int slot[CB], pos[CB], tok[CB], h[CB];
-  bool valid[CB];
-};
-
-template <int D, int CB>
-__device__ inline void load_rows(const bf16_t *Q, const MfmaView &v, int wg_pos0, int g, QRows<D, CB> &q) {
-  const int wid = threadIdx.x >> 6, n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3;
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    const int row = (wid * CB + cb) * 16 + n;
-    q.slot[cb] = row / v.hs;
-    q.pos[cb] = wg_pos0 + q.slot[cb];
-    q.valid[cb] = q.pos[cb] < v.N;
-    q.tok[cb] = q.valid[cb] ? v.perm[q.pos[cb]] : 0;
-    q.h[cb] = g * v.hs + row % v.hs;
-    const bf16_t *src = Q + ((size_t)q.tok[cb] * v.Hq + q.h[cb]) * D + 8 * quad;
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) q.qop[cb][ks] = q.valid[cb] ? ld8(src + 32 * ks) : zero8();
-  }
-}
-
-// Running softmax state of CB blocks of 16 query columns (Algorithm 1's o, l, m), shared by the pipeline kernels and
-// the block-centric selection kernel.
-template <int D, int CB>
-struct FwdState {
-  f32x4 o[CB][D / 16];  // o[cb][dt][i]: output dim acc_dim(dt, quad) + i of query column n
-  f32x4 l[CB];          // l[cb][0]: running sum of column n over all keys seen (the other three elements are unused)
-  float m[CB];          // running max (raw score units)
-};
-
-template <int D, int CB>
-__device__ inline void init_state(FwdState<D, CB> &st) {
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-#pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) st.o[cb][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    st.m[cb] = -INFINITY;
-    st.l[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-}
-
-// Walk the tiles of the key ranges rng_s/rng_e[0..nr) (LDS, workgroup-uniform).  Global loads run PF tiles (1 or 2)
-// ahead of the tile being consumed, through PF register sets used alternately; LDS holds two stages: the stage
-// written at step i is read at step i and overwritten at step i+2, with one barrier per step in between.
-// enter(r) runs when the walk reaches range r, tile(stage, kb, r) consumes one staged tile.
-// STEP: key rows consumed per step (32, or 64 when the tile set holds two consecutive 32-row tiles of one array).
-template <int D, int NROW, int NTHR = 256, int PF = 2, int STEP = 32, class Enter, class Tile>
-__device__ inline void run_pipeline(const TileSrc<NROW> &src, bf16_t *stage0, const int *rng_s, const int *rng_e, int nr,
-                                    Enter enter, Tile tile) {
-  using L = StageLayout<D, NROW>;
-  if (nr > 0) {
-    TileRegs<D, NROW, NTHR> regs[PF];
-    TileIter cur = iter_begin(rng_s, rng_e, nr);
-    TileIter ahead = cur;  // the last tile whose loads are in flight
-    tile_load<D, NROW, NTHR>(regs[0], src, cur.kb);
-    ahead = iter_next(cur, rng_s, rng_e, nr, STEP);
-    if (ahead.r < nr) tile_load<D, NROW, NTHR>(regs[1], src, ahead.kb);
-    int cur_r = -1;
-    // register set 0 always feeds LDS stage 0 and set 1 stage 1 (the steps alternate), so the stage address is a
-    // constant at each call site
-    auto step = [&](TileRegs<D, NROW, NTHR> &r, int buf) {
-      bf16_t *st = stage0 + buf * L::ELEMS;
-      tile_store<D, NROW, NTHR>(r, st);
-      // the request for the tile two steps ahead goes out while the LDS writes drain, before the barrier waits for them
-      if (ahead.r < nr) ahead = iter_next(ahead, rng_s, rng_e, nr, STEP);
-      if (ahead.r < nr) tile_load<D, NROW, NTHR>(r, src, ahead.kb);
-      __syncthreads();
-      if (cur.r != cur_r) {
-        cur_r = cur.r;
-        enter(cur_r);
-      }
-      tile(st, cur.kb, cur_r);
-      cur = iter_next(cur, rng_s, rng_e, nr, STEP);
-    };
-    static_assert(PF == 2, "two register sets, two LDS stages");
-    while (cur.r < nr) {
-      step(regs[0], 0);
-      if (!(cur.r < nr)) break;
-      step(regs[1], 1);
-    }
-  }
-  __syncthreads();
 }
 
 // Maximum over the wavefront, uniform (row permutations inside 16 lanes, then register swaps).
@@ -380,32 +203,6 @@ __device__ inline void topk_wave_bits(const uint32_t *S, int n, int T, int base,
     written += __popcll(sm);
   }
   for (int w = written + lane; w < T; w += 64) out[w] = -1;
-}
-
-// Workgroup-wide [min lo, max hi) of the per-lane key ranges, and whether every row has exactly that range.
-// scratch: 3 ints of LDS.  Returns through rs, re, uniform (all workgroup-uniform).
-template <int CB>
-__device__ inline void wg_range(int *scratch, const int (&lo)[CB], const int (&hi)[CB], const bool (&valid)[CB], int &rs,
-                                int &re, bool &uniform) {
-  if (threadIdx.x == 0) { scratch[0] = 0x7fffffff; scratch[1] = 0; scratch[2] = 1; }
-  __syncthreads();
-  int wlo = 0x7fffffff, whi = 0;
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-    if (valid[cb]) { wlo = min(wlo, lo[cb]); whi = max(whi, hi[cb]); }
-  wlo = wave_min_i(wlo);
-  whi = wave_max_i(whi);
-  if ((threadIdx.x & 63) == 0) { atomicMin(&scratch[0], wlo); atomicMax(&scratch[1], whi); }
-  __syncthreads();
-  rs = lds_uniform(&scratch[0]);
-  re = lds_uniform(&scratch[1]);
-  bool u = true;
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) u = u && valid[cb] && lo[cb] == rs && hi[cb] == re;
-  if (!__all(u) && (threadIdx.x & 63) == 0) scratch[2] = 0;
-  __syncthreads();
-  uniform = lds_uniform(&scratch[2]) != 0;
-  if (re <= rs) { rs = 0; re = 0; }
 }
 
 // ---- top-k over unsigned fixed-point scores held in LDS by one wavefront (ties -> lowest id) ----

@@ -5,12 +5,20 @@
 #include "mfma_common.h"
 #include "mfma_launch.h"
 #include "mfma_qc.h"
-#include "mfma_bc.h"
 #include "mfma_t32.h"
 
 #include <mutex>
 
 namespace {
+
+// Workgroup id -> work chunk.  Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2); the map
+// gives every XCD one contiguous run of the `total` chunks (one KV head, neighbouring blocks), so a block's rows are
+// fetched into one L2.  The grid is a multiple of 8 workgroups; ids past the end return -1.
+__device__ inline int bc_chunk_of_workgroup(int total) {
+  const int per = (total + 7) >> 3, xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
+  const int w = xcd * per + i;
+  return (i < per && w < total) ? w : -1;
+}
 
 // ---------------------------------------------------------------------------------------------------------
 // Selection branch, block-centric (Algorithm 1 with the loops exchanged): the outer loop runs over the selected blocks,
@@ -64,95 +72,6 @@ __device__ inline void bc_load_rows(const unsigned char *Q, const uint2 *ent, in
   r.prow = e < cnt ? x.y + hl : spare;
 }
 
-// What the score accumulators of a segment's last tile start from: 0, and -inf for the keys that do not exist (their rows in LDS
-// are zeros).
-__device__ inline f32x16 bc_tail(const float *tail) {
-  f32x16 s;
-  int first = t32_row(0);
-  asm volatile("" : "+v"(first));  // (or the 16 values stay in registers between the steps)
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const f32x4 x = *reinterpret_cast<const f32x4 *>(tail + first + 8 * i);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s[4 * i + j] = x[j];
-  }
-  return s;
-}
-__device__ inline void bc_write_tail(float *tail, int left) {
-  if (threadIdx.x < 32) tail[threadIdx.x] = (int)threadIdx.x < left ? 0.f : -INFINITY;
-}
-
-// Transposed scores of 32 query columns over one 32-key LDS tile: element i = key t32_row(i), column n.
-template <int D>
-__device__ inline f32x16 bc_scores(const bf16x8 (&qop)[D / 16], lds_cptr kt, const typename T32<D, false>::Lanes &ln, f32x16 s) {
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) s = mfma32(T32<D, false>::row(kt, ln, ks), qop[ks], s);
-  return s;
-}
-
-// Softmax state of 32 query columns: unnormalised output (transposed), sum (l[0]), reference exponent (log2 units).
-template <int D>
-struct BcState {
-  f32x16 o[D / 32];
-  f32x4 l;
-  float m;
-};
-
-// One step of the softmax (Algorithm 1, inner loop body) over one tile with scores s.  The reference exponent of a column is the
-// maximum of its first tile (bc_reference) and stays: later tiles cost a fused multiply-add, an exponential and half a conversion
-// per score, no maximum and no rescaling.  The result does not depend on the reference as long as nothing leaves the range of the
-// floats, which the caller checks on the finished sums (bc_in_range).
-__device__ inline float bc_reference(const f32x16 &s, float sl2) { return t32_column_max(max16(s)) * sl2; }
-template <int D, bool FIRST = false>
-__device__ inline void bc_fwd_tile(BcState<D> &st, const f32x16 &s, lds_cptr vt, const typename T32<D, false>::Lanes &ln, float sl2,
-                                   const bf16x8 &ones) {
-  if (FIRST) st.m = bc_reference(s, sl2);
-#pragma unroll
-  for (int kc = 0; kc < 2; ++kc) {
-    const bool fresh = FIRST && kc == 0;  // (no registers to clear: the products start from a constant)
-    bf16x8 p;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) p[j] = (__bf16)fast_exp2(__builtin_fmaf(s[8 * kc + j], sl2, -st.m));
-    // the normaliser on the matrix pipe, in the same bf16 rounding the numerator uses
-    st.l = mfma16(ones, p, fresh ? f32x4{0.f, 0.f, 0.f, 0.f} : st.l);
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) st.o[db] = mfma32(T32<D, false>::tr(vt, ln, db, kc), p, fresh ? splat16(0.f) : st.o[db]);
-  }
-}
-
-// The first tile's maximum contributes 1 to the sum, so nothing that counts is lost below; a sum under 2^60 leaves room for
-// values of the same size.
-__device__ inline bool bc_in_range(float l) { return l < 0x1p60f; }
-
-// The same step with a running maximum (raised lazily): what a column whose scores rise far above its first tile's goes
-// through instead.
-template <int D>
-__device__ inline void bc_fwd_tile_safe(BcState<D> &st, const bf16x8 (&qop)[D / 16], lds_cptr kt, lds_cptr vt,
-                                        const typename T32<D, false>::Lanes &ln, const f32x16 &s0, float sl2, const bf16x8 &ones) {
-  f32x16 s = bc_scores<D>(qop, kt, ln, s0);
-#pragma unroll
-  for (int i = 0; i < 16; ++i) s[i] *= sl2;
-  const float pm = max16(s);
-  if (__any(pm > st.m + 8.f)) {
-    const float mn = fmaxf(st.m, t32_column_max(pm));
-    const float alpha = mn == -INFINITY ? 1.0f : fast_exp2(st.m - mn);
-    st.l[0] *= alpha;
-    st.m = mn;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) st.o[db] *= alpha;
-  }
-  const float neg = st.m != -INFINITY ? -st.m : -INFINITY;
-#pragma unroll
-  for (int kc = 0; kc < 2; ++kc) {
-    bf16x8 p;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) p[j] = (__bf16)fast_exp2(s[8 * kc + j] + neg);
-    st.l = mfma16(ones, p, st.l);
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) st.o[db] = mfma32(T32<D, false>::tr(vt, ln, db, kc), p, st.o[db]);
-  }
-}
-
 // The 8 + 8 dims of block db that a lane holds of its column's row.
 template <int D>
 __device__ inline void bc_pick_up_row(const bf16_t *rows, uint32_t prow, f32x16 (&o)[D / 32]) {
@@ -169,10 +88,11 @@ __device__ inline void bc_pick_up_row(const bf16_t *rows, uint32_t prow, f32x16 
 
 // The partial of the earlier segments, picked up again.
 template <int D>
-__device__ inline void bc_pick_up(const BcFwdArgs &a, uint32_t prow, BcState<D> &st) {
+__device__ inline void bc_pick_up(const BcFwdArgs &a, uint32_t prow, T32State<D, SumParts> &st) {
   const float2 ml = *reinterpret_cast<const float2 *>(a.pml + (size_t)prow * 2);
   st.m = ml.x;
-  st.l = f32x4{ml.y, 0.f, 0.f, 0.f};
+  st.l.part[0] = threadIdx.x & 32 ? 0.f : ml.y;
+  st.l.part[1] = 0.f;
   bc_pick_up_row<D>(a.po, prow, st.o);
 }
 
@@ -202,7 +122,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   const int n_it = (cnt + (1 << lg_tpw) - 1) >> lg_tpw;
   const uint32_t kstride = (uint32_t)(Hkv * D);
   const float sl2 = in_vgpr(a.v.sl2);
-  const bf16x8 ones = column_ones();
   const typename T::Lanes ln = T::lanes();
   const lds_cptr kl = (lds_cptr)Kt, vl = (lds_cptr)Vt;
   const uint32_t spare = (uint32_t)((size_t)a.v.N * a.v.Hq * a.v.T);  // behind the last partial row
@@ -216,46 +135,42 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       if (wid < n_it) bc_load_rows<D>(Qb, ent, wid, cnt, lg_tpw, slot, lane_off, hl, spare, cur);
     }
     t32_stage2<D, false, 64 * NW>(a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D, kstride, k0, nk, Kt, Vt);
-    bc_write_tail(tail, nk - 32 * last);
+    t32_write_tail(tail, nk - 32 * last);
     wait_loads();  // (so that the step loop is entered with no load outstanding and its waits count what an iteration leaves)
     __syncthreads();
     const bool fresh = k0 == kbeg;
     const lds_cptr klast = kl + last * T::BYTES, vlast = vl + last * T::BYTES;
     for (int it = wid; it < n_it; it += NW) {
       const uint32_t prow = cur.prow;
-      BcState<D> st;
+      T32State<D, SumParts> st;
       if (!fresh) bc_pick_up<D>(a, prow, st);
 #pragma unroll
       for (int t = 0; t < MAXT - 1; ++t)
         if (t < last) {
-          const f32x16 s = bc_scores<D>(cur.qop, kl + t * T::BYTES, ln, splat16(0.f));
-          if (t == 0 && fresh) bc_fwd_tile<D, true>(st, s, vl, ln, sl2, ones);
-          else bc_fwd_tile<D>(st, s, vl + t * T::BYTES, ln, sl2, ones);
+          const f32x16 s = t32_scores<D, false>(cur.qop, kl + t * T::BYTES, ln, splat16(0.f));
+          if (t == 0 && fresh) t32_softmax<D, false, true>(st, s, vl, ln, sl2);
+          else t32_softmax<D, false, false>(st, s, vl + t * T::BYTES, ln, sl2);
         }
       {
-        const f32x16 s = bc_scores<D>(cur.qop, klast, ln, bc_tail(tail));
+        const f32x16 s = t32_scores<D, false>(cur.qop, klast, ln, t32_tail(tail));
         // the query rows are done with: those of the next step take their registers
         if (it + NW < n_it) bc_load_rows<D>(Qb, ent, it + NW, cnt, lg_tpw, slot, lane_off, hl, spare, cur);
-        if (last == 0 && fresh) bc_fwd_tile<D, true>(st, s, vlast, ln, sl2, ones);
-        else bc_fwd_tile<D>(st, s, vlast, ln, sl2, ones);
+        if (last == 0 && fresh) t32_softmax<D, false, true>(st, s, vlast, ln, sl2);
+        else t32_softmax<D, false, false>(st, s, vlast, ln, sl2);
       }
-      if (__builtin_expect(__any(!bc_in_range(st.l[0])), 0)) {
+      if (__builtin_expect(__any(!t32_in_range(st)), 0)) {
         BcRows<D> r;
         bc_load_rows<D>(Qb, ent, it, cnt, lg_tpw, slot, lane_off, hl, spare, r);
-        if (fresh) {
-#pragma unroll
-          for (int db = 0; db < D / 32; ++db) st.o[db] = splat16(0.f);
-          st.l = f32x4{0.f, 0.f, 0.f, 0.f};
-          st.m = -INFINITY;
-        } else {
-          bc_pick_up<D>(a, prow, st);
-        }
+        if (fresh) t32_clear(st);
+        else bc_pick_up<D>(a, prow, st);
 #pragma unroll 1
-        for (int t = 0; t <= last; ++t)
-          bc_fwd_tile_safe<D>(st, r.qop, kl + t * T::BYTES, vl + t * T::BYTES, ln, t < last ? splat16(0.f) : bc_tail(tail), sl2, ones);
+        for (int t = 0; t <= last; ++t) {
+          const f32x16 s = t32_scores<D, false>(r.qop, kl + t * T::BYTES, ln, t < last ? splat16(0.f) : t32_tail(tail));
+          t32_softmax_running<D, false>(st, s, vl + t * T::BYTES, ln, sl2);
+        }
       }
       t32_store_rows<D>(a.po, prow, st.o);
-      *reinterpret_cast<float2 *>(a.pml + (size_t)prow * 2) = make_float2(st.m, st.l[0]);  // (both lanes of a column: the same)
+      *reinterpret_cast<float2 *>(a.pml + (size_t)prow * 2) = make_float2(st.m, st.l.total());  // (both lanes of a column: the same)
     }
   }
 }
@@ -421,7 +336,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       if (wid < n_it) bc_dq_load_rows<D>(a, tl, sl, wid, cnt, g, cur);
     }
     t32_stage2<D, false, 64 * NW>(a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D, kstride, k0, nk, Kt, Vt);
-    bc_write_tail(tail, nk - 32 * last);
+    t32_write_tail(tail, nk - 32 * last);
     wait_loads();  // (so that the step loop is entered with no load outstanding and its waits count what an iteration leaves)
     __syncthreads();
     const lds_cptr klast = kt + last * T::BYTES, vlast = vt + last * T::BYTES;
@@ -440,7 +355,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
           else bc_dq_tile<D>(acc, s, dp, kt + t * T::BYTES, ln, lse2, sl2);
         }
       {
-        f32x16 s = bc_tail(tail), dp;
+        f32x16 s = t32_tail(tail), dp;
         bc_dq_scores<D>(cur, klast, vlast, ln, s, dp);
         // the rows are done with: those of the next step take their registers
         if (it + NW < n_it) bc_dq_load_rows<D>(a, tl, sl, it + NW, cnt, g, cur);

@@ -19,7 +19,6 @@
 #include "mfma_common.h"
 #include "mfma_launch.h"
 #include "mfma_qc.h"
-#include "mfma_bc.h"
 
 #include <mutex>
 

@@ -4,9 +4,9 @@
 // Operand convention of the instruction (h = lane >> 5, n = lane & 31):
 //   A (32 x 16): the lane supplies row n, contraction indices 8*h .. +7;  B (16 x 32): column n, the same indices
 //   C/D (32 x 32 fp32): the lane holds column n, rows 8*(i >> 2) + 4*h + (i & 3), i = 0 .. 15
-// A wavefront keeps 32 query columns and walks over tiles of 32 keys.  Scores are formed transposed (keys x queries), so that
-// registers 8*kc .. +7 of a lane are, for its query, the contraction slice kc (16 keys) of the next product; the keys of a slice
-// are in the order 16*kc + 8*(j >> 2) + 4*h + (j & 3), j = 0 .. 7, which the transposed operand below repeats.
+// A wavefront keeps 32 query columns and walks over tiles of 32 keys.  Scores are formed transposed (keys x queries) from key rows
+// in the order t32_order (bits 2 and 3 of row and key change places), so that registers 8*kc .. +7 of a lane are, for its query, the
+// consecutive keys 16*kc + 8*h .. +7: the contraction slice kc (16 keys) of the next product, as the B operand wants it.
 //
 // Why 32 columns and not 16: an operand taken from LDS (1 KB) feeds a matrix instruction of 32 cycles instead of 16.  With 16
 // columns the four SIMDs of a compute unit ask for as many LDS cycles as they spend matrix cycles, and the kernels wait for LDS
@@ -16,6 +16,7 @@
 #include "mfma_common.h"
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef const __attribute__((address_space(3))) unsigned char *lds_cptr;
 
 __device__ inline f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 __device__ inline f32x16 splat16(float x) {
@@ -24,7 +25,10 @@ __device__ inline f32x16 splat16(float x) {
   for (int i = 0; i < 16; ++i) z[i] = x;
   return z;
 }
-// Row of register i of an accumulator tile.
+// Key of row r of a tile, and row of key r; key of register i of a score tile.
+__device__ inline int t32_order(int r) { return (r & 0x13) | (r >> 1 & 4) | (r << 1 & 8); }
+__device__ inline int t32_key(int i) { return 16 * (i >> 3) + 8 * (threadIdx.x >> 5 & 1) + (i & 7); }
+// Row of register i of any other accumulator tile.
 __device__ inline int t32_row(int i) { return 8 * (i >> 2) + 4 * (threadIdx.x >> 5 & 1) + (i & 3); }
 
 // A tile of 32 rows x D bf16 in LDS: D/8 planes of 512 bytes, one per 16-byte segment of a row; row r lies in slot
@@ -39,8 +43,8 @@ struct T32 {
   __device__ static inline int swz(int seg) { return (seg & 3) << 2 | (SWZ ? (seg >> 2 & 1) << 1 | (seg >> 3 & 1) : 0); }
   __device__ static inline int off(int row, int seg) { return seg * 512 + ((row ^ swz(seg)) << 4); }
   struct Lanes {
-    int row[NROW];    // row operand, contraction step ks (ks & 1 without SWZ)
-    int tr[NTR][2];   // transposed operand: keys +0 .. 3 and +8 .. 11 of the slice, dim block db (the first without SWZ)
+    int row[NROW];    // row operand (rows in the order of t32_order), contraction step ks (ks & 1 without SWZ)
+    int tr[NTR][2];   // transposed operand: keys +0 .. 3 and +4 .. 7 of the lane's eight, dim block db (the first without SWZ)
   };
   // The 32 rows of a transposed operand are the dims of block db in the order that leaves a lane with 8 consecutive dims in
   // registers 0 .. 7 (32*db + 8*h ..) and in 8 .. 15 (32*db + 16 + 8*h ..): bits 2 and 3 of row and dim change places.
@@ -48,22 +52,21 @@ struct T32 {
     const int l = threadIdx.x & 63, h = l >> 5, p = l & 3, r = (l & 15) >> 2;
     Lanes x;
 #pragma unroll
-    for (int ks = 0; ks < NROW; ++ks) x.row[ks] = off(l & 31, 2 * ks + h);
+    for (int ks = 0; ks < NROW; ++ks) x.row[ks] = off(t32_order(l & 31), 2 * ks + h);
 #pragma unroll
     for (int db = 0; db < NTR; ++db)
 #pragma unroll
-      for (int k = 0; k < 2; ++k) x.tr[db][k] = off(4 * h + 8 * k + r, 4 * db + 2 * (l >> 4 & 1) + (p & 1)) + 8 * (p >> 1);
+      for (int k = 0; k < 2; ++k) x.tr[db][k] = off(8 * h + 4 * k + r, 4 * db + 2 * (l >> 4 & 1) + (p & 1)) + 8 * (p >> 1);
     return x;
   }
-  typedef const __attribute__((address_space(3))) unsigned char *ptr;
-  // A operand: rows of the tile, dims 16*ks + 8*h .. +7
-  __device__ static inline bf16x8 row(ptr tile, const Lanes &x, int ks) {
+  // A or B operand: rows of the tile in the order of t32_order, dims 16*ks + 8*h .. +7
+  __device__ static inline bf16x8 row(lds_cptr tile, const Lanes &x, int ks) {
     const int o = SWZ ? x.row[ks % NROW] : x.row[ks & 1] + (ks >> 1) * 2048;
     return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>(tile + o);
   }
   // A operand: dims of block db, contraction over the keys of slice kc (ds_read_b64_tr_b16: of a group of 16 lanes lane 4*r + p
   // hands in the address of 4 dims of row r, and lane i receives dim i of the four rows)
-  __device__ static inline bf16x8 tr(ptr tile, const Lanes &x, int db, int kc) {
+  __device__ static inline bf16x8 tr(lds_cptr tile, const Lanes &x, int db, int kc) {
     typedef __attribute__((ext_vector_type(4))) short s16x4;
     typedef __attribute__((ext_vector_type(8))) short s16x8;
     typedef __attribute__((address_space(3))) s16x4 *tr_ptr;
@@ -75,17 +78,6 @@ struct T32 {
   }
 };
 
-// Sums over the contraction slice of a B operand of the 32 x 32 x 16 instruction, for all 32 columns, by ONE 16 x 16 x 32
-// instruction: that one takes the lanes of columns n and n + 16 for the same column, and this A operand (ones where row and
-// contraction group agree) keeps them apart, so that element 0 of the result is the sum of the lane's own column.
-__device__ inline bf16x8 column_ones() {
-  const int l = threadIdx.x & 63;
-  const float w1 = __builtin_bit_cast(float, (l >> 2 & 1) == (l >> 4 & 1) ? 0x3F803F80u : 0u);
-  f32x4 w = {w1, w1, w1, w1};
-  asm volatile("" : "+v"(w));
-  return __builtin_bit_cast(bf16x8, w);
-}
-
 // Maximum over the two lanes of a column, in both.
 __device__ inline float t32_column_max(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -96,6 +88,167 @@ __device__ inline float max16(const f32x16 &x) {
 #pragma unroll
   for (int i = 1; i < 16; ++i) m = fmaxf(m, x[i]);
   return m;
+}
+
+// Transposed scores of 32 query columns over a 32-key LDS tile: element i = key t32_key(i), column n.  s: what they start from.
+template <int D, bool SWZ>
+__device__ inline f32x16 t32_scores(const bf16x8 (&qop)[D / 16], lds_cptr kt, const typename T32<D, SWZ>::Lanes &ln, f32x16 s) {
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) s = mfma32(T32<D, SWZ>::row(kt, ln, ks), qop[ks], s);
+  return s;
+}
+
+// The sum of a B operand's eight entries by products with two bf16 ones (32-bit sums), onto c.
+__device__ inline float bf16_ones() { return in_vgpr(__builtin_bit_cast(float, 0x3F803F80u)); }
+__device__ inline float sum8(bf16x8 p, float ones, float c) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    c = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{p[2 * j], p[2 * j + 1]}, __builtin_bit_cast(bf16x2, ones), c, false);
+  return c;
+}
+// Sum over the two lanes of a column, in both.
+__device__ inline float t32_column_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sums of the probabilities of 32 columns, in the same bf16 rounding the numerator uses.  In parts: two per lane, four per column.
+struct SumParts {
+  float part[2], ones;
+  __device__ inline SumParts() { ones = bf16_ones(); }
+  __device__ inline void clear() { part[0] = part[1] = 0.f; }
+  __device__ inline void add(bf16x8 p, int kc, bool first) { part[kc] = sum8(p, ones, first ? 0.f : part[kc]); }
+  __device__ inline void scale(float a) { part[0] *= a; part[1] *= a; }
+  __device__ inline float mine() const { return part[0] + part[1]; }
+  __device__ inline float total() const { return t32_column_sum(mine()); }
+};
+// On the matrix pipe, bit for bit what one 16 x 16 x 32 product with ones gives over the tile's keys in order: two
+// register swaps bring the slices of 16 columns together, so that a product of that shape sums the tile's 32 keys.  For the
+// compression branch: its normaliser scales the selection scores, and a top-k among near-equal scores depends on their last bits.
+// (A 32 x 32 x 16 product with ones gives the same but takes 16 registers, which the walk has not got: 1400 us for 1370 at 62k
+// tokens; sums in parts as above 1290 us, with the lse of most rows off in the last bit and some five rows of 100000 choosing
+// another of two blocks.)
+struct SumInOrder {
+  f32x4 sum[2];  // element 0: columns 0 .. 15, columns 16 .. 31
+  bf16x8 ones, before;
+  __device__ inline SumInOrder() {
+    const float w1 = __builtin_bit_cast(float, 0x3F803F80u);
+    f32x4 w = {w1, w1, w1, w1};
+    asm volatile("" : "+v"(w));  // (opaque, or it is rebuilt with four moves in front of every use)
+    ones = __builtin_bit_cast(bf16x8, w);
+  }
+  __device__ inline void clear() { sum[0] = sum[1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  __device__ inline void add(bf16x8 p, int kc, bool first) {
+    if (kc == 0) {
+      before = p;
+      return;
+    }
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+    const u32x4 x = __builtin_bit_cast(u32x4, before), y = __builtin_bit_cast(u32x4, p);
+    u32x4 lo, hi;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const auto h = __builtin_amdgcn_permlane32_swap(x[i], y[i], false, false);
+      const auto q = __builtin_amdgcn_permlane16_swap(h[0], h[1], false, false);
+      lo[i] = q[0];
+      hi[i] = q[1];
+    }
+    if (first) clear();
+    sum[0] = mfma16(ones, __builtin_bit_cast(bf16x8, lo), sum[0]);
+    sum[1] = mfma16(ones, __builtin_bit_cast(bf16x8, hi), sum[1]);
+  }
+  __device__ inline void scale(float a) {
+    // (the factors of the other 16 columns are in the lanes 16 away)
+    const auto f = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+    sum[0][0] *= __uint_as_float(f[0]);
+    sum[1][0] *= __uint_as_float(f[1]);
+  }
+  __device__ inline float mine() const { return threadIdx.x & 16 ? sum[1][0] : sum[0][0]; }
+  __device__ inline float total() const { return mine(); }
+};
+
+// Softmax state of 32 query columns (Algorithm 1's o, l, m): unnormalised output (transposed), sum, reference exponent in log2 units.
+template <int D, class Sum>
+struct T32State {
+  f32x16 o[D / 32];
+  Sum l;
+  float m;
+};
+template <int D, class Sum>
+__device__ inline void t32_clear(T32State<D, Sum> &st) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db) st.o[db] = splat16(0.f);
+  st.l.clear();
+  st.m = -INFINITY;
+}
+
+// One step of the softmax (Algorithm 1, inner loop body) over a tile with raw scores s.  The reference exponent of a column is the
+// maximum of its first tile (FIRST) and stays: later tiles cost a fused multiply-add, an exponential and half a conversion
+// per score, no maximum and no rescaling.  The result does not depend on the reference as long as nothing leaves the range of the
+// floats, which the caller checks on the finished sums (t32_in_range).
+template <int D, bool SWZ, bool FIRST, class Sum>
+__device__ inline void t32_softmax(T32State<D, Sum> &st, const f32x16 &s, lds_cptr vt, const typename T32<D, SWZ>::Lanes &ln, float sl2) {
+  if (FIRST) st.m = t32_column_max(max16(s)) * sl2;
+#pragma unroll
+  for (int kc = 0; kc < 2; ++kc) {
+    const bool fresh = FIRST && kc == 0;  // (no registers to clear: the products start from a constant)
+    bf16x8 p;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = (__bf16)fast_exp2(__builtin_fmaf(s[8 * kc + j], sl2, -st.m));
+    st.l.add(p, kc, FIRST);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) st.o[db] = mfma32(T32<D, SWZ>::tr(vt, ln, db, kc), p, fresh ? splat16(0.f) : st.o[db]);
+  }
+}
+
+// The first tile's maximum contributes 1 to the sum, so nothing that counts is lost below; a sum under 2^60 leaves room for
+// values of the same size.
+template <int D, class Sum>
+__device__ inline bool t32_in_range(const T32State<D, Sum> &st) { return st.l.mine() < 0x1p60f; }
+
+// The same step with a running maximum (-inf for keys that do not count): the reference is raised when some
+// score exceeds it by more than 8 log2 units, so that every exponent stays below 8.
+template <int D, bool SWZ, class Sum>
+__device__ inline void t32_softmax_running(T32State<D, Sum> &st, const f32x16 &s, lds_cptr vt, const typename T32<D, SWZ>::Lanes &ln, float sl2) {
+  const float pm = max16(s) * sl2;
+  if (__any(pm > st.m + 8.f)) {
+    const float mn = fmaxf(st.m, t32_column_max(pm));
+    const float alpha = mn == -INFINITY ? 1.0f : fast_exp2(st.m - mn);
+    st.l.scale(alpha);
+    st.m = mn;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) st.o[db][i] *= alpha;
+  }
+  const float neg = st.m != -INFINITY ? -st.m : -INFINITY;
+#pragma unroll
+  for (int kc = 0; kc < 2; ++kc) {
+    bf16x8 p;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = (__bf16)fast_exp2(__builtin_fmaf(s[8 * kc + j], sl2, neg));
+    st.l.add(p, kc, false);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) st.o[db] = mfma32(T32<D, SWZ>::tr(vt, ln, db, kc), p, st.o[db]);
+  }
+}
+
+// What the score accumulators of a range's last tile start from: 0, and -inf for the keys that do not count (32 floats of LDS).
+__device__ inline f32x16 t32_tail(const float *tail) {
+  f32x16 s;
+  int first = t32_key(0);
+  asm volatile("" : "+v"(first));  // (or the 16 values stay in registers between the steps)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 x = *reinterpret_cast<const f32x4 *>(tail + first + 16 * (i >> 1) + 4 * (i & 1));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[4 * i + j] = x[j];
+  }
+  return s;
+}
+__device__ inline void t32_write_tail(float *tail, int left) {
+  if (threadIdx.x < 32) tail[threadIdx.x] = (int)threadIdx.x < left ? 0.f : -INFINITY;
 }
 
 // Store an accumulator tile (columns x D, rows of a transposed operand as above) as bf16 rows: lane n and n + 32 hold column n's
@@ -184,4 +337,82 @@ __device__ inline void t32_stage2(const bf16_t *xa, const bf16_t *xb, uint32_t s
         *reinterpret_cast<bf16x8 *>(tb + off[u]) = rb[u];
       }
   }
+}
+
+// Global sources of a tile set: row-major arrays, already offset to the KV group; `stride` elements between rows (whole arrays stay
+// below 2^31 elements).
+template <int NROW>
+struct T32Src {
+  const bf16_t *row[NROW];
+  uint32_t stride;
+};
+
+constexpr int T32_PF = 1;  // steps the loads of a walk run ahead: a second register set costs more than it hides (spills)
+
+// Walk of a workgroup over the rows [rs, re) of NROW arrays in steps of STEP rows: 32-row tiles (one of each array; the arrays may
+// be consecutive tiles of one, with STEP a multiple of 32) go global -> registers -> LDS once per workgroup, loads PF (1 or 2) steps
+// ahead through as many register sets, two LDS stages and one barrier per step.  tile(first tile of the stage, first row) consumes a stage.
+// Rows past re are read as they lie in memory (padded arrays) and are the consumer's to mask.
+template <int D, int NROW, int NTHR, int STEP, int PF, class Tile>
+__device__ inline void t32_pipeline(const T32Src<NROW> &src, unsigned char *stage0, int rs, int re, Tile tile) {
+  using T = T32<D, true>;
+  constexpr int NI = (T::ITEMS + NTHR - 1) / NTHR;
+  static_assert(T::ITEMS % NTHR == 0 || NI == 1, "whole tiles at a time");
+  const bool mine = T::ITEMS >= NTHR || (int)threadIdx.x < T::ITEMS;
+  const int row0 = threadIdx.x / T::SEGS, seg = threadIdx.x % T::SEGS;
+  struct Regs { bf16x8 r[NROW][NI]; } regs[PF];
+  auto load = [&](Regs &x, int kb) {
+    if (!mine) return;
+#pragma unroll
+    for (int a = 0; a < NROW; ++a)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        x.r[a][i] = ld8(src.row[a] + ((uint32_t)(kb + row0 + i * (NTHR / T::SEGS)) * src.stride + (uint32_t)(seg * 8)));
+  };
+  auto step = [&](Regs &x, int buf, int kb) {
+    unsigned char *st = stage0 + buf * NROW * T::BYTES;
+    if (mine)
+#pragma unroll
+      for (int a = 0; a < NROW; ++a)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) *reinterpret_cast<bf16x8 *>(st + a * T::BYTES + T::off(row0 + i * (NTHR / T::SEGS), seg)) = x.r[a][i];
+    if (kb + PF * STEP < re) load(x, kb + PF * STEP);
+    __syncthreads();
+    tile((lds_cptr)st, kb);
+  };
+  if (rs < re) load(regs[0], rs);
+  if (PF == 2 && rs + STEP < re) load(regs[PF - 1], rs + STEP);
+  for (int kb = rs; kb < re; kb += 2 * STEP) {
+    step(regs[0], 0, kb);
+    if (kb + STEP >= re) break;
+    step(regs[PF - 1], 1, kb + STEP);
+  }
+  __syncthreads();
+}
+
+// Workgroup of NW wavefronts: 32*NW query rows = consecutive sorted tokens x the heads of one KV group, 32 per wavefront.
+struct QCol {
+  int slot, pos, tok, h;  // token slot inside the workgroup, sorted position, caller index, head
+  bool valid;             // columns past the last token repeat it and are not stored
+};
+// (Looked up again where it is needed after a walk, through an opaque thread number: held across the walk it takes registers that
+// the walk has not got.)
+__device__ inline QCol query_col(const MfmaView &v, int wg_pos0, int g) {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  const int row = (t >> 6) * 32 + (t & 31);
+  QCol q;
+  q.slot = row / v.hs;
+  q.valid = wg_pos0 + q.slot < v.N;
+  q.pos = min(wg_pos0 + q.slot, v.N - 1);
+  q.tok = v.perm[q.pos];
+  q.h = g * v.hs + row % v.hs;
+  return q;
+}
+// The B operands of this lane's column from a caller-ordered array [N][Hq][D].
+template <int D>
+__device__ inline void load_col(const bf16_t *X, const MfmaView &v, const QCol &q, bf16x8 (&op)[D / 16]) {
+  const bf16_t *src = X + ((size_t)q.tok * v.Hq + q.h) * D + 8 * (threadIdx.x >> 5 & 1);
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) op[ks] = ld8(src + 16 * ks);
 }
