@@ -127,9 +127,10 @@ __device__ inline int wave_max_i32(int v) {
 template <typename T>
 __global__ __launch_bounds__(256) void g_sort_pool(const T *__restrict__ K, const T *__restrict__ V, BlkView bv, int row /*Hkv*d*/,
                                                    float *__restrict__ Ks, float *__restrict__ Vs, float *__restrict__ Kc,
-                                                   float *__restrict__ Vc) {
+                                                   float *__restrict__ Vc, uint32_t *ticket) {
   __shared__ f4 part[2][256];
   const int c = blockIdx.x;
+  if (ticket && c == 0 && threadIdx.x == 0) *ticket = 0u;  // counter of the selection index's first pass
   const int b = bv.cmp_start[c], e = bv.cmp_start[c + 1];
   const float inv = 1.0f / (float)(e - b);
   const int c4 = row / 4, C = min(c4, 256), ngrp = 256 / C, grp = threadIdx.x / C;
@@ -1070,7 +1071,7 @@ int forward_t(const ssa_ctx &c, const void *q, const void *k, const void *v, con
   });
   const float sl2 = c.scale * LOG2E_F;
   const dim3 grid((unsigned)((c.N + tpt - 1) / tpt * tiles_per_token(c.hs)), c.Hkv);
-  g_sort_pool<T><<<c.blk->Nc, 256, 0, c.stream>>>((const T *)k, (const T *)v, bv, c.Hkv * c.d, Ks, Vs, Kc, Vc);
+  g_sort_pool<T><<<c.blk->Nc, 256, 0, c.stream>>>((const T *)k, (const T *)v, bv, c.Hkv * c.d, Ks, Vs, Kc, Vc, nullptr);
   FwdArgs a{q, gates, bv, I, c.Hq, c.Hkv, c.hs, c.d, c.T, sl2, Kc, Vc, Ob, out, L};
   g_cmp_fwd<T, DT><<<grid, 64 * NW, 0, c.stream>>>(a);
   ScoreArgs sa{q, bv, Kc, L, I, c.Hq, c.Hkv, c.hs, c.d, c.T, tw, c.blk->s_max, sl2};
@@ -1093,10 +1094,10 @@ int backward_t(const ssa_ctx &c, const void *q, const void *k, const void *v, co
   const int tpt = tokens_per_tile(c.hs), row = c.Hkv * c.d;
   const float sl2 = c.scale * LOG2E_F;
   const dim3 grid((unsigned)((c.N + tpt - 1) / tpt * tiles_per_token(c.hs)), c.Hkv);
-  g_sort_pool<T><<<c.blk->Nc, 256, 0, c.stream>>>((const T *)k, (const T *)v, bv, row, Ks, Vs, Kc, Vc);
+  const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, BC_CHUNK);
+  g_sort_pool<T><<<c.blk->Nc, 256, 0, c.stream>>>((const T *)k, (const T *)v, bv, row, Ks, Vs, Kc, Vc, sel.ticket);
   DqArgs a{q, dout, out_branch, gates, bv, topk_idx, c.Hq, c.Hkv, c.hs, c.d, c.T, c.scale, sl2, Ks, Vs, Kc, Vc, lse, dq, dgates, info};
   g_bwd_dq<T, DT><<<grid, 64 * NW, union_lds_bytes(tpt, c.T), c.stream>>>(a);
-  const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, BC_CHUNK);
   const int rc = sel_index_build(topk_idx, c.blk->perm, c.blk->slc_start, c.N, c.Hkv, c.T, c.blk->Ns, sel, true, false, true, c.stream);
   if (rc != SSA_OK) return rc;
   DkvArgs b{q, dout, bv, c.Hq, c.Hkv, c.hs, c.d, c.scale, sl2, Ks, Vs, Kc, Vc, info, sel.list, sel.chunk_start,

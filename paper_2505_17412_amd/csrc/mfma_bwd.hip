@@ -493,6 +493,7 @@ __global__ void m_bwd_finish(const int32_t *__restrict__ perm, const int32_t *__
   const float inv = 1.0f / (float)(e - b);
   for (int f = threadIdx.x; f < row; f += blockDim.x) {
     float ck = 0.f, cv = 0.f;
+#pragma unroll 8  // (or the sum waits for one load after the other)
     for (int s = 0; s < splits; ++s) {
       ck += dKc[((size_t)s * Nc + c) * row + f];
       cv += dVc[((size_t)s * Nc + c) * row + f];

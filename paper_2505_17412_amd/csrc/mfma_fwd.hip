@@ -307,7 +307,7 @@ void launch_cmp(const FwdArgs &a, hipStream_t s) {
 }
 
 template <int D>
-int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, const SelIndex &sel, const SlcPartials &part, hipStream_t s) {
+int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, const SelIndex &sel, const SlcPartials &part, hipStream_t s) {
   {
     ProfScope ps(PROF_CMP_FWD, s);
     if (cmp_waves<D>(a.v.hs, a.v.s_max) == 4) launch_cmp<D, 4>(a, s);
@@ -331,7 +331,7 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, const SelIndex &
   }
   {
     ProfScope ps(PROF_COMBINE, s);
-    const int rc = slc_merge_kernel(a.v, D, part, a.idx, gates, a.Ob, a.lse, out, s);
+    const int rc = slc_merge_kernel(a.v, D, part, a.idx, gates, a.Ob, a.lse, out, keep, s);
     if (rc != SSA_OK) return rc;
   }
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
@@ -349,12 +349,13 @@ size_t mfma_fwd_lds_bytes(int D, int hs, int s_max) {
 }
 
 int mfma_forward_kernels(const MfmaView &v, int D, const void *q, const void *gates, void *out, float *lse,
-                         int32_t *idx, void *out_branch, const SelIndex &sel, const SlcPartials &part, hipStream_t s) {
+                         int32_t *idx, void *out_branch, SlcKeep keep, const SelIndex &sel, const SlcPartials &part,
+                         hipStream_t s) {
   FwdArgs a{v, (const bf16_t *)q, (bf16_t *)out_branch, lse, idx};
   switch (D) {
-    case 32: return launch_forward<32>(a, (const bf16_t *)gates, (bf16_t *)out, sel, part, s);
-    case 64: return launch_forward<64>(a, (const bf16_t *)gates, (bf16_t *)out, sel, part, s);
-    case 128: return launch_forward<128>(a, (const bf16_t *)gates, (bf16_t *)out, sel, part, s);
+    case 32: return launch_forward<32>(a, (const bf16_t *)gates, (bf16_t *)out, keep, sel, part, s);
+    case 64: return launch_forward<64>(a, (const bf16_t *)gates, (bf16_t *)out, keep, sel, part, s);
+    case 128: return launch_forward<128>(a, (const bf16_t *)gates, (bf16_t *)out, keep, sel, part, s);
     default: return SSA_ERR_UNSUPPORTED;
   }
 }

@@ -6,8 +6,9 @@
 size_t mfma_fwd_lds_bytes(int D, int hs, int s_max);
 struct SelIndex;
 struct SlcPartials;
+struct SlcKeep { bool branch, lse; };  // whether the selection branch's output and its log-sum-exp are read by anybody
 int mfma_forward_kernels(const MfmaView &v, int D, const void *q, const void *gates, void *out, float *lse,
-                         int32_t *idx, void *out_branch, const SelIndex &sel, const SlcPartials &part, hipStream_t s);
+                         int32_t *idx, void *out_branch, SlcKeep keep, const SelIndex &sel, const SlcPartials &part, hipStream_t s);
 
 // Inverse of the selection (sel_index.hip): per (KV head, selection block) key = g*Ns + b, the ascending list of sorted
 // positions of the tokens that selected it, and the cuts of the lists into work chunks.
@@ -20,8 +21,11 @@ struct SelIndex {
   int32_t *chunk_start, *part_row_start;  // [Hkv*Ns+1] each: dK/dV work chunks and partial-sum rows per key
   int32_t *bc_chunk_start;        // [Hkv*Ns+1]: work chunks of the block-centric forward / dQ kernels
   uint32_t *bins;                 // bucket counters of the two execution orders
+  uint32_t *ticket;               // [2] workgroup counters; an earlier kernel on the stream sets the first to 0
   int4 *slot, *bc_slot;           // bucket, number in the bucket, key, chunk of every chunk
   ChunkRef *order, *bc_order;     // the chunks of either chunking in execution order (see m_chunk_order)
+  int32_t *base;                  // [2 * keys] with by_length: first place of every key's chunks in the two orders
+  bool by_length;                 // the chunks run by falling block length (see sel_index_carve)
   int chunk_len, bc_chunk_len;    // query tokens per chunk: at least 256 (dK/dV), BC_CHUNK_MIN .. BC_CHUNK
 };
 size_t sel_index_bytes(int N, int Hkv, int T, int Ns);
@@ -41,8 +45,9 @@ struct SlcPartials {
 // also writes the gated sum of eq. (4) (out_branch [3,N,Hq,D]: branches 0 and 2 read, 1 written; lse [3,N,Hq]).
 int slc_forward_kernel(const MfmaView &v, int D, const void *q, const SelIndex &sel,
                        const SlcPartials &part, hipStream_t s);
+// (keep: what the caller reads besides the gated sum).
 int slc_merge_kernel(const MfmaView &v, int D, const SlcPartials &part, const int32_t *idx, const void *gates,
-                     void *out_branch, float *lse, void *out, hipStream_t s);
+                     void *out_branch, float *lse, void *out, SlcKeep keep, hipStream_t s);
 
 // Device buffers of the backward pass (carved from the caller's workspace).
 struct BwdBuffers {

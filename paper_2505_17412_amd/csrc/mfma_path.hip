@@ -23,13 +23,15 @@ bool slc_bwd_two_kernels(const ssa_blocks *b, int D, int Hkv, int T) {
 namespace {
 
 struct Tail { bf16_t *p; size_t begin, end; };  // element range to clear
-struct Tails { Tail t[4]; };
+struct Tails { Tail t[4]; uint32_t *ticket; };  // and the counter of the selection index's first pass
 
-__global__ void m_zero_tails(Tails ts) {
-  const Tail t = ts.t[blockIdx.y];
-  if (!t.p) return;
-  for (size_t i = t.begin + (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < t.end; i += (size_t)gridDim.x * blockDim.x)
-    t.p[i] = 0;
+constexpr int TAIL_WGS = 8;  // workgroups per array
+
+// The zero rows behind the sorted and pooled arrays: the last 4 * TAIL_WGS workgroups of the preparation's launch.
+__device__ inline void zero_tail(const Tails &ts, int wg) {
+  if (wg == 0 && threadIdx.x == 0) *ts.ticket = 0u;
+  const Tail t = ts.t[wg / TAIL_WGS];
+  for (size_t i = t.begin + (size_t)(wg % TAIL_WGS) * blockDim.x + threadIdx.x; i < t.end; i += (size_t)TAIL_WGS * blockDim.x) t.p[i] = 0;
 }
 
 struct PrepOut { bf16_t *Ks, *Vs, *Kc, *Vc; };
@@ -37,8 +39,9 @@ struct PrepOut { bf16_t *Ks, *Vs, *Kc, *Vc; };
 // One workgroup per compression block: gathers its tokens' K,V rows into sorted order and writes the block mean
 // (eq. (5), mean pool over the active tokens).
 __global__ void m_prep(const bf16_t *__restrict__ K, const bf16_t *__restrict__ V, const int32_t *__restrict__ perm,
-                       const int32_t *__restrict__ cmp_start, int Hkv, int D, PrepOut o) {
+                       const int32_t *__restrict__ cmp_start, int Hkv, int D, int Nc, PrepOut o, Tails ts) {
   const int c = blockIdx.x, row = Hkv * D;
+  if (c >= Nc) return zero_tail(ts, c - Nc);
   const int b = cmp_start[c], e = cmp_start[c + 1];
   const float inv = 1.0f / (float)(e - b);
   for (int f = threadIdx.x; f < row; f += blockDim.x) {
@@ -62,9 +65,11 @@ __global__ void m_prep(const bf16_t *__restrict__ K, const bf16_t *__restrict__ 
 // added in a fixed order.
 __global__ __launch_bounds__(128) void m_prep8(const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
                                                const int32_t *__restrict__ perm, const int32_t *__restrict__ cmp_start,
-                                               int R8, PrepOut o) {
+                                               int R8, int Nc, PrepOut o, Tails ts) {
   __shared__ float part[2][128][8];
-  const int c = blockIdx.x, b = cmp_start[c], e = cmp_start[c + 1];
+  const int c = blockIdx.x;
+  if (c >= Nc) return zero_tail(ts, c - Nc);
+  const int b = cmp_start[c], e = cmp_start[c + 1];
   const int seg = threadIdx.x % R8, grp = threadIdx.x / R8, ngrp = 128 / R8;
   float sk[8], sv[8];
 #pragma unroll
@@ -128,18 +133,18 @@ MfmaView make_view(const ssa_ctx &c) {
   return v;
 }
 
-int run_prep(const ssa_ctx &c, const void *k, const void *v, const PrepOut &o) {
+int run_prep(const ssa_ctx &c, const void *k, const void *v, const PrepOut &o, uint32_t *ticket) {
   ProfScope ps(PROF_PREP, c.stream);
   const size_t row = (size_t)c.Hkv * c.d;
   const size_t nt = padded_rows(c.N) * row, nc = padded_rows(c.blk->Nc) * row;
-  const size_t t0 = (size_t)(c.N / 8) * 8 * row, c0 = (size_t)(c.blk->Nc / 8) * 8 * row;
-  Tails ts{{{o.Ks, t0, nt}, {o.Vs, t0, nt}, {o.Kc, c0, nc}, {o.Vc, c0, nc}}};
-  m_zero_tails<<<dim3(8, 4), 256, 0, c.stream>>>(ts);
+  const size_t t0 = (size_t)c.N * row, c0 = (size_t)c.blk->Nc * row;
+  Tails ts{{{o.Ks, t0, nt}, {o.Vs, t0, nt}, {o.Kc, c0, nc}, {o.Vc, c0, nc}}, ticket};
+  const unsigned grid = (unsigned)c.blk->Nc + 4 * TAIL_WGS;
   const int r8 = c.Hkv * c.d / 8;
   if ((c.Hkv * c.d) % 8 == 0 && r8 <= 64 && 128 % r8 == 0)
-    m_prep8<<<c.blk->Nc, 128, 0, c.stream>>>((const bf16_t *)k, (const bf16_t *)v, c.blk->perm, c.blk->cmp_start, r8, o);
+    m_prep8<<<grid, 128, 0, c.stream>>>((const bf16_t *)k, (const bf16_t *)v, c.blk->perm, c.blk->cmp_start, r8, c.blk->Nc, o, ts);
   else
-    m_prep<<<c.blk->Nc, 128, 0, c.stream>>>((const bf16_t *)k, (const bf16_t *)v, c.blk->perm, c.blk->cmp_start, c.Hkv, c.d, o);
+    m_prep<<<grid, 128, 0, c.stream>>>((const bf16_t *)k, (const bf16_t *)v, c.blk->perm, c.blk->cmp_start, c.Hkv, c.d, c.blk->Nc, o, ts);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
@@ -246,19 +251,19 @@ int mfma_backward(const ssa_ctx &c, const void *q, const void *k, const void *v,
   PrepOut o{};
   o.Ks = (bf16_t *)(ws + p.ks); o.Vs = (bf16_t *)(ws + p.vs);
   o.Kc = (bf16_t *)(ws + p.kc); o.Vc = (bf16_t *)(ws + p.vc);
-  int rc = run_prep(c, k, v, o);
+  BwdBuffers w{};
+  w.sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, bc_chunk_len(c.N, c.Hkv, c.T));
+  int rc = run_prep(c, k, v, o, w.sel.ticket);
   if (rc != SSA_OK) return rc;
   rc = override_pooled(c, o);
   if (rc != SSA_OK) return rc;
   MfmaView view = make_view(c);
   view.Ks = o.Ks; view.Vs = o.Vs; view.Kc = o.Kc; view.Vc = o.Vc;
-  BwdBuffers w{};
   w.dKc_out = c.dkc_out; w.dVc_out = c.dvc_out;
   w.lse2s = (float *)(ws + p.lse2s); w.deltas = (float *)(ws + p.deltas); w.gws = (float *)(ws + p.gws);
   w.deltag = (float *)(ws + p.deltag);
   w.Qs = (bf16_t *)(ws + p.qs); w.dOg = (bf16_t *)(ws + p.dos); w.dQp = (float *)(ws + p.dqp);
   w.dKs = (float *)(ws + p.dks); w.dVs = (float *)(ws + p.dvs); w.dKc = (float *)(ws + p.dkc); w.dVc = (float *)(ws + p.dvc);
-  w.sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, bc_chunk_len(c.N, c.Hkv, c.T));
   w.q_splits = p.q_splits;
   w.pK = (float *)(ws + p.pk); w.pV = (float *)(ws + p.pv); w.max_chunks = p.max_chunks;
   w.part = SlcPartials{(bf16_t *)(ws + p.pdq), nullptr};
@@ -273,15 +278,15 @@ int mfma_forward(const ssa_ctx &c, const void *q, const void *k, const void *v, 
   char *ws = (char *)ws_;
   PrepOut o{};
   o.Ks = (bf16_t *)(ws + p.ks); o.Vs = (bf16_t *)(ws + p.vs); o.Kc = (bf16_t *)(ws + p.kc); o.Vc = (bf16_t *)(ws + p.vc);
-  int rc = run_prep(c, k, v, o);
+  const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, 1024, bc_chunk_len(c.N, c.Hkv, c.T));
+  int rc = run_prep(c, k, v, o, sel.ticket);
   if (rc != SSA_OK) return rc;
   rc = override_pooled(c, o);
   if (rc != SSA_OK) return rc;
   MfmaView view = make_view(c);
   view.Ks = o.Ks; view.Vs = o.Vs; view.Kc = o.Kc; view.Vc = o.Vc;
-  const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, 1024, bc_chunk_len(c.N, c.Hkv, c.T));
   const SlcPartials part{(bf16_t *)(ws + p.po), (float *)(ws + p.pml)};
   return mfma_forward_kernels(view, c.d, q, gates, out, lse ? lse : (float *)(ws + p.lse),
                               topk_idx ? topk_idx : (int32_t *)(ws + p.idx), out_branch ? out_branch : (void *)(ws + p.ob),
-                              sel, part, c.stream);
+                              SlcKeep{out_branch != nullptr, lse != nullptr}, sel, part, c.stream);
 }

@@ -11,15 +11,6 @@
 
 namespace {
 
-// Workgroup id -> work chunk.  Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2); the map
-// gives every XCD one contiguous run of the `total` chunks (one KV head, neighbouring blocks), so a block's rows are
-// fetched into one L2.  The grid is a multiple of 8 workgroups; ids past the end return -1.
-__device__ inline int bc_chunk_of_workgroup(int total) {
-  const int per = (total + 7) >> 3, xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
-  const int w = xcd * per + i;
-  return (i < per && w < total) ? w : -1;
-}
-
 // ---------------------------------------------------------------------------------------------------------
 // Selection branch, block-centric (Algorithm 1 with the loops exchanged): the outer loop runs over the selected blocks,
 // the inner one over the query tokens that selected the block.  A workgroup takes one (KV head, selection block) and a
@@ -106,8 +97,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   float *tail = (float *)(ent + BC_CHUNK);
   const int wid = uniform(threadIdx.x >> 6), h = threadIdx.x >> 5 & 1, n = threadIdx.x & 31;
   const int hs = a.v.hs, Hkv = a.v.Hkv, Ns = a.v.Ns;
-  const int wi = bc_chunk_of_workgroup(a.chunk_start[Hkv * Ns]);
-  if (wi < 0) return;
+  const int wi = blockIdx.x;
+  if (wi >= a.chunk_start[Hkv * Ns]) return;
   const ChunkRef cr = a.chunk_order[wi];
   const int key = uniform(cr.key), g = key / Ns, blk = key % Ns;
   const int kbeg = uniform(a.v.slc_start[blk]), kend = uniform(a.v.slc_start[blk + 1]);
@@ -187,7 +178,16 @@ struct MergeArgs {
   float *lse;  // [3,N,Hq]
   bf16_t *out;
   int N, Hq, Hkv, hs, T, D;
+  SlcKeep keep;
 };
+
+// Blocks in a row of I: rows are ascending with the -1 padding at the end, and nearly all are full.
+__device__ inline int selected(const int32_t *row, int T) {
+  if (row[T - 1] >= 0) return T;
+  int nv = 0;
+  for (int j = 0; j < T; ++j) nv += row[j] >= 0 ? 1 : 0;
+  return nv;
+}
 
 __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -196,13 +196,12 @@ __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
   const int c8 = (int)(i % per_row), h = (int)(i / per_row % a.Hq), tok = (int)(i / ((size_t)per_row * a.Hq));
   const int g = h / a.hs, hl = h % a.hs;
   const size_t slot0 = ((size_t)tok * a.Hkv + g) * a.T;
-  const int32_t *row = a.idx + slot0;
-  int nv = 0;  // rows are ascending with the -1 padding at the end
-  for (int j = 0; j < a.T; ++j) nv += row[j] >= 0 ? 1 : 0;
+  const int nv = selected(a.idx + slot0, a.T);
   float M = -INFINITY;
+#pragma unroll 8
   for (int j = 0; j < nv; ++j) M = fmaxf(M, a.pml[((slot0 + j) * a.hs + hl) * 2]);
   float L = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
+#pragma unroll 8
   for (int j = 0; j < nv; ++j) {
     const size_t r = (slot0 + j) * a.hs + hl;
     const float2 ml = *reinterpret_cast<const float2 *>(a.pml + r * 2);
@@ -218,8 +217,8 @@ __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
   bf16x8 os;
 #pragma unroll
   for (int e = 0; e < 8; ++e) os[e] = (__bf16)(acc[e] * inv);
-  *reinterpret_cast<bf16x8 *>(a.Ob + NH * a.D + off) = os;
-  if (c8 == 0) a.lse[NH + th] = L > 0.f ? (M + __log2f(L)) * LN2 : -INFINITY;
+  if (a.keep.branch) *reinterpret_cast<bf16x8 *>(a.Ob + NH * a.D + off) = os;
+  if (a.keep.lse && c8 == 0) a.lse[NH + th] = L > 0.f ? (M + __log2f(L)) * LN2 : -INFINITY;
   const float w0 = bf16_to_f32(a.gates[th * 3]), w1 = bf16_to_f32(a.gates[th * 3 + 1]), w2 = bf16_to_f32(a.gates[th * 3 + 2]);
   const bf16x8 x0 = ld8(a.Ob + off), x2 = ld8(a.Ob + 2 * NH * a.D + off);
   bf16x8 o;
@@ -309,8 +308,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   float *tail = (float *)(sl + BC_CHUNK);
   const int wid = uniform(threadIdx.x >> 6);
   const int hs = a.v.hs, Hkv = a.v.Hkv, Ns = a.v.Ns;
-  const int wi = bc_chunk_of_workgroup(a.chunk_start[Hkv * Ns]);
-  if (wi < 0) return;
+  const int wi = blockIdx.x;
+  if (wi >= a.chunk_start[Hkv * Ns]) return;
   const ChunkRef cr = a.chunk_order[wi];
   const int key = uniform(cr.key), g = key / Ns, blk = key % Ns;
   const int kbeg = uniform(a.v.slc_start[blk]), kend = uniform(a.v.slc_start[blk + 1]);
@@ -385,9 +384,7 @@ __global__ __launch_bounds__(256) void m_dq_merge(DqMergeArgs a) {
   if (i >= (size_t)a.N * a.Hq * per_row) return;
   const int c8 = (int)(i % per_row), h = (int)(i / per_row % a.Hq), pos = (int)(i / ((size_t)per_row * a.Hq));
   const int g = h / a.hs, hl = h % a.hs, tok = a.perm[pos];
-  const int32_t *row = a.idx + ((size_t)tok * a.Hkv + g) * a.T;
-  int nv = 0;  // rows are ascending with the -1 padding at the end
-  for (int j = 0; j < a.T; ++j) nv += row[j] >= 0 ? 1 : 0;
+  const int nv = selected(a.idx + ((size_t)tok * a.Hkv + g) * a.T, a.T);
   const float *base = a.dQp + ((size_t)pos * a.Hq + h) * a.D + 8 * c8;
   const float4 b0 = *reinterpret_cast<const float4 *>(base), b1 = *reinterpret_cast<const float4 *>(base + 4);
   const float part[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
@@ -428,7 +425,7 @@ int launch_slc_forward(const MfmaView &v, const bf16_t *q, const SelIndex &sel, 
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   });
   BcFwdArgs b{v, q, sel.list, sel.bc_chunk_start, sel.rank, sel.bc_order, part.o, part.ml};
-  kernel<<<dim3((chunk_bound(v, sel.bc_chunk_len) + 7) / 8 * 8), 64 * BS::NW, bc_lds_bytes<D, BS::KSEG>(), s>>>(b);
+  kernel<<<dim3(chunk_bound(v, sel.bc_chunk_len)), 64 * BS::NW, bc_lds_bytes<D, BS::KSEG>(), s>>>(b);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
@@ -441,7 +438,7 @@ int launch_slc_dq(const MfmaView &v, const BwdBuffers &w, hipStream_t s) {
   });
   const size_t NH = (size_t)v.N * v.Hq;
   BcDqArgs b{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.list, w.sel.bc_chunk_start, w.sel.rank, w.sel.bc_order, w.part.o};
-  m_bwd_dq_bc<D, DQ_WAVES, DQ_KSEG, dq_wpe<D>()><<<dim3((chunk_bound(v, w.sel.bc_chunk_len) + 7) / 8 * 8), 64 * DQ_WAVES, bc_lds_bytes<D, DQ_KSEG>(), s>>>(b);
+  m_bwd_dq_bc<D, DQ_WAVES, DQ_KSEG, dq_wpe<D>()><<<dim3(chunk_bound(v, w.sel.bc_chunk_len)), 64 * DQ_WAVES, bc_lds_bytes<D, DQ_KSEG>(), s>>>(b);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
@@ -458,9 +455,9 @@ int slc_forward_kernel(const MfmaView &v, int D, const void *q, const SelIndex &
 }
 
 int slc_merge_kernel(const MfmaView &v, int D, const SlcPartials &part, const int32_t *idx, const void *gates,
-                     void *out_branch, float *lse, void *out, hipStream_t s) {
+                     void *out_branch, float *lse, void *out, SlcKeep keep, hipStream_t s) {
   MergeArgs m{part.o, part.ml, idx, (const bf16_t *)gates, (bf16_t *)out_branch, lse, (bf16_t *)out,
-              v.N, v.Hq, v.Hkv, v.hs, v.T, D};
+              v.N, v.Hq, v.Hkv, v.hs, v.T, D, keep};
   const size_t threads = (size_t)v.N * v.Hq * (D / 8);
   m_slc_merge<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(m);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
