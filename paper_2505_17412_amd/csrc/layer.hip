@@ -1,4 +1,4 @@
-// One full SSA attention layer for gfx950, composed on the host from the library's own entry points: query / key /
+// One full SSA attention layer for gfx950, composed on the host from the library's own parts: query / key /
 // value projections and the gate predictor on the input features, Spatial Sparse Attention (eq. (4)), output
 // projection; forward and backward.  Paper: gates are "a linear layer followed by a sigmoid" on the input features
 // (text after eq. (4)); the projections are those of any attention layer (Implementation Details: hidden dimension
@@ -78,8 +78,8 @@ BwdPlan bwd_plan(const ssa_params_t *p, const ssa_blocks_t *b, int Dm) {
   w.dkc = take((size_t)b->Nc * ckv * 4);
   w.dvc = take((size_t)b->Nc * ckv * 4);
   const size_t wt = align_up(cq * Dm * 2, 256) + 2 * align_up(ckv * Dm * 2, 256);  // transposed Wq, Wk, Wv
-  const size_t lin = max3(ssa_linear_workspace_bytes(p->n_tokens, (int)cq, Dm, 1), lin_dw_workspace(p->n_tokens, Dm, (int)cq),
-                          lin_dw_workspace(p->n_tokens, Dm, (int)ckv));
+  const size_t lin = max3(ssa_linear_workspace_bytes(p->n_tokens, (int)cq, Dm, 1),
+                          lin_dw_workspace(p->n_tokens, Dm, (int)cq) + 2 * lin_dw_workspace(p->n_tokens, Dm, (int)ckv), 0);
   const size_t mod = max3(cmp_module_workspace(p, b, 2, false), cmp_module_workspace(p, b, 2, true), 0);
   w.mod_in = take(cmp_module_input_bytes(p, b, 2));
   w.scratch_bytes = max3(max3(wt, lin, mod), ssa_workspace_bytes(p, b, 1), ssa_gate_workspace_bytes(p, Dm, 1)) + 256;
@@ -149,9 +149,10 @@ extern "C" int ssa_layer_forward(const ssa_params_t *p, const ssa_blocks_t *b, i
   char *wsb = (char *)align_up((size_t)ws, 256);
   char *scratch = wsb + pl.scratch;
   const int N = p->n_tokens, cq = p->n_heads_q * p->head_dim, ckv = p->n_heads_kv * p->head_dim;
-  int rc = ssa_linear_forward(N, d_model, cq, x, w->wq, w->bq, sv + s.q, stream);
-  if (rc == SSA_OK) rc = ssa_linear_forward(N, d_model, ckv, x, w->wk, w->bk, sv + s.k, stream);
-  if (rc == SSA_OK) rc = ssa_linear_forward(N, d_model, ckv, x, w->wv, w->bv, sv + s.v, stream);
+  const void *const wx[3] = {w->wq, w->wk, w->wv}, *const bx[3] = {w->bq, w->bk, w->bv};
+  void *const qkv[3] = {sv + s.q, sv + s.k, sv + s.v};
+  const int c3[3] = {cq, ckv, ckv};
+  int rc = lin_forward_multi(3, N, d_model, x, wx, bx, c3, qkv, (hipStream_t)stream);
   if (rc == SSA_OK) rc = ssa_gate_forward(p, d_model, x, w->wg, w->bg, sv + s.gates, scratch, pl.scratch_bytes, stream);
   if (rc == SSA_OK && mode == 1) {
     const ssa_cmp_weights_t ck{w->pe_k, w->wc_k, w->bc_k}, cv{w->pe_v, w->wc_v, w->bc_v};
@@ -231,17 +232,15 @@ extern "C" int ssa_layer_backward(const ssa_params_t *p, const ssa_blocks_t *b, 
   if (rc != SSA_OK) return rc;
   {
     ProfScope ps(PROF_LINEAR_BWD, st);
-    lin_dw(N, d_model, cq, x, dq, g->dwq, g->dbq, scratch, st);
-    lin_dw(N, d_model, ckv, x, dk, g->dwk, g->dbk, scratch, st);
-    lin_dw(N, d_model, ckv, x, dv, g->dwv, g->dbv, scratch, st);
+    const void *Xs[3] = {dq, dk, dv}, *Ws[3] = {w->wq, w->wk, w->wv};
+    float *const dws[3] = {g->dwq, g->dwk, g->dwv}, *const dbs[3] = {g->dbq, g->dbk, g->dbv};
+    const int Ks[3] = {cq, ckv, ckv};
+    lin_dw(3, N, d_model, Ks, x, Xs, dws, dbs, scratch, st);
     // dx = dq Wq + dk Wk + dv Wv in one launch over the three contractions
     char *wtq = scratch, *wtk = wtq + align_up((size_t)cq * d_model * 2, 256), *wtv = wtk + align_up((size_t)ckv * d_model * 2, 256);
-    lin_transpose_w(w->wq, cq, d_model, wtq, st);
-    lin_transpose_w(w->wk, ckv, d_model, wtk, st);
-    lin_transpose_w(w->wv, ckv, d_model, wtv, st);
-    const void *Xs[3] = {dq, dk, dv}, *Ws[3] = {wtq, wtk, wtv};
-    const int Ks[3] = {cq, ckv, ckv};
-    rc = lin_nt_multi(3, Xs, Ws, Ks, nullptr, N, d_model, dx, st);
+    void *Wts[3] = {wtq, wtk, wtv};
+    lin_transpose_w(3, Ws, Ks, d_model, Wts, st);
+    rc = lin_nt_multi(3, Xs, (const void *const *)Wts, Ks, nullptr, N, d_model, dx, st);
     if (rc != SSA_OK) return rc;
   }
   // gate predictor: its data gradient is added onto dx

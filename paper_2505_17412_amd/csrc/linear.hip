@@ -25,6 +25,11 @@ struct LinSrc {
   const bf16_t *X[3], *W[3];  // X_i [M][K_i], W_i [O][K_i]
   int K[3];
 };
+struct LinDst {
+  const bf16_t *bias[3];
+  bf16_t *Y[3];
+  int O[3];
+};
 
 // Y[t][o] = sum_k X[t][k] W[o][k] (+ bias[o]);  X [M][K], W [O][K], Y [M][O];  K % 128 == 0, O % 128 == 0.
 // WF x WT wavefronts, each owning CF x CT matrix-instruction tiles (16 features x 16 tokens): the workgroup tile is
@@ -32,21 +37,27 @@ struct LinSrc {
 // one token tile run on the same XCD, one after the other, so the token tile is fetched into that XCD's L2 once and the
 // weights (a few MB) stay resident in all of them.
 // The contraction may run over up to three (X, W) pairs one after the other (Y = sum_i X_i W_i^T): the data gradient
-// of projections that share their input is one launch.
+// of projections that share their input is one launch.  Or one X meets up to three weights (Y_i = X W_i^T; K[0] = K, X[0] = X):
+// the feature tiles of the three lie one after the other.  With grouped queries the key and the value projection have one or
+// two feature tiles, and by themselves leave most compute units idle: 5.5 k tokens of 1024 features, 1024 + 128 + 128 outputs
+// and the output projection, 82 us in four launches, 55 in two.
 template <int WF, int WT, int CF, int CT>
-__global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, const bf16_t *__restrict__ bias, int M, int O,
-                                                       bf16_t *__restrict__ Y) {
+__global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, int M) {
   using G = TileGeom<LIN_KC>;
   constexpr int BF = 16 * CF * WF, BT = 16 * CT * WT, NTHR = 64 * WF * WT;
   constexpr int STAGE_W = BF * LIN_KC, STAGE_X = BT * LIN_KC;  // elements per stage
   constexpr int IW = BF * 8 / NTHR, IX = BT * 8 / NTHR;         // 16-byte items per thread and chunk
   extern __shared__ __align__(16) unsigned char smem[];
   bf16_t *sw = (bf16_t *)smem, *sx = sw + 2 * STAGE_W;
-  const int n_ot = O / BF, n_tt = (M + BT - 1) / BT;
+  const int n_ot = (dst.O[0] + dst.O[1] + dst.O[2]) / BF, n_tt = (M + BT - 1) / BT;  // unused outputs have O = 0
   const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-  const int tt = (idx / n_ot) * 8 + xcd, ot = idx % n_ot;
+  const int tt = (idx / n_ot) * 8 + xcd;
   if (tt >= n_tt) return;
-  const int m0 = tt * BT, o0 = ot * BF;
+  const int f0 = idx % n_ot * BF;  // first feature of the tile, counted over all outputs
+  const int d = f0 < dst.O[0] ? 0 : (f0 < dst.O[0] + dst.O[1] ? 1 : 2);
+  const int m0 = tt * BT, o0 = f0 - (d > 0 ? dst.O[0] : 0) - (d > 1 ? dst.O[1] : 0), O = dst.O[d];
+  const bf16_t *__restrict__ bias = dst.bias[d];
+  bf16_t *__restrict__ Y = dst.Y[d];
   const int tid = threadIdx.x, wid = tid >> 6, lane = tid & 63, n = lane & 15, quad = lane >> 4;
   const int wc = wid % WF, wt = wid / WF;  // the wavefront's features and tokens inside the tile
   f32x4 acc[CF][CT];
@@ -62,7 +73,7 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, const bf16_t 
     // which pair the flat contraction index kf falls into (every K_i is a multiple of 128, so a chunk never straddles)
     const int p = kf < src.K[0] ? 0 : (kf < src.K[0] + src.K[1] ? 1 : 2);
     const int k0 = kf - (p > 0 ? src.K[0] : 0) - (p > 1 ? src.K[1] : 0), Kp = src.K[p];
-    const bf16_t *X = src.X[p], *W = src.W[p];
+    const bf16_t *X = src.X[p], *W = src.W[p + d];  // (several pairs: d = 0; several outputs: p = 0)
 #pragma unroll
     for (int i = 0; i < IW; ++i) {
       const int it = tid + NTHR * i, row = it >> 3, seg = it & 7;
@@ -141,10 +152,19 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, const bf16_t 
   }
 }
 
-// Wt[k][o] = W[o][k]: 32 x 32 tiles through LDS, both sides coalesced.
-__global__ __launch_bounds__(256) void lin_transpose(const bf16_t *__restrict__ W, int O, int K, bf16_t *__restrict__ Wt) {
+// Wt[k][o] = W[o][k]: 32 x 32 tiles through LDS, both sides coalesced; blockIdx.z picks one of up to three weights.
+struct LinTrans {
+  const bf16_t *W[3];
+  bf16_t *Wt[3];
+  int O[3];
+};
+__global__ __launch_bounds__(256) void lin_transpose(LinTrans a, int K) {
   __shared__ bf16_t t[32][33];
+  const bf16_t *__restrict__ W = a.W[blockIdx.z];
+  bf16_t *__restrict__ Wt = a.Wt[blockIdx.z];
+  const int O = a.O[blockIdx.z];
   const int k0 = blockIdx.x * 32, o0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  if (o0 >= O) return;
 #pragma unroll
   for (int r = ty; r < 32; r += 8) t[r][tx] = W[(size_t)(o0 + r) * K + k0 + tx];
   __syncthreads();
@@ -152,13 +172,24 @@ __global__ __launch_bounds__(256) void lin_transpose(const bf16_t *__restrict__ 
   for (int r = ty; r < 32; r += 8) Wt[(size_t)(k0 + r) * O + o0 + tx] = t[tx][r];
 }
 
+// Parameter gradients of up to three projections of one input: everything but the input is per projection.
+struct LinGrad {
+  const bf16_t *dY[3];
+  float *part[3], *bpart[3], *dw[3], *dbias[3];
+  int O[3], splits[3], tok_per_split[3];
+};
+
 // part[split][o][k] = sum over the split's tokens of dY[t][o] X[t][k]: workgroup = 128 x 128 output tile, one split.
-__global__ __launch_bounds__(256) void lin_tn(const bf16_t *__restrict__ dY, const bf16_t *__restrict__ X, int M, int O,
-                                              int K, int tok_per_split, float *__restrict__ part) {
+// The workgroups of the projections lie one after the other, all tiles of a split together.
+__global__ __launch_bounds__(256) void lin_tn(LinGrad a, const bf16_t *__restrict__ X, int M, int K) {
   using G = TileGeom<128>;
   __shared__ __align__(16) bf16_t sy[2][G::ROW_ELEMS], sx[2][G::ROW_ELEMS];
   const int n_kt = K / 128;
-  const int ot = blockIdx.x / n_kt, kt = blockIdx.x % n_kt, split = blockIdx.y;
+  int wg = blockIdx.x, d = 0;
+  while (d < 2 && wg >= a.O[d] / 128 * n_kt * a.splits[d]) wg -= a.O[d] / 128 * n_kt * a.splits[d], ++d;
+  const bf16_t *__restrict__ dY = a.dY[d];
+  const int O = a.O[d], tok_per_split = a.tok_per_split[d], tiles = O / 128 * n_kt;
+  const int split = wg / tiles, ot = wg % tiles / n_kt, kt = wg % n_kt;
   const int o0 = ot * 128, c0 = kt * 128;
   const int t_begin = split * tok_per_split, t_end = min(M, t_begin + tok_per_split);
   const int tid = threadIdx.x, wid = tid >> 6, lane = tid & 63, n = lane & 15, quad = lane >> 4;
@@ -193,19 +224,19 @@ __global__ __launch_bounds__(256) void lin_tn(const bf16_t *__restrict__ dY, con
   for (int t0 = t_begin, buf = 0; t0 < t_end; t0 += 32, buf ^= 1) {
     const bool more = t0 + 32 < t_end;
     if (more) fetch(t0 + 32);
-    bf16x8 a[4], b[4];
+    bf16x8 y[4], x[4];
 #pragma unroll
-    for (int oi = 0; oi < 4; ++oi) a[oi] = lds_tr_operand<128>(sy[buf], 4 * wo + oi);
+    for (int oi = 0; oi < 4; ++oi) y[oi] = lds_tr_operand<128>(sy[buf], 4 * wo + oi);
 #pragma unroll
-    for (int ki = 0; ki < 4; ++ki) b[ki] = lds_tr_operand<128>(sx[buf], 4 * wk + ki);
+    for (int ki = 0; ki < 4; ++ki) x[ki] = lds_tr_operand<128>(sx[buf], 4 * wk + ki);
 #pragma unroll
     for (int oi = 0; oi < 4; ++oi)
 #pragma unroll
-      for (int ki = 0; ki < 4; ++ki) acc[oi][ki] = mfma16(a[oi], b[ki], acc[oi][ki]);
+      for (int ki = 0; ki < 4; ++ki) acc[oi][ki] = mfma16(y[oi], x[ki], acc[oi][ki]);
     if (more) stash(buf ^ 1);
     __syncthreads();
   }
-  float *dst = part + (size_t)split * O * K;
+  float *dst = a.part[d] + (size_t)split * O * K;
 #pragma unroll
   for (int oi = 0; oi < 4; ++oi)
 #pragma unroll
@@ -215,21 +246,38 @@ __global__ __launch_bounds__(256) void lin_tn(const bf16_t *__restrict__ dY, con
         dst[(size_t)(o0 + 64 * wo + 16 * oi + 4 * quad + i) * K + c0 + 64 * wk + 16 * ki + n] = acc[oi][ki][i];
 }
 
-// out[j] = sum_s part[s][j], s ascending
-__global__ void lin_sum_parts(const float *__restrict__ part, int n_parts, size_t len, float *__restrict__ out) {
-  const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+// dw[j] = sum_s part[s][j], s ascending; blockIdx.y picks the projection.  A chain of loads that wait for each other without
+// the unrolling: the
+// four weight gradients of a layer at 10.7 k tokens 48 us in four launches of one load at a time, 32 in two (query, key and
+// value together) of eight.
+__global__ void lin_sum_parts(LinGrad a, int K) {
+  const int d = blockIdx.y, n_parts = a.splits[d];
+  const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x, len = (size_t)a.O[d] * K;
   if (j >= len) return;
+  const float *__restrict__ part = a.part[d] + j;
   float s = 0.f;
-  for (int p = 0; p < n_parts; ++p) s += part[(size_t)p * len + j];
-  out[j] = s;
+#pragma unroll 8
+  for (int p = 0; p < n_parts; ++p) s += part[(size_t)p * len];
+  a.dw[d][j] = s;
+}
+
+// out[j] = 0
+__global__ void lin_zero(float *__restrict__ out, size_t len) {
+  const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j < len) out[j] = 0.f;
 }
 
 // Column sums of dY (the bias gradient) in two steps, both with a fixed order of additions.
 // Step 1: part[chunk][o] = sum of dY[t][o] over the chunk's COLSUM_CHUNK tokens; a thread owns 8 columns and every
 // `phases`-th token, the phases are added in order through LDS.  O % 8 == 0, O / 8 <= 256 or a multiple of 256.
+// blockIdx.y picks the projection, of those with a bias.
 constexpr int COLSUM_CHUNK = 64;
-__global__ __launch_bounds__(256) void lin_colsum(const bf16_t *__restrict__ dY, int M, int O, float *__restrict__ part) {
+__global__ __launch_bounds__(256) void lin_colsum(LinGrad a, int M) {
   __shared__ float red[2048];
+  if (!a.dbias[blockIdx.y]) return;
+  const bf16_t *__restrict__ dY = a.dY[blockIdx.y];
+  float *__restrict__ part = a.bpart[blockIdx.y];
+  const int O = a.O[blockIdx.y];
   const int cols8 = O / 8;
   const int phases = cols8 >= 256 ? 1 : 256 / cols8;
   const int t_begin = blockIdx.x * COLSUM_CHUNK, t_end = min(M, t_begin + COLSUM_CHUNK);
@@ -261,8 +309,11 @@ __global__ __launch_bounds__(256) void lin_colsum(const bf16_t *__restrict__ dY,
 }
 // Step 2: out[o] = sum over the parts; a workgroup owns 8 columns, 32 thread rows each add every 32nd part, then the
 // rows are added in order.
-__global__ __launch_bounds__(256) void lin_colsum_finish(const float *__restrict__ part, int n_parts, int O, float *__restrict__ out) {
+__global__ __launch_bounds__(256) void lin_colsum_finish(LinGrad a, int n_parts) {
   __shared__ float red[32][8];
+  if (!a.dbias[blockIdx.y]) return;
+  const float *__restrict__ part = a.bpart[blockIdx.y];
+  const int O = a.O[blockIdx.y];
   const int col = blockIdx.x * 8 + (threadIdx.x & 7), row = threadIdx.x >> 3;
   float s = 0.f;
   if (col < O)
@@ -273,7 +324,7 @@ __global__ __launch_bounds__(256) void lin_colsum_finish(const float *__restrict
     float t = 0.f;
 #pragma unroll
     for (int r = 0; r < 32; ++r) t += red[r][threadIdx.x & 7];
-    out[col] = t;
+    a.dbias[blockIdx.y][col] = t;
   }
 }
 
@@ -305,47 +356,108 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
 
 }  // namespace
 
-int lin_nt_multi(int n_src, const void *const *X, const void *const *W, const int *K, const void *bias, int M, int O,
-                 void *Y, hipStream_t s) {
+namespace {
+
+int launch_nt(const LinSrc &src, const LinDst &dst, int M, hipStream_t s) {
   constexpr int WF = 2, WT = 2, CF = 4, CT = 4, BF = 16 * CF * WF, BT = 16 * CT * WT;
   const size_t lds = (size_t)2 * (BF + BT) * LIN_KC * sizeof(bf16_t);  // two stages of weights and tokens
   static const hipError_t attr =
       hipFuncSetAttribute((const void *)lin_nt<WF, WT, CF, CT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (attr != hipSuccess) return SSA_ERR_HIP;
-  LinSrc src{};
-  for (int i = 0; i < 3; ++i) {
-    src.X[i] = i < n_src ? (const bf16_t *)X[i] : nullptr;
-    src.W[i] = i < n_src ? (const bf16_t *)W[i] : nullptr;
-    src.K[i] = i < n_src ? K[i] : 0;
-  }
-  const int n_ot = O / BF, n_tt = (M + BT - 1) / BT;
+  const int n_ot = (dst.O[0] + dst.O[1] + dst.O[2]) / BF, n_tt = (M + BT - 1) / BT;
   const unsigned grid = (unsigned)(8 * ((n_tt + 7) / 8) * n_ot);
-  lin_nt<WF, WT, CF, CT><<<grid, 64 * WF * WT, lds, s>>>(src, (const bf16_t *)bias, M, O, (bf16_t *)Y);
+  lin_nt<WF, WT, CF, CT><<<grid, 64 * WF * WT, lds, s>>>(src, dst, M);
   return SSA_OK;
 }
 
-void lin_transpose_w(const void *w, int d_out, int d_in, void *wt, hipStream_t s) {
-  lin_transpose<<<dim3(d_in / 32, d_out / 32), 256, 0, s>>>((const bf16_t *)w, d_out, d_in, (bf16_t *)wt);
+}  // namespace
+
+int lin_nt_multi(int n_src, const void *const *X, const void *const *W, const int *K, const void *bias, int M, int O,
+                 void *Y, hipStream_t s) {
+  LinSrc src{};
+  for (int i = 0; i < n_src; ++i) {
+    src.X[i] = (const bf16_t *)X[i];
+    src.W[i] = (const bf16_t *)W[i];
+    src.K[i] = K[i];
+  }
+  LinDst dst{};
+  dst.bias[0] = (const bf16_t *)bias;
+  dst.Y[0] = (bf16_t *)Y;
+  dst.O[0] = O;
+  return launch_nt(src, dst, M, s);
+}
+
+int lin_forward_multi(int n_dst, int M, int K, const void *X, const void *const *W, const void *const *bias, const int *O,
+                      void *const *Y, hipStream_t s) {
+  for (int i = 0; i < n_dst; ++i) {
+    const int rc = lin_check(M, K, O[i]);
+    if (rc != SSA_OK) return rc;
+  }
+  if (M == 0) return SSA_OK;
+  LinSrc src{};
+  LinDst dst{};
+  src.X[0] = (const bf16_t *)X;
+  src.K[0] = K;
+  for (int i = 0; i < n_dst; ++i) {
+    if (!X || !W[i] || !Y[i]) return SSA_ERR_NULL;
+    if (!aligned16(X, W[i], bias[i], Y[i])) return SSA_ERR_ALIGNMENT;
+    src.W[i] = (const bf16_t *)W[i];
+    dst.bias[i] = (const bf16_t *)bias[i];
+    dst.Y[i] = (bf16_t *)Y[i];
+    dst.O[i] = O[i];
+  }
+  ProfScope ps(PROF_LINEAR_FWD, s);
+  const int rc = launch_nt(src, dst, M, s);
+  if (rc != SSA_OK) return rc;
+  SSA_HIP_TRY(hipGetLastError());
+  return SSA_OK;
+}
+
+void lin_transpose_w(int n, const void *const *w, const int *d_out, int d_in, void *const *wt, hipStream_t s) {
+  LinTrans a{};
+  int o_max = 0;
+  for (int i = 0; i < n; ++i) {
+    a.W[i] = (const bf16_t *)w[i];
+    a.Wt[i] = (bf16_t *)wt[i];
+    a.O[i] = d_out[i];
+    o_max = d_out[i] > o_max ? d_out[i] : o_max;
+  }
+  lin_transpose<<<dim3(d_in / 32, o_max / 32, n), 256, 0, s>>>(a, d_in);
 }
 
 size_t lin_dw_workspace(int M, int d_in, int d_out) {
   const LinPlan p = lin_plan(M, d_in, d_out);
-  return p.total - p.part;
+  return align_up(p.total - p.part, 256);
 }
 
-// dw [d_out][d_in] = dy^T x, dbias (optional) = column sums of dy; ws holds lin_dw_workspace() bytes, 256-byte aligned
-int lin_dw(int M, int d_in, int d_out, const void *x, const void *dy, float *dw, float *dbias, void *ws, hipStream_t s) {
-  const LinPlan pl = lin_plan(M, d_in, d_out);
-  float *part = (float *)ws, *bpart = (float *)((char *)ws + (pl.bpart - pl.part));
-  lin_tn<<<dim3((d_out / 128) * (d_in / 128), pl.splits), 256, 0, s>>>((const bf16_t *)dy, (const bf16_t *)x, M, d_out, d_in,
-                                                                     pl.tok_per_split, part);
-  const size_t len = (size_t)d_in * d_out;
-  lin_sum_parts<<<(unsigned)((len + 255) / 256), 256, 0, s>>>(part, pl.splits, len, dw);
-  if (dbias) {
-    lin_colsum<<<pl.bias_parts, 256, 0, s>>>((const bf16_t *)dy, M, d_out, bpart);
-    lin_colsum_finish<<<(d_out + 7) / 8, 256, 0, s>>>(bpart, pl.bias_parts, d_out, dbias);
+void lin_dw(int n, int M, int d_in, const int *d_out, const void *x, const void *const *dy, float *const *dw,
+            float *const *dbias, void *ws, hipStream_t s) {
+  LinGrad a{};
+  char *at = (char *)ws;
+  unsigned grid = 0, bias_parts = 1;
+  int o_max = 0, any_bias = 0;
+  for (int i = 0; i < n; ++i) {
+    const LinPlan pl = lin_plan(M, d_in, d_out[i]);
+    a.dY[i] = (const bf16_t *)dy[i];
+    a.part[i] = (float *)at;
+    a.bpart[i] = (float *)(at + (pl.bpart - pl.part));
+    a.dw[i] = dw[i];
+    a.dbias[i] = dbias[i];
+    a.O[i] = d_out[i];
+    a.splits[i] = pl.splits;
+    a.tok_per_split[i] = pl.tok_per_split;
+    at += lin_dw_workspace(M, d_in, d_out[i]);
+    grid += (unsigned)(d_out[i] / 128 * (d_in / 128) * pl.splits);
+    bias_parts = (unsigned)pl.bias_parts;
+    o_max = d_out[i] > o_max ? d_out[i] : o_max;
+    any_bias |= dbias[i] != nullptr;
   }
-  return SSA_OK;
+  lin_tn<<<grid, 256, 0, s>>>(a, (const bf16_t *)x, M, d_in);
+  lin_sum_parts<<<dim3((unsigned)((size_t)o_max * d_in / 256), n), 256, 0, s>>>(a, d_in);
+  if (any_bias) {
+    lin_colsum<<<dim3(bias_parts, n), 256, 0, s>>>(a, M);
+    lin_colsum_finish<<<dim3((o_max + 7) / 8, n), 256, 0, s>>>(a, (int)bias_parts);
+  }
 }
 
 int lin_check(int n_tokens, int d_in, int d_out) {
@@ -362,17 +474,7 @@ extern "C" size_t ssa_linear_workspace_bytes(int32_t n_tokens, int32_t d_in, int
 
 extern "C" int ssa_linear_forward(int32_t n_tokens, int32_t d_in, int32_t d_out, const void *x, const void *w,
                                   const void *bias, void *y, void *stream) {
-  const int rc = lin_check(n_tokens, d_in, d_out);
-  if (rc != SSA_OK) return rc;
-  if (n_tokens == 0) return SSA_OK;
-  if (!x || !w || !y) return SSA_ERR_NULL;
-  if (!aligned16(x, w, bias, y)) return SSA_ERR_ALIGNMENT;
-  hipStream_t s = (hipStream_t)stream;
-  ProfScope ps(PROF_LINEAR_FWD, s);
-  const int lrc = lin_nt_multi(1, &x, &w, &d_in, bias, n_tokens, d_out, y, s);
-  if (lrc != SSA_OK) return lrc;
-  SSA_HIP_TRY(hipGetLastError());
-  return SSA_OK;
+  return lin_forward_multi(1, n_tokens, d_in, x, &w, &bias, &d_out, &y, (hipStream_t)stream);
 }
 
 extern "C" int ssa_linear_backward(int32_t n_tokens, int32_t d_in, int32_t d_out, const void *x, const void *w,
@@ -383,9 +485,9 @@ extern "C" int ssa_linear_backward(int32_t n_tokens, int32_t d_in, int32_t d_out
   if (!dw) return SSA_ERR_NULL;
   hipStream_t s = (hipStream_t)stream;
   if (n_tokens == 0) {  // no tokens: the parameter gradients are zero
-    const size_t len = (size_t)d_in * d_out;  // a sum over zero partials writes zeros
-    lin_sum_parts<<<(unsigned)((len + 255) / 256), 256, 0, s>>>(nullptr, 0, len, dw);
-    if (dbias) lin_sum_parts<<<(d_out + 255) / 256, 256, 0, s>>>(nullptr, 0, (size_t)d_out, dbias);
+    const size_t len = (size_t)d_in * d_out;
+    lin_zero<<<(unsigned)((len + 255) / 256), 256, 0, s>>>(dw, len);
+    if (dbias) lin_zero<<<(d_out + 255) / 256, 256, 0, s>>>(dbias, (size_t)d_out);
     SSA_HIP_TRY(hipGetLastError());
     return SSA_OK;
   }
@@ -396,12 +498,12 @@ extern "C" int ssa_linear_backward(int32_t n_tokens, int32_t d_in, int32_t d_out
   char *ws = (char *)align_up((size_t)ws_, 256);
   ProfScope ps(PROF_LINEAR_BWD, s);
   if (dx) {
-    const void *wt = ws + pl.wt;
-    lin_transpose_w(w, d_out, d_in, ws + pl.wt, s);
-    const int lrc = lin_nt_multi(1, &dy, &wt, &d_out, nullptr, n_tokens, d_in, dx, s);
+    void *wt = ws + pl.wt;
+    lin_transpose_w(1, &w, &d_out, d_in, &wt, s);
+    const int lrc = lin_nt_multi(1, &dy, (const void *const *)&wt, &d_out, nullptr, n_tokens, d_in, dx, s);
     if (lrc != SSA_OK) return lrc;
   }
-  lin_dw(n_tokens, d_in, d_out, x, dy, dw, dbias, ws + pl.part, s);
+  lin_dw(1, n_tokens, d_in, &d_out, x, &dy, &dw, &dbias, ws + pl.part, s);
   SSA_HIP_TRY(hipGetLastError());
   return SSA_OK;
 }

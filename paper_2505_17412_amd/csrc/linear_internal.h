@@ -10,10 +10,16 @@ int lin_check(int n_tokens, int d_in, int d_out);
 int lin_nt_multi(int n_src, const void *const *X, const void *const *W, const int *K, const void *bias, int M, int O,
                  void *Y, hipStream_t s);
 
-// wt [d_in][d_out] = w [d_out][d_in]^T
-void lin_transpose_w(const void *w, int d_out, int d_in, void *wt, hipStream_t s);
+// Y_i [M][O_i] = X [M][K] W_i[O_i][K]^T (+ bias_i, may be null), i < n_dst <= 3, in one launch; checks and errors of
+// ssa_linear_forward for each of them
+int lin_forward_multi(int n_dst, int M, int K, const void *X, const void *const *W, const void *const *bias, const int *O,
+                      void *const *Y, hipStream_t s);
 
-// dw [d_out][d_in] (fp32) = dy^T x, dbias [d_out] (fp32, optional) = column sums of dy; ws: lin_dw_workspace() bytes,
-// 256-byte aligned
+// wt_i [d_in][d_out_i] = w_i [d_out_i][d_in]^T, i < n <= 3
+void lin_transpose_w(int n, const void *const *w, const int *d_out, int d_in, void *const *wt, hipStream_t s);
+
+// dw_i [d_out_i][d_in] (fp32) = dy_i^T x, dbias_i [d_out_i] (fp32, may be null) = column sums of dy_i, i < n <= 3; ws: the
+// sum of lin_dw_workspace() over them, 256-byte aligned
 size_t lin_dw_workspace(int M, int d_in, int d_out);
-int lin_dw(int M, int d_in, int d_out, const void *x, const void *dy, float *dw, float *dbias, void *ws, hipStream_t s);
+void lin_dw(int n, int M, int d_in, const int *d_out, const void *x, const void *const *dy, float *const *dw,
+            float *const *dbias, void *ws, hipStream_t s);
