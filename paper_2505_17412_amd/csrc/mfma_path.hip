@@ -34,10 +34,12 @@ __device__ inline void zero_tail(const Tails &ts, int wg) {
   for (size_t i = t.begin + (size_t)(wg % TAIL_WGS) * blockDim.x + threadIdx.x; i < t.end; i += (size_t)TAIL_WGS * blockDim.x) t.p[i] = 0;
 }
 
-struct PrepOut { bf16_t *Ks, *Vs, *Kc, *Vc; };
+// kc_in, vc_in: block-level keys and values of the caller that take the place of the means, or null
+struct PrepOut { bf16_t *Ks, *Vs, *Kc, *Vc; const bf16_t *kc_in, *vc_in; };
 
 // One workgroup per compression block: gathers its tokens' K,V rows into sorted order and writes the block mean
-// (eq. (5), mean pool over the active tokens).
+// (eq. (5), mean pool over the active tokens), or the caller's rows in its place (as two copies behind the launch those cost
+// 5 us each, in both directions).
 __global__ void m_prep(const bf16_t *__restrict__ K, const bf16_t *__restrict__ V, const int32_t *__restrict__ perm,
                        const int32_t *__restrict__ cmp_start, int Hkv, int D, int Nc, PrepOut o, Tails ts) {
   const int c = blockIdx.x, row = Hkv * D;
@@ -55,8 +57,9 @@ __global__ void m_prep(const bf16_t *__restrict__ K, const bf16_t *__restrict__ 
       sv += bf16_to_f32(vv);
     }
     const bf16_t kc = f32_to_bf16(sk * inv), vc = f32_to_bf16(sv * inv);
-    o.Kc[(size_t)c * row + f] = kc;
-    o.Vc[(size_t)c * row + f] = vc;
+    const size_t at = (size_t)c * row + f;
+    o.Kc[at] = o.kc_in ? o.kc_in[at] : kc;
+    o.Vc[at] = o.vc_in ? o.vc_in[at] : vc;
   }
 }
 
@@ -95,7 +98,9 @@ __global__ __launch_bounds__(128) void m_prep8(const bf16_t *__restrict__ K, con
       for (int gi = 0; gi < ngrp; ++gi) t += part[arr][gi * R8 + sg][j];
       out[j] = (__bf16)(t * inv);
     }
-    *reinterpret_cast<bf16x8 *>((arr == 0 ? o.Kc : o.Vc) + ((size_t)c * R8 + sg) * 8) = out;
+    const size_t at = ((size_t)c * R8 + sg) * 8;
+    const bf16_t *given = arr == 0 ? o.kc_in : o.vc_in;
+    *reinterpret_cast<bf16x8 *>((arr == 0 ? o.Kc : o.Vc) + at) = given ? ld8(given + at) : out;
   }
 }
 
@@ -146,15 +151,6 @@ int run_prep(const ssa_ctx &c, const void *k, const void *v, const PrepOut &o, u
   else
     m_prep<<<grid, 128, 0, c.stream>>>((const bf16_t *)k, (const bf16_t *)v, c.blk->perm, c.blk->cmp_start, c.Hkv, c.d, c.blk->Nc, o, ts);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
-}
-
-// Caller-supplied block-level keys/values take the place of the mean-pooled rows (the zero padding behind them stays).
-int override_pooled(const ssa_ctx &c, const PrepOut &o) {
-  if (!c.kc_in) return SSA_OK;
-  const size_t bytes = (size_t)c.blk->Nc * c.Hkv * c.d * sizeof(bf16_t);
-  SSA_HIP_TRY(hipMemcpyAsync(o.Kc, c.kc_in, bytes, hipMemcpyDeviceToDevice, c.stream));
-  SSA_HIP_TRY(hipMemcpyAsync(o.Vc, c.vc_in, bytes, hipMemcpyDeviceToDevice, c.stream));
-  return SSA_OK;
 }
 
 struct BwdPlan {
@@ -249,13 +245,12 @@ int mfma_backward(const ssa_ctx &c, const void *q, const void *k, const void *v,
   if (ws_bytes < p.total) return SSA_ERR_WORKSPACE;
   char *ws = (char *)ws_;
   PrepOut o{};
+  o.kc_in = (const bf16_t *)c.kc_in; o.vc_in = (const bf16_t *)c.vc_in;
   o.Ks = (bf16_t *)(ws + p.ks); o.Vs = (bf16_t *)(ws + p.vs);
   o.Kc = (bf16_t *)(ws + p.kc); o.Vc = (bf16_t *)(ws + p.vc);
   BwdBuffers w{};
   w.sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, bc_chunk_len(c.N, c.Hkv, c.T));
   int rc = run_prep(c, k, v, o, w.sel.ticket);
-  if (rc != SSA_OK) return rc;
-  rc = override_pooled(c, o);
   if (rc != SSA_OK) return rc;
   MfmaView view = make_view(c);
   view.Ks = o.Ks; view.Vs = o.Vs; view.Kc = o.Kc; view.Vc = o.Vc;
@@ -277,11 +272,10 @@ int mfma_forward(const ssa_ctx &c, const void *q, const void *k, const void *v, 
   if (ws_bytes < p.total) return SSA_ERR_WORKSPACE;
   char *ws = (char *)ws_;
   PrepOut o{};
+  o.kc_in = (const bf16_t *)c.kc_in; o.vc_in = (const bf16_t *)c.vc_in;
   o.Ks = (bf16_t *)(ws + p.ks); o.Vs = (bf16_t *)(ws + p.vs); o.Kc = (bf16_t *)(ws + p.kc); o.Vc = (bf16_t *)(ws + p.vc);
   const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, 1024, bc_chunk_len(c.N, c.Hkv, c.T));
   int rc = run_prep(c, k, v, o, sel.ticket);
-  if (rc != SSA_OK) return rc;
-  rc = override_pooled(c, o);
   if (rc != SSA_OK) return rc;
   MfmaView view = make_view(c);
   view.Ks = o.Ks; view.Vs = o.Vs; view.Kc = o.Kc; view.Vc = o.Vc;
