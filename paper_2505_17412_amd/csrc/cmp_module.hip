@@ -176,12 +176,14 @@ __global__ __launch_bounds__(256) void c_conv(Pair<ConvSrc> srcs, const int32_t 
 // taken from a copy of the tile's neighbour table in LDS.  Row r of a 16-row MFMA tile stands for LDS row
 // 8*(r >> 2) + 4*a + (r & 3) of its 32-row tile (a = which half), for tokens and for channels alike; the store at the end
 // undoes that numbering.
-// Bound: LDS operand reads (one per two matrix instructions) and their latency; about half of the gathered rows of a surface
-// are zeros.  At 64 tokens the products of an offset are too short to hide a weight loaded behind its last use, so the next
-// offset has registers of its own (200, two wavefronts per SIMD).  At 128 tokens those registers would cost the second
-// wavefront, so a weight is loaded again in place (210; with a second set 283 and one wavefront).  Module forward of one tensor,
-// 128 tokens with a second set -> in place: 20 k tokens 84 -> 83 us, 40 k 147 -> 114, 62 k 164 -> 126, 150 k 379 -> 296; keys and
-// values together at 17 k 148 -> 111, at 10.7 k 88 -> 90.
+// Bound: the chain index -> gathered row -> LDS -> product of an offset, with one or two wavefronts per SIMD to cover it; about half
+// of the gathered rows of a surface are zeros.  At 64 tokens the products of an offset are too short to hide a weight loaded behind
+// its last use, so the next offset's weights have registers of their own, and rows are requested two offsets ahead.  At 128 tokens
+// those registers would cost the second wavefront, so a weight is loaded again in place and rows are one offset ahead.
+// Convolution forward of keys and values, rows one -> two ahead: 7 k tokens (64 per workgroup) 91 -> 72 us; 128 per workgroup
+// 10.7 k 123 -> 115, but 17 k 136 -> 147, 30 k 155 -> 170, 60 k 312 -> 331.  With loads under conditions and one ahead: 7 k 88,
+// 10.7 k 121, 17 k 137, 30 k 162, 60 k 322.  Eight wavefronts that share 128 tokens by halves fetch the weights twice: 140 at
+// 10.7 k, 480 at 60 k.
 template <bool MIRROR, int TOK>
 __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32_t *__restrict__ nbr, int N) {
   constexpr int C = 128, MT = TOK / 16, AI = TOK / 16;  // AI: gathered 16-byte items per thread (TOK x 16 / 256)
@@ -203,47 +205,57 @@ __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32
     if (v >= 0) any_flag[MIRROR ? 26 - o : o] = 1;
   }
   __syncthreads();
+  const uint32_t used = (uint32_t)__ballot(lane < 27 && any_flag[lane < 27 ? lane : 0] != 0);
   f32x4 acc[MT][2];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) acc[mt][0] = acc[mt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // weights of one offset; with 64 tokens those of the next one have registers of their own
+  // weights of one offset; with 64 tokens those of the next one have registers of their own, and so have the rows of another offset
   constexpr bool AHEAD = TOK == 64;
   struct Weights { bf16x8 v[2][C / 32]; };
   Weights wa, wb;
-  bf16x8 ra[AI];
+  struct Rows { bf16x8 v[AI]; uint32_t missing; };
+  Rows ra, rb;
   const int wrow = 32 * wid + 8 * (n >> 2) + (n & 3);  // channel of half 0; half 1 is 4 further
   const bf16_t *Bl = Bw + (size_t)wrow * C + 8 * quad;
   auto fetch_weights = [&](int o, int ks, Weights &w) {
 #pragma unroll
     for (int a = 0; a < 2; ++a) w.v[a][ks] = ld8(Bl + (size_t)o * C * C + 4 * a * C + 32 * ks);
   };
-  auto fetch_rows = [&](int o) {
-    const int oo = MIRROR ? 26 - o : o;
+  // (loads are unconditional, a missing neighbour's from row 0 and an offset past the last from offset 26: behind a branch the
+  // compiler cannot count what is outstanding, and the products would wait for the rows just requested)
+  auto fetch_rows = [&](int o_, Rows &r) {
+    const int o = min(o_, 26), oo = MIRROR ? 26 - o : o;
+    r.missing = 0u;
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
       const int it = threadIdx.x + 256 * i;
       const int src = snbr[(it / 16) * 27 + oo];
-      ra[i] = src >= 0 ? ld8(in + (size_t)src * C + 8 * (it % 16)) : zero8();
+      r.missing |= src < 0 ? 1u << i : 0u;
+      r.v[i] = ld8(in + (uint32_t)(max(src, 0) * C + 8 * (it % 16)));
     }
   };
-  auto next = [&](int o) {
-    while (o < 27 && !any_flag[o]) ++o;
-    return o;
+  auto next = [&](int o) {  // the next offset in use, 27 behind the last
+    const uint32_t later = used & ~((2u << o) - 1u);
+    return later ? __builtin_ctz(later) : 27;
   };
-  // one offset: its rows (in registers) to LDS buffer `buf`, the next offset's operands requested, the products; with cur and
-  // nxt the same registers a weight is loaded again as soon as this offset is done with it
-  auto step = [&](int &o, int buf, Weights &cur, Weights &nxt) {
+  // one offset: its rows (in registers) to LDS buffer `buf`, the rows of the next offset (AHEAD: the one after it) requested in their
+  // place, the next offset's weights requested, the products; with cur and nxt the same registers a weight is loaded again as soon as
+  // this offset is done with it
+  int o = used ? __builtin_ctz(used) : 27, o1 = next(min(o, 27));
+  auto step = [&](int buf, Weights &cur, Weights &nxt, Rows &r) {
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
       const int it = threadIdx.x + 256 * i, row = it / 16;
-      *reinterpret_cast<bf16x8 *>(sa[buf] + (row >> 5) * G::ROW_ELEMS + G::row_off(row & 31, it % 16)) = ra[i];
+      *reinterpret_cast<bf16x8 *>(sa[buf] + (row >> 5) * G::ROW_ELEMS + G::row_off(row & 31, it % 16)) =
+          r.missing >> i & 1u ? zero8() : r.v[i];
     }
     __syncthreads();  // (the other buffer was last read before this barrier)
-    o = next(o + 1);
-    if (AHEAD && o < 27)
+    o = o1;
+    o1 = next(o1);
+    if (AHEAD)
 #pragma unroll
-      for (int ks = 0; ks < C / 32; ++ks) fetch_weights(o, ks, nxt);
-    if (o < 27) fetch_rows(o);
+      for (int ks = 0; ks < C / 32; ++ks) fetch_weights(min(o, 26), ks, nxt);
+    fetch_rows(AHEAD ? o1 : o, r);
 #pragma unroll
     for (int ks = 0; ks < C / 32; ++ks) {
 #pragma unroll
@@ -252,24 +264,22 @@ __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32
         acc[mt][0] = mfma16(av, cur.v[0][ks], acc[mt][0]);
         acc[mt][1] = mfma16(av, cur.v[1][ks], acc[mt][1]);
       }
-      if (!AHEAD) fetch_weights(min(o, 26), ks, nxt);  // (past the last offset: loaded and not used)
+      if (!AHEAD) fetch_weights(min(o, 26), ks, nxt);
     }
   };
-  int o = next(0);
-  if (o < 27) {  // (in the order of a step's requests: the compiler then counts what a step has to wait for)
-    if (!AHEAD) fetch_rows(o);
+  if (o < 27) {
+    fetch_rows(o, ra);
+    if (AHEAD) fetch_rows(o1, rb);
 #pragma unroll
     for (int ks = 0; ks < C / 32; ++ks) fetch_weights(o, ks, wa);
-    if (AHEAD) fetch_rows(o);
-  }
-  if constexpr (AHEAD) {
-    while (o < 27) {
-      step(o, 0, wa, wb);
+    Weights &w1 = AHEAD ? wb : wa;
+    Rows &r1 = AHEAD ? rb : ra;
+    while (true) {
+      step(0, wa, w1, ra);
       if (o >= 27) break;
-      step(o, 1, wb, wa);
+      step(1, w1, wa, r1);
+      if (o >= 27) break;
     }
-  } else {
-    for (int buf = 0; o < 27; buf ^= 1) step(o, buf, wa, wa);
   }
   // lane: column n of half a -> channel 32*wid + 8*(n >> 2) + 4*a + (n & 3); rows 4*quad + i of tile mt -> token
   // pos0 + 32*(mt >> 1) + 8*quad + 4*(mt & 1) + i
@@ -577,9 +587,9 @@ void launch_conv(int C, const Pair<ConvSrc> &src, int n, const int32_t *nbr, int
     case 32: c_conv<32, MIRROR, 4, 2><<<grid, 256, 0, s>>>(src, nbr, N); break;
     case 64: c_conv<64, MIRROR, 4, 4><<<grid, 256, 0, s>>>(src, nbr, N); break;
     case 128:
-      // 128 tokens per workgroup read the weights half as often, 64 fill the chip while 256 workgroups of 64 do not (one module
-      // forward, 64 against 128 tokens: 68 and 84 us at 14 k tokens, 89 and 86 at 17 k, 93 and 89 at 26 k, 171 and 126 at 62 k; of
-      // keys and values 71 and 86 at 8 k, 94 and 91 at 10.7 k)
+      // 128 tokens per workgroup read the weights half as often, 64 fill the chip while 256 workgroups of 64 do not (keys and
+      // values, 64 against 128 tokens: 123 and 123 us at 10.7 k, 162 and 136 at 17 k; before rows were two offsets ahead 71 and
+      // 86 for the module at 8 k)
       if ((size_t)N * n > 16384) c_conv128<MIRROR, 128><<<dim3((unsigned)((N + 127) / 128), 1, n), 256, 0, s>>>(src, nbr, N);
       else c_conv128<MIRROR, 64><<<dim3((unsigned)((N + 63) / 64), 1, n), 256, 0, s>>>(src, nbr, N);
       break;

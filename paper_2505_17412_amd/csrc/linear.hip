@@ -66,24 +66,30 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
 #pragma unroll
     for (int ti = 0; ti < CT; ++ti) acc[ci][ti] = f32x4{0.f, 0.f, 0.f, 0.f};
   // Two chunks are in flight in registers (A: the next chunk, B: the one after), so a global load has two loop trips
-  // to arrive; the loop is unrolled by two to alternate the register sets.
+  // to arrive; the loop is unrolled by two to alternate the register sets.  Every load is unconditional, with clamped indices
+  // (tokens past the end are not stored, chunks past the end not used): behind a branch the compiler cannot count what is
+  // outstanding and waits for the chunk just requested as well.  The launches of a
+  // layer's step (1024 features): 10.7 k tokens 182 -> 174 us, 46 k 627 -> 600.  (256 tokens per workgroup of four or eight wavefronts: 46 k 667, 660.)
   bf16x8 rwA[IW], rxA[IX], rwB[IW], rxB[IX];
   const int K = src.K[0] + src.K[1] + src.K[2];  // unused pairs have K = 0
-  auto fetch = [&](int kf, bf16x8 (&rw)[IW], bf16x8 (&rx)[IX]) {
+  int xrow[IX];
+#pragma unroll
+  for (int i = 0; i < IX; ++i) xrow[i] = min((tid + NTHR * i) >> 3, M - 1 - m0);
+  auto fetch = [&](int kf_, bf16x8 (&rw)[IW], bf16x8 (&rx)[IX]) {
+    const int kf = min(kf_, K - LIN_KC);
     // which pair the flat contraction index kf falls into (every K_i is a multiple of 128, so a chunk never straddles)
     const int p = kf < src.K[0] ? 0 : (kf < src.K[0] + src.K[1] ? 1 : 2);
-    const int k0 = kf - (p > 0 ? src.K[0] : 0) - (p > 1 ? src.K[1] : 0), Kp = src.K[p];
-    const bf16_t *X = src.X[p], *W = src.W[p + d];  // (several pairs: d = 0; several outputs: p = 0)
+    const int k0 = kf - (p > 0 ? src.K[0] : 0) - (p > 1 ? src.K[1] : 0), Kp = p == 0 ? src.K[0] : p == 1 ? src.K[1] : src.K[2];
+    const int q = p + d;  // (several pairs: d = 0; several outputs: p = 0)
+    const bf16_t *X = (p == 0 ? src.X[0] : p == 1 ? src.X[1] : src.X[2]) + (size_t)m0 * Kp + k0;
+    const bf16_t *W = (q == 0 ? src.W[0] : q == 1 ? src.W[1] : src.W[2]) + (size_t)o0 * Kp + k0;
 #pragma unroll
     for (int i = 0; i < IW; ++i) {
       const int it = tid + NTHR * i, row = it >> 3, seg = it & 7;
-      rw[i] = ld8(W + (size_t)(o0 + row) * Kp + k0 + 8 * seg);
+      rw[i] = ld8(W + (uint32_t)(row * Kp + 8 * seg));
     }
 #pragma unroll
-    for (int i = 0; i < IX; ++i) {
-      const int it = tid + NTHR * i, row = it >> 3, seg = it & 7, t = m0 + row;
-      rx[i] = t < M ? ld8(X + (size_t)t * Kp + k0 + 8 * seg) : zero8();
-    }
+    for (int i = 0; i < IX; ++i) rx[i] = ld8(X + (uint32_t)(xrow[i] * Kp + 8 * (tid & 7)));
   };
   auto stash = [&](int buf, const bf16x8 (&rw)[IW], const bf16x8 (&rx)[IX]) {
 #pragma unroll
@@ -119,11 +125,11 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
   __syncthreads();
   for (int k0 = 0; k0 < K; k0 += 2 * LIN_KC) {
     // stage 0 holds chunk k0, registers B chunk k0 + 64
-    if (k0 + 2 * LIN_KC < K) fetch(k0 + 2 * LIN_KC, rwA, rxA);
+    fetch(k0 + 2 * LIN_KC, rwA, rxA);
     compute(0);
     stash(1, rwB, rxB);  // stage 1 was last read before the previous barrier
     __syncthreads();
-    if (k0 + 3 * LIN_KC < K) fetch(k0 + 3 * LIN_KC, rwB, rxB);
+    fetch(k0 + 3 * LIN_KC, rwB, rxB);
     compute(1);
     if (k0 + 2 * LIN_KC < K) stash(0, rwA, rxA);
     __syncthreads();
