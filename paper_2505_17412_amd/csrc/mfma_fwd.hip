@@ -119,10 +119,13 @@ constexpr float SCORE_FIX = 134217728.0f;  // 2^27: a row's scores sum to h_s <=
 
 // LDS plan of the compression kernel (bytes): two stages of two tiles | repeat flag, padding | first and last tile's scores | lse per query row | per token its
 // first pooled key, the one behind its last and the first score of its item | scores [TW][s_max] | top-k marks [NW][words]
+// Blocks of an item whose scores a wavefront holds in registers for the top-k search; more are searched in T rounds over LDS.  With
+// 1024 here: one sequence of 72k tokens (1125 blocks) 5090 us for 3320 now, 131k (2048) 26900 for 11600.
+constexpr int TOPK_IN_REGISTERS = 4096;
 template <int D>
 __host__ __device__ inline size_t cmp_lds_bytes(int nw, int hs, int s_max) {
   const int tw = 32 * nw / hs;
-  return (size_t)4 * T32<D, true>::BYTES + 16 + 256 + ((size_t)32 * nw + 3 * tw + (size_t)tw * s_max + (s_max > 1024 ? nw * ((s_max + 31) / 32) : 0)) * 4;
+  return (size_t)4 * T32<D, true>::BYTES + 16 + 256 + ((size_t)32 * nw + 3 * tw + (size_t)tw * s_max + (s_max > TOPK_IN_REGISTERS ? nw * ((s_max + 31) / 32) : 0)) * 4;
 }
 
 // Second walk of the compression kernel: eq. (6) scores with the normaliser known, for HS heads per KV head, over steps of two
@@ -198,7 +201,7 @@ __device__ inline void score_walk(const FwdArgs &a, const bf16x8 (&qop)[D / 16],
 // before); 65k tokens in sequences 880 -> 830; 11k tokens 94 -> 79; 2k tokens, 32 heads of 32: 19.6 -> 14; 153k tokens, 3884 pooled
 // keys, heads of 128: 11.5 -> 9.1 ms.
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 3 : 2))) void m_cmp_fwd(FwdArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 && NW < 8 ? 3 : 2))) void m_cmp_fwd(FwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   using T = T32<D, true>;
   unsigned char *stage0 = smem;
@@ -263,6 +266,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
     else if (s_max <= 256) topk_wave_bits<4>(Sr, nb, a.v.T, b0, row);
     else if (s_max <= 512) topk_wave_bits<8>(Sr, nb, a.v.T, b0, row);
     else if (s_max <= 1024) topk_wave_bits<16>(Sr, nb, a.v.T, b0, row);
+    else if (s_max <= 2048) topk_wave_bits<32>(Sr, nb, a.v.T, b0, row);
+    else if (s_max <= TOPK_IN_REGISTERS) topk_wave_bits<64>(Sr, nb, a.v.T, b0, row);
     else topk_wave_u32(Sr, nb, a.v.T, b0, row, S + (size_t)TW * s_max + (size_t)wid * ((s_max + 31) >> 5));
   }
 }
@@ -292,11 +297,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32
   finish<D>(a, st, refs, have_ref, 2, query_col(a.v, wg_pos0, g));
 }
 
-// Wavefronts per workgroup of the compression kernel: four, or two where the scores of twice the tokens would leave a compute unit
-// one workgroup.  With two everywhere: 62k tokens 1290 -> 1527 us, 11k 79 -> 85 (each stages the pooled keys for half the columns).
-constexpr size_t CMP_LDS_TWO = 80 * 1024;
+// Wavefronts per workgroup of the compression kernel: what keeps most of them on a compute unit beside the score rows (four where
+// that is equal).  Two everywhere: 62k tokens 1290 -> 1527 us, 11k 79 -> 85 (each stages the pooled keys for half the columns).  One
+// sequence of 65k tokens, 1024 selection blocks: 2320 us by two (six on a compute unit), 1810 by eight; the 16-column kernel, with
+// half the score rows per wavefront and twelve of them, took 1620.
+constexpr size_t CMP_LDS_CU = 160 * 1024, CMP_LDS_WG = 150 * 1024;
 template <int D>
-int cmp_waves(int hs, int s_max) { return cmp_lds_bytes<D>(4, hs, s_max) <= CMP_LDS_TWO ? 4 : 2; }
+int cmp_waves(int hs, int s_max) {
+  constexpr int by_registers = D <= 64 ? 12 : 8;
+  int best = 2, most = 0;
+  for (const int nw : {4, 8, 2}) {
+    const size_t lds = cmp_lds_bytes<D>(nw, hs, s_max);
+    if (lds > CMP_LDS_WG) continue;
+    const int by_lds = (int)(CMP_LDS_CU / lds) * nw, waves = by_lds < by_registers / nw * nw ? by_lds : by_registers / nw * nw;
+    if (waves > most) {
+      most = waves;
+      best = nw;
+    }
+  }
+  return best;
+}
 
 template <int D, int NW>
 void launch_cmp(const FwdArgs &a, hipStream_t s) {
@@ -310,7 +330,9 @@ template <int D>
 int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, const SelIndex &sel, const SlcPartials &part, hipStream_t s) {
   {
     ProfScope ps(PROF_CMP_FWD, s);
-    if (cmp_waves<D>(a.v.hs, a.v.s_max) == 4) launch_cmp<D, 4>(a, s);
+    const int nw = cmp_waves<D>(a.v.hs, a.v.s_max);
+    if (nw == 4) launch_cmp<D, 4>(a, s);
+    else if (nw == 8) launch_cmp<D, 8>(a, s);
     else launch_cmp<D, 2>(a, s);
   }
   {

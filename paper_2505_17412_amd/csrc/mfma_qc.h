@@ -182,10 +182,31 @@ __device__ inline void topk_wave_bits(const uint32_t *S, int n, int T, int base,
       const uint32_t cand = thr | (1u << b);
       int cnt = 0;
 #pragma unroll
-      for (int r = 0; r < R; ++r) cnt += __popcll(__ballot(val[r] >= cand));
+      for (int r = 0; r < R; ++r) {
+        cnt += __popcll(__ballot(val[r] >= cand));
+        if (R > 16 && (r & 7) == 7) __builtin_amdgcn_sched_barrier(0);  // (more masks at a time spill)
+      }
       if (cnt >= Tn) thr = cand;
       if (cnt == Tn) break;
     }
+  }
+  if constexpr (R > 16) {  // (from LDS again, in loops that are not unrolled: see the masks above)
+    int greater = 0, written = 0, eq_before = 0;
+    for (int j0 = 0; j0 < n; j0 += 64) greater += __popcll(__ballot(j0 + lane < n && S[min(j0 + lane, n - 1)] + 1u > thr));
+    const int need = Tn - greater;
+    for (int j0 = 0; j0 < n && written < Tn; j0 += 64) {
+      const int j = j0 + lane;
+      const uint32_t v = j < n ? S[j] + 1u : 0u;
+      const bool eq = Tn > 0 && v == thr;
+      const uint64_t em = __ballot(eq);
+      const bool sel = (Tn > 0 && v > thr) || (eq && eq_before + (int)__popcll(em & lt) < need);
+      eq_before += __popcll(em);
+      const uint64_t sm = __ballot(sel);
+      if (sel) out[written + __popcll(sm & lt)] = base + j;
+      written += __popcll(sm);
+    }
+    for (int w = written + lane; w < T; w += 64) out[w] = -1;
+    return;
   }
   int greater = 0;
 #pragma unroll

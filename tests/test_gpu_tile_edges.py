@@ -2,6 +2,7 @@
 ranges of one key to one key past a segment of 256, a last tile of 1, 31 or 32 keys, 2 to 32 tokens in a wavefront's 32 columns with
 a remainder, token counts that leave the last workgroup or chunk a single token, every head grouping and head dimension.
 Tolerances of the other parity tests."""
+import numpy as np
 import pytest
 
 from paper_2505_17412_amd import inputs
@@ -23,3 +24,14 @@ pytestmark = pytest.mark.gpu
 ])
 def test_tile_edges(seed, lens, hq, hkv, d, l, topk):
     full_parity(inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk))
+
+
+# selection blocks of an item where the compression kernel's top-k takes another form (1024, 2048, 4096) and where the score rows
+# leave room for eight, four or two wavefronts
+@pytest.mark.parametrize("seed,lens,hq,hkv,d", [
+    (911, (8192, 40), 16, 2, 64), (912, (8193,), 16, 2, 64), (913, (40, 16385), 16, 2, 32), (914, (16384,), 8, 1, 64),
+    (915, (32768,), 16, 1, 32), (916, (32777,), 16, 1, 32), (917, (6100,), 8, 1, 128),
+])
+def test_many_selection_blocks(seed, lens, hq, hkv, d):
+    wl = inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=(4, 8, 16), topk=8)
+    full_parity(wl, queries=np.arange(0, wl.n_tokens, 211, dtype=np.int32))
