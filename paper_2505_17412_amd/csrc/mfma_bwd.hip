@@ -129,9 +129,9 @@ __device__ inline void dq_tile(f32x16 (&acc)[D / 32], const f32x16 &s, const f32
   }
 }
 
-// LDS plan of the dQ kernel (bytes): two stages (K rows, V rows) | what the last tile's scores start from
+// LDS plan of the dQ kernel (bytes): two stages (K rows, V rows)
 template <int D>
-__host__ __device__ inline size_t dq_lds_bytes() { return (size_t)4 * T32<D, true>::BYTES + 128; }
+__host__ __device__ inline size_t dq_lds_bytes() { return (size_t)4 * T32<D, true>::BYTES; }
 
 // dQ of the compression branch, then of the (small) window branch, in the sorted token order; the sum is kept in fp32 by
 // sorted position (dQp) for the merge with the selection branch's partials.  Bound as the forward walk (per 32 x 32 scores 384
@@ -143,7 +143,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32
   extern __shared__ __align__(16) unsigned char smem[];
   using T = T32<D, true>;
   unsigned char *stage0 = smem;
-  float *tail = (float *)(smem + 4 * T::BYTES);
   const int h = threadIdx.x >> 5 & 1;
   const int N = a.v.N, TW = 32 * NW / a.v.hs;
   const TileMap tm = xcd_tile_map((N + TW - 1) / TW, a.v.Hkv);
@@ -169,19 +168,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32
     const int r0 = uniform(of_tok[wg_pos0]), r1 = uniform(of_tok[wg_last]), own = of_tok[q.pos];
     const int rs = uniform(start[r0]), re = uniform(start[r1 + 1]), lo = start[own], hi = start[own + 1];
     const float lse2 = a.lse2s[branch * NH + row], gws = a.gws[branch * NH + row] * scale, dls = a.deltas[branch * NH + row] * scale;
-    t32_write_tail(tail, (re - rs - 1) % 32 + 1);
-    __syncthreads();
     t32_pipeline<D, 2, 64 * NW, 32, T32_PF>(T32Src<2>{{K, V}, kstride}, stage0, rs, re, [&](lds_cptr kt, int kb) {
-      f32x16 s, dp = splat16(0.f);
-      if (kb + 32 <= re) s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
-      else s = t32_scores<D, true>(qop, kt, ln, t32_tail(tail));
-      if (r0 != r1) {
-        const int rel = kb - lo;
-        const unsigned len = (unsigned)(hi - lo);
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if ((unsigned)(rel + t32_key(i)) >= len) s[i] = -INFINITY;  // lo <= key < hi as one comparison
-      }
+      f32x16 s = t32_scores<D, true>(qop, kt, ln, splat16(0.f)), dp = splat16(0.f);
+      if (r0 != r1 || kb + 32 > re) t32_only_keys(s, kb, lo, hi);
       dp = t32_scores<D, true>(dop, kt + T::BYTES, ln, dp);
       dq_tile<D>(acc, s, dp, kt, ln, sl2, lse2, gws, dls);
     });

@@ -28,27 +28,21 @@ struct FwdArgs {
 };
 
 // Walks start at a multiple of 8 (which keys are a column's first tile, and with it the reference exponent, is part of what the
-// selection scores are rounded to).  What the scores of the first and the last tile start from: 64 floats of LDS.
+// selection scores are rounded to).
 __device__ inline int walk_begin(int rs) { return rs & ~7; }
-__device__ inline void write_ends(float *ends, int rs, int re) {
-  const int i = threadIdx.x, kb = walk_begin(rs);
-  if (i < 32) ends[i] = kb + i >= rs && kb + i < re ? 0.f : -INFINITY;
-  t32_write_tail(ends + 32, (re - kb - 1) % 32 + 1);
-}
 
 // One whole walk of a workgroup over the key range [rs, re) that every column sees.
 // False if the sums of some column left the range of the floats (again: a word of LDS, 0).  refs: where the references
 // go, in score units (a float per query row of LDS).
 template <int D, int NW, class Sum>
-__device__ inline bool fwd_walk(T32State<D, Sum> &st, float *refs, const bf16x8 (&qop)[D / 16], const T32Src<2> &src, unsigned char *stage0, int *again, const float *ends,
+__device__ inline bool fwd_walk(T32State<D, Sum> &st, float *refs, const bf16x8 (&qop)[D / 16], const T32Src<2> &src, unsigned char *stage0, int *again,
                                 int rs, int re, const typename T32<D, true>::Lanes &ln, float sl2) {
   using T = T32<D, true>;
   t32_clear(st);
   const int first = walk_begin(rs);
   t32_pipeline<D, 2, 64 * NW, 32, T32_PF>(src, stage0, first, re, [&](lds_cptr kt, int kb) {
-    f32x16 s;
-    if (kb != first && kb + 32 <= re) s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
-    else s = t32_scores<D, true>(qop, kt, ln, t32_tail(ends + (kb == first ? 0 : 32)));
+    f32x16 s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
+    if (kb == first || kb + 32 > re) t32_only_keys(s, kb, rs, re);
     if (kb == first) {
       const float raw = t32_column_max(max16(s));
       refs[(threadIdx.x >> 6) * 32 + (threadIdx.x & 31)] = raw;
@@ -68,11 +62,7 @@ __device__ inline void fwd_walk_general(T32State<D, Sum> &st, const bf16x8 (&qop
   t32_clear(st);
   t32_pipeline<D, 2, 64 * NW, 32, T32_PF>(src, stage0, walk_begin(rs), re, [&](lds_cptr kt, int kb) {
     f32x16 s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
-    const int rel = kb - lo;
-    const unsigned len = (unsigned)(hi - lo);
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if ((unsigned)(rel + t32_key(i)) >= len) s[i] = -INFINITY;  // lo <= key < hi as one comparison
+    t32_only_keys(s, kb, lo, hi);
     t32_softmax_running<D, true>(st, s, kt + T32<D, true>::BYTES, ln, sl2);
   });
 }
@@ -80,11 +70,11 @@ __device__ inline void fwd_walk_general(T32State<D, Sum> &st, const bf16x8 (&qop
 // of_pos, start: the range (item, window) of a sorted position and the first key of every range.  True if every
 // column saw all keys and its reference is in refs.
 template <int D, int NW, class Sum>
-__device__ inline bool fwd_branch(T32State<D, Sum> &st, float *refs, const bf16x8 (&qop)[D / 16], const T32Src<2> &src, unsigned char *stage0, int *again, const float *ends,
+__device__ inline bool fwd_branch(T32State<D, Sum> &st, float *refs, const bf16x8 (&qop)[D / 16], const T32Src<2> &src, unsigned char *stage0, int *again,
                                   int rs, int re, bool one, const int32_t *of_pos, const int32_t *start, const MfmaView &v, int wg_pos0,
                                   float sl2) {
   const typename T32<D, true>::Lanes ln = T32<D, true>::lanes();
-  if (one && fwd_walk<D, NW>(st, refs, qop, src, stage0, again, ends, rs, re, ln, sl2)) return true;
+  if (one && fwd_walk<D, NW>(st, refs, qop, src, stage0, again, rs, re, ln, sl2)) return true;
   const int own = of_pos[query_col(v, wg_pos0, 0).pos];
   fwd_walk_general<D, NW>(st, qop, src, stage0, rs, re, start[own], start[own + 1], ln, sl2);
   return false;
@@ -117,7 +107,7 @@ __device__ inline float finish(const FwdArgs &a, const T32State<D, Sum> &st, con
 
 constexpr float SCORE_FIX = 134217728.0f;  // 2^27: a row's scores sum to h_s <= 16 < 2^5
 
-// LDS plan of the compression kernel (bytes): two stages of two tiles | repeat flag, padding | first and last tile's scores | lse per query row | per token its
+// LDS plan of the compression kernel (bytes): two stages of two tiles | repeat flag, padding | lse per query row | per token its
 // first pooled key, the one behind its last and the first score of its item | scores [TW][s_max] | top-k marks [NW][words]
 // Blocks of an item whose scores a wavefront holds in registers for the top-k search; more are searched in T rounds over LDS.  With
 // 1024 here: one sequence of 72k tokens (1125 blocks) 5090 us for 3320 now, 131k (2048) 26900 for 11600.
@@ -125,7 +115,7 @@ constexpr int TOPK_IN_REGISTERS = 4096;
 template <int D>
 __host__ __device__ inline size_t cmp_lds_bytes(int nw, int hs, int s_max) {
   const int tw = 32 * nw / hs;
-  return (size_t)4 * T32<D, true>::BYTES + 16 + 256 + ((size_t)32 * nw + 3 * tw + (size_t)tw * s_max + (s_max > TOPK_IN_REGISTERS ? nw * ((s_max + 31) / 32) : 0)) * 4;
+  return (size_t)4 * T32<D, true>::BYTES + 16 + ((size_t)32 * nw + 3 * tw + (size_t)tw * s_max + (s_max > TOPK_IN_REGISTERS ? nw * ((s_max + 31) / 32) : 0)) * 4;
 }
 
 // Second walk of the compression kernel: eq. (6) scores with the normaliser known, for HS heads per KV head, over steps of two
@@ -207,8 +197,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
   unsigned char *stage0 = smem;
   const int hs = a.v.hs, s_max = a.v.s_max, TW = 32 * NW / hs;
   int *again = (int *)(stage0 + 4 * T::BYTES);
-  float *ends = (float *)(again + 4);
-  float *lse_l = ends + 64;                  // [32*NW] per query row
+  float *lse_l = (float *)(again + 4);       // [32*NW] per query row
   int *tok_info = (int *)(lse_l + 32 * NW);  // [3][TW]
   uint32_t *S = (uint32_t *)(tok_info + 3 * TW);
   const int wid = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -222,7 +211,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
   const int rs = uniform(a.v.cmp_batch[it0]), re = uniform(a.v.cmp_batch[it1 + 1]), s0 = uniform(a.v.slc_batch[it0]);
   const bool one = it0 == it1;
   if (threadIdx.x == 0) *again = 0;
-  write_ends(ends, rs, re);
   for (int t = threadIdx.x; t < TW; t += 64 * NW) {
     const int item = a.v.tok_item[min(wg_pos0 + t, a.v.N - 1)];
     tok_info[t] = a.v.cmp_batch[item];
@@ -235,7 +223,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
   const uint32_t stride = (uint32_t)(a.v.Hkv * D);
   const float sl2 = in_vgpr(a.v.sl2);
   T32State<D, SumInOrder> st;
-  const bool have_ref = fwd_branch<D, NW>(st, lse_l, qop, T32Src<2>{{Kg, Vg}, stride}, stage0, again, ends, rs, re, one, a.v.tok_item, a.v.cmp_batch, a.v, wg_pos0, sl2);
+  const bool have_ref = fwd_branch<D, NW>(st, lse_l, qop, T32Src<2>{{Kg, Vg}, stride}, stage0, again, rs, re, one, a.v.tok_item, a.v.cmp_batch, a.v, wg_pos0, sl2);
   const float lse2 = finish<D>(a, st, lse_l, have_ref, 0, query_col(a.v, wg_pos0, g));
   if (lane < 32) lse_l[wid * 32 + lane] = -lse2;
   __syncthreads();
@@ -288,11 +276,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32
   const int w0 = uniform(a.v.tok_win[wg_pos0]), w1 = uniform(a.v.tok_win[min(wg_pos0 + TW, a.v.N) - 1]);
   const int rs = uniform(a.v.win_start[w0]), re = uniform(a.v.win_start[w1 + 1]);
   if (threadIdx.x == 0) *again = 0;
-  float *ends = (float *)(again + 4), *refs = ends + 64;
-  write_ends(ends, rs, re);
+  float *refs = (float *)(again + 4);
   __syncthreads();
   T32State<D, SumParts> st;
-  const bool have_ref = fwd_branch<D, NW>(st, refs, qop, T32Src<2>{{a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D}, (uint32_t)(a.v.Hkv * D)}, stage0, again, ends, rs, re,
+  const bool have_ref = fwd_branch<D, NW>(st, refs, qop, T32Src<2>{{a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D}, (uint32_t)(a.v.Hkv * D)}, stage0, again, rs, re,
                   w0 == w1, a.v.tok_win, a.v.win_start, a.v, wg_pos0, in_vgpr(a.v.sl2));
   finish<D>(a, st, refs, have_ref, 2, query_col(a.v, wg_pos0, g));
 }
@@ -349,7 +336,7 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, co
     ProfScope ps(PROF_WIN_FWD, s);
     constexpr int NW = 4;
     const int tw = 32 * NW / a.v.hs;
-    m_win_fwd<D, NW><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, 4 * T32<D, true>::BYTES + 16 + 256 + 32 * NW * 4, s>>>(a);
+    m_win_fwd<D, NW><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, 4 * T32<D, true>::BYTES + 16 + 32 * NW * 4, s>>>(a);
   }
   {
     ProfScope ps(PROF_COMBINE, s);

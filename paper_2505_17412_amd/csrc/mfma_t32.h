@@ -98,6 +98,16 @@ __device__ inline f32x16 t32_scores(const bf16x8 (&qop)[D / 16], lds_cptr kt, co
   return s;
 }
 
+// Scores of the tile whose first key is kb, minus infinity for the keys outside [lo, hi).  (Replaced, not added to: a tile at the end
+// of a range holds keys of the next one, whose product with any query may have left the range of the floats.)
+__device__ inline void t32_only_keys(f32x16 &s, int kb, int lo, int hi) {
+  const int rel = kb - lo;
+  const unsigned len = (unsigned)(hi - lo);
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if ((unsigned)(rel + t32_key(i)) >= len) s[i] = -INFINITY;  // lo <= key < hi as one comparison
+}
+
 // The sum of a B operand's eight entries by products with two bf16 ones (32-bit sums), onto c.
 __device__ inline float bf16_ones() { return in_vgpr(__builtin_bit_cast(float, 0x3F803F80u)); }
 __device__ inline float sum8(bf16x8 p, float ones, float c) {
@@ -203,9 +213,15 @@ __device__ inline void t32_softmax(T32State<D, Sum> &st, const f32x16 &s, lds_cp
 }
 
 // The first tile's maximum contributes 1 to the sum, so nothing that counts is lost below; a sum under 2^60 leaves room for
-// values of the same size.
+// values of the same size.  A sum that is no number (a first tile all of whose scores are minus infinity, a score of plus infinity) is
+// out of range as well: the comparison is one of the bits, as integers, because these files are compiled as if NaN did not occur and
+// the comparison of floats would come out either way.
 template <int D, class Sum>
-__device__ inline bool t32_in_range(const T32State<D, Sum> &st) { return st.l.mine() < 0x1p60f; }
+__device__ inline bool t32_in_range(const T32State<D, Sum> &st) {
+  uint32_t bits = __float_as_uint(st.l.mine());
+  asm volatile("" : "+v"(bits));
+  return bits < 0x5D800000u;  // 2^60; sums are not negative
+}
 
 // The same step with a running maximum (-inf for keys that do not count): the reference is raised when some
 // score exceeds it by more than 8 log2 units, so that every exponent stays below 8.

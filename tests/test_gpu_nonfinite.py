@@ -1,6 +1,6 @@
-"""GPU: infinities and NaN in one batch item on the fp32-arithmetic path.  Its tiles hold query columns, keys and query rows of
-neighbouring items, so a value that is not finite must not reach a row through a weight of zero.  The other items are compared
-with the oracle on the untouched inputs, at the tolerances of the other parity tests."""
+"""GPU: infinities and NaN in one batch item on the fp32-arithmetic path, and on the matrix path finite keys whose scores overflow.
+The tiles hold query columns, keys and query rows of neighbouring items, so such a value must not reach a row through a weight of
+zero.  The other items are compared with the oracle or a run on the untouched inputs, at the tolerances of the other parity tests."""
 import copy
 
 import numpy as np
@@ -66,3 +66,45 @@ def test_keys_at_minus_infinity_have_no_weight(d):
     ref = orc.forward(wl.q, wl.k, wl.v, wl.gates, topk_idx=got.topk_idx)
     assert np.isfinite(ref.out).all()
     util.assert_close(got.out, ref.out, "f32", "out")
+
+
+@pytest.mark.parametrize("seed,grid,n,hq,hkv,d", [
+    (811, 16, (300, 270, 333), 16, 2, 64), (812, 16, (300, 270, 333), 8, 1, 32), (813, 16, (300, 270, 333), 16, 2, 128),
+    (814, 16, (33, 21, 40), 4, 4, 64), (815, 16, (45, 9, 70), 2, 1, 64),
+])
+@pytest.mark.parametrize("far", [3e38, -3e38])
+def test_scores_of_other_items_that_overflow_on_the_matrix_path(seed, grid, n, hq, hkv, d, far):
+    """Finite keys of one item whose products with any query leave the range of the floats: tiles at the ends of the neighbouring
+    items' key ranges hold them, and nothing of it reaches those items.  (To the tolerance of the type, not to the bit: columns of one
+    wavefront raise their reference exponents together, and probabilities are rounded relative to the reference.)"""
+    wl = inputs.random_points_workload(seed, grid, n, hq, hkv, d, (1, 4, 8), 4, "bf16")  # one-voxel blocks: the means stay finite
+    clean = util.run_gpu(wl)
+    others = np.r_[0:n[0], n[0] + n[1]:sum(n)]
+    mine = slice(n[0], n[0] + n[1])
+    wl.k[mine] = inputs.round_to_bf16(np.float32(far) * np.sign(wl.k[mine]))
+    got = util.run_gpu(wl)
+    assert np.array_equal(got.topk_idx[others], clean.topk_idx[others])
+    for name in ("out", "dq", "dk", "dv", "dgates"):
+        util.assert_close(getattr(got, name)[others], getattr(clean, name)[others], "bf16", name)
+    util.assert_close(got.lse[:, others], clean.lse[:, others], "bf16", "lse")
+
+
+@pytest.mark.parametrize("seed,lens,hq,hkv,d,l", [
+    (821, (512, 200), 16, 2, 64, (1, 128, 128)), (822, (512, 200), 4, 4, 32, (1, 128, 128)),
+    (823, (512, 200), 8, 1, 128, (1, 128, 128)), (824, (900, 200), 16, 2, 64, (1, 300, 300)),
+])
+def test_first_keys_at_the_lowest_value_have_no_weight_on_the_matrix_path(seed, lens, hq, hkv, d, l):
+    """The first 40 keys carry the type's lowest value where every query is above one: their scores are minus infinity, no later
+    tile may be measured against them, and the other keys keep their weights."""
+    wl = inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=2)
+    wl.q[..., 0] = inputs.round_to_bf16(np.abs(wl.q[..., 0]) + 2.0)
+    wl.k[0:40, :, 0] = -3.38e38
+    wl.k = inputs.round_to_bf16(wl.k)
+    assert np.isfinite(wl.k).all()
+    orc = oracle_for(wl)
+    got = util.run_gpu(wl, backward=False)
+    ref = orc.forward(wl.q, wl.k, wl.v, wl.gates, topk_idx=got.topk_idx)
+    assert np.isfinite(ref.out).all()
+    for b in range(3):
+        util.assert_close(got.out_branch[b], ref.out_branch[b], "bf16", f"branch {b}")
+    util.assert_close(got.out, ref.out, "bf16", "out")
