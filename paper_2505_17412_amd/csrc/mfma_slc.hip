@@ -77,9 +77,15 @@ __device__ inline void bc_pick_up_row(const bf16_t *rows, uint32_t prow, f32x16 
     }
 }
 
-// The partial of the earlier segments, picked up again.
+// The partial of the earlier segments, picked up again.  Columns past the end of the chunk start from nothing: the spare row holds
+// whatever column of whatever workgroup wrote it last.
 template <int D>
-__device__ inline void bc_pick_up(const BcFwdArgs &a, uint32_t prow, T32State<D, SumParts> &st) {
+__device__ inline void bc_pick_up(const BcFwdArgs &a, uint32_t prow, uint32_t spare, T32State<D, SumParts> &st) {
+  if (prow == spare) {
+    t32_clear(st);
+    st.m = 0.f;
+    return;
+  }
   const float2 ml = *reinterpret_cast<const float2 *>(a.pml + (size_t)prow * 2);
   st.m = ml.x;
   st.l.part[0] = threadIdx.x & 32 ? 0.f : ml.y;
@@ -134,7 +140,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     for (int it = wid; it < n_it; it += NW) {
       const uint32_t prow = cur.prow;
       T32State<D, SumParts> st;
-      if (!fresh) bc_pick_up<D>(a, prow, st);
+      if (!fresh) bc_pick_up<D>(a, prow, spare, st);
 #pragma unroll
       for (int t = 0; t < MAXT - 1; ++t)
         if (t < last) {
@@ -149,11 +155,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
         if (last == 0 && fresh) t32_softmax<D, false, true>(st, s, vlast, ln, sl2);
         else t32_softmax<D, false, false>(st, s, vlast, ln, sl2);
       }
-      if (__builtin_expect(__any(!t32_in_range(st)), 0)) {
+      // (a vote of the chunk's own columns: taken or not, the path decides how their probabilities are rounded)
+      if (__builtin_expect(__any(prow != spare && !t32_in_range(st)), 0)) {
         BcRows<D> r;
         bc_load_rows<D>(Qb, ent, it, cnt, lg_tpw, slot, lane_off, hl, spare, r);
         if (fresh) t32_clear(st);
-        else bc_pick_up<D>(a, prow, st);
+        else bc_pick_up<D>(a, prow, spare, st);
 #pragma unroll 1
         for (int t = 0; t <= last; ++t) {
           const f32x16 s = t32_scores<D, false>(r.qop, kl + t * T::BYTES, ln, t < last ? splat16(0.f) : t32_tail(tail));
@@ -321,7 +328,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   }
   const int tpw = 32 / hs;
   const int n_it = (cnt + tpw - 1) / tpw;
-  const uint32_t kstride = (uint32_t)(Hkv * D);
+  const uint32_t kstride = (uint32_t)(Hkv * D), spare = (uint32_t)((size_t)a.v.N * a.v.Hq * a.v.T);  // behind the last partial row
   const float sl2 = in_vgpr(a.v.sl2);
   const typename T::Lanes ln = T::lanes();
   const lds_cptr kt = (lds_cptr)Kt, vt = (lds_cptr)Vt;
@@ -344,7 +351,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       const float lse2 = cur.lse2;
       f32x16 acc[D / 32];
       const bool fresh = k0 == kbeg;
-      if (!fresh) bc_pick_up_row<D>(a.pdq, prow, acc);  // continue from the partial of the earlier segments
+      if (!fresh) {  // continue from the partial of the earlier segments (columns past the end of the chunk: from nothing)
+        if (prow != spare) bc_pick_up_row<D>(a.pdq, prow, acc);
+        else
+#pragma unroll
+          for (int db = 0; db < D / 32; ++db) acc[db] = splat16(0.f);
+      }
 #pragma unroll
       for (int t = 0; t < MAXT - 1; ++t)
         if (t < last) {
