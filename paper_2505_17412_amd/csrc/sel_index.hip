@@ -10,6 +10,7 @@
 // Kernel times: 11k tokens, top-8, 226 lists: 22 us in two launches (25 us in five); 2k tokens, 66 lists: 18 us (28); 62k tokens,
 // top-16, 932 lists: 59 us in four (61 in five).
 #include "mfma_launch.h"
+#include "sel_order.h"
 
 namespace {
 
@@ -18,8 +19,7 @@ constexpr int TILE_WORDS = POS_TILE / 32;
 constexpr int KEY_TILE = 2048;             // selection blocks of one KV head a workgroup covers: 64 KB of bits
 constexpr int SEL_THREADS = 512;
 constexpr int FUSED_COUNTS = 16384;  // see sel_index_build
-constexpr int ORDER_BINS = 8192, ORDER_CLASSES = 8, ORDER_STEP = 64;  // see m_chunk_order
-constexpr int BY_LENGTH_TOKENS = 24576;  // see sel_index_carve
+constexpr int ORDER_STEP = 64;  // keys per class of block lengths
 
 struct SelArgs {
   const int32_t *idx, *perm;
@@ -260,7 +260,7 @@ template <int R>
 __global__ __launch_bounds__(SEL_THREADS) void m_sel_fill(SelArgs a, int n_tiles, int stride, const uint32_t *__restrict__ cnt,
                                                           const int32_t *__restrict__ start, int32_t *__restrict__ list,
                                                           uint8_t *__restrict__ rank, OrderArgs o0, OrderArgs o1, const int32_t *__restrict__ slc_start,
-                                                          int bucket, int bins_per_head, bool caller_indices) {
+                                                          SelOrder ord, bool caller_indices) {
   extern __shared__ __align__(16) uint32_t sel_bits[];
   const int tile = blockIdx.x, g = blockIdx.y, b0 = blockIdx.z * KEY_TILE, nb = min(KEY_TILE, a.Ns - b0);
   for (int i = threadIdx.x; i < nb * TILE_WORDS; i += SEL_THREADS) sel_bits[i] = 0u;
@@ -295,8 +295,8 @@ __global__ __launch_bounds__(SEL_THREADS) void m_sel_fill(SelArgs a, int n_tiles
       const int c = r / o.chunk_len;
       if (o.base) o.order[o.base[key] + c] = ChunkRef{key, c, at, min(o.chunk_len, start[key + 1] - at)};
       else {
-        const int cls = ORDER_CLASSES - 1 - min((slc_start[b[u] + 1] - slc_start[b[u]]) / ORDER_STEP, ORDER_CLASSES - 1);
-        const int bin = (cls * a.Hkv + g) * bins_per_head + (p0 + pl) / bucket;
+        const int cls = ord.classes - 1 - min((slc_start[b[u] + 1] - slc_start[b[u]]) / ORDER_STEP, ord.classes - 1);
+        const int bin = (cls * a.Hkv + g) * ord.per_head + (p0 + pl) / ord.bucket;
         o.slot[o.chunk_start[key] + c] = make_int4(bin, (int)atomicAdd(&o.bins[bin], 1u), key, c);
       }
     };
@@ -381,11 +381,7 @@ SelIndex sel_index_carve(void *ws_, int N, int Hkv, int T, int Ns, int chunk_len
   x.chunk_start = (int32_t *)(ws + p.cstart); x.part_row_start = (int32_t *)(ws + p.prow);
   x.bc_chunk_start = (int32_t *)(ws + p.bcstart); x.bins = (uint32_t *)(ws + p.bins); x.ticket = x.bins + 2 * ORDER_BINS;
   x.base = (int32_t *)(ws + p.base);
-  // Order of the work chunks: in small problems by falling length of their block, whose places the last pass can write, so that the
-  // chunks that end last are short; in large ones by stretches of tokens (m_chunk_order), which saves fetches of the query rows.
-  // Times of m_slc_fwd_bc / m_slc_bwd, us, in the order of token stretches alone and by falling length: 2k tokens 29 / - and 26 / -; 11k
-  // 139 / - and 118 / -; 21k 145 / 491 and 130 / 415; beyond, m_chunk_order's classes take the place of either (its figures there).
-  x.by_length = N <= BY_LENGTH_TOKENS;
+  x.by_length = sel_order(N, Hkv).by_length;
   x.bc_slot = (int4 *)(ws + p.bcslot); x.slot = (int4 *)(ws + p.slot);
   x.bc_order = (ChunkRef *)(ws + p.bcorder); x.order = (ChunkRef *)(ws + p.order);
   x.chunk_len = chunk_len; x.bc_chunk_len = bc_chunk_len;
@@ -399,10 +395,8 @@ int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_
   // the last of the second does the third.
   const bool fused = (long long)keys * stride <= FUSED_COUNTS;
   int32_t *const base = x.by_length ? x.base : nullptr, *const bc_base = x.by_length ? x.base + keys : nullptr;
-  // bucket width of the execution orders: ORDER_CLASSES * Hkv * ceil(N / bucket) buckets fit the LDS table
-  int bucket = 64;
-  while ((long long)ORDER_CLASSES * Hkv * ((N + bucket - 1) / bucket) > ORDER_BINS) bucket *= 2;
-  const int bph = (N + bucket - 1) / bucket, n_bins = ORDER_CLASSES * Hkv * bph;
+  const SelOrder ord = sel_order(N, Hkv);
+  const int n_bins = x.by_length ? 0 : ord.classes * Hkv * ord.per_head;
   const SelArgs a{idx, perm, N, Hkv, T, Ns};
   const dim3 grid(tiles, Hkv, (Ns + KEY_TILE - 1) / KEY_TILE);
   const size_t lds = (size_t)(Ns < KEY_TILE ? Ns : KEY_TILE) * TILE_WORDS * 4;
@@ -412,9 +406,9 @@ int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_
   m_sel_count<<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.counts, x.bins, ORDER_BINS, n_bins, fused ? x.ticket : nullptr,
                                              x.ticket + 1, sc, base, bc_base);
   if (!fused) m_sel_scan_tiles<<<(keys + 3) / 4, 256, 0, s>>>(x.cnt, keys, tiles, stride, x.counts, x.ticket + 1, sc, base, bc_base);
-  if (T <= 16) m_sel_fill<1><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, bucket, bph, caller_indices);
-  else if (T <= 32) m_sel_fill<2><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, bucket, bph, caller_indices);
-  else m_sel_fill<4><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, bucket, bph, caller_indices);
+  if (T <= 16) m_sel_fill<1><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, ord, caller_indices);
+  else if (T <= 32) m_sel_fill<2><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, ord, caller_indices);
+  else m_sel_fill<4><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, ord, caller_indices);
   if (x.by_length) return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
   if (want_bc_order && want_dkv_order) m_chunk_order<<<2, 1024, 0, s>>>(bc, dkv, x.start, keys, n_bins);
   else if (want_bc_order) m_chunk_order<<<1, 1024, 0, s>>>(bc, bc, x.start, keys, n_bins);

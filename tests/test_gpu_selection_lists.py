@@ -1,11 +1,12 @@
 """GPU: the inverse selection index at the edges of its tiles, seen through forward and backward (the selection branch of
 every gradient walks its lists): 256 sorted positions per tile, 16 / 32 / 64 list entries per token, 2048 selection blocks
-per workgroup, work chunks of 32 to 256 tokens, 24576 tokens up to which chunks run by block length alone.  Tolerances of the
-other parity tests."""
+per workgroup, work chunks of 32 to 256 tokens, 24576 tokens up to which chunks run by block length alone, more KV heads than the order of
+the chunks has buckets for at its usual fineness.  Tolerances of the other parity tests."""
 import numpy as np
 import pytest
 
 from paper_2505_17412_amd import inputs
+from tests import util
 from tests.test_gpu_parity import full_parity
 
 pytestmark = pytest.mark.gpu
@@ -26,3 +27,34 @@ def test_lists_at_tile_edges(seed, grid, n, hq, hkv, d, m, topk):
 def test_orders_of_the_work_chunks(seed, lens):
     wl = inputs.make_sequence_workload(seed, lens, hq=4, hkv=2, d=32, l=(32, 96, 64), topk=4)
     full_parity(wl, queries=np.arange(0, wl.n_tokens, 97, dtype=np.int32))
+
+
+@pytest.mark.parametrize("heads", [1025])
+def test_more_kv_heads_than_buckets(heads):
+    """Heads are independent: with more of them than 8192 buckets in eight classes of block length leave one each, the first, a middle
+    and the last head come out as in a call of these three."""
+    import torch
+    from paper_2505_17412_amd import ssa
+    n, d, topk, some = 24577, 32, 1, [0, heads // 2, heads - 1]
+    offs = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(321)
+    x = {k: torch.randn((n, heads, d), generator=gen, device="cuda", dtype=torch.bfloat16) for k in ("q", "k", "v", "dout")}
+    gates = torch.rand((n, heads, 3), generator=gen, device="cuda").to(torch.bfloat16)
+
+    def run(hs):
+        q, k, v, do, g = (t if hs is None else t[:, hs].contiguous() for t in (*x.values(), gates))
+        h = q.shape[1]
+        p = ssa.make_params(n, 1, 0, 512, 1024, 128, topk, h, h, d, "bf16")
+        blk = ssa.ssa_build_blocks_1d(p, offs)
+        out, dq, dk, dv, dg = (torch.full_like(t, float("nan")) for t in (q, q, k, v, g))
+        branch = torch.empty((3, n, h, d), dtype=torch.bfloat16, device="cuda")
+        lse, idx = torch.empty((3, n, h), device="cuda"), torch.empty((n, h, topk), dtype=torch.int32, device="cuda")
+        ssa.ssa_forward(p, blk, q, k, v, g, out, lse, idx, branch)
+        ssa.ssa_backward(p, blk, q, k, v, g, branch, lse, idx, do, dq, dk, dv, dg)
+        torch.cuda.synchronize()
+        return [t if hs is not None else t[:, some] for t in (idx, out, dq, dk, dv, dg)]
+
+    few, many = run(some), run(None)
+    assert torch.equal(few[0], many[0])
+    for name, a, b in zip(("out", "dq", "dk", "dv", "dgates"), many[1:], few[1:]):
+        util.assert_close(util.to_np(a), util.to_np(b), "bf16", name)
