@@ -13,9 +13,12 @@
 #include "mfma_launch.h"
 #include "mfma_qc.h"
 #include "mfma_t32.h"
+#include "cmp_form.h"
 #include "profile.h"
 
+#include <limits.h>
 #include <mutex>
+#include <type_traits>
 
 namespace {
 
@@ -25,6 +28,7 @@ struct FwdArgs {
   bf16_t *Ob;    // [3,N,Hq,D]
   float *lse;    // [3,N,Hq]
   int32_t *idx;  // [N,Hkv,T]
+  float *nlse;   // [N(pos)][Hq]: minus the compression branch's log-sum-exp in log2 units, from m_cmp_walk to m_cmp_scores
 };
 
 // Walks start at a multiple of 8 (which keys are a column's first tile, and with it the reference exponent, is part of what the
@@ -107,91 +111,126 @@ __device__ inline float finish(const FwdArgs &a, const T32State<D, Sum> &st, con
 
 constexpr float SCORE_FIX = 134217728.0f;  // 2^27: a row's scores sum to h_s <= 16 < 2^5
 
-// LDS plan of the compression kernel (bytes): two stages of two tiles | repeat flag, padding | lse per query row | per token its
-// first pooled key, the one behind its last and the first score of its item | scores [TW][s_max] | top-k marks [NW][words]
-// Blocks of an item whose scores a wavefront holds in registers for the top-k search; more are searched in T rounds over LDS.  With
-// 1024 here: one sequence of 72k tokens (1125 blocks) 5090 us for 3320 now, 131k (2048) 26900 for 11600.
-constexpr int TOPK_IN_REGISTERS = 4096;
-template <int D>
-__host__ __device__ inline size_t cmp_lds_bytes(int nw, int hs, int s_max) {
-  const int tw = 32 * nw / hs;
-  return (size_t)4 * T32<D, true>::BYTES + 16 + ((size_t)32 * nw + 3 * tw + (size_t)tw * s_max + (s_max > TOPK_IN_REGISTERS ? nw * ((s_max + 31) / 32) : 0)) * 4;
+static_assert(T32<64, true>::BYTES == tile_bytes(64) && T32<128, true>::BYTES == tile_bytes(128), "the LDS plans count whole tiles");
+// Top-k of one token's score row Sr[0 .. nb) out of rows of s_max <= MOST; marks: scratch of the wavefront where rows are longer than that.
+template <int MOST>
+__device__ inline void topk_slot(const uint32_t *Sr, int s_max, int nb, int T, int b0, int32_t *row, uint32_t *marks) {
+  if (s_max <= 64) topk_wave_bits<1>(Sr, nb, T, b0, row);
+  else if (s_max <= 128) topk_wave_bits<2>(Sr, nb, T, b0, row);
+  else if (s_max <= 256) topk_wave_bits<4>(Sr, nb, T, b0, row);
+  else if (s_max <= 512) topk_wave_bits<8>(Sr, nb, T, b0, row);
+  else if (MOST <= 1024 || s_max <= 1024) topk_wave_bits<16>(Sr, nb, T, b0, row);
+  else if constexpr (MOST > 1024) {
+    if (s_max <= 2048) topk_wave_bits<32>(Sr, nb, T, b0, row);
+    else if (s_max <= TOPK_IN_REGISTERS) topk_wave_bits<64>(Sr, nb, T, b0, row);
+    else topk_wave_u32(Sr, nb, T, b0, row, marks);
+  }
 }
 
-// Second walk of the compression kernel: eq. (6) scores with the normaliser known, for HS heads per KV head, over steps of two
-// 32-key tiles.  Scores NOT transposed (query rows x keys): a lane holds rows t32_row(i) for one key, and adds the heads of a token
-// in-lane; with 8 or 16 heads one register swap adds the other lane's for two tokens at once and leaves each lane with one token,
-// and one integer LDS atomic adds the sum onto the key's selection block.  l16: -lse per row (log2 units).
-template <int D, int NW, int HS>
-__device__ inline void score_walk(const FwdArgs &a, const bf16x8 (&qop)[D / 16], const T32Src<2> &src, unsigned char *stage0, int rs, int re, bool one,
-                                  const f32x16 &l16, const int *tok_info, int s0, uint32_t *S, float sl2) {
+// Sums over the HS heads of a token of a tile of probabilities (query rows x keys: the lane holds rows t32_row(i) of one key): HS of
+// 8 or 16 leaves each lane with 16 / HS of the key's tokens, fewer heads with both lanes' worth.
+template <int HS> constexpr int token_sum_count() { return HS == 16 ? 1 : 16 / HS; }
+template <int HS>
+__device__ inline void token_sums(const f32x16 &c, float (&v)[token_sum_count<HS>()]) {
+  if constexpr (HS >= 8) {  // groups of four heads: t[u] of lane h = rows 8*u + 4*h .. +3
+    float t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = ((c[4 * u] + c[4 * u + 1]) + c[4 * u + 2]) + c[4 * u + 3];
+    auto pair = [](float x, float y) {  // x's two lanes added in lane 0, y's in lane 1
+      const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+      return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    if constexpr (HS == 8) {
+      v[0] = pair(t[0], t[1]);
+      v[1] = pair(t[2], t[3]);
+    } else {
+      v[0] = pair(t[0], t[2]) + pair(t[1], t[3]);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < token_sum_count<HS>(); ++u) {
+      v[u] = c[HS * u];
+#pragma unroll
+      for (int j = 1; j < HS; ++j) v[u] += c[HS * u + j];
+    }
+  }
+}
+// Token (of the wavefront's 32 rows) that sum u belongs to.
+template <int HS>
+__device__ inline int token_of_sum(int u) {
+  const int h = threadIdx.x >> 5 & 1;
+  return HS >= 8 ? 2 * u + h : (8 * (HS * u >> 2) + 4 * h + (HS * u & 3)) / HS;
+}
+
+// Selection scores (eq. (6), the normaliser known) of one 32-key tile: kb its first key, key and blk this lane's key and its selection
+// block.  Scores NOT transposed (query rows x keys), the heads of a token added in the lane (token_sums), and one integer LDS atomic
+// adds the sum onto the score row of the token.  l16: -lse per row (log2 units); row0: first score row of the wavefront's 32 rows.
+struct ScoreRows {
+  uint32_t *S;          // [tokens][s_max]
+  const int *tok_info;  // [3][tokens]: a token's first key, the one behind its last, the first selection block of its item
+  int tokens, s_max, re, s0;
+  bool one;             // all tokens are of one item, whose keys end at re and whose blocks start at s0
+};
+template <int D, int HS, class Operand>
+__device__ inline void score_tile(const bf16x8 (&qop)[D / 16], Operand operand, const f32x16 &l16, float sl2, const ScoreRows &r, int row0, int kb, int key, int blk) {
+  f32x16 c = splat16(0.f);
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) c = mfma32(qop[ks], operand(ks), c);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) c[i] = fast_exp2(__builtin_fmaf(c[i], sl2, l16[i]));
+  constexpr int NV = token_sum_count<HS>();
+  float v[NV];
+  token_sums<HS>(c, v);
+  const bool whole = r.one && kb + 32 <= r.re;
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const int tok = row0 + token_of_sum<HS>(u);
+    if (whole) atomicAdd(&r.S[tok * r.s_max + (blk - r.s0)], (uint32_t)(v[u] * SCORE_FIX));
+    else if (key >= r.tok_info[tok] && key < r.tok_info[r.tokens + tok])
+      atomicAdd(&r.S[tok * r.s_max + (blk - r.tok_info[2 * r.tokens + tok])], (uint32_t)(v[u] * SCORE_FIX));
+  }
+}
+
+// The scores of 32 query rows per wavefront over the keys [rs, re): ST tiles per step through LDS, of which a wavefront takes every
+// KS-th from number k0.
+template <int D, int HS, int NTHR, int ST, int KS>
+__device__ inline void score_walk(const MfmaView &v, const bf16_t *Kg, uint32_t stride, const bf16x8 (&qop)[D / 16], unsigned char *stage0, int rs, int k0,
+                                  const f32x16 &l16, const ScoreRows &r, int row0, float sl2) {
   using T = T32<D, true>;
-  constexpr int TPW = 32 / HS, TW = NW * TPW;   // tokens per wavefront, per workgroup
-  constexpr int NV = HS == 16 ? 1 : 16 / HS;    // sums a lane adds per tile
   const typename T::Lanes ln = T::lanes();
-  const int n = t32_order(threadIdx.x & 31), h = threadIdx.x >> 5 & 1, wid = threadIdx.x >> 6, last = a.v.Nc - 1, s_max = a.v.s_max;
-  t32_pipeline<D, 2, 64 * NW, 64, T32_PF>(src, stage0, rs, re, [&](lds_cptr kt, int kb2) {
+  const int n = t32_order(threadIdx.x & 31), last = v.Nc - 1;
+  T32Src<ST> src;
+  src.stride = stride;
+#pragma unroll
+  for (int t = 0; t < ST; ++t) src.row[t] = Kg + (size_t)(32 * t) * stride;
+  t32_pipeline<D, ST, NTHR, 32 * ST, T32_PF>(src, stage0, rs, r.re, [&](lds_cptr kt, int kb0) {
     // the selection blocks of this lane's keys, requested before the matrix instructions
-    int sb[2];
+    int blk[ST / KS];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) sb[half] = a.v.cmp_slc[min(kb2 + 32 * half + n, last)];
+    for (int t = 0; t < ST / KS; ++t) blk[t] = v.cmp_slc[min(kb0 + 32 * (k0 + t * KS) + n, last)];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      f32x16 c = splat16(0.f);
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) c = mfma32(qop[ks], T::row(kt + half * T::BYTES, ln, ks), c);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) c[i] = fast_exp2(__builtin_fmaf(c[i], sl2, l16[i]));
-      float v[NV];
-      if constexpr (HS >= 8) {  // groups of four heads: t[u] of lane h = rows 8*u + 4*h .. +3
-        float t[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) t[u] = ((c[4 * u] + c[4 * u + 1]) + c[4 * u + 2]) + c[4 * u + 3];
-        auto pair = [](float x, float y) {  // x's two lanes added in lane 0, y's in lane 1
-          const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-          return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        };
-        if constexpr (HS == 8) {
-          v[0] = pair(t[0], t[1]);
-          v[1] = pair(t[2], t[3]);
-        } else {
-          v[0] = pair(t[0], t[2]) + pair(t[1], t[3]);
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-          v[u] = c[HS * u];
-#pragma unroll
-          for (int j = 1; j < HS; ++j) v[u] += c[HS * u + j];
-        }
-      }
-      const int key = kb2 + 32 * half + n;
-      const bool whole = one && kb2 + 32 * half + 32 <= re;
-#pragma unroll
-      for (int u = 0; u < NV; ++u) {
-        // token of sum u: rows t32_row(i) / HS
-        const int tok = wid * TPW + (HS >= 8 ? 2 * u + h : (8 * (HS * u >> 2) + 4 * h + (HS * u & 3)) / HS);
-        if (whole) atomicAdd(&S[tok * s_max + (sb[half] - s0)], (uint32_t)(v[u] * SCORE_FIX));
-        else if (key >= tok_info[tok] && key < tok_info[TW + tok])
-          atomicAdd(&S[tok * s_max + (sb[half] - tok_info[2 * TW + tok])], (uint32_t)(v[u] * SCORE_FIX));
-      }
+    for (int t = 0; t < ST / KS; ++t) {
+      const int kb = kb0 + 32 * (k0 + t * KS);
+      const lds_cptr tile = kt + (k0 + t * KS) * T::BYTES;
+      score_tile<D, HS>(qop, [&](int ks) { return T::row(tile, ln, ks); }, l16, sl2, r, row0, kb, kb + n, blk[t]);
     }
   });
 }
 
 // Compression branch (eq. (4) first term over the mean-pooled keys of eq. (5)), then the selection scores of
 // eq. (6) accumulated per selection block in LDS as fixed-point integers (integer adds commute, so the result
-// does not depend on scheduling), then the top-k.
+// does not depend on scheduling), then the top-k.  (cmp_form.h says where; elsewhere m_walk_fwd and m_cmp_scores.)
 // Bound: matrix and vector issue over both walks, at a clock that falls to 1.8 - 1.9 GHz under them: per 32 x 32 scores at head_dim
 // 64 the first walk takes 256 matrix cycles and about 280 of exponentials, multiply-adds, conversions and sums (a synthetic copy:
 // 226 ns per SIMD), the second 128 and about 250; the kernel takes about 1.45 times that.  32 query columns per wavefront against
 // 16: half the LDS operands per matrix cycle, half the staging and barriers per column.  Three wavefronts per SIMD (168 registers,
-// and LDS for three workgroups); two: 17 % slower.  The sums of the first walk cost 5 % more in the order that keeps the selected
+// none spilled, and LDS for three workgroups); two: 17 % slower.  At head_dim 128 two, with 26 of 256 registers spilled outside the
+// tile code's operands; in two kernels, whose walk spills 6, 62k tokens and 662 blocks take 3400 us for 3130.  The sums of the first walk cost 5 % more in the order that keeps the selected
 // sets what they were (SumInOrder; 1290 us without).  62k tokens, 2247 pooled keys, 16 heads of 64: 1516 -> 1370 us (16 columns
 // before); 65k tokens in sequences 880 -> 830; 11k tokens 94 -> 79; 2k tokens, 32 heads of 32: 19.6 -> 14; 153k tokens, 3884 pooled
 // keys, heads of 128: 11.5 -> 9.1 ms.
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 && NW < 8 ? 3 : 2))) void m_cmp_fwd(FwdArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 3 : 2))) void m_cmp_fwd(FwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   using T = T32<D, true>;
   unsigned char *stage0 = smem;
@@ -230,16 +269,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
   f32x16 l16;
 #pragma unroll
   for (int i = 0; i < 16; ++i) l16[i] = lse_l[wid * 32 + t32_row(i)];
-  // two consecutive 32-key tiles per step: half the barriers and staging rounds of a walk that has little work per key
-  const T32Src<2> src2{{Kg, Kg + (size_t)32 * stride}, stride};
-  auto walk = [&](auto hs_c) {  // a walk per head count: the tile code is straight-line
-    score_walk<D, NW, decltype(hs_c)::value>(a, qop, src2, stage0, rs, re, one, l16, tok_info, s0, S, sl2);
+  const ScoreRows rows{S, tok_info, TW, s_max, re, s0, one};
+  auto walk = [&](auto hs_c) {  // a walk per head count: the tile code is straight-line.  (Two tiles per step: half the barriers)
+    score_walk<D, decltype(hs_c)::value, 64 * NW, 2, 1>(a.v, Kg, stride, qop, stage0, rs, 0, l16, rows, wid * 32 / decltype(hs_c)::value, sl2);
   };
   if (hs == 8) walk(std::integral_constant<int, 8>());
   else if (hs == 16) walk(std::integral_constant<int, 16>());
-  else if (hs == 4) walk(std::integral_constant<int, 4>());
-  else if (hs == 2) walk(std::integral_constant<int, 2>());
-  else walk(std::integral_constant<int, 1>());
+  else walk(std::integral_constant<int, 4>());
   // ---- top-k: each wavefront serves its own token slots, one after the other
   const int spw = 32 / hs;  // token slots per wavefront
   for (int tl = 0; tl < spw; ++tl) {
@@ -248,79 +284,164 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
     const int tok = a.v.perm[pos], it = a.v.tok_item[pos];
     const int b0 = a.v.slc_batch[it], nb = a.v.slc_batch[it + 1] - b0;
     int32_t *row = a.idx + ((size_t)tok * a.v.Hkv + g) * a.v.T;
-    const uint32_t *Sr = S + (size_t)slot * s_max;
-    if (s_max <= 64) topk_wave_bits<1>(Sr, nb, a.v.T, b0, row);
-    else if (s_max <= 128) topk_wave_bits<2>(Sr, nb, a.v.T, b0, row);
-    else if (s_max <= 256) topk_wave_bits<4>(Sr, nb, a.v.T, b0, row);
-    else if (s_max <= 512) topk_wave_bits<8>(Sr, nb, a.v.T, b0, row);
-    else if (s_max <= 1024) topk_wave_bits<16>(Sr, nb, a.v.T, b0, row);
-    else if (s_max <= 2048) topk_wave_bits<32>(Sr, nb, a.v.T, b0, row);
-    else if (s_max <= TOPK_IN_REGISTERS) topk_wave_bits<64>(Sr, nb, a.v.T, b0, row);
-    else topk_wave_u32(Sr, nb, a.v.T, b0, row, S + (size_t)TW * s_max + (size_t)wid * ((s_max + 31) >> 5));
+    topk_slot<CMP_ONE_BLOCKS>(S + (size_t)slot * s_max, s_max, nb, a.v.T, b0, row, nullptr);
   }
 }
 
 // Window branch: keys are the tokens of the query's own window.  62k tokens, 16 heads of 64: 154 -> 105 us (16 columns per wavefront
 // before), 65k tokens in windows of 512: 270 -> 190, 153k tokens, heads of 128: 1109 -> 720.
-template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_win_fwd(FwdArgs a) {
+// CMP: the compression branch alone, over the pooled keys of the query's item, where m_cmp_scores forms the selection scores.
+template <int D, int NW, bool CMP>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_walk_fwd(FwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char *stage0 = smem;
   int *again = (int *)(stage0 + 4 * T32<D, true>::BYTES);
+  float *refs = (float *)(again + 4);
   const int TW = 32 * NW / a.v.hs;
   const TileMap tm = xcd_tile_map((a.v.N + TW - 1) / TW, a.v.Hkv);
   if (!tm.valid) return;
   const int g = tm.g, wg_pos0 = tm.tile * TW;
   bf16x8 qop[D / 16];
   load_col<D>(a.Q, a.v, query_col(a.v, wg_pos0, g), qop);
-  const int w0 = uniform(a.v.tok_win[wg_pos0]), w1 = uniform(a.v.tok_win[min(wg_pos0 + TW, a.v.N) - 1]);
-  const int rs = uniform(a.v.win_start[w0]), re = uniform(a.v.win_start[w1 + 1]);
+  // the items (windows) of the workgroup's tokens are neighbours, and so are their keys
+  const int32_t *of_pos = CMP ? a.v.tok_item : a.v.tok_win, *start = CMP ? a.v.cmp_batch : a.v.win_start;
+  const int r0 = uniform(of_pos[wg_pos0]), r1 = uniform(of_pos[min(wg_pos0 + TW, a.v.N) - 1]);
+  const int rs = uniform(start[r0]), re = uniform(start[r1 + 1]);
   if (threadIdx.x == 0) *again = 0;
-  float *refs = (float *)(again + 4);
   __syncthreads();
-  T32State<D, SumParts> st;
-  const bool have_ref = fwd_branch<D, NW>(st, refs, qop, T32Src<2>{{a.v.Ks + (size_t)g * D, a.v.Vs + (size_t)g * D}, (uint32_t)(a.v.Hkv * D)}, stage0, again, rs, re,
-                  w0 == w1, a.v.tok_win, a.v.win_start, a.v, wg_pos0, in_vgpr(a.v.sl2));
-  finish<D>(a, st, refs, have_ref, 2, query_col(a.v, wg_pos0, g));
+  T32State<D, std::conditional_t<CMP, SumInOrder, SumParts>> st;
+  const T32Src<2> src{{(CMP ? a.v.Kc : a.v.Ks) + (size_t)g * D, (CMP ? a.v.Vc : a.v.Vs) + (size_t)g * D}, (uint32_t)(a.v.Hkv * D)};
+  const bool have_ref = fwd_branch<D, NW>(st, refs, qop, src, stage0, again, rs, re, r0 == r1, of_pos, start, a.v, wg_pos0, in_vgpr(a.v.sl2));
+  const QCol q = query_col(a.v, wg_pos0, g);
+  const float lse2 = finish<D>(a, st, refs, have_ref, CMP ? 0 : 2, q);
+  if (CMP && q.valid) a.nlse[(size_t)q.pos * a.v.Hq + q.h] = -lse2;  // (both lanes of a column: the same)
 }
 
-// Wavefronts per workgroup of the compression kernel: what keeps most of them on a compute unit beside the score rows (four where
-// that is equal).  Two everywhere: 62k tokens 1290 -> 1527 us, 11k 79 -> 85 (each stages the pooled keys for half the columns).  One
-// sequence of 65k tokens, 1024 selection blocks: 2320 us by two (six on a compute unit), 1810 by eight; the 16-column kernel, with
-// half the score rows per wavefront and twelve of them, took 1620.
-constexpr size_t CMP_LDS_CU = 160 * 1024, CMP_LDS_WG = 150 * 1024;
-template <int D>
-int cmp_waves(int hs, int s_max) {
-  constexpr int by_registers = D <= 64 ? 12 : 8;
-  int best = 2, most = 0;
-  for (const int nw : {4, 8, 2}) {
-    const size_t lds = cmp_lds_bytes<D>(nw, hs, s_max);
-    if (lds > CMP_LDS_WG) continue;
-    const int by_lds = (int)(CMP_LDS_CU / lds) * nw, waves = by_lds < by_registers / nw * nw ? by_lds : by_registers / nw * nw;
-    if (waves > most) {
-      most = waves;
-      best = nw;
-    }
+// Selection scores of eq. (6) and top-k behind m_walk_fwd<.., true>: CW * KS wavefronts share the score rows of 32 * CW query rows, and
+// KS of them the 32 rows of a group, of which each takes every KS-th tile of 32 pooled keys.  The scores are the same products and
+// integer additions as in m_cmp_fwd, so the selected sets are too.  ST tiles per step go through LDS, or (ST = 0, CW = 1) every
+// wavefront loads the rows of its tiles itself, the next tile's in flight: no tile is wanted twice, and LDS is left to the score rows.
+// Bound: with the tiles in LDS the sum of matrix and vector issue; without, the L1 cache (4 KB of key rows at head_dim 64 for 128 matrix
+// cycles).
+template <int D, int HS, int CW, int KS, int ST>
+__global__ __launch_bounds__(64 * CW * KS) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 4 : HS == 1 ? 2 : 3))) void m_cmp_scores(FwdArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  using T = T32<D, true>;
+  constexpr int NW = CW * KS, TPW = 32 / HS, TW = CW * TPW;
+  static_assert(ST > 0 ? ST % KS == 0 : CW == 1, "a tile loaded by one wavefront is used by one");
+  const int s_max = a.v.s_max, N = a.v.N;
+  int *tok_info = (int *)(smem + 2 * ST * T::BYTES);  // [3][TW]
+  uint32_t *S = (uint32_t *)(tok_info + 3 * TW);      // [TW][s_max]
+  const int wid = uniform(threadIdx.x >> 6), n = threadIdx.x & 31, h = threadIdx.x >> 5 & 1, group = wid % CW, k0 = wid / CW;
+  const TileMap tm = xcd_tile_map((N + TW - 1) / TW, a.v.Hkv);
+  if (!tm.valid) return;
+  const int g = tm.g, wg_pos0 = tm.tile * TW, pos0 = wg_pos0 + group * TPW;
+  bf16x8 qop[D / 16];
+  const bf16_t *src = a.Q + ((size_t)a.v.perm[min(pos0 + n / HS, N - 1)] * a.v.Hq + g * HS + n % HS) * D + 8 * h;
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) qop[ks] = ld8(src + 16 * ks);
+  f32x16 l16;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) l16[i] = a.nlse[(size_t)min(pos0 + t32_row(i) / HS, N - 1) * a.v.Hq + g * HS + t32_row(i) % HS];
+  const int it0 = uniform(a.v.tok_item[wg_pos0]), it1 = uniform(a.v.tok_item[min(wg_pos0 + TW, N) - 1]);
+  const int rs = uniform(a.v.cmp_batch[it0]), re = uniform(a.v.cmp_batch[it1 + 1]), s0 = uniform(a.v.slc_batch[it0]);
+  if (threadIdx.x < TW) {
+    const int item = a.v.tok_item[min(wg_pos0 + (int)threadIdx.x, N - 1)];
+    tok_info[threadIdx.x] = a.v.cmp_batch[item];
+    tok_info[TW + threadIdx.x] = a.v.cmp_batch[item + 1];
+    tok_info[2 * TW + threadIdx.x] = a.v.slc_batch[item];
   }
-  return best;
+  for (int i = threadIdx.x; i < TW * s_max; i += 64 * NW) S[i] = 0u;
+  __syncthreads();
+  const uint32_t stride = (uint32_t)(a.v.Hkv * D);
+  const bf16_t *Kg = a.v.Kc + (size_t)g * D;
+  const float sl2 = in_vgpr(a.v.sl2);
+  const ScoreRows rows{S, tok_info, TW, s_max, re, s0, it0 == it1};
+  if constexpr (ST > 0) {
+    score_walk<D, HS, 64 * NW, ST, KS>(a.v, Kg, stride, qop, smem, rs, k0, l16, rows, group * TPW, sl2);
+  } else {
+    struct Keys { bf16x8 op[D / 16]; int blk; } ka, kb;
+    constexpr int STEP = 32 * NW;
+    auto load = [&](int key, Keys &k) {  // the tile at key, or (past the end: not used) the first one; rows past the last key are padding
+      const int row = (key < re ? key : rs) + n;
+      const bf16_t *x = Kg + ((uint32_t)row * stride + (uint32_t)(8 * h));
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks) k.op[ks] = ld8(x + 16 * ks);
+      k.blk = a.v.cmp_slc[min(row, a.v.Nc - 1)];
+    };
+    auto tile = [&](int key, const Keys &k) {
+      score_tile<D, HS>(qop, [&](int ks) { return k.op[ks]; }, l16, sl2, rows, 0, key, key + n, k.blk);
+    };
+    load(rs + 32 * wid, ka);
+    for (int key = rs + 32 * wid; key < re; key += 2 * STEP) {
+      load(key + STEP, kb);
+      tile(key, ka);
+      if (key + STEP >= re) break;
+      load(key + 2 * STEP, ka);
+      tile(key + STEP, kb);
+    }
+    __syncthreads();
+  }
+  for (int slot = wid; slot < TW && wg_pos0 + slot < N; slot += NW) {
+    const int pos = wg_pos0 + slot, tok = a.v.perm[pos], it = a.v.tok_item[pos];
+    const int b0 = a.v.slc_batch[it], nb = a.v.slc_batch[it + 1] - b0;
+    topk_slot<INT_MAX>(S + (size_t)slot * s_max, s_max, nb, a.v.T, b0, a.idx + ((size_t)tok * a.v.Hkv + g) * a.v.T,
+                       S + (size_t)TW * s_max + (size_t)wid * ((s_max + 31) >> 5));
+  }
+}
+// (raises the dynamic LDS limit once per process for every instantiation)
+template <class Kernel>
+void allow_lds(std::once_flag &once, Kernel kernel) {
+  std::call_once(once, [&] { (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_CU); });
 }
 
-template <int D, int NW>
-void launch_cmp(const FwdArgs &a, hipStream_t s) {
-  static std::once_flag once;  // raise the dynamic LDS limit once per process for this instantiation
-  std::call_once(once, [] { (void)hipFuncSetAttribute((const void *)m_cmp_fwd<D, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
+template <int D, int HS, int CW, int KS, int ST>
+void launch_scores(const FwdArgs &a, hipStream_t s) {
+  static std::once_flag once;
+  allow_lds(once, m_cmp_scores<D, HS, CW, KS, ST>);
+  constexpr int TW = CW * 32 / HS;
+  m_cmp_scores<D, HS, CW, KS, ST><<<dim3(xcd_grid_size((a.v.N + TW - 1) / TW, a.v.Hkv)), 64 * CW * KS, scores_lds_bytes(D, HS, CW, CW * KS, ST, a.v.s_max), s>>>(a);
+}
+template <int D, int HS>
+void launch_scores(const FwdArgs &a, CmpForm form, hipStream_t s) {
+  if constexpr (HS > 1)
+    if (form == CmpForm::tiles_in_lds) return launch_scores<D, HS, 2, 2, 2>(a, s);
+  if (form == CmpForm::own_tiles_4) launch_scores<D, HS, 1, 4, 0>(a, s);
+  else launch_scores<D, HS, 1, 8, 0>(a, s);
+}
+
+template <int D, int NW, bool CMP>
+void launch_walk(const FwdArgs &a, hipStream_t s) {
   const int tw = 32 * NW / a.v.hs;
-  m_cmp_fwd<D, NW><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, cmp_lds_bytes<D>(NW, a.v.hs, a.v.s_max), s>>>(a);
+  m_walk_fwd<D, NW, CMP><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, 4 * T32<D, true>::BYTES + 16 + 32 * NW * 4, s>>>(a);
+}
+
+template <int D>
+void launch_cmp(const FwdArgs &a, hipStream_t s) {
+  constexpr int NW = 4;
+  const CmpForm form = cmp_form(D, a.v.hs, a.v.s_max);
+  if (form == CmpForm::one_kernel) {
+    static std::once_flag once;
+    allow_lds(once, m_cmp_fwd<D, NW>);
+    const int tw = 32 * NW / a.v.hs;
+    m_cmp_fwd<D, NW><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, cmp_lds_bytes(D, NW, a.v.hs, a.v.s_max), s>>>(a);
+    return;
+  }
+  launch_walk<D, NW, true>(a, s);
+  switch (a.v.hs) {
+    case 1: return launch_scores<D, 1>(a, form, s);
+    case 2: return launch_scores<D, 2>(a, form, s);
+    case 4: return launch_scores<D, 4>(a, form, s);
+    case 8: return launch_scores<D, 8>(a, form, s);
+    default: return launch_scores<D, 16>(a, form, s);
+  }
 }
 
 template <int D>
 int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, const SelIndex &sel, const SlcPartials &part, hipStream_t s) {
   {
     ProfScope ps(PROF_CMP_FWD, s);
-    const int nw = cmp_waves<D>(a.v.hs, a.v.s_max);
-    if (nw == 4) launch_cmp<D, 4>(a, s);
-    else if (nw == 8) launch_cmp<D, 8>(a, s);
-    else launch_cmp<D, 2>(a, s);
+    launch_cmp<D>(a, s);
   }
   {
     ProfScope ps(PROF_FWD_INVERT, s);
@@ -334,9 +455,7 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, co
   }
   {
     ProfScope ps(PROF_WIN_FWD, s);
-    constexpr int NW = 4;
-    const int tw = 32 * NW / a.v.hs;
-    m_win_fwd<D, NW><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, 4 * T32<D, true>::BYTES + 16 + 32 * NW * 4, s>>>(a);
+    launch_walk<D, 4, false>(a, s);
   }
   {
     ProfScope ps(PROF_COMBINE, s);
@@ -348,19 +467,10 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, co
 
 }  // namespace
 
-// Largest dynamic LDS request of the forward kernels for this problem (bytes).
-size_t mfma_fwd_lds_bytes(int D, int hs, int s_max) {
-  switch (D) {
-    case 32: return cmp_lds_bytes<32>(cmp_waves<32>(hs, s_max), hs, s_max);
-    case 64: return cmp_lds_bytes<64>(cmp_waves<64>(hs, s_max), hs, s_max);
-    default: return cmp_lds_bytes<128>(cmp_waves<128>(hs, s_max), hs, s_max);
-  }
-}
-
 int mfma_forward_kernels(const MfmaView &v, int D, const void *q, const void *gates, void *out, float *lse,
                          int32_t *idx, void *out_branch, SlcKeep keep, const SelIndex &sel, const SlcPartials &part,
                          hipStream_t s) {
-  FwdArgs a{v, (const bf16_t *)q, (bf16_t *)out_branch, lse, idx};
+  FwdArgs a{v, (const bf16_t *)q, (bf16_t *)out_branch, lse, idx, part.ml};
   switch (D) {
     case 32: return launch_forward<32>(a, (const bf16_t *)gates, (bf16_t *)out, keep, sel, part, s);
     case 64: return launch_forward<64>(a, (const bf16_t *)gates, (bf16_t *)out, keep, sel, part, s);

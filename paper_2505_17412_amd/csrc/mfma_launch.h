@@ -3,7 +3,6 @@
 #pragma once
 #include "mfma_common.h"
 
-size_t mfma_fwd_lds_bytes(int D, int hs, int s_max);
 struct SelIndex;
 struct SlcPartials;
 struct SlcKeep { bool branch, lse; };  // whether the selection branch's output and its log-sum-exp are read by anybody

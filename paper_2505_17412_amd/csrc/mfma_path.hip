@@ -1,6 +1,7 @@
 // bf16 MFMA path: workspace layout, K/V preparation (sort, transpose, mean pool) and launch sequence.
 #include "mfma_common.h"
 #include "mfma_launch.h"
+#include "cmp_form.h"
 #include "profile.h"
 
 // The one-pass selection backward takes a block's keys in segments, each a whole pass over the query rows: it is the faster form
@@ -214,7 +215,7 @@ bool mfma_supported(const ssa_ctx &c) {
   if (c.hs != 1 && c.hs != 2 && c.hs != 4 && c.hs != 8 && c.hs != 16) return false;
   // the kernels index their staged arrays with 32-bit element offsets
   if ((unsigned long long)(c.N + 2 * SSA_KEY_PAD) * c.Hq * c.d >= (1ull << 31)) return false;
-  if (mfma_fwd_lds_bytes(c.d, c.hs, c.blk->s_max) > 150 * 1024) return false;
+  if (!cmp_rows_fit(c.d, c.hs, c.blk->s_max)) return false;
   // rows of the per-(token, head, selected block) partial arrays are numbered in 32 bits, list entries in int
   if ((unsigned long long)c.N * c.Hq * c.T >= (1ull << 32)) return false;
   if ((unsigned long long)c.N * c.Hkv * c.T >= (1ull << 31)) return false;

@@ -1,7 +1,7 @@
 """GPU: the 32 x 32 tiles of the attention kernels at their edges, on sequences, where the lengths of the blocks can be set: key
 ranges of one key to one key past a segment of 256, a last tile of 1, 31 or 32 keys, 2 to 32 tokens in a wavefront's 32 columns with
-a remainder, token counts that leave the last workgroup or chunk a single token, every head grouping and head dimension.
-Tolerances of the other parity tests."""
+a remainder, token counts that leave the last workgroup or chunk a single token, every head grouping and head dimension; and each
+form of the compression branch.  Tolerances of the other parity tests."""
 import numpy as np
 import pytest
 
@@ -26,12 +26,19 @@ def test_tile_edges(seed, lens, hq, hkv, d, l, topk):
     full_parity(inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk))
 
 
-# selection blocks of an item where the compression kernel's top-k takes another form (1024, 2048, 4096) and where the score rows
-# leave room for eight, four or two wavefronts
-@pytest.mark.parametrize("seed,lens,hq,hkv,d", [
-    (911, (8192, 40), 16, 2, 64), (912, (8193,), 16, 2, 64), (913, (40, 16385), 16, 2, 32), (914, (16384,), 8, 1, 64),
-    (915, (32768,), 16, 1, 32), (916, (32777,), 16, 1, 32), (917, (6100,), 8, 1, 128),
-])
-def test_many_selection_blocks(seed, lens, hq, hkv, d):
+# Selection blocks of an item where the top-k search takes another form (1024, 2048, 4096), and where the score rows lead to each form of
+# the compression branch (csrc/cmp_form.h; tests/test_cmp_form.py holds the last column to that rule).
+MANY_BLOCKS = [
+    (911, (8192, 40), 16, 2, 64, "tiles_in_lds"), (912, (8193,), 16, 2, 64, "tiles_in_lds"), (913, (40, 16385), 16, 2, 32, "own_tiles_4"),
+    (914, (16384,), 8, 1, 64, "own_tiles_4"), (915, (32768,), 16, 1, 32, "own_tiles_4"), (916, (32777,), 16, 1, 32, "own_tiles_4"),
+    (917, (6100,), 8, 1, 128, "tiles_in_lds"), (918, (4400, 300), 16, 2, 64, "one_kernel"), (919, (8192,), 16, 1, 32, "one_kernel"),
+    (920, (33, 7201), 4, 2, 64, "own_tiles_8"), (921, (3500, 7), 2, 2, 32, "own_tiles_8"), (922, (14401,), 4, 1, 128, "own_tiles_8"),
+    (923, (61, 59, 300), 3, 3, 64, "own_tiles_4"), (924, (45, 1, 75), 4, 1, 128, "tiles_in_lds"),
+    (925, (999, 45), 8, 2, 64, "one_kernel"),
+]
+
+
+@pytest.mark.parametrize("seed,lens,hq,hkv,d,form", MANY_BLOCKS)
+def test_many_selection_blocks(seed, lens, hq, hkv, d, form):
     wl = inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=(4, 8, 16), topk=8)
-    full_parity(wl, queries=np.arange(0, wl.n_tokens, 211, dtype=np.int32))
+    full_parity(wl, queries=np.arange(0, wl.n_tokens, 211 if wl.n_tokens > 1000 else 1, dtype=np.int32))

@@ -5,9 +5,9 @@ With Q = 0 every compression-attention probability of an item is the same number
 the blocks of the token's item ordered by (child count descending, block id ascending), with many exact ties (the rule
 stated after eq. (6): top-k by score; ties to the lowest id).  The expected sets below come from the oracle's block
 structure alone (child ranges per selection block, block ranges per item); no score is computed on the CPU.  The
-comparison is exact, with no margin.  One case per size class of the search inside the forward kernel (up to 512, up
-to 1024 and more than 1024 selection blocks per item), each with an item holding fewer than T blocks (all taken, padded
-with -1), for 8 and 16 query heads per KV head and for a small head group.
+comparison is exact, with no margin.  One case per size class of the search inside the forward kernels (up to 512, 1024,
+2048 and 4096 selection blocks per item in registers, more in rounds over LDS), most with an item holding fewer than T blocks
+(all taken, padded with -1), for 8 and 16 query heads per KV head and for small head groups.
 """
 import numpy as np
 import pytest
@@ -41,6 +41,11 @@ def closed_form_sets(wl):
     (84, 64, (3000, 4), 16, 2, 64, (2, 4, 4), 8, 1025, 4096),           # more than 1024 blocks per item
     (85, 32, (1000, 2), 8, 4, 64, (4, 8, 8), 6, 1, 512),                # 2 query heads per KV head
     (86, 64, (2500,), 16, 2, 128, (2, 4, 4), 16, 1025, 4096),           # head_dim 128, T = 16
+    (87, 64, (1900, 4), 16, 2, 64, (2, 4, 4), 8, 1025, 2048),           # (1024, 2048] blocks per item
+    (88, 64, (6000, 3), 16, 2, 64, (2, 4, 4), 8, 2049, 4096),           # (2048, 4096]
+    (89, 128, (5400, 3), 16, 1, 64, (2, 4, 4), 8, 4097, 8000),          # more: rounds over LDS
+    (90, 128, (5400, 20), 16, 1, 32, (2, 4, 4), 33, 4097, 8000),
+    (91, 32, (700, 5), 4, 4, 64, (4, 8, 8), 8, 1, 64),                  # ungrouped heads: 32 tokens' rows per workgroup
 ])
 def test_zero_queries_select_by_child_count_on_the_matrix_core_path(seed, grid, n, hq, hkv, d, m, topk, lo, hi):
     wl = inputs.random_points_workload(seed, grid, n, hq, hkv, d, m, topk, "bf16")

@@ -39,3 +39,27 @@ def test_one_pass_selection_backward_fits_its_registers(tmp_path):
     assert len(kernels) == 4  # blocks of one segment: head_dim 32 and 64, 4 and 8 wavefronts
     for name, r in kernels.items():
         assert r["Occupancy"] >= 2 and r["VGPRs Spill"] == 0, (name, r)
+
+
+def test_compression_kernels_keep_their_wavefronts(tmp_path):
+    """Three wavefronts per SIMD without a spill up to head_dim 64; at 128 two, with no more spilled than was measured."""
+    all_ = resources("mfma_fwd.hip", tmp_path)
+    kernels = {k: v for k, v in all_.items() if re.search(r"m_cmp_fwdILi|m_walk_fwdILi", k)}
+    assert len(kernels) == 9  # head dimensions 32, 64, 128: one kernel, compression walk, window walk
+    for name, r in kernels.items():
+        wide = "ILi128E" in name
+        assert r["Occupancy"] >= (2 if wide else 3), (name, r)
+        assert r["VGPRs Spill"] <= (0 if not wide or "Lb0" in name else 6 if "m_walk" in name else 26), (name, r)
+    scores = {k: v for k, v in all_.items() if "m_cmp_scoresILi" in k}
+    assert len(scores) == 3 * (5 * 2 + 4)  # 1 to 16 heads per KV head by four and eight wavefronts, 2 to 16 with tiles in LDS
+    for name, r in scores.items():
+        assert r["Occupancy"] >= (3 if "ILi128E" in name else 4) and r["VGPRs Spill"] == 0, (name, r)
+
+
+def test_selection_and_dq_kernels_keep_their_wavefronts(tmp_path):
+    kernels = {**resources("mfma_slc.hip", tmp_path), **resources("mfma_bwd.hip", tmp_path)}
+    want = {"m_slc_fwd_bcILi32E": 4, "m_slc_fwd_bcILi64E": 4, "m_slc_fwd_bcILi128E": 2, "m_bwd_dq_bcILi32E": 4, "m_bwd_dq_bcILi64E": 2,
+            "m_bwd_dq_bcILi128E": 2, "m_bwd_dqILi32E": 4, "m_bwd_dqILi64E": 3, "m_bwd_dqILi128E": 2}
+    for part, waves in want.items():
+        found = [r for name, r in kernels.items() if part in name]
+        assert len(found) == 1 and found[0]["Occupancy"] >= waves and found[0]["VGPRs Spill"] == 0, (part, found)
