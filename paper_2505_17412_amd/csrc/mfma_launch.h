@@ -20,7 +20,7 @@ struct SelIndex {
   int32_t *chunk_start, *part_row_start;  // [Hkv*Ns+1] each: dK/dV work chunks and partial-sum rows per key
   int32_t *bc_chunk_start;        // [Hkv*Ns+1]: work chunks of the block-centric forward / dQ kernels
   uint32_t *bins;                 // bucket counters of the two execution orders
-  uint32_t *ticket;               // [2] workgroup counters; an earlier kernel on the stream sets the first to 0
+  uint32_t *ticket;               // counter of the first pass's workgroups; an earlier kernel on the stream sets it to 0
   int4 *slot, *bc_slot;           // bucket, number in the bucket, key, chunk of every chunk
   ChunkRef *order, *bc_order;     // the chunks of either chunking in execution order (see m_chunk_order)
   int32_t *base;                  // [2 * keys] with by_length: first place of every key's chunks in the two orders

@@ -5,12 +5,14 @@
 // matrix in LDS (integer OR: order independent), so that the population count below a bit is the entry's rank inside its
 // tile; per-tile counts are turned into offsets, and every entry then writes itself to its final place.  Integer work
 // only, and the lists do not depend on scheduling.
-// Bound: latency of two to four small dependent launches (every pass reads or writes a few MB), so a tile is small enough that all
-// its loads are in flight at once, and prefix sums over keys are the work of whichever workgroup of the pass before ends last.
+// Bound: latency of two to five small dependent launches (every pass reads or writes a few MB), so a tile is small enough that all
+// its loads are in flight at once, and in small problems the prefix sums are the work of whichever workgroup of the first pass ends last.
 // Kernel times: 11k tokens, top-8, 226 lists: 22 us in two launches (25 us in five); 2k tokens, 66 lists: 18 us (28); 62k tokens,
 // top-16, 932 lists: 59 us in four (61 in five).
 #include "mfma_launch.h"
 #include "sel_order.h"
+
+#include <mutex>
 
 namespace {
 
@@ -48,7 +50,7 @@ __device__ inline bool last_workgroup(uint32_t *ticket, uint32_t total) {
 }
 
 struct ScanArgs {
-  const uint32_t *counts;      // [n] entries per key
+  uint32_t *counts;            // [n] entries per key
   const int32_t *slc_start;
   int32_t *start, *chunk_start, *part_row_start, *bc_chunk_start;  // [n + 1] each
   int n, Ns, chunk_len, bc_chunk_len;
@@ -145,18 +147,15 @@ __device__ inline void order_by_length(const ScanArgs &a, int32_t *base, int32_t
   }
 }
 
-// Pass 1: entries per (key, tile).  cnt[key][stride].  Workgroup column (., 0, 0) also clears the counters of the later passes.  With
+// Pass 1: entries per (key, tile).  cnt[key][stride].  Workgroup column (., 0, 0) also clears the counters of the last pass.  With
 // a ticket (a word that is 0 when the kernel starts) the last workgroup goes on with passes 2 and 3, a thread per key.
-__global__ __launch_bounds__(SEL_THREADS) void m_sel_count(SelArgs a, int n_tiles, int stride, uint32_t *__restrict__ cnt,
-                                                           uint32_t *__restrict__ counts, uint32_t *__restrict__ bins, int bins_stride,
-                                                           int n_bins, uint32_t *ticket, uint32_t *scan_ticket, ScanArgs sc,
-                                                           int32_t *base, int32_t *bc_base) {
+__global__ __launch_bounds__(SEL_THREADS) void m_sel_count(SelArgs a, int n_tiles, int stride, uint32_t *cnt,
+                                                           uint32_t *__restrict__ bins, int bins_stride, int n_bins, uint32_t *ticket,
+                                                           ScanArgs sc, int32_t *base, int32_t *bc_base) {
   extern __shared__ __align__(16) uint32_t sel_bits[];  // [nb][TILE_WORDS]
   const int tile = blockIdx.x, g = blockIdx.y, b0 = blockIdx.z * KEY_TILE, nb = min(KEY_TILE, a.Ns - b0);
-  if (g == 0 && blockIdx.z == 0) {
+  if (g == 0 && blockIdx.z == 0)
     for (int i = tile * SEL_THREADS + threadIdx.x; i < n_bins; i += n_tiles * SEL_THREADS) bins[i] = bins[bins_stride + i] = 0u;
-    if (tile == 0 && threadIdx.x == 0) *scan_ticket = 0u;
-  }
   for (int i = threadIdx.x; i < nb * TILE_WORDS; i += SEL_THREADS) sel_bits[i] = 0u;
   __syncthreads();
   const int p0 = tile * POS_TILE, npos = min(POS_TILE, a.N - p0), ne = npos * a.T;
@@ -173,8 +172,10 @@ __global__ __launch_bounds__(SEL_THREADS) void m_sel_count(SelArgs a, int n_tile
   __syncthreads();
   for (int i = threadIdx.x; i < nb; i += SEL_THREADS) {
     const uint4 x = *reinterpret_cast<const uint4 *>(sel_bits + i * TILE_WORDS), y = *reinterpret_cast<const uint4 *>(sel_bits + i * TILE_WORDS + 4);
-    store_shared(&cnt[((size_t)g * a.Ns + b0 + i) * stride + tile],
-                 __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w) + __popc(y.x) + __popc(y.y) + __popc(y.z) + __popc(y.w));
+    const uint32_t count = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w) + __popc(y.x) + __popc(y.y) + __popc(y.z) + __popc(y.w);
+    uint32_t *to = &cnt[((size_t)g * a.Ns + b0 + i) * stride + tile];
+    if (ticket) store_shared(to, count);
+    else *to = count;  // (to the next kernel; written through 60k tokens' counts take 40 us for 27)
   }
   if (!ticket || !last_workgroup(ticket, gridDim.x * gridDim.y * gridDim.z)) return;
   for (int key = threadIdx.x; key < sc.n; key += SEL_THREADS) {
@@ -197,50 +198,50 @@ __global__ __launch_bounds__(SEL_THREADS) void m_sel_count(SelArgs a, int n_tile
         if (t0 + u < n4) row[t0 + u] = make_uint4(c[0], c[1], c[2], c[3]);
       }
     }
-    counts[key] = run;
+    sc.counts[key] = run;
   }
   __syncthreads();
   scan_counts<SEL_THREADS>(sc);
   if (base) order_by_length<SEL_THREADS>(sc, base, bc_base);
 }
 
-// Pass 2: per key (one wavefront each) the exclusive prefix of its counts over the tiles, in place, and their sum; the last workgroup
-// goes on with pass 3, the prefix sums over the keys.
-__global__ __launch_bounds__(256) void m_sel_scan_tiles(uint32_t *__restrict__ cnt, int n_keys, int n_tiles, int stride,
-                                                        uint32_t *__restrict__ counts, uint32_t *ticket, ScanArgs sc,
-                                                        int32_t *base, int32_t *bc_base) {
+// Pass 2: per key (one wavefront each) the exclusive prefix of its counts over the tiles, in place, and their sum.
+__global__ __launch_bounds__(256) void m_sel_scan_tiles(uint32_t *__restrict__ cnt, int n_keys, int n_tiles, int stride, uint32_t *__restrict__ counts) {
   const int key = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (key < n_keys) {
-    uint32_t *row = cnt + (size_t)key * stride;
-    uint32_t carry = 0;
-    for (int t0 = 0; t0 < n_tiles; t0 += 256) {  // four tiles per lane and round
-      uint32_t v[4], own = 0;
+  if (key >= n_keys) return;
+  uint32_t *row = cnt + (size_t)key * stride;
+  uint32_t carry = 0;
+  for (int t0 = 0; t0 < n_tiles; t0 += 256) {  // four tiles per lane and round
+    uint32_t v[4], own = 0;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int t = t0 + lane * 4 + u;
-        v[u] = t < n_tiles ? row[t] : 0u;
-        own += v[u];
-      }
-      uint32_t incl = own;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = __shfl_up(incl, off);
-        if (lane >= off) incl += o;
-      }
-      uint32_t run = carry + incl - own;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int t = t0 + lane * 4 + u;
-        if (t < n_tiles) row[t] = run;
-        run += v[u];
-      }
-      carry += __shfl(incl, 63);
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + lane * 4 + u;
+      v[u] = t < n_tiles ? row[t] : 0u;
+      own += v[u];
     }
-    if (lane == 0) store_shared(&counts[key], carry);
+    uint32_t incl = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    uint32_t run = carry + incl - own;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + lane * 4 + u;
+      if (t < n_tiles) row[t] = run;
+      run += v[u];
+    }
+    carry += __shfl(incl, 63);
   }
-  if (!last_workgroup(ticket, gridDim.x)) return;
-  scan_counts<256>(sc);
-  if (base) order_by_length<256>(sc, base, bc_base);
+  if (lane == 0) counts[key] = carry;
+}
+
+// Pass 3, one workgroup: the prefix sums over the keys.  (By the workgroup of pass 2 that ends last, of 256 threads, instead: 62k tokens,
+// 1300 lists 14 us for 5 + 6 in two launches; 24k tokens, 4200 lists 44 for 5 + 14; 60k, 8200 lists 62 for 7 + 24.)
+__global__ __launch_bounds__(1024) void m_sel_scan_keys(ScanArgs sc, int32_t *base, int32_t *bc_base) {
+  scan_counts<1024>(sc);
+  if (base) order_by_length<1024>(sc, base, bc_base);
 }
 
 // Where the execution order of one chunking is prepared: a chunk's bucket (see m_chunk_order) is counted by the thread
@@ -359,7 +360,7 @@ Plan plan(int N, int Hkv, int T, int Ns) {
   p.cnt = take(keys * tile_stride(N) * 4); p.counts = take(keys * 4 + 4); p.base = take(2 * keys * 4); p.start = take((keys + 1) * 4);
   p.list = take(entries * 4); p.rank = take(entries);
   p.cstart = take((keys + 1) * 4); p.prow = take((keys + 1) * 4); p.bcstart = take((keys + 1) * 4);
-  p.bins = take(2 * ORDER_BINS * 4 + 2 * 4);
+  p.bins = take(2 * ORDER_BINS * 4 + 4);
   // at most one partly filled chunk per key on top of the full ones
   const size_t bc = entries / BC_CHUNK_MIN + keys + 8, dkv = entries / 256 + keys + 8;
   p.bcslot = take(bc * sizeof(int4)); p.slot = take(dkv * sizeof(int4));
@@ -391,8 +392,7 @@ SelIndex sel_index_carve(void *ws_, int N, int Hkv, int T, int Ns, int chunk_len
 int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_start, int N, int Hkv, int T, int Ns,
                     const SelIndex &x, bool caller_indices, bool want_bc_order, bool want_dkv_order, hipStream_t s) {
   const int tiles = pos_tiles(N), stride = tile_stride(N), keys = Hkv * Ns;
-  // The last workgroup of the first pass does the second and third as well where the counts are few (a thread per key); else
-  // the last of the second does the third.
+  // The last workgroup of the first pass does the second and third as well where the counts are few (a thread per key).
   const bool fused = (long long)keys * stride <= FUSED_COUNTS;
   int32_t *const base = x.by_length ? x.base : nullptr, *const bc_base = x.by_length ? x.base + keys : nullptr;
   const SelOrder ord = sel_order(N, Hkv);
@@ -403,9 +403,13 @@ int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_
   const ScanArgs sc{x.counts, slc_start, x.start, x.chunk_start, x.part_row_start, x.bc_chunk_start, keys, Ns, x.chunk_len, x.bc_chunk_len};
   OrderArgs bc{x.bc_chunk_start, x.bins, x.bc_slot, want_bc_order ? x.bc_order : nullptr, x.bc_chunk_len, bc_base};
   OrderArgs dkv{x.chunk_start, x.bins + ORDER_BINS, x.slot, want_dkv_order ? x.order : nullptr, x.chunk_len, base};
-  m_sel_count<<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.counts, x.bins, ORDER_BINS, n_bins, fused ? x.ticket : nullptr,
-                                             x.ticket + 1, sc, base, bc_base);
-  if (!fused) m_sel_scan_tiles<<<(keys + 3) / 4, 256, 0, s>>>(x.cnt, keys, tiles, stride, x.counts, x.ticket + 1, sc, base, bc_base);
+  static std::once_flag once;  // its own LDS stands beside up to 64 KB of bits
+  std::call_once(once, [] { (void)hipFuncSetAttribute((const void *)m_sel_count, hipFuncAttributeMaxDynamicSharedMemorySize, KEY_TILE * TILE_WORDS * 4); });
+  m_sel_count<<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.bins, ORDER_BINS, n_bins, fused ? x.ticket : nullptr, sc, base, bc_base);
+  if (!fused) {
+    m_sel_scan_tiles<<<(keys + 3) / 4, 256, 0, s>>>(x.cnt, keys, tiles, stride, x.counts);
+    m_sel_scan_keys<<<1, 1024, 0, s>>>(sc, base, bc_base);
+  }
   if (T <= 16) m_sel_fill<1><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, ord, caller_indices);
   else if (T <= 32) m_sel_fill<2><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, ord, caller_indices);
   else m_sel_fill<4><<<grid, SEL_THREADS, lds, s>>>(a, tiles, stride, x.cnt, x.start, x.list, x.rank, bc, dkv, slc_start, ord, caller_indices);
