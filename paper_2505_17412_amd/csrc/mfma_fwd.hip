@@ -224,17 +224,18 @@ __device__ inline void score_walk(const MfmaView &v, const bf16_t *Kg, uint32_t 
 // 64 the first walk takes 256 matrix cycles and about 280 of exponentials, multiply-adds, conversions and sums (a synthetic copy:
 // 226 ns per SIMD), the second 128 and about 250; the kernel takes about 1.45 times that.  32 query columns per wavefront against
 // 16: half the LDS operands per matrix cycle, half the staging and barriers per column.  Three wavefronts per SIMD (168 registers,
-// none spilled, and LDS for three workgroups); two: 17 % slower.  At head_dim 128 two, with 26 of 256 registers spilled outside the
-// tile code's operands; in two kernels, whose walk spills 6, 62k tokens and 662 blocks take 3400 us for 3130.  The sums of the first walk cost 5 % more in the order that keeps the selected
+// two more spilled, and LDS for three workgroups); two: 17 % slower.  At head_dim 128 two, with 30 spilled beside 256; in two kernels,
+// whose walk spills 6, 62k tokens and 662 blocks take 3400 us for 3130.  The sums of the first walk cost 5 % more in the order that keeps the selected
 // sets what they were (SumInOrder; 1290 us without).  62k tokens, 2247 pooled keys, 16 heads of 64: 1516 -> 1370 us (16 columns
 // before); 65k tokens in sequences 880 -> 830; 11k tokens 94 -> 79; 2k tokens, 32 heads of 32: 19.6 -> 14; 153k tokens, 3884 pooled
 // keys, heads of 128: 11.5 -> 9.1 ms.
-template <int D, int NW>
+template <int D, int HS, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 3 : 2))) void m_cmp_fwd(FwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   using T = T32<D, true>;
   unsigned char *stage0 = smem;
-  const int hs = a.v.hs, s_max = a.v.s_max, TW = 32 * NW / hs;
+  constexpr int TPW = 32 / HS, TW = NW * TPW;  // tokens per wavefront, per workgroup
+  const int s_max = a.v.s_max;
   int *again = (int *)(stage0 + 4 * T::BYTES);
   float *lse_l = (float *)(again + 4);       // [32*NW] per query row
   int *tok_info = (int *)(lse_l + 32 * NW);  // [3][TW]
@@ -270,16 +271,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
 #pragma unroll
   for (int i = 0; i < 16; ++i) l16[i] = lse_l[wid * 32 + t32_row(i)];
   const ScoreRows rows{S, tok_info, TW, s_max, re, s0, one};
-  auto walk = [&](auto hs_c) {  // a walk per head count: the tile code is straight-line.  (Two tiles per step: half the barriers)
-    score_walk<D, decltype(hs_c)::value, 64 * NW, 2, 1>(a.v, Kg, stride, qop, stage0, rs, 0, l16, rows, wid * 32 / decltype(hs_c)::value, sl2);
-  };
-  if (hs == 8) walk(std::integral_constant<int, 8>());
-  else if (hs == 16) walk(std::integral_constant<int, 16>());
-  else walk(std::integral_constant<int, 4>());
+  score_walk<D, HS, 64 * NW, 2, 1>(a.v, Kg, stride, qop, stage0, rs, 0, l16, rows, wid * TPW, sl2);  // (two tiles per step: half the barriers)
   // ---- top-k: each wavefront serves its own token slots, one after the other
-  const int spw = 32 / hs;  // token slots per wavefront
-  for (int tl = 0; tl < spw; ++tl) {
-    const int slot = wid * spw + tl, pos = wg_pos0 + slot;
+  for (int tl = 0; tl < TPW; ++tl) {
+    const int slot = wid * TPW + tl, pos = wg_pos0 + slot;
     if (pos >= a.v.N) break;
     const int tok = a.v.perm[pos], it = a.v.tok_item[pos];
     const int b0 = a.v.slc_batch[it], nb = a.v.slc_batch[it + 1] - b0;
@@ -291,6 +286,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
 // Window branch: keys are the tokens of the query's own window.  62k tokens, 16 heads of 64: 154 -> 105 us (16 columns per wavefront
 // before), 65k tokens in windows of 512: 270 -> 190, 153k tokens, heads of 128: 1109 -> 720.
 // CMP: the compression branch alone, over the pooled keys of the query's item, where m_cmp_scores forms the selection scores.
+constexpr int WIN_WAVES = 4;
 template <int D, int NW, bool CMP>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_walk_fwd(FwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -416,24 +412,29 @@ void launch_walk(const FwdArgs &a, hipStream_t s) {
   m_walk_fwd<D, NW, CMP><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, 4 * T32<D, true>::BYTES + 16 + 32 * NW * 4, s>>>(a);
 }
 
-template <int D>
+template <int D, int HS>
 void launch_cmp(const FwdArgs &a, hipStream_t s) {
   constexpr int NW = 4;
-  const CmpForm form = cmp_form(D, a.v.hs, a.v.s_max);
-  if (form == CmpForm::one_kernel) {
-    static std::once_flag once;
-    allow_lds(once, m_cmp_fwd<D, NW>);
-    const int tw = 32 * NW / a.v.hs;
-    m_cmp_fwd<D, NW><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, cmp_lds_bytes(D, NW, a.v.hs, a.v.s_max), s>>>(a);
-    return;
-  }
+  const CmpForm form = cmp_form(D, HS, a.v.s_max);
+  if constexpr (HS >= 4)
+    if (form == CmpForm::one_kernel) {
+      static std::once_flag once;
+      allow_lds(once, m_cmp_fwd<D, HS, NW>);
+      constexpr int TW = 32 * NW / HS;
+      m_cmp_fwd<D, HS, NW><<<dim3(xcd_grid_size((a.v.N + TW - 1) / TW, a.v.Hkv)), 64 * NW, cmp_lds_bytes(D, NW, HS, a.v.s_max), s>>>(a);
+      return;
+    }
   launch_walk<D, NW, true>(a, s);
+  launch_scores<D, HS>(a, form, s);
+}
+template <int D>
+void launch_cmp(const FwdArgs &a, hipStream_t s) {
   switch (a.v.hs) {
-    case 1: return launch_scores<D, 1>(a, form, s);
-    case 2: return launch_scores<D, 2>(a, form, s);
-    case 4: return launch_scores<D, 4>(a, form, s);
-    case 8: return launch_scores<D, 8>(a, form, s);
-    default: return launch_scores<D, 16>(a, form, s);
+    case 1: return launch_cmp<D, 1>(a, s);
+    case 2: return launch_cmp<D, 2>(a, s);
+    case 4: return launch_cmp<D, 4>(a, s);
+    case 8: return launch_cmp<D, 8>(a, s);
+    default: return launch_cmp<D, 16>(a, s);
   }
 }
 
@@ -455,7 +456,7 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, co
   }
   {
     ProfScope ps(PROF_WIN_FWD, s);
-    launch_walk<D, 4, false>(a, s);
+    launch_walk<D, WIN_WAVES, false>(a, s);
   }
   {
     ProfScope ps(PROF_COMBINE, s);

@@ -149,7 +149,7 @@ __device__ inline void order_by_length(const ScanArgs &a, int32_t *base, int32_t
 
 // Pass 1: entries per (key, tile).  cnt[key][stride].  Workgroup column (., 0, 0) also clears the counters of the last pass.  With
 // a ticket (a word that is 0 when the kernel starts) the last workgroup goes on with passes 2 and 3, a thread per key.
-__global__ __launch_bounds__(SEL_THREADS) void m_sel_count(SelArgs a, int n_tiles, int stride, uint32_t *cnt,
+__global__ __launch_bounds__(SEL_THREADS) void m_sel_count(SelArgs a, int n_tiles, int stride, uint32_t *__restrict__ cnt,
                                                            uint32_t *__restrict__ bins, int bins_stride, int n_bins, uint32_t *ticket,
                                                            ScanArgs sc, int32_t *base, int32_t *bc_base) {
   extern __shared__ __align__(16) uint32_t sel_bits[];  // [nb][TILE_WORDS]

@@ -42,14 +42,14 @@ def test_one_pass_selection_backward_fits_its_registers(tmp_path):
 
 
 def test_compression_kernels_keep_their_wavefronts(tmp_path):
-    """Three wavefronts per SIMD without a spill up to head_dim 64; at 128 two, with no more spilled than was measured."""
+    """Three wavefronts per SIMD up to head_dim 64, at 128 two, with no more spilled than was measured."""
     all_ = resources("mfma_fwd.hip", tmp_path)
     kernels = {k: v for k, v in all_.items() if re.search(r"m_cmp_fwdILi|m_walk_fwdILi", k)}
-    assert len(kernels) == 9  # head dimensions 32, 64, 128: one kernel, compression walk, window walk
+    assert len(kernels) == 3 * (3 + 2)  # head dimensions 32, 64, 128: one kernel for 4, 8, 16 heads, compression walk, window walk
     for name, r in kernels.items():
-        wide = "ILi128E" in name
-        assert r["Occupancy"] >= (2 if wide else 3), (name, r)
-        assert r["VGPRs Spill"] <= (0 if not wide or "Lb0" in name else 6 if "m_walk" in name else 26), (name, r)
+        assert r["Occupancy"] >= (2 if "ILi128E" in name else 3), (name, r)
+        most = {"m_cmp_fwdILi64": 2, "m_cmp_fwdILi128": 30, "m_walk_fwdILi128ELi4ELb1": 6}  # (the last: compression walk)
+        assert r["VGPRs Spill"] <= max((v for k, v in most.items() if k in name), default=0), (name, r)
     scores = {k: v for k, v in all_.items() if "m_cmp_scoresILi" in k}
     assert len(scores) == 3 * (5 * 2 + 4)  # 1 to 16 heads per KV head by four and eight wavefronts, 2 to 16 with tiles in LDS
     for name, r in scores.items():
