@@ -283,10 +283,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
   }
 }
 
-// Window branch: keys are the tokens of the query's own window.  62k tokens, 16 heads of 64: 154 -> 105 us (16 columns per wavefront
-// before), 65k tokens in windows of 512: 270 -> 190, 153k tokens, heads of 128: 1109 -> 720.
+// Window branch: keys are the tokens of the query's own window.  16 columns per wavefront -> now: 62k tokens, 16 heads of 64: 145 -> 115
+// us, 20k in three 64^3 shells 44 -> 31, 3k in sequences 21 -> 9, 24k in four shells, heads of 128: 80 -> 52.  64 query rows per
+// workgroup: the walk of one whose tokens lie in several windows starts where the first of them does, so a later window's first tile,
+// whose maximum is the reference, holds only some of 32 keys, and the largest weight is then seldom the exact 1 it is against its own
+// score.  With 128 rows there are twice as many such workgroups: 2-norm error of the output against 64 bits, 21k tokens in three 64^3 shells,
+// 2.7355e-3 for 2.7332e-3 (16 columns: 2.7335e-3), and the kernel takes 101 us at 62k tokens, but 17 at 3k.
 // CMP: the compression branch alone, over the pooled keys of the query's item, where m_cmp_scores forms the selection scores.
-constexpr int WIN_WAVES = 4;
+constexpr int WIN_WAVES = 2;
 template <int D, int NW, bool CMP>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_walk_fwd(FwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
