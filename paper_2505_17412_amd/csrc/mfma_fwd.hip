@@ -44,7 +44,7 @@ __device__ inline bool fwd_walk(T32State<D, Sum> &st, float *refs, const bf16x8 
   using T = T32<D, true>;
   t32_clear(st);
   const int first = walk_begin(rs);
-  t32_pipeline<D, 2, 64 * NW, 32, T32_PF>(src, stage0, first, re, [&](lds_cptr kt, int kb) {
+  t32_pipeline<D, 2, 64 * NW, 32>(src, stage0, first, re, [&](lds_cptr kt, int kb) {
     f32x16 s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
     if (kb == first || kb + 32 > re) t32_only_keys(s, kb, rs, re);
     if (kb == first) {
@@ -64,7 +64,7 @@ template <int D, int NW, class Sum>
 __device__ inline void fwd_walk_general(T32State<D, Sum> &st, const bf16x8 (&qop)[D / 16], const T32Src<2> &src, unsigned char *stage0, int rs, int re,
                                         int lo, int hi, const typename T32<D, true>::Lanes &ln, float sl2) {
   t32_clear(st);
-  t32_pipeline<D, 2, 64 * NW, 32, T32_PF>(src, stage0, walk_begin(rs), re, [&](lds_cptr kt, int kb) {
+  t32_pipeline<D, 2, 64 * NW, 32>(src, stage0, walk_begin(rs), re, [&](lds_cptr kt, int kb) {
     f32x16 s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
     t32_only_keys(s, kb, lo, hi);
     t32_softmax_running<D, true>(st, s, kt + T32<D, true>::BYTES, ln, sl2);
@@ -203,7 +203,7 @@ __device__ inline void score_walk(const MfmaView &v, const bf16_t *Kg, uint32_t 
   src.stride = stride;
 #pragma unroll
   for (int t = 0; t < ST; ++t) src.row[t] = Kg + (size_t)(32 * t) * stride;
-  t32_pipeline<D, ST, NTHR, 32 * ST, T32_PF>(src, stage0, rs, r.re, [&](lds_cptr kt, int kb0) {
+  t32_pipeline<D, ST, NTHR, 32 * ST>(src, stage0, rs, r.re, [&](lds_cptr kt, int kb0) {
     // the selection blocks of this lane's keys, requested before the matrix instructions
     int blk[ST / KS];
 #pragma unroll

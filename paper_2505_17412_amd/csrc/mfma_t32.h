@@ -363,45 +363,42 @@ struct T32Src {
   uint32_t stride;
 };
 
-constexpr int T32_PF = 1;  // steps the loads of a walk run ahead: a second register set costs more than it hides (spills)
-
 // Walk of a workgroup over the rows [rs, re) of NROW arrays in steps of STEP rows: 32-row tiles (one of each array; the arrays may
-// be consecutive tiles of one, with STEP a multiple of 32) go global -> registers -> LDS once per workgroup, loads PF (1 or 2) steps
-// ahead through as many register sets, two LDS stages and one barrier per step.  tile(first tile of the stage, first row) consumes a stage.
-// Rows past re are read as they lie in memory (padded arrays) and are the consumer's to mask.
-template <int D, int NROW, int NTHR, int STEP, int PF, class Tile>
+// be consecutive tiles of one, with STEP a multiple of 32) go global -> registers -> LDS once per workgroup, loads one step ahead (a
+// second register set costs more than it hides: spills), two LDS stages and one barrier per step.  tile(first tile of the stage, first
+// row) consumes a stage.  Rows past re are read as they lie in memory (padded arrays) and are the consumer's to mask.
+template <int D, int NROW, int NTHR, int STEP, class Tile>
 __device__ inline void t32_pipeline(const T32Src<NROW> &src, unsigned char *stage0, int rs, int re, Tile tile) {
   using T = T32<D, true>;
   constexpr int NI = (T::ITEMS + NTHR - 1) / NTHR;
   static_assert(T::ITEMS % NTHR == 0 || NI == 1, "whole tiles at a time");
   const bool mine = T::ITEMS >= NTHR || (int)threadIdx.x < T::ITEMS;
   const int row0 = threadIdx.x / T::SEGS, seg = threadIdx.x % T::SEGS;
-  struct Regs { bf16x8 r[NROW][NI]; } regs[PF];
-  auto load = [&](Regs &x, int kb) {
+  bf16x8 r[NROW][NI];
+  auto load = [&](int kb) {
     if (!mine) return;
 #pragma unroll
     for (int a = 0; a < NROW; ++a)
 #pragma unroll
       for (int i = 0; i < NI; ++i)
-        x.r[a][i] = ld8(src.row[a] + ((uint32_t)(kb + row0 + i * (NTHR / T::SEGS)) * src.stride + (uint32_t)(seg * 8)));
+        r[a][i] = ld8(src.row[a] + ((uint32_t)(kb + row0 + i * (NTHR / T::SEGS)) * src.stride + (uint32_t)(seg * 8)));
   };
-  auto step = [&](Regs &x, int buf, int kb) {
+  auto step = [&](int buf, int kb) {
     unsigned char *st = stage0 + buf * NROW * T::BYTES;
     if (mine)
 #pragma unroll
       for (int a = 0; a < NROW; ++a)
 #pragma unroll
-        for (int i = 0; i < NI; ++i) *reinterpret_cast<bf16x8 *>(st + a * T::BYTES + T::off(row0 + i * (NTHR / T::SEGS), seg)) = x.r[a][i];
-    if (kb + PF * STEP < re) load(x, kb + PF * STEP);
+        for (int i = 0; i < NI; ++i) *reinterpret_cast<bf16x8 *>(st + a * T::BYTES + T::off(row0 + i * (NTHR / T::SEGS), seg)) = r[a][i];
+    if (kb + STEP < re) load(kb + STEP);
     __syncthreads();
     tile((lds_cptr)st, kb);
   };
-  if (rs < re) load(regs[0], rs);
-  if (PF == 2 && rs + STEP < re) load(regs[PF - 1], rs + STEP);
+  if (rs < re) load(rs);
   for (int kb = rs; kb < re; kb += 2 * STEP) {
-    step(regs[0], 0, kb);
+    step(0, kb);
     if (kb + STEP >= re) break;
-    step(regs[PF - 1], 1, kb + STEP);
+    step(1, kb + STEP);
   }
   __syncthreads();
 }
