@@ -38,7 +38,7 @@ def algorithmic_flops(wl, blk_arrays, idx):
 
 # bench.py kernel name -> kernel name prefix in the rocprofv3 summaries
 ROCPROF_NAME = {
-    "cmp_fwd_scores_topk": "m_cmp_fwd<", "slc_fwd": "m_slc_fwd_bc<", "win_fwd": "m_win_fwd<",
+    "cmp_fwd_scores_topk": "m_cmp_fwd<", "slc_fwd": "m_slc_fwd_bc<", "win_fwd": "m_walk_fwd<{d}, 2, false>",
     "bwd_dq_cmp_win": "m_bwd_dq<{d},", "bwd_dq_slc": "m_bwd_dq_bc<{d},", "bwd_slc": "m_slc_bwd<{d},",
     "bwd_dkv_win": "m_bwd_dkv<{d}, {kb}, 0,", "bwd_dkv_slc": "m_bwd_dkv<{d}, {kb}, 1,", "bwd_dkv_cmp": "m_bwd_dkv<{d}, {kb}, 2,",
 }

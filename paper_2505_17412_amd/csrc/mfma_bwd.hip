@@ -136,8 +136,8 @@ __host__ __device__ inline size_t dq_lds_bytes() { return (size_t)4 * T32<D, tru
 // dQ of the compression branch, then of the (small) window branch, in the sorted token order; the sum is kept in fp32 by
 // sorted position (dQp) for the merge with the selection branch's partials.  Bound as the forward walk (per 32 x 32 scores 384
 // matrix cycles and about 280 of vector work at head_dim 64).  Three wavefronts per SIMD at head_dim 64 (163 registers).
-// 62k tokens, 16 heads of 64: 1140 -> 990 us (two blocks of 16 columns per wavefront at two per SIMD before), 21k tokens in three
-// 64^3 shells 155 -> 114, sequences 790 -> 665, 153k tokens, heads of 128: 9.0 -> 7.1 ms.
+// 62k tokens, 16 heads of 64: 1058 -> 932 us (two blocks of 16 columns per wavefront at two per SIMD before), 21k tokens in three
+// 64^3 shells 140 -> 111, sequences 748 -> 640, 153k tokens, heads of 128: 8.8 -> 6.8 ms.
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_bwd_dq(DqArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];

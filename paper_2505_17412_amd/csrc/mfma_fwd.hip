@@ -226,9 +226,9 @@ __device__ inline void score_walk(const MfmaView &v, const bf16_t *Kg, uint32_t 
 // 16: half the LDS operands per matrix cycle, half the staging and barriers per column.  Three wavefronts per SIMD (168 registers,
 // two more spilled, and LDS for three workgroups); two: 17 % slower.  At head_dim 128 two, with 30 spilled beside 256; in two kernels,
 // whose walk spills 6, 62k tokens and 662 blocks take 3400 us for 3130.  The sums of the first walk cost 5 % more in the order that keeps the selected
-// sets what they were (SumInOrder; 1290 us without).  62k tokens, 2247 pooled keys, 16 heads of 64: 1516 -> 1370 us (16 columns
-// before); 65k tokens in sequences 880 -> 830; 11k tokens 94 -> 79; 2k tokens, 32 heads of 32: 19.6 -> 14; 153k tokens, 3884 pooled
-// keys, heads of 128: 11.5 -> 9.1 ms.
+// sets what they were (SumInOrder).  62k tokens, 2247 pooled keys, 16 heads of 64: 1497 -> 1278 us (16 columns before); 65k tokens
+// in three sequences 848 -> 767; 11k tokens 94 -> 79; 2k tokens, 32 heads of 32: 21 -> 16; 153k tokens, 3884 pooled keys, heads of
+// 128: 11.4 -> 8.7 ms.
 template <int D, int HS, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 3 : 2))) void m_cmp_fwd(FwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
 }
 
 // Window branch: keys are the tokens of the query's own window.  16 columns per wavefront -> now: 62k tokens, 16 heads of 64: 145 -> 115
-// us, 20k in three 64^3 shells 44 -> 31, 3k in sequences 21 -> 9, 24k in four shells, heads of 128: 80 -> 52.  64 query rows per
+// us, 21k in three 64^3 shells 44 -> 33, 3k in sequences 21 -> 9, 24k in four shells, heads of 128: 80 -> 52.  64 query rows per
 // workgroup: the walk of one whose tokens lie in several windows starts where the first of them does, so a later window's first tile,
 // whose maximum is the reference, holds only some of 32 keys, and the largest weight is then seldom the exact 1 it is against its own
 // score.  With 128 rows there are twice as many such workgroups: 2-norm error of the output against 64 bits, 21k tokens in three 64^3 shells,

@@ -27,8 +27,8 @@ namespace {
 // but the last of a block 770 us).  32 columns per wavefront against 16: an operand read from LDS feeds twice the matrix work, and
 // the four SIMDs no longer ask LDS for every cycle it has.  Four wavefronts per SIMD at head_dim 64 (126 registers; the query rows of
 // the next step are loaded into the registers of this step's as soon as its last scores are formed).  A step's stores are not waited
-// for by the next one (t32_store_rows, wait_loads).  62k tokens, 16 heads of 64, top-16: 1010 -> 888 us; 11k tokens, top-8: 155 ->
-// 130; sequences of 64-key blocks 755 -> 650; 153k tokens, heads of 128: 10.4 -> 9.3 ms (with 16 columns per wavefront before).
+// for by the next one (t32_store_rows, wait_loads).  62k tokens, 16 heads of 64, top-16: 989 -> 874 us; 11k tokens, top-8: 154 ->
+// 114; sequences of 64-key blocks 736 -> 612; 153k tokens, heads of 128: 10.2 -> 9.2 ms (with 16 columns per wavefront before).
 // ---------------------------------------------------------------------------------------------------------
 struct BcFwdArgs {
   MfmaView v;
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
 // holds one selection block's K and V rows in LDS and runs through a chunk of the tokens that selected it; every
 // wavefront takes 32/h_s tokens per step on its own (query and dO rows in registers, no barrier, no column that did
 // not select the block).  One bf16 partial dQ per (token, KV head, selected block) goes to memory; m_dq_merge adds them
-// in rank order onto the fp32 compression + window part.  153k tokens, heads of 128: 14.3 -> 12.0 ms (16 columns before).
+// in rank order onto the fp32 compression + window part.  153k tokens, heads of 128: 13.9 -> 11.8 ms (16 columns before).
 // ---------------------------------------------------------------------------------------------------------
 struct BcDqArgs {
   MfmaView v;

@@ -8,7 +8,7 @@
 // Bound: latency of two to five small dependent launches (every pass reads or writes a few MB), so a tile is small enough that all
 // its loads are in flight at once, and in small problems the prefix sums are the work of whichever workgroup of the first pass ends last.
 // Kernel times: 11k tokens, top-8, 226 lists: 22 us in two launches (25 us in five); 2k tokens, 66 lists: 18 us (28); 62k tokens,
-// top-16, 932 lists: 59 us in four (61 in five).
+// top-16, 994 lists: 60 us in five.
 #include "mfma_launch.h"
 #include "sel_order.h"
 
