@@ -162,6 +162,36 @@ __device__ inline int token_of_sum(int u) {
   return HS >= 8 ? 2 * u + h : (8 * (HS * u >> 2) + 4 * h + (HS * u & 3)) / HS;
 }
 
+// Neighbouring keys whose additions go to the same word of a score row, eight of them as one (integer sums: the row holds the same
+// bits).  Keys 8*j .. +7 of a tile are the lanes that differ in bits 0, 1 and 3 (t32_order).  blk: the lane's selection block, which does
+// not fall with the key, so eight keys are of one block if the first and the last are.
+struct KeyGroups {
+  bool same;   // the lane's eight keys are of one block
+  bool adds;   // whether the lane adds: the first of eight, or any where they are of several blocks
+  bool often;  // at least half of the groups are of one block (uniform)
+  template <int CTRL>
+  __device__ static inline uint32_t from(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false); }
+  static constexpr int QUAD_FIRST = 0x00, QUAD_LAST = 0xFF, XOR_1 = 0xB1, XOR_2 = 0x4E, XOR_8 = 0x128;
+  __device__ inline explicit KeyGroups(int blk) {
+    const uint32_t first = from<QUAD_FIRST>(blk), last = from<QUAD_LAST>(blk), first8 = from<XOR_8>(first), last8 = from<XOR_8>(last);
+    same = threadIdx.x & 8 ? last == first8 : first == last8;
+    adds = !same || (threadIdx.x & 11) == 0;
+    often = __popcll(__ballot(same)) >= 32;
+  }
+  __device__ inline uint32_t sum(uint32_t x) const {
+    uint32_t s = x + from<XOR_1>(x);
+    s += from<XOR_2>(s);
+    s += from<XOR_8>(s);
+    return same ? s : x;
+  }
+};
+// Heads per KV head up to which the groups are looked for.  A lane has 16 / heads additions per tile (at least two), of which those of 32
+// keys of one block wait for each other; with 16 columns it was 16 keys.  16 columns / one by one / grouped, us of the compression branch: 95k
+// tokens in 16^3 selection blocks, ungrouped heads of 32 785 / 1672 / 728, 4 heads of 32 1478 / 1878 / 1252, of 64 1892 / 2369 / 1745;
+// sequences of 1024-token blocks, 64 pooled keys each, 4 heads of 64 716 / 1054 / 526; blocks of four or five pooled keys, where groups
+// are rarely of one block, 62k tokens, 4 heads of 64 977 / 995 / 1040.  With 8 and 16 heads one by one is ahead of 16 columns everywhere.
+constexpr int GROUP_HEADS = 4;
+
 // Selection scores (eq. (6), the normaliser known) of one 32-key tile: kb its first key, key and blk this lane's key and its selection
 // block.  Scores NOT transposed (query rows x keys), the heads of a token added in the lane (token_sums), and one integer LDS atomic
 // adds the sum onto the score row of the token.  l16: -lse per row (log2 units); row0: first score row of the wavefront's 32 rows.
@@ -182,6 +212,17 @@ __device__ inline void score_tile(const bf16x8 (&qop)[D / 16], Operand operand, 
   float v[NV];
   token_sums<HS>(c, v);
   const bool whole = r.one && kb + 32 <= r.re;
+  if constexpr (HS <= GROUP_HEADS) {
+    const KeyGroups grp(blk);
+    if (whole && grp.often) {
+#pragma unroll
+      for (int u = 0; u < NV; ++u) {
+        const uint32_t x = grp.sum((uint32_t)(v[u] * SCORE_FIX));
+        if (grp.adds) atomicAdd(&r.S[(row0 + token_of_sum<HS>(u)) * r.s_max + (blk - r.s0)], x);
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
     const int tok = row0 + token_of_sum<HS>(u);

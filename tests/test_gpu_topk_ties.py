@@ -46,6 +46,13 @@ def closed_form_sets(wl):
     (89, 128, (5400, 3), 16, 1, 64, (2, 4, 4), 8, 4097, 8000),          # more: rounds over LDS
     (90, 128, (5400, 20), 16, 1, 32, (2, 4, 4), 33, 4097, 8000),
     (91, 32, (700, 5), 4, 4, 64, (4, 8, 8), 8, 1, 64),                  # ungrouped heads: 32 tokens' rows per workgroup
+    # more than eight pooled keys per block and up to 4 heads per KV head: neighbouring keys' scores are added before they go to the row
+    (92, 64, (12000, 3), 4, 4, 64, (2, 8, 8), 8, 257, 512),
+    (93, 64, (11000, 5), 2, 2, 128, (1, 8, 8), 8, 257, 512),
+    (94, 64, (12000, 3), 4, 2, 32, (2, 8, 8), 8, 257, 512),
+    (95, 64, (12000, 3), 8, 2, 64, (2, 8, 8), 8, 257, 512),
+    (96, 128, (20000,), 4, 1, 128, (4, 16, 8), 8, 257, 512),
+    (97, 48, (5000, 3), 8, 2, 64, (2, 8, 8), 8, 65, 256),               # the one kernel of both walks
 ])
 def test_zero_queries_select_by_child_count_on_the_matrix_core_path(seed, grid, n, hq, hkv, d, m, topk, lo, hi):
     wl = inputs.random_points_workload(seed, grid, n, hq, hkv, d, m, topk, "bf16")

@@ -53,7 +53,7 @@ def test_compression_kernels_keep_their_wavefronts(tmp_path):
     scores = {k: v for k, v in all_.items() if "m_cmp_scoresILi" in k}
     assert len(scores) == 3 * (5 * 2 + 4)  # 1 to 16 heads per KV head by four and eight wavefronts, 2 to 16 with tiles in LDS
     for name, r in scores.items():
-        assert r["Occupancy"] >= (3 if "ILi128E" in name else 4) and r["VGPRs Spill"] == 0, (name, r)
+        assert r["Occupancy"] >= (2 if "ILi128ELi1E" in name else 3 if "ILi128E" in name else 4) and r["VGPRs Spill"] == 0, (name, r)
 
 
 def test_selection_and_dq_kernels_keep_their_wavefronts(tmp_path):
