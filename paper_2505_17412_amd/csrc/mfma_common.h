@@ -60,7 +60,7 @@ __device__ inline int acc_dim(int dt, int quad) { return tr_dim(dt, 4 * quad); }
 struct MfmaView {
   const int32_t *perm, *tok_item, *tok_win, *cmp_start, *slc_start, *win_start, *cmp_slc, *cmp_batch, *slc_batch,
       *item_start;
-  int N, Nc, Ns, Hq, Hkv, hs, T, s_max;
+  int N, Nc, Ns, Nw, Hq, Hkv, hs, T, s_max;
   float scale, sl2;  // softmax scale, scale * log2(e)
   // sorted copies (bf16), row-major [rows][Hkv][D]: token K, V and pooled K, V
   const bf16_t *Ks, *Vs, *Kc, *Vc;

@@ -331,7 +331,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
 // score.  With 128 rows there are twice as many such workgroups: 2-norm error of the output against 64 bits, 21k tokens in three 64^3 shells,
 // 2.7355e-3 for 2.7332e-3 (16 columns: 2.7335e-3), and the kernel takes 101 us at 62k tokens, but 17 at 3k.
 // CMP: the compression branch alone, over the pooled keys of the query's item, where m_cmp_scores forms the selection scores.
-constexpr int WIN_WAVES = 2;
 template <int D, int NW, bool CMP>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_walk_fwd(FwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -457,6 +456,12 @@ void launch_walk(const FwdArgs &a, hipStream_t s) {
   m_walk_fwd<D, NW, CMP><<<dim3(xcd_grid_size((a.v.N + tw - 1) / tw, a.v.Hkv)), 64 * NW, 4 * T32<D, true>::BYTES + 16 + 32 * NW * 4, s>>>(a);
 }
 
+// Whether the window branch takes 128 query rows per workgroup instead of 64: windows of 500 tokens on average.  There the error is the
+// same with both (1000 tokens, ungrouped heads, one workgroup of 128 rows in eight over two windows: output 2.32692e-3 for 2.32694e-3,
+// lse 1.2220e-5 for 1.2225e-5; 512: 1.81689e-5 both), and the larger ones stage half as often.  64 / 128 rows, us: 65k tokens in windows of 512
+// 229 / 202 (16 columns: 272), 4096 1617 / 1405 (1767), 40k in one 9488 / 8220 (10480); ungrouped 8k in one 160 / 133 (137); 3k in 512 18.9 / 19.1.
+inline bool windows_long(const MfmaView &v) { return v.N >= 500LL * v.Nw; }
+
 template <int D, int HS>
 void launch_cmp(const FwdArgs &a, hipStream_t s) {
   constexpr int NW = 4;
@@ -501,7 +506,8 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, co
   }
   {
     ProfScope ps(PROF_WIN_FWD, s);
-    launch_walk<D, WIN_WAVES, false>(a, s);
+    if (windows_long(a.v)) launch_walk<D, 4, false>(a, s);
+    else launch_walk<D, 2, false>(a, s);
   }
   {
     ProfScope ps(PROF_COMBINE, s);

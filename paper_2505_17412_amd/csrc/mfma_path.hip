@@ -134,7 +134,7 @@ MfmaView make_view(const ssa_ctx &c) {
   v.cmp_start = b->cmp_start; v.slc_start = b->slc_start; v.win_start = b->win_start;
   v.cmp_slc = b->cmp_slc; v.cmp_batch = b->cmp_batch;
   v.slc_batch = b->slc_batch; v.item_start = b->item_start;
-  v.N = c.N; v.Nc = b->Nc; v.Ns = b->Ns; v.Hq = c.Hq; v.Hkv = c.Hkv; v.hs = c.hs; v.T = c.T; v.s_max = b->s_max;
+  v.N = c.N; v.Nc = b->Nc; v.Ns = b->Ns; v.Nw = b->Nw; v.Hq = c.Hq; v.Hkv = c.Hkv; v.hs = c.hs; v.T = c.T; v.s_max = b->s_max;
   v.scale = c.scale; v.sl2 = c.scale * LOG2E;
   return v;
 }

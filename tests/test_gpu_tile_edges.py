@@ -21,6 +21,9 @@ pytestmark = pytest.mark.gpu
     (907, (530,), 2, 1, 128, (16, 256, 256), 3),         # a whole segment, then blocks of 256 and 18
     (908, (771,), 8, 2, 64, (1, 257, 300), 3),           # one key in a second segment
     (909, (300, 129), 1, 1, 32, (2, 130, 96), 2),        # one head
+    # windows of 500 tokens and more on average: 128 query rows per workgroup, some of several windows
+    (930, (1001, 513, 1600), 4, 4, 64, (8, 64, 700), 2), (931, (1025, 530), 16, 1, 32, (16, 64, 1024), 3),
+    (932, (999,), 8, 1, 128, (16, 64, 499), 3), (933, (2001,), 8, 1, 64, (16, 64, 500), 3),  # 499 and 500 a window and one shorter
 ])
 def test_tile_edges(seed, lens, hq, hkv, d, l, topk):
     full_parity(inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk))
