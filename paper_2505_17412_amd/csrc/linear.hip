@@ -41,7 +41,9 @@ struct LinDst {
 // the feature tiles of the three lie one after the other.  With grouped queries the key and the value projection have one or
 // two feature tiles, and by themselves leave most compute units idle: 5.5 k tokens of 1024 features, 1024 + 128 + 128 outputs
 // and the output projection, 82 us in four launches, 55 in two.
-template <int WF, int WT, int CF, int CT>
+// ONE: one pair and one output, known to the compiler.  Which pair a chunk and which output a tile belongs to, and fields fetched by that,
+// cost every call of ssa_linear_forward: 62k tokens 2048 -> 128 57.2 us for 47.3, 150k 384 -> 1024 214 for 190, 2k 384 -> 2048 11.9 for 10.9.
+template <int WF, int WT, int CF, int CT, bool ONE>
 __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, int M) {
   using G = TileGeom<LIN_KC>;
   constexpr int BF = 16 * CF * WF, BT = 16 * CT * WT, NTHR = 64 * WF * WT;
@@ -49,15 +51,15 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
   constexpr int IW = BF * 8 / NTHR, IX = BT * 8 / NTHR;         // 16-byte items per thread and chunk
   extern __shared__ __align__(16) unsigned char smem[];
   bf16_t *sw = (bf16_t *)smem, *sx = sw + 2 * STAGE_W;
-  const int n_ot = (dst.O[0] + dst.O[1] + dst.O[2]) / BF, n_tt = (M + BT - 1) / BT;  // unused outputs have O = 0
+  const int n_ot = (ONE ? dst.O[0] : dst.O[0] + dst.O[1] + dst.O[2]) / BF, n_tt = (M + BT - 1) / BT;  // unused outputs have O = 0
   const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
   const int tt = (idx / n_ot) * 8 + xcd;
   if (tt >= n_tt) return;
   const int f0 = idx % n_ot * BF;  // first feature of the tile, counted over all outputs
-  const int d = f0 < dst.O[0] ? 0 : (f0 < dst.O[0] + dst.O[1] ? 1 : 2);
-  const int m0 = tt * BT, o0 = f0 - (d > 0 ? dst.O[0] : 0) - (d > 1 ? dst.O[1] : 0), O = dst.O[d];
-  const bf16_t *__restrict__ bias = dst.bias[d];
-  bf16_t *__restrict__ Y = dst.Y[d];
+  const int d = ONE || f0 < dst.O[0] ? 0 : (f0 < dst.O[0] + dst.O[1] ? 1 : 2);
+  const int m0 = tt * BT, o0 = f0 - (d > 0 ? dst.O[0] : 0) - (d > 1 ? dst.O[1] : 0), O = d == 0 ? dst.O[0] : d == 1 ? dst.O[1] : dst.O[2];
+  const bf16_t *__restrict__ bias = d == 0 ? dst.bias[0] : d == 1 ? dst.bias[1] : dst.bias[2];
+  bf16_t *__restrict__ Y = d == 0 ? dst.Y[0] : d == 1 ? dst.Y[1] : dst.Y[2];
   const int tid = threadIdx.x, wid = tid >> 6, lane = tid & 63, n = lane & 15, quad = lane >> 4;
   const int wc = wid % WF, wt = wid / WF;  // the wavefront's features and tokens inside the tile
   f32x4 acc[CF][CT];
@@ -66,19 +68,18 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
 #pragma unroll
     for (int ti = 0; ti < CT; ++ti) acc[ci][ti] = f32x4{0.f, 0.f, 0.f, 0.f};
   // Two chunks are in flight in registers (A: the next chunk, B: the one after), so a global load has two loop trips
-  // to arrive; the loop is unrolled by two to alternate the register sets.  Every load is unconditional, with clamped indices
-  // (tokens past the end are not stored, chunks past the end not used): behind a branch the compiler cannot count what is
+  // to arrive; the loop is unrolled by two to alternate the register sets.  Every load of the loop is unconditional, with clamped rows
+  // (tokens past the end are not stored) and the last two chunks behind the loop: behind a branch the compiler cannot count what is
   // outstanding and waits for the chunk just requested as well.  The launches of a
   // layer's step (1024 features): 10.7 k tokens 182 -> 174 us, 46 k 627 -> 600.  (256 tokens per workgroup of four or eight wavefronts: 46 k 667, 660.)
   bf16x8 rwA[IW], rxA[IX], rwB[IW], rxB[IX];
-  const int K = src.K[0] + src.K[1] + src.K[2];  // unused pairs have K = 0
+  const int K = ONE ? src.K[0] : src.K[0] + src.K[1] + src.K[2];  // unused pairs have K = 0
   int xrow[IX];
 #pragma unroll
   for (int i = 0; i < IX; ++i) xrow[i] = min((tid + NTHR * i) >> 3, M - 1 - m0);
-  auto fetch = [&](int kf_, bf16x8 (&rw)[IW], bf16x8 (&rx)[IX]) {
-    const int kf = min(kf_, K - LIN_KC);
+  auto fetch = [&](int kf, bf16x8 (&rw)[IW], bf16x8 (&rx)[IX]) {
     // which pair the flat contraction index kf falls into (every K_i is a multiple of 128, so a chunk never straddles)
-    const int p = kf < src.K[0] ? 0 : (kf < src.K[0] + src.K[1] ? 1 : 2);
+    const int p = ONE || kf < src.K[0] ? 0 : (kf < src.K[0] + src.K[1] ? 1 : 2);
     const int k0 = kf - (p > 0 ? src.K[0] : 0) - (p > 1 ? src.K[1] : 0), Kp = p == 0 ? src.K[0] : p == 1 ? src.K[1] : src.K[2];
     const int q = p + d;  // (several pairs: d = 0; several outputs: p = 0)
     const bf16_t *X = (p == 0 ? src.X[0] : p == 1 ? src.X[1] : src.X[2]) + (size_t)m0 * Kp + k0;
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
   fetch(LIN_KC, rwB, rxB);
   stash(0, rwA, rxA);
   __syncthreads();
-  for (int k0 = 0; k0 < K; k0 += 2 * LIN_KC) {
+  for (int k0 = 0; k0 < K - 2 * LIN_KC; k0 += 2 * LIN_KC) {
     // stage 0 holds chunk k0, registers B chunk k0 + 64
     fetch(k0 + 2 * LIN_KC, rwA, rxA);
     compute(0);
@@ -131,9 +132,13 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
     __syncthreads();
     fetch(k0 + 3 * LIN_KC, rwB, rxB);
     compute(1);
-    if (k0 + 2 * LIN_KC < K) stash(0, rwA, rxA);
+    stash(0, rwA, rxA);
     __syncthreads();
   }
+  compute(0);
+  stash(1, rwB, rxB);
+  __syncthreads();
+  compute(1);
   // MFMA row r of sub-tile a of a 32-row tile is row 8*(r >> 2) + 4*a + (r & 3): with r = 4*quad + i the two sub-tiles
   // of a feature tile give the lane features 8*quad .. 8*quad+7; column n of token sub-tile b is token row
   // 8*(n >> 2) + 4*b + (n & 3).
@@ -159,18 +164,23 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
 }
 
 // Wt[k][o] = W[o][k]: 32 x 32 tiles through LDS, both sides coalesced; blockIdx.z picks one of up to three weights.
+// (The short kernels of this file have a form of their own for one projection: a workgroup that first has to fetch which weight is
+// its own starts later, 2048 x 2048: 8.0 us for 6.2 here, 24.5 for 15.9 in lin_sum_parts.)
+template <int NP>
 struct LinTrans {
-  const bf16_t *W[3];
-  bf16_t *Wt[3];
-  int O[3];
+  const bf16_t *W[NP];
+  bf16_t *Wt[NP];
+  int O[NP];
 };
-__global__ __launch_bounds__(256) void lin_transpose(LinTrans a, int K) {
+template <int NP>
+__global__ __launch_bounds__(256) void lin_transpose(LinTrans<NP> a, int K) {
   __shared__ bf16_t t[32][33];
-  const bf16_t *__restrict__ W = a.W[blockIdx.z];
-  bf16_t *__restrict__ Wt = a.Wt[blockIdx.z];
-  const int O = a.O[blockIdx.z];
+  const int d = NP == 1 ? 0 : blockIdx.z;
+  const bf16_t *__restrict__ W = a.W[d];
+  bf16_t *__restrict__ Wt = a.Wt[d];
+  const int O = a.O[d];
   const int k0 = blockIdx.x * 32, o0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  if (o0 >= O) return;
+  if (NP > 1 && o0 >= O) return;
 #pragma unroll
   for (int r = ty; r < 32; r += 8) t[r][tx] = W[(size_t)(o0 + r) * K + k0 + tx];
   __syncthreads();
@@ -179,20 +189,22 @@ __global__ __launch_bounds__(256) void lin_transpose(LinTrans a, int K) {
 }
 
 // Parameter gradients of up to three projections of one input: everything but the input is per projection.
+template <int NP>
 struct LinGrad {
-  const bf16_t *dY[3];
-  float *part[3], *bpart[3], *dw[3], *dbias[3];
-  int O[3], splits[3], tok_per_split[3];
+  const bf16_t *dY[NP];
+  float *part[NP], *bpart[NP], *dw[NP], *dbias[NP];
+  int O[NP], splits[NP], tok_per_split[NP];
 };
 
 // part[split][o][k] = sum over the split's tokens of dY[t][o] X[t][k]: workgroup = 128 x 128 output tile, one split.
 // The workgroups of the projections lie one after the other, all tiles of a split together.
-__global__ __launch_bounds__(256) void lin_tn(LinGrad a, const bf16_t *__restrict__ X, int M, int K) {
+template <int NP>
+__global__ __launch_bounds__(256) void lin_tn(LinGrad<NP> a, const bf16_t *__restrict__ X, int M, int K) {
   using G = TileGeom<128>;
   __shared__ __align__(16) bf16_t sy[2][G::ROW_ELEMS], sx[2][G::ROW_ELEMS];
   const int n_kt = K / 128;
   int wg = blockIdx.x, d = 0;
-  while (d < 2 && wg >= a.O[d] / 128 * n_kt * a.splits[d]) wg -= a.O[d] / 128 * n_kt * a.splits[d], ++d;
+  while (d < NP - 1 && wg >= a.O[d] / 128 * n_kt * a.splits[d]) wg -= a.O[d] / 128 * n_kt * a.splits[d], ++d;
   const bf16_t *__restrict__ dY = a.dY[d];
   const int O = a.O[d], tok_per_split = a.tok_per_split[d], tiles = O / 128 * n_kt;
   const int split = wg / tiles, ot = wg % tiles / n_kt, kt = wg % n_kt;
@@ -253,11 +265,11 @@ __global__ __launch_bounds__(256) void lin_tn(LinGrad a, const bf16_t *__restric
 }
 
 // dw[j] = sum_s part[s][j], s ascending; blockIdx.y picks the projection.  A chain of loads that wait for each other without
-// the unrolling: the
-// four weight gradients of a layer at 10.7 k tokens 48 us in four launches of one load at a time, 32 in two (query, key and
+// the unrolling: the four weight gradients of a layer at 10.7 k tokens 48 us in four launches of one load at a time, 32 in two (query, key and
 // value together) of eight.
-__global__ void lin_sum_parts(LinGrad a, int K) {
-  const int d = blockIdx.y, n_parts = a.splits[d];
+template <int NP>
+__global__ void lin_sum_parts(LinGrad<NP> a, int K) {
+  const int d = NP == 1 ? 0 : blockIdx.y, n_parts = a.splits[d];
   const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x, len = (size_t)a.O[d] * K;
   if (j >= len) return;
   const float *__restrict__ part = a.part[d] + j;
@@ -278,12 +290,14 @@ __global__ void lin_zero(float *__restrict__ out, size_t len) {
 // `phases`-th token, the phases are added in order through LDS.  O % 8 == 0, O / 8 <= 256 or a multiple of 256.
 // blockIdx.y picks the projection, of those with a bias.
 constexpr int COLSUM_CHUNK = 64;
-__global__ __launch_bounds__(256) void lin_colsum(LinGrad a, int M) {
+template <int NP>
+__global__ __launch_bounds__(256) void lin_colsum(LinGrad<NP> a, int M) {
   __shared__ float red[2048];
-  if (!a.dbias[blockIdx.y]) return;
-  const bf16_t *__restrict__ dY = a.dY[blockIdx.y];
-  float *__restrict__ part = a.bpart[blockIdx.y];
-  const int O = a.O[blockIdx.y];
+  const int d = NP == 1 ? 0 : blockIdx.y;
+  if (NP > 1 && !a.dbias[d]) return;
+  const bf16_t *__restrict__ dY = a.dY[d];
+  float *__restrict__ part = a.bpart[d];
+  const int O = a.O[d];
   const int cols8 = O / 8;
   const int phases = cols8 >= 256 ? 1 : 256 / cols8;
   const int t_begin = blockIdx.x * COLSUM_CHUNK, t_end = min(M, t_begin + COLSUM_CHUNK);
@@ -315,11 +329,13 @@ __global__ __launch_bounds__(256) void lin_colsum(LinGrad a, int M) {
 }
 // Step 2: out[o] = sum over the parts; a workgroup owns 8 columns, 32 thread rows each add every 32nd part, then the
 // rows are added in order.
-__global__ __launch_bounds__(256) void lin_colsum_finish(LinGrad a, int n_parts) {
+template <int NP>
+__global__ __launch_bounds__(256) void lin_colsum_finish(LinGrad<NP> a, int n_parts) {
   __shared__ float red[32][8];
-  if (!a.dbias[blockIdx.y]) return;
-  const float *__restrict__ part = a.bpart[blockIdx.y];
-  const int O = a.O[blockIdx.y];
+  const int d = NP == 1 ? 0 : blockIdx.y;
+  if (NP > 1 && !a.dbias[d]) return;
+  const float *__restrict__ part = a.bpart[d];
+  const int O = a.O[d];
   const int col = blockIdx.x * 8 + (threadIdx.x & 7), row = threadIdx.x >> 3;
   float s = 0.f;
   if (col < O)
@@ -330,7 +346,7 @@ __global__ __launch_bounds__(256) void lin_colsum_finish(LinGrad a, int n_parts)
     float t = 0.f;
 #pragma unroll
     for (int r = 0; r < 32; ++r) t += red[r][threadIdx.x & 7];
-    a.dbias[blockIdx.y][col] = t;
+    a.dbias[d][col] = t;
   }
 }
 
@@ -364,16 +380,21 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
 
 namespace {
 
+template <bool ONE>
 int launch_nt(const LinSrc &src, const LinDst &dst, int M, hipStream_t s) {
   constexpr int WF = 2, WT = 2, CF = 4, CT = 4, BF = 16 * CF * WF, BT = 16 * CT * WT;
   const size_t lds = (size_t)2 * (BF + BT) * LIN_KC * sizeof(bf16_t);  // two stages of weights and tokens
   static const hipError_t attr =
-      hipFuncSetAttribute((const void *)lin_nt<WF, WT, CF, CT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      hipFuncSetAttribute((const void *)lin_nt<WF, WT, CF, CT, ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (attr != hipSuccess) return SSA_ERR_HIP;
   const int n_ot = (dst.O[0] + dst.O[1] + dst.O[2]) / BF, n_tt = (M + BT - 1) / BT;
   const unsigned grid = (unsigned)(8 * ((n_tt + 7) / 8) * n_ot);
-  lin_nt<WF, WT, CF, CT><<<grid, 64 * WF * WT, lds, s>>>(src, dst, M);
+  lin_nt<WF, WT, CF, CT, ONE><<<grid, 64 * WF * WT, lds, s>>>(src, dst, M);
   return SSA_OK;
+}
+int launch_nt(const LinSrc &src, const LinDst &dst, int M, hipStream_t s) {
+  const bool one = src.K[1] == 0 && dst.O[1] == 0;
+  return one ? launch_nt<true>(src, dst, M, s) : launch_nt<false>(src, dst, M, s);
 }
 
 }  // namespace
@@ -419,16 +440,21 @@ int lin_forward_multi(int n_dst, int M, int K, const void *X, const void *const 
   return SSA_OK;
 }
 
-void lin_transpose_w(int n, const void *const *w, const int *d_out, int d_in, void *const *wt, hipStream_t s) {
-  LinTrans a{};
+template <int NP>
+static void transpose_w(const void *const *w, const int *d_out, int d_in, void *const *wt, hipStream_t s) {
+  LinTrans<NP> a{};
   int o_max = 0;
-  for (int i = 0; i < n; ++i) {
+  for (int i = 0; i < NP; ++i) {
     a.W[i] = (const bf16_t *)w[i];
     a.Wt[i] = (bf16_t *)wt[i];
     a.O[i] = d_out[i];
     o_max = d_out[i] > o_max ? d_out[i] : o_max;
   }
-  lin_transpose<<<dim3(d_in / 32, o_max / 32, n), 256, 0, s>>>(a, d_in);
+  lin_transpose<NP><<<dim3(d_in / 32, o_max / 32, NP), 256, 0, s>>>(a, d_in);
+}
+void lin_transpose_w(int n, const void *const *w, const int *d_out, int d_in, void *const *wt, hipStream_t s) {
+  if (n == 1) transpose_w<1>(w, d_out, d_in, wt, s);
+  else transpose_w<3>(w, d_out, d_in, wt, s);
 }
 
 size_t lin_dw_workspace(int M, int d_in, int d_out) {
@@ -436,13 +462,14 @@ size_t lin_dw_workspace(int M, int d_in, int d_out) {
   return align_up(p.total - p.part, 256);
 }
 
-void lin_dw(int n, int M, int d_in, const int *d_out, const void *x, const void *const *dy, float *const *dw,
-            float *const *dbias, void *ws, hipStream_t s) {
-  LinGrad a{};
+template <int NP>
+static void weight_grads(int M, int d_in, const int *d_out, const void *x, const void *const *dy, float *const *dw, float *const *dbias,
+                         void *ws, hipStream_t s) {
+  LinGrad<NP> a{};
   char *at = (char *)ws;
   unsigned grid = 0, bias_parts = 1;
   int o_max = 0, any_bias = 0;
-  for (int i = 0; i < n; ++i) {
+  for (int i = 0; i < NP; ++i) {
     const LinPlan pl = lin_plan(M, d_in, d_out[i]);
     a.dY[i] = (const bf16_t *)dy[i];
     a.part[i] = (float *)at;
@@ -458,12 +485,17 @@ void lin_dw(int n, int M, int d_in, const int *d_out, const void *x, const void 
     o_max = d_out[i] > o_max ? d_out[i] : o_max;
     any_bias |= dbias[i] != nullptr;
   }
-  lin_tn<<<grid, 256, 0, s>>>(a, (const bf16_t *)x, M, d_in);
-  lin_sum_parts<<<dim3((unsigned)((size_t)o_max * d_in / 256), n), 256, 0, s>>>(a, d_in);
+  lin_tn<NP><<<grid, 256, 0, s>>>(a, (const bf16_t *)x, M, d_in);
+  lin_sum_parts<NP><<<dim3((unsigned)((size_t)o_max * d_in / 256), NP), 256, 0, s>>>(a, d_in);
   if (any_bias) {
-    lin_colsum<<<dim3(bias_parts, n), 256, 0, s>>>(a, M);
-    lin_colsum_finish<<<dim3((o_max + 7) / 8, n), 256, 0, s>>>(a, (int)bias_parts);
+    lin_colsum<NP><<<dim3(bias_parts, NP), 256, 0, s>>>(a, M);
+    lin_colsum_finish<NP><<<dim3((o_max + 7) / 8, NP), 256, 0, s>>>(a, (int)bias_parts);
   }
+}
+void lin_dw(int n, int M, int d_in, const int *d_out, const void *x, const void *const *dy, float *const *dw,
+            float *const *dbias, void *ws, hipStream_t s) {
+  if (n == 1) weight_grads<1>(M, d_in, d_out, x, dy, dw, dbias, ws, s);
+  else weight_grads<3>(M, d_in, d_out, x, dy, dw, dbias, ws, s);
 }
 
 int lin_check(int n_tokens, int d_in, int d_out) {

@@ -15,10 +15,10 @@ int lin_nt_multi(int n_src, const void *const *X, const void *const *W, const in
 int lin_forward_multi(int n_dst, int M, int K, const void *X, const void *const *W, const void *const *bias, const int *O,
                       void *const *Y, hipStream_t s);
 
-// wt_i [d_in][d_out_i] = w_i [d_out_i][d_in]^T, i < n <= 3
+// wt_i [d_in][d_out_i] = w_i [d_out_i][d_in]^T, i < n, 1 or 3
 void lin_transpose_w(int n, const void *const *w, const int *d_out, int d_in, void *const *wt, hipStream_t s);
 
-// dw_i [d_out_i][d_in] (fp32) = dy_i^T x, dbias_i [d_out_i] (fp32, may be null) = column sums of dy_i, i < n <= 3; ws: the
+// dw_i [d_out_i][d_in] (fp32) = dy_i^T x, dbias_i [d_out_i] (fp32, may be null) = column sums of dy_i, i < n, 1 or 3; ws: the
 // sum of lin_dw_workspace() over them, 256-byte aligned
 size_t lin_dw_workspace(int M, int d_in, int d_out);
 void lin_dw(int n, int M, int d_in, const int *d_out, const void *x, const void *const *dy, float *const *dw,
