@@ -34,17 +34,17 @@ __global__ void g_prep_w(const bf16_t *__restrict__ w, int Dm, int J, int JR, bf
   }
 }
 
-// gates[tok][j] = sigmoid(sum_k x[tok][k] w[k][j] + b[j]); NB = blocks of 16 gate columns.  A workgroup owns two tiles of 16
-// tokens (every weight operand feeds two matrix instructions) and its four wavefronts a quarter of the contraction each, added in
-// order through LDS.  Bound: the latency of the row loads, 1 KB each, eight of them and the weights in flight per wavefront; a
-// wavefront with 32 tokens and the whole contraction left most of the chip empty: 5.5 k
-// tokens of 1024 features 24 -> 9.4 us, 46 k 40 -> 32.
-template <int NB>
+// gates[tok][j] = sigmoid(sum_k x[tok][k] w[k][j] + b[j]); NB = blocks of 16 gate columns.  A wavefront owns two tiles of 16
+// tokens (every weight operand feeds two matrix instructions).  SPLIT: the four wavefronts of a workgroup take a quarter of the
+// contraction of the same 32 tokens each, added in order through LDS; else each has its own 32 tokens and the whole contraction.
+// Bound: the latency of the row loads, 1 KB each, eight of them and the weights in flight per wavefront (gate_split says where which).
+template <int NB, bool SPLIT>
 __global__ __launch_bounds__(256) void g_fwd(const bf16_t *__restrict__ x, const bf16_t *__restrict__ wt,
                                              const bf16_t *__restrict__ bias, int N, int Dm, int J, bf16_t *__restrict__ gates) {
-  __shared__ f32x4 part[4][2 * NB][64];
+  __shared__ f32x4 part[SPLIT ? 4 : 1][SPLIT ? 2 * NB : 1][64];
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
-  const int t0 = blockIdx.x * 32;
+  const int t0 = (SPLIT ? blockIdx.x : blockIdx.x * 4 + wid) * 32;
+  if (!SPLIT && t0 >= N) return;
   const bf16_t *xr[2];
 #pragma unroll
   for (int a = 0; a < 2; ++a) xr[a] = x + (size_t)min(t0 + 16 * a + n, N - 1) * Dm + 8 * quad;  // rows past the end
@@ -54,7 +54,8 @@ __global__ __launch_bounds__(256) void g_fwd(const bf16_t *__restrict__ x, const
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[a][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int trips = Dm / 128;  // d_model is a multiple of 128: four contraction steps per trip
-  for (int k4 = trips * wid / 4; k4 < trips * (wid + 1) / 4; ++k4) {
+  const int k_begin = SPLIT ? trips * wid / 4 : 0, k_end = SPLIT ? trips * (wid + 1) / 4 : trips;
+  for (int k4 = k_begin; k4 < k_end; ++k4) {
     bf16x8 av[2][4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -70,23 +71,32 @@ __global__ __launch_bounds__(256) void g_fwd(const bf16_t *__restrict__ x, const
         acc[1][nb] = mfma16(av[1][u], bv, acc[1][nb]);
       }
   }
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) part[wid][a * NB + nb][lane] = acc[a][nb];
-  __syncthreads();
-  // C layout: lane holds gate column 16*nb + n of tokens t0 + 16*a + 4*quad + i; the wavefronts take the tiles in turn
-  for (int it = wid; it < 2 * NB; it += 4) {
-    const int a = it / NB, j = 16 * (it % NB) + n;
-    if (j >= J) continue;
-    const f32x4 p0 = part[0][it][lane], p1 = part[1][it][lane], p2 = part[2][it][lane], p3 = part[3][it][lane];
+  // C layout: lane holds gate column 16*nb + n of tokens t0 + 16*a + 4*quad + i
+  auto store = [&](int a, int nb, const f32x4 &z) {
+    const int j = 16 * nb + n;
+    if (j >= J) return;
     const float b = bf16_to_f32(bias[j]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int t = t0 + 16 * a + 4 * quad + i;
-      const float z = ((p0[i] + p1[i]) + p2[i]) + p3[i];
-      if (t < N) gates[(size_t)t * J + j] = f32_to_bf16(1.0f / (1.0f + __expf(-(z + b))));
+      if (t < N) gates[(size_t)t * J + j] = f32_to_bf16(1.0f / (1.0f + __expf(-(z[i] + b))));
     }
+  };
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) part[wid][a * NB + nb][lane] = acc[a][nb];
+    __syncthreads();
+    for (int it = wid; it < 2 * NB; it += 4) {  // the wavefronts take the tiles in turn
+      const f32x4 p0 = part[0][it][lane], p1 = part[1][it][lane], p2 = part[2][it][lane], p3 = part[3][it][lane];
+      store(it / NB, it % NB, ((p0 + p1) + p2) + p3);
+    }
+  } else {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) store(a, nb, acc[a][nb]);
   }
 }
 
@@ -281,18 +291,33 @@ extern "C" size_t ssa_gate_workspace_bytes(const ssa_params_t *p, int32_t d_mode
   return gate_plan(p->n_tokens, d_model, J, for_backward != 0).total + 256;
 }
 
+// Whether the four wavefronts of a workgroup split the contraction (g_fwd): where a wavefront per 32 tokens leaves the chip half empty, at
+// 49152 tokens and below.  Beyond, such wavefronts run in rounds of one per SIMD (32768 tokens), and a split, whose time grows with the
+// tokens alone, wins where the last round is not nearly full.  With up to 32 gate columns a split is never behind but for a d_model of
+// 128, a single trip, in the smallest.  Whole / split, us, 1024 features, 48 columns: 20k tokens 27 / 20, 49k 43 / 34, 62k (95 % of two
+// rounds) 44 / 47, 80k (81 % of three) 60 / 55, 100k (76 %) 78 / 66, 150k (92 %) 99 / 109, 250k (95 %) 155 / 181; 24 columns: 62k 37 / 34, 150k 85
+// / 82; 128 features, 12 columns: 62k 9.5 / 9.9, 150k 12.6 / 13.3.
+static bool gate_split(int N, int d_model, int NB) {
+  const long long round = 32768, full = (N + round - 1) / round * round;
+  if (NB == 1 && d_model == 128) return false;
+  return NB <= 2 || N <= 49152 || 100ll * N < 89 * full;
+}
+
 // Forward launches with the transposed weight copy in `wt` (device, ((J+15)/16*16) * d_model bf16).
 static int gate_forward_launch(int N, int d_model, int J, const void *x, const void *w, const void *bias, void *gates,
                                bf16_t *wt, hipStream_t s) {
   const int NB = (J + 15) / 16, JR = 16 * NB;
   ProfScope ps(PROF_GATE_FWD, s);
   g_prep_w<<<(unsigned)(((size_t)JR * d_model + 255) / 256), 256, 0, s>>>((const bf16_t *)w, d_model, J, JR, wt, nullptr);
-  const unsigned grid = (unsigned)((N + 31) / 32);
+  const auto run = [&](auto kernel, int tokens) {
+    kernel<<<(unsigned)((N + tokens - 1) / tokens), 256, 0, s>>>((const bf16_t *)x, wt, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates);
+  };
+  const bool split = gate_split(N, d_model, NB);
   switch (NB) {
-    case 1: g_fwd<1><<<grid, 256, 0, s>>>((const bf16_t *)x, wt, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates); break;
-    case 2: g_fwd<2><<<grid, 256, 0, s>>>((const bf16_t *)x, wt, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates); break;
-    case 3: g_fwd<3><<<grid, 256, 0, s>>>((const bf16_t *)x, wt, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates); break;
-    default: g_fwd<4><<<grid, 256, 0, s>>>((const bf16_t *)x, wt, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates); break;
+    case 1: split ? run(g_fwd<1, true>, 32) : run(g_fwd<1, false>, 128); break;
+    case 2: split ? run(g_fwd<2, true>, 32) : run(g_fwd<2, false>, 128); break;
+    case 3: split ? run(g_fwd<3, true>, 32) : run(g_fwd<3, false>, 128); break;
+    default: split ? run(g_fwd<4, true>, 32) : run(g_fwd<4, false>, 128); break;
   }
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
