@@ -25,7 +25,7 @@ struct SelIndex {
   ChunkRef *order, *bc_order;     // the chunks of either chunking in execution order (see m_chunk_order)
   int32_t *base;                  // [2 * keys] with by_length: first place of every key's chunks in the two orders
   bool by_length;                 // the chunks run by falling block length (see sel_index_carve)
-  int chunk_len, bc_chunk_len;    // query tokens per chunk: at least 256 (dK/dV), BC_CHUNK_MIN .. BC_CHUNK
+  int chunk_len, bc_chunk_len;    // query tokens per chunk: at least DKV_CHUNK_MIN, BC_CHUNK_MIN .. BC_CHUNK
 };
 size_t sel_index_bytes(int N, int Hkv, int T, int Ns);
 SelIndex sel_index_carve(void *ws, int N, int Hkv, int T, int Ns, int chunk_len, int bc_chunk_len);
@@ -33,7 +33,7 @@ int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_
                     const SelIndex &x, bool caller_indices, bool want_bc_order, bool want_dkv_order, hipStream_t s);
 
 // Block-centric selection kernels: query tokens per work chunk, and the per-(token, KV head, rank) partial results.
-constexpr int BC_CHUNK = 256, BC_CHUNK_MIN = 32;
+constexpr int BC_CHUNK = 256, BC_CHUNK_MIN = 32, DKV_CHUNK_MIN = 128;
 int bc_chunk_len(int N, int Hkv, int T);
 struct SlcPartials {
   bf16_t *o;    // [N][Hkv][T][hs][D]: unnormalised partial output (forward) / partial dQ (backward) per selected block

@@ -4,18 +4,25 @@
 //
 // A workgroup owns the keys of one selection block (32 per wavefront, as matrix operands in registers with their dK and dV
 // accumulators; the keys of a longer block in segments) and streams the query rows of a chunk of the tokens that selected the
-// block, 64 rows per stage through LDS.
+// block through LDS, 64 rows per stage and group of wavefronts.
 // Scores and dP are formed once: the dS tiles stay in registers for dK and go to LDS, transposed for free by the layout, for
 // dQ of the same rows, which the wavefronts share out by output dims.  Two separate kernels form S and dP twice, 14 matrix
 // products per pair instead of 10, and fetch the query rows twice; but a segment costs a whole pass over the query rows whatever
 // its length, with the dQ rows of the segment before read back, so that long blocks are left to them where there are many.
 //
-// The pipes of a SIMD take turns: per 32 keys x 32 query rows (d = 64) 32 + 8 matrix instructions of 16.8 cycles (S, dP, dV, dK;
-// dQ), 16 exponentials and some 100 VALU instructions, 34 LDS operands of 9 to 16 cycles, about 1430 cycles one after the other;
-// 1450 are measured, with two wavefronts per SIMD (registers).  That describes the schedule and is no lower bound: all wavefronts
-// pass the same phase behind one barrier, wait 41 % of their life and keep the matrix pipes 26 % busy.  Besides, a block that
-// does not fill its workgroup's tiles leaves wavefronts idle.  Time of the two kernels -> one pass: 62 k tokens of a 128^3 shell
-// 3344 -> 3240 us, four such shapes (147 k) 8834 -> 7200, 65 k tokens in sequences with blocks of 64 2155 -> 1300, 21 k tokens in three 64^3 shells 642 -> 506.
+// One launch serves blocks of every length, so that the few workgroups that end last are those of the shortest blocks.  A block of up to
+// 128 keys has two groups of four wavefronts with the same keys, each with rows of its own; a longer one has all eight by their keys, so
+// that dQ of a row is complete after 256.  With a launch per length (four wavefronts for up to 128 keys, eight beyond) each ended in
+// workgroups that leave most compute units idle: 62k tokens, 0.27 ms for the 5 % of the pairs in short blocks.  Where no block is longer
+// than 128 keys, workgroups of four wavefronts remain, two per compute unit, which need not keep step.
+//
+// Bound: the pipes of a SIMD take turns; per 32 keys x 32 query rows (d = 64) 40 matrix instructions of 16 cycles, 16 exponentials and
+// some 100 VALU instructions, 32 LDS operands, with two wavefronts per SIMD (registers) that pass the same phase behind one barrier.
+// The dQ product, a fifth of the matrix work, was two fifths of the time while it read K^T with every step and waited for each step's
+// operands by themselves: K^T stays in registers now and the operands of two to four steps are requested together.  us of this kernel,
+// before -> now on one card: 65k tokens in sequences, top-8, blocks of 128 keys 1017 -> 975, 192 1768 -> 1613, 256 2044 -> 1810 (760
+// TFLOP/s); 62k tokens of a 128^3 shell, top-16, 3550 -> 3243; four such shapes (147k) 7337 -> 6890; sequences with blocks of 64 1476 ->
+// 1400; 11k tokens of a 64^3 shell 385 -> 300.
 #include "mfma_common.h"
 #include "mfma_launch.h"
 #include "mfma_qc.h"
@@ -33,29 +40,31 @@ struct SlcBwdArgs {
   const ChunkRef *chunk_order;
   bf16_t *pdq;                  // [N(pos)][Hkv][T][hs][D] partial dQ, and one spare row
   float *pK, *pV;               // [rows][D] partial dK, dV per chunk
-  int len_lo, len_hi;           // this launch serves the blocks of len_lo < keys <= len_hi
 };
 
-// Geometry of a workgroup of NW wavefronts.
-template <int D, int NW>
+// Geometry of a workgroup of NW wavefronts in RG groups.  Every group holds the same keys and takes its own rows of a stage; dK and dV
+// of the groups are added at the end.
+template <int D, int NW, int RG>
 struct SlcBwdShape {
-  static constexpr int KB = 2, ST = 2, ROWS = 32 * ST, KEYS = 16 * KB * NW, NTHR = 64 * NW;
+  static constexpr int GW = NW / RG;          // wavefronts per group
+  static constexpr int KB = 2, ST = 2, ROWS = 32 * ST, KEYS = 16 * KB * GW, NTHR = 64 * NW;
+  static constexpr int TILES = ST * RG, ALL_ROWS = ROWS * RG;  // of a stage
   static constexpr int NT = D / 16;           // output dim blocks of dQ
-  static constexpr int G = NW / NT;           // groups of wavefronts that share a stage's rows
+  static constexpr int G = GW / NT;           // wavefronts of a group that share its rows
   static constexpr int QB = ROWS / 16 / G;    // 16-row blocks per wavefront in the dQ product
   static constexpr int KS = KEYS / 32;        // contraction steps of the dQ product
-  // NW = 8: dS and dQ tiles are double-buffered and the dQ product of a stage runs beside the scores of the next one, one
-  // barrier per stage; NW = 4: single tiles, the product follows the scores of its own stage behind a second barrier, and
-  // two workgroups share a compute unit.
-  static constexpr bool DOUBLE = NW == 8;
+  // 256 keys: dS and dQ tiles are double-buffered and the dQ product of a stage runs beside the scores of the next one, one
+  // barrier per stage; 128 keys: single tiles, the product follows the scores of its own stage behind a second barrier.
+  static constexpr bool DOUBLE = GW == 8;
   static constexpr int BUFS = DOUBLE ? 2 : 1, LAG = DOUBLE ? 1 : 0;
-  // LDS (bytes): stages | dS tiles [BUFS][KEYS][ROWS] | dQ tiles [BUFS][ROWS][D] | partial rows [4][ROWS] | spare | K tiles
-  static constexpr int STAGE_B = 2 * ST * PTile<D>::BYTES + 2 * ROWS * 4;
-  static constexpr int DS_B = KEYS * ROWS * 2, DQ_B = ROWS * D * 2;
+  // LDS (bytes): stages | dS tiles [BUFS][RG][KEYS][ROWS] (before the first stage the segment's K rows) | dQ tiles [BUFS][ALL_ROWS][D] |
+  // partial rows [4][ALL_ROWS] | spare.  The groups' dK and dV meet where the stages were.
+  static constexpr int STAGE_B = 2 * TILES * PTile<D>::BYTES + 2 * ALL_ROWS * 4;
+  static constexpr int DS_GROUP_B = KEYS * ROWS * 2, DS_B = RG * DS_GROUP_B, DQ_B = ALL_ROWS * D * 2;
   static constexpr int DS_OFF = 2 * STAGE_B, DQ_OFF = DS_OFF + BUFS * DS_B, ROW_OFF = DQ_OFF + BUFS * DQ_B;
-  static constexpr int SPARE = ROW_OFF + 4 * ROWS * 4, KT_OFF = SPARE + 16;
-  static constexpr int LDS_B = KT_OFF + KS * PTile<D>::BYTES;
-  static_assert(NW % NT == 0 && QB >= 1, "the dQ product is shared out evenly");
+  static constexpr int SPARE = ROW_OFF + 4 * ALL_ROWS * 4, LDS_B = SPARE + 16, KT_OFF = DS_OFF;
+  static_assert(GW % NT == 0 && QB >= 1, "the dQ product is shared out evenly");
+  static_assert(KS * PTile<D>::BYTES <= BUFS * DS_B && (RG == 1 || 2 * KEYS * D * 4 <= 2 * STAGE_B), "the LDS plan has room");
 };
 
 // dS tile in LDS: one 128-byte row of 64 query rows per key, its eight 16-byte units (8 query rows each) permuted by the key:
@@ -65,27 +74,20 @@ __device__ inline int ds_off(int key, int unit) {
   return key * 128 + ((unit ^ (((key >> 2) & 1) | (key & 2) | ((key >> 1) & 4))) << 4);
 }
 
-// SEG: blocks of more than KEYS keys are served, in segments (its second form of the stage loop spills 7 registers at d = 64).
-template <int D, int NW, bool SEG>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void m_slc_bwd(SlcBwdArgs a) {
+// A chunk of the list of one selection block.  SEG: blocks of more than KEYS keys are served.
+template <int D, int NW, int RG, bool SEG>
+__device__ __forceinline__ void slc_bwd_chunk(const SlcBwdArgs &a, unsigned char *smem, const ChunkRef &cr, int g, int kbeg, int kend) {
   using P = PTile<D>;
-  using SH = SlcBwdShape<D, NW>;
-  constexpr int KB = SH::KB, ST = SH::ST, ROWS = SH::ROWS, NTHR = SH::NTHR, QB = SH::QB, KS = SH::KS;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
+  using SH = SlcBwdShape<D, NW, RG>;
+  constexpr int KB = SH::KB, ST = SH::ST, ROWS = SH::ROWS, ALL_ROWS = SH::ALL_ROWS, TILES = SH::TILES, NTHR = SH::NTHR, GW = SH::GW, QB = SH::QB, KS = SH::KS;
+  const int wid = (threadIdx.x >> 6) % GW, grp = RG == 1 ? 0 : (threadIdx.x >> 6) / GW, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
   const int hs = a.v.hs, Hq = a.v.Hq, Hkv = a.v.Hkv;
-  const int wi = blockIdx.x;
-  if (wi >= a.chunk_start[Hkv * a.v.Ns]) return;
-  const ChunkRef cr = a.chunk_order[wi];
-  const int g = cr.key / a.v.Ns, blk = cr.key % a.v.Ns;
-  const int kbeg = a.v.slc_start[blk], kend = a.v.slc_start[blk + 1];
-  if (kend - kbeg <= a.len_lo || kend - kbeg > a.len_hi) return;
   const int qbeg = cr.first, qend = cr.first + cr.count;
   const size_t out_row0 = (size_t)a.part_row_start[cr.key] + (size_t)cr.chunk * (kend - kbeg);
   const size_t kstride = (size_t)Hkv * D;
   const float sl2 = a.v.sl2, scale = a.v.scale;
   const typename P::Lanes ln = P::lanes();
-  const int slots = ROWS / hs;  // tokens per stage
+  const int slots = ALL_ROWS / hs;  // tokens per stage
   const int n_st = (cr.count + slots - 1) / slots;
 
   // partial rows: ((pos*Hkv + g)*T + rank)*hs + head; the row behind the last one takes what belongs to no token
@@ -95,14 +97,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   // first partial row
   // (a thread's items are the same piece of rows in tiles IT_TILES apart; threads past the end repeat an item)
   static_assert(NTHR % P::ITEMS == 0, "whole tiles at a time");
-  constexpr int NI = (ST * P::ITEMS + NTHR - 1) / NTHR, IT_TILES = NTHR / P::ITEMS;
-  const int it_tile = threadIdx.x / P::ITEMS % ST;
+  constexpr int NI = (TILES * P::ITEMS + NTHR - 1) / NTHR, IT_TILES = NTHR / P::ITEMS;
+  const int it_tile = threadIdx.x / P::ITEMS % TILES;
   const int it_row = threadIdx.x % P::ITEMS / P::SEGS, it_seg = threadIdx.x % P::SEGS;
   const int it_off = it_tile * P::BYTES + P::off(it_row, it_seg);
   const int it_slot = (it_tile * 32 + it_row) / hs, it_step = IT_TILES * 32 / hs;  // (hs is 1, 2, 4, 8 or 16)
   const int it_col = (g * hs + it_row % hs) * D + it_seg * 8;
-  const bool has_sc = threadIdx.x < 2 * ROWS;
-  const int sc_arr = (threadIdx.x / ROWS) & 1, sc_r = threadIdx.x % ROWS;
+  const bool has_sc = threadIdx.x < 2 * ALL_ROWS;
+  const int sc_arr = (threadIdx.x / ALL_ROWS) & 1, sc_r = threadIdx.x % ALL_ROWS;
   const int sc_slot = sc_r / hs, sc_head = g * hs + sc_r % hs;
   const float *sc_src = sc_arr == 0 ? a.lse2s : a.deltas;
   const float sc_mul = sc_arr == 1 ? -1.0f : 1.0f;
@@ -139,13 +141,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       *reinterpret_cast<bf16x8 *>(stage + it_off + i * IT_TILES * P::BYTES) = r.rq[i];
-      *reinterpret_cast<bf16x8 *>(stage + ST * P::BYTES + it_off + i * IT_TILES * P::BYTES) = r.rd[i];
+      *reinterpret_cast<bf16x8 *>(stage + TILES * P::BYTES + it_off + i * IT_TILES * P::BYTES) = r.rd[i];
     }
     // (written by every thread, those without a scalar or a token into a spare word: a branch here would make the compiler
     // wait for everything outstanding, the stores of the dQ rows included)
-    ((float *)(smem))[has_sc ? (int)((st & 1) * SH::STAGE_B + 2 * ST * P::BYTES) / 4 + (int)threadIdx.x : SH::SPARE / 4] =
+    ((float *)(smem))[has_sc ? (int)((st & 1) * SH::STAGE_B + 2 * TILES * P::BYTES) / 4 + (int)threadIdx.x : SH::SPARE / 4] =
         r.missing ? INFINITY : r.sc * sc_mul;
-    ((uint32_t *)(smem))[(int)threadIdx.x < slots ? SH::ROW_OFF / 4 + (st & 3) * ROWS + (int)threadIdx.x : SH::SPARE / 4] =
+    ((uint32_t *)(smem))[(int)threadIdx.x < slots ? SH::ROW_OFF / 4 + (st & 3) * ALL_ROWS + (int)threadIdx.x : SH::SPARE / 4] =
         qbeg + st * slots + (int)threadIdx.x < qend ? (((uint32_t)r.tok * Hkv + g) * a.v.T + r.rank) * hs : dummy;
   };
 
@@ -153,12 +155,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   int ks0 = kbeg;
   do {
     const int nk = min(SH::KEYS, kend - ks0), n_ks = (nk + 31) >> 5;
-    // this wavefront's tiles of 16 keys: number wid and, if there are so many, wid + NW.  Wavefronts without a tile still
+    // this wavefront's tiles of 16 keys: number wid and, if there are so many, wid + GW.  Wavefronts without a tile still
     // stage rows, share the dQ product and keep the barriers.
-    const int n_tiles = (nk + 15) >> 4, my_tiles = (n_tiles > wid) + (n_tiles > wid + NW);
+    const int n_tiles = (nk + 15) >> 4, my_tiles = (n_tiles > wid) + (n_tiles > wid + GW);
     const int k0 = ks0 + wid * 16;
     load_positions(0, pos);
-    for (int i = threadIdx.x; i < 4 * ROWS; i += NTHR) ((uint32_t *)(smem + SH::ROW_OFF))[i] = dummy;
+    for (int i = threadIdx.x; i < 4 * ALL_ROWS; i += NTHR) ((uint32_t *)(smem + SH::ROW_OFF))[i] = dummy;
     // K rows of the segment into LDS, zeros past its end, for the K^T operands of dQ
     constexpr int KT0 = SH::KT_OFF;
     for (int it = threadIdx.x; it < KS * P::ITEMS; it += NTHR) {
@@ -166,13 +168,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       const bf16x8 x = key < nk ? ld8(a.v.Ks + (size_t)(ks0 + key) * kstride + (size_t)g * D + seg * 8) : zero8();
       *reinterpret_cast<bf16x8 *>(smem + KT0 + t * P::BYTES + P::off(row, seg)) = x;
     }
-    if (n_tiles & 1)  // the last contraction step of the dQ product also reads the tile that no wavefront has
-      for (int i = threadIdx.x; i < SH::BUFS * 128; i += NTHR)
-        *reinterpret_cast<bf16x8 *>(smem + SH::DS_OFF + (i >> 7) * SH::DS_B + n_tiles * 2048 + (i & 127) * 16) = zero8();
     bf16x8 kop[KB][D / 32], vop[KB][D / 32];  // this wavefront's keys (rows past the block are padded: in bounds)
 #pragma unroll
     for (int kbk = 0; kbk < KB; ++kbk) {
-      const size_t off = (size_t)min(k0 + 16 * NW * kbk + n, a.v.N + SSA_KEY_PAD / 2) * kstride + (size_t)g * D + 8 * quad;
+      const size_t off = (size_t)min(k0 + 16 * GW * kbk + n, a.v.N + SSA_KEY_PAD / 2) * kstride + (size_t)g * D + 8 * quad;
 #pragma unroll
       for (int ks = 0; ks < D / 32; ++ks) {
         kop[kbk][ks] = ld8(a.v.Ks + off + 32 * ks);
@@ -183,7 +182,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     load_positions(1, pos);
     __syncthreads();
     const int dtw = wid % SH::NT, qb0 = wid / SH::NT * QB;  // this wavefront's share of the dQ product
+    // K^T of this wavefront's dims, for the whole segment (read with every step instead, 6 LDS reads per pair of matrix instructions)
     const int kt_l = P::slot_off(4 * quad + (n >> 2), P::tr_seg(dtw) + ((n & 3) >> 1) * 2) + (n & 1) * 8;
+    typedef __attribute__((address_space(3))) s16x4 *tr_ptr;
+    typedef __attribute__((ext_vector_type(8))) short s16x8;
+    auto tr_pair = [](lds_cptr lo_at, lds_cptr hi_at) {
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)lo_at), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)hi_at);
+      const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      return __builtin_bit_cast(bf16x8, both);
+    };
+    bf16x8 kt[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const lds_cptr kb = (lds_cptr)(smem + KT0) + kt_l + ks * P::BYTES;
+      kt[ks] = tr_pair(kb, kb + 256);
+    }
+    __syncthreads();  // (the dS tiles take their place)
+    // the dQ product also reads tiles that no wavefront has, up to a multiple of four
+    for (int t = n_tiles; t < ((n_tiles + 3) & ~3); ++t)
+      for (int i = threadIdx.x; i < SH::BUFS * RG * 128; i += NTHR)
+        *reinterpret_cast<bf16x8 *>(smem + SH::DS_OFF + (i >> 7) * SH::DS_GROUP_B + t * 2048 + (i & 127) * 16) = zero8();
     f32x4 dk[KB][D / 16], dv[KB][D / 16];
 #pragma unroll
     for (int kbk = 0; kbk < KB; ++kbk)
@@ -192,30 +210,30 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     // lane parts of the dS and dQ tile addresses
     // (further units of a row are the first one's with bits 4..6 flipped, further tiles a constant away)
     static_assert(SH::DS_OFF % 128 == 0, "rows of the dS tile start on a multiple of their length");
-    const int ds_w0 = SH::DS_OFF + ds_off(wid * 16 + n, quad);
+    const int ds_w0 = SH::DS_OFF + grp * SH::DS_GROUP_B + ds_off(wid * 16 + n, quad);
     int ds_r0[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h)  // query rows 4*(n & 3) .. +3 of the block, keys 8*quad + 4*h + (n >> 2)
-      ds_r0[h] = SH::DS_OFF + ds_off(8 * quad + 4 * h + (n >> 2), 2 * qb0 + ((n >> 1) & 1)) + 8 * (n & 1);
-    const int dq_w = SH::DQ_OFF + (16 * qb0 + n) * (D * 2) + ((((acc_dim(dtw, quad) >> 3) ^ (n >> 1)) & (D / 8 - 1)) << 4) + (quad & 1) * 8;
+      ds_r0[h] = SH::DS_OFF + grp * SH::DS_GROUP_B + ds_off(8 * quad + 4 * h + (n >> 2), 2 * qb0 + ((n >> 1) & 1)) + 8 * (n & 1);
+    const int dq_w = SH::DQ_OFF + (ROWS * grp + 16 * qb0 + n) * (D * 2) + ((((acc_dim(dtw, quad) >> 3) ^ (n >> 1)) & (D / 8 - 1)) << 4) + (quad & 1) * 8;
 
     auto scores = [&](int st, auto tiles) {  // stage st: S, dP, P, dS; dV, dK; dS to LDS
       constexpr int KT = decltype(tiles)::value;
       unsigned char *stage = smem + (st & 1) * SH::STAGE_B;
-      const lds_cptr st0 = (lds_cptr)stage;
+      const lds_cptr st0 = (lds_cptr)stage + grp * ST * P::BYTES;
       const __attribute__((address_space(3))) float *scal =
-          (const __attribute__((address_space(3))) float *)(st0 + 2 * ST * P::BYTES) + 8 * quad;
+          (const __attribute__((address_space(3))) float *)((lds_cptr)stage + 2 * TILES * P::BYTES) + grp * ROWS + 8 * quad;
 #pragma unroll
       for (int rt = 0; rt < ST; ++rt) {
         // (kept apart here and below: operands of different steps in flight together spill, 3310 -> 3240 us)
         __builtin_amdgcn_sched_barrier(0);
-        const lds_cptr Qt = st0 + rt * P::BYTES, Dt = st0 + (ST + rt) * P::BYTES;
+        const lds_cptr Qt = st0 + rt * P::BYTES, Dt = st0 + (TILES + rt) * P::BYTES;
         float lse2[8];
         f32x4 s[KT][2], dp[KT][2];
         {
           typedef const __attribute__((address_space(3))) f32x4 *f4p;
           const f32x4 l0 = *(f4p)(scal + 32 * rt), l1 = *(f4p)(scal + 32 * rt + 4);
-          const f32x4 d0 = *(f4p)(scal + ROWS + 32 * rt), d1 = *(f4p)(scal + ROWS + 32 * rt + 4);
+          const f32x4 d0 = *(f4p)(scal + ALL_ROWS + 32 * rt), d1 = *(f4p)(scal + ALL_ROWS + 32 * rt + 4);
 #pragma unroll
           for (int j = 0; j < 4; ++j) { lse2[j] = l0[j]; lse2[4 + j] = l1[j]; }
 #pragma unroll
@@ -247,8 +265,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             ds[kbk][j] = (__bf16)(p * dp[kbk][j >> 2][j & 3]);
           }
           // keys past the block give finite or infinite garbage columns of dS that dQ must not see
-          if (k0 + 16 * (NW * kbk + 1) > kend && k0 + 16 * NW * kbk + n >= kend) ds[kbk] = zero8();
-          *reinterpret_cast<bf16x8 *>(smem + (SH::DOUBLE ? (st & 1) * SH::DS_B : 0) + NW * 2048 * kbk + (ds_w0 ^ (rt << 6))) = ds[kbk];
+          if (k0 + 16 * (GW * kbk + 1) > kend && k0 + 16 * GW * kbk + n >= kend) ds[kbk] = zero8();
+          *reinterpret_cast<bf16x8 *>(smem + (SH::DOUBLE ? (st & 1) * SH::DS_B : 0) + GW * 2048 * kbk + (ds_w0 ^ (rt << 6))) = ds[kbk];
         }
 #pragma unroll
         for (int dt = 0; dt < D / 16; ++dt) {
@@ -262,47 +280,57 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
     };
     // this wavefront's share of the partial rows of stage st from the segment before (written by this workgroup, read past the
-    // L1); rows that do not exist read the spare row, and their sums go back there
+    // L1); rows that do not exist read the spare row, and their sums go back there.  (Requested where they are needed: a stage earlier
+    // they take registers that the scores have not got.)
     struct Partials { uint64_t w[QB]; };
     auto load_partials = [&](int st, Partials &p) {
-      const uint32_t *rows = (const uint32_t *)(smem + SH::ROW_OFF) + (st & 3) * ROWS;
+      const uint32_t *rows = (const uint32_t *)(smem + SH::ROW_OFF) + (st & 3) * ALL_ROWS;
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
-        const int row = 16 * (qb0 + q) + n;
+        const int row = ROWS * grp + 16 * (qb0 + q) + n;
         const uint32_t pr = rows[row / hs];
         p.w[q] = __hip_atomic_load((const uint64_t *)(a.pdq + (size_t)(pr + (pr == dummy ? 0 : row % hs)) * D + acc_dim(dtw, quad)),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     };
-    auto dq_product = [&](int st, auto cont, const Partials &p) {  // rows of stage st: this wavefront's dims of dQ, to LDS
+    const bool cont = SEG && ks0 != kbeg;
+    auto dq_product = [&](int st) {  // rows of stage st: this wavefront's dims of dQ, to LDS
+      Partials p{};
+      if (cont) load_partials(st, p);
       f32x4 acc[QB];
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
-        acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (decltype(cont)::value) {
-          const bf16x4 x = __builtin_bit_cast(bf16x4, p.w[q]);
+        const bf16x4 x = __builtin_bit_cast(bf16x4, p.w[q]);  // (zeros in a block's first segment)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[q][i] = (float)x[i];
-        }
+        for (int i = 0; i < 4; ++i) acc[q][i] = SEG ? (float)x[i] : 0.f;
       }
       const lds_cptr base = (lds_cptr)smem + (SH::DOUBLE ? (st & 1) * SH::DS_B : 0);
-      typedef __attribute__((address_space(3))) s16x4 *tr_ptr;
+      // the operands of a few steps are requested together, the steps of tiles that the segment has not got left out in pairs
+      auto steps = [&](auto from, auto to) {
+        constexpr int F = decltype(from)::value, T = decltype(to)::value;
+        bf16x8 op[T > F ? T - F : 1][QB];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        if (ks < n_ks) {
-          typedef __attribute__((ext_vector_type(8))) short s16x8;
-          const lds_cptr kb = (lds_cptr)(smem + KT0) + kt_l + ks * P::BYTES;
-          const s16x4 klo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)kb), khi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(kb + 256));
-          const s16x8 k8 = __builtin_shufflevector(klo, khi, 0, 1, 2, 3, 4, 5, 6, 7);
-          const bf16x8 kt = __builtin_bit_cast(bf16x8, k8);
+        for (int ks = F; ks < T; ++ks)
 #pragma unroll
-          for (int q = 0; q < QB; ++q) {
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(base + (ds_r0[0] ^ (q << 5)) + ks * 4096));
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(base + (ds_r0[1] ^ (q << 5)) + ks * 4096));
-            const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            acc[q] = mfma16(kt, __builtin_bit_cast(bf16x8, both), acc[q]);
-          }
-        }
+          for (int q = 0; q < QB; ++q) op[ks - F][q] = tr_pair(base + (ds_r0[0] ^ (q << 5)) + ks * 4096, base + (ds_r0[1] ^ (q << 5)) + ks * 4096);
+#pragma unroll
+        for (int ks = F; ks < T; ++ks)
+#pragma unroll
+          for (int q = 0; q < QB; ++q) acc[q] = mfma16(kt[ks], op[ks - F][q], acc[q]);
+      };
+      typedef std::integral_constant<int, 0> I0;
+      typedef std::integral_constant<int, 2> I2;
+      typedef std::integral_constant<int, 4> I4;
+      typedef std::integral_constant<int, KS - 2> L2;
+      typedef std::integral_constant<int, KS> L0;
+      if (KS == 4 || n_ks <= 4) {
+        steps(I0(), I2());
+        if (n_ks > 2) steps(I2(), I4());
+      } else {
+        steps(I0(), I4());
+        steps(I4(), L2());
+        if (n_ks > 6) steps(L2(), L0());
+      }
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
         bf16x4 x;
@@ -312,8 +340,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
     };
     auto store_dq = [&](int st) {  // the finished dQ rows of stage st go out as whole lines
-      const uint32_t *rows = (const uint32_t *)(smem + SH::ROW_OFF) + (st & 3) * ROWS;
-      constexpr int CH = D / 8, ITEMS = ROWS * CH;
+      const uint32_t *rows = (const uint32_t *)(smem + SH::ROW_OFF) + (st & 3) * ALL_ROWS;
+      constexpr int CH = D / 8, ITEMS = ALL_ROWS * CH;
 #pragma unroll
       for (int i0 = 0; i0 < ITEMS; i0 += NTHR) {
         const int it = i0 + (int)threadIdx.x;
@@ -329,31 +357,42 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     // Iteration i: rows of stage i into LDS | barrier | loads of stage i+1; finished dQ rows of the stage LAG+1 before out;
     // scores of stage i; dQ product of stage i - LAG.  Loads and stores are issued in every iteration, in this order and
     // under no condition, so that the wait for the loads at the next iteration's start leaves the younger stores in flight.
-    auto stream = [&](auto cont) {
-      store_dq(-1);  // (to the spare row: the loop is entered with the same loads and stores outstanding as an iteration leaves)
+    store_dq(-1);  // (to the spare row: the loop is entered with the same loads and stores outstanding as an iteration leaves)
 #pragma unroll 1
-      for (int i = 0; i < n_st + 1 + SH::LAG; ++i) {
-        Partials part{};
-        store_stage(i, regs);
-        __syncthreads();
-        if constexpr (decltype(cont)::value) load_partials(i - SH::LAG, part);
-        load_stage(i + 1, regs, pos);
-        load_positions(i + 2, pos);
-        store_dq(i - 1 - SH::LAG);
-        if (i < n_st) {
-          if (my_tiles == 2) scores(i, std::integral_constant<int, 2>());
-          else if (my_tiles == 1) scores(i, std::integral_constant<int, 1>());
-        }
-        if (!SH::DOUBLE) __syncthreads();
-        if (i >= SH::LAG && i < n_st + SH::LAG) dq_product(i - SH::LAG, cont, part);
+    for (int i = 0; i < n_st + 1 + SH::LAG; ++i) {
+      store_stage(i, regs);
+      __syncthreads();
+      load_stage(i + 1, regs, pos);
+      load_positions(i + 2, pos);
+      store_dq(i - 1 - SH::LAG);
+      if (i < n_st) {
+        if (my_tiles == 2) scores(i, std::integral_constant<int, 2>());
+        else if (my_tiles == 1) scores(i, std::integral_constant<int, 1>());
       }
-    };
-    if (!SEG || ks0 == kbeg) stream(std::false_type());
-    else if constexpr (SEG) stream(std::true_type());
+      if (!SH::DOUBLE) __syncthreads();
+      if (i >= SH::LAG && i < n_st + SH::LAG) dq_product(i - SH::LAG);
+    }
+    if constexpr (RG == 2) {  // dK and dV of the second group to the first
+      __syncthreads();
+      f32x4 *meet = reinterpret_cast<f32x4 *>(smem) + (threadIdx.x % (64 * GW));
+      auto each = [&](auto what) {
+#pragma unroll
+        for (int kbk = 0; kbk < KB; ++kbk)
+#pragma unroll
+          for (int dt = 0; dt < D / 16; ++dt) {
+            what(dk[kbk][dt], meet[(2 * (kbk * (D / 16) + dt)) * 64 * GW]);
+            what(dv[kbk][dt], meet[(2 * (kbk * (D / 16) + dt) + 1) * 64 * GW]);
+          }
+      };
+      if (grp == 1) each([](f32x4 &x, f32x4 &m) { m = x; });
+      __syncthreads();
+      if (grp == 1) return;
+      each([](f32x4 &x, f32x4 &m) { x += m; });
+    }
     {
 #pragma unroll
       for (int kbk = 0; kbk < KB; ++kbk) {
-        const int key = k0 + 16 * NW * kbk + n;
+        const int key = k0 + 16 * GW * kbk + n;
         if (key >= kend) continue;
         const size_t off = (out_row0 + (size_t)(key - kbeg)) * D;
 #pragma unroll
@@ -372,29 +411,37 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   } while (SEG && ks0 < kend);
 }
 
+// NW = 4: no block has more than 128 keys; NW = 8: SEG, some have more than 256.
 template <int D, int NW, bool SEG>
-void launch(SlcBwdArgs a, int lo, int hi, unsigned chunks, hipStream_t s) {
-  using SH = SlcBwdShape<D, NW>;
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void m_slc_bwd(SlcBwdArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int wi = blockIdx.x;
+  if (wi >= a.chunk_start[a.v.Hkv * a.v.Ns]) return;
+  const ChunkRef cr = a.chunk_order[wi];
+  const int g = cr.key / a.v.Ns, blk = cr.key % a.v.Ns;
+  const int kbeg = a.v.slc_start[blk], kend = a.v.slc_start[blk + 1];
+  if constexpr (NW == 4) slc_bwd_chunk<D, 4, 1, false>(a, smem, cr, g, kbeg, kend);
+  else if (uniform(kend - kbeg) > SlcBwdShape<D, 8, 2>::KEYS) slc_bwd_chunk<D, 8, 1, SEG>(a, smem, cr, g, kbeg, kend);
+  else slc_bwd_chunk<D, 8, 2, false>(a, smem, cr, g, kbeg, kend);
+}
+
+template <int D, int NW, bool SEG>
+void launch(const SlcBwdArgs &a, unsigned chunks, hipStream_t s) {
+  constexpr int L1 = SlcBwdShape<D, NW, 1>::LDS_B, L2 = SlcBwdShape<D, 8, 2>::LDS_B, LDS_B = NW == 8 && L2 > L1 ? L2 : L1;
   static std::once_flag once;  // raise the dynamic LDS limit once per process for this instantiation
-  std::call_once(once, [] { (void)hipFuncSetAttribute((const void *)m_slc_bwd<D, NW, SEG>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_B); });
-  a.len_lo = lo;
-  a.len_hi = hi;
-  m_slc_bwd<D, NW, SEG><<<dim3(chunks), SH::NTHR, SH::LDS_B, s>>>(a);
+  std::call_once(once, [] { (void)hipFuncSetAttribute((const void *)m_slc_bwd<D, NW, SEG>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_B); });
+  m_slc_bwd<D, NW, SEG><<<dim3(chunks), 64 * NW, LDS_B, s>>>(a);
 }
 
 template <int D>
 int launch_slc_bwd(const MfmaView &v, const BwdBuffers &w, int slc_tok_max, hipStream_t s) {
   const size_t NH = (size_t)v.N * v.Hq;
-  SlcBwdArgs a{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.list, w.sel.chunk_start, w.sel.part_row_start, w.sel.rank,
-               w.sel.order, w.part.o, w.pK, w.pV, 0, 0};
-  constexpr int SHORT = SlcBwdShape<D, 4>::KEYS, LONG = SlcBwdShape<D, 8>::KEYS;
+  const SlcBwdArgs a{v, w.Qs, w.dOg + NH * D, w.lse2s + NH, w.deltag + NH, w.sel.list, w.sel.chunk_start, w.sel.part_row_start, w.sel.rank,
+                     w.sel.order, w.part.o, w.pK, w.pV};
   const unsigned chunks = (unsigned)w.max_chunks;
-  // blocks of up to 128 keys: 4 wavefronts, two workgroups per compute unit; longer ones: 8 wavefronts, so that dQ of a
-  // block is complete after 256 keys (4 wavefronts, which read the partial row of the first 128 keys back, took 3770 us for
-  // 3390 with the line at 160 keys, 5170 at 192)
-  launch<D, 4, false>(a, 0, SHORT, chunks, s);
-  if (slc_tok_max > LONG) launch<D, 8, true>(a, SHORT, 0x7fffffff, chunks, s);
-  else if (slc_tok_max > SHORT) launch<D, 8, false>(a, SHORT, LONG, chunks, s);
+  if (slc_tok_max <= SlcBwdShape<D, 4, 1>::KEYS) launch<D, 4, false>(a, chunks, s);
+  else if (slc_tok_max <= SlcBwdShape<D, 8, 1>::KEYS) launch<D, 8, false>(a, chunks, s);
+  else launch<D, 8, true>(a, chunks, s);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 

@@ -362,7 +362,7 @@ Plan plan(int N, int Hkv, int T, int Ns) {
   p.cstart = take((keys + 1) * 4); p.prow = take((keys + 1) * 4); p.bcstart = take((keys + 1) * 4);
   p.bins = take(2 * ORDER_BINS * 4 + 4);
   // at most one partly filled chunk per key on top of the full ones
-  const size_t bc = entries / BC_CHUNK_MIN + keys + 8, dkv = entries / 256 + keys + 8;
+  const size_t bc = entries / BC_CHUNK_MIN + keys + 8, dkv = entries / DKV_CHUNK_MIN + keys + 8;
   p.bcslot = take(bc * sizeof(int4)); p.slot = take(dkv * sizeof(int4));
   p.bcorder = take(bc * sizeof(ChunkRef)); p.order = take(dkv * sizeof(ChunkRef));
   p.total = off;

@@ -30,6 +30,19 @@ def test_selection_backward_edges(seed, lens, hq, hkv, d, l, topk):
     full_parity(inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk))
 
 
+@pytest.mark.parametrize("seed,lens,hq,hkv,d,l,topk", [
+    (531, (270, 20), 2, 2, 64, (10, 130, 64), 2),        # blocks of 130, 10 and 20 keys; 128 tokens per stage of the short ones
+    (532, (386,), 16, 1, 64, (16, 128, 64), 4),          # the longest block just short enough for four wavefronts
+    (533, (387, 3), 16, 1, 64, (3, 129, 64), 4),         # one key more: four tokens per group and stage, a list of three tokens
+    (534, (900, 257, 61), 8, 2, 64, (20, 280, 64), 3),   # a second segment of 24 keys; blocks of 60, 61 and 257 in the same launch
+    (535, (520, 90), 4, 1, 32, (65, 260, 64), 2),        # the same at head_dim 32
+    (536, (212, 5), 8, 1, 32, (12, 144, 64), 2),         # nine tiles of keys beside five
+    (537, (194, 193), 16, 2, 64, (1, 193, 64), 2),       # thirteen tiles, the last of one key; blocks of one key
+])
+def test_blocks_of_many_lengths_in_one_launch(seed, lens, hq, hkv, d, l, topk):
+    full_parity(inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk))
+
+
 def test_one_long_block_among_many_short_ones():
     """Half of the tokens on one voxel, the rest alone in their blocks: the two kernels would launch 5 million workgroups."""
     wl = inputs.random_points_workload(520, 64, (18300,) + (300,) * 60, 16, 2, 64, (1, 2, 2), 2, "bf16")
