@@ -40,7 +40,7 @@ def algorithmic_flops(wl, blk_arrays, idx):
 ROCPROF_NAME = {
     "cmp_fwd_scores_topk": "m_cmp_fwd<", "slc_fwd": "m_slc_fwd_bc<", "win_fwd": "m_walk_fwd<{d}, 2, false>",
     "bwd_dq_cmp_win": "m_bwd_dq<{d},", "bwd_dq_slc": "m_bwd_dq_bc<{d},", "bwd_slc": "m_slc_bwd<{d},",
-    "bwd_dkv_win": "m_bwd_dkv<{d}, {kb}, 0,", "bwd_dkv_slc": "m_bwd_dkv<{d}, {kb}, 1,", "bwd_dkv_cmp": "m_bwd_dkv<{d}, {kb}, 2,",
+    "bwd_dkv_cmp_win": "m_bwd_dkv<{d}, {kb}, 0,", "bwd_dkv_slc": "m_bwd_dkv<{d}, {kb}, 1,",
 }
 
 
@@ -116,10 +116,11 @@ def kernel_times(wl, steps):
     return {nm: tot / cnt for nm, (tot, cnt) in prof.items()}, arrays, sel
 
 
-def dense_dq_ms(kd, pairs):
-    """Window share of the dQ kernel that handles the compression and window branches (split by their pair counts): in the
-    dense stand-in the window is the whole item, the compression branch a few per cent of it."""
-    return kd["bwd_dq_cmp_win"] * pairs["win"] / max(pairs["win"] + pairs["cmp"], 1)
+def dense_bwd_ms(kd, pairs):
+    """Delta, and the window share of the dQ and dK/dV kernels that handle the compression and window branches (split by their pair
+    counts): in the dense stand-in the window is the whole item, the compression branch a few per cent of it."""
+    both = kd["bwd_dq_cmp_win"] + kd["bwd_dkv_cmp_win"]
+    return both * pairs["win"] / max(pairs["win"] + pairs["cmp"], 1) + kd["bwd_pre_delta"]
 
 
 # Token sweep of the sparse path against dense attention computed by the same library (the window branch with one
@@ -148,7 +149,7 @@ def dense_sweep(args):
         s_fwd = sum(ks.get(nm, 0.0) for nm in fwd_names)
         s_bwd = sum(v_ for nm, v_ in ks.items() if nm not in fwd_names) + ks["prep_sort_pool"]
         d_fwd = kd["win_fwd"]
-        d_bwd = dense_dq_ms(kd, dense_pairs) + kd["bwd_dkv_win"] + kd["bwd_pre_delta"]
+        d_bwd = dense_bwd_ms(kd, dense_pairs)
         line = {"sweep": "ssa_vs_dense", "grid": grid, "n_tokens": n, "heads": [sparse.n_heads_q, sparse.n_heads_kv],
                 "head_dim": sparse.head_dim, "ssa_fwd_ms": round(s_fwd, 3), "ssa_bwd_ms": round(s_bwd, 3),
                 "dense_fwd_ms": round(d_fwd, 3), "dense_bwd_ms": round(d_bwd, 3),
@@ -179,7 +180,7 @@ def seq1d_bench(args):
         s_fwd = sum(ks.get(nm, 0.0) for nm in FWD_KERNELS)
         s_bwd = sum(v_ for nm, v_ in ks.items() if nm not in FWD_KERNELS) + ks["prep_sort_pool"]
         d_fwd = kd["win_fwd"]
-        d_bwd = dense_dq_ms(kd, dense_pairs) + kd["bwd_dkv_win"] + kd["bwd_pre_delta"]
+        d_bwd = dense_bwd_ms(kd, dense_pairs)
         flops = 14 * sparse.head_dim * total_pairs
         line = {"bench": "sequence_partition", "lens": list(lens), "n_tokens": n, "blocks": [32, 64, 512], "topk": 16,
                 "heads": [sparse.n_heads_q, sparse.n_heads_kv], "head_dim": sparse.head_dim,
@@ -438,14 +439,14 @@ def ablation_sweep(args):
             n, d = wl.n_tokens, wl.head_dim
             ks, arrays, sel = kernel_times(wl, 2)
             pairs = algorithmic_flops(wl, arrays, sel)
-            # the compression and window branches share a dQ launch: its time is split by their pair counts
-            dq_cw = ks["bwd_dq_cmp_win"]
+            # the compression and window branches share a dQ and a dK/dV launch: their time is split by the pair counts
+            bwd_cw = ks["bwd_dq_cmp_win"] + ks["bwd_dkv_cmp_win"]
             f_c = pairs["cmp"] / max(pairs["cmp"] + pairs["win"], 1)
             branch_ms = {
-                "cmp": ks["cmp_fwd_scores_topk"] + dq_cw * f_c + ks["bwd_dkv_cmp"],
+                "cmp": ks["cmp_fwd_scores_topk"] + bwd_cw * f_c,
                 "slc": ks["slc_fwd"] + ks["fwd_invert_selection"] + ks["slc_merge_combine"] + ks["bwd_dq_slc"] + ks["bwd_dq_merge"]
-                       + ks["bwd_dkv_slc"] + ks["bwd_slc_reduce"] + ks["bwd_invert_selection"],
-                "win": ks["win_fwd"] + dq_cw * (1 - f_c) + ks["bwd_dkv_win"],
+                       + ks["bwd_dkv_slc"] + ks["bwd_invert_selection"],
+                "win": ks["win_fwd"] + bwd_cw * (1 - f_c),
             }
             other = sum(ks.values()) + ks["prep_sort_pool"] - sum(branch_ms.values())
             total = sum(branch_ms.values()) + other
@@ -562,9 +563,9 @@ def bench_workload(name, args, steps, warmup, cpu_seconds):
     # dQ kernel (6d), dV, dK on the dK/dV kernels (4d); recomputed scores are not counted
     kflops = {
         "cmp_fwd_scores_topk": 4 * d * pairs["cmp"], "slc_fwd": 4 * d * pairs["slc"], "win_fwd": 4 * d * pairs["win"],
-        "bwd_dq_cmp_win": 6 * d * (pairs["cmp"] + pairs["win"]), "bwd_dq_slc": 6 * d * pairs["slc"], "bwd_dkv_cmp": 4 * d * pairs["cmp"], "bwd_dkv_slc": 4 * d * pairs["slc"],
+        "bwd_dq_cmp_win": 6 * d * (pairs["cmp"] + pairs["win"]), "bwd_dq_slc": 6 * d * pairs["slc"], "bwd_dkv_slc": 4 * d * pairs["slc"],
         "bwd_slc": 10 * d * pairs["slc"],  # both in one pass (head_dim 32, 64)
-        "bwd_dkv_win": 4 * d * pairs["win"], "generic_path": (14 if bwd else 4) * d * all_pairs,
+        "bwd_dkv_cmp_win": 4 * d * (pairs["cmp"] + pairs["win"]), "generic_path": (14 if bwd else 4) * d * all_pairs,
     }
     dom = max(kern_ms, key=kern_ms.get) if kern_ms else None
     roofline = None

@@ -10,7 +10,7 @@
 //     compression and window branches;
 //   * m_slc_bwd: the selection branch, block-centric like its forward kernel: dK, dV and one partial dQ row per selected
 //     block, added per token in rank order by m_dq_merge; where long blocks dominate and at head_dim 128, two kernels, m_bwd_dq_bc and m_bwd_dkv;
-//   * m_bwd_dkv: key-centric; a wavefront owns 16*KB keys and streams the query rows that attend to them
+//   * m_bwd_dkv (compression and window branch in one launch, with the sums of the selection branch's chunks): key-centric; a wavefront owns 16*KB keys and streams the query rows that attend to them
 //     (scores with the query rows in the lanes); the contractions over query rows take Q^T and dO^T from the
 //     staged row-major tiles through the transposing LDS read.
 #include "mfma_common.h"
@@ -187,19 +187,28 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32
 // ---------------------------------------------------------------------------------------------------------
 // dK/dV: key-centric
 // ---------------------------------------------------------------------------------------------------------
-enum { DKV_WIN = 0, DKV_SLC = 1, DKV_CMP = 2 };
+// What a launch serves: the selection branch; or the window branch, the compression branch and the sums of the selection branch's chunks.
+// The window's walks are the longest chains and too few to fill the chip, the sums wait for memory alone: beside the compression branch
+// both cost next to nothing.  Three launches -> one, us: 11k tokens 140 -> 90, 21k in three shapes 212 -> 170, 62k 1420 -> 1268, 65k in
+// sequences 882 -> 772.  (The sums at the end of the window's walks instead of in workgroups of their own: 5k tokens, a whole pass, 451 us
+// in three launches, 472, 404.)
+enum { DKV_CMP_WIN = 0, DKV_SLC = 1 };
 
 struct DkvArgs {
   MfmaView v;
-  const bf16_t *Qs, *dOs;             // sorted copies [N(pos)][Hq][D]: Q, and the branch's gate * dO
-  const float *lse2s, *deltas;        // already offset to the branch: [N(pos)][Hq]; delta over the rounded gate * dO rows
-  const int32_t *sel_list;              // selection branch: query positions per (g, block)
-  float *dK, *dV;                       // [rows][Hkv][D] fp32 (rows: sorted tokens, or compression blocks)
-  const int32_t *chunk_start;           // selection branch: [Hkv*Ns+1] first work chunk of each (g, block)
-  const ChunkRef *chunk_order;          // selection branch: execution order of the work chunks
-  const int32_t *part_row_start;        // selection branch: [Hkv*Ns+1] first row of each (g, block)'s partial sums
-  int tiles_per_block;                  // key tiles reserved per block in the grid
-  int q_splits;                         // compression branch: query range split into this many parts
+  const bf16_t *Qs, *dOg;             // sorted copies: Q [N(pos)][Hq][D], gate_b * dO [3][N(pos)][Hq][D]
+  const float *lse2s, *deltag;        // [3][N(pos)][Hq]; delta over the rounded gate * dO rows
+  const int32_t *sel_list;            // selection branch: query positions per (g, block)
+  const int32_t *chunk_start;         // selection branch: [Hkv*Ns+1] first work chunk of each (g, block)
+  const ChunkRef *chunk_order;        // selection branch: execution order of the work chunks
+  const int32_t *part_row_start;      // selection branch: [Hkv*Ns+1] first row of each (g, block)'s partial sums
+  const int32_t *tok_slc;             // [N(pos)] selection block
+  float *dKs, *dVs;                   // [N(pos)][Hkv][D]: window branch
+  float *pK, *pV;                     // [rows][D]: selection branch, partial sums per chunk
+  float *dKc, *dVc;                   // [q_splits][Nc][Hkv][D]: compression branch, partial sums per part of the query range
+  int slc_tiles, win_tiles, cmp_tiles;  // key tiles reserved per block (window, item) in the grid
+  int n_win, n_cmp;                   // workgroups of the window and the compression branch per KV head
+  int q_splits;                       // compression branch: query range split into this many parts
 };
 
 // LDS stage of the dK/dV kernels: ST tiles of 32 query rows each, of Q and of gate * dO (PTile layout: read both as
@@ -211,31 +220,48 @@ struct DkvStage {
   static constexpr int BYTES = TILES_B + 2 * 32 * ST * 4;   // + [2][32*ST] floats
 };
 
+// The sums of a key's partial dK and dV over the chunks of its block's list, in chunk order, into the rows of the first chunk.  One thread
+// per (sorted position, 4 dims) of KV head g.
+template <int D, int NTHR>
+__device__ inline void sum_chunks(const DkvArgs &a, int g, int wg) {
+  const size_t i = (size_t)wg * NTHR + threadIdx.x;
+  const int pos = (int)(i / (D / 4)), dim = (int)(i % (D / 4)) * 4;
+  if (pos >= a.v.N) return;
+  const int b = a.tok_slc[pos], list = g * a.v.Ns + b, b0 = a.v.slc_start[b], klen = a.v.slc_start[b + 1] - b0;
+  const int chunks = a.chunk_start[list + 1] - a.chunk_start[list];
+  if (chunks < 2) return;
+  const size_t at = ((size_t)a.part_row_start[list] + (size_t)(pos - b0)) * D + dim, step = (size_t)klen * D;
+  f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = sk;
+#pragma unroll 8
+  for (int c = 0; c < chunks; ++c) {
+    sk += *reinterpret_cast<const f32x4 *>(a.pK + at + c * step);
+    sv += *reinterpret_cast<const f32x4 *>(a.pV + at + c * step);
+  }
+  *reinterpret_cast<f32x4 *>(a.pK + at) = sk;
+  *reinterpret_cast<f32x4 *>(a.pV + at) = sv;
+}
+
 // A workgroup owns 16*KB*NW keys of one block (16*KB per wavefront, held in registers as MFMA B operands with their
 // dK and dV accumulators) and streams the query rows that attend to them in stages of ST tiles of 32 rows (32/h_s
 // token slots each), staged through LDS once per workgroup, double buffered, ONE barrier per stage: the loads of
 // stage i+1 are in flight while stage i is consumed and land in the other buffer before the barrier.
 template <int D, int KB, int MODE, int NW, int ST>
-__global__ __launch_bounds__(64 * NW) void m_bwd_dkv(DkvArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 3 : 2))) void m_bwd_dkv(DkvArgs a) {
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
   const int hs = a.v.hs, Hq = a.v.Hq;
   constexpr int WG_KEYS = 16 * KB * NW, NTHR = 64 * NW;
   using P = PTile<D>;
   using SG = DkvStage<D, ST>;
-  int g = blockIdx.y, blk, tile;
+  int g, blk, tile, split = 0;
   // key range of the block and query source
   int kbeg, kend, qbeg = 0, qend = 0;
   size_t out_row0 = 0;  // selection branch: first row of this chunk's partial sums
-  const bf16_t *Kr, *Vr;
-  if (MODE == DKV_WIN) {
-    blk = blockIdx.x / a.tiles_per_block; tile = blockIdx.x % a.tiles_per_block;
-    kbeg = a.v.win_start[blk]; kend = a.v.win_start[blk + 1];
-    qbeg = kbeg; qend = kend;
-    Kr = a.v.Ks; Vr = a.v.Vs;
-  } else if (MODE == DKV_SLC) {
-    // 1-D launch: the key tiles of one work chunk get workgroup ids 8 apart, i.e. they run on the same XCD close in
+  const bf16_t *Kr = a.v.Ks, *Vr = a.v.Vs;
+  const bool win = MODE == DKV_CMP_WIN && (int)blockIdx.x < a.n_win;
+  if (MODE == DKV_SLC) {
+    // the key tiles of one work chunk get workgroup ids 8 apart, i.e. they run on the same XCD close in
     // time, so the chunk's query rows are fetched into that L2 once.
-    const int per8 = 8 * a.tiles_per_block;
+    const int per8 = 8 * a.slc_tiles;
     const int nkeys = a.v.Hkv * a.v.Ns, wi = (int)(blockIdx.x / per8) * 8 + (int)(blockIdx.x % 8);
     if (wi >= a.chunk_start[nkeys]) return;
     const ChunkRef cr = a.chunk_order[wi];
@@ -245,15 +271,22 @@ __global__ __launch_bounds__(64 * NW) void m_bwd_dkv(DkvArgs a) {
     qbeg = cr.first;
     qend = cr.first + cr.count;
     out_row0 = (size_t)a.part_row_start[key] + (size_t)cr.chunk * (kend - kbeg);
-    Kr = a.v.Ks; Vr = a.v.Vs;
+  } else if (win) {
+    g = blockIdx.y; blk = (int)blockIdx.x / a.win_tiles; tile = (int)blockIdx.x % a.win_tiles;
+    kbeg = a.v.win_start[blk]; kend = a.v.win_start[blk + 1];
+    qbeg = kbeg; qend = kend;
   } else {
-    blk = blockIdx.x / a.tiles_per_block; tile = blockIdx.x % a.tiles_per_block;  // blk = batch item
+    const int per_split = a.n_cmp / a.q_splits, w = (int)blockIdx.x - a.n_win, x = w % per_split;
+    g = blockIdx.y;
+    if (w >= a.n_cmp) return sum_chunks<D, NTHR>(a, g, w - a.n_cmp); split = w / per_split; blk = x / a.cmp_tiles; tile = x % a.cmp_tiles;  // blk = batch item
     kbeg = a.v.cmp_batch[blk]; kend = a.v.cmp_batch[blk + 1];
     const int q0 = a.v.item_start[blk], q1 = a.v.item_start[blk + 1];
     const int per = (q1 - q0 + a.q_splits - 1) / a.q_splits;
-    qbeg = min(q1, q0 + (int)blockIdx.z * per); qend = min(q1, qbeg + per);
+    qbeg = min(q1, q0 + split * per); qend = min(q1, qbeg + per);
     Kr = a.v.Kc; Vr = a.v.Vc;
   }
+  const size_t branch_rows = (size_t)(MODE == DKV_SLC ? 1 : win ? 2 : 0) * a.v.N * Hq;
+  const bf16_t *dOs = a.dOg + branch_rows * D;
   if (kbeg + tile * WG_KEYS >= kend) return;             // whole workgroup beyond the block (uniform)
   const int k0 = kbeg + tile * WG_KEYS + wid * 16 * KB;  // this wave's first key
   const bool wave_on = k0 < kend;                        // idle wavefronts still help staging and keep the barriers
@@ -296,7 +329,7 @@ __global__ __launch_bounds__(64 * NW) void m_bwd_dkv(DkvArgs a) {
   const bool has_sc = threadIdx.x < 2 * 32 * ST;
   const int sc_arr = (threadIdx.x / (32 * ST)) & 1, sc_r = threadIdx.x % (32 * ST);
   const int sc_slot = (sc_r >> 5) * slots + (sc_r & 31) / hs, sc_head = g * hs + (sc_r & 31) % hs;
-  const float *sc_src = sc_arr == 0 ? a.lse2s : a.deltas;
+  const float *sc_src = (sc_arr == 0 ? a.lse2s : a.deltag) + branch_rows;
   const float sc_mul = sc_arr == 1 ? -1.0f : 1.0f;
   // sorted position of the token at list index li (-1: past the end)
   // (every load of the staging code is unconditional, with a clamped index: loads under a branch would make the
@@ -324,7 +357,7 @@ __global__ __launch_bounds__(64 * NW) void m_bwd_dkv(DkvArgs a) {
     for (int i = 0; i < NI; ++i) {
       const uint32_t off = (uint32_t)max(p.it[i], 0) * (uint32_t)(Hq * D) + (uint32_t)it_col[i];
       r.rq[i] = ld8(a.Qs + off);
-      r.rd[i] = ld8(a.dOs + off);
+      r.rd[i] = ld8(dOs + off);
     }
     r.sc = sc_src[(uint32_t)max(p.sc, 0) * Hq + sc_head];  // (threads past the scalars load one they never store)
     r.missing = sc_arr == 0 && p.sc < 0;  // a missing row gets lse = +inf: it contributes exp2(-inf) = 0
@@ -423,82 +456,92 @@ __global__ __launch_bounds__(64 * NW) void m_bwd_dkv(DkvArgs a) {
   }
   if (!wave_on) return;
   // --- store: lane holds dims acc_dim(dt, quad) + i of key column n
+  float *oK = MODE == DKV_SLC ? a.pK : win ? a.dKs : a.dKc, *oV = MODE == DKV_SLC ? a.pV : win ? a.dVs : a.dVc;
 #pragma unroll
   for (int kbk = 0; kbk < KB; ++kbk) {
     const int key = k0 + 16 * kbk + n;
     if (key >= kend) continue;
     size_t off = ((size_t)key * a.v.Hkv + g) * D;
-    if (MODE == DKV_CMP) off += (size_t)blockIdx.z * a.v.Nc * kstride;
-    if (MODE == DKV_SLC) off = (out_row0 + (size_t)(key - kbeg)) * D;  // partial sums: [row][D]
+    if (MODE == DKV_SLC) off = (out_row0 + (size_t)(key - kbeg)) * D;
+    else if (!win) off += (size_t)split * a.v.Nc * kstride;
 #pragma unroll
     for (int dt = 0; dt < D / 16; ++dt) {
-      *reinterpret_cast<float4 *>(a.dK + off + acc_dim(dt, quad)) =
-          make_float4(dk[kbk][dt][0] * scale, dk[kbk][dt][1] * scale, dk[kbk][dt][2] * scale, dk[kbk][dt][3] * scale);
-      *reinterpret_cast<float4 *>(a.dV + off + acc_dim(dt, quad)) =
-          make_float4(dv[kbk][dt][0], dv[kbk][dt][1], dv[kbk][dt][2], dv[kbk][dt][3]);
+      *reinterpret_cast<f32x4 *>(oK + off + acc_dim(dt, quad)) = dk[kbk][dt] * scale;
+      *reinterpret_cast<f32x4 *>(oV + off + acc_dim(dt, quad)) = dv[kbk][dt];
     }
   }
 }
 
-// Selection branch: add the per-chunk partial sums of every key, in chunk order, onto the token-level gradients
-// (which the window kernel wrote earlier on the same stream).  One thread per (sorted position, group, 4 dims).
-__global__ void m_slc_reduce(const int32_t *__restrict__ tok_slc, const int32_t *__restrict__ slc_start,
-                             const int32_t *__restrict__ chunk_start, const int32_t *__restrict__ part_row_start, int N,
-                             int Hkv, int Ns, int D, const float *__restrict__ pK, const float *__restrict__ pV,
-                             float *__restrict__ dKs, float *__restrict__ dVs) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int per_row = D / 4;
-  if (i >= (size_t)N * Hkv * per_row) return;
-  const int d4 = (int)(i % per_row), g = (int)(i / per_row % Hkv), pos = (int)(i / ((size_t)per_row * Hkv));
-  const int b = tok_slc[pos], key = g * Ns + b;
-  const int klen = slc_start[b + 1] - slc_start[b], nch = chunk_start[key + 1] - chunk_start[key];
-  const size_t row0 = (size_t)part_row_start[key] + (size_t)(pos - slc_start[b]);
-  float4 sk = make_float4(0.f, 0.f, 0.f, 0.f), sv = sk;
-  for (int c = 0; c < nch; ++c) {
-    const size_t off = (row0 + (size_t)c * klen) * D + 4 * d4;
-    const float4 ak = *reinterpret_cast<const float4 *>(pK + off), av = *reinterpret_cast<const float4 *>(pV + off);
-    sk.x += ak.x; sk.y += ak.y; sk.z += ak.z; sk.w += ak.w;
-    sv.x += av.x; sv.y += av.y; sv.z += av.z; sv.w += av.w;
-  }
-  const size_t dst = ((size_t)pos * Hkv + g) * D + 4 * d4;
-  float4 ck = *reinterpret_cast<float4 *>(dKs + dst), cv = *reinterpret_cast<float4 *>(dVs + dst);
-  ck.x += sk.x; ck.y += sk.y; ck.z += sk.z; ck.w += sk.w;
-  cv.x += sv.x; cv.y += sv.y; cv.z += sv.z; cv.w += sv.w;
-  *reinterpret_cast<float4 *>(dKs + dst) = ck;
-  *reinterpret_cast<float4 *>(dVs + dst) = cv;
-}
-
 // ---------------------------------------------------------------------------------------------------------
-// Finish: dK[tok] = dKs[pos] + (sum over query splits of dKc[c]) / count(c)  (gradient of the mean pool),
-// scattered back to caller order.  One workgroup per compression block.  With dKc_out/dVc_out given (the pooled
+// Finish: dK[tok] = dKs[pos] + (sum over the selection branch's chunks) + (sum over query splits of dKc[c]) / count(c)  (gradient of the
+// mean pool), scattered back to caller order.  One workgroup per compression block.  With dKc_out/dVc_out given (the pooled
 // rows were the caller's), the summed block gradients go there instead and dK, dV keep the token-level part only.
 // ---------------------------------------------------------------------------------------------------------
-__global__ void m_bwd_finish(const int32_t *__restrict__ perm, const int32_t *__restrict__ cmp_start, int Nc, int row,
-                             int splits, const float *__restrict__ dKs, const float *__restrict__ dVs,
-                             const float *__restrict__ dKc, const float *__restrict__ dVc, bf16_t *__restrict__ dK,
-                             bf16_t *__restrict__ dV, float *__restrict__ dKc_out, float *__restrict__ dVc_out) {
-  const int c = blockIdx.x;
-  const int b = cmp_start[c], e = cmp_start[c + 1];
+struct FinishArgs {
+  const int32_t *perm, *cmp_start, *cmp_slc, *slc_start, *chunk_start, *part_row_start;
+  int Nc, Ns, Hkv, D, splits;
+  const float *dKs, *dVs, *pK, *pV, *dKc, *dVc;
+  bf16_t *dK, *dV;
+  float *dKc_out, *dVc_out;
+};
+// Bound: latency of loads that depend on few others; a thread keeps 4 dims of a row and every 256/(row/4)-th part and token, whose loads
+// are in flight together.  (With a thread per dim, parts and tokens one after the other: 11k tokens 35 us for 17, 21k 48 for 29, 62k 75 for 56.)
+__global__ __launch_bounds__(256) void m_bwd_finish(FinishArgs a) {
+  __shared__ f32x4 part[2][256];
+  const int c = blockIdx.x, cols = a.Hkv * a.D / 4, row = 4 * cols;
+  const int b = a.cmp_start[c], e = a.cmp_start[c + 1], slc = a.cmp_slc[c];
+  const int per = min(cols, 256), groups = 256 / per, grp = threadIdx.x / per;  // (threads past the last group have nothing to do)
   const float inv = 1.0f / (float)(e - b);
-  for (int f = threadIdx.x; f < row; f += blockDim.x) {
-    float ck = 0.f, cv = 0.f;
-#pragma unroll 8  // (or the sum waits for one load after the other)
-    for (int s = 0; s < splits; ++s) {
-      ck += dKc[((size_t)s * Nc + c) * row + f];
-      cv += dVc[((size_t)s * Nc + c) * row + f];
+  for (int c0 = 0; c0 < cols; c0 += per) {
+    const int f = 4 * (c0 + (int)threadIdx.x % per);
+    const bool on = grp < groups && f < row;
+    f32x4 ck = {0.f, 0.f, 0.f, 0.f}, cv = ck;
+    if (on)
+#pragma unroll 8
+      for (int s = grp; s < a.splits; s += groups) {
+        const size_t at = ((size_t)s * a.Nc + c) * row + f;
+        ck += *reinterpret_cast<const f32x4 *>(a.dKc + at);
+        cv += *reinterpret_cast<const f32x4 *>(a.dVc + at);
+      }
+    part[0][threadIdx.x] = ck;
+    part[1][threadIdx.x] = cv;
+    __syncthreads();
+    if (on) {
+      ck = cv = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < groups; ++i) {
+        ck += part[0][i * per + threadIdx.x % per];
+        cv += part[1][i * per + threadIdx.x % per];
+      }
+      if (a.dKc_out) {
+        if (grp == 0) {
+          *reinterpret_cast<f32x4 *>(a.dKc_out + (size_t)c * row + f) = ck;
+          *reinterpret_cast<f32x4 *>(a.dVc_out + (size_t)c * row + f) = cv;
+        }
+        ck = cv = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      ck *= inv;
+      cv *= inv;
+      const int list = f / a.D * a.Ns + slc;
+      const bool chosen = a.chunk_start[list + 1] > a.chunk_start[list];
+      const size_t first = chosen ? ((size_t)a.part_row_start[list] + (size_t)(b - a.slc_start[slc])) * a.D + f % a.D : 0;  // position b's sums
+#pragma unroll 4
+      for (int pos = b + grp; pos < e; pos += groups) {
+        const size_t src = (size_t)pos * row + f, dst = (size_t)a.perm[pos] * row + f, at = first + (size_t)(pos - b) * a.D;
+        f32x4 k = *reinterpret_cast<const f32x4 *>(a.dKs + src), v = *reinterpret_cast<const f32x4 *>(a.dVs + src);
+        if (chosen) {
+          k += *reinterpret_cast<const f32x4 *>(a.pK + at);
+          v += *reinterpret_cast<const f32x4 *>(a.pV + at);
+        }
+        k += ck;
+        v += cv;
+        bf16x4 x, y;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { x[i] = (__bf16)k[i]; y[i] = (__bf16)v[i]; }
+        *reinterpret_cast<bf16x4 *>(a.dK + dst) = x;
+        *reinterpret_cast<bf16x4 *>(a.dV + dst) = y;
+      }
     }
-    if (dKc_out) {
-      dKc_out[(size_t)c * row + f] = ck;
-      dVc_out[(size_t)c * row + f] = cv;
-      ck = cv = 0.f;
-    }
-    ck *= inv;
-    cv *= inv;
-    for (int pos = b; pos < e; ++pos) {
-      const size_t dst = (size_t)perm[pos] * row + f;
-      dK[dst] = f32_to_bf16(dKs[(size_t)pos * row + f] + ck);
-      dV[dst] = f32_to_bf16(dVs[(size_t)pos * row + f] + cv);
-    }
+    __syncthreads();
   }
 }
 
@@ -550,52 +593,35 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     if (rc != SSA_OK) return rc;
   }
   constexpr int KB_KEYS = D >= 128 ? 1 : KB_KEYS_MAX;
-  constexpr int DKV_WAVES = DkvWaves<D>::N, DKV_WAVES_CMP = DkvWaves<D>::N;
-  constexpr int WG_KEYS = 16 * KB_KEYS * DKV_WAVES, WG_KEYS_CMP = 16 * KB_KEYS * DKV_WAVES_CMP;
-  static_assert(WG_KEYS <= SSA_KEY_PAD && WG_KEYS_CMP <= SSA_KEY_PAD, "key tiles may read up to WG_KEYS rows past a block");
+  constexpr int DKV_WAVES = DkvWaves<D>::N, WG_KEYS = 16 * KB_KEYS * DKV_WAVES;
+  static_assert(WG_KEYS <= SSA_KEY_PAD, "key tiles may read up to WG_KEYS rows past a block");
   constexpr int ST = DkvShape<D>::ST;
   const size_t dkv_lds = (size_t)2 * DkvStage<D, ST>::BYTES;
   static std::once_flag dkv_once;
   std::call_once(dkv_once, [] {
-    (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_WIN, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_CMP, DKV_WAVES_CMP, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute((const void *)m_bwd_dkv<D, KB_KEYS, DKV_CMP_WIN, DKV_WAVES, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   });
-  DkvArgs base{v, w.Qs, nullptr, nullptr, nullptr, w.sel.list, w.dKs, w.dVs, w.sel.chunk_start, w.sel.order, w.sel.part_row_start, 1, 1};
-  {
-    ProfScope ps(PROF_BWD_DKV_WIN, s);
-    DkvArgs a = base;
-    a.lse2s = w.lse2s + 2 * NH; a.deltas = w.deltag + 2 * NH; a.dOs = w.dOg + 2 * NH * D;
-    a.tiles_per_block = (blk->win_tok_max + WG_KEYS - 1) / WG_KEYS;
-    m_bwd_dkv<D, KB_KEYS, DKV_WIN, DKV_WAVES, ST><<<dim3(blk->Nw * a.tiles_per_block, Hkv), 64 * DKV_WAVES, dkv_lds, s>>>(a);
-  }
+  DkvArgs a{v, w.Qs, w.dOg, w.lse2s, w.deltag, w.sel.list, w.sel.chunk_start, w.sel.order, w.sel.part_row_start, blk->tok_slc, w.dKs, w.dVs,
+            w.pK, w.pV, w.dKc, w.dVc, (blk->slc_tok_max + WG_KEYS - 1) / WG_KEYS, (blk->win_tok_max + WG_KEYS - 1) / WG_KEYS,
+            (blk->c_max + WG_KEYS - 1) / WG_KEYS, 0, 0, w.q_splits};
   if (two_kernels) {
     ProfScope ps(PROF_BWD_DKV_SLC, s);
-    DkvArgs a = base;
-    a.lse2s = w.lse2s + NH; a.deltas = w.deltag + NH; a.dOs = w.dOg + NH * D;
-    a.dK = w.pK; a.dV = w.pV;
-    a.tiles_per_block = (blk->slc_tok_max + WG_KEYS - 1) / WG_KEYS;
-    m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST><<<dim3((w.max_chunks + 7) / 8 * 8 * a.tiles_per_block), 64 * DKV_WAVES, dkv_lds, s>>>(a);
+    m_bwd_dkv<D, KB_KEYS, DKV_SLC, DKV_WAVES, ST><<<dim3((w.max_chunks + 7) / 8 * 8 * a.slc_tiles), 64 * DKV_WAVES, dkv_lds, s>>>(a);
   }
   {
-    ProfScope ps(PROF_BWD_DKV_CMP, s);
-    DkvArgs a = base;
-    a.lse2s = w.lse2s; a.deltas = w.deltag; a.dOs = w.dOg;
-    a.dK = w.dKc; a.dV = w.dVc;
-    a.tiles_per_block = (blk->c_max + WG_KEYS_CMP - 1) / WG_KEYS_CMP;
-    a.q_splits = w.q_splits;
-    m_bwd_dkv<D, KB_KEYS, DKV_CMP, DKV_WAVES_CMP, ST><<<dim3(B * a.tiles_per_block, Hkv, w.q_splits), 64 * DKV_WAVES_CMP, dkv_lds, s>>>(a);
-  }
-  {
-    ProfScope ps(PROF_BWD_SLC_REDUCE, s);
-    const size_t items = (size_t)N * Hkv * (D / 4);
-    m_slc_reduce<<<(unsigned)((items + 255) / 256), 256, 0, s>>>(blk->tok_slc, v.slc_start, w.sel.chunk_start, w.sel.part_row_start, N,
-                                                                 Hkv, v.Ns, D, w.pK, w.pV, w.dKs, w.dVs);
+    ProfScope ps(PROF_BWD_DKV_CMP_WIN, s);
+    constexpr int NTHR = 64 * DKV_WAVES;
+    a.n_win = blk->Nw * a.win_tiles;
+    a.n_cmp = B * a.cmp_tiles * w.q_splits;
+    const unsigned n_sum = (unsigned)(((size_t)N * (D / 4) + NTHR - 1) / NTHR);
+    m_bwd_dkv<D, KB_KEYS, DKV_CMP_WIN, DKV_WAVES, ST><<<dim3(a.n_win + a.n_cmp + n_sum, Hkv), NTHR, dkv_lds, s>>>(a);
   }
   {
     ProfScope ps(PROF_BWD_FINISH, s);
-    m_bwd_finish<<<v.Nc, 128, 0, s>>>(v.perm, v.cmp_start, v.Nc, row, w.q_splits, w.dKs, w.dVs, w.dKc, w.dVc, (bf16_t *)dk,
-                                      (bf16_t *)dv, w.dKc_out, w.dVc_out);
+    const FinishArgs f{v.perm, v.cmp_start, v.cmp_slc, v.slc_start, w.sel.chunk_start, w.sel.part_row_start, v.Nc, v.Ns, Hkv, D, w.q_splits,
+                       w.dKs, w.dVs, w.pK, w.pV, w.dKc, w.dVc, (bf16_t *)dk, (bf16_t *)dv, w.dKc_out, w.dVc_out};
+    m_bwd_finish<<<v.Nc, 256, 0, s>>>(f);
   }
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }

@@ -9,9 +9,9 @@
 namespace {
 const char *const kNames[PROF_COUNT] = {
     "prep_sort_pool", "cmp_fwd_scores_topk", "slc_fwd", "win_fwd", "slc_merge_combine",
-    "bwd_prep", "bwd_pre_delta", "bwd_dq_cmp_win", "bwd_dq_slc", "bwd_invert_selection", "bwd_dkv_win", "bwd_dkv_slc", "bwd_dkv_cmp",
+    "bwd_prep", "bwd_pre_delta", "bwd_dq_cmp_win", "bwd_dq_slc", "bwd_invert_selection", "bwd_dkv_slc", "bwd_dkv_cmp_win",
     "bwd_finish_unpool", "generic_path", "cmp_module_fwd", "cmp_module_bwd", "gate_fwd", "gate_bwd",
-    "linear_fwd", "linear_bwd", "fwd_invert_selection", "bwd_dq_merge", "bwd_slc", "bwd_slc_reduce"};
+    "linear_fwd", "linear_bwd", "fwd_invert_selection", "bwd_dq_merge", "bwd_slc"};
 struct Rec { int id; hipEvent_t a, b; };
 bool g_on = false;
 std::vector<Rec> g_pending;
