@@ -17,6 +17,7 @@
 #include "mfma_launch.h"
 #include "mfma_qc.h"
 #include "profile.h"
+#include "sel_device.h"
 
 #include <mutex>
 
@@ -37,9 +38,10 @@ struct PreArgs {
   bf16_t *Qs, *dOg;             // sorted row-major copies: Q [N(pos)][Hq][D], gate_b * dO [3][N(pos)][Hq][D]
 };
 
-__global__ __launch_bounds__(256) void m_bwd_pre(PreArgs a) {
-  extern __shared__ bf16_t tile[];  // [Hq*D]: the token's dO rows
-  const int pos = blockIdx.x, tok = a.perm[pos];
+__global__ __launch_bounds__(256) void m_bwd_pre(PreArgs a, SelBeside sel) {
+  extern __shared__ __align__(16) bf16_t tile[];  // [Hq*D]: the token's dO rows
+  if ((int)blockIdx.x < sel.n) return sel_beside<256, true, false>(sel, blockIdx.x, tile);
+  const int pos = (int)blockIdx.x - sel.n, tok = a.perm[pos];
   const int HD = a.Hq * a.D;
   const size_t base = (size_t)tok * HD;
   bf16_t *td = tile;
@@ -139,13 +141,14 @@ __host__ __device__ inline size_t dq_lds_bytes() { return (size_t)4 * T32<D, tru
 // 62k tokens, 16 heads of 64: 1058 -> 932 us (two blocks of 16 columns per wavefront at two per SIMD before), 21k tokens in three
 // 64^3 shells 140 -> 111, sequences 748 -> 640, 153k tokens, heads of 128: 8.8 -> 6.8 ms.
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_bwd_dq(DqArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 64 ? 3 : 2))) void m_bwd_dq(DqArgs a, SelBeside sel) {
   extern __shared__ __align__(16) unsigned char smem[];
+  if ((int)blockIdx.x < sel.n) return sel_beside<64 * NW, false, true>(sel, blockIdx.x, smem);
   using T = T32<D, true>;
   unsigned char *stage0 = smem;
   const int h = threadIdx.x >> 5 & 1;
   const int N = a.v.N, TW = 32 * NW / a.v.hs;
-  const TileMap tm = xcd_tile_map((N + TW - 1) / TW, a.v.Hkv);
+  const TileMap tm = xcd_tile_map((N + TW - 1) / TW, a.v.Hkv, (int)blockIdx.x - sel.n);
   if (!tm.valid) return;
   const int g = tm.g, wg_pos0 = tm.tile * TW, wg_last = min(wg_pos0 + TW, N) - 1;
   const QCol q = query_col(a.v, wg_pos0, g);
@@ -560,36 +563,51 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   const int N = v.N, Hq = v.Hq, Hkv = v.Hkv, row = Hkv * D;
   const size_t NH = (size_t)N * Hq;
   const bool two_kernels = slc_bwd_two_kernels(blk, D, Hkv, v.T);  // selection branch
+  // the selection index, beside the pre-pass and the dQ kernel where it is small
+  const bool beside = sel_beside_fits(N, Hkv, v.T, v.Ns);
+  const SelJob j = sel_index_job(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, false, two_kernels, true, beside);
+  int rc = SSA_OK;
   {
     ProfScope ps(PROF_BWD_PRE, s);
     PreArgs a{(const bf16_t *)q, (const bf16_t *)dout, (const bf16_t *)out_branch, (const bf16_t *)gates, lse, v.perm,
               N, Hq, Hkv, v.hs, D, (bf16_t *)dgates, w.lse2s, w.deltas, w.gws, w.deltag, w.Qs, w.dOg};
-    m_bwd_pre<<<N, 256, (size_t)Hq * D * sizeof(bf16_t), s>>>(a);
+    const SelBeside sel = beside ? sel_pass(j, SelPass::count) : sel_alone();
+    const size_t lds = (size_t)Hq * D * sizeof(bf16_t), sel_lds = beside ? j.lds_bytes() : 0;
+    m_bwd_pre<<<sel.n + N, 256, sel_lds > lds ? sel_lds : lds, s>>>(a, sel);
+  }
+  if (!beside || !j.ticket) {
+    ProfScope ps(PROF_BWD_INVERT, s);
+    if (!beside) rc = sel_index_count(j, s);
+    if (rc == SSA_OK) rc = sel_index_scan(j, s);
+    if (rc == SSA_OK && !beside) rc = sel_index_fill(j, s);
+    if (rc != SSA_OK) return rc;
   }
   {
     ProfScope ps0(PROF_BWD_DQ_CMP, s);
     DqArgs a{v, (const bf16_t *)q, (const bf16_t *)dout, w.lse2s, w.deltas, w.gws, w.dQp};
     constexpr int NW0 = 4;
     const int tw0 = 32 * NW0 / v.hs;
-    m_bwd_dq<D, NW0><<<dim3(xcd_grid_size((N + tw0 - 1) / tw0, Hkv)), 64 * NW0, dq_lds_bytes<D>(), s>>>(a);
+    const SelBeside sel = beside ? sel_pass(j, SelPass::fill) : sel_alone();
+    const size_t lds = dq_lds_bytes<D>(), sel_lds = beside ? j.lds_bytes() : 0;
+    m_bwd_dq<D, NW0><<<dim3(sel.n + xcd_grid_size((N + tw0 - 1) / tw0, Hkv)), 64 * NW0, sel_lds > lds ? sel_lds : lds, s>>>(a, sel);
   }
-  {
+  if (!j.base) {
     ProfScope ps(PROF_BWD_INVERT, s);
-    const int rc = sel_index_build(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, false, two_kernels, true, s);
+    rc = sel_index_order(j, s);
     if (rc != SSA_OK) return rc;
   }
   if (!two_kernels) {
     ProfScope ps1(PROF_BWD_SLC, s);
-    const int rc = slc_bwd_kernel(v, D, w, blk->slc_tok_max, s);
+    rc = slc_bwd_kernel(v, D, w, blk->slc_tok_max, s);
     if (rc != SSA_OK) return rc;
   } else {
     ProfScope ps1(PROF_BWD_DQ, s);
-    const int rc = slc_dq_kernel(v, D, w, s);
+    rc = slc_dq_kernel(v, D, w, s);
     if (rc != SSA_OK) return rc;
   }
   {
     ProfScope ps2(PROF_BWD_DQ_MERGE, s);
-    const int rc = slc_dq_merge_kernel(v, D, w, idx, dq, s);
+    rc = slc_dq_merge_kernel(v, D, w, idx, dq, s);
     if (rc != SSA_OK) return rc;
   }
   constexpr int KB_KEYS = D >= 128 ? 1 : KB_KEYS_MAX;

@@ -132,8 +132,7 @@ __host__ __device__ inline int xcd_grid_size(int n_tiles, int Hkv) {
   const int parts = 8 / Hkv;
   return 8 * ((n_tiles + parts - 1) / parts);
 }
-__device__ inline TileMap xcd_tile_map(int n_tiles, int Hkv) {
-  const int L = blockIdx.x;
+__device__ inline TileMap xcd_tile_map(int n_tiles, int Hkv, int L = blockIdx.x) {  // L: number of the workgroup
   if (Hkv > 8 || 8 % Hkv != 0) return TileMap{L % n_tiles, L / n_tiles, L < n_tiles * Hkv};
   const int xcd = L & 7, idx = L >> 3, parts = 8 / Hkv;
   const int g = xcd % Hkv, part = xcd / Hkv;

@@ -23,6 +23,19 @@ def test_lists_at_tile_edges(seed, grid, n, hq, hkv, d, m, topk):
     full_parity(inputs.random_points_workload(seed, grid, n, hq, hkv, d, m, topk, "bf16"))
 
 
+@pytest.mark.parametrize("seed,lens,hq,hkv,d,l,topk", [
+    (331, (1020, 4), 2, 2, 32, (1, 2, 16), 16),          # 512 blocks: one part of blocks per workgroup, full rounds of entries
+    (332, (1022, 4), 2, 2, 64, (1, 2, 16), 16),          # 513 blocks: a second part of one
+    (333, (1023,), 4, 2, 128, (1, 2, 16), 5),            # two kernels' lists; a tile of 255 positions
+    (334, (24576,), 4, 4, 32, (16, 32, 64), 2),          # 768 blocks, two parts: 768 workgroups, launches of its own
+    (335, (24570,), 2, 2, 32, (32, 64, 64), 3),          # 384 blocks: 192 workgroups, sums by one kernel of their own
+])
+def test_lists_built_beside_the_backward_kernels(seed, lens, hq, hkv, d, l, topk):
+    """The backward's index (csrc/sel_device.h: 512 blocks and 16 entries a row, 384 workgroups in all)."""
+    wl = inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk)
+    full_parity(wl, queries=np.arange(0, wl.n_tokens, 97 if wl.n_tokens > 10000 else 1, dtype=np.int32))
+
+
 @pytest.mark.parametrize("seed,lens", [(311, (24576,)), (312, (9000, 15577))])
 def test_orders_of_the_work_chunks(seed, lens):
     wl = inputs.make_sequence_workload(seed, lens, hq=4, hkv=2, d=32, l=(32, 96, 64), topk=4)
