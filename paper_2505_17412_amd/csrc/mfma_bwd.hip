@@ -171,7 +171,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32
     const int r0 = uniform(of_tok[wg_pos0]), r1 = uniform(of_tok[wg_last]), own = of_tok[q.pos];
     const int rs = uniform(start[r0]), re = uniform(start[r1 + 1]), lo = start[own], hi = start[own + 1];
     const float lse2 = a.lse2s[branch * NH + row], gws = a.gws[branch * NH + row] * scale, dls = a.deltas[branch * NH + row] * scale;
-    t32_pipeline<D, 2, 64 * NW, 32>(T32Src<2>{{K, V}, kstride}, stage0, rs, re, [&](lds_cptr kt, int kb) {
+    t32_pipeline<D, 2, 64 * NW, 32, false>(T32Src<2>{{K, V}, kstride}, stage0, rs, re, [&](lds_cptr kt, int kb) {
       f32x16 s = t32_scores<D, true>(qop, kt, ln, splat16(0.f)), dp = splat16(0.f);
       if (r0 != r1 || kb + 32 > re) t32_only_keys(s, kb, lo, hi);
       dp = t32_scores<D, true>(dop, kt + T::BYTES, ln, dp);

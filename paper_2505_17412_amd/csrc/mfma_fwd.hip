@@ -44,7 +44,7 @@ __device__ inline bool fwd_walk(T32State<D, Sum> &st, float *refs, const bf16x8 
   using T = T32<D, true>;
   t32_clear(st);
   const int first = walk_begin(rs);
-  t32_pipeline<D, 2, 64 * NW, 32>(src, stage0, first, re, [&](lds_cptr kt, int kb) {
+  t32_pipeline<D, 2, 64 * NW, 32, std::is_same_v<Sum, SumInOrder>>(src, stage0, first, re, [&](lds_cptr kt, int kb) {
     f32x16 s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
     if (kb == first || kb + 32 > re) t32_only_keys(s, kb, rs, re);
     if (kb == first) {
@@ -64,7 +64,7 @@ template <int D, int NW, class Sum>
 __device__ inline void fwd_walk_general(T32State<D, Sum> &st, const bf16x8 (&qop)[D / 16], const T32Src<2> &src, unsigned char *stage0, int rs, int re,
                                         int lo, int hi, const typename T32<D, true>::Lanes &ln, float sl2) {
   t32_clear(st);
-  t32_pipeline<D, 2, 64 * NW, 32>(src, stage0, walk_begin(rs), re, [&](lds_cptr kt, int kb) {
+  t32_pipeline<D, 2, 64 * NW, 32, std::is_same_v<Sum, SumInOrder>>(src, stage0, walk_begin(rs), re, [&](lds_cptr kt, int kb) {
     f32x16 s = t32_scores<D, true>(qop, kt, ln, splat16(0.f));
     t32_only_keys(s, kb, lo, hi);
     t32_softmax_running<D, true>(st, s, kt + T32<D, true>::BYTES, ln, sl2);
@@ -264,9 +264,10 @@ __device__ inline void score_walk(const MfmaView &v, const bf16_t *Kg, uint32_t 
 // Bound: matrix and vector issue over both walks, at a clock that falls to 1.8 - 1.9 GHz under them: per 32 x 32 scores at head_dim
 // 64 the first walk takes 256 matrix cycles and about 280 of exponentials, multiply-adds, conversions and sums (a synthetic copy:
 // 226 ns per SIMD), the second 128 and about 250; the kernel takes about 1.45 times that.  32 query columns per wavefront against
-// 16: half the LDS operands per matrix cycle, half the staging and barriers per column.  Three wavefronts per SIMD (168 registers,
-// two more spilled, and LDS for three workgroups); two: 17 % slower.  At head_dim 128 two, with 30 spilled beside 256; in two kernels,
-// whose walk spills 6, 62k tokens and 662 blocks take 3400 us for 3130.  The sums of the first walk cost 5 % more in the order that keeps the selected
+// 16: half the LDS operands per matrix cycle, half the staging and barriers per column.  Three wavefronts per SIMD (157 registers
+// and LDS for three workgroups); two: 17 % slower.  At head_dim 128 two (233 registers); in two kernels
+// 62k tokens and 662 blocks took 3400 us for 3130.  With the accumulators moved about once in two tiles, and 2 and 30 registers
+// spilled (t32_pipeline), 62k tokens 1314 us for 1297 now, 153k, heads of 128, 8900 for 8640.  The sums of the first walk cost 5 % more in the order that keeps the selected
 // sets what they were (SumInOrder).  62k tokens, 2247 pooled keys, 16 heads of 64: 1497 -> 1278 us (16 columns before); 65k tokens
 // in three sequences 848 -> 767; 11k tokens 94 -> 79; 2k tokens, 32 heads of 32: 21 -> 16; 153k tokens, 3884 pooled keys, heads of
 // 128: 11.4 -> 8.7 ms.

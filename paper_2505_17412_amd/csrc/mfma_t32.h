@@ -367,7 +367,10 @@ struct T32Src {
 // be consecutive tiles of one, with STEP a multiple of 32) go global -> registers -> LDS once per workgroup, loads one step ahead (a
 // second register set costs more than it hides: spills), two LDS stages and one barrier per step.  tile(first tile of the stage, first
 // row) consumes a stage.  Rows past re are read as they lie in memory (padded arrays) and are the consumer's to mask.
-template <int D, int NROW, int NTHR, int STEP, class Tile>
+// PAIRS: the loop takes two steps at a time and the last of an odd number stands behind it, instead of a way out between the two: the accumulators
+// of a softmax then stay in their registers (32 register moves per two tiles otherwise, and more spilled).  The dQ kernel keeps them either way,
+// and has no register for the third copy of its tile.
+template <int D, int NROW, int NTHR, int STEP, bool PAIRS = true, class Tile>
 __device__ inline void t32_pipeline(const T32Src<NROW> &src, unsigned char *stage0, int rs, int re, Tile tile) {
   using T = T32<D, true>;
   constexpr int NI = (T::ITEMS + NTHR - 1) / NTHR;
@@ -395,11 +398,13 @@ __device__ inline void t32_pipeline(const T32Src<NROW> &src, unsigned char *stag
     tile((lds_cptr)st, kb);
   };
   if (rs < re) load(rs);
-  for (int kb = rs; kb < re; kb += 2 * STEP) {
+  int kb = rs;
+  for (; PAIRS ? kb + STEP < re : kb < re; kb += 2 * STEP) {
     step(0, kb);
-    if (kb + STEP >= re) break;
+    if (!PAIRS && kb + STEP >= re) break;
     step(1, kb + STEP);
   }
+  if (PAIRS && kb < re) step(0, kb);
   __syncthreads();
 }
 
