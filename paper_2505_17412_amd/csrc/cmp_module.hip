@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void c_conv(Pair<ConvSrc> srcs, const int32_t 
 // 10.7 k 121, 17 k 137, 30 k 162, 60 k 322.  Eight wavefronts that share 128 tokens by halves fetch the weights twice: 140 at
 // 10.7 k, 480 at 60 k.
 template <bool MIRROR, int TOK>
-__global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32_t *__restrict__ nbr, int N) {
+__global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32_t *__restrict__ nbr, int N, size_t part_stride) {
   constexpr int C = 128, MT = TOK / 16, AI = TOK / 16;  // AI: gathered 16-byte items per thread (TOK x 16 / 256)
   using G = TileGeom<C>;
   const ConvSrc cs = srcs.v[blockIdx.z];
@@ -205,7 +205,16 @@ __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32
     if (v >= 0) any_flag[MIRROR ? 26 - o : o] = 1;
   }
   __syncthreads();
-  const uint32_t used = (uint32_t)__ballot(lane < 27 && any_flag[lane < 27 ? lane : 0] != 0);
+  uint32_t used = (uint32_t)__ballot(lane < 27 && any_flag[lane < 27 ? lane : 0] != 0);
+  if (gridDim.y > 1) {  // this workgroup's share of them
+    const int total = __popc(used), first = total * (int)blockIdx.y / (int)gridDim.y, end = total * (int)(blockIdx.y + 1) / (int)gridDim.y;
+    uint32_t later = used;
+    for (int i = 0; i < end; ++i) {
+      if (i < first) used &= used - 1u;
+      later &= later - 1u;
+    }
+    used ^= later;
+  }
   f32x4 acc[MT][2];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) acc[mt][0] = acc[mt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -281,38 +290,46 @@ __global__ __launch_bounds__(256) void c_conv128(Pair<ConvSrc> srcs, const int32
       if (o >= 27) break;
     }
   }
+  float *out = cs.out + blockIdx.y * part_stride;
   // lane: column n of half a -> channel 32*wid + 8*(n >> 2) + 4*a + (n & 3); rows 4*quad + i of tile mt -> token
   // pos0 + 32*(mt >> 1) + 8*quad + 4*(mt & 1) + i
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
     const int ch = wrow + 4 * a;
-    const float bs = cs.bias ? bf16_to_f32(cs.bias[ch]) : 0.f;
+    const float bs = cs.bias && blockIdx.y == 0 ? bf16_to_f32(cs.bias[ch]) : 0.f;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int t = pos0 + 32 * (mt >> 1) + 8 * quad + 4 * (mt & 1) + i;
-        if (t < N) cs.out[(size_t)t * C + ch] = acc[mt][a][i] + bs;
+        if (t < N) out[(size_t)t * C + ch] = acc[mt][a][i] + bs;
       }
   }
 }
 
 // Mean over the tokens of each compression block (contiguous in sorted order); one workgroup per block.
-__global__ void c_pool(Pair<const float *> Ys, const int32_t *__restrict__ cmp_start, int C, Pair<bf16_t *> xcs) {
+// A token's row is the sum of P rows part_stride apart, in order.
+template <int P>
+__global__ void c_pool(Pair<const float *> Ys, size_t part_stride, const int32_t *__restrict__ cmp_start, int C, Pair<bf16_t *> xcs) {
   const float *__restrict__ Y = Ys.v[blockIdx.z];
   const int c = blockIdx.x, b = cmp_start[c], e = cmp_start[c + 1];
   const float inv = 1.0f / (float)(e - b);  // same arithmetic as the plain mean pool of the attention path
   for (int f = threadIdx.x; f < C; f += blockDim.x) {
     float s = 0.f;
-    int pos = b;
-    for (; pos + 8 <= e; pos += 8) {  // eight rows in flight; the order of the additions stays
-      float v[8];
+    for (int pos = b; pos < e; pos += 8) {  // eight tokens in flight, those past the end again the last; the order of the additions stays
+      float v[P][8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = Y[(size_t)(pos + u) * C + f];
+      for (int p = 0; p < P; ++p)
 #pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
+        for (int u = 0; u < 8; ++u) v[p][u] = Y[p * part_stride + (size_t)min(pos + u, e - 1) * C + f];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        float x = v[0][u];
+#pragma unroll
+        for (int p = 1; p < P; ++p) x += v[p][u];
+        if (pos + u < e) s += x;
+      }
     }
-    for (; pos < e; ++pos) s += Y[(size_t)pos * C + f];
     xcs.v[blockIdx.z][(size_t)c * C + f] = f32_to_bf16(s * inv);
   }
 }
@@ -350,8 +367,8 @@ __global__ void c_dbias_partial(Pair<const float *> dxcs, int Nc, int C, Pair<fl
 }
 
 // dx[perm[pos]] += dU[pos]   (caller order, parameter dtype)
-__global__ void c_dx_accum(Pair<const float *> dUs, const int32_t *__restrict__ perm, int N, int C, Pair<bf16_t *> dxs) {
-  const float *__restrict__ dU = dUs.v[blockIdx.z];
+__global__ void c_dx_accum(Pair<float *> dUs, int parts, size_t part_stride, const int32_t *__restrict__ perm, int N, int C, Pair<bf16_t *> dxs) {
+  float *__restrict__ dU = dUs.v[blockIdx.z];
   bf16_t *dx = dxs.v[blockIdx.z];
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int per = C / 8;
@@ -359,9 +376,19 @@ __global__ void c_dx_accum(Pair<const float *> dUs, const int32_t *__restrict__ 
   const int pos = (int)(i / per), c0 = (int)(i % per) * 8;
   bf16_t *d = dx + (size_t)perm[pos] * C + c0;
   const bf16x8 cur = ld8(d);
+  float *row = dU + (size_t)pos * C + c0, v[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = row[j];
+  if (parts > 1) {  // the rows of the parts, in order, and their sum for what reads it next
+    for (int p = 1; p < parts; ++p)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] += row[p * part_stride + j];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) row[j] = v[j];
+  }
   bf16x8 r;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) r[j] = (__bf16)((float)cur[j] + dU[(size_t)pos * C + c0 + j]);
+  for (int j = 0; j < 8; ++j) r[j] = (__bf16)((float)cur[j] + v[j]);
   *reinterpret_cast<bf16x8 *>(d) = r;
 }
 
@@ -521,6 +548,22 @@ __global__ __launch_bounds__(256) void c_dw(Pair<const bf16_t *> Us, Pair<const 
 
 constexpr int PE_GROUPS = 32;  // first-level groups of the ordered dPE sum
 
+// The convolution of n tensors of 128 channels: tokens per workgroup, and parts that a tile's offsets are dealt out to, a workgroup
+// each; the kernel that reads the result adds them.  128 tokens per workgroup read the weights half as often, 64 fill the chip
+// while 256 workgroups of 64 do not (keys and values, 64 against 128 tokens: 123 and 123 us at 10.7 k, 162 and 136 at 17 k).  A
+// tile's offsets are a serial chain and a compute unit holds two workgroups, so parts are taken while all of them run at once:
+// the module of keys and values, one -> three parts, forward and backward: 1 k tokens 110 and 106 -> 79 and 92 us, 3 k 112 and 111 ->
+// 102 and 106, 10.7 k (tiles of 128) 180 and 163 -> 143 and 149; two parts at 14 k 187 and 172 -> 156 and 163.  Two parts of 64
+// tokens save less of the short chain than the second set of rows costs: 5.5 k 121 and 119 -> 126 and 124, 8 k 127 and 126 -> 133 and 133.
+struct ConvShape { int tok, parts; };
+ConvShape conv_shape(int N, int C, int n) {
+  if (C != 128) return {0, 1};
+  const int tok = (long long)N * n > 16384 ? 128 : 64;
+  const long long wgs = (long long)((N + tok - 1) / tok) * n;
+  const int parts = 3 * wgs <= 512 ? 3 : 2 * wgs <= 512 && tok == 128 ? 2 : 1;
+  return {tok, parts};
+}
+
 // Workspace of a pass over n tensors; per-tensor arrays lie one after the other.  The inputs (neighbour table and U) have a
 // region of their own: a backward pass that follows a recomputed forward pass finds them there.
 struct ModPlan {
@@ -544,10 +587,10 @@ ModPlan mod_plan(int N, int C, int m, int n, bool backward) {
   off = 0;
   if (!backward) {
     p.wt = take(n * p.wlen * 2);
-    p.y = take(n * p.rows32);
+    p.y = take(n * p.rows32 * conv_shape(N, C, n).parts);
   } else {
     p.dy = take(n * p.rows16);
-    p.du = take(n * p.rows32);
+    p.du = take(n * p.rows32 * conv_shape(N, C, n).parts);
     // a chunk is a workgroup per offset: 1024 tokens of a small problem fill the chip, 32 chunks bound the partial sums
     p.dw_chunks = N > 0 ? (N + 1023) / 1024 : 1;
     if (p.dw_chunks > 32) p.dw_chunks = 32;
@@ -580,18 +623,15 @@ int check(const ssa_params_t *p, const ssa_blocks_t *b, int *C) {
 }
 
 template <bool MIRROR>
-void launch_conv(int C, const Pair<ConvSrc> &src, int n, const int32_t *nbr, int N, hipStream_t s) {
+void launch_conv(int C, const Pair<ConvSrc> &src, int n, const int32_t *nbr, int N, ConvShape shape, size_t part_stride, hipStream_t s) {
   // 64 tokens per wavefront and up to 128 output channels per workgroup row (blockIdx.y picks the channel range)
   const dim3 grid((unsigned)((N + 255) / 256), (unsigned)(C > 128 ? C / 128 : 1), n);
   switch (C) {
     case 32: c_conv<32, MIRROR, 4, 2><<<grid, 256, 0, s>>>(src, nbr, N); break;
     case 64: c_conv<64, MIRROR, 4, 4><<<grid, 256, 0, s>>>(src, nbr, N); break;
     case 128:
-      // 128 tokens per workgroup read the weights half as often, 64 fill the chip while 256 workgroups of 64 do not (keys and
-      // values, 64 against 128 tokens: 123 and 123 us at 10.7 k, 162 and 136 at 17 k; before rows were two offsets ahead 71 and
-      // 86 for the module at 8 k)
-      if ((size_t)N * n > 16384) c_conv128<MIRROR, 128><<<dim3((unsigned)((N + 127) / 128), 1, n), 256, 0, s>>>(src, nbr, N);
-      else c_conv128<MIRROR, 64><<<dim3((unsigned)((N + 63) / 64), 1, n), 256, 0, s>>>(src, nbr, N);
+      if (shape.tok == 128) c_conv128<MIRROR, 128><<<dim3((unsigned)((N + 127) / 128), shape.parts, n), 256, 0, s>>>(src, nbr, N, part_stride);
+      else c_conv128<MIRROR, 64><<<dim3((unsigned)((N + 63) / 64), shape.parts, n), 256, 0, s>>>(src, nbr, N, part_stride);
       break;
     default: c_conv<256, MIRROR, 4, 8><<<grid, 256, 0, s>>>(src, nbr, N); break;
   }
@@ -642,8 +682,13 @@ int cmp_module_forward(const ssa_params_t *p, const ssa_blocks_t *b, int n, cons
   c_transpose_w<<<dim3((unsigned)((pl.wlen + 255) / 256), 1, n), 256, 0, s>>>(w, C, Wt);
   Pair<ConvSrc> src{};
   for (int i = 0; i < n; ++i) src.v[i] = ConvSrc{U.v[i], Wt.v[i], (const bf16_t *)t[i].w->bias, Y.v[i]};
-  launch_conv<false>(C, src, n, (const int32_t *)(in + pl.nbr), N, s);
-  c_pool<<<dim3(b->Nc, 1, n), 128, 0, s>>>(as_const(Y), b->cmp_start, C, Pair<bf16_t *>{{(bf16_t *)t[0].xc, (bf16_t *)t[n - 1].xc}});
+  const ConvShape shape = conv_shape(N, C, n);
+  const size_t part_stride = n * pl.rows32 / 4;
+  launch_conv<false>(C, src, n, (const int32_t *)(in + pl.nbr), N, shape, part_stride, s);
+  auto pool = [&](auto kernel) {
+    kernel<<<dim3(b->Nc, 1, n), 128, 0, s>>>(as_const(Y), part_stride, b->cmp_start, C, Pair<bf16_t *>{{(bf16_t *)t[0].xc, (bf16_t *)t[n - 1].xc}});
+  };
+  shape.parts == 1 ? pool(c_pool<1>) : shape.parts == 2 ? pool(c_pool<2>) : pool(c_pool<3>);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
@@ -669,8 +714,10 @@ int cmp_module_backward(const ssa_params_t *p, const ssa_blocks_t *b, int n, con
   // data gradient: dU[pos] = sum_o dY[token that took pos as neighbour o] * w[o]^T; w as given has c_out contiguous
   Pair<ConvSrc> src{};
   for (int i = 0; i < n; ++i) src.v[i] = ConvSrc{dY.v[i], (const bf16_t *)t[i].w->w, nullptr, dU.v[i]};
-  launch_conv<true>(C, src, n, nbr, N, s);
-  c_dx_accum<<<igrid, 256, 0, s>>>(as_const(dU), b->perm, N, C, Pair<bf16_t *>{{(bf16_t *)t[0].dx, (bf16_t *)t[n - 1].dx}});
+  const ConvShape shape = conv_shape(N, C, n);
+  const size_t part_stride = n * pl.rows32 / 4;
+  launch_conv<true>(C, src, n, nbr, N, shape, part_stride, s);
+  c_dx_accum<<<igrid, 256, 0, s>>>(dU, shape.parts, part_stride, b->perm, N, C, Pair<bf16_t *>{{(bf16_t *)t[0].dx, (bf16_t *)t[n - 1].dx}});
   const unsigned pgrid = (unsigned)((pl.plen + 255) / 256);
   c_dpe_partial<<<dim3(pl.pe_chunks, 1, n), 128, pl.plen * 4, s>>>(as_const(dU), b->sorted_keys, N, C, b->bits, m, pl.pe_chunk, ppe);
   c_sum_parts<<<dim3(pgrid, PE_GROUPS, n), 256, 0, s>>>(as_const(ppe), pl.pe_chunks, PE_GROUPS, pl.plen, ppe2);

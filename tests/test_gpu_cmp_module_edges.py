@@ -1,5 +1,7 @@
 """GPU: the learned compression module at the sizes where its kernels change shape: one tile of tokens less or more, the
-1024-token segments of the weight gradient, the line between 64 and 128 tokens per convolution workgroup (16384).
+1024-token segments of the weight gradient, the line between 64 and 128 tokens per convolution workgroup (16384), and the parts
+that a tile's offsets are dealt out to (one tensor: three up to 170 tiles of 64 tokens, one up to 16384 tokens, then of 128 three up to 170
+tiles, two up to 256).
 Against the fp64 oracle, tolerances as in test_gpu_cmp_module.py."""
 import numpy as np
 import pytest
@@ -14,6 +16,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("seed,n,hkv,d", [
     (61, (63,), 2, 64), (62, (65,), 2, 64), (63, (1024,), 2, 64), (64, (1, 1024), 2, 64), (65, (1100, 950), 1, 32),
     (66, (16384,), 2, 64), (67, (9000, 7401), 2, 64),
+    (68, (1,), 2, 64), (69, (1, 1, 1), 2, 64), (70, (170 * 64,), 2, 64), (71, (170 * 64 + 1,), 2, 64), (72, (170 * 128 + 1,), 2, 64),
 ])
 def test_module_edges(seed, n, hkv, d):
     m = (4, 8, 8)
