@@ -41,14 +41,18 @@ constexpr size_t LDS_CU = 160 * 1024, LDS_GRANULE = 1280;  // of a compute unit;
 // 1420 (1297), 131k 27000 (7370), 160k 40400 (10800); heads of 128, 60k 2480 (2257), 131k 31300 (13300); 4 heads, 60k 2120 (1670); ungrouped 20k
 // 718 (488).  Under some 3k tokens it was faster by up to 4 us (2k tokens 17.2, now 18.3: there is one wavefront per SIMD, and it has
 // twice the columns), which fewer launches around it make up for.
+constexpr int cmp_wavefronts(int D) { return D <= 64 ? 12 : 8; }
+inline int cmp_workgroups(size_t lds) { return (int)(LDS_CU / ((lds + LDS_GRANULE - 1) / LDS_GRANULE * LDS_GRANULE)); }
 enum class CmpForm { one_kernel, tiles_in_lds, own_tiles_4, own_tiles_8 };
 inline CmpForm cmp_form(int D, int hs, int s_max) {
-  const int by_registers = D <= 64 ? 12 : 8;
-  auto workgroups = [](size_t lds) { return (int)(LDS_CU / ((lds + LDS_GRANULE - 1) / LDS_GRANULE * LDS_GRANULE)); };
-  auto full = [&](size_t lds) { return workgroups(lds) * 4 >= by_registers; };  // (workgroups of four wavefronts)
+  auto full = [&](size_t lds) { return cmp_workgroups(lds) * 4 >= cmp_wavefronts(D); };  // (workgroups of four wavefronts)
   if ((hs >= 8 || (hs == 4 && s_max > 64)) && s_max <= CMP_ONE_BLOCKS && full(cmp_lds_bytes(D, 4, hs, s_max))) return CmpForm::one_kernel;
   if (hs >= 2 && full(scores_lds_bytes(D, hs, 2, 4, 2, s_max))) return CmpForm::tiles_in_lds;
-  return workgroups(scores_lds_bytes(D, hs, 1, 4, 0, s_max)) >= 3 ? CmpForm::own_tiles_4 : CmpForm::own_tiles_8;
+  return cmp_workgroups(scores_lds_bytes(D, hs, 1, 4, 0, s_max)) >= 3 ? CmpForm::own_tiles_4 : CmpForm::own_tiles_8;
+}
+// Whether m_cmp_fwd can count the selections of every one of n_blocks blocks beside its score rows, for nothing.
+inline bool cmp_counts(int D, int hs, int s_max, int n_blocks) {
+  return cmp_form(D, hs, s_max) == CmpForm::one_kernel && cmp_workgroups(cmp_lds_bytes(D, 4, hs, s_max) + (size_t)n_blocks * 4) * 4 >= cmp_wavefronts(D);
 }
 
 // Whether the score rows of an item's selection blocks fit the matrix-core forward: 64 query rows of them beside two stages of two key

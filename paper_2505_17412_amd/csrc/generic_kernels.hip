@@ -1098,7 +1098,7 @@ int backward_t(const ssa_ctx &c, const void *q, const void *k, const void *v, co
   g_sort_pool<T><<<c.blk->Nc, 256, 0, c.stream>>>((const T *)k, (const T *)v, bv, row, Ks, Vs, Kc, Vc, sel.ticket);
   DqArgs a{q, dout, out_branch, gates, bv, topk_idx, c.Hq, c.Hkv, c.hs, c.d, c.T, c.scale, sl2, Ks, Vs, Kc, Vc, lse, dq, dgates, info};
   g_bwd_dq<T, DT><<<grid, 64 * NW, union_lds_bytes(tpt, c.T), c.stream>>>(a);
-  const int rc = sel_index_build(topk_idx, c.blk->perm, c.blk->slc_start, c.N, c.Hkv, c.T, c.blk->Ns, sel, true, false, true, c.stream);
+  const int rc = sel_index_build(topk_idx, c.blk->perm, c.blk->slc_start, c.N, c.Hkv, c.T, c.blk->Ns, sel, true, false, true, false, c.stream);
   if (rc != SSA_OK) return rc;
   DkvArgs b{q, dout, bv, c.Hq, c.Hkv, c.hs, c.d, c.scale, sl2, Ks, Vs, Kc, Vc, info, sel.list, sel.chunk_start,
             sel.part_row_start, sel.order, (c.blk->slc_tok_max + 15) / 16, p.splits, 0, 0, 0, dKs, dVs, pK, pV, dKc, dVc};

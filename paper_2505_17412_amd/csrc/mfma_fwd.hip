@@ -29,6 +29,7 @@ struct FwdArgs {
   float *lse;    // [3,N,Hq]
   int32_t *idx;  // [N,Hkv,T]
   float *nlse;   // [N(pos)][Hq]: minus the compression branch's log-sum-exp in log2 units, from m_cmp_walk to m_cmp_scores
+  uint32_t *cnt; // [tiles of sorted positions][Hkv*Ns]: m_cmp_fwd adds how many of the tile's tokens selected a block; null: not wanted
 };
 
 // Walks start at a multiple of 8 (which keys are a column's first tile, and with it the reference exponent, is part of what the
@@ -112,17 +113,18 @@ __device__ inline float finish(const FwdArgs &a, const T32State<D, Sum> &st, con
 constexpr float SCORE_FIX = 134217728.0f;  // 2^27: a row's scores sum to h_s <= 16 < 2^5
 
 static_assert(T32<64, true>::BYTES == tile_bytes(64) && T32<128, true>::BYTES == tile_bytes(128), "the LDS plans count whole tiles");
-// Top-k of one token's score row Sr[0 .. nb) out of rows of s_max <= MOST; marks: scratch of the wavefront where rows are longer than that.
+// Top-k of one token's score row Sr[0 .. nb) out of rows of s_max <= MOST; marks: scratch of the wavefront where rows are longer than
+// TOPK_IN_REGISTERS; hist: as in topk_wave_bits, for rows up to CMP_ONE_BLOCKS.
 template <int MOST>
-__device__ inline void topk_slot(const uint32_t *Sr, int s_max, int nb, int T, int b0, int32_t *row, uint32_t *marks) {
-  if (s_max <= 64) topk_wave_bits<1>(Sr, nb, T, b0, row);
-  else if (s_max <= 128) topk_wave_bits<2>(Sr, nb, T, b0, row);
-  else if (s_max <= 256) topk_wave_bits<4>(Sr, nb, T, b0, row);
-  else if (s_max <= 512) topk_wave_bits<8>(Sr, nb, T, b0, row);
-  else if (MOST <= 1024 || s_max <= 1024) topk_wave_bits<16>(Sr, nb, T, b0, row);
+__device__ inline void topk_slot(const uint32_t *Sr, int s_max, int nb, int T, int b0, int32_t *row, uint32_t *marks, uint32_t *hist) {
+  if (s_max <= 64) topk_wave_bits<1>(Sr, nb, T, b0, row, hist);
+  else if (s_max <= 128) topk_wave_bits<2>(Sr, nb, T, b0, row, hist);
+  else if (s_max <= 256) topk_wave_bits<4>(Sr, nb, T, b0, row, hist);
+  else if (s_max <= 512) topk_wave_bits<8>(Sr, nb, T, b0, row, hist);
+  else if (MOST <= 1024 || s_max <= 1024) topk_wave_bits<16>(Sr, nb, T, b0, row, hist);
   else if constexpr (MOST > 1024) {
-    if (s_max <= 2048) topk_wave_bits<32>(Sr, nb, T, b0, row);
-    else if (s_max <= TOPK_IN_REGISTERS) topk_wave_bits<64>(Sr, nb, T, b0, row);
+    if (s_max <= 2048) topk_wave_bits<32>(Sr, nb, T, b0, row, hist);
+    else if (s_max <= TOPK_IN_REGISTERS) topk_wave_bits<64>(Sr, nb, T, b0, row, hist);
     else topk_wave_u32(Sr, nb, T, b0, row, marks);
   }
 }
@@ -299,7 +301,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
     tok_info[TW + t] = a.v.cmp_batch[item + 1];
     tok_info[2 * TW + t] = a.v.slc_batch[item];
   }
-  for (int i = threadIdx.x; i < TW * s_max; i += 64 * NW) S[i] = 0u;
+  uint32_t *hist = a.cnt ? S + (size_t)TW * s_max : nullptr;  // [Ns] tokens of the workgroup that selected a block
+  for (int i = threadIdx.x; i < TW * s_max + (hist ? a.v.Ns : 0); i += 64 * NW) S[i] = 0u;
   __syncthreads();
   const bf16_t *Kg = a.v.Kc + (size_t)g * D, *Vg = a.v.Vc + (size_t)g * D;
   const uint32_t stride = (uint32_t)(a.v.Hkv * D);
@@ -321,8 +324,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 64
     const int tok = a.v.perm[pos], it = a.v.tok_item[pos];
     const int b0 = a.v.slc_batch[it], nb = a.v.slc_batch[it + 1] - b0;
     int32_t *row = a.idx + ((size_t)tok * a.v.Hkv + g) * a.v.T;
-    topk_slot<CMP_ONE_BLOCKS>(S + (size_t)slot * s_max, s_max, nb, a.v.T, b0, row, nullptr);
+    topk_slot<CMP_ONE_BLOCKS>(S + (size_t)slot * s_max, s_max, nb, a.v.T, b0, row, nullptr, hist);
   }
+  if (!hist) return;
+  __syncthreads();
+  for (int i = threadIdx.x; i < a.v.Ns; i += 64 * NW)
+    if (hist[i]) atomicAdd(&a.cnt[((size_t)(wg_pos0 / POS_TILE) * a.v.Hkv + g) * a.v.Ns + i], hist[i]);
 }
 
 // Window branch: keys are the tokens of the query's own window.  16 columns per wavefront -> now: 62k tokens, 16 heads of 64: 145 -> 115
@@ -427,7 +434,7 @@ __global__ __launch_bounds__(64 * CW * KS) __attribute__((amdgpu_waves_per_eu(D 
     const int pos = wg_pos0 + slot, tok = a.v.perm[pos], it = a.v.tok_item[pos];
     const int b0 = a.v.slc_batch[it], nb = a.v.slc_batch[it + 1] - b0;
     topk_slot<INT_MAX>(S + (size_t)slot * s_max, s_max, nb, a.v.T, b0, a.idx + ((size_t)tok * a.v.Hkv + g) * a.v.T,
-                       S + (size_t)TW * s_max + (size_t)wid * ((s_max + 31) >> 5));
+                       S + (size_t)TW * s_max + (size_t)wid * ((s_max + 31) >> 5), nullptr);
   }
 }
 // (raises the dynamic LDS limit once per process for every instantiation)
@@ -472,7 +479,8 @@ void launch_cmp(const FwdArgs &a, hipStream_t s) {
       static std::once_flag once;
       allow_lds(once, m_cmp_fwd<D, HS, NW>);
       constexpr int TW = 32 * NW / HS;
-      m_cmp_fwd<D, HS, NW><<<dim3(xcd_grid_size((a.v.N + TW - 1) / TW, a.v.Hkv)), 64 * NW, cmp_lds_bytes(D, NW, HS, a.v.s_max), s>>>(a);
+      m_cmp_fwd<D, HS, NW><<<dim3(xcd_grid_size((a.v.N + TW - 1) / TW, a.v.Hkv)), 64 * NW,
+                                cmp_lds_bytes(D, NW, HS, a.v.s_max) + (a.cnt ? (size_t)a.v.Ns * 4 : 0), s>>>(a);
       return;
     }
   launch_walk<D, NW, true>(a, s);
@@ -497,7 +505,7 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, co
   }
   {
     ProfScope ps(PROF_FWD_INVERT, s);
-    const int rc = sel_index_build(a.idx, a.v.perm, a.v.slc_start, a.v.N, a.v.Hkv, a.v.T, a.v.Ns, sel, true, true, false, s);
+    const int rc = sel_index_build(a.idx, a.v.perm, a.v.slc_start, a.v.N, a.v.Hkv, a.v.T, a.v.Ns, sel, true, true, false, a.cnt != nullptr, s);
     if (rc != SSA_OK) return rc;
   }
   {
@@ -523,7 +531,8 @@ int launch_forward(FwdArgs a, const bf16_t *gates, bf16_t *out, SlcKeep keep, co
 int mfma_forward_kernels(const MfmaView &v, int D, const void *q, const void *gates, void *out, float *lse,
                          int32_t *idx, void *out_branch, SlcKeep keep, const SelIndex &sel, const SlcPartials &part,
                          hipStream_t s) {
-  FwdArgs a{v, (const bf16_t *)q, (bf16_t *)out_branch, lse, idx, part.ml};
+  const bool counts = sel_counted(D, v.hs, v.s_max, v.N, v.Hkv, v.Ns);
+  FwdArgs a{v, (const bf16_t *)q, (bf16_t *)out_branch, lse, idx, part.ml, counts ? sel.cnt : nullptr};
   switch (D) {
     case 32: return launch_forward<32>(a, (const bf16_t *)gates, (bf16_t *)out, keep, sel, part, s);
     case 64: return launch_forward<64>(a, (const bf16_t *)gates, (bf16_t *)out, keep, sel, part, s);

@@ -12,6 +12,7 @@ int mfma_forward_kernels(const MfmaView &v, int D, const void *q, const void *ga
 // Inverse of the selection (sel_index.hip): per (KV head, selection block) key = g*Ns + b, the ascending list of sorted
 // positions of the tokens that selected it, and the cuts of the lists into work chunks.
 struct ChunkRef { int32_t key, chunk, first, count; };  // a work chunk: its list (key), its number inside the list, its entries
+constexpr int POS_TILE = 256;     // sorted positions per tile (8 words of 32 bits per key)
 struct SelIndex {
   uint32_t *cnt;                  // [Hkv*Ns][tiles of sorted positions] entries of the key before the tile
   uint32_t *counts;               // [Hkv*Ns]
@@ -30,7 +31,11 @@ struct SelIndex {
 size_t sel_index_bytes(int N, int Hkv, int T, int Ns);
 SelIndex sel_index_carve(void *ws, int N, int Hkv, int T, int Ns, int chunk_len, int bc_chunk_len);
 int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_start, int N, int Hkv, int T, int Ns,
-                    const SelIndex &x, bool caller_indices, bool want_bc_order, bool want_dkv_order, hipStream_t s);
+                    const SelIndex &x, bool caller_indices, bool want_bc_order, bool want_dkv_order, bool counted, hipStream_t s);
+// Whether the forward's compression kernel counts the selections (x.cnt, 0 when it starts, as [tiles][keys]), so that the index is one launch
+// (counted; of which only what m_slc_fwd_bc reads is written); cnt_words: words of it to clear.
+bool sel_counted(int D, int hs, int s_max, int N, int Hkv, int Ns);
+inline size_t sel_cnt_words(int N, int Hkv, int Ns) { return ((size_t)N + POS_TILE - 1) / POS_TILE * Hkv * Ns; }
 
 // Block-centric selection kernels: query tokens per work chunk, and the per-(token, KV head, rank) partial results.
 constexpr int BC_CHUNK = 256, BC_CHUNK_MIN = 32, DKV_CHUNK_MIN = 128;

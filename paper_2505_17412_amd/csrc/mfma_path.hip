@@ -24,13 +24,14 @@ bool slc_bwd_two_kernels(const ssa_blocks *b, int D, int Hkv, int T) {
 namespace {
 
 struct Tail { bf16_t *p; size_t begin, end; };  // element range to clear
-struct Tails { Tail t[4]; uint32_t *ticket; };  // and the counter of the selection index's first pass
+struct Tails { Tail t[4]; uint32_t *ticket, *cnt; size_t n_cnt; };  // and the counter of the selection index's first pass, and its counts
 
 constexpr int TAIL_WGS = 8;  // workgroups per array
 
 // The zero rows behind the sorted and pooled arrays: the last 4 * TAIL_WGS workgroups of the preparation's launch.
 __device__ inline void zero_tail(const Tails &ts, int wg) {
   if (wg == 0 && threadIdx.x == 0) *ts.ticket = 0u;
+  for (size_t i = (size_t)wg * blockDim.x + threadIdx.x; i < ts.n_cnt; i += (size_t)4 * TAIL_WGS * blockDim.x) ts.cnt[i] = 0u;
   const Tail t = ts.t[wg / TAIL_WGS];
   for (size_t i = t.begin + (size_t)(wg % TAIL_WGS) * blockDim.x + threadIdx.x; i < t.end; i += (size_t)TAIL_WGS * blockDim.x) t.p[i] = 0;
 }
@@ -139,12 +140,12 @@ MfmaView make_view(const ssa_ctx &c) {
   return v;
 }
 
-int run_prep(const ssa_ctx &c, const void *k, const void *v, const PrepOut &o, uint32_t *ticket) {
+int run_prep(const ssa_ctx &c, const void *k, const void *v, const PrepOut &o, const SelIndex &sel, bool counted) {
   ProfScope ps(PROF_PREP, c.stream);
   const size_t row = (size_t)c.Hkv * c.d;
   const size_t nt = padded_rows(c.N) * row, nc = padded_rows(c.blk->Nc) * row;
   const size_t t0 = (size_t)c.N * row, c0 = (size_t)c.blk->Nc * row;
-  Tails ts{{{o.Ks, t0, nt}, {o.Vs, t0, nt}, {o.Kc, c0, nc}, {o.Vc, c0, nc}}, ticket};
+  Tails ts{{{o.Ks, t0, nt}, {o.Vs, t0, nt}, {o.Kc, c0, nc}, {o.Vc, c0, nc}}, sel.ticket, sel.cnt, counted ? sel_cnt_words(c.N, c.Hkv, c.blk->Ns) : 0};
   const unsigned grid = (unsigned)c.blk->Nc + 4 * TAIL_WGS;
   const int r8 = c.Hkv * c.d / 8;
   if ((c.Hkv * c.d) % 8 == 0 && r8 <= 64 && 128 % r8 == 0)
@@ -261,7 +262,7 @@ int mfma_backward(const ssa_ctx &c, const void *q, const void *k, const void *v,
   o.Kc = (bf16_t *)(ws + p.kc); o.Vc = (bf16_t *)(ws + p.vc);
   BwdBuffers w{};
   w.sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, p.chunk_len, bc_chunk_len(c.N, c.Hkv, c.T));
-  int rc = run_prep(c, k, v, o, w.sel.ticket);
+  int rc = run_prep(c, k, v, o, w.sel, false);
   if (rc != SSA_OK) return rc;
   MfmaView view = make_view(c);
   view.Ks = o.Ks; view.Vs = o.Vs; view.Kc = o.Kc; view.Vc = o.Vc;
@@ -286,7 +287,7 @@ int mfma_forward(const ssa_ctx &c, const void *q, const void *k, const void *v, 
   o.kc_in = (const bf16_t *)c.kc_in; o.vc_in = (const bf16_t *)c.vc_in;
   o.Ks = (bf16_t *)(ws + p.ks); o.Vs = (bf16_t *)(ws + p.vs); o.Kc = (bf16_t *)(ws + p.kc); o.Vc = (bf16_t *)(ws + p.vc);
   const SelIndex sel = sel_index_carve(ws + p.sel, c.N, c.Hkv, c.T, c.blk->Ns, 1024, bc_chunk_len(c.N, c.Hkv, c.T));
-  int rc = run_prep(c, k, v, o, sel.ticket);
+  int rc = run_prep(c, k, v, o, sel, sel_counted(c.d, c.hs, c.blk->s_max, c.N, c.Hkv, c.blk->Ns));
   if (rc != SSA_OK) return rc;
   MfmaView view = make_view(c);
   view.Ks = o.Ks; view.Vs = o.Vs; view.Kc = o.Kc; view.Vc = o.Vc;

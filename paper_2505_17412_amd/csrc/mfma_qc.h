@@ -158,9 +158,9 @@ __device__ inline uint32_t wave_max_dpp(uint32_t v) {
 // (up to R per lane, n <= 64*R).  The T-th largest value is found by building it bit by bit from the top: a
 // candidate threshold is kept when at least T entries reach it (one compare + ballot + population count per
 // register and bit), and the search ends at the bit where exactly T do.  Entries above the threshold are selected, entries equal to it in ascending index order until
-// T are reached.  Writes T ids (base + index) in ascending order, padded with -1.
+// T are reached.  Writes T ids (base + index) in ascending order, padded with -1, and counts them in hist[id] (LDS; null: not).
 template <int R>
-__device__ inline void topk_wave_bits(const uint32_t *S, int n, int T, int base, int32_t *out) {
+__device__ inline void topk_wave_bits(const uint32_t *S, int n, int T, int base, int32_t *out, uint32_t *hist) {
   const int lane = threadIdx.x & 63;
   const uint64_t lt = (1ull << lane) - 1ull;
   uint32_t val[R];  // score + 1 (so that every real entry is >= 1); 0 marks "no entry"
@@ -220,6 +220,7 @@ __device__ inline void topk_wave_bits(const uint32_t *S, int n, int T, int base,
     eq_before += __popcll(em);
     const uint64_t sm = __ballot(sel);
     if (sel) out[written + __popcll(sm & lt)] = base + r * 64 + lane;
+    if (sel && hist) atomicAdd(&hist[base + r * 64 + lane], 1u);
     written += __popcll(sm);
   }
   for (int w = written + lane; w < T; w += 64) out[w] = -1;

@@ -5,7 +5,6 @@
 #include "mfma_launch.h"
 #include "sel_order.h"
 
-constexpr int POS_TILE = 256;              // sorted positions per tile (8 words of 32 bits per key)
 constexpr int TILE_WORDS = POS_TILE / 32;
 constexpr int ORDER_STEP = 64;             // keys per class of block lengths
 
@@ -221,14 +220,20 @@ __device__ __forceinline__ void sel_count(const SelJob &j, const SelPlace &at, u
 }
 
 // Pass 4: every entry to its place: list[start of the key + entries of earlier tiles + entries of the key before it in
-// this tile].  R: rounds of 8 entries per thread (POS_TILE * T entries per tile).
-template <int NT, int R>
-__device__ __forceinline__ void sel_fill(const SelJob &j, const SelPlace &place, uint32_t *sel_bits) {
+// this tile].  R: rounds of 8 entries per thread (POS_TILE * T entries per tile).  keys(): where the lists lie, asked for when the entries
+// are requested.
+struct SelKeys {
+  const int32_t *start;           // [keys + 1]
+  const uint32_t *before;         // [keys][stride] entries of earlier tiles
+  int stride;
+  const int32_t *bc_base, *base;  // as in OrderArgs
+};
+template <int NT, int R, class Keys>
+__device__ __forceinline__ void sel_fill(const SelJob &j, const SelPlace &place, uint32_t *sel_bits, Keys keys) {
   const SelArgs &a = j.a;
   const SelOrder &ord = j.ord;
-  const int tile = place.tile, g = place.g, b0 = place.b0, nb = min(j.key_tile, a.Ns - b0), stride = j.stride;
-  const uint32_t *cnt = j.cnt;
-  const int32_t *start = j.sc.start, *slc_start = j.sc.slc_start;
+  const int tile = place.tile, g = place.g, b0 = place.b0, nb = min(j.key_tile, a.Ns - b0);
+  const int32_t *slc_start = j.sc.slc_start;
   for (int i = threadIdx.x; i < nb * TILE_WORDS; i += NT) sel_bits[i] = 0u;
   __syncthreads();
   const int p0 = tile * POS_TILE, npos = min(POS_TILE, a.N - p0);
@@ -236,6 +241,7 @@ __device__ __forceinline__ void sel_fill(const SelJob &j, const SelPlace &place,
   int b[8 * R];
 #pragma unroll
   for (int u = 0; u < 8 * R; ++u) b[u] = sel_block(a, p0, npos, g, u * NT + threadIdx.x);
+  const SelKeys k = keys();
 #pragma unroll
   for (int u = 0; u < 8 * R; ++u) {
     const int pl = (u * NT + (int)threadIdx.x) / a.T;
@@ -253,23 +259,25 @@ __device__ __forceinline__ void sel_fill(const SelJob &j, const SelPlace &place,
 #pragma unroll
     for (int x = 0; x < TILE_WORDS - 1; ++x) before += x < (pl >> 5) ? __popc(w[x]) : 0u;
     const int key = g * a.Ns + b[u];
-    const int r = (int)(cnt[(size_t)key * stride + tile] + before), at = start[key] + r;
+    const int r = (int)(k.before[(size_t)key * k.stride] + before), at = k.start[key] + r;
     j.list[at] = j.caller_indices ? a.perm[p0 + pl] : p0 + pl;
     j.rank[at] = (uint8_t)(e - pl * a.T);
-    auto first = [&](const OrderArgs &o) {
+    auto first = [&](const OrderArgs &o, const int32_t *base) {
       if (!o.order || r % o.chunk_len != 0) return;
       const int c = r / o.chunk_len;
-      if (o.base) o.order[o.base[key] + c] = ChunkRef{key, c, at, min(o.chunk_len, start[key + 1] - at)};
+      if (base) o.order[base[key] + c] = ChunkRef{key, c, at, min(o.chunk_len, k.start[key + 1] - at)};
       else {
         const int cls = ord.classes - 1 - min((slc_start[b[u] + 1] - slc_start[b[u]]) / ORDER_STEP, ord.classes - 1);
         const int bin = (cls * a.Hkv + g) * ord.per_head + (p0 + pl) / ord.bucket;
         o.slot[o.chunk_start[key] + c] = make_int4(bin, (int)atomicAdd(&o.bins[bin], 1u), key, c);
       }
     };
-    first(j.bc);
-    first(j.dkv);
+    first(j.bc, k.bc_base);
+    first(j.dkv, k.base);
   }
 }
+// After the three passes before it.
+__device__ inline SelKeys sel_scanned(const SelJob &j, const SelPlace &at) { return SelKeys{j.sc.start, j.cnt + at.tile, j.stride, j.bc.base, j.dkv.base}; }
 
 // Host side (sel_index.hip): what the passes take, and the passes one by one; `beside`: for sel_beside.
 SelJob sel_index_job(const int32_t *idx, const int32_t *perm, const int32_t *slc_start, int N, int Hkv, int T, int Ns, const SelIndex &x,
@@ -304,6 +312,6 @@ __device__ __forceinline__ void sel_beside(const SelBeside &b, int wg, void *lds
   if constexpr (COUNT)
     if (b.pass == SelPass::count) return sel_count<NT>(j, at, (uint32_t *)lds);
   if constexpr (FILL) {
-    sel_fill<NT, POS_TILE * SEL_BESIDE_T / 8 / NT>(j, at, (uint32_t *)lds);
+    sel_fill<NT, POS_TILE * SEL_BESIDE_T / 8 / NT>(j, at, (uint32_t *)lds, [&] { return sel_scanned(j, at); });
   }
 }

@@ -5,10 +5,12 @@
 // matrix in LDS (integer OR: order independent), so that the population count below a bit is the entry's rank inside its
 // tile; per-tile counts are turned into offsets, and every entry then writes itself to its final place.  Integer work
 // only, and the lists do not depend on scheduling.
-// Bound: latency of two to five small dependent launches (every pass reads or writes a few MB), so a tile is small enough that all
-// its loads are in flight at once, and in small problems the prefix sums are the work of whichever workgroup of the first pass ends last.
-// Kernel times: 11k tokens, top-8, 226 lists: 22 us in two launches (25 us in five); 2k tokens, 66 lists: 18 us (28); 62k tokens,
-// top-16, 994 lists: 60 us in five.
+// Bound: latency of one to five small dependent launches (every pass reads or writes a few MB), so a tile is small enough that all
+// its loads are in flight at once, and in small problems the prefix sums are the work of whichever workgroup of the first pass ends last, or
+// the counts come with the selection itself (sel_counted).
+// Kernel times: 11k tokens, top-8, 226 lists: 22 us in two launches (25 us in five), 12 in one; 2k tokens, 66 lists: 18 us (28), 10;
+// 62k tokens, top-16, 994 lists: 60 us in five.
+#include "cmp_form.h"
 #include "sel_device.h"
 
 #include <mutex>
@@ -26,7 +28,93 @@ __global__ __launch_bounds__(SEL_THREADS) void m_sel_count(SelJob j) {
 template <int R>
 __global__ __launch_bounds__(SEL_THREADS) void m_sel_fill(SelJob j) {
   extern __shared__ __align__(16) uint32_t sel_bits[];
-  sel_fill<SEL_THREADS, R>(j, SelPlace{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z * j.key_tile}, sel_bits);
+  const SelPlace at{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z * j.key_tile};
+  sel_fill<SEL_THREADS, R>(j, at, sel_bits, [&] { return sel_scanned(j, at); });
+}
+
+// Exclusive prefix over the workgroup's threads, and the sum; part: SEL_THREADS / 64 words of LDS of the call's own.
+__device__ inline uint32_t prefix_over_threads(uint32_t own, uint32_t *part, uint32_t *sum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t inc = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t o = __shfl_up(inc, off);
+    if (lane >= off) inc += o;
+  }
+  if (lane == 63) part[w] = inc;
+  __syncthreads();
+  uint32_t base = 0, all = 0;
+#pragma unroll
+  for (int ww = 0; ww < SEL_THREADS / 64; ++ww) {
+    base += ww < w ? part[ww] : 0u;
+    all += part[ww];
+  }
+  *sum = all;
+  return base + inc - own;
+}
+
+// The whole index in one launch, where the compression kernel has left the counts as [tile][key] (sel_counted): every workgroup forms
+// the prefix sums it needs, a thread per key, while its entries are on their way, and fills its tile.
+template <int R>
+__global__ __launch_bounds__(SEL_THREADS) void m_sel_fill_counted(SelJob j) {
+  extern __shared__ __align__(16) uint32_t sel_bits[];
+  constexpr int NW = SEL_THREADS / 64, STEPS = 64;
+  __shared__ uint32_t part[3][NW], steps[NW][STEPS], before[SEL_THREADS];
+  __shared__ int32_t start[SEL_THREADS + 1], base[SEL_THREADS];
+  const SelPlace at{(int)blockIdx.x, (int)blockIdx.y, 0};
+  sel_fill<SEL_THREADS, R>(j, at, sel_bits, [&] {
+    const int key = threadIdx.x, lane = key & 63, w = key >> 6, n = j.sc.n, own_key = min(key, n - 1), blk = own_key % j.a.Ns;
+    const int len = j.sc.slc_start[blk + 1] - j.sc.slc_start[blk];
+    uint32_t all = 0, earlier = 0;
+    for (int t0 = 0; t0 < j.tiles; t0 += 16) {  // (16 counts in flight, under no condition)
+      uint32_t v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = j.cnt[(size_t)min(t0 + u, j.tiles - 1) * n + own_key];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        all += t0 + u < j.tiles ? v[u] : 0u;
+        earlier += t0 + u < at.tile ? v[u] : 0u;
+      }
+    }
+    if (key >= n) all = 0u;
+    for (int i = lane; i < STEPS; i += 64) steps[w][i] = 0u;
+    uint32_t entries, chunks;
+    start[key] = (int32_t)prefix_over_threads(all, part[0], &entries);
+    before[key] = earlier;
+    if (key == n - 1) start[n] = (int32_t)entries;
+    // the places of the chunks by falling block length, as order_by_length has them, but the same in every workgroup: inside a step of
+    // 8 keys by key
+    const uint32_t c = (all + j.sc.bc_chunk_len - 1) / j.sc.bc_chunk_len;
+    const int step = STEPS - 1 - min(len / 8, STEPS - 1);
+    if (c) atomicAdd(&steps[w][step], c);
+    uint64_t same = ~0ull;  // lanes of this step
+#pragma unroll
+    for (int bit = 0; bit < 6; ++bit) {
+      const uint64_t m = __ballot(step >> bit & 1);
+      same &= step >> bit & 1 ? m : ~m;
+    }
+    same &= (1ull << lane) - 1ull;
+    uint32_t mine = 0;  // chunks of the keys before this one in the same step and wavefront
+    for (int bit = 0; __any(c >> bit); ++bit) mine += (uint32_t)__popcll(__ballot(c >> bit & 1u) & same) << bit;
+    __syncthreads();
+    uint32_t of_step = 0;  // (the first wavefront: a thread per step)
+    if (key < STEPS)
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww) of_step += steps[ww][key];
+    uint32_t run = prefix_over_threads(of_step, part[1], &chunks);
+    if (key < STEPS)
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww) {
+        const uint32_t x = steps[ww][key];
+        steps[ww][key] = run;
+        run += x;
+      }
+    __syncthreads();
+    base[key] = (int32_t)(steps[w][step] + mine);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && key == 0) j.sc.bc_chunk_start[n] = (int32_t)chunks;
+    __syncthreads();
+    return SelKeys{start, before, 1, base, nullptr};
+  });
 }
 
 // Pass 2: per key (one wavefront each) the exclusive prefix of its counts over the tiles, in place, and their sum.
@@ -196,9 +284,24 @@ int sel_index_order(const SelJob &j, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
+// A thread per list, and few enough counts that every workgroup reads all of them.  The compression kernel takes as long as before, 3 us more
+// at 11k tokens.  Whole forward, counted apart / by it: 2k tokens, 32 heads of 32 79.5 / 72.4 us, 11k, 16 heads of 64 294.8 / 286.4, a
+// layer of 5.5k 209.8 / 203.3.
+bool sel_counted(int D, int hs, int s_max, int N, int Hkv, int Ns) {
+  const long long keys = (long long)Hkv * Ns;
+  return keys <= SEL_THREADS && keys * pos_tiles(N) <= FUSED_COUNTS && sel_order(N, Hkv).by_length && cmp_counts(D, hs, s_max, Ns);
+}
+
 int sel_index_build(const int32_t *idx, const int32_t *perm, const int32_t *slc_start, int N, int Hkv, int T, int Ns,
-                    const SelIndex &x, bool caller_indices, bool want_bc_order, bool want_dkv_order, hipStream_t s) {
+                    const SelIndex &x, bool caller_indices, bool want_bc_order, bool want_dkv_order, bool counted, hipStream_t s) {
   const SelJob j = sel_index_job(idx, perm, slc_start, N, Hkv, T, Ns, x, caller_indices, want_bc_order, want_dkv_order, false);
+  if (counted) {
+    const dim3 n(j.tiles, Hkv);
+    if (T <= 16) m_sel_fill_counted<1><<<n, SEL_THREADS, j.lds_bytes(), s>>>(j);
+    else if (T <= 32) m_sel_fill_counted<2><<<n, SEL_THREADS, j.lds_bytes(), s>>>(j);
+    else m_sel_fill_counted<4><<<n, SEL_THREADS, j.lds_bytes(), s>>>(j);
+    return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
+  }
   int rc = sel_index_count(j, s);
   if (rc == SSA_OK) rc = sel_index_scan(j, s);
   if (rc == SSA_OK) rc = sel_index_fill(j, s);

@@ -36,6 +36,20 @@ def test_lists_built_beside_the_backward_kernels(seed, lens, hq, hkv, d, l, topk
     full_parity(wl, queries=np.arange(0, wl.n_tokens, 97 if wl.n_tokens > 10000 else 1, dtype=np.int32))
 
 
+@pytest.mark.parametrize("seed,lens,hq,hkv,d,l,topk", [
+    (341, (1024,), 8, 1, 32, (1, 2, 16), 16),            # 512 lists, a thread each, in full tiles
+    (342, (1026,), 8, 1, 32, (1, 2, 16), 16),            # 513: apart
+    (343, (500, 0, 13, 258), 32, 2, 32, (4, 8, 32), 8),  # items of few blocks, an empty one, workgroups over several; two heads
+    (344, (255,), 16, 2, 64, (2, 4, 16), 64),            # the longest rows, padded
+    (345, (8192,), 8, 1, 64, (8, 16, 64), 17),          # 16384 counts
+    (346, (8193,), 8, 1, 128, (8, 16, 64), 1),          # more: apart
+])
+def test_lists_counted_by_the_compression_kernel(seed, lens, hq, hkv, d, l, topk):
+    """The forward's index (csrc/sel_index.hip: 512 lists and 16384 counts of 256 positions)."""
+    wl = inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk)
+    full_parity(wl, queries=np.arange(0, wl.n_tokens, 97 if wl.n_tokens > 3000 else 1, dtype=np.int32))
+
+
 @pytest.mark.parametrize("seed,lens", [(311, (24576,)), (312, (9000, 15577))])
 def test_orders_of_the_work_chunks(seed, lens):
     wl = inputs.make_sequence_workload(seed, lens, hq=4, hkv=2, d=32, l=(32, 96, 64), topk=4)
