@@ -4,8 +4,8 @@
 // Reading: one linear layer d_model -> J = 3*H_q with bias; output [N][H_q][3] in the branch order (cmp, slc, win).
 // The layer is skinny (J <= 64 outputs), so every kernel here is bound by streaming x (or dx) once through HBM;
 // the contractions run on the matrix cores only to keep the vector ALU out of the way.
-//   forward   a wave owns 16 tokens: A = x rows straight from memory, B = W^T (contraction index contiguous, a
-//             small transposed copy), sigmoid in the epilogue;
+//   forward   a wave owns two tiles of 16 tokens: A = x rows straight from memory, B = the weights' rows through LDS, or W^T
+//             (contraction index contiguous, a small transposed copy), sigmoid in the epilogue;
 //   backward  dz = dgates * g * (1 - g) (bf16, padded to 64 columns);  dx += dz W^T with dims as MFMA rows, so a
 //             lane holds 4 consecutive dims of one token;  dW = x^T dz contracts over tokens: 32-token tiles of x and
 //             dz go through LDS row-major and both operands are transposing LDS reads;  db = column sums of dz
@@ -13,13 +13,12 @@
 // No floating point atomics: per-chunk partial sums are added in a fixed order.
 #include "mfma_common.h"
 #include "mfma_qc.h"
+#include "gate_device.h"
 #include "profile.h"
 
 #include <mutex>
 
 namespace {
-
-constexpr int JP = 64;  // padded gate count (columns of dz and of the padded weights)
 
 // Wt[j][k] = w[k][j] (j < J), zero rows up to 16*ceil(J/16);  Wp[k][j] = w[k][j], zero for J <= j < 64
 __global__ void g_prep_w(const bf16_t *__restrict__ w, int Dm, int J, int JR, bf16_t *__restrict__ wt, bf16_t *__restrict__ wp) {
@@ -35,27 +34,22 @@ __global__ void g_prep_w(const bf16_t *__restrict__ w, int Dm, int J, int JR, bf
 }
 
 // gates[tok][j] = sigmoid(sum_k x[tok][k] w[k][j] + b[j]); NB = blocks of 16 gate columns.  A wavefront owns two tiles of 16
-// tokens (every weight operand feeds two matrix instructions).  SPLIT: the four wavefronts of a workgroup take a quarter of the
-// contraction of the same 32 tokens each, added in order through LDS; else each has its own 32 tokens and the whole contraction.
+// tokens (every weight operand feeds two matrix instructions) and the whole contraction; g_fwd_split: see gate_split_tile.
 // Bound: the latency of the row loads, 1 KB each, eight of them and the weights in flight per wavefront (gate_split says where which).
-template <int NB, bool SPLIT>
-__global__ __launch_bounds__(256) void g_fwd(const bf16_t *__restrict__ x, const bf16_t *__restrict__ wt,
-                                             const bf16_t *__restrict__ bias, int N, int Dm, int J, bf16_t *__restrict__ gates) {
-  __shared__ f32x4 part[SPLIT ? 4 : 1][SPLIT ? 2 * NB : 1][64];
-  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
-  const int t0 = (SPLIT ? blockIdx.x : blockIdx.x * 4 + wid) * 32;
-  if (!SPLIT && t0 >= N) return;
+template <int NB>
+__global__ __launch_bounds__(256) void g_fwd(GateJob a, const bf16_t *__restrict__ wt) {
+  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4, Dm = a.Dm;
+  const int t0 = (blockIdx.x * 4 + wid) * 32;
+  if (t0 >= a.N) return;
   const bf16_t *xr[2];
 #pragma unroll
-  for (int a = 0; a < 2; ++a) xr[a] = x + (size_t)min(t0 + 16 * a + n, N - 1) * Dm + 8 * quad;  // rows past the end
-  f32x4 acc[2][NB];                                                                       // repeat the last token
+  for (int h = 0; h < 2; ++h) xr[h] = a.x + (size_t)min(t0 + 16 * h + n, a.N - 1) * Dm + 8 * quad;  // rows past the end
+  f32x4 acc[2][NB];                                                                         // repeat the last token
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[a][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int trips = Dm / 128;  // d_model is a multiple of 128: four contraction steps per trip
-  const int k_begin = SPLIT ? trips * wid / 4 : 0, k_end = SPLIT ? trips * (wid + 1) / 4 : trips;
-  for (int k4 = k_begin; k4 < k_end; ++k4) {
+    for (int nb = 0; nb < NB; ++nb) acc[h][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k4 = 0; k4 < Dm / 128; ++k4) {  // d_model is a multiple of 128: four contraction steps per trip
     bf16x8 av[2][4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -71,33 +65,15 @@ __global__ __launch_bounds__(256) void g_fwd(const bf16_t *__restrict__ x, const
         acc[1][nb] = mfma16(av[1][u], bv, acc[1][nb]);
       }
   }
-  // C layout: lane holds gate column 16*nb + n of tokens t0 + 16*a + 4*quad + i
-  auto store = [&](int a, int nb, const f32x4 &z) {
-    const int j = 16 * nb + n;
-    if (j >= J) return;
-    const float b = bf16_to_f32(bias[j]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int t = t0 + 16 * a + 4 * quad + i;
-      if (t < N) gates[(size_t)t * J + j] = f32_to_bf16(1.0f / (1.0f + __expf(-(z[i] + b))));
-    }
-  };
-  if constexpr (SPLIT) {
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) part[wid][a * NB + nb][lane] = acc[a][nb];
-    __syncthreads();
-    for (int it = wid; it < 2 * NB; it += 4) {  // the wavefronts take the tiles in turn
-      const f32x4 p0 = part[0][it][lane], p1 = part[1][it][lane], p2 = part[2][it][lane], p3 = part[3][it][lane];
-      store(it / NB, it % NB, ((p0 + p1) + p2) + p3);
-    }
-  } else {
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int a = 0; a < 2; ++a) store(a, nb, acc[a][nb]);
-  }
+    for (int h = 0; h < 2; ++h) gate_store(a, t0 + 16 * h, nb, acc[h][nb]);
+}
+template <int NB, bool WT>
+__global__ __launch_bounds__(256) void g_fwd_split(GateJob a, const bf16_t *__restrict__ wt) {
+  __shared__ __align__(16) unsigned char lds[gate_split_lds<NB, WT>()];
+  gate_split_tile<NB, WT>(a, wt, blockIdx.x, lds);
 }
 
 // dz[tok][j] = dgates * g * (1 - g) for j < J, zero up to column 63 (bf16)
@@ -291,7 +267,7 @@ extern "C" size_t ssa_gate_workspace_bytes(const ssa_params_t *p, int32_t d_mode
   return gate_plan(p->n_tokens, d_model, J, for_backward != 0).total + 256;
 }
 
-// Whether the four wavefronts of a workgroup split the contraction (g_fwd): where a wavefront per 32 tokens leaves the chip half empty, at
+// Whether, with a transposed copy of the weights, the four wavefronts of a workgroup split the contraction: where a wavefront per 32 tokens leaves the chip half empty, at
 // 49152 tokens and below.  Beyond, such wavefronts run in rounds of one per SIMD (32768 tokens), and a split, whose time grows with the
 // tokens alone, wins where the last round is not nearly full.  With up to 32 gate columns a split is never behind but for a d_model of
 // 128, a single trip, in the smallest.  Whole / split, us, 1024 features, 48 columns: 20k tokens 27 / 20, 49k 43 / 34, 62k (95 % of two
@@ -303,23 +279,37 @@ static bool gate_split(int N, int d_model, int NB) {
   return NB <= 2 || N <= 49152 || 100ll * N < 89 * full;
 }
 
-// Forward launches with the transposed weight copy in `wt` (device, ((J+15)/16*16) * d_model bf16).
+// Weights whose rows are whole 16-byte pieces (of the gate counts that are multiples of 3 up to 64: 24 and 48) are read as they are, by the
+// split form at every size; else a transposed copy comes first.  With a copy and as the rule above / as they are, us, 1024 features, 48
+// columns: 5.5k tokens 11.3 / 7.1, 20k 19.1 / 14.8, 46k 33.6 / 24.2; 24 columns 10.0 / 7.4, 15.5 / 10.0, 26.2 / 18.7; whole / split as they are
+// 62k 43.5 / 31.4, 150k 100 / 97, 250k 158 / 156.  In a layer they run beside the projections of the same rows (lin_nt): 5.5k tokens
+// 190.8 -> 185.7 us, a training step of 10.7k 1511 -> 1503, of 46k 7156 -> 7132.
+static bool gate_as_is(int J) { return J % 8 == 0; }
+
+// Forward launches with the transposed weight copy, where one is taken, in `wt` (device, ((J+15)/16*16) * d_model bf16).
 static int gate_forward_launch(int N, int d_model, int J, const void *x, const void *w, const void *bias, void *gates,
                                bf16_t *wt, hipStream_t s) {
   const int NB = (J + 15) / 16, JR = 16 * NB;
   ProfScope ps(PROF_GATE_FWD, s);
-  g_prep_w<<<(unsigned)(((size_t)JR * d_model + 255) / 256), 256, 0, s>>>((const bf16_t *)w, d_model, J, JR, wt, nullptr);
-  const auto run = [&](auto kernel, int tokens) {
-    kernel<<<(unsigned)((N + tokens - 1) / tokens), 256, 0, s>>>((const bf16_t *)x, wt, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates);
-  };
-  const bool split = gate_split(N, d_model, NB);
+  const GateJob a{(const bf16_t *)x, (const bf16_t *)w, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates, 0};
+  const bool as_is = gate_as_is(J), split = as_is || gate_split(N, d_model, NB);
+  if (!as_is) g_prep_w<<<(unsigned)(((size_t)JR * d_model + 255) / 256), 256, 0, s>>>(a.w, d_model, J, JR, wt, nullptr);
+  const auto run = [&](auto kernel, int tokens) { kernel<<<(unsigned)((N + tokens - 1) / tokens), 256, 0, s>>>(a, wt); };
   switch (NB) {
-    case 1: split ? run(g_fwd<1, true>, 32) : run(g_fwd<1, false>, 128); break;
-    case 2: split ? run(g_fwd<2, true>, 32) : run(g_fwd<2, false>, 128); break;
-    case 3: split ? run(g_fwd<3, true>, 32) : run(g_fwd<3, false>, 128); break;
-    default: split ? run(g_fwd<4, true>, 32) : run(g_fwd<4, false>, 128); break;
+    case 1: split ? run(g_fwd_split<1, true>, 32) : run(g_fwd<1>, 128); break;
+    case 2: as_is ? run(g_fwd_split<2, false>, 32) : split ? run(g_fwd_split<2, true>, 32) : run(g_fwd<2>, 128); break;
+    case 3: as_is ? run(g_fwd_split<3, false>, 32) : split ? run(g_fwd_split<3, true>, 32) : run(g_fwd<3>, 128); break;
+    default: split ? run(g_fwd_split<4, true>, 32) : run(g_fwd<4>, 128); break;
   }
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
+}
+
+bool gate_beside(const ssa_params_t *p, int d_model, const void *x, const void *w, const void *bias, void *gates, GateJob *out) {
+  int J;
+  if (gate_check(p, d_model, &J) != SSA_OK || !x || !w || !bias || !gates || !aligned16(x, w, bias, gates)) return false;
+  if (!gate_as_is(J)) return false;
+  *out = GateJob{(const bf16_t *)x, (const bf16_t *)w, (const bf16_t *)bias, p->n_tokens, d_model, J, (bf16_t *)gates, 0};
+  return true;
 }
 
 extern "C" int ssa_gate_forward(const ssa_params_t *p, int32_t d_model, const void *x, const void *w, const void *bias,

@@ -7,6 +7,7 @@
 #include "linear_internal.h"
 #include "profile.h"
 #include "cmp_internal.h"
+#include "gate_device.h"
 
 namespace {
 
@@ -152,8 +153,10 @@ extern "C" int ssa_layer_forward(const ssa_params_t *p, const ssa_blocks_t *b, i
   const void *const wx[3] = {w->wq, w->wk, w->wv}, *const bx[3] = {w->bq, w->bk, w->bv};
   void *const qkv[3] = {sv + s.q, sv + s.k, sv + s.v};
   const int c3[3] = {cq, ckv, ckv};
-  int rc = lin_forward_multi(3, N, d_model, x, wx, bx, c3, qkv, (hipStream_t)stream);
-  if (rc == SSA_OK) rc = ssa_gate_forward(p, d_model, x, w->wg, w->bg, sv + s.gates, scratch, pl.scratch_bytes, stream);
+  GateJob gate;
+  const bool beside = gate_beside(p, d_model, x, w->wg, w->bg, sv + s.gates, &gate);
+  int rc = lin_forward_multi(3, N, d_model, x, wx, bx, c3, qkv, beside ? &gate : nullptr, (hipStream_t)stream);
+  if (rc == SSA_OK && !beside) rc = ssa_gate_forward(p, d_model, x, w->wg, w->bg, sv + s.gates, scratch, pl.scratch_bytes, stream);
   if (rc == SSA_OK && mode == 1) {
     const ssa_cmp_weights_t ck{w->pe_k, w->wc_k, w->bc_k}, cv{w->pe_v, w->wc_v, w->bc_v};
     CmpTensor t[2]{};

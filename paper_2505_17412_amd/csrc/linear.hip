@@ -13,6 +13,7 @@
 //             fixed order.  db = column sums of dy in two steps (per 64-token chunk, then over the chunks), fixed order.
 // No floating point atomics anywhere.
 #include "mfma_common.h"
+#include "gate_device.h"
 #include "linear_internal.h"
 #include "mfma_qc.h"
 #include "profile.h"
@@ -44,13 +45,20 @@ struct LinDst {
 // ONE: one pair and one output, known to the compiler.  Which pair a chunk and which output a tile belongs to, and fields fetched by that,
 // cost every call of ssa_linear_forward: 62k tokens 2048 -> 128 57.2 us for 47.3, 150k 384 -> 1024 214 for 190, 2k 384 -> 2048 11.9 for 10.9.
 template <int WF, int WT, int CF, int CT, bool ONE>
-__global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, int M) {
+__global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, int M, GateJob gate) {
   using G = TileGeom<LIN_KC>;
   constexpr int BF = 16 * CF * WF, BT = 16 * CT * WT, NTHR = 64 * WF * WT;
   constexpr int STAGE_W = BF * LIN_KC, STAGE_X = BT * LIN_KC;  // elements per stage
   constexpr int IW = BF * 8 / NTHR, IX = BT * 8 / NTHR;         // 16-byte items per thread and chunk
   extern __shared__ __align__(16) unsigned char smem[];
   bf16_t *sw = (bf16_t *)smem, *sx = sw + 2 * STAGE_W;
+  if constexpr (!ONE) {
+    static_assert(gate_split_lds<3, false>() <= (size_t)2 * (STAGE_W + STAGE_X) * sizeof(bf16_t), "the gates' LDS");
+    if ((int)blockIdx.x >= gate.first) {
+      const int wg = (int)blockIdx.x - gate.first;
+      return gate.blocks() == 2 ? gate_split_tile<2, false>(gate, nullptr, wg, smem) : gate_split_tile<3, false>(gate, nullptr, wg, smem);
+    }
+  }
   const int n_ot = (ONE ? dst.O[0] : dst.O[0] + dst.O[1] + dst.O[2]) / BF, n_tt = (M + BT - 1) / BT;  // unused outputs have O = 0
   const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
   const int tt = (idx / n_ot) * 8 + xcd;
@@ -381,7 +389,7 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
 namespace {
 
 template <bool ONE>
-int launch_nt(const LinSrc &src, const LinDst &dst, int M, hipStream_t s) {
+int launch_nt(const LinSrc &src, const LinDst &dst, int M, GateJob gate, hipStream_t s) {
   constexpr int WF = 2, WT = 2, CF = 4, CT = 4, BF = 16 * CF * WF, BT = 16 * CT * WT;
   const size_t lds = (size_t)2 * (BF + BT) * LIN_KC * sizeof(bf16_t);  // two stages of weights and tokens
   static const hipError_t attr =
@@ -389,12 +397,13 @@ int launch_nt(const LinSrc &src, const LinDst &dst, int M, hipStream_t s) {
   if (attr != hipSuccess) return SSA_ERR_HIP;
   const int n_ot = (dst.O[0] + dst.O[1] + dst.O[2]) / BF, n_tt = (M + BT - 1) / BT;
   const unsigned grid = (unsigned)(8 * ((n_tt + 7) / 8) * n_ot);
-  lin_nt<WF, WT, CF, CT, ONE><<<grid, 64 * WF * WT, lds, s>>>(src, dst, M);
+  gate.first = (int)grid;
+  lin_nt<WF, WT, CF, CT, ONE><<<grid + (unsigned)((gate.N + 31) / 32), 64 * WF * WT, lds, s>>>(src, dst, M, gate);
   return SSA_OK;
 }
-int launch_nt(const LinSrc &src, const LinDst &dst, int M, hipStream_t s) {
-  const bool one = src.K[1] == 0 && dst.O[1] == 0;
-  return one ? launch_nt<true>(src, dst, M, s) : launch_nt<false>(src, dst, M, s);
+int launch_nt(const LinSrc &src, const LinDst &dst, int M, const GateJob *gate, hipStream_t s) {
+  const bool one = src.K[1] == 0 && dst.O[1] == 0 && !gate;
+  return one ? launch_nt<true>(src, dst, M, GateJob{}, s) : launch_nt<false>(src, dst, M, gate ? *gate : GateJob{}, s);
 }
 
 }  // namespace
@@ -411,11 +420,11 @@ int lin_nt_multi(int n_src, const void *const *X, const void *const *W, const in
   dst.bias[0] = (const bf16_t *)bias;
   dst.Y[0] = (bf16_t *)Y;
   dst.O[0] = O;
-  return launch_nt(src, dst, M, s);
+  return launch_nt(src, dst, M, nullptr, s);
 }
 
 int lin_forward_multi(int n_dst, int M, int K, const void *X, const void *const *W, const void *const *bias, const int *O,
-                      void *const *Y, hipStream_t s) {
+                      void *const *Y, const GateJob *gate, hipStream_t s) {
   for (int i = 0; i < n_dst; ++i) {
     const int rc = lin_check(M, K, O[i]);
     if (rc != SSA_OK) return rc;
@@ -434,7 +443,7 @@ int lin_forward_multi(int n_dst, int M, int K, const void *X, const void *const 
     dst.O[i] = O[i];
   }
   ProfScope ps(PROF_LINEAR_FWD, s);
-  const int rc = launch_nt(src, dst, M, s);
+  const int rc = launch_nt(src, dst, M, gate, s);
   if (rc != SSA_OK) return rc;
   SSA_HIP_TRY(hipGetLastError());
   return SSA_OK;
@@ -512,7 +521,7 @@ extern "C" size_t ssa_linear_workspace_bytes(int32_t n_tokens, int32_t d_in, int
 
 extern "C" int ssa_linear_forward(int32_t n_tokens, int32_t d_in, int32_t d_out, const void *x, const void *w,
                                   const void *bias, void *y, void *stream) {
-  return lin_forward_multi(1, n_tokens, d_in, x, &w, &bias, &d_out, &y, (hipStream_t)stream);
+  return lin_forward_multi(1, n_tokens, d_in, x, &w, &bias, &d_out, &y, nullptr, (hipStream_t)stream);
 }
 
 extern "C" int ssa_linear_backward(int32_t n_tokens, int32_t d_in, int32_t d_out, const void *x, const void *w,
