@@ -27,7 +27,7 @@ __device__ inline void gate_store(const GateJob &a, int t0, int nb, const f32x4 
   }
 }
 
-// Workgroup wg of the split form: 256 threads; each of the four wavefronts takes a quarter of the contraction of the same 32 tokens, added
+// Workgroup wg of the split form: 256 threads (or as many of a larger one, with LDS of their own); each of the four wavefronts takes a quarter of the contraction of the same 32 tokens, added
 // in order through LDS.  WT: wt holds the weights as [16*NB][Dm] (transposed), or they are read as they are, for J a multiple of 8: 32 rows
 // at a time go through the wavefront's own LDS and come back as transposed operands.
 template <int NB> constexpr size_t gate_part_bytes() { return (size_t)4 * 2 * NB * 64 * sizeof(f32x4); }
@@ -37,7 +37,7 @@ template <int NB, bool WT>
 __device__ __forceinline__ void gate_split_tile(const GateJob &a, const bf16_t *wt, int wg, unsigned char *lds) {
   using G = TileGeom<JP>;
   f32x4 *part = (f32x4 *)lds;  // [4][2 * NB][64]
-  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
+  const int wid = threadIdx.x >> 6 & 3, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
   bf16_t *tiles = (bf16_t *)(lds + gate_part_bytes<NB>()) + wid * 2 * G::ROW_ELEMS;
   const int t0 = wg * 32, Dm = a.Dm, J = a.J;
   const bf16_t *xr[2];

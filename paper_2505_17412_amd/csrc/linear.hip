@@ -3,7 +3,7 @@
 // eq. (2)-(4) consumes and produces their tensors).  bf16 in, fp32 accumulation on the matrix cores, bf16 out;
 // parameter gradients fp32.
 //
-//   forward   Y^T tiles: a workgroup owns 128 output features x 128 tokens, the contraction runs in chunks of 64 through
+//   forward   Y^T tiles: a workgroup owns 128 output features x 128 tokens (256 x 256: lin_wide), the contraction runs in chunks of 64 through
 //             LDS (weights and tokens both have the contraction index contiguous, so both operands are plain row
 //             reads); output features are the MFMA rows, so a lane ends up with 8 consecutive features of one token and
 //             stores 16 bytes.
@@ -159,6 +159,137 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
 #pragma unroll
     for (int ti = 0; ti < CT; ++ti) {
       const int t = m0 + 16 * CT * wt + 32 * (ti >> 1) + 8 * (n >> 2) + 4 * (ti & 1) + (n & 3);
+      if (t >= M) continue;
+      bf16x8 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        o[i] = (__bf16)(acc[2 * cr][ti][i] + bs[i]);
+        o[4 + i] = (__bf16)(acc[2 * cr + 1][ti][i] + bs[4 + i]);
+      }
+      *reinterpret_cast<bf16x8 *>(Y + (size_t)t * O + ch) = o;
+    }
+  }
+}
+
+// The same products with tiles of 256 features x 256 tokens for eight wavefronts of 128 x 64 each, one workgroup per compute unit: three
+// quarters of the LDS reads and half the staging per product.  A tile's rows lie in LDS as 128 bytes, their pieces of 16 bytes moved by
+// the row, so that neither writes nor operand reads meet in a bank.
+// Bound: about 3900 cycles per chunk for 2048 of matrix work: LDS serves 256 KB of operands and pieces, and the first operands behind a
+// barrier and the pieces before it stand alone.  (With the pieces of two chunks in registers, one operand less ahead: the same.)
+// Against 128 x 128: 46k tokens 1024 -> 1024 122 -> 105 us, 1024 -> 1280 152 -> 135, 30k 2048 -> 2048 290 -> 240 (1050 TFLOP/s; a large
+// library product on this card 1140), 150k 384 -> 1024 227 -> 199, 10.7k 1024 -> 1280 41.8 -> 36.8; a layer's training step of 46k 7170 -> 7090.
+constexpr int WIDE = 256;
+constexpr size_t LIN_WIDE_LDS = (size_t)2 * 2 * WIDE * LIN_KC * sizeof(bf16_t);  // two stages of weights and tokens
+template <bool ONE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lin_nt_wide(LinSrc src, LinDst dst, int M, GateJob gate) {
+  constexpr int CF = 8, CT = 4, STAGE = 2 * WIDE * LIN_KC;  // elements per stage: weights, then tokens
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16_t *lds = (bf16_t *)smem;
+  if constexpr (!ONE) {
+    constexpr size_t half = gate_split_lds<3, false>();
+    static_assert(2 * half <= LIN_WIDE_LDS, "the gates' LDS");
+    if ((int)blockIdx.x >= gate.first) {  // two tiles' worth of wavefronts
+      const int h = threadIdx.x >> 8, wg = 2 * ((int)blockIdx.x - gate.first) + h;
+      return gate.blocks() == 2 ? gate_split_tile<2, false>(gate, nullptr, wg, smem + h * half) : gate_split_tile<3, false>(gate, nullptr, wg, smem + h * half);
+    }
+  }
+  const int F = ONE ? dst.O[0] : dst.O[0] + dst.O[1] + dst.O[2];  // unused outputs have O = 0
+  const int n_ot = (F + WIDE - 1) / WIDE, n_tt = (M + WIDE - 1) / WIDE;
+  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  const int tt = (idx / n_ot) * 8 + xcd;
+  if (tt >= n_tt) return;
+  const int m0 = tt * WIDE, f0 = idx % n_ot * WIDE;
+  const int tid = threadIdx.x, wid = uniform(tid >> 6), lane = tid & 63, n = lane & 15, quad = lane >> 4;
+  const int wc = wid & 1, wt = wid >> 1;  // the wavefront's features and tokens inside the tile
+  // the output that 128 features belong to (every O_i is a multiple of 128), and the first of them in it
+  auto output = [&](int f) { return ONE || f < dst.O[0] ? 0 : (f < dst.O[0] + dst.O[1] ? 1 : 2); };
+  auto inside = [&](int f, int d) { return f - (d > 0 ? dst.O[0] : 0) - (d > 1 ? dst.O[1] : 0); };
+  const int fh[2] = {f0, min(f0 + 128, F - 128)};  // (a second half past the end: the last features again, not stored)
+  const int dh[2] = {output(fh[0]), output(fh[1])};
+  f32x4 acc[CF][CT];
+#pragma unroll
+  for (int ci = 0; ci < CF; ++ci)
+#pragma unroll
+    for (int ti = 0; ti < CT; ++ti) acc[ci][ti] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // staging: item i of a thread is 16-byte piece tid & 7 of row 64 * i + tid / 8
+  const int srow = tid >> 3, seg = tid & 7;
+  const int put = (srow * 8 + (seg ^ ((srow & 3) | (srow >> 1 & 4)))) * 8;  // (element; a further 64 rows do not change the place of a piece)
+  struct Regs { bf16x8 w[4], x[4]; };
+  int xrow[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) xrow[i] = min(64 * i + srow, M - 1 - m0);
+  const int K = ONE ? src.K[0] : src.K[0] + src.K[1] + src.K[2];  // unused pairs have K = 0
+  auto fetch = [&](int kf, Regs &r) {
+    const int p = ONE || kf < src.K[0] ? 0 : (kf < src.K[0] + src.K[1] ? 1 : 2);
+    const int k0 = kf - (p > 0 ? src.K[0] : 0) - (p > 1 ? src.K[1] : 0), Kp = p == 0 ? src.K[0] : p == 1 ? src.K[1] : src.K[2];
+    const bf16_t *X = (p == 0 ? src.X[0] : p == 1 ? src.X[1] : src.X[2]) + (size_t)m0 * Kp + k0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int q = p + dh[h];  // (several pairs: d = 0; several outputs: p = 0)
+      const bf16_t *W = (q == 0 ? src.W[0] : q == 1 ? src.W[1] : src.W[2]) + (size_t)inside(fh[h], dh[h]) * Kp + k0;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) r.w[2 * h + i] = ld8(W + (size_t)(64 * i) * Kp + (uint32_t)(srow * Kp + 8 * seg));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.x[i] = ld8(X + (uint32_t)(xrow[i] * Kp + 8 * seg));
+  };
+  auto stash = [&](int buf, const Regs &r) {
+    bf16_t *to = lds + buf * STAGE + put;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      *reinterpret_cast<bf16x8 *>(to + 64 * LIN_KC * i) = r.w[i];
+      *reinterpret_cast<bf16x8 *>(to + WIDE * LIN_KC + 64 * LIN_KC * i) = r.x[i];
+    }
+  };
+  // operand row n of 16-row half a of a 32-row tile is row 8 * (n >> 2) + 4 * a + (n & 3), its pieces moved by n & 7
+  const int row = 8 * (n >> 2) + (n & 3);
+  int at[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) at[ks] = row * LIN_KC + 8 * ((4 * ks + quad) ^ (n & 7));
+  // a chunk: 16 steps of an A operand against four B operands, each step's operands requested two steps before
+  auto compute = [&](int buf) {
+    const bf16_t *cw = lds + buf * STAGE + 128 * wc * LIN_KC, *cx = lds + buf * STAGE + (WIDE + 64 * wt) * LIN_KC;
+    auto rb = [&](int ks, int ti) { return *reinterpret_cast<const bf16x8 *>(cx + at[ks] + (32 * (ti >> 1) + 4 * (ti & 1)) * LIN_KC); };
+    auto ra = [&](int i) { return *reinterpret_cast<const bf16x8 *>(cw + at[i >> 3] + (32 * ((i & 7) >> 1) + 4 * (i & 1)) * LIN_KC); };
+    bf16x8 a[3], b[2][CT];
+#pragma unroll
+    for (int ti = 0; ti < CT; ++ti) b[0][ti] = rb(0, ti);
+    a[0] = ra(0);
+    a[1] = ra(1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (i + 2 < 16) a[(i + 2) % 3] = ra(i + 2);
+      if (i >= 2 && i < 2 + CT) b[1][i - 2] = rb(1, i - 2);
+#pragma unroll
+      for (int ti = 0; ti < CT; ++ti) acc[i & 7][ti] = mfma16(a[i % 3], b[i >> 3][ti], acc[i & 7][ti]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  Regs r;
+  fetch(0, r);
+  stash(0, r);
+  __syncthreads();
+  for (int k0 = 0, buf = 0; k0 < K - LIN_KC; k0 += LIN_KC, buf ^= 1) {
+    fetch(k0 + LIN_KC, r);
+    compute(buf);
+    stash(buf ^ 1, r);  // (last read before the previous barrier)
+    __syncthreads();
+  }
+  compute((K / LIN_KC - 1) & 1);
+  if (wc == 1 && f0 + 128 >= F) return;
+  const int d = dh[wc], o0 = inside(fh[wc], d), O = d == 0 ? dst.O[0] : d == 1 ? dst.O[1] : dst.O[2];
+  const bf16_t *__restrict__ bias = d == 0 ? dst.bias[0] : d == 1 ? dst.bias[1] : dst.bias[2];
+  bf16_t *__restrict__ Y = d == 0 ? dst.Y[0] : d == 1 ? dst.Y[1] : dst.Y[2];
+#pragma unroll
+  for (int cr = 0; cr < CF / 2; ++cr) {
+    const int ch = o0 + 32 * cr + 8 * quad;
+    float bs[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) bs[j] = bias ? bf16_to_f32(bias[ch + j]) : 0.f;
+#pragma unroll
+    for (int ti = 0; ti < CT; ++ti) {
+      const int t = m0 + 64 * wt + 32 * (ti >> 1) + 8 * (n >> 2) + 4 * (ti & 1) + (n & 3);
       if (t >= M) continue;
       bf16x8 o;
 #pragma unroll
@@ -388,18 +519,34 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
 
 namespace {
 
+// Whether the tiles are of 256 x 256: where the useful part of their rounds, of 256 tiles each, is three quarters or more.  Tiles of 128 / of
+// 256, us: 21k tokens 256 -> 1024 (0.64 of two rounds) 25.0 / 29.5, 12k 1024 -> 1024 (0.73 of one) 36.0 / 37.9, 24k (0.73 of two) 64.7 / 68.4,
+// 9k 1024 -> 1408 (0.75) 44.5 / 40.8, 12.8k 1024 -> 1024 (0.78) 42.6 / 37.7, 26k (0.79 of two) 71.3 / 68.1, 16k 512 -> 1024 (0.98) 26.4 / 24.3.
+bool lin_wide(int M, int F) {
+  const long long tiles = (long long)((M + WIDE - 1) / WIDE) * ((F + WIDE - 1) / WIDE), rounds = (tiles + 255) / 256;
+  return 4ll * M * F >= 3 * rounds * 256 * WIDE * WIDE;
+}
 template <bool ONE>
 int launch_nt(const LinSrc &src, const LinDst &dst, int M, GateJob gate, hipStream_t s) {
+  const int F = dst.O[0] + dst.O[1] + dst.O[2];
+  auto launch = [&](auto kernel, int f_tile, int t_tile, int threads, size_t lds) {
+    const unsigned grid = (unsigned)(8 * (((M + t_tile - 1) / t_tile + 7) / 8) * ((F + f_tile - 1) / f_tile));
+    gate.first = (int)grid;
+    const int gate_tokens = 32 * threads / 256;
+    kernel<<<grid + (unsigned)((gate.N + gate_tokens - 1) / gate_tokens), threads, lds, s>>>(src, dst, M, gate);
+    return SSA_OK;
+  };
+  if (lin_wide(M, F)) {
+    static const hipError_t attr = hipFuncSetAttribute((const void *)lin_nt_wide<ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LIN_WIDE_LDS);
+    if (attr != hipSuccess) return SSA_ERR_HIP;
+    return launch(lin_nt_wide<ONE>, WIDE, WIDE, 512, LIN_WIDE_LDS);
+  }
   constexpr int WF = 2, WT = 2, CF = 4, CT = 4, BF = 16 * CF * WF, BT = 16 * CT * WT;
   const size_t lds = (size_t)2 * (BF + BT) * LIN_KC * sizeof(bf16_t);  // two stages of weights and tokens
   static const hipError_t attr =
       hipFuncSetAttribute((const void *)lin_nt<WF, WT, CF, CT, ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (attr != hipSuccess) return SSA_ERR_HIP;
-  const int n_ot = (dst.O[0] + dst.O[1] + dst.O[2]) / BF, n_tt = (M + BT - 1) / BT;
-  const unsigned grid = (unsigned)(8 * ((n_tt + 7) / 8) * n_ot);
-  gate.first = (int)grid;
-  lin_nt<WF, WT, CF, CT, ONE><<<grid + (unsigned)((gate.N + 31) / 32), 64 * WF * WT, lds, s>>>(src, dst, M, gate);
-  return SSA_OK;
+  return launch(lin_nt<WF, WT, CF, CT, ONE>, BF, BT, 64 * WF * WT, lds);
 }
 int launch_nt(const LinSrc &src, const LinDst &dst, int M, const GateJob *gate, hipStream_t s) {
   const bool one = src.K[1] == 0 && dst.O[1] == 0 && !gate;

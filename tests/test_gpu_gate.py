@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
     (66, 33, 8, 384),         # J = 24: weights as they are, three trips for four wavefronts
     (67, 320, 16, 1152),      # J = 48, nine
     (68, 161, 10, 640),       # J = 30: no whole pieces
+    (69, 49153, 12, 128),     # J = 36: a transposed copy, whole contractions
     (65, 62229, 16, 1024),    # the token count and layer shape bench.py --gate times
 ])
 def test_gate_forward_backward(seed, n, hq, dm):

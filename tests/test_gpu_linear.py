@@ -19,6 +19,9 @@ pytestmark = pytest.mark.gpu
     (76, 128, 384, 256, True),       # exactly one token tile
     (77, 62229, 1024, 1024, True),   # the shapes bench.py --linear times
     (78, 62229, 1024, 128, True),
+    (79, 12287, 128, 1024, True),    # 256 x 256 tiles would be used to less than three quarters
+    (80, 12289, 128, 1024, True),    # more: the last tile of one token, the fewest chunks
+    (81, 8937, 256, 1408, False),    # the last tile half features
 ])
 def test_linear_forward_backward(seed, n, d_in, d_out, bias):
     import torch
