@@ -174,10 +174,11 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
 // The same products with tiles of 256 features x 256 tokens for eight wavefronts of 128 x 64 each, one workgroup per compute unit: three
 // quarters of the LDS reads and half the staging per product.  A tile's rows lie in LDS as 128 bytes, their pieces of 16 bytes moved by
 // the row, so that neither writes nor operand reads meet in a bank.
-// Bound: about 3900 cycles per chunk for 2048 of matrix work: LDS serves 256 KB of operands and pieces, and the first operands behind a
-// barrier and the pieces before it stand alone.  (With the pieces of two chunks in registers, one operand less ahead: the same.)
-// Against 128 x 128: 46k tokens 1024 -> 1024 122 -> 105 us, 1024 -> 1280 152 -> 135, 30k 2048 -> 2048 290 -> 240 (1050 TFLOP/s; a large
-// library product on this card 1140), 150k 384 -> 1024 227 -> 199, 10.7k 1024 -> 1280 41.8 -> 36.8; a layer's training step of 46k 7170 -> 7090.
+// Bound: about 3500 cycles per chunk for 2048 of matrix work: LDS serves 256 KB of operands and pieces, and the first operands behind a
+// barrier stand alone.  The pieces of the next chunk go to LDS one by one between the products of the second half (behind them all: 46k
+// tokens 1024 -> 1280 140 us for 130, 30k 2048 -> 2048 250 for 235; the pieces of two chunks in registers: no better).
+// Against 128 x 128: 46k tokens 1024 -> 1280 152 -> 130 us, 30k 2048 -> 2048 290 -> 235 (1070 TFLOP/s; a large library product on this
+// card 1140), 62k 1024 -> 1024 157 -> 143, 10.7k 1024 -> 1280 41.8 -> 36.8; a layer's training step of 46k 7170 -> 7090.
 constexpr int WIDE = 256;
 constexpr size_t LIN_WIDE_LDS = (size_t)2 * 2 * WIDE * LIN_KC * sizeof(bf16_t);  // two stages of weights and tokens
 template <bool ONE>
@@ -233,21 +234,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int i = 0; i < 4; ++i) r.x[i] = ld8(X + (uint32_t)(xrow[i] * Kp + 8 * seg));
   };
-  auto stash = [&](int buf, const Regs &r) {
-    bf16_t *to = lds + buf * STAGE + put;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      *reinterpret_cast<bf16x8 *>(to + 64 * LIN_KC * i) = r.w[i];
-      *reinterpret_cast<bf16x8 *>(to + WIDE * LIN_KC + 64 * LIN_KC * i) = r.x[i];
-    }
+  auto place = [&](int buf, const Regs &r, int i) {
+    *reinterpret_cast<bf16x8 *>(lds + buf * STAGE + put + (i < 4 ? 0 : WIDE * LIN_KC) + 64 * LIN_KC * (i & 3)) = i < 4 ? r.w[i & 3] : r.x[i & 3];
   };
   // operand row n of 16-row half a of a 32-row tile is row 8 * (n >> 2) + 4 * a + (n & 3), its pieces moved by n & 7
   const int row = 8 * (n >> 2) + (n & 3);
   int at[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) at[ks] = row * LIN_KC + 8 * ((4 * ks + quad) ^ (n & 7));
-  // a chunk: 16 steps of an A operand against four B operands, each step's operands requested two steps before
-  auto compute = [&](int buf) {
+  // a chunk: 16 steps of an A operand against four B operands, each step's operands requested two steps before; between: what else goes out
+  // with a step's products
+  auto compute = [&](int buf, auto between) {
     const bf16_t *cw = lds + buf * STAGE + 128 * wc * LIN_KC, *cx = lds + buf * STAGE + (WIDE + 64 * wt) * LIN_KC;
     auto rb = [&](int ks, int ti) { return *reinterpret_cast<const bf16x8 *>(cx + at[ks] + (32 * (ti >> 1) + 4 * (ti & 1)) * LIN_KC); };
     auto ra = [&](int i) { return *reinterpret_cast<const bf16x8 *>(cw + at[i >> 3] + (32 * ((i & 7) >> 1) + 4 * (i & 1)) * LIN_KC); };
@@ -261,6 +258,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int i = 0; i < 16; ++i) {
       if (i + 2 < 16) a[(i + 2) % 3] = ra(i + 2);
       if (i >= 2 && i < 2 + CT) b[1][i - 2] = rb(1, i - 2);
+      between(i);
 #pragma unroll
       for (int ti = 0; ti < CT; ++ti) acc[i & 7][ti] = mfma16(a[i % 3], b[i >> 3][ti], acc[i & 7][ti]);
       __builtin_amdgcn_sched_barrier(0);
@@ -268,15 +266,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   Regs r;
   fetch(0, r);
-  stash(0, r);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) place(0, r, i);
   __syncthreads();
   for (int k0 = 0, buf = 0; k0 < K - LIN_KC; k0 += LIN_KC, buf ^= 1) {
     fetch(k0 + LIN_KC, r);
-    compute(buf);
-    stash(buf ^ 1, r);  // (last read before the previous barrier)
+    compute(buf, [&](int i) {
+      if (i >= 8) place(buf ^ 1, r, i - 8);  // (the other stage was last read before the previous barrier)
+    });
     __syncthreads();
   }
-  compute((K / LIN_KC - 1) & 1);
+  compute((K / LIN_KC - 1) & 1, [](int) {});
   if (wc == 1 && f0 + 128 >= F) return;
   const int d = dh[wc], o0 = inside(fh[wc], d), O = d == 0 ? dst.O[0] : d == 1 ? dst.O[1] : dst.O[2];
   const bf16_t *__restrict__ bias = d == 0 ? dst.bias[0] : d == 1 ? dst.bias[1] : dst.bias[2];
