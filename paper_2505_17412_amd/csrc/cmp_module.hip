@@ -51,21 +51,32 @@ __device__ inline Site decode(uint64_t key, int bits) {
   return Site{(int)(key >> (3 * bits)), (int)compact3(code >> 2), (int)compact3(code >> 1), (int)compact3(code)};
 }
 
+// What a pass needs before its convolution, in one launch: the neighbour table, U of the tensors, and in the forward pass the transposed weights
+// (10.7k tokens: in three launches 18.8 us, 11.7 in one).  Workgroups of 256 items each, one kind after the other.
+struct PrepareArgs {
+  const uint64_t *keys;
+  const int32_t *item_start, *perm;
+  int N, G, bits, C, m;
+  int32_t *nbr;
+  Pair<const bf16_t *> x, pe, w;
+  Pair<bf16_t *> U, wt;
+  unsigned nbr_wgs, pe_wgs, wt_wgs;  // of the table; per tensor of the others
+};
+
 // nbr[pos][o] = sorted position of the token at coords(pos) + offset o in the same item, or -1.  One thread per
 // (pos, o): a binary search of the neighbour's key inside the item's range of the sorted keys.
-__global__ void c_neighbors(const uint64_t *__restrict__ keys, const int32_t *__restrict__ item_start, int N, int G,
-                            int bits, int32_t *__restrict__ nbr) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (size_t)N * 27) return;
-  const int pos = (int)(i / 27), o = (int)(i % 27);
+__device__ inline void find_neighbor(const PrepareArgs &a, size_t i) {
+  if (i >= (size_t)a.N * 27) return;
+  const uint64_t *__restrict__ keys = a.keys;
+  const int bits = a.bits, pos = (int)(i / 27), o = (int)(i % 27);
   const Site s = decode(keys[pos], bits);
   const int x = s.x + o / 9 - 1, y = s.y + o / 3 % 3 - 1, z = s.z + o % 3 - 1;
   int found = -1;
-  if ((unsigned)x < (unsigned)G && (unsigned)y < (unsigned)G && (unsigned)z < (unsigned)G) {
+  if ((unsigned)x < (unsigned)a.G && (unsigned)y < (unsigned)a.G && (unsigned)z < (unsigned)a.G) {
     const uint64_t want = ((uint64_t)s.item << (3 * bits)) |
                           (uint64_t)((spread3m((uint32_t)x) << 2) | (spread3m((uint32_t)y) << 1) | spread3m((uint32_t)z));
-    int lo = item_start[s.item];
-    const int e = item_start[s.item + 1];
+    int lo = a.item_start[s.item];
+    const int e = a.item_start[s.item + 1];
     int hi = e;  // first position in [lo, e) whose key is >= want
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -73,35 +84,38 @@ __global__ void c_neighbors(const uint64_t *__restrict__ keys, const int32_t *__
     }
     if (lo < e && keys[lo] == want) found = lo;
   }
-  nbr[i] = found;
+  a.nbr[i] = found;
 }
 
 // U[pos] = x[perm[pos]] + PE[place of the token inside its block]   (bf16, sorted order)
-__global__ void c_add_pe(Pair<const bf16_t *> xs, Pair<const bf16_t *> pes, const int32_t *__restrict__ perm,
-                         const uint64_t *__restrict__ keys, int N, int C, int bits, int m, Pair<bf16_t *> Us) {
-  const bf16_t *__restrict__ x = xs.v[blockIdx.z], *__restrict__ pe = pes.v[blockIdx.z];
-  bf16_t *__restrict__ U = Us.v[blockIdx.z];
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int per = C / 8;
-  if (i >= (size_t)N * per) return;
+__device__ inline void add_pe(const PrepareArgs &a, int tensor, size_t i) {
+  const bf16_t *__restrict__ x = a.x.v[tensor], *__restrict__ pe = a.pe.v[tensor];
+  const int per = a.C / 8, m = a.m;
+  if (i >= (size_t)a.N * per) return;
   const int pos = (int)(i / per), c0 = (int)(i % per) * 8;
-  const Site s = decode(keys[pos], bits);
+  const Site s = decode(a.keys[pos], a.bits);
   const int p = ((s.x & (m - 1)) * m + (s.y & (m - 1))) * m + (s.z & (m - 1));
-  const bf16x8 a = ld8(x + (size_t)perm[pos] * C + c0), b = ld8(pe + (size_t)p * C + c0);
+  const bf16x8 u = ld8(x + (size_t)a.perm[pos] * a.C + c0), v = ld8(pe + (size_t)p * a.C + c0);
   bf16x8 r;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) r[j] = (__bf16)((float)a[j] + (float)b[j]);
-  *reinterpret_cast<bf16x8 *>(U + (size_t)pos * C + c0) = r;
+  for (int j = 0; j < 8; ++j) r[j] = (__bf16)((float)u[j] + (float)v[j]);
+  *reinterpret_cast<bf16x8 *>(a.U.v[tensor] + (size_t)pos * a.C + c0) = r;
 }
 
-// Wt[o][c_out][c_in] = w[o][c_in][c_out]
-__global__ void c_transpose_w(Pair<const bf16_t *> ws, int C, Pair<bf16_t *> wts) {
-  const bf16_t *__restrict__ w = ws.v[blockIdx.z];
-  bf16_t *__restrict__ wt = wts.v[blockIdx.z];
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void c_prepare(PrepareArgs a) {
+  unsigned wg = blockIdx.x;
+  if (wg < a.nbr_wgs) return find_neighbor(a, (size_t)wg * 256 + threadIdx.x);
+  wg -= a.nbr_wgs;
+  if (a.wt_wgs == 0) return add_pe(a, wg / a.pe_wgs, (size_t)(wg % a.pe_wgs) * 256 + threadIdx.x);
+  const int tensor = wg / (a.pe_wgs + a.wt_wgs);
+  wg %= a.pe_wgs + a.wt_wgs;
+  if (wg < a.pe_wgs) return add_pe(a, tensor, (size_t)wg * 256 + threadIdx.x);
+  // wt[o][c_out][c_in] = w[o][c_in][c_out]
+  const int C = a.C;
+  const size_t i = (size_t)(wg - a.pe_wgs) * 256 + threadIdx.x;
   if (i >= (size_t)27 * C * C) return;
   const int ci = (int)(i % C), co = (int)(i / C % C), o = (int)(i / ((size_t)C * C));
-  wt[i] = w[((size_t)o * C + ci) * C + co];
+  a.wt.v[tensor][i] = a.w.v[tensor][((size_t)o * C + ci) * C + co];
 }
 
 // Gather-GEMM: out[pos][n] = bias[n] + sum_o sum_k in[nbr[pos][o']][k] * Bw[o][n][k], o' = o (forward) or 26 - o
@@ -334,12 +348,26 @@ __global__ void c_pool(Pair<const float *> Ys, size_t part_stride, const int32_t
   }
 }
 
-// dY[pos] = dXc[block(pos)] / count(block)   (bf16, sorted order): gradient of the mean pool
-__global__ void c_expand(Pair<const float *> dxcs, const int32_t *__restrict__ tok_cmp,
-                         const int32_t *__restrict__ cmp_start, int N, int C, Pair<bf16_t *> dYs) {
+// dY[pos] = dXc[block(pos)] / count(block)   (bf16, sorted order): gradient of the mean pool.  The workgroups behind those:
+// dbias[f] = sum over blocks of dXc[c][f]  (the pool's 1/count and the block's count cancel): partial sums over
+// DBIAS_PARTS row ranges, added in order by c_sum_last.
+constexpr int DBIAS_PARTS = 32;
+__global__ __launch_bounds__(256) void c_expand(Pair<const float *> dxcs, const int32_t *__restrict__ tok_cmp, const int32_t *__restrict__ cmp_start,
+                                                int N, int Nc, int C, Pair<bf16_t *> dYs, Pair<float *> parts) {
   const float *__restrict__ dxc = dxcs.v[blockIdx.z];
+  const unsigned expand_wgs = gridDim.x - DBIAS_PARTS;
+  if (blockIdx.x >= expand_wgs) {
+    const int part = (int)(blockIdx.x - expand_wgs), per = (Nc + DBIAS_PARTS - 1) / DBIAS_PARTS;
+    const int b = min(Nc, part * per), e = min(Nc, b + per), f = threadIdx.x;
+    if (f >= C) return;  // C <= 256
+    float s = 0.f;
+#pragma unroll 8
+    for (int c = b; c < e; ++c) s += dxc[(size_t)c * C + f];
+    parts.v[blockIdx.z][(size_t)part * C + f] = s;
+    return;
+  }
   bf16_t *__restrict__ dY = dYs.v[blockIdx.z];
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   const int per = C / 8;
   if (i >= (size_t)N * per) return;
   const int pos = (int)(i / per), c0 = (int)(i % per) * 8;
@@ -349,21 +377,6 @@ __global__ void c_expand(Pair<const float *> dxcs, const int32_t *__restrict__ t
 #pragma unroll
   for (int j = 0; j < 8; ++j) r[j] = (__bf16)(dxc[(size_t)c * C + c0 + j] * inv);
   *reinterpret_cast<bf16x8 *>(dY + (size_t)pos * C + c0) = r;
-}
-
-// dbias[f] = sum over blocks of dXc[c][f]  (the pool's 1/count and the block's count cancel): partial sums over
-// DBIAS_PARTS row ranges, added in order by c_sum_parts.
-constexpr int DBIAS_PARTS = 32;
-__global__ void c_dbias_partial(Pair<const float *> dxcs, int Nc, int C, Pair<float *> parts) {
-  const float *__restrict__ dxc = dxcs.v[blockIdx.z];
-  float *__restrict__ part = parts.v[blockIdx.z];
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= C) return;
-  const int per = (Nc + DBIAS_PARTS - 1) / DBIAS_PARTS;
-  const int b = min(Nc, (int)blockIdx.y * per), e = min(Nc, b + per);
-  float s = 0.f;
-  for (int c = b; c < e; ++c) s += dxc[(size_t)c * C + f];
-  part[(size_t)blockIdx.y * C + f] = s;
 }
 
 // dx[perm[pos]] += dU[pos]   (caller order, parameter dtype)
@@ -396,47 +409,65 @@ __global__ void c_dx_accum(Pair<float *> dUs, int parts, size_t part_stride, con
 // (LDS [m^3][C] fp32), so no two threads ever add to the same cell.
 __global__ void c_dpe_partial(Pair<const float *> dUs, const uint64_t *__restrict__ keys, int N, int C, int bits, int m,
                               int chunk, Pair<float *> parts) {
-  extern __shared__ float tbl[];
+  extern __shared__ __align__(16) float tbl[];
   const float *__restrict__ dU = dUs.v[blockIdx.z];
   float *__restrict__ part = parts.v[blockIdx.z];
   const int rows = m * m * m;
-  for (int i = threadIdx.x; i < rows * C; i += blockDim.x) tbl[i] = 0.f;
+  for (int i = threadIdx.x; i < rows * C / 4; i += blockDim.x) reinterpret_cast<float4 *>(tbl)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
   const int b = blockIdx.x * chunk, e = min(N, b + chunk);
-  for (int p0 = b; p0 < e; p0 += 8) {  // eight tokens' rows in flight, added in token order
-    int row[8];
+  for (int p0 = b; p0 < e; p0 += 16) {  // sixteen tokens' rows in flight, added in token order
+    int row[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < 16; ++u) {
       const Site s = decode(keys[min(p0 + u, e - 1)], bits);
       row[u] = (((s.x & (m - 1)) * m + (s.y & (m - 1))) * m + (s.z & (m - 1))) * C;
     }
     for (int f = threadIdx.x; f < C; f += blockDim.x) {
-      float v[8];
+      float v[16];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = dU[(size_t)min(p0 + u, e - 1) * C + f];
+      for (int u = 0; u < 16; ++u) v[u] = dU[(size_t)min(p0 + u, e - 1) * C + f];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < 16; ++u)
         if (p0 + u < e) tbl[row[u] + f] += v[u];
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < rows * C; i += blockDim.x) part[(size_t)blockIdx.x * rows * C + i] = tbl[i];
+  float4 *to = reinterpret_cast<float4 *>(part + (size_t)blockIdx.x * rows * C);
+  for (int i = threadIdx.x; i < rows * C / 4; i += blockDim.x) to[i] = reinterpret_cast<const float4 *>(tbl)[i];
 }
 
-// Ordered sum of partial results: out[g][i] = sum of part[g*group + j][i], j = 0 .. group-1 (parts past n_parts are
-// skipped).  One launch with group = n_parts gives the total; two launches (group, then the group results) keep
-// the work parallel when there are many parts.  The order of the additions is fixed either way.
+// Ordered sums of partial results.  c_sum_parts: out[g][i] = sum of part[g*group + j][i], j = 0 .. group-1 (parts past n_parts are
+// skipped), which keeps the work parallel where there are many.  c_sum_last: the totals of the three parameter gradients in one
+// launch, workgroups one after the other.  The order of the additions is fixed either way.
+__device__ inline float sum_in_order(const float *part, size_t len, int b, int e) {
+  float s = 0.f;
+#pragma unroll 8
+  for (int k = b; k < e; ++k) s += part[(size_t)k * len];
+  return s;
+}
 __global__ void c_sum_parts(Pair<const float *> parts, int n_parts, int n_groups, size_t len, Pair<float *> outs) {
-  const float *__restrict__ part = parts.v[blockIdx.z];
-  float *__restrict__ out = outs.v[blockIdx.z];
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= len) return;
   const int group = (n_parts + n_groups - 1) / n_groups;
-  const int g = blockIdx.y, b = g * group, e = min(n_parts, b + group);
-  float s = 0.f;
-#pragma unroll 8
-  for (int k = b; k < e; ++k) s += part[(size_t)k * len + i];
-  out[(size_t)g * len + i] = s;
+  const int g = blockIdx.y, b = g * group;
+  outs.v[blockIdx.z][(size_t)g * len + i] = sum_in_order(parts.v[blockIdx.z] + i, len, b, min(n_parts, b + group));
+}
+struct SumJob {
+  Pair<const float *> parts;
+  Pair<float *> outs;
+  int n_parts;
+  unsigned len;
+  __host__ __device__ unsigned wgs() const { return (len + 255) / 256; }
+};
+struct SumJobs { SumJob j[3]; };
+__global__ __launch_bounds__(256) void c_sum_last(SumJobs jobs) {
+  unsigned wg = blockIdx.x;
+  int d = 0;
+  while (d < 2 && wg >= jobs.j[d].wgs()) wg -= jobs.j[d].wgs(), ++d;
+  const SumJob &j = jobs.j[d];
+  const unsigned i = wg * 256 + threadIdx.x;
+  if (i < j.len) j.outs.v[blockIdx.z][i] = sum_in_order(j.parts.v[blockIdx.z] + i, j.len, 0, j.n_parts);
 }
 
 // Weight gradient: dW[o][ci][co] = sum_pos U[nbr[pos][o]][ci] * dY[pos][co], a contraction over tokens.  A workgroup
@@ -645,15 +676,21 @@ Pair<T *> carve(char *ws, size_t off, size_t stride) {
 template <class T>
 Pair<const T *> as_const(const Pair<T *> &p) { return Pair<const T *>{{p.v[0], p.v[1]}}; }
 
-// Neighbour table and U of the n tensors.
-void prepare_inputs(const ssa_blocks_t *b, int C, int n, const CmpTensor *t, const ModPlan &pl, char *in, hipStream_t s) {
-  const int N = b->N;
-  c_neighbors<<<(unsigned)(((size_t)N * 27 + 255) / 256), 256, 0, s>>>(b->sorted_keys, b->item_start, N, b->G, b->bits, (int32_t *)(in + pl.nbr));
-  const Pair<const bf16_t *> x{{(const bf16_t *)t[0].x, (const bf16_t *)t[n - 1].x}};
-  const Pair<const bf16_t *> pe{{(const bf16_t *)t[0].w->pe, (const bf16_t *)t[n - 1].w->pe}};
-  const size_t items = (size_t)N * (C / 8);
-  c_add_pe<<<dim3((unsigned)((items + 255) / 256), 1, n), 256, 0, s>>>(x, pe, b->perm, b->sorted_keys, N, C, b->bits, b->m_cmp,
-                                                                       carve<bf16_t>(in, pl.u, pl.rows16));
+// Neighbour table and U of the n tensors; wt: their transposed weights go there, or {null, null}.
+void prepare_inputs(const ssa_blocks_t *b, int C, int n, const CmpTensor *t, const ModPlan &pl, char *in, Pair<bf16_t *> wt, hipStream_t s) {
+  PrepareArgs a{b->sorted_keys, b->item_start, b->perm, b->N, b->G, b->bits, C, b->m_cmp, (int32_t *)(in + pl.nbr)};
+  a.U = carve<bf16_t>(in, pl.u, pl.rows16);
+  a.wt = wt;
+  for (int i = 0; i < 2; ++i) {
+    const CmpTensor &x = t[i < n ? i : n - 1];
+    a.x.v[i] = (const bf16_t *)x.x;
+    a.pe.v[i] = (const bf16_t *)x.w->pe;
+    a.w.v[i] = (const bf16_t *)x.w->w;
+  }
+  a.nbr_wgs = (unsigned)(((size_t)b->N * 27 + 255) / 256);
+  a.pe_wgs = (unsigned)(((size_t)b->N * (C / 8) + 255) / 256);
+  a.wt_wgs = wt.v[0] ? (unsigned)((pl.wlen + 255) / 256) : 0u;
+  c_prepare<<<a.nbr_wgs + n * (a.pe_wgs + a.wt_wgs), 256, 0, s>>>(a);
 }
 
 }  // namespace
@@ -677,9 +714,7 @@ int cmp_module_forward(const ssa_params_t *p, const ssa_blocks_t *b, int n, cons
   const Pair<bf16_t *> U = carve<bf16_t>(in, pl.u, pl.rows16), Wt = carve<bf16_t>(ws, pl.wt, pl.wlen * 2);
   const Pair<float *> Y = carve<float>(ws, pl.y, pl.rows32);
   ProfScope ps(PROF_CMP_MODULE, s);
-  prepare_inputs(b, C, n, t, pl, in, s);
-  const Pair<const bf16_t *> w{{(const bf16_t *)t[0].w->w, (const bf16_t *)t[n - 1].w->w}};
-  c_transpose_w<<<dim3((unsigned)((pl.wlen + 255) / 256), 1, n), 256, 0, s>>>(w, C, Wt);
+  prepare_inputs(b, C, n, t, pl, in, Wt, s);
   Pair<ConvSrc> src{};
   for (int i = 0; i < n; ++i) src.v[i] = ConvSrc{U.v[i], Wt.v[i], (const bf16_t *)t[i].w->bias, Y.v[i]};
   const ConvShape shape = conv_shape(N, C, n);
@@ -705,12 +740,10 @@ int cmp_module_backward(const ssa_params_t *p, const ssa_blocks_t *b, int n, con
   const Pair<float *> pb = carve<float>(ws, pl.pb, (size_t)DBIAS_PARTS * C * 4);
   const Pair<const float *> dxc{{t[0].dxc, t[n - 1].dxc}};
   ProfScope ps(PROF_CMP_MODULE_BWD, s);
-  if (!prepared) prepare_inputs(b, C, n, t, pl, in, s);
+  if (!prepared) prepare_inputs(b, C, n, t, pl, in, Pair<bf16_t *>{}, s);
   const size_t items = (size_t)N * (C / 8);
   const dim3 igrid((unsigned)((items + 255) / 256), 1, n);
-  c_expand<<<igrid, 256, 0, s>>>(dxc, b->tok_cmp, b->cmp_start, N, C, dY);
-  c_dbias_partial<<<dim3((C + 63) / 64, DBIAS_PARTS, n), 64, 0, s>>>(dxc, b->Nc, C, pb);
-  c_sum_parts<<<dim3((C + 255) / 256, 1, n), 256, 0, s>>>(as_const(pb), DBIAS_PARTS, 1, (size_t)C, Pair<float *>{{t[0].dbias, t[n - 1].dbias}});
+  c_expand<<<dim3(igrid.x + DBIAS_PARTS, 1, n), 256, 0, s>>>(dxc, b->tok_cmp, b->cmp_start, N, b->Nc, C, dY, pb);
   // data gradient: dU[pos] = sum_o dY[token that took pos as neighbour o] * w[o]^T; w as given has c_out contiguous
   Pair<ConvSrc> src{};
   for (int i = 0; i < n; ++i) src.v[i] = ConvSrc{dY.v[i], (const bf16_t *)t[i].w->w, nullptr, dU.v[i]};
@@ -721,7 +754,6 @@ int cmp_module_backward(const ssa_params_t *p, const ssa_blocks_t *b, int n, con
   const unsigned pgrid = (unsigned)((pl.plen + 255) / 256);
   c_dpe_partial<<<dim3(pl.pe_chunks, 1, n), 128, pl.plen * 4, s>>>(as_const(dU), b->sorted_keys, N, C, b->bits, m, pl.pe_chunk, ppe);
   c_sum_parts<<<dim3(pgrid, PE_GROUPS, n), 256, 0, s>>>(as_const(ppe), pl.pe_chunks, PE_GROUPS, pl.plen, ppe2);
-  c_sum_parts<<<dim3(pgrid, 1, n), 256, 0, s>>>(as_const(ppe2), PE_GROUPS, 1, pl.plen, Pair<float *>{{t[0].dpe, t[n - 1].dpe}});
   const int CT = C < 128 ? C : 128;
   const dim3 g(27, pl.dw_chunks, (C / CT) * (C / CT) * n);
   switch (CT) {
@@ -729,8 +761,10 @@ int cmp_module_backward(const ssa_params_t *p, const ssa_blocks_t *b, int n, con
     case 64: c_dw<64><<<g, 256, 0, s>>>(as_const(U), as_const(dY), nbr, N, C, pl.dw_chunk, pw); break;
     default: c_dw<128><<<g, 256, 0, s>>>(as_const(U), as_const(dY), nbr, N, C, pl.dw_chunk, pw); break;
   }
-  c_sum_parts<<<dim3((unsigned)((pl.wlen + 255) / 256), 1, n), 256, 0, s>>>(as_const(pw), pl.dw_chunks, 1, pl.wlen,
-                                                                            Pair<float *>{{t[0].dw, t[n - 1].dw}});
+  const SumJobs last{{{as_const(pw), Pair<float *>{{t[0].dw, t[n - 1].dw}}, pl.dw_chunks, (unsigned)pl.wlen},
+                      {as_const(ppe2), Pair<float *>{{t[0].dpe, t[n - 1].dpe}}, PE_GROUPS, (unsigned)pl.plen},
+                      {as_const(pb), Pair<float *>{{t[0].dbias, t[n - 1].dbias}}, DBIAS_PARTS, (unsigned)C}}};
+  c_sum_last<<<dim3(last.j[0].wgs() + last.j[1].wgs() + last.j[2].wgs(), 1, n), 256, 0, s>>>(last);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 

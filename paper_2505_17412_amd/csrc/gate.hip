@@ -20,17 +20,12 @@
 
 namespace {
 
-// Wt[j][k] = w[k][j] (j < J), zero rows up to 16*ceil(J/16);  Wp[k][j] = w[k][j], zero for J <= j < 64
-__global__ void g_prep_w(const bf16_t *__restrict__ w, int Dm, int J, int JR, bf16_t *__restrict__ wt, bf16_t *__restrict__ wp) {
+// Wt[j][k] = w[k][j] (j < J), zero rows up to 16*ceil(J/16)
+__global__ void g_prep_w(const bf16_t *__restrict__ w, int Dm, int J, int JR, bf16_t *__restrict__ wt) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (wt && i < (size_t)JR * Dm) {
-    const int j = (int)(i / Dm), k = (int)(i % Dm);
-    wt[i] = j < J ? w[(size_t)k * J + j] : (bf16_t)0;
-  }
-  if (wp && i < (size_t)Dm * JP) {
-    const int k = (int)(i / JP), j = (int)(i % JP);
-    wp[i] = j < J ? w[(size_t)k * J + j] : (bf16_t)0;
-  }
+  if (i >= (size_t)JR * Dm) return;
+  const int j = (int)(i / Dm), k = (int)(i % Dm);
+  wt[i] = j < J ? w[(size_t)k * J + j] : (bf16_t)0;
 }
 
 // gates[tok][j] = sigmoid(sum_k x[tok][k] w[k][j] + b[j]); NB = blocks of 16 gate columns.  A wavefront owns two tiles of 16
@@ -76,12 +71,19 @@ __global__ __launch_bounds__(256) void g_fwd_split(GateJob a, const bf16_t *__re
   gate_split_tile<NB, WT>(a, wt, blockIdx.x, lds);
 }
 
-// dz[tok][j] = dgates * g * (1 - g) for j < J, zero up to column 63 (bf16)
-__global__ void g_dz(const bf16_t *__restrict__ gates, const bf16_t *__restrict__ dgates, int N, int J, bf16_t *__restrict__ dz) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (size_t)N * JP) return;
+// dz[tok][j] = dgates * g * (1 - g) for j < J, zero up to column 63 (bf16); behind them wp[k][j] = w[k][j], zero for J <= j < 64
+__global__ void g_dz(const bf16_t *__restrict__ gates, const bf16_t *__restrict__ dgates, const bf16_t *__restrict__ w, int N, int Dm, int J,
+                     bf16_t *__restrict__ dz, bf16_t *__restrict__ wp) {
+  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool weights = i >= (size_t)N * JP;
+  if (weights) i -= (size_t)N * JP;
+  if (weights && i >= (size_t)Dm * JP) return;
   const size_t t = i / JP;
   const int j = (int)(i % JP);
+  if (weights) {
+    wp[i] = j < J ? w[t * J + j] : (bf16_t)0;
+    return;
+  }
   float v = 0.f;
   if (j < J) {
     const float g = bf16_to_f32(gates[t * J + j]);
@@ -293,7 +295,7 @@ static int gate_forward_launch(int N, int d_model, int J, const void *x, const v
   ProfScope ps(PROF_GATE_FWD, s);
   const GateJob a{(const bf16_t *)x, (const bf16_t *)w, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates, 0};
   const bool as_is = gate_as_is(J), split = as_is || gate_split(N, d_model, NB);
-  if (!as_is) g_prep_w<<<(unsigned)(((size_t)JR * d_model + 255) / 256), 256, 0, s>>>(a.w, d_model, J, JR, wt, nullptr);
+  if (!as_is) g_prep_w<<<(unsigned)(((size_t)JR * d_model + 255) / 256), 256, 0, s>>>(a.w, d_model, J, JR, wt);
   const auto run = [&](auto kernel, int tokens) { kernel<<<(unsigned)((N + tokens - 1) / tokens), 256, 0, s>>>(a, wt); };
   switch (NB) {
     case 1: split ? run(g_fwd_split<1, true>, 32) : run(g_fwd<1>, 128); break;
@@ -388,8 +390,8 @@ extern "C" int ssa_gate_backward(const ssa_params_t *p, int32_t d_model, const v
   bf16_t *wp = (bf16_t *)(ws + pl.wp), *dz = (bf16_t *)(ws + pl.dz);
   float *pw = (float *)(ws + pl.pw), *pb = (float *)(ws + pl.pb);
   ProfScope ps(PROF_GATE_BWD, s);
-  g_prep_w<<<(unsigned)(((size_t)d_model * JP + 255) / 256), 256, 0, s>>>((const bf16_t *)w, d_model, J, 0, nullptr, wp);
-  g_dz<<<(unsigned)(((size_t)N * JP + 255) / 256), 256, 0, s>>>((const bf16_t *)gates, (const bf16_t *)dgates, N, J, dz);
+  g_dz<<<(unsigned)((((size_t)N + d_model) * JP + 255) / 256), 256, 0, s>>>((const bf16_t *)gates, (const bf16_t *)dgates, (const bf16_t *)w, N,
+                                                                          d_model, J, dz, wp);
   g_dx<<<dim3((unsigned)((N + 127) / 128), (unsigned)((d_model + GDX_DIMS - 1) / GDX_DIMS)), 256, 0, s>>>(dz, wp, N, d_model, (bf16_t *)dx_accum);
   g_dw<<<dim3(d_model / 128, pl.chunks), 256, 0, s>>>((const bf16_t *)x, dz, N, d_model, pl.chunk, pw, pb);
   g_sum_parts<<<(unsigned)(((size_t)(d_model + 1) * J + 255) / 256), 256, 0, s>>>(pw, pb, pl.chunks, d_model, J, dw, dbias);
