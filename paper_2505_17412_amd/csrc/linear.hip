@@ -9,7 +9,7 @@
 //             stores 16 bytes.
 //   dx        the same kernel on a transposed copy of the weights (dx = dy W).
 //   dW        dy^T x contracts over tokens: 32-token tiles of dy and x go through LDS row-major and both operands are
-//             transposing LDS reads; the token range is split over workgroups and the fp32 partial tiles are added in a
+//             transposing LDS reads (256 x 256 tiles: lin_tn_splits); the token range is split over workgroups and the fp32 partial tiles are added in a
 //             fixed order.  db = column sums of dy in two steps (per 64-token chunk, then over the chunks), fixed order.
 // No floating point atomics anywhere.
 #include "mfma_common.h"
@@ -403,6 +403,110 @@ __global__ __launch_bounds__(256) void lin_tn(LinGrad<NP> a, const bf16_t *__res
         dst[(size_t)(o0 + 64 * wo + 16 * oi + 4 * quad + i) * K + c0 + 64 * wk + 16 * ki + n] = acc[oi][ki][i];
 }
 
+// The same with tiles of 256 x 256 for eight wavefronts of 128 outputs x 64 inputs, 64 tokens per stage; the outputs of the projections lie one
+// after the other (a tile's halves of 128 may belong to two of them), every projection in the same n_splits.
+// LDS: a token's row of 512 bytes in 16 units of 32 bytes, moved by the row, so that the four rows that 16 lanes of a transposing read
+// take their pieces from are four different units of 128 bytes.  Operands and staging as in lin_nt_wide, and the same bound; with 128 x 128
+// tiles a barrier came every 32 tokens.  Weight gradient with its sums, 128 x 128 / 256 x 256, us: 46k tokens 1024 -> 1024 151 / 118, 384 ->
+// 1024 94 / 67, 30k 2048 -> 2048 355 / 272, 20k 1024 -> 1408 116 / 82; a layer's training step of 46k 7133 / 7000, of 10.7k 1466 / 1439.
+template <int NP>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lin_tn_wide(LinGrad<NP> a, const bf16_t *__restrict__ X, int M, int K, int F,
+                                                                                            int n_splits, int tok_per_split) {
+  constexpr int CO = 8, CK = 4, ROWS = 64, ARRAY = ROWS * 512, STAGE = 2 * ARRAY;  // bytes: dY, then X
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int n_kt = (K + WIDE - 1) / WIDE, tiles = (F + WIDE - 1) / WIDE * n_kt;
+  const int split = blockIdx.x / tiles, tile = blockIdx.x % tiles, f0 = tile / n_kt * WIDE, c0 = tile % n_kt * WIDE;
+  const int t_begin = split * tok_per_split, t_end = min(M, t_begin + tok_per_split);
+  const int tid = threadIdx.x, wid = uniform(tid >> 6), lane = tid & 63, n = lane & 15, quad = lane >> 4;
+  const int wo = wid & 1, wk = wid >> 1;
+  auto owner = [&](int f) { int d = 0; while (d < NP - 1 && f >= a.O[d]) f -= a.O[d], ++d; return make_int2(d, f); };
+  // staging: item i of a thread is piece tid & 31 (16 bytes) of row 16 * i + tid / 32, of dY and of X
+  const int piece = tid & 31, trow = tid >> 5;
+  const int2 mine = owner(min(f0 + 128 * (piece >> 4), F - 128));  // (halves past the end: the last 128 again, not stored)
+  const int Oy = a.O[mine.x];
+  const bf16_t *__restrict__ dY = a.dY[mine.x] + mine.y + 8 * (piece & 15);
+  const bf16_t *__restrict__ Xc = X + min(c0 + 128 * (piece >> 4), K - 128) + 8 * (piece & 15);
+  // unit of 32 bytes u of row r lies at u ^ ((r >> 3 & 3) * 4 + (r & 3)); row 16 * i + trow: another 8 with i odd
+  const int put = trow * 512 + ((piece >> 1) ^ ((trow >> 3) * 4 + (trow & 3))) * 32 + (piece & 1) * 16;
+  f32x4 acc[CO][CK];
+#pragma unroll
+  for (int oi = 0; oi < CO; ++oi)
+#pragma unroll
+    for (int ki = 0; ki < CK; ++ki) acc[oi][ki] = f32x4{0.f, 0.f, 0.f, 0.f};
+  struct Regs { bf16x8 y[4], x[4]; } r;
+  int r_t0;
+  auto fetch = [&](int t0) {
+    r_t0 = t0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const size_t t = (size_t)min(t0 + 16 * i + trow, M - 1);
+      r.y[i] = ld8(dY + t * Oy);
+      r.x[i] = ld8(Xc + t * K);
+    }
+  };
+  auto place = [&](int buf, int i) {  // (tokens past the split's end are zeros: what was read there is another split's)
+    const int row = 16 * (i & 3);
+    const bf16x8 v = i < 4 ? r.y[i & 3] : r.x[i & 3];
+    *reinterpret_cast<bf16x8 *>(smem + buf * STAGE + (i < 4 ? 0 : ARRAY) + row * 512 + (put ^ (i & 1 ? 256 : 0))) = r_t0 + row + trow < t_end ? v : zero8();
+  };
+  // operand: 16 dims from unit u, of rows 8 * quad + 0 .. 7 of a 32-row half
+  const int at = (8 * quad + (n >> 2)) * 512 + (4 * quad + (n >> 2)) * 32 + (n & 3) * 8;
+  auto operand = [&](const unsigned char *rows, int u) {
+    const unsigned char *p = rows + (at ^ (u * 32));
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 4 * 512));
+    typedef __attribute__((ext_vector_type(8))) short s16x8;
+    const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, both);
+  };
+  auto compute = [&](int buf, auto between) {
+    const unsigned char *sy = smem + buf * STAGE, *sx = sy + ARRAY;
+    auto ra = [&](int i) { return operand(sy + (i >> 3) * 32 * 512, 8 * wo + (i & 7)); };
+    auto rb = [&](int ks, int ki) { return operand(sx + ks * 32 * 512, 4 * wk + ki); };
+    bf16x8 av[3], bv[2][CK];
+#pragma unroll
+    for (int ki = 0; ki < CK; ++ki) bv[0][ki] = rb(0, ki);
+    av[0] = ra(0);
+    av[1] = ra(1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (i + 2 < 16) av[(i + 2) % 3] = ra(i + 2);
+      if (i >= 2 && i < 2 + CK) bv[1][i - 2] = rb(1, i - 2);
+      between(i);
+#pragma unroll
+      for (int ki = 0; ki < CK; ++ki) acc[i & 7][ki] = mfma16(av[i % 3], bv[i >> 3][ki], acc[i & 7][ki]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  fetch(t_begin);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) place(0, i);
+  __syncthreads();
+  int buf = 0;
+  for (int t0 = t_begin; t0 + ROWS < t_end; t0 += ROWS, buf ^= 1) {
+    fetch(t0 + ROWS);
+    compute(buf, [&](int i) {
+      if (i >= 8) place(buf ^ 1, i - 8);  // (the other stage was last read before the previous barrier)
+    });
+    __syncthreads();
+  }
+  compute(buf, [](int) {});
+  const int f = f0 + 128 * wo;
+  if (f >= F) return;
+  const int2 out = owner(f);
+  float *dst = a.part[out.x] + (size_t)split * a.O[out.x] * K;
+#pragma unroll
+  for (int ki = 0; ki < CK; ++ki) {
+    const int col = c0 + 64 * wk + 16 * ki + n;
+    if (col >= K) continue;
+#pragma unroll
+    for (int oi = 0; oi < CO; ++oi)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dst[(size_t)(out.y + 16 * oi + 4 * quad + i) * K + col] = acc[oi][ki][i];
+  }
+}
+
 // dw[j] = sum_s part[s][j], s ascending; blockIdx.y picks the projection.  A chain of loads that wait for each other without
 // the unrolling: the four weight gradients of a layer at 10.7 k tokens 48 us in four launches of one load at a time, 32 in two (query, key and
 // value together) of eight.
@@ -489,6 +593,16 @@ __global__ __launch_bounds__(256) void lin_colsum_finish(LinGrad<NP> a, int n_pa
   }
 }
 
+// Splits of the token range with tiles of 256 x 256: one round, or 0 where the useful part of it is less than three quarters or a split
+// would have fewer than 384 tokens (1024 -> 1024, 312 tokens a split: 38.0 us, 41.3 in large tiles; 666: 53, 52; 640 -> 1024, 428: 43, 38).
+int lin_tn_splits(int M, int d_in, int F) {
+  const int tiles = (F + WIDE - 1) / WIDE * ((d_in + WIDE - 1) / WIDE);
+  int s = 256 / tiles;
+  if (s > 64) s = 64;
+  if (s < 1 || M < 384 * s) return 0;
+  return 4ll * F * d_in * s >= 3ll * 256 * WIDE * WIDE ? s : 0;
+}
+
 struct LinPlan {
   int splits, tok_per_split, bias_parts;
   size_t wt, part, bpart, total;
@@ -507,7 +621,8 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
   p.splits = M > 0 ? (M + p.tok_per_split - 1) / p.tok_per_split : 1;
   size_t off = 0;
   p.wt = off; off += align_up((size_t)d_in * d_out * sizeof(bf16_t), 256);
-  p.part = off; off += align_up((size_t)p.splits * d_in * d_out * sizeof(float), 256);
+  const int wide = lin_tn_splits(M, d_in, d_out), most = p.splits > wide ? p.splits : wide;
+  p.part = off; off += align_up((size_t)most * d_in * d_out * sizeof(float), 256);
   p.bias_parts = M > 0 ? (M + COLSUM_CHUNK - 1) / COLSUM_CHUNK : 1;
   p.bpart = off; off += align_up((size_t)p.bias_parts * d_out * sizeof(float), 256);
   p.total = off;
@@ -641,7 +756,23 @@ static void weight_grads(int M, int d_in, const int *d_out, const void *x, const
     o_max = d_out[i] > o_max ? d_out[i] : o_max;
     any_bias |= dbias[i] != nullptr;
   }
-  lin_tn<NP><<<grid, 256, 0, s>>>(a, (const bf16_t *)x, M, d_in);
+  int F = 0, fits = 1 << 30;
+  for (int i = 0; i < NP; ++i) {
+    const int most = lin_tn_splits(M, d_in, d_out[i]);
+    F += d_out[i];
+    fits = min(fits, most > a.splits[i] ? most : a.splits[i]);
+  }
+  const int wide = lin_tn_splits(M, d_in, F);
+  if (wide && wide <= fits) {
+    static const hipError_t attr = hipFuncSetAttribute((const void *)lin_tn_wide<NP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LIN_WIDE_LDS);
+    (void)attr;  // (a launch beyond the limit is refused, and that error reported)
+    const int tok = ((M + wide - 1) / wide + 63) / 64 * 64, n_splits = (M + tok - 1) / tok;
+    for (int i = 0; i < NP; ++i) a.splits[i] = n_splits;
+    const int tiles = (F + WIDE - 1) / WIDE * ((d_in + WIDE - 1) / WIDE);
+    lin_tn_wide<NP><<<tiles * n_splits, 512, LIN_WIDE_LDS, s>>>(a, (const bf16_t *)x, M, d_in, F, n_splits, tok);
+  } else {
+    lin_tn<NP><<<grid, 256, 0, s>>>(a, (const bf16_t *)x, M, d_in);
+  }
   lin_sum_parts<NP><<<dim3((unsigned)((size_t)o_max * d_in / 256), NP), 256, 0, s>>>(a, d_in);
   if (any_bias) {
     lin_colsum<NP><<<dim3(bias_parts, NP), 256, 0, s>>>(a, M);

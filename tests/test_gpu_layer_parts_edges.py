@@ -72,4 +72,6 @@ def test_projections_in_wide_tiles(seed, n, hq, hkv, d, dm):
     ssa.ssa_backward(p, blk, q, k, v, g, ob, lse, idx, d_o, dq, dk, dv, dg)
     dz = (dg.float() * g.float() * (1 - g.float())).bfloat16().float().reshape(n, 3 * hq)
     close(d_o.reshape(n, cq), dy.float() @ f["wo"], "dO")
+    for s, t in (("dwq", dq), ("dwk", dk), ("dwv", dv)):
+        close(grads[s], t.reshape(n, -1).float().T @ x.float(), s)
     close(dx, dq.reshape(n, cq).float() @ f["wq"] + dk.reshape(n, c).float() @ f["wk"] + dv.reshape(n, c).float() @ f["wv"] + dz @ f["wg"].T, "dx")

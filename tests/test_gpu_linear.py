@@ -22,6 +22,10 @@ pytestmark = pytest.mark.gpu
     (79, 12287, 128, 1024, True),    # 256 x 256 tiles would be used to less than three quarters
     (80, 12289, 128, 1024, True),    # more: the last tile of one token, the fewest chunks
     (81, 8937, 256, 1408, False),    # the last tile half features
+    (82, 6143, 1024, 1024, False),   # the weight gradient by 128 x 128
+    (83, 6144, 1024, 1024, True),    # and by 256 x 256, 384 tokens a split
+    (84, 8065, 640, 1024, False),    # a tile of half its inputs, a split of one token
+    (85, 3841, 1024, 1408, True),    # a tile of half its outputs
 ])
 def test_linear_forward_backward(seed, n, d_in, d_out, bias):
     import torch
