@@ -196,6 +196,8 @@ __device__ inline int selected(const int32_t *row, int T) {
   return nv;
 }
 
+// FEW: up to 8 blocks a row, whose partials are requested before it is known how many there are (what lies in the other rows is not used).
+template <bool FEW>
 __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int per_row = a.D / 8;
@@ -203,20 +205,38 @@ __global__ __launch_bounds__(256) void m_slc_merge(MergeArgs a) {
   const int c8 = (int)(i % per_row), h = (int)(i / per_row % a.Hq), tok = (int)(i / ((size_t)per_row * a.Hq));
   const int g = h / a.hs, hl = h % a.hs;
   const size_t slot0 = ((size_t)tok * a.Hkv + g) * a.T;
-  const int nv = selected(a.idx + slot0, a.T);
-  float M = -INFINITY;
-#pragma unroll 8
-  for (int j = 0; j < nv; ++j) M = fmaxf(M, a.pml[((slot0 + j) * a.hs + hl) * 2]);
-  float L = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-  for (int j = 0; j < nv; ++j) {
-    const size_t r = (slot0 + j) * a.hs + hl;
-    const float2 ml = *reinterpret_cast<const float2 *>(a.pml + r * 2);
-    const bf16x8 x = ld8(a.po + r * a.D + 8 * c8);
+  float M = -INFINITY, L = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto add = [&](const float2 &ml, const bf16x8 &x) {
     const float wj = ml.x == -INFINITY ? 0.f : fast_exp2(ml.x - M);
     L += wj * ml.y;
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] += wj * (float)x[e];
+  };
+  if constexpr (FEW) {
+    float2 ml[8];
+    bf16x8 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const size_t r = (slot0 + min(j, a.T - 1)) * a.hs + hl;
+      ml[j] = *reinterpret_cast<const float2 *>(a.pml + r * 2);
+      x[j] = ld8(a.po + r * a.D + 8 * c8);
+    }
+    const int nv = selected(a.idx + slot0, a.T);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j < nv) M = fmaxf(M, ml[j].x);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j < nv) add(ml[j], x[j]);
+  } else {
+    const int nv = selected(a.idx + slot0, a.T);
+#pragma unroll 8
+    for (int j = 0; j < nv; ++j) M = fmaxf(M, a.pml[((slot0 + j) * a.hs + hl) * 2]);
+#pragma unroll 8
+    for (int j = 0; j < nv; ++j) {
+      const size_t r = (slot0 + j) * a.hs + hl;
+      add(*reinterpret_cast<const float2 *>(a.pml + r * 2), ld8(a.po + r * a.D + 8 * c8));
+    }
   }
   const float inv = L > 0.f ? 1.0f / L : 0.f;
   const size_t th = (size_t)tok * a.Hq + h, NH = (size_t)a.N * a.Hq;
@@ -471,7 +491,11 @@ int slc_merge_kernel(const MfmaView &v, int D, const SlcPartials &part, const in
   MergeArgs m{part.o, part.ml, idx, (const bf16_t *)gates, (bf16_t *)out_branch, lse, (bf16_t *)out,
               v.N, v.Hq, v.Hkv, v.hs, v.T, D, keep};
   const size_t threads = (size_t)v.N * v.Hq * (D / 8);
-  m_slc_merge<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(m);
+  // Small problems wait for one round trip to memory instead of two.  Whole forward, one after the other / together, us: 1k tokens, top-8 59.0 / 57.0,
+  // 5k, top-4 100.3 / 98.1, 11k, top-8 267.8 / 264.8, 8k, heads of 128 338.6 / 333.8; with two blocks a row the eight requests are too many (11k
+  // 172.5 / 177.3), and in large ones the registers cost wavefronts (40k 1210 / 1215).
+  const bool few = v.T >= 4 && v.T <= 8 && (size_t)v.N * v.Hq * v.T <= (size_t)1 << 21;
+  (few ? m_slc_merge<true> : m_slc_merge<false>)<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(m);
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 

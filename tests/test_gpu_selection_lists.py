@@ -56,6 +56,31 @@ def test_orders_of_the_work_chunks(seed, lens):
     full_parity(wl, queries=np.arange(0, wl.n_tokens, 97, dtype=np.int32))
 
 
+@pytest.mark.parametrize("topk", [3, 4, 8, 9])
+def test_merge_of_rows_with_few_blocks(topk):
+    """Rows of I with fewer blocks than top-k (items of 1 to 12): what the workspace held before, here NaNs, is in no result (the merge requests
+    the partials of 4 to 8 blocks before it knows how many there are)."""
+    import torch
+    from paper_2505_17412_amd import ssa
+    wl = inputs.make_sequence_workload(351, (5, 17, 90, 33, 1), hq=8, hkv=1, d=32, l=(4, 8, 16), topk=topk)
+    p, blk = util.build_blocks_gpu(wl)
+    q, k, v, g = (util.to_dev(t, "bf16") for t in (wl.q, wl.k, wl.v, wl.gates))
+    n = wl.n_tokens
+
+    def run(fill):
+        out, branch = torch.empty_like(q), torch.empty((3, *q.shape), dtype=q.dtype, device="cuda")
+        lse, idx = torch.empty((3, n, 8), device="cuda"), torch.empty((n, 1, topk), dtype=torch.int32, device="cuda")
+        ws = torch.full((ssa.ssa_workspace_bytes(p, blk, False),), fill, dtype=torch.uint8, device="cuda")
+        ssa.ssa_forward(p, blk, q, k, v, g, out, lse, idx, branch, workspace=ws)
+        torch.cuda.synchronize()
+        return out, lse, idx, branch
+
+    a, b = run(0), run(255)
+    assert (b[2] == -1).any() and torch.isfinite(b[0].float()).all()
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("heads", [1025])
 def test_more_kv_heads_than_buckets(heads):
     """Heads are independent: with more of them than 8192 buckets in eight classes of block length leave one each, the first, a middle
