@@ -328,7 +328,7 @@ int ssa_layer_backward(const ssa_params_t *params, const ssa_blocks_t *blocks, i
  * Measurement hook (not an operation of the paper; for benchmarks that need the duration of single kernels).
  * While enabled, every kernel the library launches is bracketed by a HIP event pair recorded on the launch
  * stream.  ssa_profile_enable(on) clears the totals; ssa_profile_get(i, ...) waits for the recorded events and
- * returns kernel i's name (static string), total milliseconds and number of launches since the last enable.
+ * returns kernel i's name (static string), total milliseconds and number of passes it ran in since the last enable.
  * Not thread-safe.
  */
 int ssa_profile_enable(int on);

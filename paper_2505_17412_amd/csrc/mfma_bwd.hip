@@ -580,6 +580,7 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     if (!beside) rc = sel_index_count(j, s);
     if (rc == SSA_OK) rc = sel_index_scan(j, s);
     if (rc == SSA_OK && !beside) rc = sel_index_fill(j, s);
+    if (rc == SSA_OK && !beside) rc = sel_index_order(j, s);  // (behind the dQ kernel its slots lie in no cache any more)
     if (rc != SSA_OK) return rc;
   }
   {
@@ -591,8 +592,8 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     const size_t lds = dq_lds_bytes<D>(), sel_lds = beside ? j.lds_bytes() : 0;
     m_bwd_dq<D, NW0><<<dim3(sel.n + xcd_grid_size((N + tw0 - 1) / tw0, Hkv)), 64 * NW0, sel_lds > lds ? sel_lds : lds, s>>>(a, sel);
   }
-  if (!j.base) {
-    ProfScope ps(PROF_BWD_INVERT, s);
+  if (beside && !j.base) {
+    ProfScope ps(PROF_BWD_INVERT, s, j.ticket != nullptr);
     rc = sel_index_order(j, s);
     if (rc != SSA_OK) return rc;
   }

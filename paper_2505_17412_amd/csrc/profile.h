@@ -11,16 +11,18 @@ enum ProfId {
 
 bool prof_enabled();
 void prof_begin(int id, hipStream_t s);
-void prof_end(int id, hipStream_t s);
+void prof_end(int id, hipStream_t s, bool counted);
 
+// counted: whether the scope adds one to the kernel's launches.  What a pass does in two places is one launch of two scopes, the later not
+// counted, so that total time over launches stays the time of a pass.
 struct ProfScope {
   int id;
   hipStream_t s;
-  bool on;
-  ProfScope(int id_, hipStream_t s_) : id(id_), s(s_), on(prof_enabled()) {
+  bool counted, on;
+  ProfScope(int id_, hipStream_t s_, bool counted_ = true) : id(id_), s(s_), counted(counted_), on(prof_enabled()) {
     if (on) prof_begin(id, s);
   }
   ~ProfScope() {
-    if (on) prof_end(id, s);
+    if (on) prof_end(id, s, counted);
   }
 };

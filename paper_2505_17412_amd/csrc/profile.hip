@@ -12,7 +12,7 @@ const char *const kNames[PROF_COUNT] = {
     "bwd_prep", "bwd_pre_delta", "bwd_dq_cmp_win", "bwd_dq_slc", "bwd_invert_selection", "bwd_dkv_slc", "bwd_dkv_cmp_win",
     "bwd_finish_unpool", "generic_path", "cmp_module_fwd", "cmp_module_bwd", "gate_fwd", "gate_bwd",
     "linear_fwd", "linear_bwd", "fwd_invert_selection", "bwd_dq_merge", "bwd_slc"};
-struct Rec { int id; hipEvent_t a, b; };
+struct Rec { int id; hipEvent_t a, b; bool counted; };
 bool g_on = false;
 std::vector<Rec> g_pending;
 std::vector<hipEvent_t> g_pool;
@@ -31,7 +31,7 @@ void drain() {
     float ms = 0.f;
     if (hipEventSynchronize(r.b) == hipSuccess && hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
       g_ms[r.id] += ms;
-      g_cnt[r.id] += 1;
+      g_cnt[r.id] += r.counted;
     }
     g_pool.push_back(r.a);
     g_pool.push_back(r.b);
@@ -45,10 +45,10 @@ void prof_begin(int id, hipStream_t s) {
   g_open[id] = get_event();
   (void)hipEventRecord(g_open[id], s);
 }
-void prof_end(int id, hipStream_t s) {
+void prof_end(int id, hipStream_t s, bool counted) {
   hipEvent_t e = get_event();
   (void)hipEventRecord(e, s);
-  g_pending.push_back(Rec{id, g_open[id], e});
+  g_pending.push_back(Rec{id, g_open[id], e, counted});
 }
 
 extern "C" int ssa_profile_enable(int on) {
