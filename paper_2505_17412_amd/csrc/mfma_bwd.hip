@@ -14,6 +14,7 @@
 //     (scores with the query rows in the lanes); the contractions over query rows take Q^T and dO^T from the
 //     staged row-major tiles through the transposing LDS read.
 #include "mfma_common.h"
+#include "cmp_form.h"
 #include "mfma_launch.h"
 #include "mfma_qc.h"
 #include "profile.h"
@@ -38,9 +39,12 @@ struct PreArgs {
   bf16_t *Qs, *dOg;             // sorted row-major copies: Q [N(pos)][Hq][D], gate_b * dO [3][N(pos)][Hq][D]
 };
 
+// BESIDE: with the index's count pass, whose own LDS a token's dO rows leave no room for where they take all there is.
+template <bool BESIDE>
 __global__ __launch_bounds__(256) void m_bwd_pre(PreArgs a, SelBeside sel) {
   extern __shared__ __align__(16) bf16_t tile[];  // [Hq*D]: the token's dO rows
-  if ((int)blockIdx.x < sel.n) return sel_beside<256, true, false>(sel, blockIdx.x, tile);
+  if constexpr (BESIDE)
+    if ((int)blockIdx.x < sel.n) return sel_beside<256, true, false>(sel, blockIdx.x, tile);
   const int pos = (int)blockIdx.x - sel.n, tok = a.perm[pos];
   const int HD = a.Hq * a.D;
   const size_t base = (size_t)tok * HD;
@@ -564,7 +568,8 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
   const size_t NH = (size_t)N * Hq;
   const bool two_kernels = slc_bwd_two_kernels(blk, D, Hkv, v.T);  // selection branch
   // the selection index, beside the pre-pass and the dQ kernel where it is small
-  const bool beside = sel_beside_fits(N, Hkv, v.T, v.Ns);
+  const size_t do_rows = (size_t)Hq * D * sizeof(bf16_t);
+  const bool beside = sel_beside_fits(N, Hkv, v.T, v.Ns) && do_rows + SEL_COUNT_LDS <= LDS_CU;
   const SelJob j = sel_index_job(idx, v.perm, v.slc_start, N, Hkv, v.T, v.Ns, w.sel, false, two_kernels, true, beside);
   int rc = SSA_OK;
   {
@@ -572,8 +577,8 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     PreArgs a{(const bf16_t *)q, (const bf16_t *)dout, (const bf16_t *)out_branch, (const bf16_t *)gates, lse, v.perm,
               N, Hq, Hkv, v.hs, D, (bf16_t *)dgates, w.lse2s, w.deltas, w.gws, w.deltag, w.Qs, w.dOg};
     const SelBeside sel = beside ? sel_pass(j, SelPass::count) : sel_alone();
-    const size_t lds = (size_t)Hq * D * sizeof(bf16_t), sel_lds = beside ? j.lds_bytes() : 0;
-    m_bwd_pre<<<sel.n + N, 256, sel_lds > lds ? sel_lds : lds, s>>>(a, sel);
+    const size_t sel_lds = beside ? j.lds_bytes() : 0;
+    (beside ? m_bwd_pre<true> : m_bwd_pre<false>)<<<sel.n + N, 256, sel_lds > do_rows ? sel_lds : do_rows, s>>>(a, sel);
   }
   if (!beside || !j.ticket) {
     ProfScope ps(PROF_BWD_INVERT, s);

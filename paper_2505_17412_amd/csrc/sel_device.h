@@ -294,6 +294,7 @@ int sel_index_order(const SelJob &j, hipStream_t s);
 // 1293 / 1293, of sequences of 65k in 64-token blocks (1024) 1020 / 1018, of 147k 2573 / 2700.  Entries of a row beyond 16 take more
 // registers than the dQ kernel has.  (Beside the forward's window branch, whose workgroups have 128 threads: 2k tokens 83 / 91, 11k 273 / 274.)
 constexpr int SEL_BESIDE_KEYS = 512, SEL_BESIDE_T = 16, SEL_BESIDE_MOST = 384;
+constexpr size_t SEL_COUNT_LDS = 1024;  // what sel_count takes besides its bits, at most
 enum class SelPass { none, count, fill };
 struct SelBeside {
   SelJob j;

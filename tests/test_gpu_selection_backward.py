@@ -43,6 +43,15 @@ def test_blocks_of_many_lengths_in_one_launch(seed, lens, hq, hkv, d, l, topk):
     full_parity(inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk))
 
 
+@pytest.mark.parametrize("seed,hq,hkv,d", [
+    (541, 640, 40, 128),  # all LDS of a compute unit: the index has launches of its own
+    (542, 636, 159, 128),  # 1 KB less: its count pass beside the pre-pass
+    (543, 2560, 160, 32),
+])
+def test_dout_rows_that_fill_the_lds(seed, hq, hkv, d):
+    full_parity(inputs.make_sequence_workload(seed, (19, 5), hq=hq, hkv=hkv, d=d, l=(2, 4, 8), topk=2))
+
+
 def test_one_long_block_among_many_short_ones():
     """Half of the tokens on one voxel, the rest alone in their blocks: the two kernels would launch 5 million workgroups."""
     wl = inputs.random_points_workload(520, 64, (18300,) + (300,) * 60, 16, 2, 64, (1, 2, 2), 2, "bf16")

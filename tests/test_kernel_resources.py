@@ -18,7 +18,7 @@ def resources(source, tmp_path):
            os.path.join(build.CSRC, source), "-o", str(tmp_path / "o.o")]
     text = subprocess.run(cmd, capture_output=True, text=True, check=True).stderr
     out, name = {}, None
-    for what, value in re.findall(r"remark: [^\n]*?\b(Function Name|VGPRs|VGPRs Spill|Occupancy \[waves/SIMD\]): (\S+)", text):
+    for what, value in re.findall(r"remark: [^\n]*?\b(Function Name|VGPRs|VGPRs Spill|LDS Size \[bytes/block\]|Occupancy \[waves/SIMD\]): (\S+)", text):
         if what == "Function Name":
             name = value
             out[name] = {}
@@ -63,3 +63,11 @@ def test_selection_and_dq_kernels_keep_their_wavefronts(tmp_path):
     for part, waves in want.items():
         found = [r for name, r in kernels.items() if part in name]
         assert len(found) == 1 and found[0]["Occupancy"] >= waves and found[0]["VGPRs Spill"] == 0, (part, found)
+
+
+def test_backward_pre_pass_leaves_the_lds_to_its_rows(tmp_path):
+    """A token's dO rows may take all LDS there is (81920 elements): alone the kernel has none of its own, beside the count pass of the
+    selection index no more than the launch reserves (SEL_COUNT_LDS)."""
+    kernels = {k: v for k, v in resources("mfma_bwd.hip", tmp_path).items() if "m_bwd_pre" in k}
+    lds = {"Lb1E" in name: r["LDS Size"] for name, r in kernels.items()}
+    assert lds[False] == 0 and lds[True] <= 1024, kernels
