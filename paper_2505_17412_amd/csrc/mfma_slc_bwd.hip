@@ -80,14 +80,14 @@ __device__ __forceinline__ void slc_bwd_chunk(const SlcBwdArgs &a, unsigned char
   using P = PTile<D>;
   using SH = SlcBwdShape<D, NW, RG>;
   constexpr int KB = SH::KB, ST = SH::ST, ROWS = SH::ROWS, ALL_ROWS = SH::ALL_ROWS, TILES = SH::TILES, NTHR = SH::NTHR, GW = SH::GW, QB = SH::QB, KS = SH::KS;
-  const int wid = (threadIdx.x >> 6) % GW, grp = RG == 1 ? 0 : (threadIdx.x >> 6) / GW, lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
-  const int hs = a.v.hs, Hq = a.v.Hq, Hkv = a.v.Hkv;
+  const int wid = uniform((threadIdx.x >> 6) % GW), grp = RG == 1 ? 0 : uniform((threadIdx.x >> 6) / GW), lane = threadIdx.x & 63, n = lane & 15, quad = lane >> 4;
+  const int hs = a.v.hs, hs_log = 31 - __builtin_clz(hs), Hq = a.v.Hq, Hkv = a.v.Hkv;  // (hs is 1, 2, 4, 8 or 16)
   const int qbeg = cr.first, qend = cr.first + cr.count;
   const size_t out_row0 = (size_t)a.part_row_start[cr.key] + (size_t)cr.chunk * (kend - kbeg);
   const size_t kstride = (size_t)Hkv * D;
   const float sl2 = a.v.sl2, scale = a.v.scale;
   const typename P::Lanes ln = P::lanes();
-  const int slots = ALL_ROWS / hs;  // tokens per stage
+  const int slots = ALL_ROWS >> hs_log;  // tokens per stage
   const int n_st = (cr.count + slots - 1) / slots;
 
   // partial rows: ((pos*Hkv + g)*T + rank)*hs + head; the row behind the last one takes what belongs to no token
@@ -101,11 +101,11 @@ __device__ __forceinline__ void slc_bwd_chunk(const SlcBwdArgs &a, unsigned char
   const int it_tile = threadIdx.x / P::ITEMS % TILES;
   const int it_row = threadIdx.x % P::ITEMS / P::SEGS, it_seg = threadIdx.x % P::SEGS;
   const int it_off = it_tile * P::BYTES + P::off(it_row, it_seg);
-  const int it_slot = (it_tile * 32 + it_row) / hs, it_step = IT_TILES * 32 / hs;  // (hs is 1, 2, 4, 8 or 16)
-  const int it_col = (g * hs + it_row % hs) * D + it_seg * 8;
+  const int it_slot = (it_tile * 32 + it_row) >> hs_log, it_step = IT_TILES * 32 >> hs_log;
+  const int it_col = (g * hs + (it_row & (hs - 1))) * D + it_seg * 8;
   const bool has_sc = threadIdx.x < 2 * ALL_ROWS;
   const int sc_arr = (threadIdx.x / ALL_ROWS) & 1, sc_r = threadIdx.x % ALL_ROWS;
-  const int sc_slot = sc_r / hs, sc_head = g * hs + sc_r % hs;
+  const int sc_slot = sc_r >> hs_log, sc_head = g * hs + (sc_r & (hs - 1));
   const float *sc_src = sc_arr == 0 ? a.lse2s : a.deltas;
   const float sc_mul = sc_arr == 1 ? -1.0f : 1.0f;
   // (loads are unconditional with clamped indices, so the compiler's wait counts are exact)
@@ -288,8 +288,8 @@ __device__ __forceinline__ void slc_bwd_chunk(const SlcBwdArgs &a, unsigned char
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
         const int row = ROWS * grp + 16 * (qb0 + q) + n;
-        const uint32_t pr = rows[row / hs];
-        p.w[q] = __hip_atomic_load((const uint64_t *)(a.pdq + (size_t)(pr + (pr == dummy ? 0 : row % hs)) * D + acc_dim(dtw, quad)),
+        const uint32_t pr = rows[row >> hs_log];
+        p.w[q] = __hip_atomic_load((const uint64_t *)(a.pdq + (size_t)(pr + (pr == dummy ? 0 : row & (hs - 1))) * D + acc_dim(dtw, quad)),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     };
@@ -347,10 +347,10 @@ __device__ __forceinline__ void slc_bwd_chunk(const SlcBwdArgs &a, unsigned char
         const int it = i0 + (int)threadIdx.x;
         if (ITEMS % NTHR != 0 && it >= ITEMS) break;
         const int row = it / CH, ch = it % CH;
-        const uint32_t pr = rows[row / hs];
+        const uint32_t pr = rows[row >> hs_log];
         const bf16x8 x = *reinterpret_cast<const bf16x8 *>(smem + SH::DQ_OFF + (SH::DOUBLE ? (st & 1) * SH::DQ_B : 0) + row * (D * 2) + (((ch ^ (row >> 1)) & (CH - 1)) << 4));
         // (unconditional: rows that do not exist go to the spare row, so that the compiler can count the stores)
-        __builtin_nontemporal_store(x, reinterpret_cast<bf16x8 *>(a.pdq + (size_t)(pr + (pr == dummy ? 0 : row % hs)) * D + ch * 8));
+        __builtin_nontemporal_store(x, reinterpret_cast<bf16x8 *>(a.pdq + (size_t)(pr + (pr == dummy ? 0 : row & (hs - 1))) * D + ch * 8));
       }
     };
 
@@ -412,8 +412,10 @@ __device__ __forceinline__ void slc_bwd_chunk(const SlcBwdArgs &a, unsigned char
 }
 
 // NW = 4: no block has more than 128 keys; NW = 8: SEG, some have more than 256.
+// Registers for two wavefronts per SIMD; at head_dim 32 and NW = 4 for three (168; two -> three, us, 32 heads of 32, top-16, blocks of 32, 64
+// and 128 keys: 12k tokens 317 -> 251, 347 -> 288, 436 -> 391; 40k 939 -> 722, 1011 -> 820, 1354 -> 1228).
 template <int D, int NW, bool SEG>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void m_slc_bwd(SlcBwdArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32 && NW == 4 ? 3 : 2))) void m_slc_bwd(SlcBwdArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int wi = blockIdx.x;
   if (wi >= a.chunk_start[a.v.Hkv * a.v.Ns]) return;

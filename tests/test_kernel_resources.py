@@ -41,6 +41,14 @@ def test_one_pass_selection_backward_fits_its_registers(tmp_path):
         assert r["Occupancy"] >= 2 and r["VGPRs Spill"] == 0, (name, r)
 
 
+def test_selection_backward_of_short_blocks_at_head_dim_32(tmp_path):
+    """Three workgroups of four wavefronts per compute unit: a fifth of the kernel's time at two."""
+    kernels = {k: v for k, v in resources("mfma_slc_bwd.hip", tmp_path).items() if "m_slc_bwdILi32ELi4E" in k}
+    assert len(kernels) == 1
+    for name, r in kernels.items():
+        assert r["Occupancy"] >= 3 and r["VGPRs Spill"] == 0, (name, r)
+
+
 def test_compression_kernels_keep_their_wavefronts(tmp_path):
     """Three wavefronts per SIMD up to head_dim 64, at 128 two, with no more spilled than was measured."""
     all_ = resources("mfma_fwd.hip", tmp_path)
