@@ -38,7 +38,7 @@ bool sel_counted(int D, int hs, int s_max, int N, int Hkv, int Ns);
 inline size_t sel_cnt_words(int N, int Hkv, int Ns) { return ((size_t)N + POS_TILE - 1) / POS_TILE * Hkv * Ns; }
 
 // Block-centric selection kernels: query tokens per work chunk, and the per-(token, KV head, rank) partial results.
-constexpr int BC_CHUNK = 256, BC_CHUNK_MIN = 32, DKV_CHUNK_MIN = 128;
+constexpr int BC_CHUNK = 256, BC_CHUNK_MIN = 32;
 int bc_chunk_len(int N, int Hkv, int T);
 struct SlcPartials {
   bf16_t *o;    // [N][Hkv][T][hs][D]: unnormalised partial output (forward) / partial dQ (backward) per selected block

@@ -2,6 +2,7 @@
 #include "mfma_common.h"
 #include "mfma_launch.h"
 #include "cmp_form.h"
+#include "sel_order.h"
 #include "profile.h"
 
 // The one-pass selection backward takes a block's keys in segments, each a whole pass over the query rows: it is the faster form
@@ -162,18 +163,6 @@ struct BwdPlan {
 
 constexpr int DKV_WG_KEYS = 128;  // keys per workgroup of the dK/dV kernels (4 waves x 2 blocks of 16)
 
-// Query tokens per work chunk of the one-pass selection backward.  Long chunks write fewer partial dK and dV rows; the compute units want
-// a chunk each, two where no block has more than 128 keys and workgroups are of four wavefronts.  us of the kernel, the sums of its partial
-// rows and the index, chunks of 128 / 256 / 512: 3k tokens, top-8 (48k entries) 177 / 233 / 387; 6k 210 / 197 / 205; 11k 546 / 478 / 454;
-// 21k in three shapes 526 / 485 / 468; 46k, top-16, 2334 / 2349 / 2215; blocks of 64 keys, 16k tokens, top-8 (262k) 259 / 266 / 305, 65k,
-// top-16, 1668 / 1525 / 1530.  (1024 was slower.)
-int one_pass_chunk_len(const ssa_blocks *b, long long entries) {
-  const int wanted = b->slc_tok_max > 128 ? 320 : 1024;
-  int len = 512;
-  while (len > DKV_CHUNK_MIN && entries / len < wanted) len /= 2;
-  return len;
-}
-
 BwdPlan bwd_plan(const ssa_ctx &c) {
   BwdPlan p{};
   const ssa_blocks *b = c.blk;
@@ -199,7 +188,7 @@ BwdPlan bwd_plan(const ssa_ctx &c) {
   // slc_tok_max * entries/chunk_len + N*Hkv.  A chunk is one workgroup; the two-kernel form measured best at 1024.
   // chunk_len grows until the partial sums fit in about 1 GiB.
   const size_t entries = (size_t)c.N * c.Hkv * c.T;
-  p.chunk_len = slc_bwd_two_kernels(b, c.d, c.Hkv, c.T) ? 1024 : one_pass_chunk_len(b, (long long)entries);
+  p.chunk_len = slc_bwd_two_kernels(b, c.d, c.Hkv, c.T) ? 1024 : one_pass_chunk_len(b->slc_tok_max, (long long)entries);
   size_t rows;
   for (;;) {
     rows = (size_t)b->slc_tok_max * (entries / p.chunk_len + 1) + (size_t)c.N * c.Hkv;

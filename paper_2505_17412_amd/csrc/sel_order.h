@@ -1,5 +1,5 @@
-// How the work chunks of the selection kernels are ordered (sel_index.hip), as a rule on the problem's sizes alone.  Host code without
-// HIP.
+// How the work chunks of the selection kernels are ordered (sel_index.hip) and how long those of the one-pass backward are, as rules on
+// the problem's sizes alone.  Host code without HIP.
 #pragma once
 
 constexpr int ORDER_BINS = 8192;         // bucket counters that fit the LDS table of m_chunk_order
@@ -35,4 +35,19 @@ inline SelOrder sel_order(int n_tokens, int kv_heads) {
     }
   }
   return o;
+}
+
+// Query tokens per work chunk of the one-pass selection backward, for lists of `entries` tokens in all and blocks of up to `longest` keys.
+// Long chunks write fewer partial dK and dV rows; a compute unit wants two chunks of eight wavefronts or, where no block has more
+// than 128 keys, eight of four, so that the last ones to end leave few of them idle.  us of the kernel, the index, the launches beside it, the sums
+// of the partial rows and the finish, chunks of 128 / 256 / 512.  Blocks of up to 128 keys, by entries: 64k 220 / 229 / 268, 256k 432 / 448 / 496,
+// 544k 955 / 945 / 969, 640k 951 / 947 / 953, 1.3M 2182 / 2113 / 2129, 2.2M 4823 / 4713 / 4700; heads of 32 256k 437 / 464 / 490, 640k 1003 / 1017
+// / 1051, 2.2M 5358 / 5271 / 5331.  Longer ones: 96k 264 / 258 / 293, 128k 367 / 383 / 470, 170k 546 / 509 / 561 and 561 / 507 / 541, 256k 635 / 662 /
+// 704, 341k in three shapes 827 / 803 / 790, 384k 1242 / 1055 / 976, 640k 2308 / 2198 / 2203.  (1024 was slower.)
+constexpr int DKV_CHUNK_MIN = 128;
+inline int one_pass_chunk_len(int longest, long long entries) {
+  const int wanted = longest > 128 ? 560 : 2048;
+  int len = 512;
+  while (len > DKV_CHUNK_MIN && entries / len < wanted) len /= 2;
+  return len;
 }
