@@ -491,13 +491,14 @@ struct FinishArgs {
   bf16_t *dK, *dV;
   float *dKc_out, *dVc_out;
 };
-// Bound: latency of loads that depend on few others; a thread keeps 4 dims of a row and every 256/(row/4)-th part and token, whose loads
+// Bound: latency of loads that depend on few others; a thread keeps 4 dims of a row and every NT/(row/4)-th part and token, whose loads
 // are in flight together.  (With a thread per dim, parts and tokens one after the other: 11k tokens 35 us for 17, 21k 48 for 29, 62k 75 for 56.)
-__global__ __launch_bounds__(256) void m_bwd_finish(FinishArgs a) {
-  __shared__ f32x4 part[2][256];
+template <int NT>
+__global__ __launch_bounds__(NT) void m_bwd_finish(FinishArgs a) {
+  __shared__ f32x4 part[2][NT];
   const int c = blockIdx.x, cols = a.Hkv * a.D / 4, row = 4 * cols;
   const int b = a.cmp_start[c], e = a.cmp_start[c + 1], slc = a.cmp_slc[c];
-  const int per = min(cols, 256), groups = 256 / per, grp = threadIdx.x / per;  // (threads past the last group have nothing to do)
+  const int per = min(cols, NT), groups = NT / per, grp = threadIdx.x / per;  // (threads past the last group have nothing to do)
   const float inv = 1.0f / (float)(e - b);
   for (int c0 = 0; c0 < cols; c0 += per) {
     const int f = 4 * (c0 + (int)threadIdx.x % per);
@@ -550,6 +551,16 @@ __global__ __launch_bounds__(256) void m_bwd_finish(FinishArgs a) {
     }
     __syncthreads();
   }
+}
+
+// Threads of a block's workgroup.  Where there are many blocks of few pieces (of 4 dims of a token), workgroups of one or two wavefronts hold
+// more blocks at a time.  us with 64 / 128 / 256 threads, sequences of 30k tokens, blocks of 4 tokens, rows of 32, 64, 128 dims (32, 64, 128 pieces): 22 / 28
+// / 55, 30 / 37 / 54, 38 / 43 / 57; 80k, blocks of 32, rows of 32 (256) 20 / 22 / 30, of 64 (512) 35 / 35 / 42, of 128 (1024) 64 / 66 / 71; 62k in a
+// 128^3 shell (886) 67 / 59 / 57.  Few blocks have all workgroups in flight and wait for the sums over the parts: 500 of 16 tokens, rows of 128 13 / 10 / 9.
+int finish_threads(int cols, int N, int Nc) {
+  if (Nc < 768) return 256;
+  const long long pieces = (long long)cols * N / Nc;
+  return pieces <= 256 ? 64 : pieces <= 512 ? 128 : 256;
 }
 
 constexpr int KB_KEYS_MAX = 2;  // key blocks of 16 per wavefront in the dK/dV kernels (1 at head_dim 128: registers)
@@ -645,7 +656,8 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     ProfScope ps(PROF_BWD_FINISH, s);
     const FinishArgs f{v.perm, v.cmp_start, v.cmp_slc, v.slc_start, w.sel.chunk_start, w.sel.part_row_start, v.Nc, v.Ns, Hkv, D, w.q_splits,
                        w.dKs, w.dVs, w.pK, w.pV, w.dKc, w.dVc, (bf16_t *)dk, (bf16_t *)dv, w.dKc_out, w.dVc_out};
-    m_bwd_finish<<<v.Nc, 256, 0, s>>>(f);
+    const int nt = finish_threads(row / 4, N, v.Nc);
+    (nt == 64 ? m_bwd_finish<64> : nt == 128 ? m_bwd_finish<128> : m_bwd_finish<256>)<<<v.Nc, nt, 0, s>>>(f);
   }
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }

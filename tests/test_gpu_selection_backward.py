@@ -5,7 +5,9 @@ between the forms.  Tolerances of the other parity tests."""
 import numpy as np
 import pytest
 
-from paper_2505_17412_amd import inputs
+from oracle import compare
+from oracle.ssa_oracle import oracle_for
+from paper_2505_17412_amd import harness, inputs
 from tests.test_gpu_parity import full_parity
 
 pytestmark = pytest.mark.gpu
@@ -50,6 +52,29 @@ def test_blocks_of_many_lengths_in_one_launch(seed, lens, hq, hkv, d, l, topk):
 ])
 def test_dout_rows_that_fill_the_lds(seed, hq, hkv, d):
     full_parity(inputs.make_sequence_workload(seed, (19, 5), hq=hq, hkv=hkv, d=d, l=(2, 4, 8), topk=2))
+
+
+@pytest.mark.parametrize("seed,lens,hq,hkv,d,l,topk", [
+    (551, (1534, 2), 8, 8, 64, (2, 4, 8), 2),      # 768 blocks of 2 tokens, rows of 512: one wavefront, two passes over the columns
+    (552, (3071, 1), 2, 1, 32, (4, 8, 16), 2),     # 769 of 4, one of them of one token, rows of 32: eight groups of threads in one wavefront
+    (553, (3200,), 12, 6, 32, (4, 8, 16), 3),      # rows of 192 (48 pieces): a group of threads, the rest idle
+    (554, (6144, 6145), 4, 2, 64, (16, 32, 64), 2),  # 769 of 16, rows of 128: two wavefronts
+    (555, (3068,), 12, 6, 32, (4, 8, 16), 3),      # 767: four
+])
+def test_finish_by_one_to_four_wavefronts(seed, lens, hq, hkv, d, l, topk):
+    """dK and dV for the sets the forward selected: with one or two heads per KV head and pooled keys of two to four tokens, the rounding of
+    these keys moves a score by more than the margin check_topk leaves."""
+    wl = inputs.make_sequence_workload(seed, lens, hq=hq, hkv=hkv, d=d, l=l, topk=topk)
+    queries = np.arange(0, wl.n_tokens, 61, dtype=np.int32) if wl.n_tokens > 10000 else None
+    dout = wl.dout.copy()
+    if queries is not None:
+        dout[np.setdiff1d(np.arange(wl.n_tokens), queries)] = 0
+    g = harness.run_gpu(wl, dout=dout)
+    orc = oracle_for(wl)
+    ref = orc.forward(wl.q, wl.k, wl.v, wl.gates, topk_idx=g.topk_idx, queries=queries)
+    rb = orc.backward(wl.q, wl.k, wl.v, wl.gates, dout, g.topk_idx, out_branch=ref.out_branch, queries=queries)
+    compare.assert_close(g.dk, rb.dk, wl.dtype, "dk")
+    compare.assert_close(g.dv, rb.dv, wl.dtype, "dv")
 
 
 def test_one_long_block_among_many_short_ones():
