@@ -15,6 +15,7 @@
 #include "mfma_common.h"
 #include "gate_device.h"
 #include "linear_internal.h"
+#include "lin_form.h"
 #include "mfma_qc.h"
 #include "profile.h"
 
@@ -179,7 +180,6 @@ __global__ __launch_bounds__(64 * WF * WT) void lin_nt(LinSrc src, LinDst dst, i
 // tokens 1024 -> 1280 140 us for 130, 30k 2048 -> 2048 250 for 235; the pieces of two chunks in registers: no better).
 // Against 128 x 128: 46k tokens 1024 -> 1280 152 -> 130 us, 30k 2048 -> 2048 290 -> 235 (1070 TFLOP/s; a large library product on this
 // card 1140), 62k 1024 -> 1024 157 -> 143, 10.7k 1024 -> 1280 41.8 -> 36.8; a layer's training step of 46k 7170 -> 7090.
-constexpr int WIDE = 256;
 constexpr size_t LIN_WIDE_LDS = (size_t)2 * 2 * WIDE * LIN_KC * sizeof(bf16_t);  // two stages of weights and tokens
 template <bool ONE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lin_nt_wide(LinSrc src, LinDst dst, int M, GateJob gate) {
@@ -634,13 +634,6 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
 
 namespace {
 
-// Whether the tiles are of 256 x 256: where the useful part of their rounds, of 256 tiles each, is three quarters or more.  Tiles of 128 / of
-// 256, us: 21k tokens 256 -> 1024 (0.64 of two rounds) 25.0 / 29.5, 12k 1024 -> 1024 (0.73 of one) 36.0 / 37.9, 24k (0.73 of two) 64.7 / 68.4,
-// 9k 1024 -> 1408 (0.75) 44.5 / 40.8, 12.8k 1024 -> 1024 (0.78) 42.6 / 37.7, 26k (0.79 of two) 71.3 / 68.1, 16k 512 -> 1024 (0.98) 26.4 / 24.3.
-bool lin_wide(int M, int F) {
-  const long long tiles = (long long)((M + WIDE - 1) / WIDE) * ((F + WIDE - 1) / WIDE), rounds = (tiles + 255) / 256;
-  return 4ll * M * F >= 3 * rounds * 256 * WIDE * WIDE;
-}
 template <bool ONE>
 int launch_nt(const LinSrc &src, const LinDst &dst, int M, GateJob gate, hipStream_t s) {
   const int F = dst.O[0] + dst.O[1] + dst.O[2];
@@ -651,7 +644,7 @@ int launch_nt(const LinSrc &src, const LinDst &dst, int M, GateJob gate, hipStre
     kernel<<<grid + (unsigned)((gate.N + gate_tokens - 1) / gate_tokens), threads, lds, s>>>(src, dst, M, gate);
     return SSA_OK;
   };
-  if (lin_wide(M, F)) {
+  if (lin_wide(M, F, src.K[0] + src.K[1] + src.K[2])) {
     static const hipError_t attr = hipFuncSetAttribute((const void *)lin_nt_wide<ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LIN_WIDE_LDS);
     if (attr != hipSuccess) return SSA_ERR_HIP;
     return launch(lin_nt_wide<ONE>, WIDE, WIDE, 512, LIN_WIDE_LDS);

@@ -27,8 +27,11 @@ def test_convolution_with_few_offsets(seed, n):
 
 
 @pytest.mark.parametrize("seed,n,hq,hkv,d,dm", [
-    (82, 12400, 16, 2, 64, 1024),   # three projections, gates beside them; the data gradient over three contractions
-    (83, 32768, 1, 1, 128, 256),    # 384 features, the last tile half; gates alone (J = 3)
+    (82, 12400, 16, 2, 64, 1024),   # the data gradient over three contractions; q, k, v would take a second round and stay in tiles of 128
+    (83, 32768, 1, 1, 128, 256),    # too short a contraction for them; gates alone (J = 3)
+    (84, 12288, 16, 2, 64, 1024),   # three projections, 48 gates beside them
+    (85, 12225, 8, 1, 128, 1024),   # 24 gates, the last of their workgroups with one token in its first half and none in its second
+    (86, 32768, 1, 1, 128, 768),    # 384 features, the last tile half
 ])
 def test_projections_in_wide_tiles(seed, n, hq, hkv, d, dm):
     """A layer's q, k, v and gates against float32 products of the same bf16 numbers, and its dx against those of what the library's attention

@@ -10,6 +10,17 @@ from tests import util
 pytestmark = pytest.mark.gpu
 
 
+#: either side of the line to tiles of 256 x 256 (csrc/lin_form.h); the last field: whether y is computed in them
+WIDE_CASES = [
+    (86, 12287, 768, 1024, True, False),   # they would be used to less than three quarters
+    (87, 12289, 768, 1024, True, True),    # more: the last tile of one token
+    (88, 12288, 768, 1280, False, True),   # every XCD has 30 tiles
+    (89, 12289, 768, 1280, False, False),  # one 35 of them, a second round
+    (90, 8937, 768, 1408, True, True),     # the last tile of half its features
+    (91, 14746, 256, 1024, True, True),    # the fewest chunks
+]
+
+
 @pytest.mark.parametrize("seed,n,d_in,d_out,bias", [
     (71, 1000, 256, 128, True),      # ragged token tail, one feature tile
     (72, 333, 128, 384, False),      # a single contraction chunk pair, three feature tiles
@@ -19,13 +30,14 @@ pytestmark = pytest.mark.gpu
     (76, 128, 384, 256, True),       # exactly one token tile
     (77, 62229, 1024, 1024, True),   # the shapes bench.py --linear times
     (78, 62229, 1024, 128, True),
-    (79, 12287, 128, 1024, True),    # 256 x 256 tiles would be used to less than three quarters
-    (80, 12289, 128, 1024, True),    # more: the last tile of one token, the fewest chunks
-    (81, 8937, 256, 1408, False),    # the last tile half features
+    (79, 12287, 128, 1024, True),    # a short contraction over many tokens
+    (80, 12289, 128, 1024, True),
+    (81, 8937, 256, 1408, False),
     (82, 6143, 1024, 1024, False),   # the weight gradient by 128 x 128
     (83, 6144, 1024, 1024, True),    # and by 256 x 256, 384 tokens a split
     (84, 8065, 640, 1024, False),    # a tile of half its inputs, a split of one token
     (85, 3841, 1024, 1408, True),    # a tile of half its outputs
+    *(case[:-1] for case in WIDE_CASES),
 ])
 def test_linear_forward_backward(seed, n, d_in, d_out, bias):
     import torch

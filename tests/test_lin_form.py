@@ -1,0 +1,49 @@
+"""CPU: the rules that pick the projections' tiles (csrc/lin_form.h), compiled with g++: the form that was the faster where both were
+measured, and the cases of the GPU tests run the form they name."""
+import os
+import subprocess
+
+from tests.test_gpu_linear import WIDE_CASES
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r"""
+#include "lin_form.h"
+#include <cstdio>
+#include <cstdlib>
+int main(int argc, char **argv) {
+  for (int i = 1; i + 2 < argc; i += 3) printf("%d\n", (int)lin_wide(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2])));
+  return 0;
+}
+"""
+#: tokens, features, contraction, time in tiles of 128 over time in tiles of 256
+MEASURED = [
+    (12800, 1280, 1024, 0.85), (10655, 1408, 1024, 0.73), (10655, 1408, 2048, 0.78), (12800, 1280, 128, 0.81), (20000, 1024, 1024, 0.88),
+    (32768, 640, 1024, 0.91), (12800, 1024, 1024, 1.13), (10655, 1280, 1024, 1.15), (32768, 1280, 1024, 1.15), (45904, 1280, 1024, 1.22),
+    (45904, 1024, 1024, 1.10), (20000, 1408, 512, 0.97), (24576, 1024, 512, 0.97), (45904, 1280, 512, 1.12), (16384, 1024, 256, 1.15),
+    (24576, 1024, 256, 0.94), (12800, 1024, 256, 1.11), (10655, 1280, 512, 1.15), (20000, 640, 256, 1.08), (32768, 384, 512, 0.96), (32768, 384, 256, 0.98),
+    (100000, 1408, 128, 1.14), (150000, 1280, 128, 1.17), (150000, 1024, 128, 1.10), (62229, 2048, 128, 0.96), (62229, 1280, 256, 1.11), (24576, 1024, 128, 0.86), (24576, 2048, 128, 0.95), (20000, 2048, 128, 0.90),
+]
+
+
+def forms(tmp_path, sizes):
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text(PROGRAM)
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover",
+                           "-I" + os.path.join(ROOT, "paper_2505_17412_amd", "csrc"), "-o", str(exe), str(src)])
+    args = [str(x) for s in sizes for x in s]
+    out = subprocess.run([str(exe), *args], capture_output=True, text=True, timeout=60, check=True).stdout
+    return [line == "1" for line in out.split()]
+
+
+def test_wide_tiles_where_they_are_faster(tmp_path):
+    for (m, f, k, ratio), wide in zip(MEASURED, forms(tmp_path, [s[:3] for s in MEASURED])):
+        assert wide == (ratio > 1), (m, f, k, ratio)
+
+
+def test_cases_of_the_gpu_test(tmp_path):
+    sizes = [(n, d_out, d_in) for _, n, d_in, d_out, _, _ in WIDE_CASES]
+    assert forms(tmp_path, sizes) == [wide for *_, wide in WIDE_CASES]
+    # a layer's query, key and value projections, and their data gradient, in test_projections_in_wide_tiles
+    assert forms(tmp_path, [(12400, 1280, 1024), (12400, 1024, 1280), (12288, 1280, 1024), (12225, 1280, 1024), (32768, 384, 768)]) == [False] + 4 * [True]
+    largest = 2 ** 31 - 1  # tokens x the larger dimension stay below 2^31
+    assert all(isinstance(w, bool) for w in forms(tmp_path, [(0, 128, 128), (1, 128, 128), (largest // 128, 128, 128), (largest // 16384, 16384, 16384)]))
