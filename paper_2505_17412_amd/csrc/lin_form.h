@@ -21,3 +21,26 @@ inline bool lin_wide(int M, int F, int K) {
   const int percent = K >= 768 ? 75 : rounds == 1 && K >= 256 ? 76 : K >= 384 ? 85 : K >= 256 ? 90 : rounds >= 9 ? 80 : 101;
   return 100ll * M * F >= percent * rounds * 256 * WIDE * WIDE;
 }
+
+// Splits of the token range in which the weight gradient dY^T X (d_in inputs, F outputs) runs in tiles of 256 x 256, one round of them, or 0: in
+// tiles of 128, `narrow` workgroups of them, three to a compute unit.  From how many tokens a split on wide tiles win depends on what they
+// are against (speed of tiles of 256 over that of 128, by tokens a split, four runs of either in turn):
+//   384   rounds of tiles of 128 that end with most units idle: 1024 -> 1280 384 1.08, 800 1.21; 1408 -> 1280 384 1.20; 4096 -> 1280 384 1.02
+//   384   full rounds, an odd number of tiles of 128 along the inputs, so that every XCD reads all of X: 640 -> 1024 384 1.28, 768 1.42;
+//         1408 -> 256 300 0.97, 384 1.06, 768 1.43; with a useful part of 0.75 in 32 splits 384 -> 1024 384 1.09, 640 1.19, but 384 -> 2048 450 0.94
+//   512   full rounds, few outputs and inputs, and with them small partial sums: 1024 -> 256 300 0.92, 450 1.02, 520 1.05; 256 -> 1280 450 1.00, 640 1.04
+//   704   other full rounds: 1024 -> 1024 384 0.97, 640 1.01, 768 1.05, 1500 1.17; 2048 -> 256 384 0.92, 640 0.95, 768 0.98, 1024 1.00; 2048 -> 2048 384 0.90, 640
+//         0.97, 768 1.00, 1024 1.06; 1024 -> 2048 384 0.97, 640 1.06; with a useful part of 0.75 384 -> 2048 640 1.00, 384 -> 4096 768 0.98, 1024 1.01
+// A tile's idle half costs more among the outputs: useful part 0.75, full rounds, 1024 -> 384 640 0.92, 1500 0.96.
+constexpr int LIN_TN_ROUND = 768;
+inline int lin_tn_splits(int M, int d_in, int F, long long narrow) {
+  const int tiles = (F + WIDE - 1) / WIDE * ((d_in + WIDE - 1) / WIDE), s = tiles < 4 ? 64 : 256 / tiles;
+  const long long useful = (long long)F * d_in * s, whole = 256ll * WIDE * WIDE;  // of the round
+  if (s < 1 || 4 * useful < 3 * whole) return 0;
+  const long long narrow_rounds = (narrow + LIN_TN_ROUND - 1) / LIN_TN_ROUND;
+  const bool full = 10 * useful * narrow_rounds * LIN_TN_ROUND < 12 * whole * narrow, mostly = 10 * useful >= 8 * whole;
+  if (full && !mostly && F % WIDE) return 0;
+  const bool scattered = d_in / 128 % 2 && (mostly || s >= 32);
+  const long long line = !full || scattered ? 384 : s > 50 ? 512 : 704;
+  return M >= line * s ? s : 0;
+}

@@ -593,16 +593,6 @@ __global__ __launch_bounds__(256) void lin_colsum_finish(LinGrad<NP> a, int n_pa
   }
 }
 
-// Splits of the token range with tiles of 256 x 256: one round, or 0 where the useful part of it is less than three quarters or a split
-// would have fewer than 384 tokens (1024 -> 1024, 312 tokens a split: 38.0 us, 41.3 in large tiles; 666: 53, 52; 640 -> 1024, 428: 43, 38).
-int lin_tn_splits(int M, int d_in, int F) {
-  const int tiles = (F + WIDE - 1) / WIDE * ((d_in + WIDE - 1) / WIDE);
-  int s = 256 / tiles;
-  if (s > 64) s = 64;
-  if (s < 1 || M < 384 * s) return 0;
-  return 4ll * F * d_in * s >= 3ll * 256 * WIDE * WIDE ? s : 0;
-}
-
 struct LinPlan {
   int splits, tok_per_split, bias_parts;
   size_t wt, part, bpart, total;
@@ -612,7 +602,7 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
   LinPlan p{};
   const int tiles = (d_out / 128) * (d_in / 128);
   // three workgroups per compute unit; two for skinny outputs, where the traffic of the partial tiles weighs more
-  int s = ((tiles >= 16 ? 768 : 512) + tiles - 1) / tiles;
+  int s = ((tiles >= 16 ? LIN_TN_ROUND : 512) + tiles - 1) / tiles;
   const int max_s = (M + 255) / 256;   // at least 256 tokens per split
   if (s > max_s) s = max_s;
   if (s < 1) s = 1;
@@ -621,7 +611,7 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
   p.splits = M > 0 ? (M + p.tok_per_split - 1) / p.tok_per_split : 1;
   size_t off = 0;
   p.wt = off; off += align_up((size_t)d_in * d_out * sizeof(bf16_t), 256);
-  const int wide = lin_tn_splits(M, d_in, d_out), most = p.splits > wide ? p.splits : wide;
+  const int wide = lin_tn_splits(M, d_in, d_out, tiles * p.splits), most = p.splits > wide ? p.splits : wide;
   p.part = off; off += align_up((size_t)most * d_in * d_out * sizeof(float), 256);
   p.bias_parts = M > 0 ? (M + COLSUM_CHUNK - 1) / COLSUM_CHUNK : 1;
   p.bpart = off; off += align_up((size_t)p.bias_parts * d_out * sizeof(float), 256);
@@ -751,11 +741,11 @@ static void weight_grads(int M, int d_in, const int *d_out, const void *x, const
   }
   int F = 0, fits = 1 << 30;
   for (int i = 0; i < NP; ++i) {
-    const int most = lin_tn_splits(M, d_in, d_out[i]);
+    const int most = lin_tn_splits(M, d_in, d_out[i], d_out[i] / 128 * (d_in / 128) * a.splits[i]);
     F += d_out[i];
     fits = min(fits, most > a.splits[i] ? most : a.splits[i]);
   }
-  const int wide = lin_tn_splits(M, d_in, F);
+  const int wide = lin_tn_splits(M, d_in, F, grid);
   if (wide && wide <= fits) {
     static const hipError_t attr = hipFuncSetAttribute((const void *)lin_tn_wide<NP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LIN_WIDE_LDS);
     (void)attr;  // (a launch beyond the limit is refused, and that error reported)

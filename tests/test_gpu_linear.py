@@ -17,7 +17,17 @@ WIDE_CASES = [
     (88, 12288, 768, 1280, False, True),   # every XCD has 30 tiles
     (89, 12289, 768, 1280, False, False),  # one 35 of them, a second round
     (90, 8937, 768, 1408, True, True),     # the last tile of half its features
-    (91, 14746, 256, 1024, True, True),    # the fewest chunks
+    (91, 14746, 256, 1024, True, True),    # four chunks
+    (92, 131073, 128, 1024, True, True),   # the fewest, in nine rounds
+]
+#: weight gradients on either side of the line to tiles of 256 x 256 (csrc/lin_form.h): tokens, inputs, outputs, workgroups in tiles of 128 x 128,
+#: whether it is computed in them
+WEIGHT_GRADIENT_CASES = [
+    (11263, 1024, 1024, 768, False),  # rounds of tiles of 128 that are full: 704 tokens a split
+    (11264, 1024, 1024, 768, True),
+    (8063, 640, 1024, 800, False),    # one that is half empty behind a full one: 384
+    (8065, 640, 1024, 800, True),     # a tile of half its inputs, a split of one token
+    (3841, 1024, 1408, 792, True),    # a tile of half its outputs
 ]
 
 
@@ -33,11 +43,12 @@ WIDE_CASES = [
     (79, 12287, 128, 1024, True),    # a short contraction over many tokens
     (80, 12289, 128, 1024, True),
     (81, 8937, 256, 1408, False),
-    (82, 6143, 1024, 1024, False),   # the weight gradient by 128 x 128
-    (83, 6144, 1024, 1024, True),    # and by 256 x 256, 384 tokens a split
-    (84, 8065, 640, 1024, False),    # a tile of half its inputs, a split of one token
-    (85, 3841, 1024, 1408, True),    # a tile of half its outputs
+    (82, 6143, 1024, 1024, False),
+    (83, 6144, 1024, 1024, True),
+    (84, 8065, 640, 1024, False),
+    (85, 3841, 1024, 1408, True),
     *(case[:-1] for case in WIDE_CASES),
+    *((93 + i, *case[:3], True) for i, case in enumerate(WEIGHT_GRADIENT_CASES[:3])),
 ])
 def test_linear_forward_backward(seed, n, d_in, d_out, bias):
     import torch
