@@ -14,6 +14,7 @@
 #include "mfma_common.h"
 #include "mfma_qc.h"
 #include "gate_device.h"
+#include "gate_form.h"
 #include "profile.h"
 
 #include <mutex>
@@ -60,10 +61,13 @@ __global__ __launch_bounds__(256) void g_fwd(GateJob a, const bf16_t *__restrict
         acc[1][nb] = mfma16(av[1][u], bv, acc[1][nb]);
       }
   }
+  float bias[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) bias[nb] = gate_bias(a, nb);
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) gate_store(a, t0 + 16 * h, nb, acc[h][nb]);
+    for (int h = 0; h < 2; ++h) gate_store(a, t0 + 16 * h, nb, acc[h][nb], bias[nb]);
 }
 template <int NB, bool WT>
 __global__ __launch_bounds__(256) void g_fwd_split(GateJob a, const bf16_t *__restrict__ wt) {
@@ -269,47 +273,31 @@ extern "C" size_t ssa_gate_workspace_bytes(const ssa_params_t *p, int32_t d_mode
   return gate_plan(p->n_tokens, d_model, J, for_backward != 0).total + 256;
 }
 
-// Whether, with a transposed copy of the weights, the four wavefronts of a workgroup split the contraction: where a wavefront per 32 tokens leaves the chip half empty, at
-// 49152 tokens and below.  Beyond, such wavefronts run in rounds of one per SIMD (32768 tokens), and a split, whose time grows with the
-// tokens alone, wins where the last round is not nearly full.  With up to 32 gate columns a split is never behind but for a d_model of
-// 128, a single trip, in the smallest.  Whole / split, us, 1024 features, 48 columns: 20k tokens 27 / 20, 49k 43 / 34, 62k (95 % of two
-// rounds) 44 / 47, 80k (81 % of three) 60 / 55, 100k (76 %) 78 / 66, 150k (92 %) 99 / 109, 250k (95 %) 155 / 181; 24 columns: 62k 37 / 34, 150k 85
-// / 82; 128 features, 12 columns: 62k 9.5 / 9.9, 150k 12.6 / 13.3.
-static bool gate_split(int N, int d_model, int NB) {
-  const long long round = 32768, full = (N + round - 1) / round * round;
-  if (NB == 1 && d_model == 128) return false;
-  return NB <= 2 || N <= 49152 || 100ll * N < 89 * full;
-}
-
-// Weights whose rows are whole 16-byte pieces (of the gate counts that are multiples of 3 up to 64: 24 and 48) are read as they are, by the
-// split form at every size; else a transposed copy comes first.  With a copy and as the rule above / as they are, us, 1024 features, 48
-// columns: 5.5k tokens 11.3 / 7.1, 20k 19.1 / 14.8, 46k 33.6 / 24.2; 24 columns 10.0 / 7.4, 15.5 / 10.0, 26.2 / 18.7; whole / split as they are
-// 62k 43.5 / 31.4, 150k 100 / 97, 250k 158 / 156.  In a layer they run beside the projections of the same rows (lin_nt): 5.5k tokens
-// 190.8 -> 185.7 us, a training step of 10.7k 1511 -> 1503, of 46k 7156 -> 7132.
-static bool gate_as_is(int J) { return J % 8 == 0; }
-
 // Forward launches with the transposed weight copy, where one is taken, in `wt` (device, ((J+15)/16*16) * d_model bf16).
 static int gate_forward_launch(int N, int d_model, int J, const void *x, const void *w, const void *bias, void *gates,
                                bf16_t *wt, hipStream_t s) {
   const int NB = (J + 15) / 16, JR = 16 * NB;
   ProfScope ps(PROF_GATE_FWD, s);
   const GateJob a{(const bf16_t *)x, (const bf16_t *)w, (const bf16_t *)bias, N, d_model, J, (bf16_t *)gates, 0};
-  const bool as_is = gate_as_is(J), split = as_is || gate_split(N, d_model, NB);
+  const bool as_is = gate_as_is(N, d_model, J), split = gate_split(N, d_model, NB);
   if (!as_is) g_prep_w<<<(unsigned)(((size_t)JR * d_model + 255) / 256), 256, 0, s>>>(a.w, d_model, J, JR, wt);
   const auto run = [&](auto kernel, int tokens) { kernel<<<(unsigned)((N + tokens - 1) / tokens), 256, 0, s>>>(a, wt); };
   switch (NB) {
     case 1: split ? run(g_fwd_split<1, true>, 32) : run(g_fwd<1>, 128); break;
-    case 2: as_is ? run(g_fwd_split<2, false>, 32) : split ? run(g_fwd_split<2, true>, 32) : run(g_fwd<2>, 128); break;
+    case 2: as_is ? run(g_fwd_split<2, false>, 32) : run(g_fwd_split<2, true>, 32); break;  // (split at every size)
     case 3: as_is ? run(g_fwd_split<3, false>, 32) : split ? run(g_fwd_split<3, true>, 32) : run(g_fwd<3>, 128); break;
     default: split ? run(g_fwd_split<4, true>, 32) : run(g_fwd<4>, 128); break;
   }
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
+// In a layer they run beside the projections of the same rows (lin_nt), at every size: 5.5k tokens 190.8 -> 185.7 us, a training step of 10.7k
+// 1511 -> 1503, of 46k 7156 -> 7132; projections and gates, apart / beside: 98k tokens, 24 columns, 128 features 113 / 106, 256 143 / 137, 1024 383 / 364; 131k, 48
+// columns 207 / 215, 277 / 279, 759 / 748.
 bool gate_beside(const ssa_params_t *p, int d_model, const void *x, const void *w, const void *bias, void *gates, GateJob *out) {
   int J;
   if (gate_check(p, d_model, &J) != SSA_OK || !x || !w || !bias || !gates || !aligned16(x, w, bias, gates)) return false;
-  if (!gate_as_is(J)) return false;
+  if (!gate_whole_pieces(J)) return false;
   *out = GateJob{(const bf16_t *)x, (const bf16_t *)w, (const bf16_t *)bias, p->n_tokens, d_model, J, (bf16_t *)gates, 0};
   return true;
 }

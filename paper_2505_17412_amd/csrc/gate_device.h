@@ -15,11 +15,12 @@ struct GateJob {
   __host__ __device__ int blocks() const { return (J + 15) / 16; }
 };
 
-// gates[tok][j] = sigmoid(z + b[j]); C layout: lane holds gate column 16*nb + n of tokens t0 + 4*quad + i
-__device__ inline void gate_store(const GateJob &a, int t0, int nb, const f32x4 &z) {
+// The lane's bias of column block nb, for before the first store: behind one the load waits for it.
+__device__ inline float gate_bias(const GateJob &a, int nb) { return bf16_to_f32(a.bias[min(16 * nb + (int)(threadIdx.x & 15), a.J - 1)]); }
+// gates[tok][j] = sigmoid(z + b); C layout: lane holds gate column 16*nb + n of tokens t0 + 4*quad + i
+__device__ inline void gate_store(const GateJob &a, int t0, int nb, const f32x4 &z, float b) {
   const int n = threadIdx.x & 15, quad = threadIdx.x >> 4 & 3, j = 16 * nb + n;
   if (j >= a.J) return;
-  const float b = bf16_to_f32(a.bias[j]);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int t = t0 + 4 * quad + i;
@@ -94,7 +95,7 @@ __device__ __forceinline__ void gate_split_tile(const GateJob &a, const bf16_t *
     f32x4 p[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) p[w] = part[(w * 2 * NB + it) * 64 + lane];
-    gate_store(a, t0 + 16 * (it / NB), it % NB, ((p[0] + p[1]) + p[2]) + p[3]);
+    gate_store(a, t0 + 16 * (it / NB), it % NB, ((p[0] + p[1]) + p[2]) + p[3], gate_bias(a, it % NB));
   }
 }
 

@@ -13,8 +13,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("seed,n,hq,dm", [
     (71, 31, 16, 384), (72, 33, 5, 640), (73, 64, 21, 128),
-    (76, 49152, 11, 128), (77, 49153, 16, 128), (78, 60001, 21, 256),   # the last split, whole contractions in two rounds, four column blocks
-    (79, 66000, 16, 128), (80, 129, 5, 128),                            # split again: the third round is nearly empty; whole with one block
+    (76, 49152, 11, 128), (77, 49153, 16, 128), (78, 60001, 21, 256),   # the last split, a copy of 48 columns, whole contractions of four blocks
+    (79, 66000, 16, 128), (80, 129, 5, 128),                            # split: the third round is nearly empty; whole with one block
+    (81, 49152, 16, 128), (82, 114689, 8, 128), (83, 62229, 16, 128),   # 48 columns as they are; a copy of 24; of 48, whole contractions
 ])
 def test_gate_splits(seed, n, hq, dm):
     test_gpu_gate.test_gate_forward_backward(seed, n, hq, dm)
