@@ -188,7 +188,7 @@ BwdPlan bwd_plan(const ssa_ctx &c) {
   // slc_tok_max * entries/chunk_len + N*Hkv.  A chunk is one workgroup; the two-kernel form measured best at 1024.
   // chunk_len grows until the partial sums fit in about 1 GiB.
   const size_t entries = (size_t)c.N * c.Hkv * c.T;
-  p.chunk_len = slc_bwd_two_kernels(b, c.d, c.Hkv, c.T) ? 1024 : one_pass_chunk_len(b->slc_tok_max, (long long)entries);
+  p.chunk_len = slc_bwd_two_kernels(b, c.d, c.Hkv, c.T) ? 1024 : one_pass_chunk_len(b->slc_tok_max, (long long)entries, c.hs);
   size_t rows;
   for (;;) {
     rows = (size_t)b->slc_tok_max * (entries / p.chunk_len + 1) + (size_t)c.N * c.Hkv;

@@ -37,17 +37,27 @@ inline SelOrder sel_order(int n_tokens, int kv_heads) {
   return o;
 }
 
-// Query tokens per work chunk of the one-pass selection backward, for lists of `entries` tokens in all and blocks of up to `longest` keys.
-// Long chunks write fewer partial dK and dV rows; a compute unit wants two chunks of eight wavefronts or, where no block has more
-// than 128 keys, eight of four, so that the last ones to end leave few of them idle.  us of the kernel, the index, the launches beside it, the sums
-// of the partial rows and the finish, chunks of 128 / 256 / 512.  Blocks of up to 128 keys, by entries: 64k 220 / 229 / 268, 256k 432 / 448 / 496,
-// 544k 955 / 945 / 969, 640k 951 / 947 / 953, 1.3M 2182 / 2113 / 2129, 2.2M 4823 / 4713 / 4700; heads of 32 256k 437 / 464 / 490, 640k 1003 / 1017
-// / 1051, 2.2M 5358 / 5271 / 5331.  Longer ones: 96k 264 / 258 / 293, 128k 367 / 383 / 470, 170k 546 / 509 / 561 and 561 / 507 / 541, 256k 635 / 662 /
-// 704, 341k in three shapes 827 / 803 / 790, 384k 1242 / 1055 / 976, 640k 2308 / 2198 / 2203.  (1024 was slower.)
+// Query tokens per work chunk of the one-pass selection backward, for lists of `entries` tokens in all, blocks of up to `longest` keys and `heads`
+// query heads per KV head.  Long chunks write fewer partial dK and dV rows and pay less for the keys they begin with, in a block of
+// more than 256 keys once per segment of 256; short ones leave fewer compute units idle at the end.  So there is a number of chunks
+// wanted: of four wavefronts and a few rows, some 2000; of eight, some 500; of segments, 180 of 256 tokens and twice as many of 512; fewer where
+// few heads make few rows of a token.  us of the kernel, the index, the launches beside it, the sums of the partial rows and the finish, chunks
+// of 128 / 256 / 512, by entries.
+//   up to 128 keys, 8 heads  64k 220 / 229 / 268, 256k 432 / 448 / 496, 544k 955 / 945 / 969, 640k 951 / 947 / 953, 1.3M 2182 / 2113 / 2129, 2.2M 4823 / 4713 /
+//                            4700; 16 heads of 32 256k 437 / 464 / 490, 640k 1003 / 1017 / 1051, 2.2M 5358 / 5271 / 5331
+//                   2 heads  16k 65 / 72 / 78, 160k 217 / 209 / 209, 384k 257 / 242 / 234;  1: 64k 96 / 91 / 89, 192k 240 / 224 / 214, 640k 277 / 245 / 220
+//   up to 256 keys, 8 heads  96k 264 / 258 / 293, 128k 367 / 383 / 470, 256k 635 / 662 / 704, 341k in three shapes 827 / 803 / 790, 640k 1517 / 1448 / 1478
+//                   4 heads  40k 163 / 152 / 185, 96k 295 / 277 / 265, 480k 1392 / 1314 / 1284;  1: 32k 99 / 89 / 95, 80k 137 / 128 / 119, 480k 746 / 636 / 572
+//   longer,         8 heads  40k 248 / 302 / 443, 53k (1618 keys) 1744 / 1422 / 1837, 64k 425 / 404 / 533, 137k 488 / 447 / 549, 170k 546 / 509 / 561, 224k 806 / 748 / 722,
+//                            384k 1242 / 1055 / 976;  1: 16k 196 / 175 / 190, 32k 462 / 320 / 310, 53k 1500 / 892 / 635
 constexpr int DKV_CHUNK_MIN = 128;
-inline int one_pass_chunk_len(int longest, long long entries) {
-  const int wanted = longest > 128 ? 560 : 2048;
+inline int one_pass_chunk_len(int longest, long long entries, int heads) {
+  auto wanted = [&](int len) {
+    if (longest <= 128) return 256 * (heads < 8 ? heads : 8);
+    if (longest <= 256) return heads < 8 ? 150 : 560;
+    return len / 256 * 45 * (heads < 4 ? heads : 4);
+  };
   int len = 512;
-  while (len > DKV_CHUNK_MIN && entries / len < wanted) len /= 2;
+  while (len > DKV_CHUNK_MIN && entries / len < wanted(len)) len /= 2;
   return len;
 }

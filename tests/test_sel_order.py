@@ -25,18 +25,21 @@ int main() {
         return 1;
       }
     }
-  const struct { int longest, entries, fast, also; } measured[] = {
-      {64, 64000, 128, 128}, {64, 256000, 128, 128}, {112, 544000, 256, 128}, {32, 640000, 256, 128}, {64, 1280000, 256, 512}, {64, 2240000, 512, 256},
-      {156, 96000, 256, 128}, {213, 128000, 128, 128}, {290, 170480, 256, 256}, {276, 170480, 256, 256}, {192, 256000, 128, 256}, {241, 340960, 512, 256},
-      {290, 384000, 512, 512}, {285, 640000, 256, 512}};
+  const struct { int longest, entries, heads, fast, also; } measured[] = {
+      {64, 64000, 8, 128, 128}, {64, 256000, 8, 128, 128}, {112, 544000, 8, 256, 128}, {32, 640000, 8, 256, 128}, {64, 1280000, 8, 256, 512}, {64, 2240000, 8, 512, 256},
+      {32, 640000, 16, 128, 256}, {64, 16000, 2, 128, 128}, {64, 160000, 2, 256, 512}, {64, 384000, 2, 512, 512}, {64, 640000, 1, 512, 512}, {64, 160000, 1, 256, 512},
+      {156, 96000, 8, 256, 128}, {213, 128000, 8, 128, 128}, {192, 256000, 8, 128, 256}, {241, 340960, 8, 512, 256}, {192, 96000, 4, 512, 256}, {192, 480000, 4, 512, 256},
+      {192, 480000, 1, 512, 512}, {192, 80000, 1, 512, 256}, {316, 40000, 8, 128, 128}, {1618, 53400, 8, 256, 256}, {2765, 50000, 16, 256, 256}, {365, 64000, 8, 256, 256},
+      {335, 136592, 8, 256, 256}, {290, 170480, 8, 256, 256}, {314, 224000, 8, 512, 256}, {290, 384000, 8, 512, 512}, {285, 640000, 8, 256, 512}, {1618, 53400, 1, 512, 512},
+      {1004, 32000, 1, 256, 512}, {520, 16000, 1, 256, 256}, {1618, 26700, 8, 128, 256}, {1004, 32000, 16, 128, 128}};
   for (const auto &m : measured) {
-    const int len = one_pass_chunk_len(m.longest, m.entries);
+    const int len = one_pass_chunk_len(m.longest, m.entries, m.heads);
     if (len != m.fast && len != m.also) {
-      printf("blocks of up to %d keys, %d entries: chunks of %d\n", m.longest, m.entries, len);
+      printf("blocks of up to %d keys, %d entries, %d heads: chunks of %d\n", m.longest, m.entries, m.heads, len);
       return 1;
     }
   }
-  return one_pass_chunk_len(1, 0) == DKV_CHUNK_MIN && one_pass_chunk_len(1 << 30, 1ll << 31) == 512 ? 0 : 1;
+  return one_pass_chunk_len(1, 0, 1) == DKV_CHUNK_MIN && one_pass_chunk_len(1 << 30, 1ll << 31, 16) == 512 ? 0 : 1;
 }
 """
 
