@@ -85,7 +85,8 @@ def _imports():
 
 def kernel_times(wl, steps):
     """Average HIP-event time per kernel (ms) over `steps` forward+backward passes; also returns what the work count
-    needs: the handle's arrays and the selected sets."""
+    needs: the handle's arrays and the selected sets.  (In small problems the backward's selection index runs beside its pre-pass and dQ
+    kernel: there is no bwd_invert_selection then, or only what is left of it, and its time is in theirs.)"""
     torch, _, ssa, util = _imports()
     n, hq, hkv, T = wl.n_tokens, wl.n_heads_q, wl.n_heads_kv, wl.topk
     p, blk = util.build_blocks_gpu(wl)
@@ -116,9 +117,14 @@ def kernel_times(wl, steps):
     return {nm: tot / cnt for nm, (tot, cnt) in prof.items()}, arrays, sel
 
 
+#: what the backward times of single branches are: two launches serve two branches each
+ATTRIBUTION = "dQ and dK/dV of the compression and window branches share a launch each: split by pair counts, the selection branch's chunk sums, which run in the second, included"
+
+
 def dense_bwd_ms(kd, pairs):
-    """Delta, and the window share of the dQ and dK/dV kernels that handle the compression and window branches (split by their pair
-    counts): in the dense stand-in the window is the whole item, the compression branch a few per cent of it."""
+    """Delta, and the window's share of the launches it has in common with the compression branch (dQ; dK/dV, with the sums of the selection
+    branch's chunks), by pair counts.  In the dense stand-in the window is the whole item, the compression branch a few per cent of it, and
+    the sums, one row per token and block of its one selected block, less: an attribution that charges them to the dense side."""
     both = kd["bwd_dq_cmp_win"] + kd["bwd_dkv_cmp_win"]
     return both * pairs["win"] / max(pairs["win"] + pairs["cmp"], 1) + kd["bwd_pre_delta"]
 
@@ -152,7 +158,7 @@ def dense_sweep(args):
         d_bwd = dense_bwd_ms(kd, dense_pairs)
         line = {"sweep": "ssa_vs_dense", "grid": grid, "n_tokens": n, "heads": [sparse.n_heads_q, sparse.n_heads_kv],
                 "head_dim": sparse.head_dim, "ssa_fwd_ms": round(s_fwd, 3), "ssa_bwd_ms": round(s_bwd, 3),
-                "dense_fwd_ms": round(d_fwd, 3), "dense_bwd_ms": round(d_bwd, 3),
+                "dense_fwd_ms": round(d_fwd, 3), "dense_bwd_ms": round(d_bwd, 3), "attribution": ATTRIBUTION,
                 "speedup_fwd": round(d_fwd / s_fwd, 2), "speedup_bwd": round(d_bwd / s_bwd, 2),
                 "speedup_fwd_bwd": round((d_fwd + d_bwd) / (s_fwd + s_bwd), 2),
                 "dense_fwd_tflops": round(4 * sparse.head_dim * n * n * sparse.n_heads_q / (d_fwd * 1e-3) / 1e12, 1)}
@@ -189,7 +195,7 @@ def seq1d_bench(args):
                 "pairs_cmp_slc_win": [pairs["cmp"], pairs["slc"], pairs["win"]],
                 "algorithmic_tflops": round(flops / ((s_fwd + s_bwd) * 1e-3) / 1e12, 1),
                 "frac_of_mfma_peak": round(flops / ((s_fwd + s_bwd) * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4),
-                "dense_fwd_ms": round(d_fwd, 3), "dense_bwd_ms": round(d_bwd, 3),
+                "dense_fwd_ms": round(d_fwd, 3), "dense_bwd_ms": round(d_bwd, 3), "attribution": ATTRIBUTION,
                 "speedup_fwd_bwd": round((d_fwd + d_bwd) / (s_fwd + s_bwd), 2),
                 "kernel_ms": {k_: round(v_, 3) for k_, v_ in ks.items()}}
         print(json.dumps(line), flush=True)
@@ -439,13 +445,13 @@ def ablation_sweep(args):
             n, d = wl.n_tokens, wl.head_dim
             ks, arrays, sel = kernel_times(wl, 2)
             pairs = algorithmic_flops(wl, arrays, sel)
-            # the compression and window branches share a dQ and a dK/dV launch: their time is split by the pair counts
+            # the compression and window branches share a dQ and a dK/dV launch, the latter with the selection branch's sums: see ATTRIBUTION
             bwd_cw = ks["bwd_dq_cmp_win"] + ks["bwd_dkv_cmp_win"]
             f_c = pairs["cmp"] / max(pairs["cmp"] + pairs["win"], 1)
             branch_ms = {
                 "cmp": ks["cmp_fwd_scores_topk"] + bwd_cw * f_c,
                 "slc": ks["slc_fwd"] + ks["fwd_invert_selection"] + ks["slc_merge_combine"] + ks["bwd_dq_slc"] + ks["bwd_dq_merge"]
-                       + ks["bwd_dkv_slc"] + ks["bwd_invert_selection"],
+                       + ks["bwd_dkv_slc"] + ks.get("bwd_invert_selection", 0.0),
                 "win": ks["win_fwd"] + bwd_cw * (1 - f_c),
             }
             other = sum(ks.values()) + ks["prep_sort_pool"] - sum(branch_ms.values())
@@ -454,7 +460,7 @@ def ablation_sweep(args):
             line = {"bench": "stress_ablation", "workload": "g128_thick", "n_tokens": n, "head_dim": d,
                     "heads": [wl.n_heads_q, wl.n_heads_kv], "topk": topk, "m_win": m_win,
                     "fwd_bwd_ms": round(total, 3), "tokens_per_s": round(n / (total * 1e-3)),
-                    "branch_ms": {b: round(v_, 3) for b, v_ in branch_ms.items()}, "other_ms": round(other, 3),
+                    "branch_ms": {b: round(v_, 3) for b, v_ in branch_ms.items()}, "attribution": ATTRIBUTION, "other_ms": round(other, 3),
                     "branch_tflops": {b: round(v_, 1) for b, v_ in tf.items()},
                     "branch_frac_of_mfma_peak": {b: round(v_ / MFMA_BF16_PEAK_TFLOPS, 4) for b, v_ in tf.items()},
                     "whole_step_frac_of_mfma_peak": round(14 * d * sum(pairs[b] for b in branch_ms) / (total * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4),

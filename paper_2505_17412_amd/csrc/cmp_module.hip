@@ -586,6 +586,8 @@ constexpr int PE_GROUPS = 32;  // first-level groups of the ordered dPE sum
 // the module of keys and values, one -> three parts, forward and backward: 1 k tokens 110 and 106 -> 79 and 92 us, 3 k 112 and 111 ->
 // 102 and 106, 10.7 k (tiles of 128) 180 and 163 -> 143 and 149; two parts at 14 k 187 and 172 -> 156 and 163.  Two parts of 64
 // tokens save less of the short chain than the second set of rows costs: 5.5 k 121 and 119 -> 126 and 124, 8 k 127 and 126 -> 133 and 133.
+// The parts are 32-bit rows added in order, another order of the same sum than one chain over the offsets: at 8 sizes of 0.7 to 30 k tokens the
+// 2-norm error of pooled rows and dx (bf16) against 64 bits is the same to 8 digits, that of the PE gradient, a 32-bit sum of dU, 21 to 39 % smaller.
 struct ConvShape { int tok, parts; };
 ConvShape conv_shape(int N, int C, int n) {
   if (C != 128) return {0, 1};

@@ -283,9 +283,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 32
     kbeg = a.v.win_start[blk]; kend = a.v.win_start[blk + 1];
     qbeg = kbeg; qend = kend;
   } else {
-    const int per_split = a.n_cmp / a.q_splits, w = (int)blockIdx.x - a.n_win, x = w % per_split;
+    const int w = (int)blockIdx.x - a.n_win;
     g = blockIdx.y;
-    if (w >= a.n_cmp) return sum_chunks<D, NTHR>(a, g, w - a.n_cmp); split = w / per_split; blk = x / a.cmp_tiles; tile = x % a.cmp_tiles;  // blk = batch item
+    if (w >= a.n_cmp) return sum_chunks<D, NTHR>(a, g, w - a.n_cmp);
+    const int per_split = a.n_cmp / a.q_splits, x = w % per_split;
+    split = w / per_split;
+    blk = x / a.cmp_tiles;  // batch item
+    tile = x % a.cmp_tiles;
     kbeg = a.v.cmp_batch[blk]; kend = a.v.cmp_batch[blk + 1];
     const int q0 = a.v.item_start[blk], q1 = a.v.item_start[blk + 1];
     const int per = (q1 - q0 + a.q_splits - 1) / a.q_splits;

@@ -59,7 +59,7 @@ template <int R>
 __global__ __launch_bounds__(SEL_THREADS) void m_sel_fill_counted(SelJob j) {
   extern __shared__ __align__(16) uint32_t sel_bits[];
   constexpr int NW = SEL_THREADS / 64, STEPS = 64;
-  __shared__ uint32_t part[3][NW], steps[NW][STEPS], before[SEL_THREADS];
+  __shared__ uint32_t part[2][NW], steps[NW][STEPS], before[SEL_THREADS];
   __shared__ int32_t start[SEL_THREADS + 1], base[SEL_THREADS];
   const SelPlace at{(int)blockIdx.x, (int)blockIdx.y, 0};
   sel_fill<SEL_THREADS, R>(j, at, sel_bits, [&] {

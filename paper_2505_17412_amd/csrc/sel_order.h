@@ -40,7 +40,7 @@ inline SelOrder sel_order(int n_tokens, int kv_heads) {
 // Query tokens per work chunk of the one-pass selection backward, for lists of `entries` tokens in all, blocks of up to `longest` keys and `heads`
 // query heads per KV head.  Long chunks write fewer partial dK and dV rows and pay less for the keys they begin with, in a block of
 // more than 256 keys once per segment of 256; short ones leave fewer compute units idle at the end.  So there is a number of chunks
-// wanted: of four wavefronts and a few rows, some 2000; of eight, some 500; of segments, 180 of 256 tokens and twice as many of 512; fewer where
+// wanted: of four wavefronts and a few rows, some 2000; of eight, some 500; of segments, 192 of 256 tokens and twice as many of 512; fewer where
 // few heads make few rows of a token.  us of the kernel, the index, the launches beside it, the sums of the partial rows and the finish, chunks
 // of 128 / 256 / 512, by entries.
 //   up to 128 keys, 8 heads  64k 220 / 229 / 268, 256k 432 / 448 / 496, 544k 955 / 945 / 969, 640k 951 / 947 / 953, 1.3M 2182 / 2113 / 2129, 2.2M 4823 / 4713 /
@@ -55,7 +55,7 @@ inline int one_pass_chunk_len(int longest, long long entries, int heads) {
   auto wanted = [&](int len) {
     if (longest <= 128) return 256 * (heads < 8 ? heads : 8);
     if (longest <= 256) return heads < 8 ? 150 : 560;
-    return len / 256 * 45 * (heads < 4 ? heads : 4);
+    return len / 256 * 48 * (heads < 4 ? heads : 4);
   };
   int len = 512;
   while (len > DKV_CHUNK_MIN && entries / len < wanted(len)) len /= 2;
