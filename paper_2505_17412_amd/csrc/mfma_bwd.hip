@@ -600,7 +600,7 @@ int launch_backward(const MfmaView &v, const BwdBuffers &w, const void *q, const
     if (!beside) rc = sel_index_count(j, s);
     if (rc == SSA_OK) rc = sel_index_scan(j, s);
     if (rc == SSA_OK && !beside) rc = sel_index_fill(j, s);
-    if (rc == SSA_OK && !beside) rc = sel_index_order(j, s);  // (behind the dQ kernel its slots lie in no cache any more)
+    if (rc == SSA_OK && !beside) rc = sel_index_order(j, s);  // (behind the dQ kernel its slots lie in no cache any more: 62k tokens 16.2 us for 12.4, 153k 41 for 27)
     if (rc != SSA_OK) return rc;
   }
   {
