@@ -16,9 +16,15 @@ constexpr int WIDE = 256;  // features and tokens of a wide tile
 //    256  24k -> 1024 (0.75) 22.8 / 24.4, 100k -> 1408 (0.84) 130 / 131, 46k -> 1024 (0.93) 40.9 / 38.6; in one round 12.8k -> 1024 (0.78) 16.0 / 14.3
 //    128  24k -> 1024 (0.75) 17.3 / 20.0, 25k -> 2048 (1.0) 28.7 / 30.2, 62k -> 2048 (0.95, eight rounds) 71.0 / 74.0, 100k -> 1408 (0.84, ten)
 //         110 / 96, 150k -> 1280 (0.95, twelve) 148 / 126
-inline bool lin_wide(int M, int F, int K) {
+// A data gradient (gradient) is followed by the weight gradient, which takes longer behind wide tiles of it: 150k tokens, 1024 inputs, 128 outputs: the
+// data gradient 98 / 94, the weight gradient behind it 131 / 145.  With a short contraction that is more than they win.  Both directions of ssa_linear_backward:
+//    256 (outputs)  one round 62 / 60 (16k, 1024 inputs), two 83 / 80 (16k, 2048) and 88 / 88 (33k, 1024); four 145 / 149 (65k, 1024), ten 309 / 331 (160k), 21
+//                   587 / 603 (330k); 1280 four 134 / 139, 13 369 / 375, twenty 588 / 578
+//    128            ten 248 / 270 (160k, 1024), 16 421 / 440 (260k), 375 / 379 (131k, 2048), 390 / 384 (200k, 1280); 20 506 / 484 (260k), 25 553 / 529 (200k, 2048)
+inline bool lin_wide(int M, int F, int K, bool gradient = false) {
   const long long tiles_m = (M + WIDE - 1) / WIDE, tiles_f = (F + WIDE - 1) / WIDE, rounds = ((tiles_m + 7) / 8 * tiles_f + 31) / 32;
   const int percent = K >= 768 ? 75 : rounds == 1 && K >= 256 ? 76 : K >= 384 ? 85 : K >= 256 ? 90 : rounds >= 9 ? 80 : 101;
+  if (gradient && (K >= 256 ? K < 384 && rounds > 2 : rounds < 19)) return false;
   return 100ll * M * F >= percent * rounds * 256 * WIDE * WIDE;
 }
 

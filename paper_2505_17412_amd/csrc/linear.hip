@@ -625,7 +625,7 @@ LinPlan lin_plan(int M, int d_in, int d_out) {
 namespace {
 
 template <bool ONE>
-int launch_nt(const LinSrc &src, const LinDst &dst, int M, GateJob gate, hipStream_t s) {
+int launch_nt(const LinSrc &src, const LinDst &dst, int M, bool gradient, GateJob gate, hipStream_t s) {
   const int F = dst.O[0] + dst.O[1] + dst.O[2];
   auto launch = [&](auto kernel, int f_tile, int t_tile, int threads, size_t lds) {
     const unsigned grid = (unsigned)(8 * (((M + t_tile - 1) / t_tile + 7) / 8) * ((F + f_tile - 1) / f_tile));
@@ -634,7 +634,7 @@ int launch_nt(const LinSrc &src, const LinDst &dst, int M, GateJob gate, hipStre
     kernel<<<grid + (unsigned)((gate.N + gate_tokens - 1) / gate_tokens), threads, lds, s>>>(src, dst, M, gate);
     return SSA_OK;
   };
-  if (lin_wide(M, F, src.K[0] + src.K[1] + src.K[2])) {
+  if (lin_wide(M, F, src.K[0] + src.K[1] + src.K[2], gradient)) {
     static const hipError_t attr = hipFuncSetAttribute((const void *)lin_nt_wide<ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LIN_WIDE_LDS);
     if (attr != hipSuccess) return SSA_ERR_HIP;
     return launch(lin_nt_wide<ONE>, WIDE, WIDE, 512, LIN_WIDE_LDS);
@@ -646,9 +646,9 @@ int launch_nt(const LinSrc &src, const LinDst &dst, int M, GateJob gate, hipStre
   if (attr != hipSuccess) return SSA_ERR_HIP;
   return launch(lin_nt<WF, WT, CF, CT, ONE>, BF, BT, 64 * WF * WT, lds);
 }
-int launch_nt(const LinSrc &src, const LinDst &dst, int M, const GateJob *gate, hipStream_t s) {
+int launch_nt(const LinSrc &src, const LinDst &dst, int M, bool gradient, const GateJob *gate, hipStream_t s) {
   const bool one = src.K[1] == 0 && dst.O[1] == 0 && !gate;
-  return one ? launch_nt<true>(src, dst, M, GateJob{}, s) : launch_nt<false>(src, dst, M, gate ? *gate : GateJob{}, s);
+  return one ? launch_nt<true>(src, dst, M, gradient, GateJob{}, s) : launch_nt<false>(src, dst, M, gradient, gate ? *gate : GateJob{}, s);
 }
 
 }  // namespace
@@ -665,7 +665,7 @@ int lin_nt_multi(int n_src, const void *const *X, const void *const *W, const in
   dst.bias[0] = (const bf16_t *)bias;
   dst.Y[0] = (bf16_t *)Y;
   dst.O[0] = O;
-  return launch_nt(src, dst, M, nullptr, s);
+  return launch_nt(src, dst, M, true, nullptr, s);
 }
 
 int lin_forward_multi(int n_dst, int M, int K, const void *X, const void *const *W, const void *const *bias, const int *O,
@@ -688,7 +688,7 @@ int lin_forward_multi(int n_dst, int M, int K, const void *X, const void *const 
     dst.O[i] = O[i];
   }
   ProfScope ps(PROF_LINEAR_FWD, s);
-  const int rc = launch_nt(src, dst, M, gate, s);
+  const int rc = launch_nt(src, dst, M, false, gate, s);
   if (rc != SSA_OK) return rc;
   SSA_HIP_TRY(hipGetLastError());
   return SSA_OK;

@@ -15,7 +15,8 @@ int main(int argc, char **argv) {
     for (int i = 2; i + 3 < argc; i += 4) printf("%d\n", lin_tn_splits(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3])));
     return 0;
   }
-  for (int i = 1; i + 2 < argc; i += 3) printf("%d\n", (int)lin_wide(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2])));
+  const int gradient = argc > 1 && argv[1][0] == 'g';
+  for (int i = 1 + gradient; i + 2 < argc; i += 3) printf("%d\n", (int)lin_wide(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), gradient));
   return 0;
 }
 """
@@ -28,6 +29,12 @@ MEASURED = [
     (100000, 1408, 128, 1.14), (150000, 1280, 128, 1.17), (150000, 1024, 128, 1.10), (62229, 2048, 128, 0.96), (62229, 1280, 256, 1.11), (24576, 1024, 128, 0.86), (24576, 2048, 128, 0.95), (20000, 2048, 128, 0.90),
 ]
 
+#: the same of a data gradient with the weight gradient behind it (features are the inputs, the contraction the outputs)
+MEASURED_GRADIENT = [
+    (160000, 1024, 128, 0.92), (260000, 640, 128, 0.97), (100000, 2048, 128, 0.97), (200000, 2048, 128, 1.04), (260000, 1280, 128, 1.045), (16384, 1024, 256, 1.04),
+    (40960, 768, 256, 1.02), (16384, 2048, 256, 1.04), (80000, 1024, 256, 0.95), (160000, 1024, 256, 0.93), (330000, 1024, 256, 0.97), (49152, 1280, 256, 0.96),
+    (200000, 2048, 256, 0.98), (260000, 768, 384, 1.05), (131072, 1280, 384, 1.04), (160000, 1024, 512, 1.05),
+]
 
 #: tokens, inputs, outputs, workgroups in tiles of 128, time in them over time in tiles of 256 (weight gradient)
 MEASURED_TN = [
@@ -51,6 +58,8 @@ def forms(tmp_path, sizes, kind=()):
 def test_wide_tiles_where_they_are_faster(tmp_path):
     for (m, f, k, ratio), wide in zip(MEASURED, forms(tmp_path, [s[:3] for s in MEASURED])):
         assert wide == (ratio > 1), (m, f, k, ratio)
+    for (m, f, k, ratio), wide in zip(MEASURED_GRADIENT, forms(tmp_path, [s[:3] for s in MEASURED_GRADIENT], "g")):
+        assert wide == (ratio > 1), ("gradient", m, f, k, ratio)
 
 
 def test_weight_gradient_in_wide_tiles_where_they_are_faster(tmp_path):
@@ -62,7 +71,8 @@ def test_cases_of_the_gpu_test(tmp_path):
     sizes = [(n, d_out, d_in) for _, n, d_in, d_out, _, _ in WIDE_CASES]
     assert forms(tmp_path, sizes) == [wide for *_, wide in WIDE_CASES]
     # a layer's query, key and value projections, and their data gradient, in test_projections_in_wide_tiles
-    assert forms(tmp_path, [(12400, 1280, 1024), (12400, 1024, 1280), (12288, 1280, 1024), (12225, 1280, 1024), (32768, 384, 768)]) == [False] + 4 * [True]
+    assert forms(tmp_path, [(12400, 1280, 1024), (12288, 1280, 1024), (12225, 1280, 1024), (32768, 384, 768)]) == [False] + 3 * [True]
+    assert forms(tmp_path, [(12400, 1024, 1280)], "g") == [True]
     sizes = [(n, d_in, d_out, wgs) for n, d_in, d_out, wgs, _ in WEIGHT_GRADIENT_CASES]
     assert [s > 0 for s in forms(tmp_path, sizes, "t")] == [wide for *_, wide in WEIGHT_GRADIENT_CASES]
     largest = 2 ** 31 - 1  # tokens x the larger dimension stay below 2^31
